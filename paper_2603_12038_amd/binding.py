@@ -1,4 +1,5 @@
-"""ctypes binding of libsfi.so: argument marshalling only; every step of the path runs in the HIP kernels.
+"""Binding of libsfi.so: argument marshalling only; every step of the path runs in the HIP kernels.
+The calls of a decode loop go through a small CPython module (_sfi.so, csrc/sfi_py.cpp), everything else through ctypes.
 
 Functions carry the names of the C entry points declared in include/sfi.h.  Tensors are torch
 tensors on the GPU (torch is used for device memory and streams only); their ``data_ptr()`` goes
@@ -39,6 +40,7 @@ class SfiConfig(C.Structure):
 
 
 _lib: Optional[C.CDLL] = None
+_hot = None  # the CPython module with the hot calls
 
 EXPORTS = ("sfi_workspace_bytes", "sfi_create", "sfi_set_block_table", "sfi_destroy", "sfi_strerror", "sfi_slow_step", "sfi_slow_attn",
            "sfi_slow_select", "sfi_evidence_add", "sfi_evidence_add_causal", "sfi_evidence_select", "sfi_dense_attn",
@@ -123,6 +125,24 @@ def load_library() -> C.CDLL:
     return lib
 
 
+def _load_hot():
+    """The CPython module _sfi.so, bound to torch's current-stream lookup; raises if it has not been built."""
+    global _hot
+    if _hot is None:
+        import torch
+
+        load_library()
+        try:
+            from . import _sfi
+        except ImportError as e:
+            raise FileNotFoundError("_sfi.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'`") from e
+        if torch.cuda.is_available():
+            torch.cuda.init()
+        _sfi.bind(SfiError, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _hot = _sfi
+    return _hot
+
+
 def _ptr(t) -> Optional[int]:
     if t is None:
         return None
@@ -171,51 +191,41 @@ def sfi_destroy(ctx: int) -> None:
 
 
 def sfi_slow_step(ctx, q, K, V, ctx_len, max_len, budget, out, sel_idx, n_sel, stream=None) -> None:
-    _check(load_library().sfi_slow_step(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(ctx_len), max_len, budget, _ptr(out),
-                                        _ptr(sel_idx), _ptr(n_sel), _stream(stream)), "sfi_slow_step")
+    (_hot or _load_hot()).sfi_slow_step(ctx, q, K, V, ctx_len, max_len, budget, out, sel_idx, n_sel, stream)
 
 
 def sfi_slow_attn(ctx, q, K, V, ctx_len, max_len, out, stream=None) -> None:
-    _check(load_library().sfi_slow_attn(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(ctx_len), max_len, _ptr(out),
-                                        _stream(stream)), "sfi_slow_attn")
+    (_hot or _load_hot()).sfi_slow_attn(ctx, q, K, V, ctx_len, max_len, out, stream)
 
 
 def sfi_slow_select(ctx, ctx_len, max_len, budget, sel_idx, n_sel, stream=None) -> None:
-    _check(load_library().sfi_slow_select(ctx, _ptr(ctx_len), max_len, budget, _ptr(sel_idx), _ptr(n_sel),
-                                          _stream(stream)), "sfi_slow_select")
+    (_hot or _load_hot()).sfi_slow_select(ctx, ctx_len, max_len, budget, sel_idx, n_sel, stream)
 
 
 def sfi_evidence_add(ctx, q, K, V, ctx_len, max_len, out, first: bool, stream=None) -> None:
-    _check(load_library().sfi_evidence_add(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(ctx_len), max_len, _ptr(out),
-                                           1 if first else 0, _stream(stream)), "sfi_evidence_add")
+    (_hot or _load_hot()).sfi_evidence_add(ctx, q, K, V, ctx_len, max_len, out, bool(first), stream)
 
 
 def sfi_evidence_add_causal(ctx, q, K, V, ctx_len, q_len, max_len, out, first: bool, stream=None) -> None:
-    _check(load_library().sfi_evidence_add_causal(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(ctx_len), _ptr(q_len), max_len,
-                                                  _ptr(out), 1 if first else 0, _stream(stream)), "sfi_evidence_add_causal")
+    (_hot or _load_hot()).sfi_evidence_add_causal(ctx, q, K, V, ctx_len, q_len, max_len, out, bool(first), stream)
 
 
 def sfi_evidence_select(ctx, n_added: int, ctx_len, max_len, budget, sel_idx, n_sel, stream=None) -> None:
-    _check(load_library().sfi_evidence_select(ctx, n_added, _ptr(ctx_len), max_len, budget, _ptr(sel_idx), _ptr(n_sel),
-                                              _stream(stream)), "sfi_evidence_select")
+    (_hot or _load_hot()).sfi_evidence_select(ctx, n_added, ctx_len, max_len, budget, sel_idx, n_sel, stream)
 
 
 def sfi_dense_attn(ctx, q, K, V, ctx_len, max_len, out, stream=None) -> None:
-    _check(load_library().sfi_dense_attn(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(ctx_len), max_len, _ptr(out),
-                                         _stream(stream)), "sfi_dense_attn")
+    (_hot or _load_hot()).sfi_dense_attn(ctx, q, K, V, ctx_len, max_len, out, stream)
 
 
 def sfi_fast_step(ctx, q, K, V, sel_idx, n_sel, sel_stride, recent_start, ctx_len, out, stream=None) -> None:
-    _check(load_library().sfi_fast_step(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(sel_idx), _ptr(n_sel), sel_stride,
-                                        _ptr(recent_start), _ptr(ctx_len), _ptr(out), _stream(stream)),
-           "sfi_fast_step")
+    (_hot or _load_hot()).sfi_fast_step(ctx, q, K, V, sel_idx, n_sel, sel_stride, recent_start, ctx_len, out, stream)
 
 
 def sfi_fast_step_static(cfg: SfiConfig, q, K, V, sel_idx, n_sel, sel_stride, recent_start, ctx_len, out, stream=None) -> None:
     """The fast step on the library's static scratch: no context, no workspace (cfg is the host-side SfiConfig)."""
-    _check(load_library().sfi_fast_step_static(C.byref(cfg), _ptr(q), _ptr(K), _ptr(V), _ptr(sel_idx), _ptr(n_sel),
-                                               sel_stride, _ptr(recent_start), _ptr(ctx_len), _ptr(out),
-                                               _stream(stream)), "sfi_fast_step_static")
+    (_hot or _load_hot()).sfi_fast_step_static(C.addressof(cfg), q, K, V, sel_idx, n_sel, sel_stride, recent_start,
+                                               ctx_len, out, stream)
 
 
 def sfi_dense_attn_floor(ctx, K, V, ctx_len, max_len, variant: int, stream=None) -> None:
@@ -237,53 +247,46 @@ def sfi_fast_step_floor(ctx, q, K, V, sel_idx, n_sel, sel_stride, recent_start, 
 def sfi_reorg(ctx, K, V, sel_idx, n_sel, sel_stride, ctx_len, is_slow, Kc, Vc, stream=None) -> None:
     """Kc / Vc: bf16 tensors [B, Hkv, c_rows, 128] with contiguous rows; strides are taken from them."""
     assert Kc.stride() == Vc.stride() and Kc.stride(3) == 1 and Kc.stride(2) == Kc.shape[3]
-    _check(load_library().sfi_reorg(ctx, _ptr(K), _ptr(V), _ptr(sel_idx), _ptr(n_sel), sel_stride, _ptr(ctx_len),
-                                    _ptr(is_slow), _ptr(Kc), _ptr(Vc), Kc.stride(0), Kc.stride(1), Kc.shape[2],
-                                    _stream(stream)), "sfi_reorg")
+    (_hot or _load_hot()).sfi_reorg(ctx, K, V, sel_idx, n_sel, sel_stride, ctx_len, is_slow, Kc, Vc, Kc.stride(0),
+                                    Kc.stride(1), Kc.shape[2], stream)
 
 
 def sfi_fast_step_compact(ctx, q, Kc, Vc, n_sel, sel_stride, K, V, recent_start, ctx_len, out, stream=None) -> None:
     assert Kc.stride() == Vc.stride() and Kc.stride(3) == 1 and Kc.stride(2) == Kc.shape[3]
-    _check(load_library().sfi_fast_step_compact(ctx, _ptr(q), _ptr(Kc), _ptr(Vc), Kc.stride(0), Kc.stride(1),
-                                                Kc.shape[2], _ptr(n_sel), sel_stride, _ptr(K), _ptr(V),
-                                                _ptr(recent_start), _ptr(ctx_len), _ptr(out), _stream(stream)),
-           "sfi_fast_step_compact")
+    (_hot or _load_hot()).sfi_fast_step_compact(ctx, q, Kc, Vc, Kc.stride(0), Kc.stride(1), Kc.shape[2], n_sel,
+                                                sel_stride, K, V, recent_start, ctx_len, out, stream)
 
 
 def sfi_mixed_step(ctx, q, K, V, is_slow, ctx_len, recent_start, max_len, budget, out, sel_idx, n_sel,
                    stream=None) -> None:
-    _check(load_library().sfi_mixed_step(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(is_slow), _ptr(ctx_len),
-                                         _ptr(recent_start), max_len, budget, _ptr(out), _ptr(sel_idx),
-                                         _ptr(n_sel), _stream(stream)), "sfi_mixed_step")
+    (_hot or _load_hot()).sfi_mixed_step(ctx, q, K, V, is_slow, ctx_len, recent_start, max_len, budget, out, sel_idx,
+                                         n_sel, stream)
 
 
 def sfi_mixed_step_compact(ctx, q, K, V, is_slow, ctx_len, recent_start, max_len, budget, out, sel_idx, n_sel, Kc, Vc,
                            stream=None) -> None:
     assert Kc.stride() == Vc.stride() and Kc.stride(3) == 1 and Kc.stride(2) == Kc.shape[3]
-    _check(load_library().sfi_mixed_step_compact(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(is_slow), _ptr(ctx_len),
-                                                 _ptr(recent_start), max_len, budget, _ptr(out), _ptr(sel_idx),
-                                                 _ptr(n_sel), _ptr(Kc), _ptr(Vc), Kc.stride(0), Kc.stride(1), Kc.shape[2],
-                                                 _stream(stream)), "sfi_mixed_step_compact")
+    (_hot or _load_hot()).sfi_mixed_step_compact(ctx, q, K, V, is_slow, ctx_len, recent_start, max_len, budget, out,
+                                                 sel_idx, n_sel, Kc, Vc, Kc.stride(0), Kc.stride(1), Kc.shape[2],
+                                                 stream)
 
 
 def sfi_step_begin(ctx, desc, last_token, trigger_bitmap, vocab_size, t_max, advance: bool, stream=None) -> None:
     """desc: int32 device tensor [B, 4] = (ctx_len, recent_start, is_slow, since_slow) per sequence."""
-    _check(load_library().sfi_step_begin(ctx, _ptr(desc), _ptr(last_token), _ptr(trigger_bitmap), vocab_size, t_max,
-                                         1 if advance else 0, _stream(stream)), "sfi_step_begin")
+    (_hot or _load_hot()).sfi_step_begin(ctx, desc, last_token, trigger_bitmap, vocab_size, t_max, bool(advance),
+                                         stream)
 
 
 def sfi_mixed_step_desc(ctx, q, K, V, desc, max_len, budget, out, sel_idx, n_sel, stream=None) -> None:
-    _check(load_library().sfi_mixed_step_desc(ctx, _ptr(q), _ptr(K), _ptr(V), _ptr(desc), max_len, budget, _ptr(out),
-                                              _ptr(sel_idx), _ptr(n_sel), _stream(stream)), "sfi_mixed_step_desc")
+    (_hot or _load_hot()).sfi_mixed_step_desc(ctx, q, K, V, desc, max_len, budget, out, sel_idx, n_sel, stream)
 
 
 def sfi_trigger(ctx, last_token, trigger_bitmap, vocab_size, t_max, since_slow, is_slow, stream=None) -> None:
-    _check(load_library().sfi_trigger(ctx, _ptr(last_token), _ptr(trigger_bitmap), vocab_size, t_max, _ptr(since_slow),
-                                      _ptr(is_slow), _stream(stream)), "sfi_trigger")
+    (_hot or _load_hot()).sfi_trigger(ctx, last_token, trigger_bitmap, vocab_size, t_max, since_slow, is_slow, stream)
 
 
 def sfi_advance(ctx, ctx_len, recent_start, stream=None) -> None:
-    _check(load_library().sfi_advance(ctx, _ptr(ctx_len), _ptr(recent_start), _stream(stream)), "sfi_advance")
+    (_hot or _load_hot()).sfi_advance(ctx, ctx_len, recent_start, stream)
 
 
 def sfi_set_profiling(ctx, max_calls: int) -> None:

@@ -1,14 +1,16 @@
-"""Compile libsfi.so (HIP, gfx950 only) in-tree next to this file."""
+"""Compile libsfi.so (HIP, gfx950 only) and its CPython module _sfi.so in-tree next to this file."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsfi.so")
+PY_LIB = os.path.join(HERE, "_sfi.so")
 
 # packed-fp32 code generation is switched off on purpose for this target
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -30,7 +32,19 @@ def build_lib(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err)
+    build_py_module()
     return LIB
+
+
+def build_py_module() -> str:
+    """The hot calls as a CPython module (host code only), linked to libsfi.so beside it."""
+    cxx = os.environ.get("CXX", "g++")
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "sfi_py.cpp"), LIB, "-Wl,-rpath,$ORIGIN", "-o", PY_LIB]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cxx} failed:\n" + r.stderr)
+    return PY_LIB
 
 
 if __name__ == "__main__":
