@@ -254,7 +254,7 @@ int sfi_fast_step(sfi_ctx* ctx, const void* q, const void* K, const void* V, con
  * capture that owns no buffers of its own, tight serving loops, harnesses that forbid hipMalloc.  Same result
  * as sfi_fast_step on a context created from *cfg (HOST pointer; read during the call only), same argument
  * meaning and preconditions; no sfi_ctx and no workspace are involved.  The split records and arrival counters
- * of the in-kernel merge live in a file-scope device array of the library instead (4.2 MiB, held by every GPU
+ * of the in-kernel merge live in a file-scope device array of the library instead (6.2 MiB, held by every GPU
  * the library runs on until the process ends), which sets the limits:
  *   batch * n_q_heads <= 8192  and  batch * n_kv_heads <= 4096, else SFI_EUNSUPPORTED;
  *   at most 8192 / (batch * n_q_heads) workgroups per (sequence, KV head): larger shapes run with a coarser split

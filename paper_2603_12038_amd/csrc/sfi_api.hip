@@ -106,7 +106,7 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->segcnt = (uint32_t*)take((size_t)(B * Hkv) * n_seg * sizeof(uint32_t));
   ws->jstat = (float2*)take((size_t)(B * Hq) * sizeof(float2));
   ws->mu = (float*)take((size_t)(B * Hkv) * ld * sizeof(float));
-  ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * sizeof(uint32_t));
+  ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * kWaves * kArriveStride * sizeof(uint32_t));
   ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears both
   ws->prior = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->znms = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
@@ -702,9 +702,10 @@ int sfi_fast_step_floor(sfi_ctx* x, const void* q, const void* K, const void* V,
 // Split records and arrival counters live in a file-scope device array instead of a caller's workspace.
 namespace {
 constexpr int kStaticRecords = 8192;   // split records the scratch holds: batch * n_q_heads * splits per pair
-constexpr int kStaticPairs = 4096;     // arrival counters: batch * n_kv_heads
+constexpr int kStaticPairs = 4096;     // batch * n_kv_heads (an arrival counter per wave of a workgroup each)
 constexpr size_t kStaticRecordBytes = (size_t)kStaticRecords * kPartStride * sizeof(float);
-constexpr size_t kStaticBytes = kStaticRecordBytes + (size_t)kStaticPairs * sizeof(uint32_t) + 256;
+constexpr int kStaticCounters = kStaticPairs * kWaves * kArriveStride;
+constexpr size_t kStaticBytes = kStaticRecordBytes + (size_t)kStaticCounters * sizeof(uint32_t) + 256;
 constexpr int kMaxDevices = 64;
 }  // namespace
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
@@ -763,10 +764,10 @@ int sfi_fast_step_static(const sfi_config* cfg, const void* q, const void* K, co
   hipStream_t st = (hipStream_t)stream;
   float* part = reinterpret_cast<float*>(S.ptr);
   uint32_t* arrive = reinterpret_cast<uint32_t*>(S.ptr + kStaticRecordBytes);
-  const int32_t* one_word = reinterpret_cast<const int32_t*>(arrive + kStaticPairs);  // readable, never written
+  const int32_t* one_word = reinterpret_cast<const int32_t*>(arrive + kStaticCounters);  // readable, never written
   const int max_splits = (int)(kStaticRecords / heads);  // >= 1
   if (!S.counters_clean) {  // first call on this device, or the call before did not get its launch out
-    hipLaunchKernelGGL(clear_words_kernel, dim3((kStaticPairs + 255) / 256), dim3(256), 0, st, arrive, kStaticPairs);
+    hipLaunchKernelGGL(clear_words_kernel, dim3((kStaticCounters + 255) / 256), dim3(256), 0, st, arrive, kStaticCounters);
     if (hipGetLastError() != hipSuccess) return SFI_ELAUNCH;
   }
   S.counters_clean = false;

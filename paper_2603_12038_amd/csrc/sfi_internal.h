@@ -19,6 +19,9 @@ constexpr int kMaxSplits = 63;     // split workgroups per (sequence, KV head)
 // records per (sequence, query head): the dense kernel writes one per wave, (splits + 1 sink/recent
 // workgroup) x 4 waves; the gather kernel one per workgroup
 constexpr int kSlotCap = (kMaxSplits + 1) * kWaves;
+// Words between two arrival counters of the fast step's in-kernel merge: a cache line each.  Atomics on one line are
+// performed one after the other, about 30 ns apiece.
+constexpr int kArriveStride = 32;
 constexpr int kSelSeg = 2048;      // Selector positions per workgroup
 constexpr int kSelThreads = 256;
 constexpr int kHist1Bits = 12;     // first radix pass: bits [30:19] of the fp32 score
@@ -79,7 +82,7 @@ struct Workspace {
   float* znms;        // [B*Hkv][ld]  full Selector: log2-domain score after Soft-NMS
   double* segstat;    // [B*Hkv][n_seg_cap][kSegStats]  full Selector: per-segment sums for lambda*
   float* mu;          // [B*Hkv][ld]  windowed evidence: accumulator over the window's queries
-  uint32_t* arrive;   // [B*Hkv]  workgroups of a split fast-step launch that have written their record
+  uint32_t* arrive;   // [B*Hkv][kWaves][kArriveStride]  workgroups of a split fast-step launch whose wave w has written its heads' records
   int32_t* guard;     // [1]  SFI_GUARD_* bits of device-side inputs the kernels found out of range and clamped
   int64_t ld_pos;     // multiple of kSelSeg
   int32_t n_seg_cap;
@@ -118,9 +121,9 @@ struct AttnArgs {
   int32_t big_stash;             // dense mode with logits: the variant with the 32 KB stash per wave (one workgroup per CU)
   int32_t pipelined;             // gather mode: few workgroups per (b, h), each wave walks several tiles
   float* out_direct;             // gather / compact mode with n_split == 1: write the output here, no record
-  float* out_merge;              // gather / compact mode, nullptr or: the pair's last workgroup to finish merges
-  uint32_t* arrive;              //   the pair's records into out_merge; arrive[b * Hkv + h] counts the finished
-                                 //   workgroups of the pair (zero between launches)
+  float* out_merge;              // gather / compact mode, nullptr or: the pair's last waves to finish merge the
+  uint32_t* arrive;              //   pair's records into out_merge; arrive[((b * Hkv + h) * kWaves + w) * kArriveStride] counts the
+                                 //   workgroups whose wave w is done (zero between launches)
   const int32_t* table;          // paged cache: block table [B][table_stride], logical page -> block of the pool
   int64_t table_stride;
   int32_t page_lg;               // log2 of the page size in rows
