@@ -15,6 +15,8 @@ PY_LIB = os.path.join(HERE, "_sfi.so")
 # packed-fp32 code generation is switched off on purpose for this target
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               # leading scalar kernel arguments arrive in registers
+               "-mllvm", "-amdgpu-kernarg-preload-count=14",
                "-Wall", "-Wno-unused-function"]
 
 

@@ -177,12 +177,10 @@ void set_dense_bounds(const sfi_ctx* x, AttnArgs* a, int max_len) {
 }
 
 // Gather launch geometry: the balanced split above.  With one workgroup per pair the workgroup
-// finishes the softmax itself (no records, no merge).  A split that leaves every wave at most one
-// tile runs the one-tile kernel, any other the pipelined one.  (Config 2: 6 workgroups per pair, up to
+// finishes the softmax itself (no records, no merge).  (Config 2: 6 workgroups per pair, up to
 // 3 tiles per wave; 33 sequences of 8 KV heads: 2 workgroups per pair instead of 1, 10 % faster.)
-// fast_tiles_per_wave > 0 overrides: 1 = one tile per wave, t > 1 = pipelined with about t tiles per
-// wave.
-int fast_splits_for(const sfi_ctx* x, int sel_stride, int* pipelined, int max_splits = kMaxSplits) {
+// fast_tiles_per_wave > 0 overrides: about that many tiles per wave.
+int fast_splits_for(const sfi_ctx* x, int sel_stride, int max_splits = kMaxSplits) {
   const int rows = x->cfg.n_sink + sel_stride + x->cfg.recent;
   const int tiles = (rows + kTile - 1) / kTile;
   const int pairs = x->cfg.batch * x->cfg.n_kv_heads;
@@ -196,7 +194,6 @@ int fast_splits_for(const sfi_ctx* x, int sel_stride, int* pipelined, int max_sp
     s = balanced_splits(pairs, tiles, one, x->n_cu, x->tail_merge != 0);
   if (s > one) s = one;
   if (s < 1) s = 1;
-  *pipelined = s * kWaves < tiles;
   return s;
 }
 
@@ -629,11 +626,11 @@ int fast_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const 
   a.slot_cap = slot_cap;
   a.guard = guard;
   a.recent_start = recent_start;
-  // an index list of width 0: the pipelined kernel still reads one word where the list would start
+  // an index list of width 0: the kernel still reads one word where the list would start
   a.sel_idx = sel_stride > 0 ? sel_idx : one_word;
   a.n_sel = n_sel;
   a.sel_stride = sel_stride;
-  a.n_split = fast_splits_for(x, sel_stride, &a.pipelined, max_splits);
+  a.n_split = fast_splits_for(x, sel_stride, max_splits);
   x->last_fast_splits = a.n_split;
   if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
   else if (x->tail_merge) { a.out_merge = out; a.arrive = arrive; }
@@ -681,7 +678,7 @@ int sfi_fast_step_floor(sfi_ctx* x, const void* q, const void* K, const void* V,
   a.sel_idx = sel_stride > 0 ? sel_idx : x->ws.guard;
   a.n_sel = n_sel;
   a.sel_stride = sel_stride;
-  a.n_split = fast_splits_for(x, sel_stride, &a.pipelined);
+  a.n_split = fast_splits_for(x, sel_stride);
   const int tiles = (x->cfg.n_sink + sel_stride + x->cfg.recent + kTile - 1) / kTile;
   int tpw = (tiles + a.n_split - 1) / a.n_split;
   if (burst) {  // the workgroup's tiles must fit its LDS (nine tiles of 16 KB)
@@ -907,7 +904,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
     f.c_sb = cb->stride_b; f.c_sh = cb->stride_h; f.c_rows = cb->rows;
     f.n_split = compact_splits_for(x, budget);
   } else {
-    f.n_split = fast_splits_for(x, budget, &f.pipelined);
+    f.n_split = fast_splits_for(x, budget);
   }
   if (f.n_split == 1) f.out_direct = out;
   else if (x->tail_merge) { f.out_merge = out; f.arrive = x->ws.arrive; }  // slow sequences' workgroups never arrive
@@ -1089,9 +1086,8 @@ int sfi_plan_splits(const sfi_ctx* x, int32_t max_len, int32_t sel_stride, int32
   int ml;
   const int rc = resolve_max_len(x, max_len, &ml);
   if (rc != SFI_OK) return rc;
-  int pipelined;
   if (dense_splits) *dense_splits = dense_splits_for(x, ml, false);
-  if (fast_splits) *fast_splits = fast_splits_for(x, sel_stride, &pipelined);
+  if (fast_splits) *fast_splits = fast_splits_for(x, sel_stride);
   return SFI_OK;
 }
 

@@ -11,10 +11,9 @@
 //          (Eq. allowed_set).  A wave keeps the two kinds in separate records, so the J-only softmax
 //          normaliser of Eq. selector_pt is just the merge of the J records.  Every wave writes its
 //          own records: waves never wait for each other.
-//   gather kernels (fast step): the list is  sink ++ sel_idx[0:n_sel] ++ [recent_start, L)
+//   gather kernel (fast step): the list is  sink ++ sel_idx[0:n_sel] ++ [recent_start, L)
 //          (Eq. index_set_head), strided over n_split workgroups; the four waves of a workgroup
-//          are combined into one record (fewer records for the merge that follows).  One tile per
-//          wave, or a pipelined walk over several for large launches.
+//          are combined into one record (fewer records for the merge that follows).
 //   compact kernel (fast step, two-segment layout of Sec. 4.2) and the Reorg copy that feeds it.
 //
 // Mapping to the matrix cores.  A wave owns 32 positions per iteration, as two 16-row blocks.
@@ -280,30 +279,34 @@ __device__ __forceinline__ void issue_rows(Tile& T, const Rows& R, int ra, int r
   issue_v_rows<OffT, WIDE>(T, R, ra, rb);
 }
 
-// Q^T operand: head n, dims kblk*32 + 8*jg .. +8; zero for heads >= G (no branch around the loads).
+// Q^T operand: head n, dims kblk*32 + 8*jg .. +8; columns of heads >= G read another head's row and are zeroed by mask_q
+// (apart, so that nothing has to wait for q before it is needed; no branch around the loads).
+// WIDE: column n = 8 * half + head holds dims 64 * kb + 32 * half + 8 * jg .. + 8 of q[head]; qreg[2], qreg[3] unused.
 template <bool WIDE = false>
-__device__ __forceinline__ void load_q(bf16x8 (&qreg)[4], const uint16_t* q, int64_t head0, int G, int jg, int n) {
-  if (WIDE) {  // column n = 8 * half + head: dims 64 * kb + 32 * half + 8 * jg .. + 8 of q[head]; qreg[2], qreg[3] unused
-    const int head = n & 7;
-    const uint16_t* qw = q + (head0 + (head < G ? head : 0)) * kHeadDim + (n >> 3) * 32 + jg * 8;
-    const uint32_t kp = head < G ? 0xffffffffu : 0u;
+__device__ __forceinline__ void load_q_raw(bf16x8 (&qreg)[4], const uint16_t* q, int64_t head0, int G, int jg, int n) {
+  const int head = WIDE ? n & 7 : n;
+  const uint16_t* qp = q + (head0 + (head < G ? head : 0)) * kHeadDim + (WIDE ? (n >> 3) * 32 : 0) + jg * 8;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      uint4 t = *reinterpret_cast<const uint4*>(qw + kb * 64);
-      t.x &= kp; t.y &= kp; t.z &= kp; t.w &= kp;
-      qreg[kb] = as_bf16x8(t);
-      qreg[2 + kb] = as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
-    }
-    return;
-  }
-  const uint16_t* qp = q + (head0 + (n < G ? n : 0)) * kHeadDim + jg * 8;
-  const uint32_t keep = n < G ? 0xffffffffu : 0u;
+  for (int kb = 0; kb < (WIDE ? 2 : 4); ++kb) qreg[kb] = as_bf16x8(*reinterpret_cast<const uint4*>(qp + kb * (WIDE ? 64 : 32)));
+}
+template <bool WIDE = false>
+__device__ __forceinline__ void mask_q(bf16x8 (&qreg)[4], int G, int n) {
+  const uint32_t keep = (WIDE ? n & 7 : n) < G ? 0xffffffffu : 0u;
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
-    uint4 t = *reinterpret_cast<const uint4*>(qp + kb * 32);
-    t.x &= keep; t.y &= keep; t.z &= keep; t.w &= keep;
-    qreg[kb] = as_bf16x8(t);
+    if (WIDE && kb >= 2) {
+      qreg[kb] = as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
+    } else {
+      uint4 t = __builtin_bit_cast(uint4, qreg[kb]);
+      t.x &= keep; t.y &= keep; t.z &= keep; t.w &= keep;
+      qreg[kb] = as_bf16x8(t);
+    }
   }
+}
+template <bool WIDE = false>
+__device__ __forceinline__ void load_q(bf16x8 (&qreg)[4], const uint16_t* q, int64_t head0, int G, int jg, int n) {
+  load_q_raw<WIDE>(qreg, q, head0, G, jg, n);
+  mask_q<WIDE>(qreg, G, n);
 }
 
 // One 32-position tile in three phases: S^T = K Q^T, online softmax in the log2 domain, O += P V.
@@ -450,18 +453,6 @@ __device__ __forceinline__ void pv_phase(const Tile& T, const bf16x8& a_hi, cons
   }
 }
 
-// All three phases on a tile that is already in registers.  MASKED: ragged last tile of a list.
-template <bool MASKED, bool WIDE = false>
-__device__ __forceinline__ void tile_math(Tile& T, const bf16x8 (&qreg)[4], float c2, f32x4 (&acc)[8],
-                                          float& m_run, float& l_run, int jg, int p0, int N) {
-  float y[8];
-  qk_phase<WIDE>(T, qreg, c2, y);
-  if (MASKED) mask_tail<true, WIDE>(T, y, jg, p0, N);
-  bf16x8 a_hi, a_lo;
-  softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
-  pv_phase(T, a_hi, a_lo, acc);
-}
-
 // Device-scope accesses: visible to / from every compute unit of the device whatever L2 it sits behind,
 // without a fence (records that one workgroup hands to another inside a launch).  They go through a buffer
 // descriptor, 16 bytes at a time: the records of one (b, h) pair as a raw buffer
@@ -525,10 +516,7 @@ struct ListWalk {
     N = nS + nSel + (L - rs);
     r_hi = max(L, 1) - 1;
   }
-  __device__ __forceinline__ int sel_at(int p) const {  // index stored for list position p (valid inside the sel part)
-    return sel_cap >= 0 ? sel[min(max(p - n_sink, 0), sel_cap)] : 0;
-  }
-  __device__ __forceinline__ int sel_at_nonempty(int p) const {  // the same without the branch; needs sel_cap >= 0
+  __device__ __forceinline__ int sel_at_nonempty(int p) const {  // index stored for list position p (valid inside the sel part)
     return sel[min(max(p - n_sink, 0), sel_cap)];
   }
   __device__ __forceinline__ int row_of(int p, int s) {
@@ -1063,112 +1051,51 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// gather kernel
+// gather kernel: each wave walks tiles first, first + step, ... of its list with the dense kernel's loop: one tile
+// buffer whose K half is refilled with the next tile's rows right after S^T, the V half right after P V; the selected
+// indices are read two tiles ahead.  Loads past the wave's last tile fall on row 0 (no branch around a load, so every
+// wait names exactly the loads it needs).  A launch whose split leaves every wave at most one tile skips the loop.
+//
+// A short launch is its chain of round trips: kernel arguments, then the step's scalars and the first indices, then the
+// rows.  The first argument load of a wave takes 0.5 us, so what the second link needs travels in the leading scalar
+// arguments, which the hardware hands to the wave in registers (-amdgpu-kernarg-preload-count); the rest of the
+// arguments arrives while the indices are on their way.  Nothing waits for q before the rows are requested, and no
+// division stands in the way (a vector instruction of a lone wave takes 1.7 us per thousand).  Measured with this order
+// against arguments read where they are used and q masked where it is loaded: 131072 rows / 8 KV heads 9.6 -> 9.0 us,
+// 4 x 32768 rows 11.1 -> 10.6 us, 4096 rows / 2 KV heads 6.4 -> 5.6 us.
 // ------------------------------------------------------------------------------------------------
+// The preloaded arguments: shape = Hkv | (log2 of the metadata stride) << 16 | (is_slow given) << 20.
 template <bool PAGED, bool WIDE>
-__global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const AttnArgs a) {
-  constexpr int NW = kWaves;
+__global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int32_t* sel_idx, const int32_t* n_sel_p, const int32_t* ctx_len_p,
+                                                                      const int32_t* recent_start_p, const uint8_t* is_slow_p,
+                                                                      const uint32_t sel_stride, const uint32_t shape, const int n_sink,
+                                                                      const int n_split, const AttnArgs a) {
   const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] != 0) return;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
-  const int G = a.G;
-  const int bh = b * a.Hkv + h;
-  const int64_t head0 = (int64_t)b * a.Hq + h * G;
-  const int first = slot * NW + w, step = a.n_split * NW;
-  // The step's three scalars are requested together, ahead of everything else: read one by one where
-  // they are used, the wait for the first would hold back the requests for the others (a round trip each).
-  const int L_in = a.ctx_len[b * a.ms], n_sel_in = a.n_sel[bh], rs_in = a.recent_start[b * a.ms];
-
-  // ---- first round of loads, none depending on another: the selected indices of this wave's first
-  // tile (read before the list length is known, clamped to the row of sel_idx), q, the scalars.
+  const int bh = b * (int)(shape & 0xffffu) + h;
+  const int bm = b << ((shape >> 16) & 15u);
+  const bool flagged = ((shape >> 20) & 1u) != 0u;
+  const int first = slot * kWaves + w, step = n_split * kWaves;
+  const int p_first = first * kTile, pstep = step * kTile;
+  // First round of loads, none depending on another: the scalars and the flag, the indices of the first tile (read before
+  // the list length is known, clamped to the row of sel_idx), and the arguments that come from memory.
+  const int L_in = ctx_len_p[bm], n_sel_in = n_sel_p[bh], rs_in = recent_start_p[bm];
   ListWalk W;
-  W.sel = a.sel_idx + (int64_t)bh * a.sel_stride;
-  W.sel_cap = (int)a.sel_stride - 1;
-  W.n_sink = a.n_sink;
-  int sA = W.sel_at(first * kTile + n);
-  int sB = W.sel_at(first * kTile + 16 + n);
-  bf16x8 qreg[4];
-  load_q<WIDE>(qreg, a.q, head0, G, jg, n);
-  W.bad = 0;
-  const int L = guarded_len(L_in, a.len_cap, W.bad);
-  W.set_counts(L, n_sel_in, rs_in, (int)a.sel_stride);
-
-  Rows R;
-  R.Kb = reinterpret_cast<const char*>(a.K + b * a.k_sb + h * a.k_sh);
-  R.Vb = reinterpret_cast<const char*>(a.V + b * a.v_sb + h * a.v_sh);
-  R.k_st = (uint32_t)a.k_st * 2u;
-  R.v_st = (uint32_t)a.v_st * 2u;
-  R.k_lane = k_lane_of<WIDE>(jg, n);
-  R.v_lane = n * 16;
-  R.jg = jg;
-  R.n = n;
-
-  Tile T;
-  float m_run = kNeg, l_run = 0.f;
-  f32x4 acc[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int nT = (W.N + kTile - 1) / kTile;
-  for (int t = first; t < nT; t += step) {  // normally a single trip
-    const int p0 = t * kTile;
-    if (t != first) {
-      sA = W.sel_at(p0 + n);
-      sB = W.sel_at(p0 + 16 + n);
-    }
-    int ra = W.row_of(p0 + n, sA), rb = W.row_of(p0 + 16 + n, sB);
-    if (PAGED) {  // one more dependent round: row -> block-table entry -> physical row
-      const Pages P = pages_of(a, b, L);
-      ra = P.phys(ra, P.page_of(ra), W.bad);
-      rb = P.phys(rb, P.page_of(rb), W.bad);
-    }
-    issue_rows<typename RowOff<PAGED>::type, WIDE>(T, R, ra, rb);
-    if (p0 + kTile <= W.N) tile_math<false, WIDE>(T, qreg, a.scale_log2, acc, m_run, l_run, jg, p0, W.N);
-    else tile_math<true, WIDE>(T, qreg, a.scale_log2, acc, m_run, l_run, jg, p0, W.N);
-  }
-  l_run = rows_sum(l_run);
-  finish_wg<WIDE ? 8 : 16>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run);
-  report_guard(a.guard, W.bad);  // last: the way to the record and the merge is the launch's critical path
-}
-
-// ------------------------------------------------------------------------------------------------
-// gather kernel, pipelined: for launches whose index lists are long or many enough that one tile
-// per wave would take several rounds of workgroups (large batches, large budgets).  Few workgroups
-// per (b, h), each wave walks tiles first, first + step, ... with the dense kernel's loop: one tile
-// buffer whose K half is refilled with the next tile's rows right after S^T, the V half right
-// after P V; the selected indices are read two tiles ahead.  Loads past the wave's last tile fall
-// on row 0 (no branch around a load, so every wait names exactly the loads it needs).
-// ------------------------------------------------------------------------------------------------
-template <bool PAGED, bool WIDE>
-__global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_stream_kernel(const AttnArgs a) {
-  const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] != 0) return;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
-  const int jg = lane >> 4, n = lane & 15;
-  const int G = a.G;
-  const int bh = b * a.Hkv + h;
-  const int64_t head0 = (int64_t)b * a.Hq + h * G;
-  const int first = slot * kWaves + w, step = a.n_split * kWaves;
-  const int pstep = step * kTile;
-  // The step's three scalars are requested together, ahead of everything else: read one by one where
-  // they are used, the wait for the first would hold back the requests for the others (a round trip each).
-  const int L_in = a.ctx_len[b * a.ms], n_sel_in = a.n_sel[bh], rs_in = a.recent_start[b * a.ms];
-
-  ListWalk W;
-  W.sel = a.sel_idx + (int64_t)bh * a.sel_stride;
-  W.sel_cap = max((int)a.sel_stride - 1, 0);  // sel_stride = 0: the host points sel_idx at one readable word
-  W.n_sink = a.n_sink;
-  const int p_first = first * kTile;
+  W.sel = sel_idx + (int64_t)bh * sel_stride;
+  W.sel_cap = max((int)sel_stride - 1, 0);  // sel_stride = 0: the host points sel_idx at one readable word
+  W.n_sink = n_sink;
+  const int slow = is_slow_p[flagged ? (uint32_t)b << (2u * ((shape >> 16) & 15u)) : 0u];  // (a readable byte in any case)
   const int sA = W.sel_at_nonempty(p_first + n), sB = W.sel_at_nonempty(p_first + 16 + n);
+  __builtin_amdgcn_sched_barrier(0);
+  // everything uniform is asked for before the first of it is used: one wait
+  asm volatile("" ::"s"(L_in), "s"(n_sel_in), "s"(rs_in), "s"(a.q), "s"(a.K), "s"(a.V), "s"(a.k_sb), "s"(a.k_sh), "s"(a.k_st),
+               "s"(a.v_sb), "s"(a.v_sh), "s"(a.v_st), "s"(a.Hq), "s"(a.G), "s"(a.scale_log2), "s"(a.len_cap));
+  if (PAGED) asm volatile("" ::"s"(a.table), "s"(a.table_stride), "s"(a.page_lg), "s"(a.page_rpb), "s"(a.n_blocks));
+  const int G = a.G;
+  const int64_t head0 = (int64_t)b * a.Hq + h * G;
   bf16x8 qreg[4];
-  load_q<WIDE>(qreg, a.q, head0, G, jg, n);
-  W.bad = 0;
-  const int L = guarded_len(L_in, a.len_cap, W.bad);
-  W.set_counts(L, n_sel_in, rs_in, (int)a.sel_stride);
-
+  load_q_raw<WIDE>(qreg, a.q, head0, G, jg, n);
   Rows R;
   R.Kb = reinterpret_cast<const char*>(a.K + b * a.k_sb + h * a.k_sh);
   R.Vb = reinterpret_cast<const char*>(a.V + b * a.v_sb + h * a.v_sh);
@@ -1178,6 +1105,13 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_stream_kernel(con
   R.v_lane = n * 16;
   R.jg = jg;
   R.n = n;
+  W.bad = 0;
+  const int L = guarded_len(L_in, a.len_cap, W.bad);
+  W.set_counts(L, n_sel_in, rs_in, (int)sel_stride);
+  const int nT = (W.N + kTile - 1) / kTile;
+  asm volatile("" ::"s"(R.Kb), "s"(R.Vb), "s"(W.nS), "s"(W.nSel), "s"(W.rs), "s"(W.N), "s"(nT));  // worked out while the indices travel
+  __builtin_amdgcn_sched_barrier(0);
+  if (flagged && __builtin_amdgcn_readfirstlane(slow) != 0) return;
 
   Tile T;
   float m_run = kNeg, l_run = 0.f;
@@ -1185,8 +1119,6 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_stream_kernel(con
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int nT = (W.N + kTile - 1) / kTile;
-  const int K = first < nT ? (nT - first + step - 1) / step : 0;
   // Memory instructions go out in the same order here as in an iteration of the loop below -- K rows,
   // the indices of the tile after, V rows -- so the in-order load counter reads the same on both ways
   // into the loop.  A wave without tiles reads row 0 and skips the loop.
@@ -1226,11 +1158,12 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_stream_kernel(con
     issue_v_rows<typename RowOff<PAGED>::type, WIDE>(T, R, ra, rb);
     __builtin_amdgcn_sched_barrier(0);
   }
+  mask_q<WIDE>(qreg, G, n);
   // The last tile is taken after the loop, without the refill: no rows are requested for a tile that does not
   // exist, and nothing is in flight when the wave reaches the record write (worth 0.05 us at most: the tail
   // waits for its own stores far longer than for such rows).
-  for (int k = 0; k + 1 < K; ++k) {
-    const int p0 = p_first + k * pstep;
+  int p0 = p_first;
+  for (int t = first; t + step < nT; t += step) {
     const int pn = p0 + pstep;
     float y[8];
     qk_phase<WIDE>(T, qreg, a.scale_log2, y);
@@ -1257,9 +1190,9 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_stream_kernel(con
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     pv_phase(T, a_hi, a_lo, acc);
     issue_v_rows<typename RowOff<PAGED>::type, WIDE>(T, R, ra, rb);
+    p0 = pn;
   }
-  if (K > 0) {
-    const int p0 = p_first + (K - 1) * pstep;
+  if (first < nT) {
     float y[8];
     qk_phase<WIDE>(T, qreg, a.scale_log2, y);
     if (p0 + kTile > W.N) mask_tail<true, WIDE>(T, y, jg, p0, W.N);
@@ -1848,20 +1781,21 @@ hipError_t launch_reorg(const ReorgArgs& a, int B, int rows, hipStream_t s) {
   else hipLaunchKernelGGL(reorg_kernel<false>, grid, dim3(kAttnThreads), 0, s, a);
   return hipGetLastError();
 }
-template <bool WIDE>
-static void launch_gather_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
-  if (a.pipelined) {
-    if (a.table != nullptr) hipLaunchKernelGGL((attn_gather_stream_kernel<true, WIDE>), grid, dim3(kAttnThreads), 0, s, a);
-    else hipLaunchKernelGGL((attn_gather_stream_kernel<false, WIDE>), grid, dim3(kAttnThreads), 0, s, a);
-    return;
-  }
-  if (a.table != nullptr) hipLaunchKernelGGL((attn_gather_kernel<true, WIDE>), grid, dim3(kAttnThreads), 0, s, a);
-  else hipLaunchKernelGGL((attn_gather_kernel<false, WIDE>), grid, dim3(kAttnThreads), 0, s, a);
-}
 hipError_t launch_attn_gather(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
-  const dim3 grid(n_slots, a.Hkv, B);
-  if (a.G <= 8) launch_gather_t<true>(a, grid, s);
-  else launch_gather_t<false>(a, grid, s);
+  const dim3 grid(n_slots, a.Hkv, B), block(kAttnThreads);
+  const uint8_t* flags = a.is_slow != nullptr ? a.is_slow : reinterpret_cast<const uint8_t*>(a.ctx_len);
+  const uint32_t shape = (uint32_t)a.Hkv | (a.ms == 4 ? 2u << 16 : 0u) | (a.is_slow != nullptr ? 1u << 20 : 0u);
+#define SFI_GATHER(PAGED, WIDE)                                                                                             \
+  hipLaunchKernelGGL((attn_gather_kernel<PAGED, WIDE>), grid, block, 0, s, a.sel_idx, a.n_sel, a.ctx_len, a.recent_start,  \
+                     flags, (uint32_t)a.sel_stride, shape, a.n_sink, a.n_split, a)
+  if (a.G <= 8) {
+    if (a.table != nullptr) SFI_GATHER(true, true);
+    else SFI_GATHER(false, true);
+  } else {
+    if (a.table != nullptr) SFI_GATHER(true, false);
+    else SFI_GATHER(false, false);
+  }
+#undef SFI_GATHER
   return hipGetLastError();
 }
 hipError_t launch_merge(const MergeArgs& a, int B, hipStream_t s) {
