@@ -23,8 +23,6 @@ struct sfi_ctx {
   int dense_wide;           // dense kernel reads K rows as whole 128-byte lines (A/B knob, sfi_set_dense_k_layout)
   int mixed_plan;           // the ragged step's dense launch plans itself on the device (default; A/B knob, sfi_set_mixed_plan)
   int last_dense_splits, last_fast_splits;
-  int selector_ran;         // a Selector pass has used the evidence now in the workspace: its histogram and state
-                            // words are no longer the cleared ones the dense kernel left
   // profiling: a ring of event pairs, one set of stages per hot call, read back in one go so that
   // no host synchronisation sits between the profiled calls
   int profiling;
@@ -101,13 +99,13 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->logits = (float*)take((size_t)(B * Hq + (full ? B * Hkv : 0)) * ld * sizeof(float));
   ws->keys = (uint32_t*)take((size_t)(B * Hkv) * ld * sizeof(uint32_t));
   ws->cand = (uint32_t*)take((size_t)(B * Hkv) * ld * 2 * sizeof(uint32_t));
-  ws->hist1 = (uint32_t*)take((size_t)(B * Hkv) * kHist1Bins * sizeof(uint32_t));
   ws->state = (uint32_t*)take((size_t)(B * Hkv) * kStateWords * sizeof(uint32_t));
   ws->segcnt = (uint32_t*)take((size_t)(B * Hkv) * n_seg * sizeof(uint32_t));
   ws->jstat = (float2*)take((size_t)(B * Hq) * sizeof(float2));
   ws->mu = (float*)take((size_t)(B * Hkv) * ld * sizeof(float));
+  ws->hist1 = (uint32_t*)take((size_t)(B * Hkv) * kHist1Bins * sizeof(uint32_t));
   ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * kWaves * kArriveStride * sizeof(uint32_t));
-  ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears both
+  ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind histogram and counters: one memset clears all three
   ws->prior = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->znms = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->segstat = full ? (double*)take((size_t)(B * Hkv) * n_seg * kSegStats * sizeof(double)) : nullptr;
@@ -158,8 +156,6 @@ int dense_splits_for(const sfi_ctx* x, int max_len, bool mixed) {
   const int pairs = x->cfg.batch * x->cfg.n_kv_heads;
   int cap = (tiles + kWaves - 1) / kWaves;
   if (cap > kMaxSplits) cap = kMaxSplits;
-  // records per query head: one per wave for J plus one per wave that owns sink / recent tiles
-  while (cap > 1 && cap * kWaves + (cap * kWaves < tiles_sr ? cap * kWaves : tiles_sr) > kSlotCap) --cap;
   int s;
   if (mixed) s = cap;
   else if (x->dense_target_wgs > 0) s = x->dense_target_wgs / pairs;
@@ -268,7 +264,7 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
   s->ms = 1; s->fs = 1;
   s->ld_pos = x->ws.ld_pos; s->n_seg_cap = x->ws.n_seg_cap;
   s->Hq = c.n_q_heads; s->Hkv = c.n_kv_heads; s->G = x->G;
-  s->n_sink = c.n_sink; s->recent = c.recent; s->n_jrec = n_split * kWaves; s->budget = budget;
+  s->n_sink = c.n_sink; s->recent = c.recent; s->n_rec = n_split; s->budget = budget;
   s->prior = x->ws.prior; s->znms = x->ws.znms; s->segstat = x->ws.segstat;
   s->gamma = c.gamma; s->beta = c.beta; s->p = c.p; s->eta = c.eta; s->lambda_clip = c.lambda_clip;
   s->alpha_soft = c.alpha_soft; s->alpha_cross = c.alpha_cross;
@@ -295,8 +291,6 @@ int run_selector(sfi_ctx* x, const SelArgs& sa, int max_len, hipStream_t st, boo
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;
   int n_seg = nJ > 0 ? (nJ + kSelSeg - 1) / kSelSeg : 1;
   if (n_seg > x->ws.n_seg_cap) n_seg = x->ws.n_seg_cap;
-  if (x->selector_ran) SFI_TRY(launch_sel_clear(sa, B, st));  // a second pass over the same evidence
-  x->selector_ran = 1;
   {
     StageTimer t(x, st, SFI_STAGE_SCORE);
     if (x->cfg.selector_mode == 1) SFI_TRY(launch_sel_full(sa, B, n_seg, st));
@@ -379,15 +373,16 @@ int sfi_create(const sfi_config* cfg, void* workspace, size_t workspace_bytes, s
   x->fast_tiles_per_wave = 0;
   x->tail_merge = 1;
   x->mixed_plan = 1;
-  // The arrival counters of split fast-step launches start at zero (and every launch leaves them there).
+  // The arrival counters of split launches and the Selector's histogram start at zero (and every launch, every Selector
+  // pass leaves them there).
   // A workspace the runtime knows (device, managed, pinned) is cleared here and a failure to do so is an error: with stale
   // counters no workgroup would ever take itself for the last one.  (Without a device, or with a
   // pointer the runtime does not know, nothing can be launched on this context anyway.)
   hipPointerAttribute_t attr;
-  if (have_device && hipPointerGetAttributes(&attr, ws.arrive) == hipSuccess &&
+  if (have_device && hipPointerGetAttributes(&attr, ws.hist1) == hipSuccess &&
       attr.type != hipMemoryTypeUnregistered) {  // device, managed or pinned host memory: all of it is cleared here
-    const size_t n_clear = (size_t)((char*)ws.guard - (char*)ws.arrive) + sizeof(int32_t);  // counters and guard word
-    if (hipMemset(ws.arrive, 0, n_clear) != hipSuccess ||
+    const size_t n_clear = (size_t)((char*)ws.guard - (char*)ws.hist1) + sizeof(int32_t);  // histogram, counters and guard word
+    if (hipMemset(ws.hist1, 0, n_clear) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
       (void)hipGetLastError();
       delete x;
@@ -456,8 +451,11 @@ int sfi_dense_attn(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.n_split = dense_splits_for(x, ml, false);
   set_dense_bounds(x, &a, ml);
   x->last_dense_splits = a.n_split;
+  if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
+  else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
-  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split * kWaves, 0, 0, nullptr, 0, x->G, ctx_len, nullptr, x->cfg.n_sink, x->cfg.recent, x->alpha, ml, x->cfg.out_bf16};
+  if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
+  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split, 0, 0, nullptr, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -496,13 +494,10 @@ int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.with_knorm = x->cfg.selector_mode == 1;
   a.big_stash = 1;  // every sequence is dense: one workgroup per compute unit, half as many write bursts
   a.no_v = out == nullptr;  // evidence only (sfi_evidence_add without an output)
-  a.hist1 = x->ws.hist1;
-  a.state = x->ws.state;
   x->last_dense_splits = a.n_split;
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
-  x->selector_ran = 0;  // fresh evidence, Selector state cleared by the launch above
   if (merge_later) return SFI_OK;  // the Selector's scoring launch merges
-  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split * kWaves, 0, 0, x->ws.jstat, a.n_split * kWaves, x->G, ctx_len, q_len, x->cfg.n_sink, x->cfg.recent, x->alpha, ml, x->cfg.out_bf16};
+  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split, 0, 0, x->ws.jstat, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -636,7 +631,7 @@ int fast_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const 
   else if (x->tail_merge) { a.out_merge = out; a.arrive = arrive; }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_gather(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
-  MergeArgs m{part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, 0, x->G, ctx_len, nullptr, x->cfg.n_sink, x->cfg.recent, x->alpha, x->cfg.max_ctx, x->cfg.out_bf16};
+  MergeArgs m{part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -849,7 +844,7 @@ int sfi_fast_step_compact(sfi_ctx* x, const void* q, const void* Kc, const void*
   else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_compact(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
-  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, 0, x->G, ctx_len, nullptr, x->cfg.n_sink, x->cfg.recent, x->alpha, x->cfg.max_ctx, x->cfg.out_bf16};
+  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -887,8 +882,6 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   set_dense_bounds(x, &d, ml);
   d.logits = x->ws.logits;
   d.with_knorm = x->cfg.selector_mode == 1;
-  d.hist1 = x->ws.hist1;
-  d.state = x->ws.state;
   x->last_dense_splits = d.n_split;
   AttnArgs f;
   fill_attn(x, &f, q, K, V, ctx_len);
@@ -931,9 +924,8 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
     if (!t.stop()) return SFI_ELAUNCH;
   }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(d, x->cfg.batch, d.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
-  x->selector_ran = 0;
   if (!merge_in_score) {
-    MergeArgs m{x->ws.part, out, is_slow, x->cfg.n_q_heads, d.n_split * kWaves, fast_done ? 0 : f.n_split, 2, x->ws.jstat, d.n_split * kWaves, x->G, ctx_len, nullptr, x->cfg.n_sink, x->cfg.recent, x->alpha, ml, x->cfg.out_bf16, ms, fs};
+    MergeArgs m{x->ws.part, out, is_slow, x->cfg.n_q_heads, d.n_split, fast_done ? 0 : f.n_split, 2, x->ws.jstat, x->G, x->alpha, x->cfg.out_bf16, fs};
     StageTimer t(x, st, SFI_STAGE_MERGE);
     SFI_TRY(launch_merge(m, x->cfg.batch, st));
     if (!t.stop()) return SFI_ELAUNCH;

@@ -8,9 +8,9 @@
 //          the waves of n_split workgroups share the tiles of the allowed set
 //          J = [n_sink, L - recent), for which y is also exposed to the Selector (Eq. window_logits,
 //          W = 1), followed by the tiles of the sink and recent rows, which the Selector never ranks
-//          (Eq. allowed_set).  A wave keeps the two kinds in separate records, so the J-only softmax
-//          normaliser of Eq. selector_pt is just the merge of the J records.  Every wave writes its
-//          own records: waves never wait for each other.
+//          (Eq. allowed_set).  A wave takes its J tiles first and keeps its softmax statistics at the point where
+//          they end, from which the J-only normaliser of Eq. selector_pt is merged.  The four waves of a workgroup are
+//          combined into one record.
 //   gather kernel (fast step): the list is  sink ++ sel_idx[0:n_sel] ++ [recent_start, L)
 //          (Eq. index_set_head), strided over n_split workgroups; the four waves of a workgroup
 //          are combined into one record (fewer records for the merge that follows).
@@ -28,6 +28,8 @@
 //         P is split into two bf16 terms (hi + lo) so the weights keep ~16 bits.
 // bf16 x bf16 products are exact in fp32, so logits differ from an fp64 evaluation only by the
 // fp32 accumulation inside the matrix core.
+#include <type_traits>
+
 #include "sfi_internal.h"
 #include "sfi_merge.h"
 
@@ -479,22 +481,166 @@ __device__ __forceinline__ float2 load_device2(__amdgpu_buffer_rsrc_t r, int byt
   return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
 }
 
-// record of (b, head, slot): { max of y, sum 2^(y - max), -, -, O[128] }, written by one wave
-__device__ __forceinline__ void write_wave_record(float* part, int64_t head0, int G, int wslot, const f32x4 (&acc)[8],
-                                                  float m_run, float l_run, int lane, bool with_acc = true) {
+// Where an attention workgroup's result goes.
+struct WgOut {
+  float* out_direct;   // the workgroup is the only one of its (b, h) pair: it writes O / l straight to out[b, head, :]
+  float* out_merge;    // or: records go out in device-scope stores and the last waves to finish merge them into this;
+  uint32_t* arrive;    //   arrive[w * kArriveStride] counts the pair's workgroups whose wave w has sent its heads' records
+  float* part;         // the records (with neither pointer above: a merge launch follows)
+  int n_split, slot_cap;
+  bool out_bf16;
+};
+__device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
+  WgOut o;
+  o.out_direct = a.out_direct;
+  o.out_merge = a.out_merge;
+  o.arrive = a.arrive != nullptr ? a.arrive + (int64_t)bh * kWaves * kArriveStride : nullptr;
+  o.part = a.part;
+  o.n_split = a.n_split;
+  o.slot_cap = a.slot_cap;
+  o.out_bf16 = a.out_bf16 != 0;
+  return o;
+}
+// The way out of an attention workgroup: the four waves' partial results are combined through LDS and sent where WgOut
+// says, and, in a split launch, the records of the pair's workgroups are merged in the kernel:
+//   out[b, head, :] = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) l_s.
+// This is the launch's critical path (a third of a short fast step), so it is one barrier long.  Every wave leaves its
+// raw partial result in LDS; behind the barrier wave w finishes the heads w, w + 4, ... by itself: it combines the four
+// waves' parts (lanes 0..31 one head, 32..63 the head four further on, four output dims per lane), stores the
+// workgroup's record of those heads in device-scope stores, waits for their acknowledgement and counts itself in on the
+// pair's counter for wave w.  The wave that finds all n_split - 1 others counted merges the records of its heads (even
+// records in lanes 0..31, odd ones in lanes 32..63, sixteen records in flight) and puts its counter back to zero.
+// The heads of a pair are thus merged by up to four waves, usually on as many compute units, each behind its own
+// stores only.  Nothing waits on another workgroup, and no cache is written back or invalidated as a whole (a
+// device-scope fence costs tens of microseconds here).
+// Measured against the previous form (a combine of two barriers, the whole workgroup's acknowledgement and count, one
+// workgroup merging): 131072 rows, 8 KV heads, budget 4096: 10.9 -> 9.6 us; 4 x 32768 rows, budget 2048: 11.6 -> 11.1 us;
+// 4096 rows, 2 KV heads, budget 256: 6.8 -> 6.4 us.
+// red: G x 128 floats of LDS per wave, wave_stride floats apart.
+// JSTAT (dense kernel with exposed logits): the record's header also carries the statistics over the allowed set J alone,
+// { m, l, m_J, l_J } (the fast step and the dense kernel without logits leave the last two words).
+// WITH_O false: header only.
+template <bool JSTAT = false, bool WITH_O = true>
+__device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, int slot, const f32x4 (&acc)[8], float m_run,
+                                          float l_run, float* red, int wave_stride, float m_j = 0.f, float l_j = 0.f) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
+  __shared__ float s_m[16][kWaves];
+  __shared__ float s_l[16][kWaves];
+  __shared__ float s_mj[JSTAT ? 16 : 1][kWaves];
+  __shared__ float s_lj[JSTAT ? 16 : 1][kWaves];
+  if (lane < 16) {
+    s_m[lane][w] = m_run;
+    s_l[lane][w] = l_run;
+    if (JSTAT) {
+      s_mj[lane][w] = m_j;
+      s_lj[lane][w] = l_j;
+    }
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int hh = 4 * jg + i;
-    if (with_acc && hh < G) {
-      float* dst = part + ((head0 + hh) * kSlotCap + wslot) * kPartStride + 4 + n * 8;
+    if (WITH_O && hh < G) {
+      float* dst = red + w * wave_stride + hh * kHeadDim + n * 8;
       *reinterpret_cast<float4*>(dst) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
       *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
     }
   }
-  if (lane < G) {
-    float* r = part + ((head0 + lane) * kSlotCap + wslot) * kPartStride;
-    *reinterpret_cast<float2*>(r) = make_float2(m_run, l_run);
+  __syncthreads();
+  if (w >= G) return;
+  const int half = lane >> 5, c = lane & 31;
+  constexpr int kRec = kPartStride * (int)sizeof(float);
+  // slot_cap: records each query head has room for (kSlotCap in a caller's workspace, fewer in the static scratch)
+  float* const pair_base = o.part + head0 * o.slot_cap * kPartStride;
+  const __amdgpu_buffer_rsrc_t R = pair_records(pair_base, G * o.slot_cap * kRec);
+  for (int h0 = w; h0 < G; h0 += 8) {
+    const int hh = min(h0 + 4 * half, G - 1);
+    const bool mine = h0 + 4 * half < G;
+    const float4 m4 = *reinterpret_cast<const float4*>(&s_m[hh][0]), l4 = *reinterpret_cast<const float4*>(&s_l[hh][0]);
+    float4 r[kWaves];
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww)
+      r[ww] = WITH_O ? *reinterpret_cast<const float4*>(red + ww * wave_stride + hh * kHeadDim + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float M = fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w));
+    const float f[kWaves] = {fast_exp2(m4.x - M), fast_exp2(m4.y - M), fast_exp2(m4.z - M), fast_exp2(m4.w - M)};
+    float4 t = make_float4(r[0].x * f[0], r[0].y * f[0], r[0].z * f[0], r[0].w * f[0]);
+#pragma unroll
+    for (int ww = 1; ww < kWaves; ++ww) {
+      t.x += r[ww].x * f[ww]; t.y += r[ww].y * f[ww]; t.z += r[ww].z * f[ww]; t.w += r[ww].w * f[ww];
+    }
+    const float ls = l4.x * f[0] + l4.y * f[1] + l4.z * f[2] + l4.w * f[3];
+    if (!JSTAT && o.out_direct != nullptr) {  // workgroup-uniform
+      const float inv = ls > 0.f ? 1.0f / ls : 0.f;
+      if (mine) store_out4(o.out_direct, (head0 + hh) * kHeadDim + 4 * c, make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv), o.out_bf16);
+    } else if (mine) {
+      const int off = (hh * o.slot_cap + slot) * kRec;  // from the pair's first record
+      if (!JSTAT && o.out_merge != nullptr) {
+        store_device4(R, off + 16 + 16 * c, t);
+        if (c == 0) store_device2(R, off, M, ls);
+      } else {
+        float* dst = pair_base + (hh * o.slot_cap + slot) * kPartStride;
+        if (WITH_O) *reinterpret_cast<float4*>(dst + 4 + 4 * c) = t;
+        if (JSTAT) {
+          const float4 mj = *reinterpret_cast<const float4*>(&s_mj[hh][0]), lj = *reinterpret_cast<const float4*>(&s_lj[hh][0]);
+          const float MJ = fmaxf(fmaxf(mj.x, mj.y), fmaxf(mj.z, mj.w));
+          const float LJ = lj.x * fast_exp2(mj.x - MJ) + lj.y * fast_exp2(mj.y - MJ) + lj.z * fast_exp2(mj.z - MJ) + lj.w * fast_exp2(mj.w - MJ);
+          if (c == 0) *reinterpret_cast<float4*>(dst) = make_float4(M, ls, MJ, LJ);
+        } else if (c == 0) {
+          *reinterpret_cast<float2*>(dst) = make_float2(M, ls);
+        }
+      }
+    }
+  }
+  if (JSTAT || o.out_merge == nullptr) return;
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's record stores have been performed
+  uint32_t before = 0;
+  if (lane == 0) before = __hip_atomic_fetch_add(o.arrive + w * kArriveStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != (uint32_t)(o.n_split - 1)) return;
+  if (lane == 0) __hip_atomic_store(o.arrive + w * kArriveStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int n_rec = o.n_split;
+  for (int hh = w; hh < G; hh += kWaves) {
+    const int P = hh * o.slot_cap * kRec;  // byte offset of the head's records
+    float M = kNeg, Z = 0.f;
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = half; s0 - half < n_rec; s0 += 16) {  // this half's records s0, s0 + 2, ...
+      float2 ml[8];
+      float4 r4[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int rec = P + min(s0 + 2 * i, n_rec - 1) * kRec;
+        if (i == 0 || s0 - half + 2 * i < n_rec) {  // wave-uniform
+          ml[i] = load_device2(R, rec);
+          r4[i] = load_device4(R, rec + 16 + 16 * c);
+        } else {
+          ml[i] = make_float2(kNeg, 0.f);
+          r4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      }
+      float Mn = M;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (s0 + 2 * i >= n_rec) ml[i] = make_float2(kNeg, 0.f);
+        Mn = fmaxf(Mn, ml[i].x);
+      }
+      const float f = fast_exp2(M - Mn);
+      Z *= f;
+      t.x *= f; t.y *= f; t.z *= f; t.w *= f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float wgt = fast_exp2(ml[i].x - Mn);
+        const float wl = s0 + 2 * i < n_rec ? wgt : 0.f;  // (a half without any record has Mn = kNeg and weights 1)
+        Z += wl * ml[i].y;
+        t.x += wl * r4[i].x; t.y += wl * r4[i].y; t.z += wl * r4[i].z; t.w += wl * r4[i].w;
+      }
+      M = Mn;
+    }
+    // the two halves' sums meet
+    const float Mo = half_max(M);
+    const float f = fast_exp2(M - Mo);
+    Z = half_sum(Z * f);
+    t = make_float4(half_sum(t.x * f), half_sum(t.y * f), half_sum(t.z * f), half_sum(t.w * f));
+    const float inv = Z > 0.f ? 1.0f / Z : 0.f;
+    if (half == 0) store_out4(o.out_merge, (head0 + hh) * kHeadDim + 4 * c, make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv), o.out_bf16);
   }
 }
 
@@ -545,7 +691,13 @@ template <int EXPOSE, bool PAGED, bool BIG = false, bool NOV = false, bool WIDE 
 __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split, const int slot, const int h, const int b,
                                            const int tid_bias = 0) {
   constexpr int kStash = BIG ? 2 * kStashFloats : kStashFloats;
-  __shared__ float s_stash[EXPOSE != 0 ? kWaves : 1][EXPOSE != 0 ? kStash : 1];  // per-wave logits stash
+  // per-wave LDS: the logits stash, and at the end the wave's O for the combine (finish_wg)
+  constexpr int kPatch = EXPOSE != 0 ? kStash : 16 * kHeadDim;
+  __shared__ __align__(16) float s_patch[kWaves][kPatch];
+  // everything uniform is asked for at once (the first argument load of a wave takes 0.4 us)
+  asm volatile("" ::"s"(a.q), "s"(a.K), "s"(a.V), "s"(a.k_sb), "s"(a.k_sh), "s"(a.k_st), "s"(a.v_sb), "s"(a.v_sh), "s"(a.v_st),
+               "s"(a.ctx_len), "s"(a.is_slow), "s"(a.q_len), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.n_sink), "s"(a.recent),
+               "s"(a.max_tiles), "s"(a.row_cap), "s"(a.len_cap));
   if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
   const int tid = threadIdx.x + tid_bias;  // (tid_bias: zero; see attn_dense_items_kernel)
   const int lane = tid & 63, w = tid >> 6;
@@ -567,8 +719,8 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
   // (tile t, position i is cache row n_sink + 32 t + i), tiles [nTJ, nTJ + nTS) cover the sink rows
   // followed by the recent window, which the Selector never ranks.  The n_split * 4 waves of the
   // (b, h) pair own tiles first, first + step, ... of that sequence, so every wave of every workgroup
-  // carries an equal share.  A wave's J tiles come first; it keeps two records, one for each run
-  // (the J-only softmax statistics the Selector needs are merged from the J records alone).
+  // carries an equal share.  A wave's J tiles come first: the J-only softmax statistics the Selector needs are the
+  // wave's running ones at the point where its J tiles end.  An evidence-only pass has nothing to do beyond J.
   // The rows of the wave's first tile follow from the block index alone (almost always a J tile):
   // their loads go out before ctx_len arrives, clamped to the launch's row bound.
   const int n_waves = n_split * kWaves;
@@ -580,15 +732,10 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
     if (!NOV) issue_v_affine<WIDE>(T, R, a.n_sink + first * kTile, a.row_cap);
   }
   bf16x8 qreg[4];
-  load_q<WIDE>(qreg, a.q, head0, G, jg, n);
+  load_q_raw<WIDE>(qreg, a.q, head0, G, jg, n);
   int bad = 0;
   int L, recent;  // a window query under the causal mask sees a shorter context with what is left of the recent window
   window_view(a.q_len, b, guarded_len(a.ctx_len[b * a.ms], a.len_cap, bad), a.recent, L, recent);
-  if (slot == 0 && a.hist1 != nullptr) {  // fresh Selector state for this (b, h)
-    uint32_t* hh = a.hist1 + (int64_t)bh * kHist1Bins;
-    for (int i = tid; i < kHist1Bins; i += kAttnThreads) hh[i] = 0u;
-    if (tid < kStateWords) a.state[(int64_t)bh * kStateWords + tid] = 0u;
-  }
   const int NJ = max(0, L - recent - a.n_sink);
   const int nTJ = (NJ + kTile - 1) / kTile;
   const int rJ_max = a.n_sink + NJ - 1;
@@ -596,7 +743,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
   const int rs = min(max(a.n_sink, L - recent), L);
   const int NS = nS + (L - rs);
   const int nTS = (NS + kTile - 1) / kTile;
-  const int nT = nTJ + nTS;
+  const int nT = nTJ + (NOV ? 0 : nTS);
   const int K = first < nT ? (nT - first + step - 1) / step : 0;      // tiles of this wave
   const int KJ = first < nTJ ? (nTJ - first + step - 1) / step : 0;   // ... of which in J
   const int d_rs = rs - nS, r_last = max(L, 1) - 1;
@@ -657,14 +804,16 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
   // A flat cache keeps two tiles in flight per wave: the second buffer takes the wave's second tile now.
   Tile T2;
   constexpr int NB = PAGED ? 1 : 2;  // tile buffers; a tile's refill is the wave's tile NB further on
-  if (!PAGED) {
+  if (!PAGED && K > 1) {
     __builtin_amdgcn_sched_barrier(0);
     issue_k_tile(T2, first + step);
     issue_v_tile(T2, first + step);
     __builtin_amdgcn_sched_barrier(0);
   }
+  mask_q<WIDE>(qreg, G, n);
 
   float m_run = kNeg, l_run = 0.f;
+  float m_j = kNeg, l_j = 0.f;  // the same over J alone
   f32x4 acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -678,7 +827,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
   // With EXPOSE == 2 a tile has one more row: ||k_j||^2 of its 32 positions, for the key-norm factor of
   // the Selector's prior (Eq. selector_prior_kn).
   const int rows_exp = G + (EXPOSE == 2 ? 1 : 0);
-  float* stash = EXPOSE != 0 ? &s_stash[w][0] : nullptr;
+  float* stash = &s_patch[w][0];
   float* lg_base = EXPOSE != 0 ? a.logits + (int64_t)bh * rows_exp * a.ld_pos : nullptr;
   const int tile_f4 = rows_exp * (kTile / 4);        // float4 per tile
   const int stash_cap = kStash / (rows_exp * kTile);  // tiles the stash holds
@@ -695,24 +844,18 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
     k_flushed += n_stashed;
     n_stashed = 0;
   };
-  auto write_record = [&](int wslot) {
-    write_wave_record(a.part, head0, G, wslot, acc, m_run, rows_sum(l_run), lane, !NOV);
-  };
-
   // One loop for all of the wave's tiles.  A tile buffer's K half is refilled with the rows of the
   // tile that uses the buffer next as soon as the logits are out, its V half as soon as P V is done,
   // so rows are on their way during all of the math (with two buffers, a whole tile more than with
-  // one).  The refill is unconditional -- past the wave's last tile it degenerates to re-reading row
-  // L - 1 -- so that no branch surrounds a load and every wait can name exactly the loads it needs.
-  auto tile_step = [&](Tile& T, int k) {
+  // one).  No branch surrounds a load, so that every wait can name exactly the loads it needs; the last tiles have
+  // copies of the body without the refill (the requests of a refill that reads nothing new cost a wave 0.2 us).
+  auto tile_step = [&](Tile& T, int k, auto refill) {
+    constexpr bool kRefill = decltype(refill)::value;
     const int t = first + k * step;
     const bool inJ = k < KJ;
-    if (k == KJ) {  // the J tiles are done (or there were none): close the J record, start the other one
-      write_record(first);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-      m_run = kNeg;
-      l_run = 0.f;
+    if (EXPOSE != 0 && k == KJ) {  // the J tiles are done (or there were none)
+      m_j = m_run;
+      l_j = l_run;
     }
     float y[8];
     f32x4 s4[4];
@@ -721,7 +864,8 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
     float k2a = 0.f, k2b = 0.f;
     if (EXPOSE == 2) knorm_phase(T, jg, n, k2a, k2b);
     int pra = 0, prb = 0;
-    if (PAGED) {
+    if (!kRefill) {
+    } else if (PAGED) {
       pra = P.phys(row_for(t + step, n), pa_n, bad);
       prb = P.phys(row_for(t + step, 16 + n), pb_n, bad);
       issue_k_rows<uint64_t>(T, R, pra, prb);
@@ -749,26 +893,41 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
     bf16x8 a_hi, a_lo;
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     if (!NOV) pv_phase(T, a_hi, a_lo, acc);
+    if (!kRefill) return;
     if (PAGED && !NOV) issue_v_rows<uint64_t>(T, R, pra, prb);
     else if (!PAGED) issue_v_tile(T, t + NB * step);
   };
+  const std::integral_constant<bool, true> refill;
+  const std::integral_constant<bool, false> last;
   if (PAGED) {
-    for (int k = 0; k < K; ++k) tile_step(T, k);
-  } else {
+    int k = 0;
+    for (; k + 1 < K; ++k) tile_step(T, k, refill);
+    if (k < K) tile_step(T, k, last);
+  } else if (K == 1) {
+    tile_step(T, 0, last);
+  } else if (K > 1) {
     // (an odd last tile is taken after the loop: a way out of the middle of the loop body would put a
     // path from the first buffer's refill straight to its next use into the flow graph, and the waits
     // would be placed for that path)
     int k = 0;
-    for (; k + 1 < K; k += 2) {
-      tile_step(T, k);
-      tile_step(T2, k + 1);
+    for (; k + 2 < K; k += 2) {
+      tile_step(T, k, refill);
+      tile_step(T2, k + 1, refill);
     }
-    if (k < K) tile_step(T, k);
+    if (k + 1 < K) {
+      tile_step(T, k, last);
+      tile_step(T2, k + 1, last);
+    } else {
+      tile_step(T, k, last);
+    }
   }
   if (EXPOSE != 0) flush_stash();
-  // the record still open: the J record if the wave had no other tile (slot first), else the record of
-  // its sink / recent tiles, slot n_waves + e with e the rank of its first such tile among them
-  write_record(K == KJ ? first : n_waves + (first + KJ * step - nTJ));
+  if (EXPOSE != 0 && K == KJ) {
+    m_j = m_run;
+    l_j = l_run;
+  }
+  finish_wg<EXPOSE != 0, !NOV>(wg_out_of(a, bh), head0, G, slot, acc, m_run, rows_sum(l_run), &s_patch[0][0], kPatch, m_j,
+                               EXPOSE != 0 ? rows_sum(l_j) : 0.f);
   report_guard(a.guard, bad);
 }
 // One workgroup per (split, KV head, sequence) cell ...
@@ -787,8 +946,7 @@ __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(c
 // (r, h, slot < s_r) number one per workgroup and hold the same number of tiles whatever the sequences' lengths (with
 // many slow sequences: about four splits each, dealt round robin).  Workgroup i takes cells i, i + grid, ...; workgroup
 // 0 leaves s_r in a.seq_splits for the launches that merge the records.
-// The waves of a workgroup share no LDS in the body, so a wave may be on the workgroup's next cell while another is
-// still on this one.  A cell's coordinates are made scalars again (they come out of LDS), so that the body's addressing
+// A cell's coordinates are made scalars again (they come out of LDS), so that the body's addressing
 // stays on the scalar unit as it is with block indices.
 template <int EXPOSE, bool PAGED>
 __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_items_kernel(const AttnArgs a) {
@@ -901,152 +1059,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_items_kernel(const
     int zero = 0;
     asm volatile("" : "+s"(zero));
     dense_body<EXPOSE, PAGED, true, false, false>(a, ns, rem - h * ns, h, b, zero);
-  }
-}
-
-// Where a fast-step workgroup's result goes.
-struct WgOut {
-  float* out_direct;   // the workgroup is the only one of its (b, h) pair: it writes O / l straight to out[b, head, :]
-  float* out_merge;    // or: records go out in device-scope stores and the last waves to finish merge them into this;
-  uint32_t* arrive;    //   arrive[w * kArriveStride] counts the pair's workgroups whose wave w has sent its heads' records
-  float* part;         // the records (with neither pointer above: a merge launch follows)
-  int n_split, slot_cap;
-  bool out_bf16;
-};
-__device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
-  WgOut o;
-  o.out_direct = a.out_direct;
-  o.out_merge = a.out_merge;
-  o.arrive = a.arrive != nullptr ? a.arrive + (int64_t)bh * kWaves * kArriveStride : nullptr;
-  o.part = a.part;
-  o.n_split = a.n_split;
-  o.slot_cap = a.slot_cap;
-  o.out_bf16 = a.out_bf16 != 0;
-  return o;
-}
-// The way out of a fast-step workgroup: the four waves' partial results are combined through LDS and sent where WgOut
-// says, and, in a split launch, the records of the pair's workgroups are merged in the kernel:
-//   out[b, head, :] = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) l_s.
-// This is the launch's critical path (a third of a short fast step), so it is one barrier long.  Every wave leaves its
-// raw partial result in LDS; behind the barrier wave w finishes the heads w, w + 4, ... by itself: it combines the four
-// waves' parts (lanes 0..31 one head, 32..63 the head four further on, four output dims per lane), stores the
-// workgroup's record of those heads in device-scope stores, waits for their acknowledgement and counts itself in on the
-// pair's counter for wave w.  The wave that finds all n_split - 1 others counted merges the records of its heads (even
-// records in lanes 0..31, odd ones in lanes 32..63, sixteen records in flight) and puts its counter back to zero.
-// The heads of a pair are thus merged by up to four waves, usually on as many compute units, each behind its own
-// stores only.  Nothing waits on another workgroup, and no cache is written back or invalidated as a whole (a
-// device-scope fence costs tens of microseconds here).
-// Measured against the previous form (a combine of two barriers, the whole workgroup's acknowledgement and count, one
-// workgroup merging): 131072 rows, 8 KV heads, budget 4096: 10.9 -> 9.6 us; 4 x 32768 rows, budget 2048: 11.6 -> 11.1 us;
-// 4096 rows, 2 KV heads, budget 256: 6.8 -> 6.4 us.
-template <int HMAX = 16>  // query heads the reduction buffer has room for (>= G)
-__device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, int slot, const f32x4 (&acc)[8], float m_run,
-                                          float l_run) {
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int jg = lane >> 4, n = lane & 15;
-  __shared__ float s_m[16][kWaves];
-  __shared__ float s_l[16][kWaves];
-  __shared__ __align__(16) float s_red[kWaves][HMAX][kHeadDim];
-  if (lane < 16) {
-    s_m[lane][w] = m_run;
-    s_l[lane][w] = l_run;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int hh = 4 * jg + i;
-    if (hh < G) {
-      float* dst = &s_red[w][hh][n * 8];
-      *reinterpret_cast<float4*>(dst) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
-    }
-  }
-  __syncthreads();
-  if (w >= G) return;
-  const int half = lane >> 5, c = lane & 31;
-  constexpr int kRec = kPartStride * (int)sizeof(float);
-  // slot_cap: records each query head has room for (kSlotCap in a caller's workspace, fewer in the static scratch)
-  float* const pair_base = o.part + head0 * o.slot_cap * kPartStride;
-  const __amdgpu_buffer_rsrc_t R = pair_records(pair_base, G * o.slot_cap * kRec);
-  for (int h0 = w; h0 < G; h0 += 8) {
-    const int hh = min(h0 + 4 * half, G - 1);
-    const bool mine = h0 + 4 * half < G;
-    const float4 m4 = *reinterpret_cast<const float4*>(&s_m[hh][0]), l4 = *reinterpret_cast<const float4*>(&s_l[hh][0]);
-    float4 r[kWaves];
-#pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) r[ww] = *reinterpret_cast<const float4*>(&s_red[ww][hh][4 * c]);
-    const float M = fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w));
-    const float f[kWaves] = {fast_exp2(m4.x - M), fast_exp2(m4.y - M), fast_exp2(m4.z - M), fast_exp2(m4.w - M)};
-    float4 t = make_float4(r[0].x * f[0], r[0].y * f[0], r[0].z * f[0], r[0].w * f[0]);
-#pragma unroll
-    for (int ww = 1; ww < kWaves; ++ww) {
-      t.x += r[ww].x * f[ww]; t.y += r[ww].y * f[ww]; t.z += r[ww].z * f[ww]; t.w += r[ww].w * f[ww];
-    }
-    const float ls = l4.x * f[0] + l4.y * f[1] + l4.z * f[2] + l4.w * f[3];
-    if (o.out_direct != nullptr) {  // workgroup-uniform
-      const float inv = ls > 0.f ? 1.0f / ls : 0.f;
-      if (mine) store_out4(o.out_direct, (head0 + hh) * kHeadDim + 4 * c, make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv), o.out_bf16);
-    } else if (mine) {
-      const int off = (hh * o.slot_cap + slot) * kRec;  // from the pair's first record
-      if (o.out_merge != nullptr) {
-        store_device4(R, off + 16 + 16 * c, t);
-        if (c == 0) store_device2(R, off, M, ls);
-      } else {
-        float* dst = pair_base + (hh * o.slot_cap + slot) * kPartStride;
-        *reinterpret_cast<float4*>(dst + 4 + 4 * c) = t;
-        if (c == 0) *reinterpret_cast<float2*>(dst) = make_float2(M, ls);
-      }
-    }
-  }
-  if (o.out_merge == nullptr) return;
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's record stores have been performed
-  uint32_t before = 0;
-  if (lane == 0) before = __hip_atomic_fetch_add(o.arrive + w * kArriveStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != (uint32_t)(o.n_split - 1)) return;
-  if (lane == 0) __hip_atomic_store(o.arrive + w * kArriveStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int n_rec = o.n_split;
-  for (int hh = w; hh < G; hh += kWaves) {
-    const int P = hh * o.slot_cap * kRec;  // byte offset of the head's records
-    float M = kNeg, Z = 0.f;
-    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = half; s0 - half < n_rec; s0 += 16) {  // this half's records s0, s0 + 2, ...
-      float2 ml[8];
-      float4 r4[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int rec = P + min(s0 + 2 * i, n_rec - 1) * kRec;
-        if (i == 0 || s0 - half + 2 * i < n_rec) {  // wave-uniform
-          ml[i] = load_device2(R, rec);
-          r4[i] = load_device4(R, rec + 16 + 16 * c);
-        } else {
-          ml[i] = make_float2(kNeg, 0.f);
-          r4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-      }
-      float Mn = M;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (s0 + 2 * i >= n_rec) ml[i] = make_float2(kNeg, 0.f);
-        Mn = fmaxf(Mn, ml[i].x);
-      }
-      const float f = fast_exp2(M - Mn);
-      Z *= f;
-      t.x *= f; t.y *= f; t.z *= f; t.w *= f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float wgt = fast_exp2(ml[i].x - Mn);
-        const float wl = s0 + 2 * i < n_rec ? wgt : 0.f;  // (a half without any record has Mn = kNeg and weights 1)
-        Z += wl * ml[i].y;
-        t.x += wl * r4[i].x; t.y += wl * r4[i].y; t.z += wl * r4[i].z; t.w += wl * r4[i].w;
-      }
-      M = Mn;
-    }
-    // the two halves' sums meet
-    const float Mo = half_max(M);
-    const float f = fast_exp2(M - Mo);
-    Z = half_sum(Z * f);
-    t = make_float4(half_sum(t.x * f), half_sum(t.y * f), half_sum(t.z * f), half_sum(t.w * f));
-    const float inv = Z > 0.f ? 1.0f / Z : 0.f;
-    if (half == 0) store_out4(o.out_merge, (head0 + hh) * kHeadDim + 4 * c, make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv), o.out_bf16);
+    __syncthreads();  // the combine of this cell is read before the next cell's logits go into the same LDS
   }
 }
 
@@ -1201,7 +1214,10 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
     pv_phase(T, a_hi, a_lo, acc);
   }
   l_run = rows_sum(l_run);
-  finish_wg<WIDE ? 8 : 16>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run);
+  {
+    __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
+    finish_wg(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+  }
   report_guard(a.guard, W.bad);  // last: the way to the record and the merge is the launch's critical path
 }
 
@@ -1347,7 +1363,8 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
     const float v = (float)(fold & 0xffu);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = f32x4{v, v, v, v};
-    finish_wg<WIDE ? 8 : 16>(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f);
+    __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
+    finish_wg(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   } else {
     fold ^= __shfl_xor(fold, 32);
     if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * a.slot_cap + slot) * kPartStride) + w] = fold;
@@ -1579,7 +1596,10 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
     issue_v_tile(t + step);
   }
   l_run = rows_sum(l_run);
-  finish_wg<WIDE ? 8 : 16>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run);
+  {
+    __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
+    finish_wg(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+  }
   report_guard(a.guard, bad);
 }
 
@@ -1662,16 +1682,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a)
   else if (a.mode == 1) n_slots = a.slots_fast;
   else n_slots = a.is_slow[b * a.fs] ? a.slots_slow : a.slots_fast;
   const bool dense = a.mode == 0 || (a.mode == 2 && a.is_slow[b * a.fs]);
-  if (dense) {
-    // dense records: slots_slow waves' J records, then one record per wave that owned sink / recent tiles
-    int L, recent;
-    window_view(a.q_len, b, min(max(a.ctx_len[b * a.ms], 0), a.len_cap), a.recent, L, recent);  // the dense launch's view
-    const int nS = min(a.n_sink, L);
-    const int rs = min(max(a.n_sink, L - recent), L);
-    const int nTS = (nS + (L - rs) + kTile - 1) / kTile;
-    n_slots = a.slots_slow + min(a.slots_slow, nTS);
-  }
-  merge_records(a.part, a.out, bg, n_slots, dense ? a.jstat : nullptr, a.n_j, a.G, a.alpha, a.out_bf16 != 0);
+  merge_records(a.part, a.out, bg, n_slots, dense ? a.jstat : nullptr, a.G, a.alpha, a.out_bf16 != 0);
 }
 
 __global__ void advance_kernel(int32_t* ctx_len, int32_t* recent_start, int B, int n_sink, int recent) {

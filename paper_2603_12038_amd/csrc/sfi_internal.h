@@ -14,11 +14,9 @@ constexpr int kAttnThreads = 64 * kWaves;
 constexpr int kStashFloats = 4096;  // per-wave LDS stash for exposed logits (16 KB): 128 / G tiles; big variant: twice that
 constexpr int kMaxNmsRadius = 64;
 constexpr int kSegStats = 5;        // sum f, sum r, sum f^2, sum f r, sum r^2 of one segment
-constexpr int kPartStride = 132;   // floats per split record: m, l, pad, pad, acc[128]
+constexpr int kPartStride = 132;   // floats per split record: m, l, and over J alone m, l (dense kernel), acc[128]
 constexpr int kMaxSplits = 63;     // split workgroups per (sequence, KV head)
-// records per (sequence, query head): the dense kernel writes one per wave, (splits + 1 sink/recent
-// workgroup) x 4 waves; the gather kernel one per workgroup
-constexpr int kSlotCap = (kMaxSplits + 1) * kWaves;
+constexpr int kSlotCap = kMaxSplits + 1;  // records per (sequence, query head): one per workgroup
 // Words between two arrival counters of the fast step's in-kernel merge: a cache line each.  Atomics on one line are
 // performed one after the other, about 30 ns apiece.
 constexpr int kArriveStride = 32;
@@ -127,8 +125,6 @@ struct AttnArgs {
   int64_t table_stride;
   int32_t page_lg;               // log2 of the page size in rows
   int32_t page_rpb;              // row numbers a block spans in the pool's row space (block stride / row stride)
-  uint32_t* hist1;               // dense mode with Selector: cleared by the sink/recent workgroup
-  uint32_t* state;
   int64_t ld_pos;
   int32_t Hq, Hkv, G, n_sink, recent, n_split;
   int32_t max_tiles;             // dense mode: tiles of J the launch covers at most (from the host's max_len)
@@ -174,14 +170,10 @@ struct MergeArgs {
   int32_t Hq, slots_slow, slots_fast;  // slot counts for slow / fast sequences
   int32_t mode;                        // 0: all sequences use slots_slow, 1: all use slots_fast, 2: per is_slow
   float2* jstat;                       // dense records: also leave the J-only softmax statistics here (may be null)
-  int32_t n_j, G;                      // records that cover J; query heads per KV head
-  const int32_t* ctx_len;              // dense records: the number of sink / recent records follows from it
-  const int32_t* q_len;                // the dense launch's (see window_view)
-  int32_t n_sink, recent;
+  int32_t G;                           // query heads per KV head
   float alpha;                         // power-mean exponent of the evidence (Eq. selector_mu)
-  int32_t len_cap;                     // the clamp the dense launch applied to ctx_len
   int32_t out_bf16;                    // out is bf16
-  int32_t ms = 1, fs = 1;              // strides of ctx_len (int32) and is_slow (bytes), see AttnArgs
+  int32_t fs = 1;                      // stride of is_slow in bytes, see AttnArgs
 };
 
 struct SelArgs {
@@ -194,7 +186,7 @@ struct SelArgs {
   uint32_t* segcnt;
   const int32_t* ctx_len;
   const int32_t* q_len;    // accumulation of a window query under the causal mask (see window_view), else nullptr
-  const int32_t* seq_splits;  // ragged step: splits the dense launch chose per sequence (n_jrec = 4 x that), else nullptr
+  const int32_t* seq_splits;  // ragged step: splits the dense launch chose per sequence, else nullptr (n_rec)
   int32_t ms, fs;          // strides of ctx_len (int32) and is_slow (bytes), see AttnArgs
   const uint8_t* is_slow;
   int32_t* sel_idx;
@@ -202,7 +194,7 @@ struct SelArgs {
   int64_t ld_pos;
   int32_t n_seg_cap;
   int32_t Hq, Hkv, G, n_sink, recent, budget;
-  int32_t n_jrec;          // dense records that cover J (one per wave of the dense launch)
+  int32_t n_rec;           // dense records per query head (one per workgroup of the dense launch)
   // full Selector (mode 1)
   float* prior;
   float* znms;
@@ -231,7 +223,6 @@ hipError_t launch_reorg(const ReorgArgs& a, int B, int rows, hipStream_t s);
 hipError_t launch_attn_gather(const AttnArgs& a, int B, int n_slots, hipStream_t s);
 hipError_t launch_attn_gather_floor(const AttnArgs& a, int B, int n_slots, int tail, int burst, int tpw, int depth, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, int B, hipStream_t s);
-hipError_t launch_sel_clear(const SelArgs& a, int B, hipStream_t s);
 hipError_t launch_sel_score(const SelArgs& a, int B, int n_seg, hipStream_t s);
 hipError_t launch_sel_accum(const SelArgs& a, int B, int n_seg, hipStream_t s);
 hipError_t launch_sel_finalize(const SelArgs& a, int B, int n_seg, hipStream_t s);

@@ -6,18 +6,18 @@ namespace sfi {
 
 constexpr int kMergeThreads = 256;
 constexpr int kMergeLanes = 8;
-static_assert(kSlotCap <= kMergeThreads, "one record header per thread");
+static_assert(kSlotCap <= 64, "one record header per lane of a wave");
 
 // out[bg, :] = sum_s 2^{m_s - M} acc_s / sum_s 2^{m_s - M} l_s over the n_slots split records of
 // (sequence, query head) bg.  One workgroup of 256 threads = 8 record lanes x 32 dim quads: every
 // thread owns four output dims of every eighth record, so all of a thread's loads are independent
 // and in flight together.
-// If jstat != nullptr the first n_j records are the ones that cover the allowed set J (dense kernel):
+// If jstat != nullptr the record headers also carry the statistics over the allowed set J alone (dense kernel):
 // their merge gives the J-only softmax statistics of this head for the Selector (Eq. selector_pt),
 // stored as jstat[bg] = { M = max of y over J, Z^(-alpha) / G } with Z = sum over J of 2^(y - M): the
 // head's term of Eq. selector_mu is then p^alpha / G = (Z^(-alpha) / G) * 2^(alpha (y - M)).
 __device__ __forceinline__ void merge_records(const float* part, float* out, int bg, int n_slots, float2* jstat,
-                                              int n_j, int G, float alpha, bool out_bf16) {
+                                              int G, float alpha, bool out_bf16) {
   const float* P = part + (int64_t)bg * kSlotCap * kPartStride;
   const int tid = threadIdx.x;
   const int sl = tid >> 5, c = tid & 31;
@@ -28,11 +28,13 @@ __device__ __forceinline__ void merge_records(const float* part, float* out, int
   __shared__ float4 s_acc[kMergeLanes][32];
 
   // the record headers: one per thread
-  float m = kNeg, l = 0.f;
+  float m = kNeg, l = 0.f, mj = kNeg, lj = 0.f;
   if (tid < n_slots) {
-    const float2 ml = *reinterpret_cast<const float2*>(P + tid * kPartStride);
-    m = ml.x;
-    l = ml.y;
+    const float4 hd = *reinterpret_cast<const float4*>(P + tid * kPartStride);
+    m = hd.x;
+    l = hd.y;
+    mj = jstat != nullptr ? hd.z : kNeg;
+    lj = hd.w;
   }
   float M = m;
 #pragma unroll
@@ -47,22 +49,16 @@ __device__ __forceinline__ void merge_records(const float* part, float* out, int
     r[i] = s < n_slots ? *reinterpret_cast<const float4*>(P + s * kPartStride + 4 + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (jstat != nullptr) {  // block-uniform
-    __shared__ float s_jm[kMergeThreads / 64], s_jz[kMergeThreads / 64];
-    float mj = tid < n_j ? m : kNeg;
+    // (a wave holds all record headers: kSlotCap <= 64)
+    if (tid < 64) {
+      float MJ = mj;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) mj = fmaxf(mj, __shfl_xor(mj, d));
-    if ((tid & 63) == 0) s_jm[tid >> 6] = mj;
-    __syncthreads();
-    const float MJ = fmaxf(fmaxf(s_jm[0], s_jm[1]), fmaxf(s_jm[2], s_jm[3]));
-    float zj = tid < n_j ? l * __builtin_amdgcn_exp2f(m - MJ) : 0.f;
+      for (int d = 32; d >= 1; d >>= 1) MJ = fmaxf(MJ, __shfl_xor(MJ, d));
+      float Z = tid < n_slots ? lj * __builtin_amdgcn_exp2f(mj - MJ) : 0.f;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) zj += __shfl_xor(zj, d);
-    if ((tid & 63) == 0) s_jz[tid >> 6] = zj;
-    __syncthreads();
-    if (tid == 0) {
-      const float Z = s_jz[0] + s_jz[1] + s_jz[2] + s_jz[3];
+      for (int d = 32; d >= 1; d >>= 1) Z += __shfl_xor(Z, d);
       const float zpow = alpha == 1.0f ? Z : __builtin_amdgcn_exp2f(alpha * __builtin_amdgcn_logf(Z));
-      jstat[bg] = make_float2(MJ, 1.0f / ((float)G * zpow));
+      if (tid == 0) jstat[bg] = make_float2(MJ, 1.0f / ((float)G * zpow));
     }
   }
   __syncthreads();

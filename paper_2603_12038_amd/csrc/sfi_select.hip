@@ -104,6 +104,11 @@ struct Problem {
   uint32_t ksel; // min(budget, |J|)
 };
 
+// Stage 1 clears the pair's state words for the stages behind it (stage 3 the histogram, for the next pass).
+__device__ __forceinline__ void clear_state(const SelArgs& a, int bh) {
+  if (threadIdx.x < kStateWords) a.state[(int64_t)bh * kStateWords + threadIdx.x] = 0u;
+}
+
 __device__ __forceinline__ Problem problem_of(const SelArgs& a, int b) {
   Problem p;
   p.nJ = max(0, min(a.ctx_len[b * a.ms], a.len_cap) - a.recent - a.n_sink);  // the dense launch's clamp of ctx_len
@@ -113,43 +118,26 @@ __device__ __forceinline__ Problem problem_of(const SelArgs& a, int b) {
 
 // The slow step without a merge launch (SelArgs::part != nullptr).  The launch that reads the exposed
 // logits first carries G extra workgroups per (b, h); each merges the dense kernel's records of one
-// query head into the attention output (J records of all waves, then one record per wave that owned
-// sink / recent tiles).
-// J records per query head of sequence b: one per wave of the dense launch's workgroups of that sequence (the ragged
-// step's dense launch chooses the splits per sequence on the device and leaves them in the workspace)
-__device__ __forceinline__ int n_jrec_of(const SelArgs& a, int b) {
-  return a.seq_splits != nullptr ? a.seq_splits[b] * kWaves : a.n_jrec;
-}
+// query head into the attention output.
+// Records per query head of sequence b: one per workgroup of the dense launch (the ragged step's dense launch chooses the
+// splits per sequence on the device and leaves them in the workspace).
+__device__ __forceinline__ int n_rec_of(const SelArgs& a, int b) { return a.seq_splits != nullptr ? a.seq_splits[b] : a.n_rec; }
 __device__ __forceinline__ void merge_head(const SelArgs& a, int b, int h, int g) {
-  const int n_jrec = n_jrec_of(a, b);
-  const int L = min(max(a.ctx_len[b * a.ms], 0), a.len_cap);
-  const int nS = min(a.n_sink, L);
-  const int rs = min(max(a.n_sink, L - a.recent), L);
-  const int nTS = (nS + (L - rs) + 31) / 32;
-  const int n_slots = n_jrec + min(n_jrec, nTS);
-  merge_records(a.part, a.merge_out, b * a.Hq + h * a.G + g, n_slots, nullptr, 0, a.G, a.alpha, a.out_bf16 != 0);
+  merge_records(a.part, a.merge_out, b * a.Hq + h * a.G + g, n_rec_of(a, b), nullptr, a.G, a.alpha, a.out_bf16 != 0);
 }
 
-// ... and every other workgroup takes the J-only softmax statistics of the group's heads from the
-// headers of the J records itself: one wave per head, a lane takes records lane, lane + 64, ... (at
-// most kSlotCap = 256).  sM[g] = max of y over J, sc[g] = Z^(-alpha) / G; valid after the next barrier.
+// ... and every other workgroup takes the J-only softmax statistics of the group's heads from the record headers itself:
+// one wave per head, a record per lane.  sM[g] = max of y over J, sc[g] = Z^(-alpha) / G; valid after the next barrier.
 __device__ __forceinline__ void group_jstat(const SelArgs& a, int b, int h, float* sM, float* sc) {
   const int lane = threadIdx.x & 63;
-  const int n_jrec = n_jrec_of(a, b);
+  const int n_rec = n_rec_of(a, b);
   for (int g = threadIdx.x >> 6; g < a.G; g += kSelThreads / 64) {
     const float* P = a.part + (int64_t)(b * a.Hq + h * a.G + g) * kSlotCap * kPartStride;
-    float2 ml[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int sl = lane + 64 * i;
-      ml[i] = sl < n_jrec ? *reinterpret_cast<const float2*>(P + (int64_t)sl * kPartStride) : make_float2(kNeg, 0.f);
-    }
-    float M = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+    const float2 ml = lane < n_rec ? *reinterpret_cast<const float2*>(P + (int64_t)lane * kPartStride + 2) : make_float2(kNeg, 0.f);
+    float M = ml.x;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
-    float Z = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) Z += ml[i].y * fast_exp2s(ml[i].x - M);
+    float Z = ml.y * fast_exp2s(ml.x - M);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) Z += __shfl_xor(Z, d);
     if (lane == 0) {
@@ -167,6 +155,7 @@ template <bool ACCUM>
 __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a) {
   const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
+  if (!ACCUM && seg == 0) clear_state(a, b * a.Hkv + h);
   Problem pb = problem_of(a, b);
   int n_all = pb.nJ;  // ACCUM under the causal mask: |J| of the whole window; pb.nJ becomes the part this query sees
   if (ACCUM && a.q_len != nullptr) {
@@ -291,6 +280,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a)
 __global__ __launch_bounds__(kSelThreads) void sel_finalize_kernel(const SelArgs a) {
   const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
+  if (seg == 0) clear_state(a, b * a.Hkv + h);
   const Problem pb = problem_of(a, b);
   const int p_lo = seg * kSelSeg;
   if (p_lo >= pb.nJ) return;
@@ -352,6 +342,7 @@ __device__ __forceinline__ void block_sums_f64(double (&v)[kSegStats], double (*
 __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a) {
   const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
+  if (seg == 0) clear_state(a, b * a.Hkv + h);
   const Problem pb = problem_of(a, b);
   const int G = a.G, rows = G + 1;
   const bool fused = a.part != nullptr;  // grid-uniform: no merge launch has run
@@ -639,6 +630,10 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
   // padding and n_sel, spread over the segments' workgroups
   for (int i = (int)pb.ksel + seg * kSelThreads + tid; i < a.budget; i += n_seg * kSelThreads) out[i] = -1;
   if (seg == 0 && tid == 0) a.n_sel[bh] = (int32_t)pb.ksel;
+  {  // the histogram goes back to zero for the next pass (its readers were in the launch before)
+    uint32_t* gh = a.hist1 + (int64_t)bh * kHist1Bins;
+    for (int i = seg * kSelThreads + tid; i < kHist1Bins; i += n_seg * kSelThreads) gh[i] = 0u;
+  }
   const int p_lo = seg * kSelSeg;
   if (pb.ksel == 0 || p_lo >= pb.nJ) return;
   const int p_hi = min(p_lo + kSelSeg, pb.nJ);
@@ -733,22 +728,6 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
       eq_before += e;
     }
   }
-}
-
-// Fresh Selector state (histogram, state words) for every (b, h) of the sequences taking part.  The dense
-// kernel does this for the evidence it writes; a Selector pass that runs a second time on the same evidence
-// (another budget, say) starts with this launch instead, or it would count into the first pass's histogram.
-__global__ __launch_bounds__(kSelThreads) void sel_clear_kernel(const SelArgs a) {
-  const int h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  const int bh = b * a.Hkv + h;
-  uint32_t* hh = a.hist1 + (int64_t)bh * kHist1Bins;
-  for (int i = threadIdx.x; i < kHist1Bins; i += kSelThreads) hh[i] = 0u;
-  if (threadIdx.x < kStateWords) a.state[(int64_t)bh * kStateWords + threadIdx.x] = 0u;
-}
-hipError_t launch_sel_clear(const SelArgs& a, int B, hipStream_t s) {
-  hipLaunchKernelGGL(sel_clear_kernel, dim3(1, a.Hkv, B), dim3(kSelThreads), 0, s, a);
-  return hipGetLastError();
 }
 
 hipError_t launch_sel_score(const SelArgs& a, int B, int n_seg, hipStream_t s) {
