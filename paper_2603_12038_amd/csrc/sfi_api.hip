@@ -86,7 +86,7 @@ int validate(const sfi_config* c) {
 size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   const int64_t B = c->batch, Hq = c->n_q_heads, Hkv = c->n_kv_heads;
   const int64_t ld = (int64_t)align_up((size_t)c->max_ctx, kSelSeg);
-  const int n_seg = (int)(ld / kSelSeg);
+  const int n_seg = (int)(ld / kPriorSeg);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char* p = base ? base + off : nullptr;
@@ -103,13 +103,13 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->segcnt = (uint32_t*)take((size_t)(B * Hkv) * n_seg * sizeof(uint32_t));
   ws->jstat = (float2*)take((size_t)(B * Hq) * sizeof(float2));
   ws->mu = (float*)take((size_t)(B * Hkv) * ld * sizeof(float));
-  ws->hist1 = (uint32_t*)take((size_t)(B * Hkv) * kHist1Bins * sizeof(uint32_t));
+  ws->hist = (uint32_t*)take((size_t)(B * Hkv) * n_seg * (kHistBins / 2) * sizeof(uint32_t));
   ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * kWaves * kArriveStride * sizeof(uint32_t));
-  ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind histogram and counters: one memset clears all three
+  ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears both
   ws->prior = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
-  ws->znms = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
+  ws->fbuf = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->segstat = full ? (double*)take((size_t)(B * Hkv) * n_seg * kSegStats * sizeof(double)) : nullptr;
-  ws->seq_splits = (int32_t*)take((size_t)B * sizeof(int32_t));
+  ws->slow_list = (int32_t*)take((4 + 4 * (size_t)B) * sizeof(int32_t));
   ws->ld_pos = ld;
   ws->n_seg_cap = n_seg;
   return off;
@@ -259,13 +259,13 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
   memset(s, 0, sizeof(*s));
   const sfi_config& c = x->cfg;
   s->jstat = x->ws.jstat; s->logits = x->ws.logits; s->keys = x->ws.keys; s->cand = x->ws.cand;
-  s->hist1 = x->ws.hist1; s->state = x->ws.state; s->segcnt = x->ws.segcnt;
+  s->hist = x->ws.hist; s->state = x->ws.state; s->segcnt = x->ws.segcnt;
   s->ctx_len = ctx_len; s->is_slow = is_slow; s->sel_idx = sel_idx; s->n_sel = n_sel;
   s->ms = 1; s->fs = 1;
   s->ld_pos = x->ws.ld_pos; s->n_seg_cap = x->ws.n_seg_cap;
   s->Hq = c.n_q_heads; s->Hkv = c.n_kv_heads; s->G = x->G;
   s->n_sink = c.n_sink; s->recent = c.recent; s->n_rec = n_split; s->budget = budget;
-  s->prior = x->ws.prior; s->znms = x->ws.znms; s->segstat = x->ws.segstat;
+  s->prior = x->ws.prior; s->fbuf = x->ws.fbuf; s->segstat = x->ws.segstat;
   s->gamma = c.gamma; s->beta = c.beta; s->p = c.p; s->eta = c.eta; s->lambda_clip = c.lambda_clip;
   s->alpha_soft = c.alpha_soft; s->alpha_cross = c.alpha_cross;
   s->inv_temp = c.temp > 0.f ? 1.0f / c.temp : 1.0f;
@@ -286,20 +286,30 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
 
 // Selector kernels after a dense launch that exposed logits.
 // windowed: rank the accumulated evidence (sa.mu_scale set) instead of the last query's.
+// How many launches: the whole of J in the registers of one workgroup per pair (up to 16384 positions) saves the histogram,
+// the candidates and a launch; below about 24576 logits per pair (96 KB, which a compute unit reads in the time a
+// launch costs) that workgroup scores as well.
 int run_selector(sfi_ctx* x, const SelArgs& sa, int max_len, hipStream_t st, bool windowed = false) {
   const int B = x->cfg.batch;
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;
-  int n_seg = nJ > 0 ? (nJ + kSelSeg - 1) / kSelSeg : 1;
-  if (n_seg > x->ws.n_seg_cap) n_seg = x->ws.n_seg_cap;
+  const bool pick = nJ <= kPickMax;
+  int src = 0;
   {
     StageTimer t(x, st, SFI_STAGE_SCORE);
-    if (x->cfg.selector_mode == 1) SFI_TRY(launch_sel_full(sa, B, n_seg, st));
-    else if (windowed) SFI_TRY(launch_sel_finalize(sa, B, n_seg, st));
-    else SFI_TRY(launch_sel_score(sa, B, n_seg, st));
+    if (x->cfg.selector_mode == 1) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
+    else if (windowed && pick) src = 2;
+    else if (windowed) SFI_TRY(launch_sel_finalize(sa, B, nJ, st));
+    else if (sa.part != nullptr && sel_pick_scores(nJ, x->G)) src = 1;
+    else SFI_TRY(launch_sel_score(sa, B, nJ, !pick, st));
     if (!t.stop()) return SFI_ELAUNCH;
   }
-  { StageTimer t(x, st, SFI_STAGE_CAND);  SFI_TRY(launch_sel_cand(sa, B, n_seg, st));  if (!t.stop()) return SFI_ELAUNCH; }
-  { StageTimer t(x, st, SFI_STAGE_WRITE); SFI_TRY(launch_sel_write(sa, B, n_seg, st)); if (!t.stop()) return SFI_ELAUNCH; }
+  if (pick) {
+    StageTimer t(x, st, SFI_STAGE_WRITE);
+    SFI_TRY(launch_sel_pick(sa, B, nJ, src, st));
+    return t.stop() ? SFI_OK : SFI_ELAUNCH;
+  }
+  { StageTimer t(x, st, SFI_STAGE_CAND);  SFI_TRY(launch_sel_cand(sa, B, nJ, st));  if (!t.stop()) return SFI_ELAUNCH; }
+  { StageTimer t(x, st, SFI_STAGE_WRITE); SFI_TRY(launch_sel_write(sa, B, nJ, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
 
@@ -373,16 +383,15 @@ int sfi_create(const sfi_config* cfg, void* workspace, size_t workspace_bytes, s
   x->fast_tiles_per_wave = 0;
   x->tail_merge = 1;
   x->mixed_plan = 1;
-  // The arrival counters of split launches and the Selector's histogram start at zero (and every launch, every Selector
-  // pass leaves them there).
+  // The arrival counters of split launches start at zero (and every launch leaves them there).
   // A workspace the runtime knows (device, managed, pinned) is cleared here and a failure to do so is an error: with stale
   // counters no workgroup would ever take itself for the last one.  (Without a device, or with a
   // pointer the runtime does not know, nothing can be launched on this context anyway.)
   hipPointerAttribute_t attr;
-  if (have_device && hipPointerGetAttributes(&attr, ws.hist1) == hipSuccess &&
+  if (have_device && hipPointerGetAttributes(&attr, ws.arrive) == hipSuccess &&
       attr.type != hipMemoryTypeUnregistered) {  // device, managed or pinned host memory: all of it is cleared here
-    const size_t n_clear = (size_t)((char*)ws.guard - (char*)ws.hist1) + sizeof(int32_t);  // histogram, counters and guard word
-    if (hipMemset(ws.hist1, 0, n_clear) != hipSuccess ||
+    const size_t n_clear = (size_t)((char*)ws.guard - (char*)ws.arrive) + sizeof(int32_t);  // counters and guard word
+    if (hipMemset(ws.arrive, 0, n_clear) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
       (void)hipGetLastError();
       delete x;
@@ -568,16 +577,17 @@ int evidence_add_impl(sfi_ctx* x, const void* q, const void* K, const void* V, c
   int ml;
   if ((rc = resolve_max_len(x, max_len, &ml)) != SFI_OK) return rc;
   CallRecord call_record(x);
-  if ((rc = slow_attn_impl(x, q, K, V, ctx_len, ml, out, st, false, q_len)) != SFI_OK) return rc;
+  // no merge launch: the accumulation takes the statistics from the record headers and merges the output, if there is one
+  if ((rc = slow_attn_impl(x, q, K, V, ctx_len, ml, out, st, true, q_len)) != SFI_OK) return rc;
   SelArgs sa;
   fill_sel(x, &sa, ctx_len, ml, nullptr, 0, x->last_dense_splits, nullptr, nullptr);
+  sa.part = x->ws.part;
+  sa.merge_out = out;
   sa.accum_first = first != 0;
   sa.q_len = q_len;
   // a query under the causal mask may see up to `recent` more positions of its own, shorter context as allowed set
   const int nJ = ml - (q_len != nullptr ? 0 : x->cfg.recent) - x->cfg.n_sink;
-  int n_seg = nJ > 0 ? (nJ + kSelSeg - 1) / kSelSeg : 1;
-  if (n_seg > x->ws.n_seg_cap) n_seg = x->ws.n_seg_cap;
-  { StageTimer t(x, st, SFI_STAGE_SCORE); SFI_TRY(launch_sel_accum(sa, x->cfg.batch, n_seg, st)); if (!t.stop()) return SFI_ELAUNCH; }
+  { StageTimer t(x, st, SFI_STAGE_SCORE); SFI_TRY(launch_sel_accum(sa, x->cfg.batch, nJ, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
 }  // namespace
@@ -913,7 +923,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   if (planned) {
     d.item_batch = x->cfg.batch;
     d.item_wgs = x->n_cu;
-    d.seq_splits = x->ws.seq_splits;
+    d.slow_list = x->ws.slow_list;
   }
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
@@ -937,7 +947,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
     sa.part = x->ws.part;
     sa.merge_out = out;
   }
-  if (planned) sa.seq_splits = x->ws.seq_splits;
+  if (planned) sa.slow_list = x->ws.slow_list;
   if ((rc = run_selector(x, sa, ml, st)) != SFI_OK) return rc;
   if (cb == nullptr) return SFI_OK;
   // Reorg_i for the sequences that were refreshed (Sel_i -> Reorg_i)

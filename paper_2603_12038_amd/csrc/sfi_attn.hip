@@ -945,7 +945,7 @@ __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(c
 // wave, what the rounding left over going one by one to the sequence with the most tiles per split -- so that the cells
 // (r, h, slot < s_r) number one per workgroup and hold the same number of tiles whatever the sequences' lengths (with
 // many slow sequences: about four splits each, dealt round robin).  Workgroup i takes cells i, i + grid, ...; workgroup
-// 0 leaves s_r in a.seq_splits for the launches that merge the records.
+// 0 leaves the list of slow sequences with s_r for the Selector's launches, which then need workgroups for those alone.
 // A cell's coordinates are made scalars again (they come out of LDS), so that the body's addressing
 // stays on the scalar unit as it is with block indices.
 template <int EXPOSE, bool PAGED>
@@ -994,7 +994,10 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_items_kernel(const
     n_slow += t;
   }
   n_slow = __builtin_amdgcn_readfirstlane(n_slow);
-  if (n_slow == 0) return;
+  if (n_slow == 0) {
+    if (blockIdx.x == 0 && tid == 0) a.slow_list[0] = 0;
+    return;
+  }
   const int total = max(1, s_scr[4] + s_scr[5] + s_scr[6] + s_scr[7]);
   // splits to hand out among the slow sequences: one cell per workgroup, or, with many slow sequences, about four
   // splits each, so that dealing the cells round robin still balances
@@ -1039,8 +1042,12 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_items_kernel(const
     s_first[n_slow] = acc;
   }
   __syncthreads();
-  if (blockIdx.x == 0)
-    for (int r = tid; r < n_slow; r += kAttnThreads) a.seq_splits[s_list[r]] = s_split[r];
+  if (blockIdx.x == 0) {
+    if (tid == 0) a.slow_list[0] = n_slow;
+    for (int r = tid; r < n_slow; r += kAttnThreads)
+      reinterpret_cast<int4*>(a.slow_list)[1 + r] =
+          make_int4(s_list[r], min(max(a.ctx_len[(int64_t)s_list[r] * a.ms], 0), a.len_cap), s_split[r], 0);
+  }
   const int n_items = __builtin_amdgcn_readfirstlane(s_first[n_slow]);
   for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
     int lo = 0, hi = n_slow;  // the sequence whose cells include this one: s_first[lo] <= item < s_first[lo + 1]

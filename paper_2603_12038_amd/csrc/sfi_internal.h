@@ -22,8 +22,13 @@ constexpr int kSlotCap = kMaxSplits + 1;  // records per (sequence, query head):
 constexpr int kArriveStride = 32;
 constexpr int kSelSeg = 2048;      // Selector positions per workgroup
 constexpr int kSelThreads = 256;
-constexpr int kHist1Bits = 12;     // first radix pass: bits [30:19] of the fp32 score
-constexpr int kHist1Bins = 1 << kHist1Bits;
+constexpr int kPickThreads = 1024;  // one workgroup selects for a pair (short J)
+constexpr int kPickMax = 16 * kPickThreads;     // longest J it takes (16 keys per thread in registers)
+constexpr int kPickLogits = 24576;  // logits of a pair up to which it also scores
+constexpr int kPriorSeg = 1024;     // positions per workgroup of the full Selector's first kernel
+constexpr int kFuseThreads = 1024;   // full Selector, second kernel: workgroup ...
+constexpr int kFuseSpan = 512;      // ... and positions (of every KV head) it takes
+constexpr int kHistBins = 512;     // bins of a segment's coarse key histogram (long J)
 constexpr int kStateWords = 8;     // per (b, h) Selector state, see SelState
 constexpr float kNeg = -1.0e30f;   // "minus infinity" that stays finite under subtraction
 constexpr float kLog2e = 1.4426950408889634f;
@@ -46,9 +51,7 @@ __device__ __forceinline__ void store_out4(float* out, int64_t elem, float4 v, b
 }
 
 // Per (sequence, KV head) Selector state words.
-enum SelState { ST_CAND = 0, ST_BIN1 = 1, ST_K1 = 2, ST_TAU = 3, ST_TAKE = 4, ST_FLAGS = 5, ST_KSEL = 6 };
-constexpr uint32_t kFlagAll = 1u;   // budget >= |J|: take every position of J
-constexpr uint32_t kFlagNone = 2u;  // nothing to select
+enum SelState { ST_CAND = 0, ST_BIN1 = 1, ST_K1 = 2 };
 
 // A window query under the causal mask (Eq. window_logits): the query sits at row q_len - 1 of a context that ends
 // at row L_end - 1, sees rows [0, q_len) only, and its evidence covers the part of the allowed set
@@ -71,14 +74,14 @@ struct Workspace {
   float* logits;      // [B*Hq][ld_pos]   J-relative positions
   uint32_t* keys;     // [B*Hkv][ld_pos]  fp32 bit pattern of the evidence f
   uint32_t* cand;     // [B*Hkv][ld_pos][2]  keys falling into the threshold bin, each with its segment
-  uint32_t* hist1;    // [B*Hkv][kHist1Bins]
+  uint32_t* hist;     // [B*Hkv][n_seg_cap][kHistBins / 2]  coarse key histogram of each segment, 16-bit counters
   uint32_t* state;    // [B*Hkv][kStateWords]
   uint32_t* segcnt;   // [B*Hkv][n_seg_cap]  keys of each segment above the threshold bin
-  int32_t* seq_splits;  // [B]  ragged step: splits per (sequence, KV head) the dense launch chose for each slow sequence
+  int32_t* slow_list;   // [4 + 4 * B]  ragged step: the slow sequences as the dense launch planned them (see SelArgs)
   float2* jstat;      // [B*Hq]  J-only softmax statistics of each query head (slow step)
   float* prior;       // [B*Hkv][ld]  full Selector: unnormalised prior pi_kn * pi_pos
-  float* znms;        // [B*Hkv][ld]  full Selector: log2-domain score after Soft-NMS
-  double* segstat;    // [B*Hkv][n_seg_cap][kSegStats]  full Selector: per-segment sums for lambda*
+  float* fbuf;        // [B*Hkv][ld]  full Selector: evidence f
+  double* segstat;    // [B*Hkv][n_seg_cap][kSegStats]  full Selector: sums for lambda* per kPriorSeg positions
   float* mu;          // [B*Hkv][ld]  windowed evidence: accumulator over the window's queries
   uint32_t* arrive;   // [B*Hkv][kWaves][kArriveStride]  workgroups of a split fast-step launch whose wave w has written its heads' records
   int32_t* guard;     // [1]  SFI_GUARD_* bits of device-side inputs the kernels found out of range and clamped
@@ -102,7 +105,7 @@ struct AttnArgs {
   int32_t item_batch;            // dense mode, ragged step: > 0 = the launch is a fixed number of workgroups that deal the
                                  //   slow sequences' cells among themselves (attn_dense_items_kernel); the batch size
   int32_t item_wgs;              //   ... and that number of workgroups
-  int32_t* seq_splits;           //   ... and where the splits chosen for each slow sequence are left, [batch]
+  int32_t* slow_list;            //   ... and where the plan is left for the Selector's launches (see SelArgs)
   const int32_t* q_len;          // dense mode, nullptr or: rows each sequence's query sees (window query under the causal mask)
   const int32_t* recent_start;   // gather mode
   const int32_t* sel_idx;        // gather mode
@@ -181,12 +184,13 @@ struct SelArgs {
   const float* logits;
   uint32_t* keys;
   uint32_t* cand;
-  uint32_t* hist1;
+  uint32_t* hist;
   uint32_t* state;
   uint32_t* segcnt;
   const int32_t* ctx_len;
   const int32_t* q_len;    // accumulation of a window query under the causal mask (see window_view), else nullptr
-  const int32_t* seq_splits;  // ragged step: splits the dense launch chose per sequence, else nullptr (n_rec)
+  const int32_t* slow_list;  // ragged step with the planned dense launch, else nullptr: [0] number of slow sequences, then
+                             //   from word 4 on { sequence, ctx_len (clamped), records per query head, 0 } for each
   int32_t ms, fs;          // strides of ctx_len (int32) and is_slow (bytes), see AttnArgs
   const uint8_t* is_slow;
   int32_t* sel_idx;
@@ -197,7 +201,7 @@ struct SelArgs {
   int32_t n_rec;           // dense records per query head (one per workgroup of the dense launch)
   // full Selector (mode 1)
   float* prior;
-  float* znms;
+  float* fbuf;
   double* segstat;
   float gamma, beta, p, eta, lambda_clip, alpha_soft, alpha_cross, inv_temp, eps;
   int32_t nms_radius;
@@ -211,7 +215,7 @@ struct SelArgs {
   // slow step in one go, mode 0: the scoring launch also merges the dense kernel's records (one more
   // workgroup per query head) and takes the J-only softmax statistics from the record headers itself
   const float* part;       // nullptr: a merge launch has run, jstat is valid
-  float* merge_out;
+  float* merge_out;        // nullptr: nothing to merge here
   int32_t len_cap;         // the clamp the dense launch applied to ctx_len
   int32_t out_bf16;        // merge_out is bf16
 };
@@ -223,12 +227,15 @@ hipError_t launch_reorg(const ReorgArgs& a, int B, int rows, hipStream_t s);
 hipError_t launch_attn_gather(const AttnArgs& a, int B, int n_slots, hipStream_t s);
 hipError_t launch_attn_gather_floor(const AttnArgs& a, int B, int n_slots, int tail, int burst, int tpw, int depth, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, int B, hipStream_t s);
-hipError_t launch_sel_score(const SelArgs& a, int B, int n_seg, hipStream_t s);
-hipError_t launch_sel_accum(const SelArgs& a, int B, int n_seg, hipStream_t s);
-hipError_t launch_sel_finalize(const SelArgs& a, int B, int n_seg, hipStream_t s);
-hipError_t launch_sel_full(const SelArgs& a, int B, int n_seg, hipStream_t s);
-hipError_t launch_sel_cand(const SelArgs& a, int B, int n_seg, hipStream_t s);
-hipError_t launch_sel_write(const SelArgs& a, int B, int n_seg, hipStream_t s);
+// nJ: upper bound of |J|; hist: with the segments' histograms (sel_cand and sel_write follow, else sel_pick)
+hipError_t launch_sel_score(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s);
+hipError_t launch_sel_accum(const SelArgs& a, int B, int nJ, hipStream_t s);
+hipError_t launch_sel_finalize(const SelArgs& a, int B, int nJ, hipStream_t s);
+hipError_t launch_sel_full(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s);
+bool sel_pick_scores(int nJ, int G);  // whether the selecting workgroup also scores (src 1)
+hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t s);  // src 0: keys, 1: logits, 2: window evidence
+hipError_t launch_sel_cand(const SelArgs& a, int B, int nJ, hipStream_t s);
+hipError_t launch_sel_write(const SelArgs& a, int B, int nJ, hipStream_t s);
 hipError_t launch_trigger(const int32_t* last_token, const uint32_t* bitmap, int vocab, int t_max, int32_t* since_slow,
                           uint8_t* is_slow, int B, hipStream_t s);
 hipError_t launch_advance(int32_t* ctx_len, int32_t* recent_start, int B, int n_sink, int recent, hipStream_t s);

@@ -16,16 +16,24 @@ static_assert(kSlotCap <= 64, "one record header per lane of a wave");
 // their merge gives the J-only softmax statistics of this head for the Selector (Eq. selector_pt),
 // stored as jstat[bg] = { M = max of y over J, Z^(-alpha) / G } with Z = sum over J of 2^(y - M): the
 // head's term of Eq. selector_mu is then p^alpha / G = (Z^(-alpha) / G) * 2^(alpha (y - M)).
+// NG > 1: the workgroup has NG groups of 256 threads, each merging a row of its own (bg per group); a group with
+// live = false goes along without storing anything.
+template <int NG = 1>
 __device__ __forceinline__ void merge_records(const float* part, float* out, int bg, int n_slots, float2* jstat,
-                                              int G, float alpha, bool out_bf16) {
+                                              int G, float alpha, bool out_bf16, bool live = true) {
   const float* P = part + (int64_t)bg * kSlotCap * kPartStride;
-  const int tid = threadIdx.x;
+  const int tid = NG == 1 ? threadIdx.x : threadIdx.x % kMergeThreads;
+  const int grp = NG == 1 ? 0 : threadIdx.x / kMergeThreads;
   const int sl = tid >> 5, c = tid & 31;
 
-  __shared__ float s_w[kSlotCap];          // 2^{m_s - M}
-  __shared__ float s_wl[kSlotCap];         // 2^{m_s - M} l_s
-  __shared__ float s_max[kMergeThreads / 64];
-  __shared__ float4 s_acc[kMergeLanes][32];
+  __shared__ float g_w[NG][kSlotCap];          // 2^{m_s - M}
+  __shared__ float g_wl[NG][kSlotCap];         // 2^{m_s - M} l_s
+  __shared__ float g_max[NG][kMergeThreads / 64];
+  __shared__ float4 g_acc[NG][kMergeLanes][32];
+  float* s_w = g_w[grp];
+  float* s_wl = g_wl[grp];
+  float* s_max = g_max[grp];
+  float4(*s_acc)[32] = g_acc[grp];
 
   // the record headers: one per thread
   float m = kNeg, l = 0.f, mj = kNeg, lj = 0.f;
@@ -93,7 +101,7 @@ __device__ __forceinline__ void merge_records(const float* part, float* out, int
       t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
     }
     const float inv = Z > 0.f ? 1.0f / Z : 0.f;
-    if (out != nullptr)  // nullptr: only the J statistics were wanted (evidence-only pass)
+    if (out != nullptr && live)  // nullptr: only the J statistics were wanted (evidence-only pass)
       store_out4(out, (int64_t)bg * kHeadDim + 4 * tid, make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv),
                  out_bf16);
   }

@@ -7,82 +7,121 @@
 //            heads of the group are the observation window; alpha = 1: f is the mean of the p_g)
 // Mode 0 ranks by f alone: z = log(f + eps) is monotone in mu, so the Top-K of Eq. topk_out is taken
 // on mu itself.  Mode 1 goes through the prior, the reverse-KL fusion with lambda*, Soft-NMS and the
-// cross-head exclusivity first (three kernels further down) and ranks by e^z_adj.
-// Top-K is a radix select on the fp32 bit pattern of the ranking value (positive floats order like
-// unsigned integers): a 12-bit histogram over all of J (stage 1, with the scoring), the keys of the
-// threshold bin collected with the segment they came from (stage 2), and, in one launch (stage 3), an
-// exact 19-bit refinement among those few keys followed by an index-ordered compaction that takes every
-// key above the threshold and the lowest-index keys equal to it.  Integer atomics only count, so the result
-// does not depend on scheduling.
+// cross-head exclusivity first (two kernels further down) and ranks by e^z_adj.
+// Top-K is a radix select on the fp32 bit pattern of the ranking value (positive floats order like unsigned integers),
+// followed by an index-ordered compaction that takes every key above the threshold and the lowest-index keys
+// equal to it.  Integer atomics only count, so the result does not depend on scheduling.
+//
+// Everything here is latency: a slow step's logits are a few MB, and what a launch costs is its chain of round trips and
+// barriers.  So the number of launches follows the size of J (launch rules in sfi_api.hip):
+//   one workgroup per pair does it all (sel_pick_kernel): from the logits where they are few, else from the keys that a
+//   scoring launch of many workgroups has left;
+//   long J: scoring with a coarse histogram per segment (stage 1), the keys of the threshold bin collected with the segment
+//   they came from (stage 2), the exact refinement among those few keys and the compaction (stage 3), a workgroup per
+//   segment each.  The segments' histograms are added up by their readers: device-scope atomics on one cache line are
+//   performed word by word, about 30 ns each, and a common histogram per pair cost a slow step 8 us (32768 positions) to
+//   25 us (131072 positions, full Selector).
+// In the kernels all loads that do not depend on another are requested together, uniform arguments at once, and
+// prefix sums and reductions over a wave run on the vector ALU (row shifts) instead of the LDS crossbar.
 #include "sfi_internal.h"
 #include "sfi_merge.h"
 
 namespace sfi {
 
 __device__ __forceinline__ float fast_exp2s(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float fast_log2s(float x) { return __builtin_amdgcn_logf(x); }
 
-// Exclusive prefix sum of one value per thread over a 256-thread block; returns the exclusive
-// prefix and leaves the block total in *total.  scratch: 8 words of LDS.
+// ---- wave and block primitives -----------------------------------------------------------------
+// Inclusive prefix sum over the 64 lanes: shifts within the rows of 16, then the row totals handed on.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+#define SFI_SCAN(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false)
+  SFI_SCAN(0x111, 0xf);  // row_shr:1
+  SFI_SCAN(0x112, 0xf);  // row_shr:2
+  SFI_SCAN(0x114, 0xf);  // row_shr:4
+  SFI_SCAN(0x118, 0xf);  // row_shr:8
+  SFI_SCAN(0x142, 0xa);  // row_bcast:15 into rows 1, 3
+  SFI_SCAN(0x143, 0xc);  // row_bcast:31 into rows 2, 3
+#undef SFI_SCAN
+  return v;
+}
+// Sum over the wave, the same in every lane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63); }
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// Maximum / sum of a float over the wave in every lane (fixed order).
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, row_move<0x128>(v));
+  v = fmaxf(v, row_move<0x124>(v));
+  v = fmaxf(v, row_move<0x122>(v));
+  v = fmaxf(v, row_move<0x121>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float wave_sum_f(float v) {
+  v += row_move<0x128>(v);
+  v += row_move<0x124>(v);
+  v += row_move<0x122>(v);
+  v += row_move<0x121>(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// The same for a double (two registers moved alike).
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double wave_sum_d(double v) {
+  v += row_move<0x128>(v);
+  v += row_move<0x124>(v);
+  v += row_move<0x122>(v);
+  v += row_move<0x121>(v);
+  uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  v = __builtin_bit_cast(double, (uint64_t)h[0] << 32 | l[0]) + __builtin_bit_cast(double, (uint64_t)h[1] << 32 | l[1]);
+  u = __builtin_bit_cast(uint64_t, v);
+  const auto l2 = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+  const auto h2 = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  return __builtin_bit_cast(double, (uint64_t)h2[0] << 32 | l2[0]) + __builtin_bit_cast(double, (uint64_t)h2[1] << 32 | l2[1]);
+}
+
+// Exclusive prefix sum of one value per thread over an NT-thread block; returns the exclusive
+// prefix and leaves the block total in *total.  scratch: NT / 64 words of LDS that nobody still reads.  One barrier.
+template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* scratch, uint32_t* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t t = __shfl_up(inc, d);
-    if (lane >= d) inc += t;
-  }
-  __syncthreads();  // scratch may still be read from a previous call
+  const uint32_t inc = wave_incl_scan(v);
   if (lane == 63) scratch[w] = inc;
   __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < kSelThreads / 64; ++i) {
-    const uint32_t s = scratch[i];
-    if (i < w) base += s;
-    tot += s;
-  }
-  *total = tot;
+  constexpr int NW = NT / 64;
+  const uint32_t t = lane < NW ? scratch[lane] : 0u;  // the waves' totals, scanned once more
+  const uint32_t ti = wave_incl_scan(t);
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)ti, NW - 1);
+  const uint32_t base = (uint32_t)__shfl((int)(ti - t), w);
   return base + inc - v;
 }
 
-// Finds, scanning bins from the highest down, the bin holding the k-th largest key (1-based k,
-// k <= total count).  Writes res[0] = bin, res[1] = how many keys of that bin are still needed.
-// hist may live in LDS or global memory; nbins is a multiple of 256.
-__device__ __forceinline__ void find_kth_desc(const uint32_t* hist, int nbins, uint32_t k, uint32_t* res,
-                                              uint32_t* scratch) {
-  const int per = nbins / kSelThreads;
-  const int hi = nbins - (int)threadIdx.x * per;  // exclusive upper bin of this thread
-  if (threadIdx.x == 0) res[0] = res[1] = 0u;      // defined result even if k exceeds the total
-  uint32_t c = 0;
-  for (int i = 1; i <= per; ++i) c += hist[hi - i];
-  uint32_t total;
-  const uint32_t above = block_excl_scan(c, scratch, &total);
-  if (above < k && k <= above + c) {
-    uint32_t cum = above;
-    for (int i = 1; i <= per; ++i) {
-      const uint32_t hv = hist[hi - i];
-      if (cum + hv >= k) {
-        res[0] = (uint32_t)(hi - i);
-        res[1] = k - cum;
-        break;
-      }
-      cum += hv;
-    }
-  }
-  __syncthreads();
-}
-
-// The same with the thread's bins already in registers: hv[i] is bin (nbins - tid * N) - 1 - i.
-template <int N>
-__device__ __forceinline__ void find_kth_desc_regs(const uint32_t (&hv)[N], int nbins, uint32_t k, uint32_t* res,
-                                                   uint32_t* scratch) {
+// Finds, scanning bins from the highest down, the bin holding the k-th largest key (1-based k, k <= total count), with the
+// thread's bins in registers: hv[i] is bin (nbins - tid * N) - 1 - i (threads past the last bin pass zeros).  Leaves
+// res[0] = bin, res[1] = how many keys of that bin are still needed; valid behind the second of its two barriers.
+template <int NT, int N>
+__device__ __forceinline__ void find_kth_desc(const uint32_t (&hv)[N], int nbins, uint32_t k, uint32_t* res, uint32_t* scratch) {
   const int hi = nbins - (int)threadIdx.x * N;
-  if (threadIdx.x == 0) res[0] = res[1] = 0u;
+  if (threadIdx.x == 0) res[0] = res[1] = 0u;  // defined result even if k exceeds the total
   uint32_t c = 0;
 #pragma unroll
   for (int i = 0; i < N; ++i) c += hv[i];
   uint32_t total;
-  const uint32_t above = block_excl_scan(c, scratch, &total);
+  const uint32_t above = block_excl_scan<NT>(c, scratch, &total);
   if (above < k && k <= above + c) {
     uint32_t cum = above;
     bool found = false;
@@ -98,663 +137,938 @@ __device__ __forceinline__ void find_kth_desc_regs(const uint32_t (&hv)[N], int 
   }
   __syncthreads();
 }
+// The same with the histogram in LDS (N bins per thread, nbins <= NT * N).
+template <int NT, int N>
+__device__ __forceinline__ void find_kth_desc_lds(const uint32_t* hist, int nbins, uint32_t k, uint32_t* res, uint32_t* scratch) {
+  uint32_t hv[N];
+  const int hi = nbins - (int)threadIdx.x * N;
+#pragma unroll
+  for (int i = 0; i < N; ++i) hv[i] = hi - 1 - i >= 0 ? hist[max(hi - 1 - i, 0)] : 0u;
+  find_kth_desc<NT, N>(hv, nbins, k, res, scratch);
+}
 
-struct Problem {
-  int nJ;        // |J|
-  uint32_t ksel; // min(budget, |J|)
+// ---- which pair a workgroup works on ---------------------------------------------------------------
+// LIST: the ragged step with the dense launch planned on the device.  That launch left the list of slow sequences, one record
+// each { sequence, ctx_len (clamped), records per query head, - }, with their number in front; workgroups with blockIdx.z =
+// r, r + gridDim.z, ... take list entries (few workgroups are launched, whatever the batch).
+// Otherwise blockIdx.z is the sequence, and what does not depend on its length can be requested before the length is there.
+struct Cell {
+  int b, bh;
+  int L_in;      // ctx_len as it was read
+  int n_rec;     // dense records per query head
 };
-
-// Stage 1 clears the pair's state words for the stages behind it (stage 3 the histogram, for the next pass).
-__device__ __forceinline__ void clear_state(const SelArgs& a, int bh) {
-  if (threadIdx.x < kStateWords) a.state[(int64_t)bh * kStateWords + threadIdx.x] = 0u;
+template <bool LIST>
+__device__ __forceinline__ int cell_count(const SelArgs& a) { return LIST ? __builtin_amdgcn_readfirstlane(a.slow_list[0]) : (int)gridDim.z; }
+template <bool LIST>
+__device__ __forceinline__ Cell cell_of(const SelArgs& a, int r) {
+  Cell c;
+  if (LIST) {
+    const int4 e = reinterpret_cast<const int4*>(a.slow_list)[1 + r];
+    c.b = __builtin_amdgcn_readfirstlane(e.x);
+    c.L_in = __builtin_amdgcn_readfirstlane(e.y);
+    c.n_rec = __builtin_amdgcn_readfirstlane(e.z);
+  } else {
+    c.b = r;
+    c.L_in = a.ctx_len[r * a.ms];
+    c.n_rec = a.n_rec;
+  }
+  c.bh = c.b * a.Hkv + (int)blockIdx.y;
+  return c;
+}
+// A sequence that does not take part (flags without a list: the ragged step's launch with a workgroup per cell).
+template <bool LIST>
+__device__ __forceinline__ bool cell_off(const SelArgs& a, const Cell& c) { return !LIST && a.is_slow != nullptr && a.is_slow[c.b * a.fs] == 0; }
+__device__ __forceinline__ int nJ_of(const SelArgs& a, const Cell& c) {
+  return max(0, min(c.L_in, a.len_cap) - a.recent - a.n_sink);  // the dense launch's clamp of ctx_len
+}
+__device__ __forceinline__ uint32_t ksel_of(const SelArgs& a, int nJ) { return (uint32_t)min(a.budget, nJ); }
+// Uniform arguments every kernel here reads, asked for at once.
+__device__ __forceinline__ void ask(const SelArgs& a) {
+  asm volatile("" ::"s"(a.slow_list), "s"(a.ctx_len), "s"(a.is_slow), "s"(a.ms), "s"(a.fs), "s"(a.Hkv), "s"(a.len_cap), "s"(a.recent),
+               "s"(a.n_sink), "s"(a.n_rec), "s"(a.ld_pos), "s"(a.keys), "s"(a.budget));
+}
+// Runs body(cell, thread index) for the workgroup's cells; a cell's LDS is free for the next behind a barrier.
+template <bool LIST, typename F>
+__device__ __forceinline__ void for_cells(const SelArgs& a, F body) {
+  if (!LIST) {
+    body(cell_of<false>(a, blockIdx.z), (int)threadIdx.x);
+    return;
+  }
+  const int n = cell_count<true>(a);
+  for (int r = blockIdx.z; r < n; r += gridDim.z) {
+    // A zero the compiler cannot see through: without it everything a body derives from the thread index is
+    // computed once in front of this loop and kept in registers across the body.
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    body(cell_of<true>(a, r), (int)threadIdx.x + zero);
+    __syncthreads();
+  }
 }
 
-__device__ __forceinline__ Problem problem_of(const SelArgs& a, int b) {
-  Problem p;
-  p.nJ = max(0, min(a.ctx_len[b * a.ms], a.len_cap) - a.recent - a.n_sink);  // the dense launch's clamp of ctx_len
-  p.ksel = (uint32_t)min(a.budget, p.nJ);
-  return p;
-}
-
-// The slow step without a merge launch (SelArgs::part != nullptr).  The launch that reads the exposed
-// logits first carries G extra workgroups per (b, h); each merges the dense kernel's records of one
-// query head into the attention output.
-// Records per query head of sequence b: one per workgroup of the dense launch (the ragged step's dense launch chooses the
-// splits per sequence on the device and leaves them in the workspace).
-__device__ __forceinline__ int n_rec_of(const SelArgs& a, int b) { return a.seq_splits != nullptr ? a.seq_splits[b] : a.n_rec; }
-__device__ __forceinline__ void merge_head(const SelArgs& a, int b, int h, int g) {
-  merge_records(a.part, a.merge_out, b * a.Hq + h * a.G + g, n_rec_of(a, b), nullptr, a.G, a.alpha, a.out_bf16 != 0);
-}
-
-// ... and every other workgroup takes the J-only softmax statistics of the group's heads from the record headers itself:
-// one wave per head, a record per lane.  sM[g] = max of y over J, sc[g] = Z^(-alpha) / G; valid after the next barrier.
-__device__ __forceinline__ void group_jstat(const SelArgs& a, int b, int h, float* sM, float* sc) {
+// J-only softmax statistics of the group's heads from the headers of the dense records (one per workgroup of the dense
+// launch): wave w takes heads w, w + n_waves, ..., a record per lane.  sM[g] = max of y over J, sc[g] = Z^(-alpha) / G;
+// valid after the next barrier.
+__device__ __forceinline__ void group_jstat(const SelArgs& a, const Cell& c, int n_waves, float* sM, float* sc) {
   const int lane = threadIdx.x & 63;
-  const int n_rec = n_rec_of(a, b);
-  for (int g = threadIdx.x >> 6; g < a.G; g += kSelThreads / 64) {
-    const float* P = a.part + (int64_t)(b * a.Hq + h * a.G + g) * kSlotCap * kPartStride;
-    const float2 ml = lane < n_rec ? *reinterpret_cast<const float2*>(P + (int64_t)lane * kPartStride + 2) : make_float2(kNeg, 0.f);
-    float M = ml.x;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
-    float Z = ml.y * fast_exp2s(ml.x - M);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) Z += __shfl_xor(Z, d);
+  for (int g = threadIdx.x >> 6; g < a.G; g += n_waves) {
+    const float* P = a.part + (int64_t)(c.bh * a.G + g) * kSlotCap * kPartStride;
+    const float2 ml = lane < c.n_rec ? *reinterpret_cast<const float2*>(P + (int64_t)lane * kPartStride + 2) : make_float2(kNeg, 0.f);
+    const float M = wave_max(ml.x);
+    const float Z = wave_sum_f(ml.y * fast_exp2s(ml.x - M));
     if (lane == 0) {
-      const float zpow = a.alpha == 1.0f ? Z : fast_exp2s(a.alpha * __builtin_amdgcn_logf(Z));
+      const float zpow = a.alpha == 1.0f ? Z : fast_exp2s(a.alpha * fast_log2s(Z));
       sM[g] = M;
       sc[g] = 1.0f / ((float)a.G * zpow);
     }
   }
 }
+// The slow step has no merge launch: the launch that reads the logits first carries extra workgroups that merge the dense
+// records of a query head into the attention output.
+__device__ __forceinline__ void merge_head(const SelArgs& a, const Cell& c, int g) {
+  merge_records(a.part, a.merge_out, c.bh * a.G + g, c.n_rec, nullptr, a.G, a.alpha, a.out_bf16 != 0);
+}
 
-// ---- stage 1: evidence f, its key, and the 12-bit histogram ------------------------------------
-// ACCUM: windowed evidence (Eq. selector_mu over several queries): instead of ranking, add this
-// query's head-mean to the accumulator mu (or start it, a.accum_first); sel_finalize_kernel ranks later.
-template <bool ACCUM>
-__global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a) {
-  const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  if (!ACCUM && seg == 0) clear_state(a, b * a.Hkv + h);
-  Problem pb = problem_of(a, b);
-  int n_all = pb.nJ;  // ACCUM under the causal mask: |J| of the whole window; pb.nJ becomes the part this query sees
-  if (ACCUM && a.q_len != nullptr) {
-    int Lq, rec;
-    window_view(a.q_len, b, min(max(a.ctx_len[b * a.ms], 0), a.len_cap), a.recent, Lq, rec);
-    pb.nJ = max(0, Lq - rec - a.n_sink);
+// Logits of (b, h): tile-major, [tile of 32 positions][rows][32], rows = the G heads (and the key norms in mode 1).
+__device__ __forceinline__ float4 logits4(const float* lg, int rows, int p, int g) {
+  return *reinterpret_cast<const float4*>(lg + (int64_t)(p >> 5) * (rows * kTile) + g * kTile + (p & 31));
+}
+__device__ __forceinline__ void add_evidence(float (&f)[4], const float4& l, float al, float M, float c) {
+  f[0] += c * fast_exp2s(al * (l.x - M));
+  f[1] += c * fast_exp2s(al * (l.y - M));
+  f[2] += c * fast_exp2s(al * (l.z - M));
+  f[3] += c * fast_exp2s(al * (l.w - M));
+}
+// mu of NQ quads of positions p[q]: sum over heads of sc[g] 2^(alpha (y_g - sM[g])) (Eq. selector_mu).  GT >= G heads are
+// loaded, all at once and without a branch; the columns past G repeat the last head with weight 0 (sM, sc hold GT entries).
+template <int NQ, int GT>
+__device__ __forceinline__ void request_logits(float4 (&lq)[NQ][GT], const float* lg, int rows, int G, const int (&p)[NQ]) {
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int g = 0; g < GT; ++g) lq[q][g] = logits4(lg, rows, p[q], min(g, G - 1));
+}
+template <int NQ, int GT>
+__device__ __forceinline__ void evidence(float (&f)[NQ][4], const float4 (&lq)[NQ][GT], float al, const float* sM, const float* sc) {
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[q][i] = 0.f;
+#pragma unroll
+  for (int g = 0; g < GT; ++g) {
+    const float M = sM[g], c = sc[g];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) add_evidence(f[q], lq[q][g], al, M, c);
   }
+}
+// The statistics of the group's heads in LDS (GT entries), from the record headers or, behind a merge launch, from jstat.
+template <int GT>
+__device__ __forceinline__ void group_stats(const SelArgs& a, const Cell& c, int n_waves, float* sM, float* sc) {
   const int tid = threadIdx.x;
-  const int bh = b * a.Hkv + h;
-  const int G = a.G;
-  const bool fused = !ACCUM && a.part != nullptr;  // grid-uniform
-  if (fused && seg >= (int)gridDim.x - G) {
-    merge_head(a, b, h, seg - ((int)gridDim.x - G));
-    return;
+  if (tid >= a.G && tid < GT) {
+    sM[tid] = 0.f;
+    sc[tid] = 0.f;
   }
-  const int p_lo = seg * kSelSeg;
-  if (ACCUM && a.accum_first && n_all > pb.nJ) {  // the first query of a window starts the accumulator: zero where it sees nothing
-    float* mu0 = a.mu + (int64_t)bh * a.ld_pos;
-    // (from the next whole quad on: the quad that straddles the edge is written by the thread that owns it)
-    for (int p = max(p_lo, (pb.nJ + 3) & ~3) + tid; p < min(p_lo + kSelSeg, n_all); p += kSelThreads) mu0[p] = 0.f;
-  }
-  if (p_lo >= pb.nJ) return;
-
-  __shared__ float s_jM[16], s_jc[16];
-  if (fused) group_jstat(a, b, h, s_jM, s_jc);
-
-  __shared__ uint32_t s_hist[kHist1Bins];
-  for (int i = tid; i < kHist1Bins; i += kSelThreads) s_hist[i] = 0u;
-
-  // logits of (b, h): tile-major, [tile of 32 positions][G heads][32].  A thread owns two quads of
-  // positions, half a segment apart; for G <= 8 all its loads are issued before any is used.
-  const int rows = a.lg_rows;  // G, or G + 1 when the dense kernel also exposed the key norms
-  const float* lg = a.logits + (int64_t)bh * rows * a.ld_pos;
-  uint32_t* keys = a.keys + (int64_t)bh * a.ld_pos;
-  constexpr int kHalf = kSelSeg / 2;
-  const int pq[2] = {p_lo + tid * 4, p_lo + kHalf + tid * 4};
-  float4 lq[2][8];
-  if (G <= 8) {
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int g = 0; g < 8; ++g)
-        lq[r][g] = (pq[r] < pb.nJ && g < G)
-                       ? *reinterpret_cast<const float4*>(lg + (int64_t)(pq[r] >> 5) * rows * kTile + g * kTile + (pq[r] & 31))
-                       : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  // J-only softmax statistics of the heads of this group, left by the merge kernel:
-  // f(j) = sum_g c_g 2^(y_g(j) - M_g) with (M_g, c_g) = jstat[head g]
-  const float al = a.alpha;  // mu(j) = sum_g sc[g] 2^(alpha (y_g(j) - sM[g]))  (Eq. selector_mu)
-  float sM[16], sc[16];
-  if (!fused) {
-#pragma unroll
-    for (int g = 0; g < 16; ++g) {
-      const float2 t = g < G ? a.jstat[b * a.Hq + h * G + g] : make_float2(0.f, 0.f);
-      sM[g] = t.x;
-      sc[g] = t.y;
-    }
-  }
-  __syncthreads();  // histogram cleared, statistics in place
-  if (fused) {
-#pragma unroll
-    for (int g = 0; g < 16; ++g) {
-      sM[g] = g < G ? s_jM[g] : 0.f;
-      sc[g] = g < G ? s_jc[g] : 0.f;
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int p = pq[r];
-    if (p >= pb.nJ) continue;
-    float f0 = 0.f, f1 = 0.f, f2 = 0.f, f3 = 0.f;
-    if (G <= 8) {
-#pragma unroll
-      for (int g = 0; g < 8; ++g) {
-        if (g < G) {
-          f0 += sc[g] * fast_exp2s(al * (lq[r][g].x - sM[g]));
-          f1 += sc[g] * fast_exp2s(al * (lq[r][g].y - sM[g]));
-          f2 += sc[g] * fast_exp2s(al * (lq[r][g].z - sM[g]));
-          f3 += sc[g] * fast_exp2s(al * (lq[r][g].w - sM[g]));
-        }
-      }
-    } else {
-      const float* lt = lg + (int64_t)(p >> 5) * rows * kTile + (p & 31);
-#pragma unroll
-      for (int g = 0; g < 16; ++g) {
-        if (g < G) {
-          const float4 l4 = *reinterpret_cast<const float4*>(lt + g * kTile);
-          f0 += sc[g] * fast_exp2s(al * (l4.x - sM[g]));
-          f1 += sc[g] * fast_exp2s(al * (l4.y - sM[g]));
-          f2 += sc[g] * fast_exp2s(al * (l4.z - sM[g]));
-          f3 += sc[g] * fast_exp2s(al * (l4.w - sM[g]));
-        }
-      }
-    }
-    if (ACCUM) {
-      float4* mp = reinterpret_cast<float4*>(a.mu + (int64_t)bh * a.ld_pos + p);
-      float4 m4 = a.accum_first ? make_float4(0.f, 0.f, 0.f, 0.f) : *mp;
-      m4.x += f0;                       // positions of the quad past the part this query sees take nothing from it
-      m4.y += p + 1 < pb.nJ ? f1 : 0.f;
-      m4.z += p + 2 < pb.nJ ? f2 : 0.f;
-      m4.w += p + 3 < pb.nJ ? f3 : 0.f;
-      *mp = m4;
-      continue;
-    }
-    const uint4 k4 = make_uint4(__float_as_uint(f0), __float_as_uint(f1), __float_as_uint(f2), __float_as_uint(f3));
-    *reinterpret_cast<uint4*>(keys + p) = k4;
-    atomicAdd(&s_hist[k4.x >> 19], 1u);
-    if (p + 1 < pb.nJ) atomicAdd(&s_hist[k4.y >> 19], 1u);
-    if (p + 2 < pb.nJ) atomicAdd(&s_hist[k4.z >> 19], 1u);
-    if (p + 3 < pb.nJ) atomicAdd(&s_hist[k4.w >> 19], 1u);
-  }
-  if (ACCUM) return;
-  __syncthreads();
-  uint32_t* gh = a.hist1 + (int64_t)bh * kHist1Bins;
-  for (int i = tid; i < kHist1Bins; i += kSelThreads) {
-    const uint32_t c = s_hist[i];
-    if (c) atomicAdd(&gh[i], c);
+  if (a.part != nullptr) {
+    group_jstat(a, c, n_waves, sM, sc);
+  } else if (tid < a.G) {
+    const float2 t = a.jstat[c.bh * a.G + tid];
+    sM[tid] = t.x;
+    sc[tid] = t.y;
   }
 }
 
-// Windowed evidence, mode 0: the accumulated mu times 1 / (number of queries added) is the ranking value.
+// The coarse histogram of a segment of kSelSeg keys: kHistBins bins of an eighth of an octave from 2^-64 up (keys outside
+// fall into the end bins), two 16-bit counters per word.
+__device__ __forceinline__ uint32_t bin_of(uint32_t key) {
+  return (uint32_t)min(max((int)(key >> 20) - (1024 - kHistBins), 0), kHistBins - 1);
+}
+__device__ __forceinline__ void hist_add4(uint32_t* s_hist, const uint32_t (&k)[4], int p, int nJ) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t bin = bin_of(k[i]);
+    if (p + i < nJ) atomicAdd(&s_hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u);
+  }
+}
+__device__ __forceinline__ uint32_t* seg_hist(const SelArgs& a, int bh, int seg) {
+  return a.hist + ((int64_t)bh * a.n_seg_cap + seg) * (kHistBins / 2);
+}
+
+// ---- scoring: evidence f and its key, a workgroup per NQ x 1024 positions ------------------------------
+// HIST: with the segment's histogram (long J, stages 2 and 3 follow; NQ = 2: a segment per workgroup).
+// ACCUM: windowed evidence (Eq. selector_mu over several queries): instead of ranking, add this
+// query's head-mean to the accumulator mu (or start it, a.accum_first).
+template <int NQ, bool HIST, bool ACCUM, bool LIST, int GT>
+__global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a) {
+  ask(a);
+  asm volatile("" ::"s"(a.logits), "s"(a.lg_rows), "s"(a.part), "s"(a.G), "s"(a.alpha), "s"(a.jstat), "s"(a.merge_out));
+  const int seg = blockIdx.x;
+  const int G = a.G, rows = a.lg_rows;
+  __shared__ float s_jM[GT], s_jc[GT];
+  __shared__ uint32_t s_hist[HIST ? kHistBins / 2 : 1];
+  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    const int p_lo = seg * (NQ * 1024);
+    const float* lg = a.logits + (int64_t)c.bh * rows * a.ld_pos;
+    int p[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) p[q] = p_lo + q * 1024 + tid * 4;
+    if (a.merge_out != nullptr && seg >= (int)gridDim.x - G) {  // workgroup-uniform
+      if (!cell_off<LIST>(a, c)) merge_head(a, c, seg - ((int)gridDim.x - G));
+      return;
+    }
+    // (rows of logits and of the accumulator are padded to whole segments: readable whatever |J| is)
+    float4 lq[NQ][GT];
+    request_logits<NQ, GT>(lq, lg, rows, G, p);
+    float4 m4[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      m4[q] = ACCUM && !a.accum_first ? *reinterpret_cast<const float4*>(a.mu + (int64_t)c.bh * a.ld_pos + p[q]) : make_float4(0.f, 0.f, 0.f, 0.f);
+    group_stats<GT>(a, c, kSelThreads / 64, s_jM, s_jc);
+    const int n_all = nJ_of(a, c);  // ACCUM under the causal mask: |J| of the whole window; nJ is the part this query sees
+    int nJ = n_all;
+    if (ACCUM && a.q_len != nullptr) {
+      int Lq, rec;
+      window_view(a.q_len, c.b, min(max(c.L_in, 0), a.len_cap), a.recent, Lq, rec);
+      nJ = max(0, Lq - rec - a.n_sink);
+    }
+    if (ACCUM && a.accum_first && n_all > nJ) {  // the first query of a window starts the accumulator: zero where it sees nothing
+      float* mu0 = a.mu + (int64_t)c.bh * a.ld_pos;
+      // (from the next whole quad on: the quad that straddles the edge is written by the thread that owns it)
+      for (int i = max(p_lo, (nJ + 3) & ~3) + tid; i < min(p_lo + NQ * 1024, n_all); i += kSelThreads) mu0[i] = 0.f;
+    }
+    if (p_lo >= nJ || cell_off<LIST>(a, c)) return;
+    static_assert(kHistBins / 2 == kSelThreads, "one word of the histogram per thread");
+    if (HIST) s_hist[tid] = 0u;
+    __syncthreads();  // histogram cleared, statistics in place
+    float f[NQ][4];
+    evidence<NQ, GT>(f, lq, a.alpha, s_jM, s_jc);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      if (p[q] >= nJ) continue;
+      if (ACCUM) {
+        float4 m = m4[q];
+        m.x += f[q][0];  // positions of the quad past the part this query sees take nothing from it
+        m.y += p[q] + 1 < nJ ? f[q][1] : 0.f;
+        m.z += p[q] + 2 < nJ ? f[q][2] : 0.f;
+        m.w += p[q] + 3 < nJ ? f[q][3] : 0.f;
+        *reinterpret_cast<float4*>(a.mu + (int64_t)c.bh * a.ld_pos + p[q]) = m;
+        continue;
+      }
+      const uint32_t k[4] = {__float_as_uint(f[q][0]), __float_as_uint(f[q][1]), __float_as_uint(f[q][2]), __float_as_uint(f[q][3])};
+      *reinterpret_cast<uint4*>(a.keys + (int64_t)c.bh * a.ld_pos + p[q]) = make_uint4(k[0], k[1], k[2], k[3]);
+      if (HIST) hist_add4(s_hist, k, p[q], nJ);
+    }
+    if (HIST) {
+      __syncthreads();
+      seg_hist(a, c.bh, seg)[tid] = s_hist[tid];
+    }
+  });
+}
+
+// Windowed evidence, mode 0, long J: the accumulated mu times 1 / (number of queries added) is the ranking value.
 __global__ __launch_bounds__(kSelThreads) void sel_finalize_kernel(const SelArgs a) {
-  const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  if (seg == 0) clear_state(a, b * a.Hkv + h);
-  const Problem pb = problem_of(a, b);
+  ask(a);
+  const int seg = blockIdx.x, tid = threadIdx.x;
+  const Cell c = cell_of<false>(a, blockIdx.z);
   const int p_lo = seg * kSelSeg;
-  if (p_lo >= pb.nJ) return;
-  const int tid = threadIdx.x;
-  const int bh = b * a.Hkv + h;
-  __shared__ uint32_t s_hist[kHist1Bins];
-  for (int i = tid; i < kHist1Bins; i += kSelThreads) s_hist[i] = 0u;
+  const int nJ = nJ_of(a, c);
+  if (p_lo >= nJ) return;
+  __shared__ uint32_t s_hist[kHistBins / 2];
+  uint32_t* keys = a.keys + (int64_t)c.bh * a.ld_pos;
+  const float* mu = a.mu + (int64_t)c.bh * a.ld_pos;
+  float4 m4[2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) m4[r] = *reinterpret_cast<const float4*>(mu + p_lo + r * (kSelSeg / 2) + tid * 4);
+  s_hist[tid] = 0u;
   __syncthreads();
-  uint32_t* keys = a.keys + (int64_t)bh * a.ld_pos;
-  const float* mu = a.mu + (int64_t)bh * a.ld_pos;
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     const int p = p_lo + r * (kSelSeg / 2) + tid * 4;
-    if (p >= pb.nJ) continue;
-    const float4 m4 = *reinterpret_cast<const float4*>(mu + p);
-    const uint4 k4 = make_uint4(__float_as_uint(m4.x * a.mu_scale), __float_as_uint(m4.y * a.mu_scale),
-                                __float_as_uint(m4.z * a.mu_scale), __float_as_uint(m4.w * a.mu_scale));
-    *reinterpret_cast<uint4*>(keys + p) = k4;
-    atomicAdd(&s_hist[k4.x >> 19], 1u);
-    if (p + 1 < pb.nJ) atomicAdd(&s_hist[k4.y >> 19], 1u);
-    if (p + 2 < pb.nJ) atomicAdd(&s_hist[k4.z >> 19], 1u);
-    if (p + 3 < pb.nJ) atomicAdd(&s_hist[k4.w >> 19], 1u);
+    if (p >= nJ) continue;
+    const uint32_t k[4] = {__float_as_uint(m4[r].x * a.mu_scale), __float_as_uint(m4[r].y * a.mu_scale),
+                           __float_as_uint(m4[r].z * a.mu_scale), __float_as_uint(m4[r].w * a.mu_scale)};
+    *reinterpret_cast<uint4*>(keys + p) = make_uint4(k[0], k[1], k[2], k[3]);
+    hist_add4(s_hist, k, p, nJ);
   }
   __syncthreads();
-  uint32_t* gh = a.hist1 + (int64_t)bh * kHist1Bins;
-  for (int i = tid; i < kHist1Bins; i += kSelThreads) {
-    const uint32_t c = s_hist[i];
-    if (c) atomicAdd(&gh[i], c);
-  }
+  seg_hist(a, c.bh, seg)[tid] = s_hist[tid];
 }
 
-// ---- full Selector (mode 1): three kernels in place of stage 1 -------------------------------------
+// ---- full Selector (mode 1): two kernels in place of the scoring --------------------------------------
 // All scores of this part live in the log2 domain, Z = log2(s + eps) = z / ln 2: Soft-NMS is
 // homogeneous of degree one in z, the head softmax of z / T is 2^(Z / T) normalised, and the
 // adjustment alpha_cross * log(r) becomes alpha_cross * log2(r); the ranking key is 2^Z_adj = e^z_adj,
-// a positive fp32 whose bit pattern orders like z_adj, so stages 2-4 are shared with mode 0.
-__device__ __forceinline__ float fast_log2s(float x) { return __builtin_amdgcn_logf(x); }
-
-// Deterministic block sums of kSegStats doubles per thread (fixed tree, one pair of barriers for all of
-// them); results valid in every thread.  scratch: [kSelThreads / 64][kSegStats] doubles of LDS.
-__device__ __forceinline__ void block_sums_f64(double (&v)[kSegStats], double (*scratch)[kSegStats]) {
-#pragma unroll
-  for (int i = 0; i < kSegStats; ++i) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v[i] += __shfl_xor(v[i], d);
-  }
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int i = 0; i < kSegStats; ++i) scratch[threadIdx.x >> 6][i] = v[i];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kSegStats; ++i) v[i] = (scratch[0][i] + scratch[1][i]) + (scratch[2][i] + scratch[3][i]);
-}
+// a positive fp32 whose bit pattern orders like z_adj, so the Top-K is shared with mode 0.
 
 // (1a) evidence f (as in mode 0) and the unnormalised prior pi_kn * pi_pos (Eqs. selector_prior_kn,
-// selector_u, selector_prior_pos) of one segment, and the segment's sums for lambda*.
+// selector_u, selector_prior_pos) of 1024 positions, and their sums for lambda*.
+// FROM_MU: windowed evidence, f from the accumulator.
+template <bool FROM_MU, bool LIST, int GT>
 __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a) {
-  const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  if (seg == 0) clear_state(a, b * a.Hkv + h);
-  const Problem pb = problem_of(a, b);
+  ask(a);
+  asm volatile("" ::"s"(a.logits), "s"(a.part), "s"(a.G), "s"(a.alpha), "s"(a.jstat), "s"(a.prior), "s"(a.segstat), "s"(a.n_seg_cap),
+               "s"(a.merge_out), "s"(a.gamma), "s"(a.beta), "s"(a.p), "s"(a.eta), "s"(a.eps));
+  const int seg = blockIdx.x;
   const int G = a.G, rows = G + 1;
-  const bool fused = a.part != nullptr;  // grid-uniform: no merge launch has run
-  if (fused && seg >= (int)gridDim.x - G) {
-    merge_head(a, b, h, seg - ((int)gridDim.x - G));
-    return;
-  }
-  const int p_lo = seg * kSelSeg;
-  if (p_lo >= pb.nJ) return;
-  const int tid = threadIdx.x;
-  const int bh = b * a.Hkv + h;
-  const float* lg = a.logits + (int64_t)bh * rows * a.ld_pos;  // [tile][G heads + key norms][32]
-  float* fbuf = reinterpret_cast<float*>(a.keys) + (int64_t)bh * a.ld_pos;
-  float* prior = a.prior + (int64_t)bh * a.ld_pos;
-  const float al = a.alpha;  // mu(j) = sum_g sc[g] 2^(alpha (y_g(j) - sM[g]))  (Eq. selector_mu)
-  __shared__ float s_jM[16], s_jc[16];
-  if (fused) {
-    group_jstat(a, b, h, s_jM, s_jc);
-    __syncthreads();
-  }
-  float sM[16], sc[16];
-#pragma unroll
-  for (int g = 0; g < 16; ++g) {
-    const float2 t = g >= G ? make_float2(0.f, 0.f) : fused ? make_float2(s_jM[g], s_jc[g]) : a.jstat[b * a.Hq + h * G + g];
-    sM[g] = t.x;
-    sc[g] = t.y;
-  }
-  // u(j) = p / D, 1 - u(j) + eps = ((|J| - 1 - p) + eps) / D + eps with D = |J| - 1 + eps: the second
-  // form keeps full relative precision near the tail, where 1 - u cancels.
-  const float D = (float)(pb.nJ - 1) + a.eps;
-  const float inv_D = 1.0f / D;
-  const float beta2 = a.beta * 1.4426950408889634f;
-  double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int p = p_lo + r * (kSelSeg / 2) + tid * 4;
-    if (p >= pb.nJ) continue;
-    const float* lt = lg + (int64_t)(p >> 5) * rows * kTile + (p & 31);
-    float f[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int g = 0; g < 16; ++g) {
-      if (g < G) {
-        const float4 l4 = *reinterpret_cast<const float4*>(lt + g * kTile);
-        f[0] += sc[g] * fast_exp2s(al * (l4.x - sM[g]));
-        f[1] += sc[g] * fast_exp2s(al * (l4.y - sM[g]));
-        f[2] += sc[g] * fast_exp2s(al * (l4.z - sM[g]));
-        f[3] += sc[g] * fast_exp2s(al * (l4.w - sM[g]));
-      }
+  __shared__ float s_jM[GT], s_jc[GT];
+  __shared__ double s_scr[kSelThreads / 64][kSegStats];
+  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    if (!FROM_MU && a.merge_out != nullptr && seg >= (int)gridDim.x - G) {
+      if (!cell_off<LIST>(a, c)) merge_head(a, c, seg - ((int)gridDim.x - G));
+      return;
     }
-    if (a.f_from_mu) {  // windowed evidence: mu was accumulated over the window's queries
-      const float4 m4 = *reinterpret_cast<const float4*>(a.mu + (int64_t)bh * a.ld_pos + p);
-      f[0] = m4.x * a.mu_scale; f[1] = m4.y * a.mu_scale; f[2] = m4.z * a.mu_scale; f[3] = m4.w * a.mu_scale;
-    }
-    if (al != 1.0f) {  // f = mu^(1/alpha) up to the normalisation done with the segment sums (Eq. selector_f)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) f[c] = fast_exp2s(a.inv_alpha * fast_log2s(f[c]));
-    }
-    const float4 k4 = *reinterpret_cast<const float4*>(lt + G * kTile);
+    const int p_lo = seg * kPriorSeg;
+    const int p[1] = {p_lo + tid * 4};
+    const float* lg = a.logits + (int64_t)c.bh * rows * a.ld_pos;  // [tile][G heads + key norms][32]
+    float4 lq[1][GT];
+    float4 m4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (FROM_MU) m4 = *reinterpret_cast<const float4*>(a.mu + (int64_t)c.bh * a.ld_pos + p[0]);
+    else request_logits<1, GT>(lq, lg, rows, G, p);
+    const float4 k4 = logits4(lg, rows, p[0], G);
+    if (!FROM_MU) group_stats<GT>(a, c, kSelThreads / 64, s_jM, s_jc);
+    const int nJ = nJ_of(a, c);
+    if (p_lo >= nJ || cell_off<LIST>(a, c)) return;
+    // (the next launch adds to the segments' histograms)
+    if (seg % (kSelSeg / kPriorSeg) == 0) seg_hist(a, c.bh, seg / (kSelSeg / kPriorSeg))[tid] = 0u;
+    // u(j) = p / D, 1 - u(j) + eps = ((|J| - 1 - p) + eps) / D + eps with D = |J| - 1 + eps: the second
+    // form keeps full relative precision near the tail, where 1 - u cancels.
+    const float D = (float)(nJ - 1) + a.eps;
+    const float inv_D = 1.0f / D;
+    const float beta2 = a.beta * 1.4426950408889634f;
     const float k2[4] = {k4.x, k4.y, k4.z, k4.w};
     float rr[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int pc = p + c;
-      const float pi_kn = fast_exp2s(-a.gamma * fast_log2s(sqrtf(k2[c]) + a.eps));
+    for (int i = 0; i < 4; ++i) {
+      const int pc = p[0] + i;
+      const float kn = -a.gamma * fast_log2s(sqrtf(k2[i]) + a.eps);  
       const float u = (float)pc * inv_D;
-      const float omu = ((float)(pb.nJ - 1 - pc) + a.eps) * inv_D + a.eps;
+      const float omu = ((float)(nJ - 1 - pc) + a.eps) * inv_D + a.eps;
       const float up = u > 0.f ? fast_exp2s(a.p * fast_log2s(u)) : 0.f;
-      const float pi_pos = fast_exp2s(-beta2 * up + a.eta * fast_log2s(omu));
-      const bool ok = pc < pb.nJ;
-      rr[c] = ok ? pi_kn * pi_pos : 0.f;
-      f[c] = ok ? f[c] : 0.f;
-      sums[0] += (double)f[c];
-      sums[1] += (double)rr[c];
-      sums[2] += (double)f[c] * (double)f[c];
-      sums[3] += (double)f[c] * (double)rr[c];
-      sums[4] += (double)rr[c] * (double)rr[c];
+      const float pos = -beta2 * up + a.eta * fast_log2s(omu);
+      rr[i] = pc < nJ ? fast_exp2s(kn) * fast_exp2s(pos) : 0.f;
     }
-    *reinterpret_cast<float4*>(fbuf + p) = make_float4(f[0], f[1], f[2], f[3]);
-    *reinterpret_cast<float4*>(prior + p) = make_float4(rr[0], rr[1], rr[2], rr[3]);
-  }
-  __shared__ double s_scr[kSelThreads / 64][kSegStats];
-  double* out = a.segstat + ((int64_t)bh * a.n_seg_cap + seg) * kSegStats;
-  block_sums_f64(sums, s_scr);
-  if (tid == 0) {
-#pragma unroll
-    for (int i = 0; i < kSegStats; ++i) out[i] = sums[i];
-  }
-}
-
-// (1b) lambda* (Eq. selector_lambda_closed) from the segment sums, the fused score (Eq. selector_closed),
-// Z = log2(s + eps) (Eq. z_base) over the segment and a halo of nms_radius positions on either side,
-// then Soft-NMS on the un-updated scores with the neighbourhood clipped to J (Eqs. nms_pool, nms).
-__global__ __launch_bounds__(kSelThreads) void sel_fuse_kernel(const SelArgs a) {
-  const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  const Problem pb = problem_of(a, b);
-  const int p_lo = seg * kSelSeg;
-  if (p_lo >= pb.nJ) return;
-  const int tid = threadIdx.x;
-  const int bh = b * a.Hkv + h;
-  const float* fbuf = reinterpret_cast<const float*>(a.keys) + (int64_t)bh * a.ld_pos;
-  const float* prior = a.prior + (int64_t)bh * a.ld_pos;
-  float* zn = a.znms + (int64_t)bh * a.ld_pos;
-  __shared__ double s_scr[kSelThreads / 64][kSegStats];
-  __shared__ float s_z[kSelSeg + 2 * kMaxNmsRadius];
-  const int n_seg = (pb.nJ + kSelSeg - 1) / kSelSeg;
-  const double* st = a.segstat + (int64_t)bh * a.n_seg_cap * kSegStats;
-  double tot[kSegStats];
-#pragma unroll
-  for (int i = 0; i < kSegStats; ++i) {
-    double v = 0.0;
-    for (int s = tid; s < n_seg; s += kSelThreads) v += st[(int64_t)s * kSegStats + i];
-    tot[i] = v;
-  }
-  block_sums_f64(tot, s_scr);
-  // f and r normalised to sum 1: |f|^2 = tot2 / F^2, f.r = tot3 / (F R), |r|^2 = tot4 / R^2
-  const double F = tot[0], Rs = tot[1];
-  const double ff = tot[2] / (F * F), fr = tot[3] / (F * Rs), rr = tot[4] / (Rs * Rs);
-  const double den = ff - 2.0 * fr + rr;
-  double lambda = den > 1e-300 ? (ff - fr) / den : 0.0;
-  lambda = fmin(fmax(lambda, 0.0), (double)a.lambda_clip);
-  const float wf = (float)((1.0 - lambda) / F), wr = (float)(lambda / Rs);
-  const int rad = a.nms_radius;
-  const int n_here = min(kSelSeg, pb.nJ - p_lo);
-  for (int i = tid; i < n_here + 2 * rad; i += kSelThreads) {
-    const int p = p_lo - rad + i;
-    s_z[i] = (p >= 0 && p < pb.nJ) ? fast_log2s(wf * fbuf[p] + wr * prior[p] + a.eps) : -INFINITY;
-  }
-  __syncthreads();
-  for (int i = tid; i < n_here; i += kSelThreads) {
-    const float z = s_z[i + rad];
-    float m = z;
-    for (int d = 0; d <= 2 * rad; ++d) m = fmaxf(m, s_z[i + d]);
-    zn[p_lo + i] = z - a.alpha_soft * fmaxf(m - z, 0.f);
-  }
-}
-
-// (1c) cross-head exclusivity at each position over the Hkv heads of the sequence (Eqs. head_softmax,
-// head_mutex), then the ranking key and the 12-bit histogram exactly as stage 1 of mode 0.
-__global__ __launch_bounds__(kSelThreads) void sel_cross_kernel(const SelArgs a) {
-  const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  const Problem pb = problem_of(a, b);
-  const int p_lo = seg * kSelSeg;
-  if (p_lo >= pb.nJ) return;
-  const int tid = threadIdx.x;
-  const int bh = b * a.Hkv + h;
-  __shared__ uint32_t s_hist[kHist1Bins];
-  for (int i = tid; i < kHist1Bins; i += kSelThreads) s_hist[i] = 0u;
-  __syncthreads();
-  const float* zb = a.znms + (int64_t)b * a.Hkv * a.ld_pos;
-  uint32_t* keys = a.keys + (int64_t)bh * a.ld_pos;
-  const float log2_eps = fast_log2s(a.eps);
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int p = p_lo + r * (kSelSeg / 2) + tid * 4;
-    if (p >= pb.nJ) continue;
-    const float4 own4 = *reinterpret_cast<const float4*>(zb + (int64_t)h * a.ld_pos + p);
-    const float own[4] = {own4.x, own4.y, own4.z, own4.w};
-    float mx[4] = {own[0], own[1], own[2], own[3]};
-    for (int hh = 0; hh < a.Hkv; ++hh) {
-      const float4 t = *reinterpret_cast<const float4*>(zb + (int64_t)hh * a.ld_pos + p);
-      mx[0] = fmaxf(mx[0], t.x); mx[1] = fmaxf(mx[1], t.y); mx[2] = fmaxf(mx[2], t.z); mx[3] = fmaxf(mx[3], t.w);
+    if (!FROM_MU) __syncthreads();
+    float f4[1][4];
+    float(&f)[4] = f4[0];
+    if (FROM_MU) {  // mu was accumulated over the window's queries
+      f[0] = m4.x * a.mu_scale; f[1] = m4.y * a.mu_scale; f[2] = m4.z * a.mu_scale; f[3] = m4.w * a.mu_scale;
+    } else {
+      evidence<1, GT>(f4, lq, a.alpha, s_jM, s_jc);
     }
-    float zs[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int hh = 0; hh < a.Hkv; ++hh) {
-      const float4 t = *reinterpret_cast<const float4*>(zb + (int64_t)hh * a.ld_pos + p);
-      zs[0] += fast_exp2s((t.x - mx[0]) * a.inv_temp);
-      zs[1] += fast_exp2s((t.y - mx[1]) * a.inv_temp);
-      zs[2] += fast_exp2s((t.z - mx[2]) * a.inv_temp);
-      zs[3] += fast_exp2s((t.w - mx[3]) * a.inv_temp);
-    }
-    uint32_t k[4];
+    if (a.alpha != 1.0f) {  // f = mu^(1/alpha) up to the normalisation done with the segment sums (Eq. selector_f)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      // log2 of the responsibility, floored at log2(eps)
-      const float lr = fmaxf((own[c] - mx[c]) * a.inv_temp - fast_log2s(zs[c]), log2_eps);
-      k[c] = __float_as_uint(fast_exp2s(own[c] + a.alpha_cross * lr));
+      for (int i = 0; i < 4; ++i) f[i] = fast_exp2s(a.inv_alpha * fast_log2s(f[i]));
     }
-    *reinterpret_cast<uint4*>(keys + p) = make_uint4(k[0], k[1], k[2], k[3]);
-    atomicAdd(&s_hist[k[0] >> 19], 1u);
-    if (p + 1 < pb.nJ) atomicAdd(&s_hist[k[1] >> 19], 1u);
-    if (p + 2 < pb.nJ) atomicAdd(&s_hist[k[2] >> 19], 1u);
-    if (p + 3 < pb.nJ) atomicAdd(&s_hist[k[3] >> 19], 1u);
-  }
-  __syncthreads();
-  uint32_t* gh = a.hist1 + (int64_t)bh * kHist1Bins;
-  for (int i = tid; i < kHist1Bins; i += kSelThreads) {
-    const uint32_t c = s_hist[i];
-    if (c) atomicAdd(&gh[i], c);
-  }
-}
-
-// ---- stage 2: find the threshold bin, collect its keys -----------------------------------------
-__global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) {
-  const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  const int p_lo = seg * kSelSeg;
-  const int tid = threadIdx.x;
-  const int bh = b * a.Hkv + h;
-  uint32_t* st = a.state + (int64_t)bh * kStateWords;
-  // Requested before ctx_len has arrived (all of it readable whatever the context is): the thread's 8
-  // consecutive keys -- the key row is padded to a whole segment, so both 16-byte loads are always in
-  // bounds -- and its 16 bins of the pair's histogram.
-  constexpr int kPer = kSelSeg / kSelThreads;
-  static_assert(kPer == 8, "two 16-byte key loads per thread");
-  const int p0 = p_lo + tid * kPer;
-  uint32_t key[kPer];
-  {
-    const uint32_t* keys = a.keys + (int64_t)bh * a.ld_pos;
-    const uint4 k0 = *reinterpret_cast<const uint4*>(keys + p0);
-    const uint4 k1 = *reinterpret_cast<const uint4*>(keys + p0 + 4);
-    key[0] = k0.x; key[1] = k0.y; key[2] = k0.z; key[3] = k0.w;
-    key[4] = k1.x; key[5] = k1.y; key[6] = k1.z; key[7] = k1.w;
-  }
-  constexpr int kBinsPer = kHist1Bins / kSelThreads;
-  uint32_t hv[kBinsPer];  // bins hi - 1, hi - 2, ... of this thread, hi = kHist1Bins - tid * kBinsPer
-  {
-    const uint4* hq = reinterpret_cast<const uint4*>(a.hist1 + (int64_t)bh * kHist1Bins + (kHist1Bins - (tid + 1) * kBinsPer));
-    static_assert(kBinsPer == 16, "four 16-byte histogram loads per thread");
+    double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint4 q4 = hq[3 - i];
-      hv[4 * i] = q4.w; hv[4 * i + 1] = q4.z; hv[4 * i + 2] = q4.y; hv[4 * i + 3] = q4.x;
+      f[i] = p[0] + i < nJ ? f[i] : 0.f;
+      const double fd = (double)f[i], rd = (double)rr[i];
+      sums[0] += fd;
+      sums[1] += rd;
+      sums[2] += fd * fd;
+      sums[3] += fd * rd;
+      sums[4] += rd * rd;
     }
-  }
-  const Problem pb = problem_of(a, b);
-  if (pb.ksel == 0 || pb.ksel == (uint32_t)pb.nJ) {
-    if (seg == 0 && tid == 0) {
-      st[ST_KSEL] = pb.ksel;
-      st[ST_FLAGS] = pb.ksel == 0 ? kFlagNone : kFlagAll;
-    }
-    return;
-  }
-  if (p_lo >= pb.nJ) return;
-
-  uint2* cand = reinterpret_cast<uint2*>(a.cand) + (int64_t)bh * a.ld_pos;  // (key, segment it came from)
-  __shared__ uint32_t s_res[2];
-  __shared__ uint32_t s_scr[8];
-  find_kth_desc_regs(hv, kHist1Bins, pb.ksel, s_res, s_scr);
-  const uint32_t bin1 = s_res[0];
-  if (seg == 0 && tid == 0) {
-    st[ST_BIN1] = bin1;
-    st[ST_K1] = s_res[1];
-    st[ST_KSEL] = pb.ksel;
-    st[ST_FLAGS] = 0u;
-  }
-  uint32_t mine = 0;  // bit i: key i falls into the threshold bin
-  uint32_t above = 0; // keys of this thread in a higher bin: selected whatever the exact threshold is
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    if (p0 + i < pb.nJ) {
-      if ((key[i] >> 19) == bin1) mine |= 1u << i;
-      above += (key[i] >> 19) > bin1;
-    }
-  }
-  // One prefix sum over the workgroup gives both the segment's count of keys above the threshold bin (for
-  // the write stage's prefix) and every thread's place in the segment's run of candidates; one atomic per
-  // workgroup reserves the run in the pair's list (one per wave made the long-context launches crawl:
-  // hundreds of atomics on one counter).
-  uint32_t total;
-  const uint32_t ex = block_excl_scan((uint32_t)__popc(mine) | (above << 16), s_scr, &total);
-  __shared__ uint32_t s_base;
-  if (tid == 0) {
-    a.segcnt[(int64_t)bh * a.n_seg_cap + seg] = total >> 16;
-    s_base = (total & 0xffffu) != 0u ? atomicAdd(&st[ST_CAND], total & 0xffffu) : 0u;
-  }
-  __syncthreads();
-  uint32_t base = s_base + (ex & 0xffffu);
-#pragma unroll
-  for (int i = 0; i < kPer; ++i)
-    if (mine & (1u << i)) cand[base++] = make_uint2(key[i], (uint32_t)seg);
-}
-
-// ---- stage 3: exact threshold among the candidates, index-ordered write of the selected set ------
-__global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a) {
-  const int seg = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  const Problem pb = problem_of(a, b);
-  const int tid = threadIdx.x;
-  const int bh = b * a.Hkv + h;
-  const uint32_t* st = a.state + (int64_t)bh * kStateWords;
-  int32_t* out = a.sel_idx + (int64_t)bh * a.budget;
-  const int n_seg = gridDim.x;
-  // padding and n_sel, spread over the segments' workgroups
-  for (int i = (int)pb.ksel + seg * kSelThreads + tid; i < a.budget; i += n_seg * kSelThreads) out[i] = -1;
-  if (seg == 0 && tid == 0) a.n_sel[bh] = (int32_t)pb.ksel;
-  {  // the histogram goes back to zero for the next pass (its readers were in the launch before)
-    uint32_t* gh = a.hist1 + (int64_t)bh * kHist1Bins;
-    for (int i = seg * kSelThreads + tid; i < kHist1Bins; i += n_seg * kSelThreads) gh[i] = 0u;
-  }
-  const int p_lo = seg * kSelSeg;
-  if (pb.ksel == 0 || p_lo >= pb.nJ) return;
-  const int p_hi = min(p_lo + kSelSeg, pb.nJ);
-  if (pb.ksel == (uint32_t)pb.nJ) {  // everything is selected
-    for (int p = p_lo + tid; p < p_hi; p += kSelThreads) out[p] = a.n_sink + p;
-    return;
-  }
-
-  __shared__ uint32_t s_h[1024];
-  __shared__ uint32_t s_res[2];
-  __shared__ uint32_t s_base[2];
-  __shared__ uint32_t s_scr[8];
-  const uint32_t bin1 = st[ST_BIN1], k1 = st[ST_K1], n_cand = st[ST_CAND];
-  const uint2* cand = reinterpret_cast<const uint2*>(a.cand) + (int64_t)bh * a.ld_pos;
-  const uint32_t* keys = a.keys + (int64_t)bh * a.ld_pos;
-  constexpr int kPer = kSelSeg / kSelThreads;  // consecutive positions per thread
-  const int p0 = p_lo + tid * kPer;
-  static_assert(kPer == 8, "two 16-byte key loads per thread");
-  uint32_t key[kPer];
-  {  // fetched while the threshold is worked out; the key row is padded to a multiple of kSelSeg, so the
-     // full 32 bytes are always readable
-    const uint4 lo4 = *reinterpret_cast<const uint4*>(keys + p0);
-    const uint4 hi4 = *reinterpret_cast<const uint4*>(keys + p0 + 4);
-    key[0] = lo4.x; key[1] = lo4.y; key[2] = lo4.z; key[3] = lo4.w;
-    key[4] = hi4.x; key[5] = hi4.y; key[6] = hi4.z; key[7] = hi4.w;
-  }
-  // Exact threshold tau and tie quota among the keys of the threshold bin (typically a few hundred):
-  // two LDS radix passes, bits [18:9] then [8:0]; every workgroup of the pair does the same.
-  for (int i = tid; i < 1024; i += kSelThreads) s_h[i] = 0u;
-  if (tid < 2) s_base[tid] = 0u;
-  __syncthreads();
-  for (uint32_t i = tid; i < n_cand; i += kSelThreads) atomicAdd(&s_h[(cand[i].x >> 9) & 1023u], 1u);
-  __syncthreads();
-  find_kth_desc(s_h, 1024, k1, s_res, s_scr);
-  const uint32_t bin2 = s_res[0], k2 = s_res[1];
-  __syncthreads();
-  for (int i = tid; i < 512; i += kSelThreads) s_h[i] = 0u;
-  __syncthreads();
-  for (uint32_t i = tid; i < n_cand; i += kSelThreads) {
-    const uint32_t key = cand[i].x;
-    if (((key >> 9) & 1023u) == bin2) atomicAdd(&s_h[key & 511u], 1u);
-  }
-  __syncthreads();
-  find_kth_desc(s_h, 512, k2, s_res, s_scr);
-  const uint32_t tau = (bin1 << 19) | (bin2 << 9) | s_res[0];
-  const uint32_t take = s_res[1];
-  {  // keys selected in the segments before this one: those above the threshold bin (counted by stage 2)
-     // plus the bin's own keys above tau; and the ties before this segment
-    uint32_t gt = 0, eq = 0;
-    for (int sg = tid; sg < seg; sg += kSelThreads) gt += a.segcnt[(int64_t)bh * a.n_seg_cap + sg];
-    for (uint32_t i = tid; i < n_cand; i += kSelThreads) {
-      const uint2 c = cand[i];
-      if ((int)c.y < seg) {
-        gt += c.x > tau;
-        eq += c.x == tau;
-      }
+    if (p[0] < nJ) {
+      *reinterpret_cast<float4*>(a.fbuf + (int64_t)c.bh * a.ld_pos + p[0]) = make_float4(f[0], f[1], f[2], f[3]);
+      *reinterpret_cast<float4*>(a.prior + (int64_t)c.bh * a.ld_pos + p[0]) = make_float4(rr[0], rr[1], rr[2], rr[3]);
     }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      gt += __shfl_xor(gt, d);
-      eq += __shfl_xor(eq, d);
-    }
+    for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
     if ((tid & 63) == 0) {
-      atomicAdd(&s_base[0], gt);
-      atomicAdd(&s_base[1], eq);
+#pragma unroll
+      for (int i = 0; i < kSegStats; ++i) s_scr[tid >> 6][i] = sums[i];
     }
-  }
-  __syncthreads();
-  const uint32_t base_gt = s_base[0], base_eq = s_base[1];
+    __syncthreads();
+    if (tid < kSegStats)
+      a.segstat[((int64_t)c.bh * a.n_seg_cap + seg) * kSegStats + tid] = (s_scr[0][tid] + s_scr[1][tid]) + (s_scr[2][tid] + s_scr[3][tid]);
+  });
+}
 
-  uint32_t cg = 0, ce = 0;
+// (1b) lambda* (Eq. selector_lambda_closed) of every KV head from its segment sums, the fused score (Eq. selector_closed),
+// Z = log2(s + eps) (Eq. z_base) over the workgroup's positions and a halo of nms_radius on either side, Soft-NMS on the
+// un-updated scores with the neighbourhood clipped to J (Eqs. nms_pool, nms), and the cross-head exclusivity at each
+// position over the Hkv heads of the sequence (Eqs. head_softmax, head_mutex), then the ranking keys.
+// A workgroup takes kFuseSpan positions of all KV heads of a sequence, eight heads at a time, so the heads' scores meet in
+// LDS and no score goes to memory in between (a launch for the fusion and one for the exclusivity, each reading all heads'
+// rows, took 27 us for a J of 131072 positions of 8 heads).  More than eight heads: the scores are worked out twice, once
+// for the head softmax's running maximum and sum, once for the keys.
+// HIST: also the heads' histograms, added to their segment's (kSelSeg / kFuseSpan workgroups share one).
+template <bool HIST, bool LIST>
+__global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a) {
+  ask(a);
+  asm volatile("" ::"s"(a.fbuf), "s"(a.prior), "s"(a.segstat), "s"(a.n_seg_cap), "s"(a.nms_radius), "s"(a.eps), "s"(a.alpha_soft),
+               "s"(a.alpha_cross), "s"(a.inv_temp), "s"(a.lambda_clip));
+  constexpr int kGroup = 8;
+  __shared__ uint32_t s_hist[HIST ? kGroup : 1][HIST ? kHistBins / 2 : 1];
+  __shared__ float s_z[kGroup][kFuseSpan + 2 * kMaxNmsRadius];
+  __shared__ float s_zn[kGroup][kFuseSpan];
+  __shared__ float s_mx[kFuseSpan], s_sum[kFuseSpan];
+  __shared__ float s_w[2][kGroup];  // weights of f and of the prior
+  const int Hkv = a.Hkv, rad = a.nms_radius;
+  const int zs = kFuseSpan + 2 * rad;
+  for_cells<LIST>(a, [&](const Cell& c, const int tid) {  // (blockIdx.y is 0: c.bh is the sequence's first pair)
+    const int lane = tid & 63, w = tid >> 6;
+    const int nJ = nJ_of(a, c);
+    const int p_lo = blockIdx.x * kFuseSpan;
+    if (p_lo >= nJ || cell_off<LIST>(a, c)) return;
+    const int n_here = min(kFuseSpan, nJ - p_lo);
+    // scores after Soft-NMS of heads h0 .. h0 + nh - 1 -> s_zn
+    auto scores = [&](int h0, int nh) {
+      const int n_seg = (nJ + kPriorSeg - 1) / kPriorSeg;
+      float fb[kGroup], pr[kGroup];  // this thread's column (position p_lo - rad + tid) of all heads, requested together
+      {
+        const int64_t o = (int64_t)(c.bh + h0) * a.ld_pos + min(max(p_lo - rad + tid, 0), nJ - 1);
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    if (p0 + i < p_hi) {
-      cg += key[i] > tau;
-      ce += key[i] == tau;
-    }
-  }
-  uint32_t total;
-  const uint32_t ex = block_excl_scan(cg | (ce << 16), s_scr, &total);
-  uint32_t gt_before = base_gt + (ex & 0xffffu);
-  uint32_t eq_before = base_eq + (ex >> 16);
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    if (p0 + i < p_hi) {
-      const bool g = key[i] > tau, e = key[i] == tau;
-      if (g || (e && eq_before < take)) {
-        const uint32_t pos = gt_before + min(eq_before, take);
-        if (pos < pb.ksel) out[pos] = a.n_sink + p0 + i;  // always true when ctx_len <= max_len held
+        for (int hh = 0; hh < kGroup; ++hh) {
+          fb[hh] = a.fbuf[o + (int64_t)min(hh, nh - 1) * a.ld_pos];
+          pr[hh] = a.prior[o + (int64_t)min(hh, nh - 1) * a.ld_pos];
+        }
       }
-      gt_before += g;
-      eq_before += e;
+      if (w < nh) {  // a wave per head: lambda* in double precision, in a fixed order
+        const double* st = a.segstat + (int64_t)(c.bh + h0 + w) * a.n_seg_cap * kSegStats;
+        double tot[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int s = lane; s < n_seg; s += 64) {
+#pragma unroll
+          for (int i = 0; i < kSegStats; ++i) tot[i] += st[(int64_t)s * kSegStats + i];
+        }
+#pragma unroll
+        for (int i = 0; i < kSegStats; ++i) tot[i] = wave_sum_d(tot[i]);
+        // f and r normalised to sum 1: |f|^2 = tot2 / F^2, f.r = tot3 / (F R), |r|^2 = tot4 / R^2
+        const double F = tot[0], Rs = tot[1];
+        const double ff = tot[2] / (F * F), fr = tot[3] / (F * Rs), rr = tot[4] / (Rs * Rs);
+        const double den = ff - 2.0 * fr + rr;
+        double lambda = den > 1e-300 ? (ff - fr) / den : 0.0;
+        lambda = fmin(fmax(lambda, 0.0), (double)a.lambda_clip);
+        if (lane == 0) {
+          s_w[0][w] = (float)((1.0 - lambda) / F);
+          s_w[1][w] = (float)(lambda / Rs);
+        }
+      }
+      __syncthreads();
+      static_assert(kFuseSpan + 2 * kMaxNmsRadius <= kFuseThreads, "a column per thread");
+      if (tid < zs) {
+        const int q = p_lo - rad + tid;
+#pragma unroll
+        for (int hh = 0; hh < kGroup; ++hh) {
+          const float z = fast_log2s(s_w[0][hh] * fb[hh] + s_w[1][hh] * pr[hh] + a.eps);
+          if (hh < nh) s_z[hh][tid] = (q >= 0 && q < nJ) ? z : -INFINITY;
+        }
+      }
+      __syncthreads();
+      for (int i = tid; i < nh * kFuseSpan; i += kFuseThreads) {
+        const int hh = i / kFuseSpan, q = i % kFuseSpan;
+        const float* zc = &s_z[hh][q];
+        const float z = zc[rad];
+        float m = z;
+        for (int d = 0; d <= 2 * rad; ++d) m = fmaxf(m, zc[d]);
+        s_zn[hh][q] = z - a.alpha_soft * fmaxf(m - z, 0.f);
+      }
+      __syncthreads();
+    };
+    // cross-head softmax at each position: maximum and sum over the heads
+    for (int h0 = 0; h0 < Hkv; h0 += kGroup) {
+      const int nh = min(kGroup, Hkv - h0);
+      scores(h0, nh);
+      for (int q = tid; q < kFuseSpan; q += kFuseThreads) {
+        float mx = s_zn[0][q];
+        for (int hh = 1; hh < nh; ++hh) mx = fmaxf(mx, s_zn[hh][q]);
+        float sum = 0.f;
+        if (h0 > 0) {
+          const float before = s_mx[q];
+          mx = fmaxf(mx, before);
+          sum = s_sum[q] * fast_exp2s((before - mx) * a.inv_temp);
+        }
+        for (int hh = 0; hh < nh; ++hh) sum += fast_exp2s((s_zn[hh][q] - mx) * a.inv_temp);
+        s_mx[q] = mx;
+        s_sum[q] = sum;
+      }
+      if (HIST && h0 == 0) {
+        for (int i = tid; i < kGroup * kHistBins / 2; i += kFuseThreads) s_hist[i / (kHistBins / 2)][i % (kHistBins / 2)] = 0u;
+      }
+      __syncthreads();
     }
-  }
+    const float log2_eps = fast_log2s(a.eps);
+    for (int h0 = 0; h0 < Hkv; h0 += kGroup) {
+      const int nh = min(kGroup, Hkv - h0);
+      if (Hkv > kGroup) scores(h0, nh);
+      for (int i = tid; i < nh * kFuseSpan; i += kFuseThreads) {
+        const int hh = i / kFuseSpan, q = i % kFuseSpan;
+        if (q < n_here) {
+          const float own = s_zn[hh][q];
+          // log2 of the responsibility, floored at log2(eps)
+          const float lr = fmaxf((own - s_mx[q]) * a.inv_temp - fast_log2s(s_sum[q]), log2_eps);
+          const uint32_t k = __float_as_uint(fast_exp2s(own + a.alpha_cross * lr));
+          a.keys[(int64_t)(c.bh + h0 + hh) * a.ld_pos + p_lo + q] = k;
+          if (HIST) {
+            const uint32_t bin = bin_of(k);
+            atomicAdd(&s_hist[hh][bin >> 1], (bin & 1u) ? 0x10000u : 1u);
+          }
+        }
+      }
+      __syncthreads();
+      if (HIST) {
+        for (int i = tid; i < nh * (kHistBins / 2); i += kFuseThreads) {
+          const int hh = i / (kHistBins / 2), wd = i % (kHistBins / 2);
+          const uint32_t v = s_hist[hh][wd];
+          if (v != 0u) {
+            s_hist[hh][wd] = 0u;  // for the next eight heads
+            atomicAdd(&seg_hist(a, c.bh + h0 + hh, p_lo / kSelSeg)[wd], v);
+          }
+        }
+        __syncthreads();
+      }
+    }
+  });
 }
 
-hipError_t launch_sel_score(const SelArgs& a, int B, int n_seg, hipStream_t s) {
+// ---- short J: one workgroup per pair selects --------------------------------------------------------
+// SRC 0: the keys a scoring launch left; 1: straight from the logits (scoring included; workgroups blockIdx.x > 0 merge the
+// dense records, four query heads each); 2: the accumulated evidence of a window.
+// A thread holds P consecutive positions in registers.  The three radix passes run on LDS histograms over all of J;
+// no list of candidates, no global histogram.
+template <int P, int SRC, bool LIST, int GT>
+__global__ __launch_bounds__(kPickThreads) void sel_pick_kernel(const SelArgs a) {
+  ask(a);
+  asm volatile("" ::"s"(a.sel_idx), "s"(a.n_sel));
+  if (SRC == 1) asm volatile("" ::"s"(a.logits), "s"(a.lg_rows), "s"(a.part), "s"(a.Hq), "s"(a.G), "s"(a.alpha), "s"(a.merge_out));
+  constexpr int NW = kPickThreads / 64;
+  __shared__ __align__(16) uint32_t s_h[4096 + 1024 + 512];
+  __shared__ uint32_t s_res[2], s_scr[4][NW];
+  __shared__ float s_jM[GT], s_jc[GT];
+  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    if (cell_off<LIST>(a, c)) return;
+    if (SRC == 1 && blockIdx.x > 0) {  // workgroup-uniform: one head per 256 threads
+      const int g = ((int)blockIdx.x - 1) * (kPickThreads / kMergeThreads) + (tid >> 8);
+      merge_records<kPickThreads / kMergeThreads>(a.part, a.merge_out, c.bh * a.G + min(g, a.G - 1), c.n_rec, nullptr, a.G, a.alpha,
+                                                  a.out_bf16 != 0, g < a.G);
+      return;
+    }
+    const int nJ = nJ_of(a, c);
+    const uint32_t ksel = ksel_of(a, nJ);
+    int32_t* out = a.sel_idx + (int64_t)c.bh * a.budget;
+    const int p0 = tid * P;
+    uint32_t key[P];
+    if (SRC == 1) {
+      constexpr int NQ = P / 4;
+      int p[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) p[q] = p0 + 4 * q;
+      const float* lg = a.logits + (int64_t)c.bh * a.lg_rows * a.ld_pos;
+      float4 lq[NQ][GT];
+      if (p0 < nJ) request_logits<NQ, GT>(lq, lg, a.lg_rows, a.G, p);
+      group_stats<GT>(a, c, NW, s_jM, s_jc);
+      for (int i = tid; i < (4096 + 1024 + 512) / 4; i += kPickThreads) reinterpret_cast<uint4*>(s_h)[i] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+      float f[NQ][4];
+      if (p0 < nJ) evidence<NQ, GT>(f, lq, a.alpha, s_jM, s_jc);
+#pragma unroll
+      for (int i = 0; i < P; ++i) key[i] = p0 + i < nJ ? __float_as_uint(f[i / 4][i % 4]) : 0u;
+    } else {
+      const uint32_t* src = (SRC == 0 ? a.keys : reinterpret_cast<const uint32_t*>(a.mu)) + (int64_t)c.bh * a.ld_pos;
+#pragma unroll
+      for (int q = 0; q < P / 4; ++q) {
+        uint4 k4 = make_uint4(0u, 0u, 0u, 0u);
+        if (p0 + 4 * q < nJ) k4 = *reinterpret_cast<const uint4*>(src + p0 + 4 * q);
+        key[4 * q] = k4.x; key[4 * q + 1] = k4.y; key[4 * q + 2] = k4.z; key[4 * q + 3] = k4.w;
+      }
+      for (int i = tid; i < (4096 + 1024 + 512) / 4; i += kPickThreads) reinterpret_cast<uint4*>(s_h)[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (SRC == 2) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) key[i] = __float_as_uint(__uint_as_float(key[i]) * a.mu_scale);
+      }
+      __syncthreads();
+    }
+    for (int i = (int)ksel + tid; i < a.budget; i += kPickThreads) out[i] = -1;
+    if (tid == 0) a.n_sel[c.bh] = (int32_t)ksel;
+    if (ksel == 0u || ksel == (uint32_t)nJ) {  // nothing, or everything
+      if (ksel != 0u)
+        for (int p = tid; p < nJ; p += kPickThreads) out[p] = a.n_sink + p;
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+      if (p0 + i < nJ) atomicAdd(&s_h[min(key[i] >> 19, 4095u)], 1u);
+    __syncthreads();
+    find_kth_desc_lds<kPickThreads, 4096 / kPickThreads>(s_h, 4096, ksel, s_res, s_scr[0]);
+    const uint32_t bin1 = s_res[0], k1 = s_res[1];
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+      if (p0 + i < nJ && (key[i] >> 19) == bin1) atomicAdd(&s_h[4096 + ((key[i] >> 9) & 1023u)], 1u);
+    __syncthreads();
+    find_kth_desc_lds<kPickThreads, 1>(s_h + 4096, 1024, k1, s_res, s_scr[1]);
+    const uint32_t top22 = bin1 << 10 | s_res[0], k2 = s_res[1];
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+      if (p0 + i < nJ && (key[i] >> 9) == top22) atomicAdd(&s_h[4096 + 1024 + (key[i] & 511u)], 1u);
+    __syncthreads();
+    find_kth_desc_lds<kPickThreads, 1>(s_h + 4096 + 1024, 512, k2, s_res, s_scr[2]);
+    const uint32_t tau = top22 << 9 | s_res[0], take = s_res[1];
+    uint32_t cg = 0, ce = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      if (p0 + i < nJ) {
+        cg += key[i] > tau;
+        ce += key[i] == tau;
+      }
+    }
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kPickThreads>(cg | ce << 16, s_scr[3], &total);  // both at most 16384
+    uint32_t gt = ex & 0xffffu, eq = ex >> 16;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      if (p0 + i < nJ) {
+        const bool g = key[i] > tau, e = key[i] == tau;
+        if (g || (e && eq < take)) {
+          const uint32_t pos = gt + min(eq, take);
+          if (pos < ksel) out[pos] = a.n_sink + p0 + i;
+        }
+        gt += g;
+        eq += e;
+      }
+    }
+  });
+}
+
+// ---- long J, stage 2: find the threshold bin, collect its keys ------------------------------------------
+template <bool LIST>
+__global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) {
+  ask(a);
+  asm volatile("" ::"s"(a.state), "s"(a.hist), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap));
+  const int seg = blockIdx.x;
+  const int p_lo = seg * kSelSeg;
+  __shared__ __align__(16) uint32_t s_cnt[kSelThreads / 64][kHistBins];
+  __shared__ uint32_t s_res[2], s_before[kSelThreads / 64], s_all[kSelThreads / 64];
+  __shared__ uint32_t s_scr[2][kSelThreads / 64];
+  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    const int lane = tid & 63, w = tid >> 6;
+    if (cell_off<LIST>(a, c)) return;
+    const int nJ = nJ_of(a, c);
+    const uint32_t ksel = ksel_of(a, nJ);
+    const int n_seg = (nJ + kSelSeg - 1) / kSelSeg;
+    if (ksel == 0u || ksel == (uint32_t)nJ || p_lo >= nJ) return;
+    // The thread's 8 consecutive keys: the key row is padded to a whole segment, so both 16-byte loads are always in
+    // bounds.  Then the pair's histogram: wave w adds up segments w, w + 4, ..., a lane four words (eight bins) of each.
+    constexpr int kPer = kSelSeg / kSelThreads;
+    static_assert(kPer == 8, "two 16-byte key loads per thread");
+    const int p0 = p_lo + tid * kPer;
+    uint32_t key[kPer];
+    {
+      const uint32_t* keys = a.keys + (int64_t)c.bh * a.ld_pos;
+      const uint4 k0 = *reinterpret_cast<const uint4*>(keys + p0);
+      const uint4 k1 = *reinterpret_cast<const uint4*>(keys + p0 + 4);
+      key[0] = k0.x; key[1] = k0.y; key[2] = k0.z; key[3] = k0.w;
+      key[4] = k1.x; key[5] = k1.y; key[6] = k1.z; key[7] = k1.w;
+    }
+    uint32_t cnt[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+    static_assert(kHistBins == 8 * 64, "eight bins per lane");
+#pragma unroll 4
+    for (int sg = w; sg < n_seg; sg += kSelThreads / 64) {
+      const uint4 q = reinterpret_cast<const uint4*>(seg_hist(a, c.bh, sg))[lane];
+      cnt[0] += q.x & 0xffffu; cnt[1] += q.x >> 16; cnt[2] += q.y & 0xffffu; cnt[3] += q.y >> 16;
+      cnt[4] += q.z & 0xffffu; cnt[5] += q.z >> 16; cnt[6] += q.w & 0xffffu; cnt[7] += q.w >> 16;
+    }
+    *reinterpret_cast<uint4*>(&s_cnt[w][8 * lane]) = make_uint4(cnt[0], cnt[1], cnt[2], cnt[3]);
+    *reinterpret_cast<uint4*>(&s_cnt[w][8 * lane + 4]) = make_uint4(cnt[4], cnt[5], cnt[6], cnt[7]);
+    __syncthreads();
+    uint32_t hv[2];  // bins kHistBins - 1 - 2 tid and the one below
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int bin = kHistBins - 1 - 2 * tid - i;
+      hv[i] = s_cnt[0][bin] + s_cnt[1][bin] + s_cnt[2][bin] + s_cnt[3][bin];
+    }
+    uint32_t* st = a.state + (int64_t)c.bh * kStateWords;
+    uint2* cand = reinterpret_cast<uint2*>(a.cand) + (int64_t)c.bh * a.ld_pos;  // (key, segment it came from)
+    find_kth_desc<kSelThreads, 2>(hv, kHistBins, ksel, s_res, s_scr[0]);
+    const uint32_t bin1 = s_res[0];
+    // candidates of the segments before this one: where this segment's run starts in the pair's list
+    uint32_t before = 0, all = 0;
+    for (int sg = tid; sg < n_seg; sg += kSelThreads) {
+      const uint32_t v = seg_hist(a, c.bh, sg)[bin1 >> 1];
+      const uint32_t x = (bin1 & 1u) ? v >> 16 : v & 0xffffu;
+      all += x;
+      before += sg < seg ? x : 0u;
+    }
+    before = wave_sum(before);
+    all = wave_sum(all);
+    if (lane == 0) {
+      s_before[w] = before;
+      s_all[w] = all;
+    }
+    uint32_t mine = 0;  // bit i: key i falls into the threshold bin
+    uint32_t above = 0; // keys of this thread in a higher bin: selected whatever the exact threshold is
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (p0 + i < nJ) {
+        const uint32_t bin = bin_of(key[i]);
+        if (bin == bin1) mine |= 1u << i;
+        above += bin > bin1;
+      }
+    }
+    // One prefix sum over the workgroup gives both the segment's count of keys above the threshold bin (for
+    // the write stage's prefix) and every thread's place in the segment's run of candidates.
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kSelThreads>((uint32_t)__popc(mine) | (above << 16), s_scr[1], &total);  // (its barrier covers s_before)
+    if (tid == 0) {
+      a.segcnt[(int64_t)c.bh * a.n_seg_cap + seg] = total >> 16;
+      if (seg == 0)
+        *reinterpret_cast<uint4*>(st) = make_uint4(s_all[0] + s_all[1] + s_all[2] + s_all[3], bin1, s_res[1], 0u);
+    }
+    uint32_t base = s_before[0] + s_before[1] + s_before[2] + s_before[3] + (ex & 0xffffu);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (mine & (1u << i)) cand[base++] = make_uint2(key[i], (uint32_t)seg);
+  });
+}
+
+// ---- long J, stage 3: exact threshold among the candidates, index-ordered write of the selected set -------
+template <bool LIST>
+__global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a) {
+  ask(a);
+  asm volatile("" ::"s"(a.state), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap), "s"(a.sel_idx), "s"(a.n_sel));
+  const int seg = blockIdx.x;
+  const int n_seg = gridDim.x;
+  __shared__ __align__(16) uint32_t s_h[2048 + 1024 + 1024];
+  __shared__ uint32_t s_res[2], s_gt[kSelThreads / 64], s_eq[kSelThreads / 64];
+  __shared__ uint32_t s_scr[4][kSelThreads / 64];
+  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    if (cell_off<LIST>(a, c)) return;
+    const int nJ = nJ_of(a, c);
+    const uint32_t ksel = ksel_of(a, nJ);
+    const int p_lo = seg * kSelSeg;
+    constexpr int kPer = kSelSeg / kSelThreads;  // consecutive positions per thread
+    static_assert(kPer == 8, "two 16-byte key loads per thread");
+    const int p0 = p_lo + tid * kPer;
+    const int64_t bh = c.bh;
+    // Requested together: the state words, the thread's keys (the key row is padded to whole segments), the counts of the
+    // segments before this one, and the first kSpec candidates per thread, whether or not there are so many.
+    constexpr int kSpec = 4;
+    const uint4 st4 = *reinterpret_cast<const uint4*>(a.state + bh * kStateWords);
+    const uint2* cand = reinterpret_cast<const uint2*>(a.cand) + bh * a.ld_pos;
+    uint2 cd[kSpec];
+#pragma unroll
+    for (int i = 0; i < kSpec; ++i) cd[i] = cand[tid + i * kSelThreads];
+    uint32_t key[kPer];
+    {
+      const uint32_t* keys = a.keys + bh * a.ld_pos;
+      const uint4 lo4 = *reinterpret_cast<const uint4*>(keys + p0);
+      const uint4 hi4 = *reinterpret_cast<const uint4*>(keys + p0 + 4);
+      key[0] = lo4.x; key[1] = lo4.y; key[2] = lo4.z; key[3] = lo4.w;
+      key[4] = hi4.x; key[5] = hi4.y; key[6] = hi4.z; key[7] = hi4.w;
+    }
+    uint32_t gt = 0, eq = 0;
+    for (int sg = tid; sg < seg; sg += kSelThreads) gt += a.segcnt[bh * a.n_seg_cap + sg];
+    int32_t* out = a.sel_idx + bh * a.budget;
+    // padding and n_sel, spread over the segments' workgroups
+    for (int i = (int)ksel + seg * kSelThreads + tid; i < a.budget; i += n_seg * kSelThreads) out[i] = -1;
+    if (seg == 0 && tid == 0) a.n_sel[bh] = (int32_t)ksel;
+    if (ksel == 0u || p_lo >= nJ) return;
+    const int p_hi = min(p_lo + kSelSeg, nJ);
+    if (ksel == (uint32_t)nJ) {  // everything is selected
+      for (int p = p_lo + tid; p < p_hi; p += kSelThreads) out[p] = a.n_sink + p;
+      return;
+    }
+    // Exact threshold tau and tie quota among the keys of the threshold bin (typically a few hundred): two LDS radix
+    // passes, bits [19:10] then [9:0]; every workgroup of the pair does the same.  The end bins of the histogram
+    // hold keys of any magnitude: a pass over bits [30:20] comes first.
+    const uint32_t n_cand = st4.x, bin1 = st4.y;
+    uint32_t k_left = st4.z, prefix = bin1 + (1024 - kHistBins);  // bits [30:20] of the threshold
+    static_assert(ST_CAND == 0 && ST_BIN1 == 1 && ST_K1 == 2, "one 16-byte load");
+    const bool end_bin = bin1 == 0u || bin1 == (uint32_t)kHistBins - 1u;
+    for (int i = tid; i < (2048 + 1024 + 1024) / 4; i += kSelThreads) reinterpret_cast<uint4*>(s_h)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    auto each_candidate = [&](auto f) {
+#pragma unroll
+      for (int i = 0; i < kSpec; ++i)
+        if (tid + i * kSelThreads < n_cand) f(cd[i]);
+      for (uint32_t i = tid + kSpec * kSelThreads; i < n_cand; i += kSelThreads) f(cand[i]);
+    };
+    if (end_bin) {  // uniform over the pair
+      each_candidate([&](const uint2& x) { atomicAdd(&s_h[2048 + ((x.x >> 20) & 2047u)], 1u); });
+      __syncthreads();
+      find_kth_desc_lds<kSelThreads, 8>(s_h + 2048, 2048, k_left, s_res, s_scr[3]);
+      prefix = s_res[0];
+      k_left = s_res[1];
+      for (int i = tid; i < 1024 / 4; i += kSelThreads) reinterpret_cast<uint4*>(s_h + 2048)[i] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+    }
+    each_candidate([&](const uint2& x) {
+      if ((x.x >> 20) == prefix) atomicAdd(&s_h[(x.x >> 10) & 1023u], 1u);
+    });
+    __syncthreads();
+    find_kth_desc_lds<kSelThreads, 4>(s_h, 1024, k_left, s_res, s_scr[0]);
+    const uint32_t top21 = prefix << 10 | s_res[0], k2 = s_res[1];
+    each_candidate([&](const uint2& x) {
+      if ((x.x >> 10) == top21) atomicAdd(&s_h[1024 + (x.x & 1023u)], 1u);
+    });
+    __syncthreads();
+    find_kth_desc_lds<kSelThreads, 4>(s_h + 1024, 1024, k2, s_res, s_scr[1]);
+    const uint32_t tau = top21 << 10 | s_res[0];
+    const uint32_t take = s_res[1];
+    // keys selected in the segments before this one: those above the threshold bin (counted by stage 2)
+    // plus the bin's own keys above tau; and the ties before this segment
+    each_candidate([&](const uint2& x) {
+      if ((int)x.y < seg) {
+        gt += x.x > tau;
+        eq += x.x == tau;
+      }
+    });
+    gt = wave_sum(gt);
+    eq = wave_sum(eq);
+    if ((tid & 63) == 0) {
+      s_gt[tid >> 6] = gt;
+      s_eq[tid >> 6] = eq;
+    }
+    uint32_t cg = 0, ce = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (p0 + i < p_hi) {
+        cg += key[i] > tau;
+        ce += key[i] == tau;
+      }
+    }
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kSelThreads>(cg | (ce << 16), s_scr[2], &total);  // (its barrier covers s_gt, s_eq)
+    uint32_t gt_before = s_gt[0] + s_gt[1] + s_gt[2] + s_gt[3] + (ex & 0xffffu);
+    uint32_t eq_before = s_eq[0] + s_eq[1] + s_eq[2] + s_eq[3] + (ex >> 16);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (p0 + i < p_hi) {
+        const bool g = key[i] > tau, e = key[i] == tau;
+        if (g || (e && eq_before < take)) {
+          const uint32_t pos = gt_before + min(eq_before, take);
+          if (pos < ksel) out[pos] = a.n_sink + p0 + i;  // always true when ctx_len <= max_len held
+        }
+        gt_before += g;
+        eq_before += e;
+      }
+    }
+  });
+}
+
+// ---- launches -------------------------------------------------------------------------------------------
+// Workgroups along z: one per sequence, or, where the slow sequences come as a list, enough for a few of them (n_wgs
+// workgroups per list entry and launch).
+static unsigned z_of(const SelArgs& a, int B, int n_wgs) {
+  if (a.slow_list == nullptr) return (unsigned)B;
+  const int z = 1024 / (n_wgs < 1 ? 1 : n_wgs);
+  return (unsigned)(z < 1 ? 1 : z > B ? B : z);
+}
+static int ceil_seg(int nJ, int per) { return nJ > 0 ? (nJ + per - 1) / per : 1; }
+// Head counts the scoring kernels are built for: the smallest that holds G.
+template <int NQ, bool HIST, bool ACCUM, bool LIST>
+static void launch_score_t(const SelArgs& a, dim3 grid, hipStream_t s) {
+  const dim3 block(kSelThreads);
+  if (a.G <= 1) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 1>), grid, block, 0, s, a);
+  else if (a.G <= 2) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 2>), grid, block, 0, s, a);
+  else if (a.G <= 4) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 4>), grid, block, 0, s, a);
+  else if (a.G <= 5) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 5>), grid, block, 0, s, a);
+  else if (a.G <= 8) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 8>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 16>), grid, block, 0, s, a);
+}
+hipError_t launch_sel_score(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s) {
   // with the merge on board: one more workgroup per query head
-  hipLaunchKernelGGL(sel_score_kernel<false>, dim3(n_seg + (a.part != nullptr ? a.G : 0), a.Hkv, B), dim3(kSelThreads), 0, s, a);
+  const int n_seg = ceil_seg(nJ, hist ? kSelSeg : 1024) + (a.merge_out != nullptr ? a.G : 0);
+  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
+  if (a.slow_list != nullptr) {
+    if (hist) launch_score_t<2, true, false, true>(a, grid, s);
+    else launch_score_t<1, false, false, true>(a, grid, s);
+  } else {
+    if (hist) launch_score_t<2, true, false, false>(a, grid, s);
+    else launch_score_t<1, false, false, false>(a, grid, s);
+  }
   return hipGetLastError();
 }
-hipError_t launch_sel_accum(const SelArgs& a, int B, int n_seg, hipStream_t s) {
-  hipLaunchKernelGGL(sel_score_kernel<true>, dim3(n_seg, a.Hkv, B), dim3(kSelThreads), 0, s, a);
+hipError_t launch_sel_accum(const SelArgs& a, int B, int nJ, hipStream_t s) {
+  launch_score_t<1, false, true, false>(a, dim3(ceil_seg(nJ, 1024) + (a.merge_out != nullptr ? a.G : 0), a.Hkv, B), s);
   return hipGetLastError();
 }
-hipError_t launch_sel_finalize(const SelArgs& a, int B, int n_seg, hipStream_t s) {
-  hipLaunchKernelGGL(sel_finalize_kernel, dim3(n_seg, a.Hkv, B), dim3(kSelThreads), 0, s, a);
+hipError_t launch_sel_finalize(const SelArgs& a, int B, int nJ, hipStream_t s) {
+  hipLaunchKernelGGL(sel_finalize_kernel, dim3(ceil_seg(nJ, kSelSeg), a.Hkv, B), dim3(kSelThreads), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_sel_full(const SelArgs& a, int B, int n_seg, hipStream_t s) {
-  hipLaunchKernelGGL(sel_prior_kernel, dim3(n_seg + (a.part != nullptr ? a.G : 0), a.Hkv, B), dim3(kSelThreads), 0, s, a);
-  hipLaunchKernelGGL(sel_fuse_kernel, dim3(n_seg, a.Hkv, B), dim3(kSelThreads), 0, s, a);
-  hipLaunchKernelGGL(sel_cross_kernel, dim3(n_seg, a.Hkv, B), dim3(kSelThreads), 0, s, a);
+template <bool FROM_MU, bool LIST>
+static void launch_prior_t(const SelArgs& a, dim3 grid, hipStream_t s) {
+  const dim3 block(kSelThreads);
+  if (FROM_MU || a.G <= 1) hipLaunchKernelGGL((sel_prior_kernel<FROM_MU, LIST, 1>), grid, block, 0, s, a);
+  else if (a.G <= 2) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 2>), grid, block, 0, s, a);
+  else if (a.G <= 4) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 4>), grid, block, 0, s, a);
+  else if (a.G <= 5) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 5>), grid, block, 0, s, a);
+  else if (a.G <= 8) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 8>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 16>), grid, block, 0, s, a);
+}
+hipError_t launch_sel_full(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s) {
+  const int n_seg = ceil_seg(nJ, kPriorSeg) + (a.merge_out != nullptr ? a.G : 0);
+  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
+  if (a.f_from_mu) launch_prior_t<true, false>(a, grid, s);  // (a window's evidence is never ranked in the ragged step)
+  else if (a.slow_list != nullptr) launch_prior_t<false, true>(a, grid, s);
+  else launch_prior_t<false, false>(a, grid, s);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int n_span = ceil_seg(nJ, kFuseSpan);
+  const dim3 fgrid(n_span, 1, z_of(a, B, n_span)), fblock(kFuseThreads);
+  if (a.slow_list != nullptr) {
+    if (hist) hipLaunchKernelGGL((sel_fuse_kernel<true, true>), fgrid, fblock, 0, s, a);
+    else hipLaunchKernelGGL((sel_fuse_kernel<false, true>), fgrid, fblock, 0, s, a);
+  } else {
+    if (hist) hipLaunchKernelGGL((sel_fuse_kernel<true, false>), fgrid, fblock, 0, s, a);
+    else hipLaunchKernelGGL((sel_fuse_kernel<false, false>), fgrid, fblock, 0, s, a);
+  }
   return hipGetLastError();
 }
-hipError_t launch_sel_cand(const SelArgs& a, int B, int n_seg, hipStream_t s) {
-  hipLaunchKernelGGL(sel_cand_kernel, dim3(n_seg, a.Hkv, B), dim3(kSelThreads), 0, s, a);
+template <int P, bool LIST>
+static void launch_pick_logits_t(const SelArgs& a, dim3 grid, hipStream_t s) {
+  const dim3 block(kPickThreads);
+  if (a.G <= 1) hipLaunchKernelGGL((sel_pick_kernel<P, 1, LIST, 1>), grid, block, 0, s, a);
+  else if (a.G <= 2) hipLaunchKernelGGL((sel_pick_kernel<P, 1, LIST, 2>), grid, block, 0, s, a);
+  else if (a.G <= 4) hipLaunchKernelGGL((sel_pick_kernel<P, 1, LIST, 4>), grid, block, 0, s, a);
+  else if (P == 8 || a.G <= 5) hipLaunchKernelGGL((sel_pick_kernel<P, 1, LIST, 5>), grid, block, 0, s, a);
+  else if (a.G <= 8) hipLaunchKernelGGL((sel_pick_kernel<4, 1, LIST, 8>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sel_pick_kernel<4, 1, LIST, 16>), grid, block, 0, s, a);
+}
+template <int SRC, bool LIST>
+static void launch_pick_keys_t(const SelArgs& a, int nJ, dim3 grid, hipStream_t s) {
+  const dim3 block(kPickThreads);
+  if (nJ <= 4 * kPickThreads) hipLaunchKernelGGL((sel_pick_kernel<4, SRC, LIST, 1>), grid, block, 0, s, a);
+  else if (nJ <= 8 * kPickThreads) hipLaunchKernelGGL((sel_pick_kernel<8, SRC, LIST, 1>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sel_pick_kernel<16, SRC, LIST, 1>), grid, block, 0, s, a);
+}
+bool sel_pick_scores(int nJ, int G) {  // more than 4096 positions leave room for the logits of five heads in registers
+  return (int64_t)nJ * G <= kPickLogits && nJ <= (G <= 5 ? 8 : 4) * kPickThreads;
+}
+hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t s) {
+  const int per_wg = kPickThreads / kMergeThreads;
+  const int extra = src == 1 ? (a.G + per_wg - 1) / per_wg : 0;
+  const dim3 grid(1 + extra, a.Hkv, z_of(a, B, (1 + extra) * a.Hkv * 4));
+  const bool list = a.slow_list != nullptr;
+  if (src == 1) {
+    if (nJ <= 4 * kPickThreads) {
+      if (list) launch_pick_logits_t<4, true>(a, grid, s);
+      else launch_pick_logits_t<4, false>(a, grid, s);
+    } else {
+      if (list) launch_pick_logits_t<8, true>(a, grid, s);
+      else launch_pick_logits_t<8, false>(a, grid, s);
+    }
+  } else if (src == 2) {
+    launch_pick_keys_t<2, false>(a, nJ, grid, s);
+  } else {
+    if (list) launch_pick_keys_t<0, true>(a, nJ, grid, s);
+    else launch_pick_keys_t<0, false>(a, nJ, grid, s);
+  }
   return hipGetLastError();
 }
-hipError_t launch_sel_write(const SelArgs& a, int B, int n_seg, hipStream_t s) {
-  hipLaunchKernelGGL(sel_write_kernel, dim3(n_seg, a.Hkv, B), dim3(kSelThreads), 0, s, a);
+hipError_t launch_sel_cand(const SelArgs& a, int B, int nJ, hipStream_t s) {
+  const int n_seg = ceil_seg(nJ, kSelSeg);
+  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
+  if (a.slow_list != nullptr) hipLaunchKernelGGL(sel_cand_kernel<true>, grid, dim3(kSelThreads), 0, s, a);
+  else hipLaunchKernelGGL(sel_cand_kernel<false>, grid, dim3(kSelThreads), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t launch_sel_write(const SelArgs& a, int B, int nJ, hipStream_t s) {
+  const int n_seg = ceil_seg(nJ, kSelSeg);
+  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
+  if (a.slow_list != nullptr) hipLaunchKernelGGL(sel_write_kernel<true>, grid, dim3(kSelThreads), 0, s, a);
+  else hipLaunchKernelGGL(sel_write_kernel<false>, grid, dim3(kSelThreads), 0, s, a);
   return hipGetLastError();
 }
 
