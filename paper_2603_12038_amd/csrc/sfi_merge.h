@@ -4,6 +4,31 @@
 
 namespace sfi {
 
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// Maximum / sum of a float over the wave in every lane (fixed order).
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, row_move<0x128>(v));
+  v = fmaxf(v, row_move<0x124>(v));
+  v = fmaxf(v, row_move<0x122>(v));
+  v = fmaxf(v, row_move<0x121>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float wave_sum_f(float v) {
+  v += row_move<0x128>(v);
+  v += row_move<0x124>(v);
+  v += row_move<0x122>(v);
+  v += row_move<0x121>(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 constexpr int kMergeThreads = 256;
 constexpr int kMergeLanes = 8;
 static_assert(kSlotCap <= 64, "one record header per lane of a wave");
@@ -59,12 +84,9 @@ __device__ __forceinline__ void merge_records(const float* part, float* out, int
   if (jstat != nullptr) {  // block-uniform
     // (a wave holds all record headers: kSlotCap <= 64)
     if (tid < 64) {
-      float MJ = mj;
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) MJ = fmaxf(MJ, __shfl_xor(MJ, d));
-      float Z = tid < n_slots ? lj * __builtin_amdgcn_exp2f(mj - MJ) : 0.f;
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) Z += __shfl_xor(Z, d);
+      // (the Selector's launches take the same statistics from the headers themselves: same order of operations)
+      const float MJ = wave_max(mj);
+      const float Z = wave_sum_f(lj * __builtin_amdgcn_exp2f(mj - MJ));
       const float zpow = alpha == 1.0f ? Z : __builtin_amdgcn_exp2f(alpha * __builtin_amdgcn_logf(Z));
       if (tid == 0) jstat[bg] = make_float2(MJ, 1.0f / ((float)G * zpow));
     }

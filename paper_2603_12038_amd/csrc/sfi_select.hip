@@ -46,31 +46,6 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
 }
 // Sum over the wave, the same in every lane.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63); }
-template <int CTRL>
-__device__ __forceinline__ float row_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-// Maximum / sum of a float over the wave in every lane (fixed order).
-__device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, row_move<0x128>(v));
-  v = fmaxf(v, row_move<0x124>(v));
-  v = fmaxf(v, row_move<0x122>(v));
-  v = fmaxf(v, row_move<0x121>(v));
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float wave_sum_f(float v) {
-  v += row_move<0x128>(v);
-  v += row_move<0x124>(v);
-  v += row_move<0x122>(v);
-  v += row_move<0x121>(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
 // The same for a double (two registers moved alike).
 template <int CTRL>
 __device__ __forceinline__ double row_move(double v) {
@@ -501,8 +476,8 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
                "s"(a.alpha_cross), "s"(a.inv_temp), "s"(a.lambda_clip));
   constexpr int kGroup = 8;
   __shared__ uint32_t s_hist[HIST ? kGroup : 1][HIST ? kHistBins / 2 : 1];
-  __shared__ float s_z[kGroup][kFuseSpan + 2 * kMaxNmsRadius];
-  __shared__ float s_zn[kGroup][kFuseSpan];
+  __shared__ __align__(16) float s_z[kGroup][kFuseSpan + 2 * kMaxNmsRadius];
+  __shared__ __align__(16) float s_zn[kGroup][kFuseSpan];
   __shared__ float s_mx[kFuseSpan], s_sum[kFuseSpan];
   __shared__ float s_w[2][kGroup];  // weights of f and of the prior
   const int Hkv = a.Hkv, rad = a.nms_radius;
@@ -528,21 +503,27 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
       if (w < nh) {  // a wave per head: lambda* in double precision, in a fixed order
         const double* st = a.segstat + (int64_t)(c.bh + h0 + w) * a.n_seg_cap * kSegStats;
         double tot[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        for (int s = lane; s < n_seg; s += 64) {
+        for (int s0 = lane; s0 - lane < n_seg; s0 += 128) {  // two segments' sums in flight per lane
+          double t0[kSegStats], t1[kSegStats];
 #pragma unroll
-          for (int i = 0; i < kSegStats; ++i) tot[i] += st[(int64_t)s * kSegStats + i];
+          for (int i = 0; i < kSegStats; ++i) {
+            t0[i] = st[(int64_t)min(s0, n_seg - 1) * kSegStats + i];
+            t1[i] = st[(int64_t)min(s0 + 64, n_seg - 1) * kSegStats + i];
+          }
+#pragma unroll
+          for (int i = 0; i < kSegStats; ++i) tot[i] += (s0 < n_seg ? t0[i] : 0.0) + (s0 + 64 < n_seg ? t1[i] : 0.0);
         }
 #pragma unroll
         for (int i = 0; i < kSegStats; ++i) tot[i] = wave_sum_d(tot[i]);
         // f and r normalised to sum 1: |f|^2 = tot2 / F^2, f.r = tot3 / (F R), |r|^2 = tot4 / R^2
-        const double F = tot[0], Rs = tot[1];
-        const double ff = tot[2] / (F * F), fr = tot[3] / (F * Rs), rr = tot[4] / (Rs * Rs);
+        const double iF = 1.0 / tot[0], iR = 1.0 / tot[1];
+        const double ff = tot[2] * iF * iF, fr = tot[3] * iF * iR, rr = tot[4] * iR * iR;
         const double den = ff - 2.0 * fr + rr;
         double lambda = den > 1e-300 ? (ff - fr) / den : 0.0;
         lambda = fmin(fmax(lambda, 0.0), (double)a.lambda_clip);
         if (lane == 0) {
-          s_w[0][w] = (float)((1.0 - lambda) / F);
-          s_w[1][w] = (float)(lambda / Rs);
+          s_w[0][w] = (float)((1.0 - lambda) * iF);
+          s_w[1][w] = (float)(lambda * iR);
         }
       }
       __syncthreads();
@@ -556,13 +537,29 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
         }
       }
       __syncthreads();
-      for (int i = tid; i < nh * kFuseSpan; i += kFuseThreads) {
-        const int hh = i / kFuseSpan, q = i % kFuseSpan;
-        const float* zc = &s_z[hh][q];
-        const float z = zc[rad];
-        float m = z;
-        for (int d = 0; d <= 2 * rad; ++d) m = fmaxf(m, zc[d]);
-        s_zn[hh][q] = z - a.alpha_soft * fmaxf(m - z, 0.f);
+      static_assert(kGroup * kFuseSpan == 4 * kFuseThreads, "four consecutive positions per thread");
+      {
+        const int hh = tid / (kFuseSpan / 4), q0 = 4 * (tid % (kFuseSpan / 4));
+        const float* zc = &s_z[hh][q0];  // window of output o: zc[o .. o + 2 rad]
+        if (hh < nh) {
+          float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+          for (int e0 = 0; e0 < 2 * rad + 4; e0 += 4) {
+            const float4 v4 = *reinterpret_cast<const float4*>(zc + e0);
+            const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+              for (int o = 0; o < 4; ++o)
+                if (e0 + k >= o && e0 + k <= o + 2 * rad) m[o] = fmaxf(m[o], v[k]);
+          }
+          float zn[4];
+#pragma unroll
+          for (int o = 0; o < 4; ++o) {
+            const float z = zc[rad + o];
+            zn[o] = z - a.alpha_soft * fmaxf(m[o] - z, 0.f);
+          }
+          *reinterpret_cast<float4*>(&s_zn[hh][q0]) = make_float4(zn[0], zn[1], zn[2], zn[3]);
+        }
       }
       __syncthreads();
     };
