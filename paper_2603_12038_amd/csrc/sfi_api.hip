@@ -23,6 +23,7 @@ struct sfi_ctx {
   int dense_wide;           // dense kernel reads K rows as whole 128-byte lines (A/B knob, sfi_set_dense_k_layout)
   int mixed_plan;           // the ragged step's dense launch plans itself on the device (default; A/B knob, sfi_set_mixed_plan)
   int last_dense_splits, last_fast_splits;
+  int last_dense_planned;   // the last dense launch planned itself: its records per sequence are in ws.seq_rec
   // profiling: a ring of event pairs, one set of stages per hot call, read back in one go so that
   // no host synchronisation sits between the profiled calls
   int profiling;
@@ -110,6 +111,7 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->fbuf = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->segstat = full ? (double*)take((size_t)(B * Hkv) * n_seg * kSegStats * sizeof(double)) : nullptr;
   ws->slow_list = (int32_t*)take((4 + 4 * (size_t)B) * sizeof(int32_t));
+  ws->seq_rec = (int32_t*)take((size_t)B * sizeof(int32_t));
   ws->ld_pos = ld;
   ws->n_seg_cap = n_seg;
   return off;
@@ -163,6 +165,36 @@ int dense_splits_for(const sfi_ctx* x, int max_len, bool mixed) {
   if (s > cap) s = cap;
   if (s < 1) s = 1;
   return s;
+}
+
+// Where the dense launch plans itself on the device: more than one sequence (with one there is nothing to even out, and
+// the launch with a workgroup per cell requests its first rows before the length has arrived), unless a knob asks for the
+// other launch.  Workgroups per KV head: as many as give every compute unit one; where the heads do not divide the units
+// (fewer than nine in ten busy), up to four rounds.  A workgroup takes at least a tile per wave, and enough tiles that the
+// longest sequence stays within its records.  (8 paged sequences of 20011 to 24571 rows, 8 KV heads: dense launch 122 -> 109 us.)
+void plan_dense(sfi_ctx* x, AttnArgs* a, int max_len, bool mixed) {
+  x->last_dense_planned = 0;
+  const int B = x->cfg.batch, Hkv = x->cfg.n_kv_heads;
+  if (B < 2 || B > kListCap || x->dense_target_wgs > 0 || x->dense_wide) return;
+  const int tiles = (max_len + kTile - 1) / kTile + 2;  // J, then sink and recent rows: a ragged tile at the end of each
+  if (!mixed && (B * Hkv > 2 * x->n_cu || (int64_t)tiles * B * Hkv < (a->no_v ? 16 : 8) * (int64_t)kWaves * x->n_cu)) return;
+  int best = 1;
+  double fill = 0.0;
+  for (int rounds = 1; rounds <= 4 && fill < 0.9; ++rounds) {
+    const int wgs = rounds * x->n_cu / Hkv;
+    const double f = (double)wgs * Hkv / ((double)rounds * x->n_cu);
+    if (wgs >= 1 && f > fill) {
+      best = wgs;
+      fill = f;
+    }
+  }
+  const int most = (int)(((int64_t)tiles * B + kWaves - 1) / kWaves);  // workgroups there are tiles for
+  a->plan_batch = B;
+  a->plan_wgs = best < most ? best : most;
+  a->plan_min = ((tiles + kSlotCap - 3) / (kSlotCap - 2) + kWaves - 1) / kWaves * kWaves;
+  a->plan_even = mixed ? 0 : a->n_split;
+  a->seq_rec = x->ws.seq_rec;
+  x->last_dense_planned = 1;
 }
 
 void set_dense_bounds(const sfi_ctx* x, AttnArgs* a, int max_len) {
@@ -460,11 +492,13 @@ int sfi_dense_attn(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.n_split = dense_splits_for(x, ml, false);
   set_dense_bounds(x, &a, ml);
   x->last_dense_splits = a.n_split;
-  if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
+  if (x->tail_merge) plan_dense(x, &a, ml, false);
+  if (a.plan_batch > 0) { a.out_merge = out; a.arrive = x->ws.arrive; }
+  else if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
   else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
-  if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
-  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split, 0, 0, nullptr, x->G, x->alpha, x->cfg.out_bf16};
+  if (a.out_direct != nullptr || a.out_merge != nullptr) return SFI_OK;
+  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split, 0, 0, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -504,9 +538,10 @@ int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.big_stash = 1;  // every sequence is dense: one workgroup per compute unit, half as many write bursts
   a.no_v = out == nullptr;  // evidence only (sfi_evidence_add without an output)
   x->last_dense_splits = a.n_split;
+  plan_dense(x, &a, ml, false);
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (merge_later) return SFI_OK;  // the Selector's scoring launch merges
-  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split, 0, 0, x->ws.jstat, x->G, x->alpha, x->cfg.out_bf16};
+  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split, 0, 0, x->ws.jstat, a.plan_batch > 0 ? x->ws.seq_rec : nullptr, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -536,6 +571,7 @@ int sfi_slow_step(sfi_ctx* x, const void* q, const void* K, const void* V, const
   fill_sel(x, &sa, ctx_len, ml, nullptr, budget, x->last_dense_splits, sel_idx, n_sel);
   sa.part = x->ws.part;
   sa.merge_out = out;
+  if (x->last_dense_planned) sa.seq_rec = x->ws.seq_rec;
   return run_selector(x, sa, ml, st);
 }
 
@@ -583,6 +619,7 @@ int evidence_add_impl(sfi_ctx* x, const void* q, const void* K, const void* V, c
   fill_sel(x, &sa, ctx_len, ml, nullptr, 0, x->last_dense_splits, nullptr, nullptr);
   sa.part = x->ws.part;
   sa.merge_out = out;
+  if (x->last_dense_planned) sa.seq_rec = x->ws.seq_rec;
   sa.accum_first = first != 0;
   sa.q_len = q_len;
   // a query under the causal mask may see up to `recent` more positions of its own, shorter context as allowed set
@@ -641,7 +678,7 @@ int fast_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const 
   else if (x->tail_merge) { a.out_merge = out; a.arrive = arrive; }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_gather(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
-  MergeArgs m{part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, x->G, x->alpha, x->cfg.out_bf16};
+  MergeArgs m{part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -854,7 +891,7 @@ int sfi_fast_step_compact(sfi_ctx* x, const void* q, const void* Kc, const void*
   else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_compact(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
-  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, x->G, x->alpha, x->cfg.out_bf16};
+  MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};
   { StageTimer t(x, st, SFI_STAGE_MERGE); SFI_TRY(launch_merge(m, x->cfg.batch, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }
@@ -917,14 +954,10 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   // runs when the in-kernel merge is switched off (for both kinds: it skips what is already done).
   const bool fast_done = f.n_split == 1 || f.out_merge != nullptr;
   const bool merge_in_score = fast_done;
-  // The dense launch plans itself on the device (one workgroup per compute unit, splits per slow sequence in proportion to
-  // its length: attn_dense_items_kernel) where its records are merged by the scoring launch, which reads the plan back.
-  const bool planned = x->mixed_plan != 0 && merge_in_score && x->cfg.batch <= kListCap;
-  if (planned) {
-    d.item_batch = x->cfg.batch;
-    d.item_wgs = x->n_cu;
-    d.slow_list = x->ws.slow_list;
-  }
+  // The dense launch plans itself on the device where its records are merged by the scoring launch, which reads the plan back.
+  if (x->mixed_plan != 0 && merge_in_score) plan_dense(x, &d, ml, true);
+  const bool planned = d.plan_batch > 0;
+  if (planned) d.slow_list = x->ws.slow_list;
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
   {
@@ -935,7 +968,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(d, x->cfg.batch, d.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (!merge_in_score) {
-    MergeArgs m{x->ws.part, out, is_slow, x->cfg.n_q_heads, d.n_split, fast_done ? 0 : f.n_split, 2, x->ws.jstat, x->G, x->alpha, x->cfg.out_bf16, fs};
+    MergeArgs m{x->ws.part, out, is_slow, x->cfg.n_q_heads, d.n_split, fast_done ? 0 : f.n_split, 2, x->ws.jstat, nullptr, x->G, x->alpha, x->cfg.out_bf16, fs};
     StageTimer t(x, st, SFI_STAGE_MERGE);
     SFI_TRY(launch_merge(m, x->cfg.batch, st));
     if (!t.stop()) return SFI_ELAUNCH;

@@ -4,8 +4,8 @@
 // share it, logits l_g(j) = scale * <q_g, k_j> over a list of positions, and the flash-style
 // partial  (m, sum_j e^{l-m}, sum_j e^{l-m} v_j)  of a share of that list, in the log2 domain
 // (y = log2(e) * l, weights 2^(y - m)).
-//   dense  kernel (slow step; in the ragged step with the launch planned on the device, attn_dense_items_kernel):
-//          the waves of n_split workgroups share the tiles of the allowed set
+//   dense  kernels (slow step, dense attention; batches with the launch planned on the device, attn_dense_planned_kernel):
+//          the waves of several workgroups share the tiles of the allowed set
 //          J = [n_sink, L - recent), for which y is also exposed to the Selector (Eq. window_logits,
 //          W = 1), followed by the tiles of the sink and recent rows, which the Selector never ranks
 //          (Eq. allowed_set).  A wave takes its J tiles first and keeps its softmax statistics at the point where
@@ -28,10 +28,12 @@
 //         P is split into two bf16 terms (hi + lo) so the weights keep ~16 bits.
 // bf16 x bf16 products are exact in fp32, so logits differ from an fp64 evaluation only by the
 // fp32 accumulation inside the matrix core.
+#include <algorithm>
 #include <type_traits>
 
 #include "sfi_internal.h"
 #include "sfi_merge.h"
+#include "sfi_wave.h"
 
 namespace sfi {
 
@@ -684,12 +686,20 @@ struct ListWalk {
 // PAGED: K / V are block pools addressed through the sequence's block table.
 // EXPOSE 1: also write y over J for the Selector; 2: y and the squared key norms.
 // BIG: twice the logits stash per wave, which leaves room for one workgroup per compute unit only
-// (launches where every sequence is dense, and the ragged step's planned launch, run one per unit anyway; the ragged
+// (launches where every sequence is dense, and the planned launch, run one per unit anyway; the ragged
 // step's launch with a workgroup per cell keeps two).
 // NOV: evidence only -- no V row is read, no P V product, the records carry the softmax statistics alone.
-template <int EXPOSE, bool PAGED, bool BIG = false, bool NOV = false, bool WIDE = false>
-__device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split, const int slot, const int h, const int b,
-                                           const int tid_bias = 0) {
+// PLANNED: the caller has the sequence's length and a range of its tiles (attn_dense_planned_kernel).
+struct DenseShare {
+  int first, step;   // tiles of wave w: first + w, first + w + step, ... below end (step: a multiple of the waves)
+  int end;
+  int slot, n_rec;   // the workgroup's record among the pair's
+  int L, recent;     // PLANNED: rows the query sees, and what of the recent window it sees
+  int bad;           // PLANNED: guard bits so far
+  bool have_k;       // PLANNED: K rows of the first tile are on their way into T
+};
+template <int EXPOSE, bool PAGED, bool BIG, bool NOV, bool WIDE, bool PLANNED>
+__device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& sh, const int h, const int b, Tile& T, const int tid_bias = 0) {
   constexpr int kStash = BIG ? 2 * kStashFloats : kStashFloats;
   // per-wave LDS: the logits stash, and at the end the wave's O for the combine (finish_wg)
   constexpr int kPatch = EXPOSE != 0 ? kStash : 16 * kHeadDim;
@@ -698,8 +708,10 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
   asm volatile("" ::"s"(a.q), "s"(a.K), "s"(a.V), "s"(a.k_sb), "s"(a.k_sh), "s"(a.k_st), "s"(a.v_sb), "s"(a.v_sh), "s"(a.v_st),
                "s"(a.ctx_len), "s"(a.is_slow), "s"(a.q_len), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.n_sink), "s"(a.recent),
                "s"(a.max_tiles), "s"(a.row_cap), "s"(a.len_cap));
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
-  const int tid = threadIdx.x + tid_bias;  // (tid_bias: zero; see attn_dense_items_kernel)
+  // the length is on its way before the first rows: behind them it would take the loaded memory's 1.5 us
+  const int L_in = PLANNED ? 0 : a.ctx_len[b * a.ms];
+  if (!PLANNED && a.is_slow != nullptr && a.is_slow[b * a.fs] == 0) return;
+  const int tid = threadIdx.x + tid_bias;  // (tid_bias: zero; see attn_dense_planned_kernel)
   const int lane = tid & 63, w = tid >> 6;
   const int jg = lane >> 4, n = lane & 15;
   const int G = a.G;
@@ -717,25 +729,22 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
 
   // The prefix of (b, h) is cut into 32-row tiles in two runs: tiles [0, nTJ) cover the allowed set J
   // (tile t, position i is cache row n_sink + 32 t + i), tiles [nTJ, nTJ + nTS) cover the sink rows
-  // followed by the recent window, which the Selector never ranks.  The n_split * 4 waves of the
-  // (b, h) pair own tiles first, first + step, ... of that sequence, so every wave of every workgroup
-  // carries an equal share.  A wave's J tiles come first: the J-only softmax statistics the Selector needs are the
-  // wave's running ones at the point where its J tiles end.  An evidence-only pass has nothing to do beyond J.
-  // The rows of the wave's first tile follow from the block index alone (almost always a J tile):
+  // followed by the recent window, which the Selector never ranks.  The waves of the workgroups on a
+  // (b, h) pair share its tiles evenly.  A wave's J tiles come first: the J-only softmax statistics the Selector needs
+  // are the wave's running ones at the point where its J tiles end.  An evidence-only pass has nothing to do beyond J.
+  // Not PLANNED, the rows of the wave's first tile follow from the block index alone (almost always a J tile):
   // their loads go out before ctx_len arrives, clamped to the launch's row bound.
-  const int n_waves = n_split * kWaves;
-  const int first = slot * kWaves + w, step = n_waves;
-  Tile T;
+  const int first = sh.first + w, step = sh.step;
   // (a paged cache has valid blocks only up to ctx_len: no load before ctx_len is known)
-  if (!PAGED && first < a.max_tiles) {
+  if (!PLANNED && !PAGED && first < a.max_tiles) {
     issue_k_affine<WIDE>(T, R, a.n_sink + first * kTile, a.row_cap);
     if (!NOV) issue_v_affine<WIDE>(T, R, a.n_sink + first * kTile, a.row_cap);
   }
   bf16x8 qreg[4];
   load_q_raw<WIDE>(qreg, a.q, head0, G, jg, n);
-  int bad = 0;
-  int L, recent;  // a window query under the causal mask sees a shorter context with what is left of the recent window
-  window_view(a.q_len, b, guarded_len(a.ctx_len[b * a.ms], a.len_cap, bad), a.recent, L, recent);
+  int bad = PLANNED ? sh.bad : 0;
+  int L = sh.L, recent = sh.recent;  // a window query under the causal mask sees a shorter context with what is left of the recent window
+  if (!PLANNED) window_view(a.q_len, b, guarded_len(L_in, a.len_cap, bad), a.recent, L, recent);
   const int NJ = max(0, L - recent - a.n_sink);
   const int nTJ = (NJ + kTile - 1) / kTile;
   const int rJ_max = a.n_sink + NJ - 1;
@@ -743,9 +752,10 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
   const int rs = min(max(a.n_sink, L - recent), L);
   const int NS = nS + (L - rs);
   const int nTS = (NS + kTile - 1) / kTile;
-  const int nT = nTJ + (NOV ? 0 : nTS);
+  const int nT = PLANNED ? min(sh.end, nTJ + (NOV ? 0 : nTS)) : nTJ + (NOV ? 0 : nTS);
+  const int nTJw = min(nTJ, nT);
   const int K = first < nT ? (nT - first + step - 1) / step : 0;      // tiles of this wave
-  const int KJ = first < nTJ ? (nTJ - first + step - 1) / step : 0;   // ... of which in J
+  const int KJ = first < nTJw ? (nTJw - first + step - 1) / step : 0;  // ... of which in J
   const int d_rs = rs - nS, r_last = max(L, 1) - 1;
   // cache row of position i of tile t; tiles past the end (the refill after the last tile) read row L - 1
   // (row 0 of an empty context: the cache holds max_ctx >= 1 rows)
@@ -782,32 +792,42 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
     }
   };
   Pages P;
-  int pa_n = 0, pb_n = 0;  // PAGED: block-table entries of the next tile's K rows (this lane's rows n and 16 + n)
+  int pra2 = 0, prb2 = 0;  // PAGED: physical rows of the second tile
+  int pa_n = 0, pb_n = 0;  // PAGED: block-table entries of the next refill's K rows (this lane's rows n and 16 + n)
   if (PAGED) {
-    // Same order of memory instructions as an iteration of the loop: K rows, the table entries of the
-    // tile after, V rows.  Waves without tiles read row L - 1.
+    // Same order of memory instructions as an iteration of the loop: K rows, the table entries of the next refill, V rows.
+    // Waves without tiles read row L - 1.
     P = pages_of(a, b, L);
     const int ra = row_for(first, n), rb = row_for(first, 16 + n);
-    const int pra = P.phys(ra, P.page_of(ra), bad), prb = P.phys(rb, P.page_of(rb), bad);
+    const int ra2 = row_for(first + step, n), rb2 = row_for(first + step, 16 + n);
+    const int pa = P.page_of(ra), pb = P.page_of(rb), pa2 = P.page_of(ra2), pb2 = P.page_of(rb2);
+    const int pra = P.phys(ra, pa, bad), prb = P.phys(rb, pb, bad);
+    pra2 = P.phys(ra2, pa2, bad);
+    prb2 = P.phys(rb2, pb2, bad);
     __builtin_amdgcn_sched_barrier(0);
     issue_k_rows<uint64_t>(T, R, pra, prb);
     __builtin_amdgcn_sched_barrier(0);
-    pa_n = P.page_of(row_for(first + step, n));
-    pb_n = P.page_of(row_for(first + step, 16 + n));
+    pa_n = P.page_of(row_for(first + 2 * step, n));
+    pb_n = P.page_of(row_for(first + 2 * step, 16 + n));
     __builtin_amdgcn_sched_barrier(0);
     if (!NOV) issue_v_rows<uint64_t>(T, R, pra, prb);
     __builtin_amdgcn_sched_barrier(0);
-  } else if (K > 0 && first >= nTJ) {  // short context: the first tile is a sink / recent tile after all
-    issue_k_tile(T, first);
+  } else if (K > 0 && (PLANNED || first >= nTJ)) {  // (short context: the first tile is a sink / recent tile after all)
+    if (!PLANNED || !sh.have_k || first >= nTJ) issue_k_tile(T, first);
     issue_v_tile(T, first);
   }
-  // A flat cache keeps two tiles in flight per wave: the second buffer takes the wave's second tile now.
+  // Two tiles are in flight per wave: the second buffer takes the wave's second tile now.
   Tile T2;
-  constexpr int NB = PAGED ? 1 : 2;  // tile buffers; a tile's refill is the wave's tile NB further on
-  if (!PAGED && K > 1) {
+  constexpr int NB = 2;  // tile buffers; a tile's refill is the wave's tile NB further on
+  if (K > 1) {
     __builtin_amdgcn_sched_barrier(0);
-    issue_k_tile(T2, first + step);
-    issue_v_tile(T2, first + step);
+    if (PAGED) {
+      issue_k_rows<uint64_t>(T2, R, pra2, prb2);
+      if (!NOV) issue_v_rows<uint64_t>(T2, R, pra2, prb2);
+    } else {
+      issue_k_tile(T2, first + step);
+      issue_v_tile(T2, first + step);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
   mask_q<WIDE>(qreg, G, n);
@@ -866,11 +886,11 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
     int pra = 0, prb = 0;
     if (!kRefill) {
     } else if (PAGED) {
-      pra = P.phys(row_for(t + step, n), pa_n, bad);
-      prb = P.phys(row_for(t + step, 16 + n), pb_n, bad);
+      pra = P.phys(row_for(t + NB * step, n), pa_n, bad);
+      prb = P.phys(row_for(t + NB * step, 16 + n), pb_n, bad);
       issue_k_rows<uint64_t>(T, R, pra, prb);
-      pa_n = P.page_of(row_for(t + 2 * step, n));
-      pb_n = P.page_of(row_for(t + 2 * step, 16 + n));
+      pa_n = P.page_of(row_for(t + (NB + 1) * step, n));
+      pb_n = P.page_of(row_for(t + (NB + 1) * step, 16 + n));
     } else {
       issue_k_tile(T, t + NB * step);
     }
@@ -899,11 +919,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
   };
   const std::integral_constant<bool, true> refill;
   const std::integral_constant<bool, false> last;
-  if (PAGED) {
-    int k = 0;
-    for (; k + 1 < K; ++k) tile_step(T, k, refill);
-    if (k < K) tile_step(T, k, last);
-  } else if (K == 1) {
+  if (K == 1) {
     tile_step(T, 0, last);
   } else if (K > 1) {
     // (an odd last tile is taken after the loop: a way out of the middle of the loop body would put a
@@ -926,147 +942,209 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const int n_split,
     m_j = m_run;
     l_j = l_run;
   }
-  finish_wg<EXPOSE != 0, !NOV>(wg_out_of(a, bh), head0, G, slot, acc, m_run, rows_sum(l_run), &s_patch[0][0], kPatch, m_j,
+  WgOut o = wg_out_of(a, bh);
+  o.n_split = sh.n_rec;
+  if (PLANNED && sh.n_rec == 1) {
+    o.out_direct = o.out_merge;
+    o.out_merge = nullptr;
+  }
+  finish_wg<EXPOSE != 0, !NOV>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), &s_patch[0][0], kPatch, m_j,
                                EXPOSE != 0 ? rows_sum(l_j) : 0.f);
   report_guard(a.guard, bad);
 }
-// One workgroup per (split, KV head, sequence) cell ...
+// One workgroup per (split, KV head, sequence) cell: wave w of split s takes tiles 4 s + w, 4 (s + n_split) + w, ...
 template <int EXPOSE, bool PAGED, bool BIG = false, bool NOV = false, bool WIDE = false>
 __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(const AttnArgs a) {
-  dense_body<EXPOSE, PAGED, BIG, NOV, WIDE>(a, a.n_split, blockIdx.x, blockIdx.y, blockIdx.z);
+  const DenseShare sh{(int)blockIdx.x * kWaves, a.n_split * kWaves, 0, (int)blockIdx.x, a.n_split, 0, 0, 0, false};
+  Tile T;
+  dense_body<EXPOSE, PAGED, BIG, NOV, WIDE, false>(a, sh, blockIdx.y, blockIdx.z, T);
 }
-// ... or, in the ragged step (sfi_mixed_step*), one workgroup per compute unit that plans the launch on the device.
-// Which sequences are slow is only known there, so the host cannot size the launch for them: one workgroup per (split,
-// KV head, sequence) cell with the finest split and an early exit for fast sequences leaves the kernel with a handful
-// of tiles per wave (a wave's start and end weigh as much as its tiles), thousands of empty workgroups, and shares
-// that follow the sequences' lengths.  Here every workgroup builds the same plan from the flags and lengths: the slow
-// sequences' ids; for each its tiles T_r (the body's own count: tiles of J plus tiles of sink ++ recent) and its splits
-// s_r = T_r x (grid / Hkv) / sum T rounded down, at least 1 and at most the host's bound a.n_split or one tile per
-// wave, what the rounding left over going one by one to the sequence with the most tiles per split -- so that the cells
-// (r, h, slot < s_r) number one per workgroup and hold the same number of tiles whatever the sequences' lengths (with
-// many slow sequences: about four splits each, dealt round robin).  Workgroup i takes cells i, i + grid, ...; workgroup
-// 0 leaves the list of slow sequences with s_r for the Selector's launches, which then need workgroups for those alone.
-// A cell's coordinates are made scalars again (they come out of LDS), so that the body's addressing
-// stays on the scalar unit as it is with block indices.
-template <int EXPOSE, bool PAGED>
-__global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_items_kernel(const AttnArgs a) {
-  __shared__ int s_list[kListCap];       // slow sequence ids, ascending
-  __shared__ int s_tiles[kListCap];      // their tiles
-  __shared__ int s_split[kListCap];      // their splits
-  __shared__ int s_first[kListCap + 1];  // cells in front of sequence r (prefix of s_r * Hkv)
-  __shared__ int s_scr[8];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  // flags and lengths of this thread's four sequences, all requested together
-  int flag[4], len[4], c = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int b = min(4 * tid + j, a.item_batch - 1);
-    flag[j] = a.is_slow[(int64_t)b * a.fs];
-    len[j] = a.ctx_len[(int64_t)b * a.ms];
+// The launch planned on the device: more than one sequence, every one with a length of its own (which only the device
+// knows) and, in the ragged step (sfi_mixed_step*), only some of them slow.  With a workgroup per cell the shares follow the
+// sequences' lengths, and in the ragged step thousands of workgroups find nothing to do.  Here the tiles of the
+// sequences taking part are laid end to end, per KV head, and cut into one equal share per workgroup (W per head, about
+// one workgroup per compute unit in all), so that a workgroup's share can reach into several sequences; it leaves a
+// record (and a combine) for each.
+// - A position in the list counts in 1/1024 of a share; sequence r begins at X_r = P_r * scale + r (P_r: the tiles in
+//   front of it), so that every sequence is at least 1 long.
+// - A second sequence costs a workgroup its way out and its way in again, about kCross tiles' time: between two
+//   sequences the list has kCross tiles of nothing.  A border that is closer to a share's end than half of that is moved
+//   there instead, and then nothing is lost: sequences of equal lengths get whole workgroups.
+// - The workgroups that have nothing but one sequence interleave their tiles (wave by wave, as in the launch above);
+//   ranges of consecutive tiles would start at multiples of one large stride, and run at the same pace over the
+//   same few memory channels.  The first and the last workgroup of a sequence take their part at its ends.
+// - Every wave works out the plan by itself (a sequence per lane, a scan over the lanes; no LDS, no barrier), from
+//   leading arguments that it has in registers when it starts.  The workgroup with a sequence's first record notes how many records it has, for the
+//   launches that merge them, and the list of the sequences taking part for the Selector's.
+struct PlanArgs {
+  int W, n_on, total;
+  float scale;
+  int h;  // half a border's gap, in positions; also how far a border moves
+};
+constexpr int kShareLg = 10;
+constexpr float kCross = 5.f;
+// Position of the border in front of sequence `rank` with P tiles before it; off: the gap on either side of it.
+__device__ __forceinline__ int plan_border(const PlanArgs& p, int P, int rank, int& off) {
+  int x = (int)((float)P * p.scale) + rank;
+  const int f = x & ((1 << kShareLg) - 1), up = (1 << kShareLg) - f;
+  off = f > p.h && up > p.h ? p.h : 0;
+  x += f <= p.h ? -f : up <= p.h ? up : 0;
+  if (P == 0) x = 0, off = 0;
+  if (P == p.total) x = p.W << kShareLg, off = 0;
+  return x;
+}
+template <int EXPOSE, bool PAGED, bool NOV>
+__global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
+                                                                             uint32_t strides, int B, int W_max, float per_min, int n_sink,
+                                                                             int recent_in, int len_cap, const AttnArgs a) {
+  const int j = blockIdx.x, h = blockIdx.y;
+  const int lane = threadIdx.x & 63;
+  const int ms = strides & 0xffff, fs = strides >> 16;
+  // rows seen, recent window seen and tiles of sequence b (at least one tile: an empty context has a record too)
+  auto view_of = [&](int b, int L_in, int& L, int& recent, int& bad) -> int {
+    window_view(q_len, b, guarded_len(L_in, len_cap, bad), recent_in, L, recent);
+    const int NJ = max(0, L - recent - n_sink);
+    const int nS = min(n_sink, L), rs = min(max(n_sink, L - recent), L);
+    return max(1, (NJ + kTile - 1) / kTile + (NOV ? 0 : (nS + (L - rs) + kTile - 1) / kTile));
+  };
+  // this lane's sequences: per consecutive ones, tiles of sequence i among them (0: takes no part)
+  const int per = (B + 63) / 64;
+  auto tiles_of = [&](int b, int bc, int L_in, int on, int& L) -> int {
+    int rec, bad = 0;
+    const int t = view_of(bc, L_in, L, rec, bad);
+    return b < B && on != 0 ? t : 0;
+  };
+  auto lane_seq = [&](int i, int& L_in, int& L) -> int {
+    const int b = lane * per + i, bc = min(b, B - 1);
+    L_in = ctx_len[bc * ms];
+    return tiles_of(b, bc, L_in, is_slow == nullptr || is_slow[bc * fs] != 0, L);
+  };
+  const int b0 = lane * per, bc0 = min(b0, B - 1);
+  int L0 = ctx_len[bc0 * ms];
+  int on0 = 1;
+  if (is_slow != nullptr) on0 = is_slow[bc0 * fs];
+  __builtin_amdgcn_sched_barrier(0);
+  // the guess: this workgroup's place if all sequences are equally long
+  const int even = a.plan_even;
+  const int b_even = even > 0 ? j / even : B, slot_even = j - b_even * even;
+  Tile T;
+  if (!PAGED && b_even < B) {
+    Rows R;
+    R.Kb = reinterpret_cast<const char*>(a.K + b_even * a.k_sb + h * a.k_sh);
+    R.k_st = (uint32_t)a.k_st * 2u;
+    R.k_lane = k_lane_of<false>(lane >> 4, lane & 15);
+    R.n = lane & 15;
+    issue_k_affine<false>(T, R, n_sink + (slot_even * kWaves + ((int)threadIdx.x >> 6)) * kTile, a.row_cap);
   }
-  int tiles = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    flag[j] = 4 * tid + j < a.item_batch && flag[j] != 0;
-    const int L = min(max(len[j], 0), a.len_cap);
-    const int NJ = max(0, L - a.recent - a.n_sink);
-    const int nS = min(a.n_sink, L), rs = min(max(a.n_sink, L - a.recent), L);
-    len[j] = (NJ + kTile - 1) / kTile + (nS + (L - rs) + kTile - 1) / kTile;  // from here on: the sequence's tiles
-    c += flag[j];
-    tiles += flag[j] ? len[j] : 0;
+  __builtin_amdgcn_sched_barrier(0);
+  int L_0;
+  const int t0 = tiles_of(b0, bc0, L0, on0, L_0);
+  const int L_in_all = __builtin_amdgcn_readfirstlane(L0), L_all = __builtin_amdgcn_readfirstlane(L_0);
+  bool same = even > 0 && (b0 >= B || (L0 == L_in_all && L_0 == L_all));
+  int tiles = t0, count = t0 > 0;
+  float least = t0 > 0 ? (float)t0 : 3e38f;
+  for (int i = 1; i < per; ++i) {
+    int L_in, L;
+    const int t = lane_seq(i, L_in, L);
+    same = same && (b0 + i >= B || (L_in == L_in_all && L == L_all));
+    tiles += t;
+    count += t > 0;
+    least = t > 0 ? fminf(least, (float)t) : least;
   }
-  int inc = c;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(inc, d);
-    if (lane >= d) inc += t;
-  }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) tiles += __shfl_xor(tiles, d);
-  if (lane == 63) s_scr[w] = inc;
-  if (lane == 0) s_scr[4 + w] = tiles;
-  __syncthreads();
-  int base = 0, n_slow = 0;
-#pragma unroll
-  for (int i = 0; i < kWaves; ++i) {
-    const int t = s_scr[i];
-    if (i < w) base += t;
-    n_slow += t;
-  }
-  n_slow = __builtin_amdgcn_readfirstlane(n_slow);
-  if (n_slow == 0) {
-    if (blockIdx.x == 0 && tid == 0) a.slow_list[0] = 0;
+  if (__all(same)) {
+    if (b_even >= B) return;
+    DenseShare sh;
+    sh.bad = 0;
+    view_of(b_even, L_in_all, sh.L, sh.recent, sh.bad);
+    sh.first = slot_even * kWaves;
+    sh.step = even * kWaves;
+    sh.end = 1 << 30;
+    sh.slot = slot_even;
+    sh.n_rec = even;
+    sh.have_k = !PAGED;
+    if (slot_even == 0 && h == 0 && threadIdx.x == 0) a.seq_rec[b_even] = even;
+    dense_body<EXPOSE, PAGED, true, NOV, false, true>(a, sh, h, b_even, T);
     return;
   }
-  const int total = max(1, s_scr[4] + s_scr[5] + s_scr[6] + s_scr[7]);
-  // splits to hand out among the slow sequences: one cell per workgroup, or, with many slow sequences, about four
-  // splits each, so that dealing the cells round robin still balances
-  const int per_head = max(max(1, (int)gridDim.x / a.Hkv), 4 * n_slow);
-  {
-    int o = base + inc - c;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (flag[j]) {
-        s_list[o] = 4 * tid + j;
-        s_tiles[o] = len[j];
-        const int want = (int)((int64_t)len[j] * per_head / total);  // rounded down: the sum must not pass per_head
-        s_split[o] = max(1, min(want, min(a.n_split, (len[j] + kWaves - 1) / kWaves)));
-        ++o;
-      }
+  const int inc_t = (int)wave_incl_scan((uint32_t)tiles), inc_c = (int)wave_incl_scan((uint32_t)count);
+  PlanArgs p;
+  p.total = __builtin_amdgcn_readlane(inc_t, 63);
+  p.n_on = __builtin_amdgcn_readlane(inc_c, 63);
+  if (a.slow_list != nullptr && h == 0 && j == 0 && threadIdx.x == 0) a.slow_list[0] = p.n_on;
+  p.W = max(1, min(W_max, (int)((float)p.total * per_min)));
+  if (j >= p.W || p.total == 0) return;
+  p.scale = (float)((p.W << kShareLg) - p.n_on) * __builtin_amdgcn_rcpf((float)p.total) * 0.999999f;
+  p.h = -wave_max(-least) * p.scale > 2.f * kCross * p.scale + 8.f ? min((int)(0.5f * kCross * p.scale) + 1, 1 << (kShareLg - 2)) : 0;
+  const int start = j << kShareLg;
+  // the sequence at the share's start
+  int before = inc_t - tiles, rank = inc_c - count;  // tiles, sequences in front of this lane's
+  int hit_i = -1, hit_P = 0, hit_rank = 0, hit_L = 0;
+  for (int i = 0; i < per; ++i) {
+    int L_in = L0;
+    int off, L;
+    const int t = i == 0 ? t0 : lane_seq(i, L_in, L);
+    if (t > 0 && plan_border(p, before, rank, off) <= start && start < plan_border(p, before + t, rank + 1, off)) {
+      hit_i = i;
+      hit_P = before;
+      hit_rank = rank;
+      hit_L = L_in;
     }
+    before += t;
+    rank += t > 0;
   }
-  __syncthreads();
-  if (tid == 0) {  // (a few dozen sequences at most in practice; done by one thread, the plan is the same everywhere)
-    int acc = 0;
-    for (int r = 0; r < n_slow; ++r) acc += s_split[r];
-    // what rounding down left over goes, one split at a time, to the sequence with the most tiles per split
-    for (int left = per_head - acc; left > 0 && n_slow <= 64; --left) {
-      int best = -1;
-      float worst = 0.f;
-      for (int r = 0; r < n_slow; ++r) {
-        const int cap = min(a.n_split, (s_tiles[r] + kWaves - 1) / kWaves);
-        const float load = (float)s_tiles[r] / (float)s_split[r];
-        if (s_split[r] < cap && load > worst) {
-          worst = load;
-          best = r;
-        }
-      }
-      if (best < 0) break;
-      ++s_split[best];
+  const int src = __builtin_ctzll(__ballot(hit_i >= 0));
+  int b = src * per + __builtin_amdgcn_readlane(hit_i, src), P = __builtin_amdgcn_readlane(hit_P, src);
+  int r = __builtin_amdgcn_readlane(hit_rank, src), L_in = __builtin_amdgcn_readlane(hit_L, src);
+  for (;;) {
+    DenseShare sh;
+    sh.bad = 0;
+    const int t_b = view_of(b, L_in, sh.L, sh.recent, sh.bad);
+    int g0, g1;
+    const int x0 = plan_border(p, P, r, g0), x1 = plan_border(p, P + t_b, r + 1, g1);
+    const int w0 = __builtin_amdgcn_readfirstlane(x0 >> kShareLg), w1 = __builtin_amdgcn_readfirstlane((x1 - 1) >> kShareLg);
+    sh.slot = j - w0;
+    sh.n_rec = w1 - w0 + 1;
+    // the tiles of the first workgroup and those in front of the last one, where they share with another sequence
+    const int lo = x0 + g0, hi = x1 - g1;
+    const float f = (float)t_b * __builtin_amdgcn_rcpf((float)(hi - lo));
+    const bool part0 = w1 > w0 && (x0 & ((1 << kShareLg) - 1)) != 0, part1 = w1 > w0 && (x1 & ((1 << kShareLg) - 1)) != 0;
+    const int A = part0 ? min(t_b, (int)((float)(((w0 + 1) << kShareLg) - lo) * f)) : 0;
+    const int Z = part1 ? min(t_b, (int)((float)((w1 << kShareLg) - lo) * f)) : t_b;
+    const int n_full = sh.n_rec - part0 - part1;
+    int first, step = kWaves, end;
+    if (part0 && sh.slot == 0) {
+      first = 0;
+      end = A;
+    } else if (part1 && j == w1) {
+      first = Z;
+      end = t_b;
+    } else {
+      first = A + (sh.slot - part0) * kWaves;
+      step = n_full * kWaves;
+      end = Z;
     }
-    acc = 0;
-    for (int r = 0; r < n_slow; ++r) {
-      s_first[r] = acc;
-      acc += s_split[r] * a.Hkv;
+    sh.first = __builtin_amdgcn_readfirstlane(first);
+    sh.step = __builtin_amdgcn_readfirstlane(step);
+    sh.end = __builtin_amdgcn_readfirstlane(end);
+    if (sh.slot == 0 && h == 0 && threadIdx.x == 0) {
+      a.seq_rec[b] = sh.n_rec;
+      if (a.slow_list != nullptr)
+        reinterpret_cast<int4*>(a.slow_list)[1 + r] = make_int4(b, min(max(L_in, 0), len_cap), sh.n_rec, 0);
     }
-    s_first[n_slow] = acc;
-  }
-  __syncthreads();
-  if (blockIdx.x == 0) {
-    if (tid == 0) a.slow_list[0] = n_slow;
-    for (int r = tid; r < n_slow; r += kAttnThreads)
-      reinterpret_cast<int4*>(a.slow_list)[1 + r] =
-          make_int4(s_list[r], min(max(a.ctx_len[(int64_t)s_list[r] * a.ms], 0), a.len_cap), s_split[r], 0);
-  }
-  const int n_items = __builtin_amdgcn_readfirstlane(s_first[n_slow]);
-  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-    int lo = 0, hi = n_slow;  // the sequence whose cells include this one: s_first[lo] <= item < s_first[lo + 1]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (s_first[mid] <= item) lo = mid;
-      else hi = mid;
-    }
-    const int r = lo;
-    const int ns = __builtin_amdgcn_readfirstlane(s_split[r]);
-    const int rem = item - __builtin_amdgcn_readfirstlane(s_first[r]);
-    const int h = rem / ns;
-    const int b = __builtin_amdgcn_readfirstlane(s_list[r]);
     // A zero the compiler cannot see through: without it everything the body derives from the thread index is
     // computed once in front of this loop and kept in registers across the body.
     int zero = 0;
     asm volatile("" : "+s"(zero));
-    dense_body<EXPOSE, PAGED, true, false, false>(a, ns, rem - h * ns, h, b, zero);
-    __syncthreads();  // the combine of this cell is read before the next cell's logits go into the same LDS
+    sh.have_k = false;
+    dense_body<EXPOSE, PAGED, true, NOV, false, true>(a, sh, h, b, T, zero);
+    P += t_b;
+    if (__builtin_amdgcn_readfirstlane(x1) >= start + (1 << kShareLg)) return;
+    do {  // (there is one: the list goes on)
+      ++b;
+    } while (is_slow != nullptr && is_slow[b * fs] == 0);
+    ++r;
+    L_in = ctx_len[b * ms];
+    __syncthreads();  // the combine of this sequence is read before the next one's logits go into the same LDS
   }
 }
 
@@ -1688,6 +1766,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a)
   if (a.mode == 0) n_slots = a.slots_slow;
   else if (a.mode == 1) n_slots = a.slots_fast;
   else n_slots = a.is_slow[b * a.fs] ? a.slots_slow : a.slots_fast;
+  if (a.mode == 0 && a.seq_rec != nullptr) n_slots = a.seq_rec[b];
   const bool dense = a.mode == 0 || (a.mode == 2 && a.is_slow[b * a.fs]);
   merge_records(a.part, a.out, bg, n_slots, dense ? a.jstat : nullptr, a.G, a.alpha, a.out_bf16 != 0);
 }
@@ -1747,9 +1826,18 @@ hipError_t launch_trigger(const int32_t* last_token, const uint32_t* bitmap, int
 
 template <bool PAGED>
 static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
-  if (a.item_batch > 0) {  // ragged step (logits always exposed, never the big stash, never evidence-only)
-    if (a.with_knorm) hipLaunchKernelGGL((attn_dense_items_kernel<2, PAGED>), grid, dim3(kAttnThreads), 0, s, a);
-    else hipLaunchKernelGGL((attn_dense_items_kernel<1, PAGED>), grid, dim3(kAttnThreads), 0, s, a);
+  if (a.plan_batch > 0) {
+    const dim3 pgrid(std::max(a.plan_wgs, a.plan_even * a.plan_batch), a.Hkv);
+    const uint32_t strides = (uint32_t)a.ms | (uint32_t)a.fs << 16;
+#define SFI_PLANNED(EXPOSE, NOV)                                                                                             \
+  hipLaunchKernelGGL((attn_dense_planned_kernel<EXPOSE, PAGED, NOV>), pgrid, dim3(kAttnThreads), 0, s, a.ctx_len, a.is_slow, \
+                     a.q_len, strides, a.plan_batch, a.plan_wgs, 1.0f / (float)a.plan_min, a.n_sink, a.recent, a.len_cap, a)
+    if (a.logits == nullptr) SFI_PLANNED(0, false);
+    else if (a.no_v && a.with_knorm) SFI_PLANNED(2, true);
+    else if (a.no_v) SFI_PLANNED(1, true);
+    else if (a.with_knorm) SFI_PLANNED(2, false);
+    else SFI_PLANNED(1, false);
+#undef SFI_PLANNED
     return;
   }
   if constexpr (!PAGED) {
@@ -1776,8 +1864,7 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
     hipLaunchKernelGGL((attn_dense_kernel<0, PAGED>), grid, dim3(kAttnThreads), 0, s, a);
 }
 hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
-  // ragged step: a fixed number of workgroups (no more than there are cells)
-  const dim3 grid = a.item_batch > 0 ? dim3((unsigned)min((int64_t)n_slots * a.Hkv * B, (int64_t)a.item_wgs)) : dim3(n_slots, a.Hkv, B);
+  const dim3 grid(n_slots, a.Hkv, B);
   if (a.table != nullptr) launch_dense_t<true>(a, grid, s);
   else launch_dense_t<false>(a, grid, s);
   return hipGetLastError();

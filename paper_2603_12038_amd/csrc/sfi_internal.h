@@ -67,7 +67,7 @@ __device__ __forceinline__ void window_view(const int32_t* q_len, int b, int L_e
   }
 }
 
-constexpr int kListCap = 1024;  // sequences the ragged step's dense launch can plan for on the device (see attn_dense_items_kernel)
+constexpr int kListCap = 1024;  // sequences a dense launch is planned on the device for (attn_dense_planned_kernel)
 
 struct Workspace {
   float* part;        // [B*Hq][kSlotCap][kPartStride]
@@ -78,6 +78,7 @@ struct Workspace {
   uint32_t* state;    // [B*Hkv][kStateWords]
   uint32_t* segcnt;   // [B*Hkv][n_seg_cap]  keys of each segment above the threshold bin
   int32_t* slow_list;   // [4 + 4 * B]  ragged step: the slow sequences as the dense launch planned them (see SelArgs)
+  int32_t* seq_rec;     // [B]  records per query head a planned dense launch left for each sequence
   float2* jstat;      // [B*Hq]  J-only softmax statistics of each query head (slow step)
   float* prior;       // [B*Hkv][ld]  full Selector: unnormalised prior pi_kn * pi_pos
   float* fbuf;        // [B*Hkv][ld]  full Selector: evidence f
@@ -102,10 +103,11 @@ struct AttnArgs {
   const int32_t* ctx_len;
   int32_t ms, fs;                // strides of the per-sequence entries: ctx_len / recent_start in int32, is_slow in bytes
                                  //   (1, 1 for plain arrays; 4, 16 when they are fields of a packed sfi_step_desc array)
-  int32_t item_batch;            // dense mode, ragged step: > 0 = the launch is a fixed number of workgroups that deal the
-                                 //   slow sequences' cells among themselves (attn_dense_items_kernel); the batch size
-  int32_t item_wgs;              //   ... and that number of workgroups
-  int32_t* slow_list;            //   ... and where the plan is left for the Selector's launches (see SelArgs)
+  int32_t plan_batch;            // dense mode: > 0 = the launch plans itself on the device (attn_dense_planned_kernel); the batch
+  int32_t plan_wgs, plan_min;    //   ... workgroups per KV head; fewest tiles a workgroup takes
+  int32_t plan_even;             //   ... workgroups per pair if all sequences turn out equally long (0: do not look)
+  int32_t* slow_list;            //   ... where the plan is left for the Selector's launches (see SelArgs), or nullptr
+  int32_t* seq_rec;              //   ... records per query head of each sequence, [batch]
   const int32_t* q_len;          // dense mode, nullptr or: rows each sequence's query sees (window query under the causal mask)
   const int32_t* recent_start;   // gather mode
   const int32_t* sel_idx;        // gather mode
@@ -173,6 +175,7 @@ struct MergeArgs {
   int32_t Hq, slots_slow, slots_fast;  // slot counts for slow / fast sequences
   int32_t mode;                        // 0: all sequences use slots_slow, 1: all use slots_fast, 2: per is_slow
   float2* jstat;                       // dense records: also leave the J-only softmax statistics here (may be null)
+  const int32_t* seq_rec;              // mode 0, nullptr or: records of each sequence (planned dense launch), not slots_slow
   int32_t G;                           // query heads per KV head
   float alpha;                         // power-mean exponent of the evidence (Eq. selector_mu)
   int32_t out_bf16;                    // out is bf16
@@ -191,6 +194,7 @@ struct SelArgs {
   const int32_t* q_len;    // accumulation of a window query under the causal mask (see window_view), else nullptr
   const int32_t* slow_list;  // ragged step with the planned dense launch, else nullptr: [0] number of slow sequences, then
                              //   from word 4 on { sequence, ctx_len (clamped), records per query head, 0 } for each
+  const int32_t* seq_rec;  // nullptr (n_rec) or: records per query head of each sequence (planned dense launch)
   int32_t ms, fs;          // strides of ctx_len (int32) and is_slow (bytes), see AttnArgs
   const uint8_t* is_slow;
   int32_t* sel_idx;

@@ -1,34 +1,10 @@
 // Merge of split records into the attention output (device function, one workgroup per output row).
 #pragma once
 #include "sfi_internal.h"
+#include "sfi_wave.h"
 
 namespace sfi {
 
-template <int CTRL>
-__device__ __forceinline__ float row_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-// Maximum / sum of a float over the wave in every lane (fixed order).
-__device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, row_move<0x128>(v));
-  v = fmaxf(v, row_move<0x124>(v));
-  v = fmaxf(v, row_move<0x122>(v));
-  v = fmaxf(v, row_move<0x121>(v));
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float wave_sum_f(float v) {
-  v += row_move<0x128>(v);
-  v += row_move<0x124>(v);
-  v += row_move<0x122>(v);
-  v += row_move<0x121>(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
 constexpr int kMergeThreads = 256;
 constexpr int kMergeLanes = 8;
 static_assert(kSlotCap <= 64, "one record header per lane of a wave");

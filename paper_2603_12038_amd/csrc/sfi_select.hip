@@ -25,50 +25,14 @@
 // prefix sums and reductions over a wave run on the vector ALU (row shifts) instead of the LDS crossbar.
 #include "sfi_internal.h"
 #include "sfi_merge.h"
+#include "sfi_wave.h"
 
 namespace sfi {
 
 __device__ __forceinline__ float fast_exp2s(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2s(float x) { return __builtin_amdgcn_logf(x); }
 
-// ---- wave and block primitives -----------------------------------------------------------------
-// Inclusive prefix sum over the 64 lanes: shifts within the rows of 16, then the row totals handed on.
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-#define SFI_SCAN(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false)
-  SFI_SCAN(0x111, 0xf);  // row_shr:1
-  SFI_SCAN(0x112, 0xf);  // row_shr:2
-  SFI_SCAN(0x114, 0xf);  // row_shr:4
-  SFI_SCAN(0x118, 0xf);  // row_shr:8
-  SFI_SCAN(0x142, 0xa);  // row_bcast:15 into rows 1, 3
-  SFI_SCAN(0x143, 0xc);  // row_bcast:31 into rows 2, 3
-#undef SFI_SCAN
-  return v;
-}
-// Sum over the wave, the same in every lane.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63); }
-// The same for a double (two registers moved alike).
-template <int CTRL>
-__device__ __forceinline__ double row_move(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-__device__ __forceinline__ double wave_sum_d(double v) {
-  v += row_move<0x128>(v);
-  v += row_move<0x124>(v);
-  v += row_move<0x122>(v);
-  v += row_move<0x121>(v);
-  uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-  v = __builtin_bit_cast(double, (uint64_t)h[0] << 32 | l[0]) + __builtin_bit_cast(double, (uint64_t)h[1] << 32 | l[1]);
-  u = __builtin_bit_cast(uint64_t, v);
-  const auto l2 = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
-  const auto h2 = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-  return __builtin_bit_cast(double, (uint64_t)h2[0] << 32 | l2[0]) + __builtin_bit_cast(double, (uint64_t)h2[1] << 32 | l2[1]);
-}
-
+// ---- block primitives -----------------------------------------------------------------
 // Exclusive prefix sum of one value per thread over an NT-thread block; returns the exclusive
 // prefix and leaves the block total in *total.  scratch: NT / 64 words of LDS that nobody still reads.  One barrier.
 template <int NT>
@@ -145,7 +109,7 @@ __device__ __forceinline__ Cell cell_of(const SelArgs& a, int r) {
   } else {
     c.b = r;
     c.L_in = a.ctx_len[r * a.ms];
-    c.n_rec = a.n_rec;
+    c.n_rec = a.seq_rec != nullptr ? a.seq_rec[r] : a.n_rec;
   }
   c.bh = c.b * a.Hkv + (int)blockIdx.y;
   return c;
@@ -160,7 +124,7 @@ __device__ __forceinline__ uint32_t ksel_of(const SelArgs& a, int nJ) { return (
 // Uniform arguments every kernel here reads, asked for at once.
 __device__ __forceinline__ void ask(const SelArgs& a) {
   asm volatile("" ::"s"(a.slow_list), "s"(a.ctx_len), "s"(a.is_slow), "s"(a.ms), "s"(a.fs), "s"(a.Hkv), "s"(a.len_cap), "s"(a.recent),
-               "s"(a.n_sink), "s"(a.n_rec), "s"(a.ld_pos), "s"(a.keys), "s"(a.budget));
+               "s"(a.n_sink), "s"(a.n_rec), "s"(a.seq_rec), "s"(a.ld_pos), "s"(a.keys), "s"(a.budget));
 }
 // Runs body(cell, thread index) for the workgroup's cells; a cell's LDS is free for the next behind a barrier.
 template <bool LIST, typename F>
