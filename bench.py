@@ -272,7 +272,7 @@ def bench_serving(args):
                                f"k{w.budget} R{w.recent} sink{w.n_sink}, per-sequence slow gaps ~ Geometric(1/20)",
                    "step": f"{SEG} decode steps (sfi_mixed_step) x {NL} virtual layers", "virtual_layers": NL,
                    "launch": "graph", "mixed_dense": args.mixed_dense, "slow_sequence_steps_in_timed_region": n_slow},
-        "roofline": {"bound": "hbm", "kernel": "sfi::attn_gather_stream_kernel (all-fast step)", "achieved": fast_gbs,
+        "roofline": {"bound": "hbm", "kernel": "sfi::attn_gather_kernel (all-fast step)", "achieved": fast_gbs,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": fast_gbs / HBM_PEAK_GBS, "traffic": None,
                      "algorithmic_bytes_per_launch": fast_bytes, "us_per_launch": gather_us},
         "whole_run_kv_GBps": kv / wall / 1e9, "whole_run_frac_of_8TBps": kv / wall / 1e9 / HBM_PEAK_GBS,
@@ -349,7 +349,7 @@ def bench_retention(args):
         "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": f"kernel table shape: B{B} Hq{Hq} Hkv{Hkv} d{d} KV length {L}, recent {R}, sink {n_sink}",
                    "virtual_layers": NL, "timing": "dense kernel + merge vs gather kernel + merge, HIP events"},
-        "roofline": {"bound": "hbm", "kernel": "sfi::attn_dense_kernel<0> + merge", "achieved": dense_bytes / (dense_us * 1e-6) / 1e9,
+        "roofline": {"bound": "hbm", "kernel": "sfi::attn_dense_planned_kernel<0> (merge included)", "achieved": dense_bytes / (dense_us * 1e-6) / 1e9,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dense_bytes / (dense_us * 1e-6) / 1e9 / HBM_PEAK_GBS,
                      "traffic": None},
         "table": rows, "device_status": sfi.sfi_device_status(ctx.handle), "cpu_baseline": None,
@@ -758,7 +758,7 @@ def bench_mix(args):
     # HBM bytes per launch: from the committed counter profile of this workload, if it was taken on these kernel sources
     traffic, traffic_source = None, "not measured in this run (counters need the profiler); no committed counter profile of this workload"
     if args.workload == "llama8b" and args.ctx == 32768 and args.batch == 4 and not compact:
-        traffic, traffic_source = committed_traffic("attn_gather_stream_kernel" if dominant != "dense" else "attn_dense_kernel")
+        traffic, traffic_source = committed_traffic("attn_gather_kernel" if dominant != "dense" else "attn_dense_planned_kernel")
     # The floor of the fast-step launch: its memory skeleton (same grid, scalars, indices and row loads, same record
     # hand-over, no arithmetic), timed the same way, and the shorter chains underneath it.
     floor = None
@@ -791,7 +791,7 @@ def bench_mix(args):
                        "attention_and_merge_with_logits_us": float(graph_avg_ms(
                            lambda l, step: sfi.sfi_slow_attn(h, q_all[step, l], Ks[l], Vs[l], ctx_d, max_ctx, outs[l]), 2) * 1e3)}
     roof = {
-        "bound": "hbm", "kernel": f"sfi::attn_{dominant}_kernel",
+        "bound": "hbm", "kernel": f"sfi::attn_{dominant}_kernel" if dominant != "dense" or args.batch == 1 else "sfi::attn_dense_planned_kernel",
         "achieved": fast_gbs if dominant != "dense" else dense_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": (fast_gbs if dominant != "dense" else dense_gbs) / HBM_PEAK_GBS, "traffic": traffic,
         "traffic_source": traffic_source,
@@ -810,10 +810,6 @@ def bench_mix(args):
     device_status = 0
     for c in ring:
         device_status |= sfi.sfi_device_status(c.handle)
-    # fewer workgroups per pair than one tile per wave needs: the pipelined gather kernel ran
-    fast_tiles = -(-(w.n_sink + w.budget + w.recent) // 32)
-    if not compact and fsp * 4 < fast_tiles and roof["kernel"] == "sfi::attn_gather_kernel":
-        roof["kernel"] = "sfi::attn_gather_stream_kernel"
     res = {
         "metric": "decode attn tokens/s (slow+fast mix)", "value": value, "unit": "tokens/s per attention layer",
         "n_gpus": 1, "steps": K_seg, "warmup": W_seg, "ms_per_step": total_s * 1e3 / K_seg,

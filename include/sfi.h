@@ -391,7 +391,7 @@ int sfi_stage_times(sfi_ctx* ctx, float* ms_sum /* host, [SFI_N_STAGES] */, int3
  *                      evenly (one workgroup per compute unit, all resident at once, where the pairs
  *                      divide the compute units);
  * fast_tiles_per_wave  32-row tiles each wave of the gather launch gets.  Default: decided per launch by
- *                      the same rule -- one tile per wave (one-tile kernel) or several (pipelined loop);
+ *                      the same rule -- one tile per wave or several (pipelined loop);
  * fast_merge           how the split records of a fast step become the output: 1 (default) inside the
  *                      attention kernel, by the last workgroup of each (sequence, KV head) to finish;
  *                      2 in a merge launch of its own.  Other values > 2: SFI_EINVAL. */
