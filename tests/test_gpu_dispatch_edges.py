@@ -1,0 +1,101 @@
+"""GPU parity at the sizes where the launches change: the Selector's forms (one workgroup per pair that scores as well, one
+that reads keys, segments with histograms of their own), the dense launch planned on the device (equal and unequal
+lengths, more sequences than lanes, empty contexts, the most records one sequence can have) and the fast step's merge by
+one to four waves.  The bars are the library's own: outputs within 2e-3 row-relative of the fp64 oracle (bf16 inputs,
+probabilities kept as two bf16 terms), index sets identical outside the 1e-5 band of tied scores."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import sfi_synth as syn
+from helpers import Runner, check_out, check_selection
+from oracle.sfi_oracle import SelectorParams
+
+pytestmark = pytest.mark.gpu
+
+N_SINK, RECENT = 4, 64
+
+
+def _workload(B, Hkv, G, lens, budget, seed):
+    w = syn.make_tiny(L0=max(int(max(lens)), RECENT + 16), steps=3, budget=budget, recent=RECENT, n_support=4, B=B, Hq=G * Hkv,
+                      Hkv=Hkv, seed=seed)
+    w.n_sink = N_SINK
+    w.L0 = np.array(lens, np.int32)
+    return w
+
+
+def _check_slow(oracle, w, r, sp=None):
+    q, c = w.q(0), w.ctx_len(0)
+    out, sel, nsel = r.slow(q, c, w.budget, max_len=int(c.max()))
+    check_out(out, oracle.dense(q, w.K, w.V, c))
+    kw = {} if sp is None else dict(sp=sp)
+    sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, w.budget, w.n_sink, w.recent, **kw)
+    check_selection(sel, nsel, sel_ref, nsel_ref, z, c, w.n_sink, w.recent, w.budget)
+    return sel, nsel
+
+
+# |J| on either side of 4096, 8192 and 16384 positions, and of 24576 logits per pair; head groups around the built sizes
+@pytest.mark.parametrize("n_j,G", [(0, 4), (1, 4), (4096, 5), (4097, 5), (4097, 8), (3072, 8), (3073, 8), (1536, 16), (1537, 16),
+                                   (4915, 5), (4916, 5), (6144, 4), (6145, 4), (8192, 3), (8193, 1), (16384, 2), (16385, 2),
+                                   (18433, 7)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_selector_where_its_form_changes(oracle, n_j, G, mode):
+    print(f"[gpu-edges] selector mode {mode}: |J| = {n_j}, G = {G}", flush=True)
+    w = _workload(1, 2, G, [n_j + N_SINK + RECENT], 129, seed=4000 + n_j + G)
+    sp, d = None, None
+    if mode == 1:
+        sp = dataclasses.replace(SelectorParams(mode=1), alpha=1.0)
+        d = {k: getattr(sp, k) for k in ("gamma", "beta", "p", "eta", "lambda_clip", "alpha_soft", "alpha_cross", "temp", "eps",
+                                          "nms_radius")}
+    r = Runner(w, selector=d, alpha=1.0 if d else 0.0)
+    try:
+        _check_slow(oracle, w, r, sp)
+    finally:
+        r.close()
+
+
+PLANNED = {
+    "equal": (8, 8, 4, [4100] * 8),
+    "one long, the others short": (8, 8, 4, [4133] + [33, 64, 65, 1, 100, 97, 31]),
+    "empty contexts among them": (8, 8, 2, [0, 4097, 0, 2000, 3000, 0, 1, 4096]),
+    "unequal": (8, 8, 5, [1024, 4096, 2500, 3333, 1111, 2048, 4095, 3900]),
+    "more sequences than lanes": (65, 4, 2, [1100 - 13 * (i % 40) for i in range(64)] + [1]),
+    "more sequences than lanes, equal": (65, 4, 2, [1060] * 65),
+    "most records per sequence": (2, 2, 2, [65536, 33]),
+    "heads that do not divide the units": (9, 6, 3, [5000 - 431 * i for i in range(9)]),
+}
+
+
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("name", list(PLANNED))
+def test_planned_dense_launch(oracle, name, page):
+    B, Hkv, G, lens = PLANNED[name]
+    print(f"[gpu-edges] planned dense launch: {name}, page {page}", flush=True)
+    w = _workload(B, Hkv, G, lens, 65, seed=77 + len(name))
+    r = Runner(w, page_size=page)
+    try:
+        q, c = w.q(0), w.ctx_len(0)
+        check_out(r.dense(q, c, max_len=int(c.max())), oracle.dense(q, w.K, w.V, c))
+        _check_slow(oracle, w, r)
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("tiles_per_wave", [1, 33])
+def test_fast_step_merge(oracle, G, tiles_per_wave):
+    """One workgroup per pair (33 tiles per wave) and as many as the list has tiles for (1), twice on one context: the
+    arrival counters have to be back at zero after the first."""
+    print(f"[gpu-edges] fast step: G = {G}, {tiles_per_wave} tiles per wave", flush=True)
+    w = _workload(2, 2, G, [2500, 1999], 777, seed=900 + G)
+    r = Runner(w)
+    try:
+        sel, nsel = _check_slow(oracle, w, r)
+        r.sfi.sfi_set_tuning(r.ctx.handle, -1, tiles_per_wave, 1)
+        for t in (1, 2):
+            q, c, rs = w.q(t), w.ctx_len(t), w.recent_start(t)
+            check_out(r.fast(q, sel, nsel, rs, c), oracle.sparse(q, w.K, w.V, sel, nsel, rs, c, w.n_sink))
+    finally:
+        r.close()

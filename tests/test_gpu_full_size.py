@@ -1,6 +1,6 @@
 """GPU parity at the baseline configurations' full sizes, in the launch configuration bench.py times.
 
-The oracle finishes most of these sizes in about a second per step on the GPU machine's host cores, so every
+The oracle finishes most of these sizes in about a second per step on sixteen host cores, so every
 output element and every index set is compared; the full serving batch (32 ragged sequences of up to 65536
 rows) is the exception: the GPU computes all of it, the oracle checks every sequence's fast steps and a sample
 of the dense ones, named in the test."""
