@@ -1848,10 +1848,14 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
       return;
     }
   }
-  if (a.logits != nullptr && a.no_v && a.with_knorm)  // evidence only (always with the big stash)
+  if (a.logits != nullptr && a.no_v && a.with_knorm && a.big_stash)  // (no_v: evidence only)
     hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, true, true>), grid, dim3(kAttnThreads), 0, s, a);
-  else if (a.logits != nullptr && a.no_v)
+  else if (a.logits != nullptr && a.no_v && a.with_knorm)
+    hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, false, true>), grid, dim3(kAttnThreads), 0, s, a);
+  else if (a.logits != nullptr && a.no_v && a.big_stash)
     hipLaunchKernelGGL((attn_dense_kernel<1, PAGED, true, true>), grid, dim3(kAttnThreads), 0, s, a);
+  else if (a.logits != nullptr && a.no_v)
+    hipLaunchKernelGGL((attn_dense_kernel<1, PAGED, false, true>), grid, dim3(kAttnThreads), 0, s, a);
   else if (a.logits != nullptr && a.with_knorm && a.big_stash)
     hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);
   else if (a.logits != nullptr && a.with_knorm)

@@ -99,3 +99,40 @@ def test_fast_step_merge(oracle, G, tiles_per_wave):
             check_out(r.fast(q, sel, nsel, rs, c), oracle.sparse(q, w.K, w.V, sel, nsel, rs, c, w.n_sink))
     finally:
         r.close()
+
+
+# evidence alone (no output), split over two workgroups per compute unit where a wave's share fits the small stash
+@pytest.mark.parametrize("B,Hkv,G,lens", [(2, 8, 4, [4200, 700]), (2, 8, 16, [9000, 8990]), (2, 8, 15, [4097, 33]), (1, 8, 4, [2000]),
+                                          (9, 8, 5, [1500] * 8 + [70]), (1, 8, 1, [131])])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("page", [0, 16])
+def test_evidence_of_a_window(oracle, B, Hkv, G, lens, mode, page):
+    import torch
+    from helpers import i32_dev, to_dev
+    print(f"[gpu-edges] evidence: B={B} Hkv={Hkv} G={G} {lens} mode={mode} page={page}", flush=True)
+    W = 3
+    w = _workload(B, Hkv, G, lens, 65, seed=300 + G + mode)
+    sp = dataclasses.replace(SelectorParams(mode=mode), alpha=1.0)
+    d = {k: getattr(sp, k) for k in ("gamma", "beta", "p", "eta", "lambda_clip", "alpha_soft", "alpha_cross", "temp", "eps",
+                                      "nms_radius")} if mode else None
+    r = Runner(w, selector=d, alpha=1.0, page_size=page)
+    try:
+        ctx = w.ctx_len(0)
+        ctx_d = i32_dev(ctx)
+        sel = torch.full((B, Hkv, w.budget), -7, dtype=torch.int32, device="cuda")
+        nsel = torch.full((B, Hkv), -7, dtype=torch.int32, device="cuda")
+        vis = np.zeros((B, Hkv * W * G), np.int32)
+        q_cat = np.empty((B, Hkv * W * G, w.d), np.uint16)
+        for t in range(W):
+            q, q_len = w.q(t), (ctx - W + t + 1).astype(np.int32)
+            r.sfi.sfi_evidence_add_causal(r.ctx.handle, to_dev(q), r.K, None, ctx_d, i32_dev(q_len), int(ctx.max()), None, t == 0)
+            for h in range(Hkv):
+                q_cat[:, h * W * G + t * G:h * W * G + (t + 1) * G] = q[:, h * G:(h + 1) * G]
+                vis[:, h * W * G + t * G:h * W * G + (t + 1) * G] = q_len[:, None]
+        r.sfi.sfi_evidence_select(r.ctx.handle, W, ctx_d, int(ctx.max()), w.budget, sel, nsel)
+        torch.cuda.synchronize()
+        sel_ref, nsel_ref, z = oracle.selector(q_cat, w.K, ctx, w.budget, w.n_sink, w.recent, sp=sp, vis=vis)
+        check_selection(sel.cpu().numpy(), nsel.cpu().numpy(), sel_ref, nsel_ref, z, ctx, w.n_sink, w.recent, w.budget)
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
