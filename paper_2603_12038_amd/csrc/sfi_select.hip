@@ -178,7 +178,8 @@ __device__ __forceinline__ void add_evidence(float (&f)[4], const float4& l, flo
   f[3] += c * fast_exp2s(al * (l.w - M));
 }
 // mu of NQ quads of positions p[q]: sum over heads of sc[g] 2^(alpha (y_g - sM[g])) (Eq. selector_mu).  GT >= G heads are
-// loaded, all at once and without a branch; the columns past G repeat the last head with weight 0 (sM, sc hold GT entries).
+// loaded, all at once and without a branch; the columns past G repeat the last head and count for nothing: weight 0 and a
+// maximum that makes their exponential 0 (0 times an exponential that overflowed would be NaN).  sM, sc hold GT entries.
 template <int NQ, int GT>
 __device__ __forceinline__ void request_logits(float4 (&lq)[NQ][GT], const float* lg, int rows, int G, const int (&p)[NQ]) {
 #pragma unroll
@@ -204,7 +205,7 @@ template <int GT>
 __device__ __forceinline__ void group_stats(const SelArgs& a, const Cell& c, int n_waves, float* sM, float* sc) {
   const int tid = threadIdx.x;
   if (tid >= a.G && tid < GT) {
-    sM[tid] = 0.f;
+    sM[tid] = -kNeg;
     sc[tid] = 0.f;
   }
   if (a.part != nullptr) {
