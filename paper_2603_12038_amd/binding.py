@@ -13,6 +13,7 @@ from typing import Optional, Tuple
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsfi.so")
+PY_LIB_PATH = os.path.join(HERE, "_sfi.so")
 
 SFI_N_STAGES = 8
 STAGE_NAMES = ("attn", "merge", "score", "cand", "count", "write", "attn_gather_mixed", "reorg")
@@ -126,19 +127,19 @@ def load_library() -> C.CDLL:
 
 
 def _load_hot():
-    """The CPython module _sfi.so, bound to torch's current-stream lookup; raises if it has not been built."""
+    """The CPython module _sfi.so, bound to the loaded library and torch's current-stream lookup; raises if it has not been built."""
     global _hot
     if _hot is None:
         import torch
 
-        load_library()
-        try:
-            from . import _sfi
-        except ImportError as e:
-            raise FileNotFoundError("_sfi.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'`") from e
+        lib = load_library()
+        if not os.path.exists(PY_LIB_PATH):
+            raise FileNotFoundError(f"{PY_LIB_PATH} is not built: run `python -c 'import __graft_entry__ as g; g.build()'`")
+        from . import _sfi
         if torch.cuda.is_available():
             torch.cuda.init()
-        _sfi.bind(SfiError, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _sfi.bind(SfiError, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+                  {name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS})
         _hot = _sfi
     return _hot
 

@@ -39,10 +39,10 @@ def build_lib(verbose: bool = False) -> str:
 
 
 def build_py_module() -> str:
-    """The hot calls as a CPython module (host code only), linked to libsfi.so beside it."""
+    """The hot calls as a CPython module (host code only); it gets libsfi's entry points from binding.py, not from the linker."""
     cxx = os.environ.get("CXX", "g++")
     cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
-           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "sfi_py.cpp"), LIB, "-Wl,-rpath,$ORIGIN", "-o", PY_LIB]
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "sfi_py.cpp"), "-o", PY_LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"{cxx} failed:\n" + r.stderr)

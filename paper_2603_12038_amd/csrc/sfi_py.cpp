@@ -78,6 +78,7 @@ T convert(PyObject* o, bool stream) {
 template <typename... P, size_t... I>
 PyObject* call(int (*fn)(P...), const char* where, PyObject* const* args, Py_ssize_t n, std::index_sequence<I...>) {
   constexpr size_t N = sizeof...(P);
+  if (fn == nullptr) return PyErr_Format(PyExc_RuntimeError, "%s: bind() has not been called", where);
   if (n != (Py_ssize_t)N) return PyErr_Format(PyExc_TypeError, "%s takes %zu arguments, got %zd", where, N, n);
   std::tuple<P...> a{convert<P>(args[I], I == N - 1)...};  // braces: left to right
   if (PyErr_Occurred()) return nullptr;
@@ -103,15 +104,28 @@ PyObject* call(int (*fn)(P...), const char* where, PyObject* const* args, Py_ssi
   X(sfi_evidence_select) X(sfi_dense_attn) X(sfi_fast_step) X(sfi_fast_step_static) X(sfi_reorg) X(sfi_fast_step_compact) \
   X(sfi_mixed_step) X(sfi_mixed_step_compact) X(sfi_step_begin) X(sfi_mixed_step_desc) X(sfi_trigger) X(sfi_advance)
 
-#define X(name) \
-  PyObject* py_##name(PyObject*, PyObject* const* args, Py_ssize_t n) { return call(&name, #name, args, n); }
+// The entry points, handed over by bind: this module is not linked to libsfi, so it works on the very library that
+// binding.py has loaded, wherever the package lies and whatever other copies of it are in the process.
+#define X(name)                      \
+  decltype(&name) fn_##name = nullptr; \
+  PyObject* py_##name(PyObject*, PyObject* const* args, Py_ssize_t n) { return call(fn_##name, #name, args, n); }
 HOT_CALLS(X)
 #undef X
 
-// bind(error class, current-device function, raw-stream function): called once by binding.py
+// bind(error class, current-device function, raw-stream function, {entry point: address}): called once by binding.py
 PyObject* bind(PyObject*, PyObject* args) {
-  PyObject *e, *d, *s;
-  if (!PyArg_ParseTuple(args, "OOO", &e, &d, &s)) return nullptr;
+  PyObject *e, *d, *s, *fns;
+  if (!PyArg_ParseTuple(args, "OOOO!", &e, &d, &s, &PyDict_Type, &fns)) return nullptr;
+#define X(name)                                                                                            \
+  {                                                                                                        \
+    PyObject* at = PyDict_GetItemString(fns, #name);                                                       \
+    const uint64_t v = at != nullptr ? to_word(at) : 0;                                                    \
+    if (PyErr_Occurred()) return nullptr;                                                                  \
+    if (v == 0) return PyErr_Format(PyExc_KeyError, "no address of %s", #name);                            \
+    fn_##name = reinterpret_cast<decltype(fn_##name)>(v);                                                  \
+  }
+  HOT_CALLS(X)
+#undef X
   Py_INCREF(e); Py_INCREF(d); Py_INCREF(s);
   Py_XSETREF(g_error, e);
   Py_XSETREF(g_get_device, d);
