@@ -38,8 +38,16 @@ void* to_pointer(PyObject* o) {
   if (PyLong_Check(o)) return reinterpret_cast<void*>(to_word(o));
   PyObject* p = PyObject_CallMethodNoArgs(o, g_data_ptr);
   if (p == nullptr && PyErr_ExceptionMatches(PyExc_AttributeError)) {  // a ctypes pointer (a context handle, say)
-    PyErr_Clear();
+    PyObject *type, *value, *trace;
+    PyErr_Fetch(&type, &value, &trace);
     p = PyObject_GetAttr(o, g_value);
+    if (p == nullptr) {  // neither: the error that names data_ptr
+      PyErr_Restore(type, value, trace);
+      return nullptr;
+    }
+    Py_XDECREF(type);
+    Py_XDECREF(value);
+    Py_XDECREF(trace);
     if (p == Py_None) {
       Py_DECREF(p);
       return nullptr;
@@ -69,8 +77,10 @@ void* to_stream(PyObject* o) {
   return v;
 }
 
+// (an argument behind one that failed is not looked at: no Python code runs with an exception pending)
 template <typename T>
 T convert(PyObject* o, bool stream) {
+  if (PyErr_Occurred() != nullptr) return T{};
   if constexpr (std::is_pointer_v<T>) return reinterpret_cast<T>(stream ? to_stream(o) : to_pointer(o));
   else return static_cast<T>(to_word(o));
 }
