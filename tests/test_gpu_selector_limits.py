@@ -83,3 +83,65 @@ def test_columns_beyond_the_last_head_count_for_nothing(oracle, n_j, G, mode):
         _check_window(oracle, w, r, sp, queries, band=BAND[mode])
     finally:
         r.close()
+
+
+# |J| = 20000 and 16900: ten and nine segments of 2048 positions.  The tie class spans three of them and is larger than any.
+@pytest.mark.parametrize("case", ["random", "ties", "all_equal"])
+def test_long_form_takes_ties_by_index_across_segments(oracle, case):
+    w = _workload(2, 2, 4, [20000 + N_SINK + RECENT, 16900 + N_SINK + RECENT], 700, seed=91)
+    if case == "ties":
+        w.K[:, :, 3000:7200] = w.K[:, :, 3000:3001]
+    if case == "all_equal":
+        w.K[:] = 0
+    r = Runner(w, max_budget=20100)
+    try:
+        q, c = w.q(0), w.ctx_len(0)
+        for budget in (700, 1, 64, 2500, 16900, 20100):
+            print(f"[gpu-limits] long form, {case}, budget {budget}", flush=True)
+            sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, budget, w.n_sink, w.recent)
+            _, sel, nsel = r.slow(q, c, budget, max_len=int(c.max()))
+            check_selection(sel, nsel, sel_ref, nsel_ref, z, c, w.n_sink, w.recent, budget)
+            if case == "all_equal":
+                for b in range(w.B):
+                    k = int(nsel[b, 0])
+                    assert (sel[b, :, :k] == N_SINK + np.arange(k)).all()
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
+
+
+# Logits of standard deviation 19 (scale 1.6): the 1200th best of 20000 positions has a weight of 2^-67 and less, below the
+# histogram's range, whose lowest bin holds keys of any magnitude.  The oracle ranks by log(f + eps) with eps far below
+# every weight.  Band: |y| stays below 256, where half an ulp is 7.6e-6; eight roundings of the logit, its scaling and the
+# subtraction of the maximum, in log2, for a score and the one it is compared with: 2 * 10 * 7.6e-6 * ln 2.
+@pytest.mark.parametrize("budget", [300, 1200, 4000])
+def test_long_form_threshold_below_the_histograms_range(oracle, budget):
+    print(f"[gpu-limits] threshold below the histogram's range, budget {budget}", flush=True)
+    w = _workload(1, 2, 1, [20000 + N_SINK + RECENT], budget, seed=17)
+    w.K[:, :, :] = syn.normal_bf16(np.random.default_rng(5), w.K.shape)
+    sp = dataclasses.replace(SelectorParams(mode=0), eps=1e-300)
+    r = Runner(w, scale=1.6)
+    try:
+        q, c = w.q(0), w.ctx_len(0)
+        sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, budget, w.n_sink, w.recent, sp=sp, scale=1.6)
+        kth = [np.sort(z[0, h, N_SINK:N_SINK + 20000])[-budget] / np.log(2.0) for h in range(w.Hkv)]
+        assert all(-126 < t for t in kth) and (budget < 1200 or all(t < -63 for t in kth)), kth
+        _, sel, nsel = r.slow(q, c, budget, max_len=int(c.max()))
+        check_selection(sel, nsel, sel_ref, nsel_ref, z, c, w.n_sink, w.recent, budget, band=1.1e-4)
+    finally:
+        r.close()
+
+
+# 8 sequences of 8 KV heads and 8200 rows at most: 16576 tiles, from 16384 on the evidence-only launch is planned on the device
+@pytest.mark.parametrize("lens", [[8200, 6000, 7777, 5001, 8199, 4100, 7001, 8000], [8200] * 8], ids=["unequal", "equal"])
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_planned_launch_that_leaves_evidence_only(oracle, mode, page, lens):
+    print(f"[gpu-limits] planned evidence-only launch: mode {mode}, page {page}, {lens}", flush=True)
+    w = _workload(8, 8, 2, lens, 129, seed=300)
+    sp, d = _selector(mode)
+    r = Runner(w, selector=d, alpha=1.0, page_size=page)
+    try:
+        _check_window(oracle, w, r, sp, [w.q(t) for t in range(3)])
+    finally:
+        r.close()
