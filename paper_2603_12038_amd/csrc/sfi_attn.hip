@@ -1323,27 +1323,41 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
 __device__ __forceinline__ uint32_t fold16(const uint4& v) { return v.x ^ v.y ^ v.z ^ v.w; }
 
 //   depth  1: stop after the scalars and indices; 2: load nothing at all (the cost of the bare launch).
+// The leading arguments are the gather kernel's: they arrive in registers, and the scalars and the first indices are
+// requested from them before the arguments that come from memory are asked for.
 template <bool WIDE, bool TAIL, bool BURST>
-__global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor_kernel(const AttnArgs a, int tpw, int depth) {
+__global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor_kernel(const int32_t* sel_idx, const int32_t* n_sel_p,
+                                                                                        const int32_t* ctx_len_p, const int32_t* recent_start_p,
+                                                                                        const uint8_t*, const uint32_t sel_stride,
+                                                                                        const uint32_t shape, const int n_sink,
+                                                                                        const int n_split, const AttnArgs a, int tpw,
+                                                                                        int depth) {
   extern __shared__ uint4 s_rows[];  // BURST: [tpw][16 instructions][64 lanes]
   const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int jg = lane >> 4, n = lane & 15;
-  const int G = a.G;
-  const int bh = b * a.Hkv + h;
-  const int64_t head0 = (int64_t)b * a.Hq + h * G;
+  const int bh = b * (int)(shape & 0xffffu) + h;
+  const int bm = b << ((shape >> 16) & 15u);
   uint32_t fold = 0u;
   if (!TAIL && !BURST && depth == 2) {  // wave-uniform: the bare launch
+    const int64_t head0 = (int64_t)b * a.Hq + h * a.G;
     if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * a.slot_cap + slot) * kPartStride) + w] = (uint32_t)slot;
     return;
   }
-  const int L_in = a.ctx_len[b * a.ms], n_sel_in = a.n_sel[bh], rs_in = a.recent_start[b * a.ms];
+  const int p_first = (BURST ? slot * tpw + w : slot * kWaves + w) * kTile;
+  const int L_in = ctx_len_p[bm], n_sel_in = n_sel_p[bh], rs_in = recent_start_p[bm];
   ListWalk W;
-  W.sel = a.sel_idx + (int64_t)bh * a.sel_stride;
-  W.sel_cap = max((int)a.sel_stride - 1, 0);
-  W.n_sink = a.n_sink;
+  W.sel = sel_idx + (int64_t)bh * sel_stride;
+  W.sel_cap = max((int)sel_stride - 1, 0);
+  W.n_sink = n_sink;
   W.bad = 0;
+  const int sA0 = W.sel_at_nonempty(p_first + n), sB0 = W.sel_at_nonempty(p_first + 16 + n);
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(L_in), "s"(n_sel_in), "s"(rs_in), "s"(a.K), "s"(a.V), "s"(a.k_sb), "s"(a.k_sh), "s"(a.k_st), "s"(a.v_sb),
+               "s"(a.v_sh), "s"(a.v_st), "s"(a.Hq), "s"(a.G), "s"(a.len_cap));
+  const int G = a.G;
+  const int64_t head0 = (int64_t)b * a.Hq + h * G;
   Rows R;
   R.Kb = reinterpret_cast<const char*>(a.K + b * a.k_sb + h * a.k_sh);
   R.Vb = reinterpret_cast<const char*>(a.V + b * a.v_sb + h * a.v_sh);
@@ -1354,26 +1368,26 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
   R.jg = jg;
   R.n = n;
   if (!TAIL && !BURST && depth == 1) {  // wave-uniform: scalars and the first tile's indices, nothing else
-    const int first = slot * kWaves + w;
-    const int sA = W.sel_at_nonempty(first * kTile + n), sB = W.sel_at_nonempty(first * kTile + 16 + n);
-    fold = (uint32_t)(L_in ^ n_sel_in ^ rs_in ^ sA ^ sB);
+    fold = (uint32_t)(L_in ^ n_sel_in ^ rs_in ^ sA0 ^ sB0);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) fold ^= __shfl_xor(fold, d);
     if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * a.slot_cap + slot) * kPartStride) + w] = fold;
     return;
   }
   if (BURST) {
-    // indices of all of this wave's tiles first (rows n and 16 + n of each), then the scalars
+    // indices of all of this wave's tiles (rows n and 16 + n of each)
     constexpr int kMaxT = 4;  // tiles per wave: tpw <= 16
     int sA[kMaxT], sB[kMaxT];
+    sA[0] = sA0;
+    sB[0] = sB0;
 #pragma unroll
-    for (int k = 0; k < kMaxT; ++k) {
-      const int p0 = (slot * tpw + w + kWaves * k) * kTile;
+    for (int k = 1; k < kMaxT; ++k) {
+      const int p0 = p_first + kWaves * k * kTile;
       sA[k] = W.sel_at_nonempty(p0 + n);
       sB[k] = W.sel_at_nonempty(p0 + 16 + n);
     }
     const int L = guarded_len(L_in, a.len_cap, W.bad);
-    W.set_counts(L, n_sel_in, rs_in, (int)a.sel_stride);
+    W.set_counts(L, n_sel_in, rs_in, (int)sel_stride);
     const int nT = (W.N + kTile - 1) / kTile;
 #pragma unroll
     for (int k = 0; k < kMaxT; ++k) {
@@ -1406,16 +1420,15 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
       }
     }
   } else {
-    const int first = slot * kWaves + w, step = a.n_split * kWaves;
+    const int first = slot * kWaves + w, step = n_split * kWaves;
     const int pstep = step * kTile;
-    const int p_first = first * kTile;
-    const int sA = W.sel_at_nonempty(p_first + n), sB = W.sel_at_nonempty(p_first + 16 + n);
     const int L = guarded_len(L_in, a.len_cap, W.bad);
-    W.set_counts(L, n_sel_in, rs_in, (int)a.sel_stride);
+    W.set_counts(L, n_sel_in, rs_in, (int)sel_stride);
     Tile T;
     const int nT = (W.N + kTile - 1) / kTile;
-    const int K = first < nT ? (nT - first + step - 1) / step : 0;
-    int ra = W.row_of(p_first + n, sA), rb = W.row_of(p_first + 16 + n, sB);
+    asm volatile("" ::"s"(R.Kb), "s"(R.Vb), "s"(W.nS), "s"(W.nSel), "s"(W.rs), "s"(W.N), "s"(nT));  // as the kernel does
+    __builtin_amdgcn_sched_barrier(0);
+    int ra = W.row_of(p_first + n, sA0), rb = W.row_of(p_first + 16 + n, sB0);
     __builtin_amdgcn_sched_barrier(0);
     issue_k_rows<uint32_t, WIDE>(T, R, ra, rb);
     __builtin_amdgcn_sched_barrier(0);
@@ -1423,8 +1436,9 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
     __builtin_amdgcn_sched_barrier(0);
     issue_v_rows<uint32_t, WIDE>(T, R, ra, rb);
     __builtin_amdgcn_sched_barrier(0);
-    for (int k = 0; k + 1 < K; ++k) {
-      const int pn = p_first + (k + 1) * pstep;
+    int pn = p_first;
+    for (int t = first; t + step < nT; t += step) {  // (no division in front of the rows, as in the kernel)
+      pn += pstep;
 #pragma unroll
       for (int i = 0; i < 4; ++i) fold ^= fold16(T.ka[i]) ^ fold16(T.kb[i]);   // the K half is consumed ...
       ra = W.row_of(pn + n, sAn);
@@ -1436,7 +1450,7 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
       for (int i = 0; i < 8; ++i) fold ^= fold16(T.v[i]);                      // then the V half
       issue_v_rows<uint32_t, WIDE>(T, R, ra, rb);
     }
-    if (K > 0) {
+    if (first < nT) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) fold ^= fold16(T.ka[i]) ^ fold16(T.kb[i]);
 #pragma unroll
@@ -1457,6 +1471,13 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
   report_guard(a.guard, W.bad);
 }
 
+// The leading arguments of the gather kernel and its skeleton (gather_shape: see attn_gather_kernel).
+static uint32_t gather_shape(const AttnArgs& a) {
+  return (uint32_t)a.Hkv | (a.ms == 4 ? 2u << 16 : 0u) | (a.is_slow != nullptr ? 1u << 20 : 0u);
+}
+static const uint8_t* gather_flags(const AttnArgs& a) {  // (a readable byte in any case)
+  return a.is_slow != nullptr ? a.is_slow : reinterpret_cast<const uint8_t*>(a.ctx_len);
+}
 hipError_t launch_attn_gather_floor(const AttnArgs& a, int B, int n_slots, int tail, int burst, int tpw, int depth, hipStream_t s) {
   const dim3 grid(n_slots, a.Hkv, B);
   const size_t lds = burst ? (size_t)tpw * 16 * 64 * sizeof(uint4) : 0;
@@ -1465,7 +1486,9 @@ hipError_t launch_attn_gather_floor(const AttnArgs& a, int B, int n_slots, int t
     if (lds > 0 && hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_gather_floor_kernel<WIDE, TAIL, BURST>),   \
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)            \
       return hipGetLastError();                                                                                        \
-    hipLaunchKernelGGL((attn_gather_floor_kernel<WIDE, TAIL, BURST>), grid, dim3(kAttnThreads), lds, s, a, tpw, depth);       \
+    hipLaunchKernelGGL((attn_gather_floor_kernel<WIDE, TAIL, BURST>), grid, dim3(kAttnThreads), lds, s, a.sel_idx, a.n_sel,   \
+                       a.ctx_len, a.recent_start, gather_flags(a), (uint32_t)a.sel_stride, gather_shape(a), a.n_sink,          \
+                       a.n_split, a, tpw, depth);                                                                              \
   } while (0)
   const bool wide = a.G <= 8;
   if (wide && tail && burst) SFI_FLOOR(true, true, true);
@@ -1892,11 +1915,9 @@ hipError_t launch_reorg(const ReorgArgs& a, int B, int rows, hipStream_t s) {
 }
 hipError_t launch_attn_gather(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
   const dim3 grid(n_slots, a.Hkv, B), block(kAttnThreads);
-  const uint8_t* flags = a.is_slow != nullptr ? a.is_slow : reinterpret_cast<const uint8_t*>(a.ctx_len);
-  const uint32_t shape = (uint32_t)a.Hkv | (a.ms == 4 ? 2u << 16 : 0u) | (a.is_slow != nullptr ? 1u << 20 : 0u);
 #define SFI_GATHER(PAGED, WIDE)                                                                                             \
   hipLaunchKernelGGL((attn_gather_kernel<PAGED, WIDE>), grid, block, 0, s, a.sel_idx, a.n_sel, a.ctx_len, a.recent_start,  \
-                     flags, (uint32_t)a.sel_stride, shape, a.n_sink, a.n_split, a)
+                     gather_flags(a), (uint32_t)a.sel_stride, gather_shape(a), a.n_sink, a.n_split, a)
   if (a.G <= 8) {
     if (a.table != nullptr) SFI_GATHER(true, true);
     else SFI_GATHER(false, true);
