@@ -29,6 +29,8 @@ constexpr int kPriorSeg = 1024;     // positions per workgroup of the full Selec
 constexpr int kFuseThreads = 1024;   // full Selector, second kernel: workgroup ...
 constexpr int kFuseSpan = 512;      // ... and positions (of every KV head) it takes
 constexpr int kHistBins = 512;     // bins of a segment's coarse key histogram (long J)
+constexpr int kHistGroup = 64;      // segments whose histograms a launch of its own adds up ...
+constexpr int kHistGroupFrom = 128;  // ... of a J of more segments than this
 constexpr int kStateWords = 8;     // per (b, h) Selector state, see SelState
 constexpr float kNeg = -1.0e30f;   // "minus infinity" that stays finite under subtraction
 constexpr float kLog2e = 1.4426950408889634f;

@@ -217,7 +217,7 @@ __device__ __forceinline__ void group_stats(const SelArgs& a, const Cell& c, int
   }
 }
 
-// The coarse histogram of a segment of kSelSeg keys: kHistBins bins of an eighth of an octave from 2^-64 up (keys outside
+// The coarse histogram of a segment of kSelSeg keys: kHistBins bins of an eighth of an octave from 2^-63 up (keys outside
 // fall into the end bins), two 16-bit counters per word.
 __device__ __forceinline__ uint32_t bin_of(uint32_t key) {
   return (uint32_t)min(max((int)(key >> 20) - (1024 - kHistBins), 0), kHistBins - 1);
@@ -231,6 +231,12 @@ __device__ __forceinline__ void hist_add4(uint32_t* s_hist, const uint32_t (&k)[
 }
 __device__ __forceinline__ uint32_t* seg_hist(const SelArgs& a, int bh, int seg) {
   return a.hist + ((int64_t)bh * a.n_seg_cap + seg) * (kHistBins / 2);
+}
+// The sum over a group of kHistGroup segments, a word per bin.  (The pair's room holds n_seg_cap segments of kPriorSeg
+// positions; segments of kSelSeg use half of it, and two places per group follow behind them.)
+static_assert(kSelSeg == 2 * kPriorSeg && kHistGroup >= 4, "the groups' histograms fit behind the segments'");
+__device__ __forceinline__ uint32_t* group_hist(const SelArgs& a, int bh, int grp) {
+  return seg_hist(a, bh, a.n_seg_cap / 2 + 2 * grp);
 }
 
 // ---- scoring: evidence f and its key, a workgroup per NQ x 1024 positions ------------------------------
@@ -692,8 +698,34 @@ __global__ __launch_bounds__(kPickThreads) void sel_pick_kernel(const SelArgs a)
   });
 }
 
-// ---- long J, stage 2: find the threshold bin, collect its keys ------------------------------------------
+// ---- very long J: the segments' histograms added up by groups --------------------------------------------
+// In stage 2 every segment's workgroup adds up all histograms of its pair, which grows with the square of |J|; of a J of
+// more than kHistGroupFrom segments it reads the groups' sums that this launch leaves.  Both launches against stage 2
+// without them, 8 pairs: 64 segments 11.2 / 8.1 us, 128 segments 12.8 / 11.9, 192 segments 13.4 / 19.6, 512 segments
+// (1048576 rows) 18.0 / 84.8; 16 pairs of 128 segments 13.7 / 16.9.
 template <bool LIST>
+__global__ __launch_bounds__(kSelThreads) void sel_group_kernel(const SelArgs a) {
+  ask(a);
+  asm volatile("" ::"s"(a.hist), "s"(a.n_seg_cap));
+  const int grp = blockIdx.x;
+  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    const int n_seg = (nJ_of(a, c) + kSelSeg - 1) / kSelSeg;
+    const int s0 = grp * kHistGroup, s1 = min(s0 + kHistGroup, n_seg);
+    if (s0 >= n_seg || cell_off<LIST>(a, c)) return;
+    uint32_t lo = 0, hi = 0;
+#pragma unroll 8
+    for (int sg = s0; sg < s1; ++sg) {
+      const uint32_t v = seg_hist(a, c.bh, sg)[tid];
+      lo += v & 0xffffu;
+      hi += v >> 16;
+    }
+    *reinterpret_cast<uint2*>(group_hist(a, c.bh, grp) + 2 * tid) = make_uint2(lo, hi);
+  });
+}
+
+// ---- long J, stage 2: find the threshold bin, collect its keys ------------------------------------------
+// GROUPS: behind sel_group_kernel.
+template <bool LIST, bool GROUPS>
 __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.hist), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap));
@@ -724,8 +756,18 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
     }
     uint32_t cnt[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     static_assert(kHistBins == 8 * 64, "eight bins per lane");
+    const int n_grp = (n_seg + kHistGroup - 1) / kHistGroup;
+    if (GROUPS) {
+#pragma unroll 2
+      for (int gr = w; gr < n_grp; gr += kSelThreads / 64) {
+        const uint4* gh = reinterpret_cast<const uint4*>(group_hist(a, c.bh, gr)) + 2 * lane;
+        const uint4 q0 = gh[0], q1 = gh[1];
+        cnt[0] += q0.x; cnt[1] += q0.y; cnt[2] += q0.z; cnt[3] += q0.w;
+        cnt[4] += q1.x; cnt[5] += q1.y; cnt[6] += q1.z; cnt[7] += q1.w;
+      }
+    }
 #pragma unroll 4
-    for (int sg = w; sg < n_seg; sg += kSelThreads / 64) {
+    for (int sg = w; !GROUPS && sg < n_seg; sg += kSelThreads / 64) {
       const uint4 q = reinterpret_cast<const uint4*>(seg_hist(a, c.bh, sg))[lane];
       cnt[0] += q.x & 0xffffu; cnt[1] += q.x >> 16; cnt[2] += q.y & 0xffffu; cnt[3] += q.y >> 16;
       cnt[4] += q.z & 0xffffu; cnt[5] += q.z >> 16; cnt[6] += q.w & 0xffffu; cnt[7] += q.w >> 16;
@@ -745,10 +787,16 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
     const uint32_t bin1 = s_res[0];
     // candidates of the segments before this one: where this segment's run starts in the pair's list
     uint32_t before = 0, all = 0;
-    for (int sg = tid; sg < n_seg; sg += kSelThreads) {
+    const int my_grp = seg / kHistGroup;
+    for (int gr = tid; GROUPS && gr < n_grp; gr += kSelThreads) {
+      const uint32_t x = group_hist(a, c.bh, gr)[bin1];
+      all += x;
+      before += gr < my_grp ? x : 0u;
+    }
+    for (int sg = (GROUPS ? my_grp * kHistGroup : 0) + tid; sg < (GROUPS ? seg : n_seg); sg += kSelThreads) {
       const uint32_t v = seg_hist(a, c.bh, sg)[bin1 >> 1];
       const uint32_t x = (bin1 & 1u) ? v >> 16 : v & 0xffffu;
-      all += x;
+      if (!GROUPS) all += x;
       before += sg < seg ? x : 0u;
     }
     before = wave_sum(before);
@@ -1021,9 +1069,22 @@ hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t
 }
 hipError_t launch_sel_cand(const SelArgs& a, int B, int nJ, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kSelSeg);
-  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
-  if (a.slow_list != nullptr) hipLaunchKernelGGL(sel_cand_kernel<true>, grid, dim3(kSelThreads), 0, s, a);
-  else hipLaunchKernelGGL(sel_cand_kernel<false>, grid, dim3(kSelThreads), 0, s, a);
+  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv)), block(kSelThreads);
+  const bool list = a.slow_list != nullptr;
+  if (n_seg > kHistGroupFrom) {
+    const int n_grp = (n_seg + kHistGroup - 1) / kHistGroup;
+    const dim3 ggrid(n_grp, a.Hkv, z_of(a, B, n_grp * a.Hkv));
+    if (list) hipLaunchKernelGGL(sel_group_kernel<true>, ggrid, block, 0, s, a);
+    else hipLaunchKernelGGL(sel_group_kernel<false>, ggrid, block, 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (list) hipLaunchKernelGGL((sel_cand_kernel<true, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sel_cand_kernel<false, true>), grid, block, 0, s, a);
+  } else if (list) {
+    hipLaunchKernelGGL((sel_cand_kernel<true, false>), grid, block, 0, s, a);
+  } else {
+    hipLaunchKernelGGL((sel_cand_kernel<false, false>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 hipError_t launch_sel_write(const SelArgs& a, int B, int nJ, hipStream_t s) {

@@ -145,3 +145,31 @@ def test_planned_launch_that_leaves_evidence_only(oracle, mode, page, lens):
         _check_window(oracle, w, r, sp, [w.q(t) for t in range(3)])
     finally:
         r.close()
+
+
+# 280000 positions: 137 segments, three groups of 64 whose histograms are added up first (from 129 segments on); the other
+# sequence has one group.  The tie class spans the border of the first two groups (segment 64 begins at position 131072).
+@pytest.mark.parametrize("case", ["random", "ties"])
+def test_very_long_form_adds_histograms_by_groups(oracle, case):
+    import torch
+    w = _workload(2, 1, 2, [280000 + N_SINK + RECENT, 100000 + N_SINK + RECENT], 30000, seed=61)
+    if case == "ties":
+        w.K[:, :, 125000:140000] = w.K[:, :, 125000:125001]
+    r = Runner(w)
+    try:
+        q, c = w.q(0), w.ctx_len(0)
+        for budget in (700, 30000):
+            print(f"[gpu-limits] histograms by groups, {case}, budget {budget}", flush=True)
+            sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, budget, w.n_sink, w.recent)
+            _, sel, nsel = r.slow(q, c, budget, max_len=int(c.max()))
+            check_selection(sel, nsel, sel_ref, nsel_ref, z, c, w.n_sink, w.recent, budget)
+            # the ragged step, whose launches take the slow sequences from a list: same evidence, same sets
+            sel_d = torch.full((2, 1, budget), -7, dtype=torch.int32, device="cuda")
+            nsel_d = torch.zeros((2, 1), dtype=torch.int32, device="cuda")
+            r.sfi.sfi_mixed_step(r.ctx.handle, to_dev(q), r.K, r.V, torch.ones(2, dtype=torch.uint8, device="cuda"), i32_dev(c),
+                                 i32_dev(w.recent_start(0)), int(c.max()), budget, r.out, sel_d, nsel_d)
+            torch.cuda.synchronize()
+            check_selection(sel_d.cpu().numpy(), nsel_d.cpu().numpy(), sel_ref, nsel_ref, z, c, w.n_sink, w.recent, budget)
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
