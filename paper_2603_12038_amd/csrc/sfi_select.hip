@@ -958,10 +958,14 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
 
 // ---- launches -------------------------------------------------------------------------------------------
 // Workgroups along z: one per sequence, or, where the slow sequences come as a list, enough for a few of them (n_wgs
-// workgroups per list entry and launch).
+// workgroups per list entry and launch).  The limit is four times what the chip holds of these kernels' workgroups (eight per
+// unit): they differ in length, and with fewer the last ones walk their entries alone.  Measured on 32 sequences of 16384 to
+// 65536 rows, 8 KV heads, limits of 1024 / 2048 / 4096 / 8192 / none: all slow 1312 / 1288 / 1270 / 1266 / 1264 us a step (scoring
+// launch 141 / 128 / 120 / 117 / 117), 16 slow 662 / 652 / 647 / 648 / 648, 1 to 4 slow no difference; without a limit a batch
+// of hundreds would launch workgroups that find nothing to do.
 static unsigned z_of(const SelArgs& a, int B, int n_wgs) {
   if (a.slow_list == nullptr) return (unsigned)B;
-  const int z = 1024 / (n_wgs < 1 ? 1 : n_wgs);
+  const int z = 8192 / (n_wgs < 1 ? 1 : n_wgs);
   return (unsigned)(z < 1 ? 1 : z > B ? B : z);
 }
 static int ceil_seg(int nJ, int per) { return nJ > 0 ? (nJ + per - 1) / per : 1; }

@@ -173,3 +173,31 @@ def test_very_long_form_adds_histograms_by_groups(oracle, case):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
+
+
+# 300 slow sequences: more than the Selector's launches have workgroups along the list, so each walks several entries
+@pytest.mark.parametrize("mode", [0, 1])
+def test_more_slow_sequences_than_workgroups(oracle, mode):
+    import torch
+    print(f"[gpu-limits] 300 slow sequences, mode {mode}", flush=True)
+    lens = [60 + (37 * i) % 500 for i in range(300)]
+    w = _workload(300, 8, 4, lens, 33, seed=12)
+    sp, d = _selector(mode)
+    r = Runner(w, selector=d, alpha=1.0)
+    try:
+        q, c = w.q(0), w.ctx_len(0)
+        flags = np.ones(300, np.uint8)
+        flags[[0, 7, 299]] = 0
+        sel = torch.full((300, 8, 33), -7, dtype=torch.int32, device="cuda")
+        nsel = torch.zeros((300, 8), dtype=torch.int32, device="cuda")
+        r.sfi.sfi_mixed_step(r.ctx.handle, to_dev(q), r.K, r.V, torch.from_numpy(flags).cuda(), i32_dev(c), i32_dev(w.recent_start(0)),
+                             int(c.max()), 33, r.out, sel, nsel)
+        torch.cuda.synchronize()
+        sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, 33, w.n_sink, w.recent, sp=sp)
+        on = flags != 0
+        check_out(r.out.cpu().numpy()[on], oracle.dense(q, w.K, w.V, c)[on])
+        check_selection(sel.cpu().numpy()[on], nsel.cpu().numpy()[on], sel_ref[on], nsel_ref[on], z[on], c[on], w.n_sink, w.recent, 33)
+        assert (sel.cpu().numpy()[~on] == -7).all()
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
