@@ -201,3 +201,37 @@ def test_more_slow_sequences_than_workgroups(oracle, mode):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
+
+
+# A ragged step of one sequence is launched as a slow step: same outputs and index sets, bit for bit, and nothing when it is fast
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("n", [1, 60, 1000, 5003, 17000])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_ragged_step_of_one_sequence(oracle, mode, n, page):
+    import torch
+    print(f"[gpu-limits] ragged step of one sequence: {n} rows, mode {mode}, page {page}", flush=True)
+    w = _workload(1, 2, 5, [n], 65, seed=700 + n)
+    sp, d = _selector(mode)
+    r = Runner(w, selector=d, alpha=1.0, page_size=page)
+    try:
+        q, c, rs = w.q(0), w.ctx_len(0), w.recent_start(0)
+        out, sel, nsel = r.slow(q, c, 65, max_len=n)
+        check_out(out, oracle.dense(q, w.K, w.V, c))
+        for slow in (1, 0):
+            sel_d, nsel_d = i32_dev(sel), i32_dev(nsel)
+            if slow:
+                sel_d.fill_(-7)
+                nsel_d.fill_(-7)
+            r.out.fill_(float("nan"))
+            r.sfi.sfi_mixed_step(r.ctx.handle, to_dev(q), r.K, r.V, torch.full((1,), slow, dtype=torch.uint8, device="cuda"), i32_dev(c),
+                                 i32_dev(rs), n, 65, r.out, sel_d, nsel_d)
+            torch.cuda.synchronize()
+            got = r.out.cpu().numpy()
+            assert (sel_d.cpu().numpy() == sel).all() and (nsel_d.cpu().numpy() == nsel).all()
+            if slow:
+                assert (got == out).all()
+            else:
+                check_out(got, oracle.sparse(q, w.K, w.V, sel, nsel, rs, c, w.n_sink))
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
