@@ -214,6 +214,16 @@ void plan_dense(sfi_ctx* x, AttnArgs* a, int max_len, bool mixed) {
   x->last_dense_planned = 1;
 }
 
+// The paged launch without logits: with 256 registers (two workgroups per unit) its two tile buffers and the block-table
+// stage spill 10, with 512 none.  One per unit where no unit gets a second one, or where a workgroup's share of the longest
+// sequence is more than 16 tiles; many short shares hide each other's starts.  (Two / one per unit, us, 8 KV heads: 1 x 131072
+// rows 111 / 88, 1 x 32768 35.7 / 29.1, 32 x 200..500 17.1 / 13.5, 128 x 2000..8000 558 / 491, 1100 x 600..1200 839 / 780;
+// 64 x 100..300 16.9 / 17.8, 1100 x 100..500 316 / 340.)
+bool one_per_unit(const sfi_ctx* x, int n_split, int max_len) {
+  const int tiles = (max_len + kTile - 1) / kTile;
+  return x->cfg.batch * x->cfg.n_kv_heads * n_split <= x->n_cu || tiles > 16 * n_split;
+}
+
 void set_dense_bounds(const sfi_ctx* x, AttnArgs* a, int max_len) {
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;
   a->max_tiles = nJ > 0 ? (nJ + kTile - 1) / kTile : 0;
@@ -510,6 +520,7 @@ int sfi_dense_attn(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   set_dense_bounds(x, &a, ml);
   x->last_dense_splits = a.n_split;
   if (x->tail_merge) plan_dense(x, &a, ml, false);
+  a.big_stash = x->table != nullptr && one_per_unit(x, a.n_split, ml);
   if (a.plan_batch > 0) { a.out_merge = out; a.arrive = x->ws.arrive; }
   else if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
   else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; }

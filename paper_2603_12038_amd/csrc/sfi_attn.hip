@@ -687,7 +687,9 @@ struct ListWalk {
 // EXPOSE 1: also write y over J for the Selector; 2: y and the squared key norms.
 // BIG: twice the logits stash per wave, which leaves room for one workgroup per compute unit only
 // (launches where every sequence is dense, and the planned launch, run one per unit anyway; the ragged
-// step's launch with a workgroup per cell keeps two).
+// step's launch with a workgroup per cell keeps two, although that kernel spills 6 to 26 of its 256 registers: with one,
+// 12 sequences of 5003 to 30011 rows, 4 of them slow, take 110 us a step instead of 104, 1100 of 100 to 500 rows, 100 slow,
+// 249 instead of 215).
 // NOV: evidence only -- no V row is read, no P V product, the records carry the softmax statistics alone.
 // PLANNED: the caller has the sequence's length and a range of its tiles (attn_dense_planned_kernel).
 struct DenseShare {
@@ -1887,8 +1889,15 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
     hipLaunchKernelGGL((attn_dense_kernel<1, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);
   else if (a.logits != nullptr)
     hipLaunchKernelGGL((attn_dense_kernel<1, PAGED>), grid, dim3(kAttnThreads), 0, s, a);
-  else
+  else {
+    if constexpr (PAGED) {
+      if (a.big_stash) {  // (no stash without logits: one workgroup per unit is what is meant, and its registers)
+        hipLaunchKernelGGL((attn_dense_kernel<0, true, true>), grid, dim3(kAttnThreads), 0, s, a);
+        return;
+      }
+    }
     hipLaunchKernelGGL((attn_dense_kernel<0, PAGED>), grid, dim3(kAttnThreads), 0, s, a);
+  }
 }
 hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
   const dim3 grid(n_slots, a.Hkv, B);

@@ -235,3 +235,19 @@ def test_ragged_step_of_one_sequence(oracle, mode, n, page):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
+
+
+# Paged dense launch with one workgroup per unit (few workgroups, or long shares) and with two (many short shares)
+@pytest.mark.parametrize("B, lens", [(1, [17000]), (1, [1]), (3, [700, 33, 512]), (48, [100 + 9 * i for i in range(48)]),
+                                     (48, [15 + 4 * i for i in range(48)])],
+                         ids=["one long", "one row", "few", "long shares", "short shares"])
+def test_paged_dense_launch_by_workgroups_per_unit(oracle, B, lens):
+    print(f"[gpu-limits] paged dense launch: {B} sequences of up to {max(lens)} rows", flush=True)
+    w = _workload(B, 8, 3, lens, 33, seed=40 + B)
+    r = Runner(w, page_size=16)
+    try:
+        q, c = w.q(0), w.ctx_len(0)
+        check_out(r.dense(q, c, max_len=int(c.max())), oracle.dense(q, w.K, w.V, c))
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
