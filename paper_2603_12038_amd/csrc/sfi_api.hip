@@ -224,6 +224,16 @@ bool one_per_unit(const sfi_ctx* x, int n_split, int max_len) {
   return x->cfg.batch * x->cfg.n_kv_heads * n_split <= x->n_cu || tiles > 16 * n_split;
 }
 
+// Whether the per-cell dense launch merges its records itself.  In the kernel a wave merges its heads (a quarter of the group)
+// one after the other, sixteen records a trip; a merge launch takes all heads at once and costs a launch.  With four heads
+// per wave the launch is faster, with three where there is more than one trip per head and the shares are short.  (In
+// the kernel / in a launch, us, 8 KV heads, G = 16: 1 x 4096 rows 15.8 / 12.2, 1 x 32768 33.8 / 28.6, 1 x 131072 88.6 / 88.3, 3 x 2000
+// 13.7 / 13.0; G = 12: 14.2 / 12.1, 31.9 / 28.9, 86.5 / 88.4, 12.9 / 12.9; G = 8: 12.4 / 11.9, 29.8 / 28.3, 84.8 / 88.8, 11.8 / 12.7.)
+bool merges_in_kernel(const sfi_ctx* x, int n_split, int max_len) {
+  if (!x->tail_merge || x->G > 12) return false;
+  return x->G <= 8 || n_split <= 16 || (max_len + kTile - 1) / kTile > 16 * kWaves * n_split;
+}
+
 void set_dense_bounds(const sfi_ctx* x, AttnArgs* a, int max_len) {
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;
   a->max_tiles = nJ > 0 ? (nJ + kTile - 1) / kTile : 0;
@@ -523,7 +533,7 @@ int sfi_dense_attn(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.big_stash = x->table != nullptr && one_per_unit(x, a.n_split, ml);
   if (a.plan_batch > 0) { a.out_merge = out; a.arrive = x->ws.arrive; }
   else if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
-  else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; }
+  else if (merges_in_kernel(x, a.n_split, ml)) { a.out_merge = out; a.arrive = x->ws.arrive; }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.out_direct != nullptr || a.out_merge != nullptr) return SFI_OK;
   MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, a.n_split, 0, 0, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};

@@ -251,3 +251,19 @@ def test_paged_dense_launch_by_workgroups_per_unit(oracle, B, lens):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
+
+
+# Dense attention with one to four heads per merging wave, few and many records, in the kernel and in a launch of its own
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("G", [1, 8, 9, 12, 13, 16])
+def test_dense_attention_merges_groups_of_any_size(oracle, G, page):
+    w = _workload(2, 4, G, [9001, 4100], 33, seed=900 + G)
+    r = Runner(w, page_size=page)
+    try:
+        for lens in ([9001, 4100], [2100, 2099], [300, 77], [1, 0]):  # up to 63 records per head, 16, 3, none to merge
+            print(f"[gpu-limits] dense attention, G = {G}, page {page}, {lens}", flush=True)
+            c = np.array(lens, np.int32)
+            check_out(r.dense(w.q(0), c, max_len=int(c.max())), oracle.dense(w.q(0), w.K, w.V, c))
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
