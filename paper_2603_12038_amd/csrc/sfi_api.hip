@@ -176,7 +176,8 @@ int dense_splits_for(const sfi_ctx* x, int max_len, bool mixed) {
 // 2000..4000 rows, full Selector, 18.3 -> 17.3 us; the small stash without the second workgroup costs 1 %.)
 void split_evidence(const sfi_ctx* x, AttnArgs* a, int max_len) {
   if (x->dense_target_wgs > 0) return;
-  const int tiles = (max_len - x->cfg.n_sink + kTile - 1) / kTile;  // (a query under the causal mask sees up to that much of J)
+  const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;  // (a query under the causal mask sees no more of J than the window has)
+  const int tiles = nJ > 0 ? (nJ + kTile - 1) / kTile : 0;
   const int per_wave = (tiles + 2 * kWaves * a->n_split - 1) / (2 * kWaves * a->n_split);
   if (2 * a->n_split > kMaxSplits || 2 * kWaves * a->n_split > tiles + kWaves - 1) return;
   if (per_wave * kTile * (x->G + (a->with_knorm ? 1 : 0)) > kStashFloats) return;
@@ -661,8 +662,7 @@ int evidence_add_impl(sfi_ctx* x, const void* q, const void* K, const void* V, c
   if (x->last_dense_planned) sa.seq_rec = x->ws.seq_rec;
   sa.accum_first = first != 0;
   sa.q_len = q_len;
-  // a query under the causal mask may see up to `recent` more positions of its own, shorter context as allowed set
-  const int nJ = ml - (q_len != nullptr ? 0 : x->cfg.recent) - x->cfg.n_sink;
+  const int nJ = ml - x->cfg.recent - x->cfg.n_sink;  // (under the causal mask too: window_view leaves L - rec <= L_end - recent)
   { StageTimer t(x, st, SFI_STAGE_SCORE); SFI_TRY(launch_sel_accum(sa, x->cfg.batch, nJ, st)); if (!t.stop()) return SFI_ELAUNCH; }
   return SFI_OK;
 }

@@ -267,3 +267,18 @@ def test_dense_attention_merges_groups_of_any_size(oracle, G, page):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
+
+
+# A recent window longer than a workgroup's 1024 positions, with J shorter and longer than it: a masked query sees no more of
+# J than the whole window has, which is what the accumulating launch covers
+@pytest.mark.parametrize("mode", [0, 1])
+def test_window_behind_a_long_recent_window(oracle, mode):
+    print(f"[gpu-limits] window behind a recent window of 1500 rows, mode {mode}", flush=True)
+    w = _workload(4, 2, 2, [3999, 1700, 1505, 2600], 129, seed=73)
+    w.recent = 1500
+    sp, d = _selector(mode)
+    r = Runner(w, selector=d, alpha=1.0)
+    try:
+        _check_window(oracle, w, r, sp, [w.q(t) for t in range(3)])
+    finally:
+        r.close()
