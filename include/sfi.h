@@ -187,8 +187,7 @@ int sfi_slow_step(sfi_ctx* ctx, const void* q, const void* K, const void* V, con
  *                    stays in this context's workspace;
  *   sfi_slow_select  the Selector on that evidence -> sel_idx, n_sel.  ctx_len, max_len must be the ones
  *                    given to the sfi_slow_attn call it follows.  It may be called again on the same evidence
- *                    (another budget): a repeat starts with one more small launch that resets the Selector's
- *                    counters.
+ *                    (another budget).
  * sfi_slow_step is the two in a row on one stream.  To overlap Sel_i with Attn_{i+1}, give the layers
  * in flight a context (and workspace) each -- a ring of a few -- run sfi_slow_attn on the main stream and
  * sfi_slow_select on a second stream that waits for an event recorded after it; before a context is
@@ -368,16 +367,18 @@ int sfi_advance(sfi_ctx* ctx, int32_t* ctx_len, int32_t* recent_start, void* str
  * of the next max_calls hot calls bracket every kernel it launches with a pair of HIP events on the
  * caller's stream (no host synchronisation in between); max_calls = 0 switches it off.
  * sfi_stage_times waits for the recorded events and returns, per stage, the sum of elapsed
- * milliseconds and the number of launches over the calls recorded since profiling was switched on.
+ * milliseconds and how often the stage launched something over the calls recorded since profiling was switched on.
  * Not for production loops: event records add a gap of a few microseconds around every kernel.
  */
 enum {
   SFI_STAGE_ATTN = 0,     /* split attention kernel (dense; gather or compact in a fast step) */
   SFI_STAGE_MERGE = 1,    /* split merge */
-  SFI_STAGE_SCORE = 2,    /* evidence + first radix histogram (mode 1: the three scoring kernels together) */
-  SFI_STAGE_CAND = 3,     /* threshold-bin candidates */
-  SFI_STAGE_COUNT = 4,    /* exact threshold + per-segment counts */
-  SFI_STAGE_WRITE = 5,    /* ordered index write */
+  SFI_STAGE_SCORE = 2,    /* evidence and ranking keys, with the segments' histograms where J is long (mode 1: both
+                             kernels together); none where one workgroup per pair scores or reads a window's evidence */
+  SFI_STAGE_CAND = 3,     /* long J only: threshold-bin candidates (very long J: and the histograms' sums by groups) */
+  SFI_STAGE_COUNT = 4,    /* not used: always 0 */
+  SFI_STAGE_WRITE = 5,    /* ordered index write; short J: the whole selection, with the scoring and the output's merge
+                             where no SCORE stage ran in a slow step */
   SFI_STAGE_ATTN2 = 6,    /* the gather attention kernel of a mixed step */
   SFI_STAGE_REORG = 7,    /* compact-buffer gather */
   SFI_N_STAGES = 8
@@ -392,9 +393,11 @@ int sfi_stage_times(sfi_ctx* ctx, float* ms_sum /* host, [SFI_N_STAGES] */, int3
  *                      divide the compute units);
  * fast_tiles_per_wave  32-row tiles each wave of the gather launch gets.  Default: decided per launch by
  *                      the same rule -- one tile per wave or several (pipelined loop);
- * fast_merge           how the split records of a fast step become the output: 1 (default) inside the
- *                      attention kernel, by the last workgroup of each (sequence, KV head) to finish;
- *                      2 in a merge launch of its own.  Other values > 2: SFI_EINVAL. */
+ * fast_merge           how the split records of a fast step, a dense call or a ragged step become the output: 1
+ *                      (default) inside the attention kernel -- wave w of a workgroup counts itself in when the
+ *                      records of its heads w, w + 4, ... are out, and the last wave w of each (sequence, KV head)
+ *                      merges those heads -- or, for large head groups of a dense call, in a launch where that is
+ *                      faster; 2 always in a merge launch of its own.  Other values > 2: SFI_EINVAL. */
 int sfi_set_tuning(sfi_ctx* ctx, int32_t dense_target_wgs, int32_t fast_tiles_per_wave, int32_t fast_merge);
 
 /* A/B knob of the dense kernel's K loads: 0 (default) = a K row leaves the compute unit as four 64-byte requests, the
@@ -406,11 +409,12 @@ int sfi_set_dense_k_layout(sfi_ctx* ctx, int32_t whole_lines);
 
 /* A/B knob of the dense launch inside sfi_mixed_step, sfi_mixed_step_compact and sfi_mixed_step_desc (the ragged step of
  * Sec. 4.2, where which sequences take a slow step is only known on the device).  on = 1 (default): the launch is one
- * workgroup per compute unit; every workgroup derives the same plan from the flags and lengths -- the slow sequences
- * and, for each, a number of splits in proportion to its length -- and takes its share of the cells, so the shares are
- * equal whatever the mix (batches of up to 1024 sequences, and only where the fast step's merge runs inside its kernel;
- * otherwise as with on = 0).  on = 0: one workgroup per (split, KV head, sequence) cell of the whole batch with the
- * finest split; workgroups of fast sequences exit at once.  Same results.  Other values: SFI_EINVAL. */
+ * workgroup per compute unit; every wave derives the same plan from the flags and lengths -- per KV head, the tiles of
+ * the slow sequences laid end to end and cut into one equal share per workgroup, which may reach into several
+ * sequences -- so the shares are equal whatever the mix (batches of 2 to 1024 sequences, and only where the fast
+ * step's merge runs inside its kernel; otherwise as with on = 0).  on = 0: one workgroup per (split, KV head, sequence)
+ * cell of the whole batch with the finest split (a batch of one: the slow step's split); workgroups of fast sequences
+ * exit at once.  Same results.  Other values: SFI_EINVAL. */
 int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);
 
 /* Launch geometry the library would choose, without launching anything (host arithmetic only): split
@@ -449,13 +453,14 @@ int sfi_device_status(sfi_ctx* ctx, int32_t* flags, int32_t clear, void* stream)
  * sfi_fast_step and launches its grid with its loads but none of its arithmetic; `out` receives no meaningful values.
  * variant:
  *   bit 0      also run the record hand-over of the real launch (LDS combine, device-scope record stores, arrival
- *              counter, merge by the pair's last workgroup);
+ *              counters, merge by the last wave of each head group);
  *   bit 1      every wave requests the rows of all its tiles at once, straight into LDS, instead of walking them through
  *              one register buffer (at most nine tiles per workgroup: the split is made finer if need be, SFI_EUNSUPPORTED
  *              if that is not enough; not together with bit 0);
  *   bits 2-3   how far down the chain of dependent loads the launch goes: 0 = all of it (the three per-step scalars and the
  *              indices, then the K and V rows); 1 = scalars and indices only; 2 = nothing (an empty grid of the same shape).
- * Flat caches only.  The time of this launch is the floor the fast-step kernel of the same shape is held against.
+ * Flat caches only.  The launch's leading arguments arrive in registers, as the fast step's do.  Its time is what the
+ * fast-step kernel of the same shape is held against: what the launch costs whose arithmetic is free.
  */
 int sfi_fast_step_floor(sfi_ctx* ctx, const void* q, const void* K, const void* V, const int32_t* sel_idx,
                         const int32_t* n_sel, int32_t sel_stride, const int32_t* recent_start,

@@ -126,10 +126,12 @@ inline bool misaligned(const void* p, size_t a) { return (reinterpret_cast<uintp
 // is a wave's tiles plus a start and an end worth about three tiles; in a single round the waves
 // move in step, one trip to memory per tile, so the wave with the most tiles counts.  A launch that
 // merges its records in the kernel pays about two thirds of a tile for every further group of eight
-// workgroups per pair.  Take the s with the lowest cost, the smaller s on a tie.  (Measured at 12, 24,
-// 33 and 40 sequences of 8 KV heads: 13 to 43 % faster dense launches than one workgroup per compute
-// unit rounded down; one long stream: 18 workgroups per pair instead of 32, 6 % faster fast steps; the
-// same choice as one workgroup per compute unit where the pairs divide the compute units.)
+// workgroups per pair.  Take the s with the lowest cost, the smaller s on a tie.  (The same choice as one
+// workgroup per compute unit where the pairs divide the units.  Fast steps, chosen split against 1, 2, 3 and 4
+// tiles per wave, us a layer, 8 KV heads: 4 x 32768 rows, budget 2048: 10.2 against 12.4, 12.5, 10.8, 12.3; 8 sequences,
+// G = 5, budget 1024: 11.7 against 12.8, 13.2, 11.8, 12.2; 1 x 131072 rows, budget 4096: 9.6 against 10.5, 9.6, 9.9, 11.0;
+// 8 and 16 sequences, budget 2048: 16.3 against 20.0, 18.9, 18.0, 20.1 and 27.2 against 35.1, 32.4, 29.4, 31.9; paged
+// caches alike.  Dense launches of 12, 24, 33 and 40 sequences: 13 to 43 % faster than one workgroup per unit rounded down.)
 int balanced_splits(int pairs, int tiles, int cap, int n_cu, bool merges_in_kernel) {
   int best = 1;
   double best_cost = 1e300;
@@ -189,7 +191,14 @@ void split_evidence(const sfi_ctx* x, AttnArgs* a, int max_len) {
 // the launch with a workgroup per cell requests its first rows before the length has arrived), unless a knob asks for the
 // other launch.  Workgroups per KV head: as many as give every compute unit one; where the heads do not divide the units
 // (fewer than nine in ten busy), up to four rounds.  A workgroup takes at least a tile per wave, and enough tiles that the
-// longest sequence stays within its records.  (8 paged sequences of 20011 to 24571 rows, 8 KV heads: dense launch 122 -> 109 us.)
+// longest sequence stays within its records.  Outside the ragged step the other launch stays where it is the better one:
+// - few tiles: below 8 per wave (16 without V: half the bytes, and two workgroups per unit to set against).  Per cell /
+//   planned, us a layer, 8 KV heads: 4 x 2000..4000 rows 19.9 / 22.4 (4 tiles per wave), 4 x 4096..8192 33.1 / 34.8 (8), 8 x 4000..8192
+//   dense 41.1 / 39.8 (8), 4 x 8000..16000 40.1 / 39.1 (16), 8 x 6000..12000 57.5 / 54.0 (24), 8 x 8000..16000 74.7 / 68.6 (32);
+//   equal lengths gain nothing: 8 x 8192 42.3 / 45.6; a window of 8 queries, 4 x 8000..16000 221 / 244 (16), 8 x 8000..16000 438 / 415 (31);
+// - many sequences: every one a workgroup meets costs it a way out and in.  512 x 300..900 rows dense 214 / 389, 1000 x 200..600 302 /
+//   727, 256 x 1000..4000 450 / 468.  (The line, two pairs per unit, does not see their length: 128 x 2000..8000 would gain,
+//   480 / 424, and 96 x 2000..16000, 772 / 553.)
 void plan_dense(sfi_ctx* x, AttnArgs* a, int max_len, bool mixed) {
   x->last_dense_planned = 0;
   const int B = x->cfg.batch, Hkv = x->cfg.n_kv_heads;
@@ -358,18 +367,23 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
 // windowed: rank the accumulated evidence (sa.mu_scale set) instead of the last query's.
 // How many launches: the whole of J in the registers of one workgroup per pair (up to 16384 positions) saves the histogram,
 // the candidates and a launch; below about 24576 logits per pair (96 KB, which a compute unit reads in the time a
-// launch costs) that workgroup scores as well.
+// launch costs) that workgroup scores as well.  Slow step with three Selector launches / with two, us, 8 KV heads: 9000 rows
+// 24.4 / 23.3, 12000 24.9 / 24.2, 16400 28.95 / 29.0 (one sequence); 41.0 / 40.0, 48.9 / 47.7, 60.2 / 59.8 (four): at 16384
+// positions the single workgroup's reading has caught up.
+// Growth: up to 262144 positions a segment's workgroup adds up all histograms of its pair, above it the groups' (sel_group_kernel);
+// mode 1's second kernel adds up five sums per 1024 positions in every workgroup at any length (1048576 rows of 8 KV heads:
+// both scoring kernels 139 us of a step of 916).
 int run_selector(sfi_ctx* x, const SelArgs& sa, int max_len, hipStream_t st, bool windowed = false) {
   const int B = x->cfg.batch;
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;
-  const bool pick = nJ <= kPickMax;
-  int src = 0;
-  {
+  const bool pick = nJ <= kPickMax, full = x->cfg.selector_mode == 1;
+  int src = 0;  // what the selecting workgroup reads: keys that a scoring launch leaves, or (nothing is launched before it) ...
+  if (!full && windowed && pick) src = 2;                                                             // ... the window's evidence
+  else if (!full && !windowed && sa.part != nullptr && pick && sel_pick_scores(nJ, x->G)) src = 1;  // ... the logits
+  if (src == 0) {
     StageTimer t(x, st, SFI_STAGE_SCORE);
-    if (x->cfg.selector_mode == 1) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
-    else if (windowed && pick) src = 2;
+    if (full) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
     else if (windowed) SFI_TRY(launch_sel_finalize(sa, B, nJ, st));
-    else if (sa.part != nullptr && sel_pick_scores(nJ, x->G)) src = 1;
     else SFI_TRY(launch_sel_score(sa, B, nJ, !pick, st));
     if (!t.stop()) return SFI_ELAUNCH;
   }

@@ -23,7 +23,7 @@ constexpr int kArriveStride = 32;
 constexpr int kSelSeg = 2048;      // Selector positions per workgroup
 constexpr int kSelThreads = 256;
 constexpr int kPickThreads = 1024;  // one workgroup selects for a pair (short J)
-constexpr int kPickMax = 16 * kPickThreads;     // longest J it takes (16 keys per thread in registers)
+constexpr int kPickMax = 16 * kPickThreads;     // longest J it takes (16 keys per thread in registers; both sides: run_selector)
 constexpr int kPickLogits = 24576;  // logits of a pair up to which it also scores
 constexpr int kPriorSeg = 1024;     // positions per workgroup of the full Selector's first kernel
 constexpr int kFuseThreads = 1024;   // full Selector, second kernel: workgroup ...
@@ -39,10 +39,6 @@ constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ uint32_t bf16_rne(float v) {
   const uint32_t u = __float_as_uint(v);
   return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ void store_out(float* out, int64_t elem, float v, bool as_bf16) {
-  if (as_bf16) reinterpret_cast<uint16_t*>(out)[elem] = (uint16_t)bf16_rne(v);
-  else out[elem] = v;
 }
 __device__ __forceinline__ void store_out4(float* out, int64_t elem, float4 v, bool as_bf16) {  // elem % 4 == 0
   if (as_bf16)

@@ -282,3 +282,34 @@ def test_window_behind_a_long_recent_window(oracle, mode):
         _check_window(oracle, w, r, sp, [w.q(t) for t in range(3)])
     finally:
         r.close()
+
+
+# A stage counts launches: where one workgroup does all (short J) or reads the window's evidence, the scoring stage has none
+@pytest.mark.parametrize("n_j, mode, want", [(1500, 0, dict(score=0, cand=0, write=1)), (9000, 0, dict(score=1, cand=0, write=1)),
+                                             (17000, 0, dict(score=1, cand=1, write=1)), (1500, 1, dict(score=1, cand=0, write=1))])
+def test_stages_count_what_was_launched(n_j, mode, want):
+    import torch
+    from paper_2603_12038_amd.binding import STAGE_NAMES
+    print(f"[gpu-limits] stage counts: |J| = {n_j}, mode {mode}", flush=True)
+    w = _workload(1, 2, 4, [n_j + N_SINK + RECENT], 65, seed=8)
+    sp, d = _selector(mode)
+    r = Runner(w, selector=d, alpha=1.0)
+    try:
+        q, c, h = w.q(0), w.ctx_len(0), r.ctx.handle
+        r.slow(q, c, 65, max_len=int(c.max()))
+        r.sfi.sfi_set_profiling(h, 1)
+        r.slow(q, c, 65, max_len=int(c.max()))
+        ms, cnt = r.sfi.sfi_stage_times(h)
+        got = dict(zip(STAGE_NAMES, cnt))
+        assert {k: got[k] for k in want} == want, got
+        assert ms[STAGE_NAMES.index("score")] > 0 or want["score"] == 0
+        if mode == 0 and n_j <= 16384:
+            sel = torch.empty((1, 2, 65), dtype=torch.int32, device="cuda")
+            nsel = torch.empty((1, 2), dtype=torch.int32, device="cuda")
+            r.sfi.sfi_evidence_add(h, to_dev(q), r.K, None, i32_dev(c), int(c.max()), None, True)
+            r.sfi.sfi_set_profiling(h, 1)
+            r.sfi.sfi_evidence_select(h, 1, i32_dev(c), int(c.max()), 65, sel, nsel)
+            got = dict(zip(STAGE_NAMES, r.sfi.sfi_stage_times(h)[1]))
+            assert (got["score"], got["write"]) == (0, 1), got
+    finally:
+        r.close()
