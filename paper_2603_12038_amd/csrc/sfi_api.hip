@@ -379,7 +379,7 @@ int run_selector(sfi_ctx* x, const SelArgs& sa, int max_len, hipStream_t st, boo
   const bool pick = nJ <= kPickMax, full = x->cfg.selector_mode == 1;
   int src = 0;  // what the selecting workgroup reads: keys that a scoring launch leaves, or (nothing is launched before it) ...
   if (!full && windowed && pick) src = 2;                                                             // ... the window's evidence
-  else if (!full && !windowed && sa.part != nullptr && pick && sel_pick_scores(nJ, x->G)) src = 1;  // ... the logits
+  else if (!full && !windowed && sa.part != nullptr && pick && sel_pick_scores(nJ, x->G, B * x->cfg.n_kv_heads, x->n_cu)) src = 1;  // ... the logits
   if (src == 0) {
     StageTimer t(x, st, SFI_STAGE_SCORE);
     if (full) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));

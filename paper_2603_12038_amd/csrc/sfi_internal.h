@@ -234,7 +234,7 @@ hipError_t launch_sel_score(const SelArgs& a, int B, int nJ, bool hist, hipStrea
 hipError_t launch_sel_accum(const SelArgs& a, int B, int nJ, hipStream_t s);
 hipError_t launch_sel_finalize(const SelArgs& a, int B, int nJ, hipStream_t s);
 hipError_t launch_sel_full(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s);
-bool sel_pick_scores(int nJ, int G);  // whether the selecting workgroup also scores (src 1)
+bool sel_pick_scores(int nJ, int G, int pairs, int n_cu);  // whether the selecting workgroup also scores (src 1)
 hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t s);  // src 0: keys, 1: logits, 2: window evidence
 hipError_t launch_sel_cand(const SelArgs& a, int B, int nJ, hipStream_t s);
 hipError_t launch_sel_write(const SelArgs& a, int B, int nJ, hipStream_t s);

@@ -1047,8 +1047,13 @@ static void launch_pick_keys_t(const SelArgs& a, int nJ, dim3 grid, hipStream_t 
   else if (nJ <= 8 * kPickThreads) hipLaunchKernelGGL((sel_pick_kernel<8, SRC, LIST, 1>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((sel_pick_kernel<16, SRC, LIST, 1>), grid, block, 0, s, a);
 }
-bool sel_pick_scores(int nJ, int G) {  // more than 4096 positions leave room for the logits of five heads in registers
-  return (int64_t)nJ * G <= kPickLogits && nJ <= (G <= 5 ? 8 : 4) * kPickThreads;
+// More than 4096 positions leave room for the logits of five heads in registers.  Groups of more than eight heads fill a unit
+// with every 1024-thread workgroup and load columns they do not need, so where the pairs and the merging workgroups with them
+// (four per pair) do not fit the chip at once, a scoring launch of small workgroups is the faster one.  Slow step, scoring here /
+// in a launch before, us, 600 rows: G = 9, 64 pairs 16.5 / 19.1, 128 pairs 24.4 / 22.1, 800 pairs 131 / 95; G = 16: 19.2 / 20.5,
+// 25.2 / 25.8, 118 / 106.  G = 8: 15.1 / 17.6, 18.7 / 20.9, 87.1 / 85.6.
+bool sel_pick_scores(int nJ, int G, int pairs, int n_cu) {
+  return (int64_t)nJ * G <= kPickLogits && nJ <= (G <= 5 ? 8 : 4) * kPickThreads && (G <= 8 || 4 * pairs <= n_cu);
 }
 hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t s) {
   const int per_wg = kPickThreads / kMergeThreads;

@@ -25,7 +25,7 @@ def _check_slow(oracle, w, r, sp, q, **bars):
     c = w.ctx_len(0)
     out, sel, nsel = r.slow(q, c, w.budget, max_len=int(c.max()))
     check_out(out, oracle.dense(q, w.K, w.V, c))
-    sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, w.budget, w.n_sink, w.recent, sp=sp)
+    sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, w.budget, w.n_sink, w.recent, **({} if sp is None else dict(sp=sp)))
     check_selection(sel, nsel, sel_ref, nsel_ref, z, c, w.n_sink, w.recent, w.budget, **bars)
     return sel, nsel
 
@@ -175,13 +175,14 @@ def test_very_long_form_adds_histograms_by_groups(oracle, case):
         r.close()
 
 
-# 300 slow sequences: more than the Selector's launches have workgroups along the list, so each walks several entries
-@pytest.mark.parametrize("mode", [0, 1])
-def test_more_slow_sequences_than_workgroups(oracle, mode):
+# 300 slow sequences: more than the Selector's launches have workgroups along the list, so each walks several entries.
+# (A group of nine heads: as many pairs are scored in a launch of their own.)
+@pytest.mark.parametrize("G, mode", [(4, 0), (4, 1), (9, 0)])
+def test_more_slow_sequences_than_workgroups(oracle, G, mode):
     import torch
-    print(f"[gpu-limits] 300 slow sequences, mode {mode}", flush=True)
+    print(f"[gpu-limits] 300 slow sequences, G = {G}, mode {mode}", flush=True)
     lens = [60 + (37 * i) % 500 for i in range(300)]
-    w = _workload(300, 8, 4, lens, 33, seed=12)
+    w = _workload(300, 8, G, lens, 33, seed=12)
     sp, d = _selector(mode)
     r = Runner(w, selector=d, alpha=1.0)
     try:
@@ -311,5 +312,18 @@ def test_stages_count_what_was_launched(n_j, mode, want):
             r.sfi.sfi_evidence_select(h, 1, i32_dev(c), int(c.max()), 65, sel, nsel)
             got = dict(zip(STAGE_NAMES, r.sfi.sfi_stage_times(h)[1]))
             assert (got["score"], got["write"]) == (0, 1), got
+    finally:
+        r.close()
+
+
+# Groups of more than eight heads score in the selecting workgroup up to 64 pairs, in a launch before it with more
+@pytest.mark.parametrize("B", [8, 9])
+@pytest.mark.parametrize("G", [8, 9, 16])
+def test_large_groups_score_by_the_number_of_pairs(oracle, G, B):
+    print(f"[gpu-limits] scoring of {8 * B} pairs, G = {G}", flush=True)
+    w = _workload(B, 8, G, [1100 - 97 * i for i in range(B)], 65, seed=30 + G + B)
+    r = Runner(w)
+    try:
+        _check_slow(oracle, w, r, None, w.q(0))
     finally:
         r.close()
