@@ -252,13 +252,14 @@ __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a)
   __shared__ float s_jM[GT], s_jc[GT];
   __shared__ uint32_t s_hist[HIST ? kHistBins / 2 : 1];
   for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    if (cell_off<LIST>(a, c)) return;  // in front of the logits' requests: a fast sequence has none to read
     const int p_lo = seg * (NQ * 1024);
     const float* lg = a.logits + (int64_t)c.bh * rows * a.ld_pos;
     int p[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) p[q] = p_lo + q * 1024 + tid * 4;
     if (a.merge_out != nullptr && seg >= (int)gridDim.x - G) {  // workgroup-uniform
-      if (!cell_off<LIST>(a, c)) merge_head(a, c, seg - ((int)gridDim.x - G));
+      merge_head(a, c, seg - ((int)gridDim.x - G));
       return;
     }
     // (rows of logits and of the accumulator are padded to whole segments: readable whatever |J| is)
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a)
       // (from the next whole quad on: the quad that straddles the edge is written by the thread that owns it)
       for (int i = max(p_lo, (nJ + 3) & ~3) + tid; i < min(p_lo + NQ * 1024, n_all); i += kSelThreads) mu0[i] = 0.f;
     }
-    if (p_lo >= nJ || cell_off<LIST>(a, c)) return;
+    if (p_lo >= nJ) return;
     static_assert(kHistBins / 2 == kSelThreads, "one word of the histogram per thread");
     if (HIST) s_hist[tid] = 0u;
     __syncthreads();  // histogram cleared, statistics in place
@@ -358,8 +359,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
   __shared__ float s_jM[GT], s_jc[GT];
   __shared__ double s_scr[kSelThreads / 64][kSegStats];
   for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+    if (cell_off<LIST>(a, c)) return;
     if (!FROM_MU && a.merge_out != nullptr && seg >= (int)gridDim.x - G) {
-      if (!cell_off<LIST>(a, c)) merge_head(a, c, seg - ((int)gridDim.x - G));
+      merge_head(a, c, seg - ((int)gridDim.x - G));
       return;
     }
     const int p_lo = seg * kPriorSeg;
@@ -372,7 +374,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
     const float4 k4 = logits4(lg, rows, p[0], G);
     if (!FROM_MU) group_stats<GT>(a, c, kSelThreads / 64, s_jM, s_jc);
     const int nJ = nJ_of(a, c);
-    if (p_lo >= nJ || cell_off<LIST>(a, c)) return;
+    if (p_lo >= nJ) return;
     // (the next launch adds to the segments' histograms)
     if (seg % (kSelSeg / kPriorSeg) == 0) seg_hist(a, c.bh, seg / (kSelSeg / kPriorSeg))[tid] = 0u;
     // u(j) = p / D, 1 - u(j) + eps = ((|J| - 1 - p) + eps) / D + eps with D = |J| - 1 + eps: the second
