@@ -522,7 +522,10 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
 // JSTAT (dense kernel with exposed logits): the record's header also carries the statistics over the allowed set J alone,
 // { m, l, m_J, l_J } (the fast step and the dense kernel without logits leave the last two words).
 // WITH_O false: header only.
-template <bool JSTAT = false, bool WITH_O = true>
+// AT_ONCE: heads a wave merges at a time.  Two where a group has more than eight heads (the kernels with the plain K layout),
+// so that up to four heads take two chains of trips, not four: 16 heads, 33 records, fast step 13.5 -> 12.8 us.  One for
+// smaller groups, whose waves have one or two: the second head's code costs them 0.1 us.
+template <bool JSTAT = false, bool WITH_O = true, int AT_ONCE = 1>
 __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, int slot, const f32x4 (&acc)[8], float m_run,
                                           float l_run, float* red, int wave_stride, float m_j = 0.f, float l_j = 0.f) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -600,49 +603,69 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
   if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != (uint32_t)(o.n_split - 1)) return;
   if (lane == 0) __hip_atomic_store(o.arrive + w * kArriveStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int n_rec = o.n_split;
-  for (int hh = w; hh < G; hh += kWaves) {
-    const int P = hh * o.slot_cap * kRec;  // byte offset of the head's records
-    float M = kNeg, Z = 0.f;
-    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = half; s0 - half < n_rec; s0 += 16) {  // this half's records s0, s0 + 2, ...
-      float2 ml[8];
-      float4 r4[8];
+  for (int hh = w; hh < G; hh += AT_ONCE * kWaves) {
+    const bool two = AT_ONCE > 1 && hh + kWaves < G;  // wave-uniform
+    int P[AT_ONCE];  // byte offsets of the heads' records
+    float M[AT_ONCE], Z[AT_ONCE];
+    float4 t[AT_ONCE];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int rec = P + min(s0 + 2 * i, n_rec - 1) * kRec;
-        if (i == 0 || s0 - half + 2 * i < n_rec) {  // wave-uniform
-          ml[i] = load_device2(R, rec);
-          r4[i] = load_device4(R, rec + 16 + 16 * c);
-        } else {
-          ml[i] = make_float2(kNeg, 0.f);
-          r4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k = 0; k < AT_ONCE; ++k) {
+      P[k] = (hh + k * kWaves) * o.slot_cap * kRec;
+      M[k] = kNeg;
+      Z[k] = 0.f;
+      t[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int s0 = half; s0 - half < n_rec; s0 += 16) {  // this half's records s0, s0 + 2, ...
+      float2 ml[AT_ONCE][8];
+      float4 r4[AT_ONCE][8];
+#pragma unroll
+      for (int k = 0; k < AT_ONCE; ++k) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int rec = P[k] + min(s0 + 2 * i, n_rec - 1) * kRec;
+          if ((k == 0 || two) && (i == 0 || s0 - half + 2 * i < n_rec)) {  // wave-uniform
+            ml[k][i] = load_device2(R, rec);
+            r4[k][i] = load_device4(R, rec + 16 + 16 * c);
+          } else {
+            ml[k][i] = make_float2(kNeg, 0.f);
+            r4[k][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+          }
         }
       }
-      float Mn = M;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (s0 + 2 * i >= n_rec) ml[i] = make_float2(kNeg, 0.f);
-        Mn = fmaxf(Mn, ml[i].x);
-      }
-      const float f = fast_exp2(M - Mn);
-      Z *= f;
-      t.x *= f; t.y *= f; t.z *= f; t.w *= f;
+      for (int k = 0; k < AT_ONCE; ++k) {
+        if (k > 0 && !two) break;
+        float Mn = M[k];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float wgt = fast_exp2(ml[i].x - Mn);
-        const float wl = s0 + 2 * i < n_rec ? wgt : 0.f;  // (a half without any record has Mn = kNeg and weights 1)
-        Z += wl * ml[i].y;
-        t.x += wl * r4[i].x; t.y += wl * r4[i].y; t.z += wl * r4[i].z; t.w += wl * r4[i].w;
+        for (int i = 0; i < 8; ++i) {
+          if (s0 + 2 * i >= n_rec) ml[k][i] = make_float2(kNeg, 0.f);
+          Mn = fmaxf(Mn, ml[k][i].x);
+        }
+        const float f = fast_exp2(M[k] - Mn);
+        Z[k] *= f;
+        t[k].x *= f; t[k].y *= f; t[k].z *= f; t[k].w *= f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float wgt = fast_exp2(ml[k][i].x - Mn);
+          const float wl = s0 + 2 * i < n_rec ? wgt : 0.f;  // (a half without any record has Mn = kNeg and weights 1)
+          Z[k] += wl * ml[k][i].y;
+          t[k].x += wl * r4[k][i].x; t[k].y += wl * r4[k][i].y; t[k].z += wl * r4[k][i].z; t[k].w += wl * r4[k][i].w;
+        }
+        M[k] = Mn;
       }
-      M = Mn;
     }
-    // the two halves' sums meet
-    const float Mo = half_max(M);
-    const float f = fast_exp2(M - Mo);
-    Z = half_sum(Z * f);
-    t = make_float4(half_sum(t.x * f), half_sum(t.y * f), half_sum(t.z * f), half_sum(t.w * f));
-    const float inv = Z > 0.f ? 1.0f / Z : 0.f;
-    if (half == 0) store_out4(o.out_merge, (head0 + hh) * kHeadDim + 4 * c, make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv), o.out_bf16);
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k) {
+      if (k > 0 && !two) break;
+      // the two halves' sums meet
+      const float Mo = half_max(M[k]);
+      const float f = fast_exp2(M[k] - Mo);
+      const float Zs = half_sum(Z[k] * f);
+      const float4 ts = make_float4(half_sum(t[k].x * f), half_sum(t[k].y * f), half_sum(t[k].z * f), half_sum(t[k].w * f));
+      const float inv = Zs > 0.f ? 1.0f / Zs : 0.f;
+      if (half == 0)
+        store_out4(o.out_merge, (head0 + hh + k * kWaves) * kHeadDim + 4 * c, make_float4(ts.x * inv, ts.y * inv, ts.z * inv, ts.w * inv), o.out_bf16);
+    }
   }
 }
 
@@ -1303,7 +1326,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
   l_run = rows_sum(l_run);
   {
     __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+    finish_wg<false, true, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   }
   report_guard(a.guard, W.bad);  // last: the way to the record and the merge is the launch's critical path
 }
@@ -1465,7 +1488,7 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = f32x4{v, v, v, v};
     __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+    finish_wg<false, true, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   } else {
     fold ^= __shfl_xor(fold, 32);
     if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * a.slot_cap + slot) * kPartStride) + w] = fold;
@@ -1708,7 +1731,7 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
   l_run = rows_sum(l_run);
   {
     __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+    finish_wg<false, true, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   }
   report_guard(a.guard, bad);
 }
