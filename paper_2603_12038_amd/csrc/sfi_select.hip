@@ -243,7 +243,9 @@ __device__ __forceinline__ uint32_t* group_hist(const SelArgs& a, int bh, int gr
 // HIST: with the segment's histogram (long J, stages 2 and 3 follow; NQ = 2: a segment per workgroup).
 // ACCUM: windowed evidence (Eq. selector_mu over several queries): instead of ranking, add this
 // query's head-mean to the accumulator mu (or start it, a.accum_first).
-template <int NQ, bool HIST, bool ACCUM, bool LIST, int GT>
+// FLAGS: flags without a list; looked at before the logits are requested, which a fast sequence does not have.  (A kernel of its own:
+// the branch in front of the requests costs the slow step 0.4 us.)
+template <int NQ, bool HIST, bool ACCUM, bool LIST, bool FLAGS, int GT>
 __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.logits), "s"(a.lg_rows), "s"(a.part), "s"(a.G), "s"(a.alpha), "s"(a.jstat), "s"(a.merge_out));
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a)
   __shared__ float s_jM[GT], s_jc[GT];
   __shared__ uint32_t s_hist[HIST ? kHistBins / 2 : 1];
   for_cells<LIST>(a, [&](const Cell& c, const int tid) {
-    if (cell_off<LIST>(a, c)) return;  // in front of the logits' requests: a fast sequence has none to read
+    if (FLAGS && cell_off<LIST>(a, c)) return;
     const int p_lo = seg * (NQ * 1024);
     const float* lg = a.logits + (int64_t)c.bh * rows * a.ld_pos;
     int p[NQ];
@@ -349,7 +351,8 @@ __global__ __launch_bounds__(kSelThreads) void sel_finalize_kernel(const SelArgs
 // (1a) evidence f (as in mode 0) and the unnormalised prior pi_kn * pi_pos (Eqs. selector_prior_kn,
 // selector_u, selector_prior_pos) of 1024 positions, and their sums for lambda*.
 // FROM_MU: windowed evidence, f from the accumulator.
-template <bool FROM_MU, bool LIST, int GT>
+// FLAGS: as in the scoring kernel.
+template <bool FROM_MU, bool LIST, bool FLAGS, int GT>
 __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.logits), "s"(a.part), "s"(a.G), "s"(a.alpha), "s"(a.jstat), "s"(a.prior), "s"(a.segstat), "s"(a.n_seg_cap),
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
   __shared__ float s_jM[GT], s_jc[GT];
   __shared__ double s_scr[kSelThreads / 64][kSegStats];
   for_cells<LIST>(a, [&](const Cell& c, const int tid) {
-    if (cell_off<LIST>(a, c)) return;
+    if (FLAGS && cell_off<LIST>(a, c)) return;
     if (!FROM_MU && a.merge_out != nullptr && seg >= (int)gridDim.x - G) {
       merge_head(a, c, seg - ((int)gridDim.x - G));
       return;
@@ -972,53 +975,57 @@ static unsigned z_of(const SelArgs& a, int B, int n_wgs) {
 }
 static int ceil_seg(int nJ, int per) { return nJ > 0 ? (nJ + per - 1) / per : 1; }
 // Head counts the scoring kernels are built for: the smallest that holds G.
-template <int NQ, bool HIST, bool ACCUM, bool LIST>
+template <int NQ, bool HIST, bool ACCUM, bool LIST, bool FLAGS>
 static void launch_score_t(const SelArgs& a, dim3 grid, hipStream_t s) {
   const dim3 block(kSelThreads);
-  if (a.G <= 1) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 1>), grid, block, 0, s, a);
-  else if (a.G <= 2) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 2>), grid, block, 0, s, a);
-  else if (a.G <= 4) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 4>), grid, block, 0, s, a);
-  else if (a.G <= 5) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 5>), grid, block, 0, s, a);
-  else if (a.G <= 8) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 8>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, 16>), grid, block, 0, s, a);
+  if (a.G <= 1) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 1>), grid, block, 0, s, a);
+  else if (a.G <= 2) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 2>), grid, block, 0, s, a);
+  else if (a.G <= 4) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 4>), grid, block, 0, s, a);
+  else if (a.G <= 5) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 5>), grid, block, 0, s, a);
+  else if (a.G <= 8) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 8>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 16>), grid, block, 0, s, a);
 }
 hipError_t launch_sel_score(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s) {
   // with the merge on board: one more workgroup per query head
   const int n_seg = ceil_seg(nJ, hist ? kSelSeg : 1024) + (a.merge_out != nullptr ? a.G : 0);
   const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
   if (a.slow_list != nullptr) {
-    if (hist) launch_score_t<2, true, false, true>(a, grid, s);
-    else launch_score_t<1, false, false, true>(a, grid, s);
+    if (hist) launch_score_t<2, true, false, true, false>(a, grid, s);
+    else launch_score_t<1, false, false, true, false>(a, grid, s);
+  } else if (a.is_slow != nullptr) {
+    if (hist) launch_score_t<2, true, false, false, true>(a, grid, s);
+    else launch_score_t<1, false, false, false, true>(a, grid, s);
   } else {
-    if (hist) launch_score_t<2, true, false, false>(a, grid, s);
-    else launch_score_t<1, false, false, false>(a, grid, s);
+    if (hist) launch_score_t<2, true, false, false, false>(a, grid, s);
+    else launch_score_t<1, false, false, false, false>(a, grid, s);
   }
   return hipGetLastError();
 }
 hipError_t launch_sel_accum(const SelArgs& a, int B, int nJ, hipStream_t s) {
-  launch_score_t<1, false, true, false>(a, dim3(ceil_seg(nJ, 1024) + (a.merge_out != nullptr ? a.G : 0), a.Hkv, B), s);
+  launch_score_t<1, false, true, false, false>(a, dim3(ceil_seg(nJ, 1024) + (a.merge_out != nullptr ? a.G : 0), a.Hkv, B), s);
   return hipGetLastError();
 }
 hipError_t launch_sel_finalize(const SelArgs& a, int B, int nJ, hipStream_t s) {
   hipLaunchKernelGGL(sel_finalize_kernel, dim3(ceil_seg(nJ, kSelSeg), a.Hkv, B), dim3(kSelThreads), 0, s, a);
   return hipGetLastError();
 }
-template <bool FROM_MU, bool LIST>
+template <bool FROM_MU, bool LIST, bool FLAGS>
 static void launch_prior_t(const SelArgs& a, dim3 grid, hipStream_t s) {
   const dim3 block(kSelThreads);
-  if (FROM_MU || a.G <= 1) hipLaunchKernelGGL((sel_prior_kernel<FROM_MU, LIST, 1>), grid, block, 0, s, a);
-  else if (a.G <= 2) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 2>), grid, block, 0, s, a);
-  else if (a.G <= 4) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 4>), grid, block, 0, s, a);
-  else if (a.G <= 5) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 5>), grid, block, 0, s, a);
-  else if (a.G <= 8) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 8>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((sel_prior_kernel<false, LIST, 16>), grid, block, 0, s, a);
+  if (FROM_MU || a.G <= 1) hipLaunchKernelGGL((sel_prior_kernel<FROM_MU, LIST, FLAGS, 1>), grid, block, 0, s, a);
+  else if (a.G <= 2) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 2>), grid, block, 0, s, a);
+  else if (a.G <= 4) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 4>), grid, block, 0, s, a);
+  else if (a.G <= 5) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 5>), grid, block, 0, s, a);
+  else if (a.G <= 8) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 8>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 16>), grid, block, 0, s, a);
 }
 hipError_t launch_sel_full(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kPriorSeg) + (a.merge_out != nullptr ? a.G : 0);
   const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
-  if (a.f_from_mu) launch_prior_t<true, false>(a, grid, s);  // (a window's evidence is never ranked in the ragged step)
-  else if (a.slow_list != nullptr) launch_prior_t<false, true>(a, grid, s);
-  else launch_prior_t<false, false>(a, grid, s);
+  if (a.f_from_mu) launch_prior_t<true, false, false>(a, grid, s);  // (a window's evidence is never ranked in the ragged step)
+  else if (a.slow_list != nullptr) launch_prior_t<false, true, false>(a, grid, s);
+  else if (a.is_slow != nullptr) launch_prior_t<false, false, true>(a, grid, s);
+  else launch_prior_t<false, false, false>(a, grid, s);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int n_span = ceil_seg(nJ, kFuseSpan);
