@@ -171,20 +171,30 @@ int dense_splits_for(const sfi_ctx* x, int max_len, bool mixed) {
   return s;
 }
 
-// A launch that leaves evidence only reads no V: half of a tile's loads are missing, and a wave spends more of a tile's time
-// on its arithmetic and its waits.  Two workgroups per compute unit (which the small stash leaves room for) fill each
-// other's gaps, as long as a wave's share fits that stash in one piece and the records suffice; a launch that stays as it
-// is keeps the large stash.  (Query of a window, 8 KV heads: 2 sequences of 12000..16384 rows 21.2 -> 19.6 us, 8 of
-// 2000..4000 rows, full Selector, 18.3 -> 17.3 us; the small stash without the second workgroup costs 1 %.)
-void split_evidence(const sfi_ctx* x, AttnArgs* a, int max_len) {
-  if (x->dense_target_wgs > 0) return;
+// Workgroups per pair of a launch that leaves evidence only (attn_evidence_kernel).  Up to one workgroup per unit, a wave takes
+// two tiles (it has two on their way at once); up to four per unit pay where each wave still takes four, and more, up to 32
+// per pair (every one leaves a record that the accumulation reads), where each takes six: they even unequal lengths out.
+// Then as few as leave the longest share what it is.  (Windows, us per query and tiles per wave: 2 x 12000..16384 rows 8: 17.8, 4: 17.1, 3: 19.1,
+// 2: 19.4; 2 x 4096 rows 8: 14.4, 4: 10.9, 2: 9.7; 8 x 8000..16000 rows 32: 46.9, 8: 42.6, 4: 41.4, 2: 50.0; 24 x 3000..8000 rows of 4 groups of 16
+// heads 32: 49.8, 6: 45.3, 4: 47.2, 2: 56.2; 20 x 8000..32000 rows 42: 217, 16: 199, 8: 196, 6: 197; 32 x 8000..16000 rows 125: 202, 32: 187, 6: 182;
+// 4 x 60000..130000 rows in 8, 32 and 63 workgroups per pair: 198, 175, 182.  The dense launch planned on the device without
+// its V half: 218, 198, 184 for the last three.)
+int evidence_splits_for(const sfi_ctx* x, int max_len) {
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;  // (a query under the causal mask sees no more of J than the window has)
-  const int tiles = nJ > 0 ? (nJ + kTile - 1) / kTile : 0;
-  const int per_wave = (tiles + 2 * kWaves * a->n_split - 1) / (2 * kWaves * a->n_split);
-  if (2 * a->n_split > kMaxSplits || 2 * kWaves * a->n_split > tiles + kWaves - 1) return;
-  if (per_wave * kTile * (x->G + (a->with_knorm ? 1 : 0)) > kStashFloats) return;
-  a->n_split *= 2;
-  a->big_stash = 0;
+  const int tiles = nJ > 0 ? (nJ + kTile - 1) / kTile : 1;
+  const int pairs = x->cfg.batch * x->cfg.n_kv_heads;
+  auto splits = [&](int tiles_per_wave, int wgs) {
+    const int most = (tiles + tiles_per_wave * kWaves - 1) / (tiles_per_wave * kWaves), s = wgs / pairs;
+    return s < most ? s : most;
+  };
+  int s = splits(2, x->n_cu);
+  if (s < splits(4, 4 * x->n_cu)) s = splits(4, 4 * x->n_cu);
+  if (s < splits(6, 32 * pairs)) s = splits(6, 32 * pairs);
+  if (x->dense_target_wgs > 0) s = splits(1, x->dense_target_wgs);
+  if (s > kMaxSplits) s = kMaxSplits;
+  if (s < 1) s = 1;
+  const int per_wave = (tiles + kWaves * s - 1) / (kWaves * s);
+  return (tiles + kWaves * per_wave - 1) / (kWaves * per_wave);
 }
 
 // Where the dense launch plans itself on the device: more than one sequence (with one there is nothing to even out, and
@@ -192,10 +202,10 @@ void split_evidence(const sfi_ctx* x, AttnArgs* a, int max_len) {
 // other launch.  Workgroups per KV head: as many as give every compute unit one; where the heads do not divide the units
 // (fewer than nine in ten busy), up to four rounds.  A workgroup takes at least a tile per wave, and enough tiles that the
 // longest sequence stays within its records.  Outside the ragged step the other launch stays where it is the better one:
-// - few tiles: below 8 per wave (16 without V: half the bytes, and two workgroups per unit to set against).  Per cell /
+// - few tiles: below 8 per wave.  Per cell /
 //   planned, us a layer, 8 KV heads: 4 x 2000..4000 rows 19.9 / 22.4 (4 tiles per wave), 4 x 4096..8192 33.1 / 34.8 (8), 8 x 4000..8192
 //   dense 41.1 / 39.8 (8), 4 x 8000..16000 40.1 / 39.1 (16), 8 x 6000..12000 57.5 / 54.0 (24), 8 x 8000..16000 74.7 / 68.6 (32);
-//   equal lengths gain nothing: 8 x 8192 42.3 / 45.6; a window of 8 queries, 4 x 8000..16000 221 / 244 (16), 8 x 8000..16000 438 / 415 (31);
+//   equal lengths gain nothing: 8 x 8192 42.3 / 45.6;
 // - many sequences: every one a workgroup meets costs it a way out and in.  512 x 300..900 rows dense 214 / 389, 1000 x 200..600 302 /
 //   727, 256 x 1000..4000 450 / 468.  (The line, two pairs per unit, does not see their length: 128 x 2000..8000 would gain,
 //   480 / 424, and 96 x 2000..16000, 772 / 553.)
@@ -204,7 +214,7 @@ void plan_dense(sfi_ctx* x, AttnArgs* a, int max_len, bool mixed) {
   const int B = x->cfg.batch, Hkv = x->cfg.n_kv_heads;
   if (B < 2 || B > kListCap || x->dense_target_wgs > 0 || x->dense_wide) return;
   const int tiles = (max_len + kTile - 1) / kTile + 2;  // J, then sink and recent rows: a ragged tile at the end of each
-  if (!mixed && (B * Hkv > 2 * x->n_cu || (int64_t)tiles * B * Hkv < (a->no_v ? 16 : 8) * (int64_t)kWaves * x->n_cu)) return;
+  if (!mixed && (B * Hkv > 2 * x->n_cu || (int64_t)tiles * B * Hkv < 8 * (int64_t)kWaves * x->n_cu)) return;
   int best = 1;
   double fill = 0.0;
   for (int rounds = 1; rounds <= 4 && fill < 0.9; ++rounds) {
@@ -584,14 +594,20 @@ int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   AttnArgs a;
   fill_attn(x, &a, q, K, V, ctx_len);
   a.q_len = q_len;
-  a.n_split = dense_splits_for(x, ml, false);
   set_dense_bounds(x, &a, ml);
   a.logits = x->ws.logits;
   a.with_knorm = x->cfg.selector_mode == 1;
+  if (out == nullptr) {  // evidence only (sfi_evidence_add without an output)
+    a.n_split = evidence_splits_for(x, ml);
+    x->last_dense_splits = a.n_split;
+    x->last_dense_planned = 0;
+    StageTimer t(x, st, SFI_STAGE_ATTN);
+    SFI_TRY(launch_attn_evidence(a, x->cfg.batch, a.n_split, st));
+    return t.stop() ? SFI_OK : SFI_ELAUNCH;
+  }
+  a.n_split = dense_splits_for(x, ml, false);
   a.big_stash = 1;  // every sequence is dense: one workgroup per compute unit, half as many write bursts
-  a.no_v = out == nullptr;  // evidence only (sfi_evidence_add without an output)
   plan_dense(x, &a, ml, false);
-  if (a.no_v && a.plan_batch == 0) split_evidence(x, &a, ml);
   x->last_dense_splits = a.n_split;
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (merge_later) return SFI_OK;  // the Selector's scoring launch merges

@@ -84,17 +84,22 @@ __device__ __forceinline__ int row_quad(int v) {
 template <int I>
 __device__ __forceinline__ float row_quad(float v) { return __int_as_float(row_quad<I>(__float_as_int(v))); }
 
-// K and V rows are read once per step: stream them past the caches.  base is uniform over the
+// K and V rows are read once per step: stream them past the caches (STREAM false: rows that the next launches read
+// again).  base is uniform over the
 // workgroup, off a 32-bit byte offset (the API rejects layouts whose per-head extent exceeds 4 GiB).
 // The pieces of a row sit at constant distances (imm) behind its offset and share the one offset register.
+template <bool STREAM = true>
 __device__ __forceinline__ uint4 load_row16(const char* base, uint32_t off, int imm = 0) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  if (!STREAM) return *reinterpret_cast<const uint4*>(base + off + imm);
   const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + off + imm));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 // The same with a 64-bit byte offset: block pools of a paged cache may exceed 4 GiB.
+template <bool STREAM = true>
 __device__ __forceinline__ uint4 load_row16(const char* base, uint64_t off, int imm = 0) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  if (!STREAM) return *reinterpret_cast<const uint4*>(base + off + imm);
   const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + off + imm));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
@@ -395,15 +400,15 @@ __device__ __forceinline__ void stage_logits(float* stage, const float (&y)[8], 
 
 // Ragged last tile: positions >= N carry no weight; their V rows may hold anything, so zero them
 // to keep 0 * v finite.
-template <bool WITH_V = true, bool WIDE = false>  // WITH_V false: the tile holds no V rows (evidence-only pass)
+template <bool WIDE = false>
 __device__ __forceinline__ void mask_tail(Tile& T, float (&y)[8], int jg, int p0, int N) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const bool oka = p0 + slot_pos<WIDE>(jg, i) < N, okb = p0 + slot_pos<WIDE>(jg, 4 + i) < N;
     y[i] = oka ? y[i] : kNeg;
     y[4 + i] = okb ? y[4 + i] : kNeg;
-    if (WITH_V && !oka) T.v[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (WITH_V && !okb) T.v[4 + i] = make_uint4(0u, 0u, 0u, 0u);
+    if (!oka) T.v[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (!okb) T.v[4 + i] = make_uint4(0u, 0u, 0u, 0u);
   }
 }
 
@@ -521,11 +526,10 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
 // red: G x 128 floats of LDS per wave, wave_stride floats apart.
 // JSTAT (dense kernel with exposed logits): the record's header also carries the statistics over the allowed set J alone,
 // { m, l, m_J, l_J } (the fast step and the dense kernel without logits leave the last two words).
-// WITH_O false: header only.
 // AT_ONCE: heads a wave merges at a time.  Two where a group has more than eight heads (the kernels with the plain K layout),
 // so that up to four heads take two chains of trips, not four: 16 heads, 33 records, fast step 13.5 -> 12.8 us.  One for
 // smaller groups, whose waves have one or two: the second head's code costs them 0.1 us.
-template <bool JSTAT = false, bool WITH_O = true, int AT_ONCE = 1>
+template <bool JSTAT = false, int AT_ONCE = 1>
 __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, int slot, const f32x4 (&acc)[8], float m_run,
                                           float l_run, float* red, int wave_stride, float m_j = 0.f, float l_j = 0.f) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -545,7 +549,7 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int hh = 4 * jg + i;
-    if (WITH_O && hh < G) {
+    if (hh < G) {
       float* dst = red + w * wave_stride + hh * kHeadDim + n * 8;
       *reinterpret_cast<float4*>(dst) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
       *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
@@ -565,7 +569,7 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
     float4 r[kWaves];
 #pragma unroll
     for (int ww = 0; ww < kWaves; ++ww)
-      r[ww] = WITH_O ? *reinterpret_cast<const float4*>(red + ww * wave_stride + hh * kHeadDim + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      r[ww] = *reinterpret_cast<const float4*>(red + ww * wave_stride + hh * kHeadDim + 4 * c);
     const float M = fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w));
     const float f[kWaves] = {fast_exp2(m4.x - M), fast_exp2(m4.y - M), fast_exp2(m4.z - M), fast_exp2(m4.w - M)};
     float4 t = make_float4(r[0].x * f[0], r[0].y * f[0], r[0].z * f[0], r[0].w * f[0]);
@@ -584,7 +588,7 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
         if (c == 0) store_device2(R, off, M, ls);
       } else {
         float* dst = pair_base + (hh * o.slot_cap + slot) * kPartStride;
-        if (WITH_O) *reinterpret_cast<float4*>(dst + 4 + 4 * c) = t;
+        *reinterpret_cast<float4*>(dst + 4 + 4 * c) = t;
         if (JSTAT) {
           const float4 mj = *reinterpret_cast<const float4*>(&s_mj[hh][0]), lj = *reinterpret_cast<const float4*>(&s_lj[hh][0]);
           const float MJ = fmaxf(fmaxf(mj.x, mj.y), fmaxf(mj.z, mj.w));
@@ -713,7 +717,6 @@ struct ListWalk {
 // step's launch with a workgroup per cell keeps two, although that kernel spills 6 to 26 of its 256 registers: with one,
 // 12 sequences of 5003 to 30011 rows, 4 of them slow, take 110 us a step instead of 104, 1100 of 100 to 500 rows, 100 slow,
 // 249 instead of 215).
-// NOV: evidence only -- no V row is read, no P V product, the records carry the softmax statistics alone.
 // PLANNED: the caller has the sequence's length and a range of its tiles (attn_dense_planned_kernel).
 struct DenseShare {
   int first, step;   // tiles of wave w: first + w, first + w + step, ... below end (step: a multiple of the waves)
@@ -723,7 +726,7 @@ struct DenseShare {
   int bad;           // PLANNED: guard bits so far
   bool have_k;       // PLANNED: K rows of the first tile are on their way into T
 };
-template <int EXPOSE, bool PAGED, bool BIG, bool NOV, bool WIDE, bool PLANNED>
+template <int EXPOSE, bool PAGED, bool BIG, bool WIDE, bool PLANNED>
 __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& sh, const int h, const int b, Tile& T, const int tid_bias = 0) {
   constexpr int kStash = BIG ? 2 * kStashFloats : kStashFloats;
   // per-wave LDS: the logits stash, and at the end the wave's O for the combine (finish_wg)
@@ -756,14 +759,14 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   // (tile t, position i is cache row n_sink + 32 t + i), tiles [nTJ, nTJ + nTS) cover the sink rows
   // followed by the recent window, which the Selector never ranks.  The waves of the workgroups on a
   // (b, h) pair share its tiles evenly.  A wave's J tiles come first: the J-only softmax statistics the Selector needs
-  // are the wave's running ones at the point where its J tiles end.  An evidence-only pass has nothing to do beyond J.
+  // are the wave's running ones at the point where its J tiles end.
   // Not PLANNED, the rows of the wave's first tile follow from the block index alone (almost always a J tile):
   // their loads go out before ctx_len arrives, clamped to the launch's row bound.
   const int first = sh.first + w, step = sh.step;
   // (a paged cache has valid blocks only up to ctx_len: no load before ctx_len is known)
   if (!PLANNED && !PAGED && first < a.max_tiles) {
     issue_k_affine<WIDE>(T, R, a.n_sink + first * kTile, a.row_cap);
-    if (!NOV) issue_v_affine<WIDE>(T, R, a.n_sink + first * kTile, a.row_cap);
+    issue_v_affine<WIDE>(T, R, a.n_sink + first * kTile, a.row_cap);
   }
   bf16x8 qreg[4];
   load_q_raw<WIDE>(qreg, a.q, head0, G, jg, n);
@@ -777,7 +780,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   const int rs = min(max(a.n_sink, L - recent), L);
   const int NS = nS + (L - rs);
   const int nTS = (NS + kTile - 1) / kTile;
-  const int nT = PLANNED ? min(sh.end, nTJ + (NOV ? 0 : nTS)) : nTJ + (NOV ? 0 : nTS);
+  const int nT = PLANNED ? min(sh.end, nTJ + nTS) : nTJ + nTS;
   const int nTJw = min(nTJ, nT);
   const int K = first < nT ? (nT - first + step - 1) / step : 0;      // tiles of this wave
   const int KJ = first < nTJw ? (nTJw - first + step - 1) / step : 0;  // ... of which in J
@@ -809,7 +812,6 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
     }
   };
   auto issue_v_tile = [&](Tile& T, int t) {
-    if (NOV) return;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       T.v[i] = load_row16(R.Vb, (uint32_t)row_for(t, slot_pos<WIDE>(jg, i)) * R.v_st + R.v_lane);
@@ -835,7 +837,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
     pa_n = P.page_of(row_for(first + 2 * step, n));
     pb_n = P.page_of(row_for(first + 2 * step, 16 + n));
     __builtin_amdgcn_sched_barrier(0);
-    if (!NOV) issue_v_rows<uint64_t>(T, R, pra, prb);
+    issue_v_rows<uint64_t>(T, R, pra, prb);
     __builtin_amdgcn_sched_barrier(0);
   } else if (K > 0 && (PLANNED || first >= nTJ)) {  // (short context: the first tile is a sink / recent tile after all)
     if (!PLANNED || !sh.have_k || first >= nTJ) issue_k_tile(T, first);
@@ -848,7 +850,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
     __builtin_amdgcn_sched_barrier(0);
     if (PAGED) {
       issue_k_rows<uint64_t>(T2, R, pra2, prb2);
-      if (!NOV) issue_v_rows<uint64_t>(T2, R, pra2, prb2);
+      issue_v_rows<uint64_t>(T2, R, pra2, prb2);
     } else {
       issue_k_tile(T2, first + step);
       issue_v_tile(T2, first + step);
@@ -934,13 +936,13 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
     }
     const int p0 = (inJ ? t : t - nTJ) * kTile;
     const int N = inJ ? NJ : NS;
-    if (p0 + kTile > N) mask_tail<!NOV, WIDE>(T, y, jg, p0, N);
+    if (p0 + kTile > N) mask_tail<WIDE>(T, y, jg, p0, N);
     bf16x8 a_hi, a_lo;
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
-    if (!NOV) pv_phase(T, a_hi, a_lo, acc);
+    pv_phase(T, a_hi, a_lo, acc);
     if (!kRefill) return;
-    if (PAGED && !NOV) issue_v_rows<uint64_t>(T, R, pra, prb);
-    else if (!PAGED) issue_v_tile(T, t + NB * step);
+    if (PAGED) issue_v_rows<uint64_t>(T, R, pra, prb);
+    else issue_v_tile(T, t + NB * step);
   };
   const std::integral_constant<bool, true> refill;
   const std::integral_constant<bool, false> last;
@@ -973,16 +975,16 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
     o.out_direct = o.out_merge;
     o.out_merge = nullptr;
   }
-  finish_wg<EXPOSE != 0, !NOV>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), &s_patch[0][0], kPatch, m_j,
+  finish_wg<EXPOSE != 0>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), &s_patch[0][0], kPatch, m_j,
                                EXPOSE != 0 ? rows_sum(l_j) : 0.f);
   report_guard(a.guard, bad);
 }
 // One workgroup per (split, KV head, sequence) cell: wave w of split s takes tiles 4 s + w, 4 (s + n_split) + w, ...
-template <int EXPOSE, bool PAGED, bool BIG = false, bool NOV = false, bool WIDE = false>
+template <int EXPOSE, bool PAGED, bool BIG = false, bool WIDE = false>
 __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(const AttnArgs a) {
   const DenseShare sh{(int)blockIdx.x * kWaves, a.n_split * kWaves, 0, (int)blockIdx.x, a.n_split, 0, 0, 0, false};
   Tile T;
-  dense_body<EXPOSE, PAGED, BIG, NOV, WIDE, false>(a, sh, blockIdx.y, blockIdx.z, T);
+  dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.y, blockIdx.z, T);
 }
 // The launch planned on the device: more than one sequence, every one with a length of its own (which only the device
 // knows) and, in the ragged step (sfi_mixed_step*), only some of them slow.  With a workgroup per cell the shares follow the
@@ -1018,7 +1020,7 @@ __device__ __forceinline__ int plan_border(const PlanArgs& p, int P, int rank, i
   if (P == p.total) x = p.W << kShareLg, off = 0;
   return x;
 }
-template <int EXPOSE, bool PAGED, bool NOV>
+template <int EXPOSE, bool PAGED>
 __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
                                                                              uint32_t strides, int B, int W_max, float per_min, int n_sink,
                                                                              int recent_in, int len_cap, const AttnArgs a) {
@@ -1030,7 +1032,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     window_view(q_len, b, guarded_len(L_in, len_cap, bad), recent_in, L, recent);
     const int NJ = max(0, L - recent - n_sink);
     const int nS = min(n_sink, L), rs = min(max(n_sink, L - recent), L);
-    return max(1, (NJ + kTile - 1) / kTile + (NOV ? 0 : (nS + (L - rs) + kTile - 1) / kTile));
+    return max(1, (NJ + kTile - 1) / kTile + (nS + (L - rs) + kTile - 1) / kTile);
   };
   // this lane's sequences: per consecutive ones, tiles of sequence i among them (0: takes no part)
   const int per = (B + 63) / 64;
@@ -1088,7 +1090,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     sh.n_rec = even;
     sh.have_k = !PAGED;
     if (slot_even == 0 && h == 0 && threadIdx.x == 0) a.seq_rec[b_even] = even;
-    dense_body<EXPOSE, PAGED, true, NOV, false, true>(a, sh, h, b_even, T);
+    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b_even, T);
     return;
   }
   const int inc_t = (int)wave_incl_scan((uint32_t)tiles), inc_c = (int)wave_incl_scan((uint32_t)count);
@@ -1161,7 +1163,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     int zero = 0;
     asm volatile("" : "+s"(zero));
     sh.have_k = false;
-    dense_body<EXPOSE, PAGED, true, NOV, false, true>(a, sh, h, b, T, zero);
+    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b, T, zero);
     P += t_b;
     if (__builtin_amdgcn_readfirstlane(x1) >= start + (1 << kShareLg)) return;
     do {  // (there is one: the list goes on)
@@ -1171,6 +1173,205 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     L_in = ctx_len[b * ms];
     __syncthreads();  // the combine of this sequence is read before the next one's logits go into the same LDS
   }
+}
+
+// ------------------------------------------------------------------------------------------------
+// evidence kernel: the logits of one query over the allowed set J (and the key norms), and their softmax statistics;
+// no V row is read.  This is a query of a window: the next launches read the same K rows, so their loads leave them to the
+// caches instead of streaming past them (16 queries over 58 MB of K: 309 us streamed, 274 not; over 800 MB, more than the caches hold, 4 queries 835 / 747: the
+// two halves of a 128-byte line are asked for one after the other, and a streamed line may be gone in between).
+// What bounds it: the rows, at the rate the last-level cache gives them (58 MB: loads alone 10.0 us behind a launch of
+// 1.6 us).  So every wave has two tiles on their way all the time, each refilled when its products are done; the
+// statistics are kept per lane (its own positions of its head) and meet once at the end, so that nothing in the loop
+// crosses lanes; the code is a loop of one step, and the first tile is requested from arguments in registers.  The two
+// tiles lie a workgroup's stride apart: as neighbours (16 KB in one piece per wave) they take 13 % longer.
+// Against the dense kernel without its V half, which this replaces, us per query with the accumulation behind it, 8 KV heads: 2 sequences of
+// 12000..16384 rows with norms 19.9 -> 17.0; 2 x 4096 11.7 -> 9.6; 8 x 8000..16000 51.7 -> 42.6; 1 x 130000 54.6 -> 45.1.
+// ------------------------------------------------------------------------------------------------
+constexpr int kEvidenceStash = 2432;  // floats of logits a wave parks in LDS: four tiles of 16 heads and norms, 15 of 4 heads and norms
+struct KPair {    // two tiles of K: tile hf is blocks 2 hf and 2 hf + 1
+  uint4 k[4][4];  // block i: row 16 (i & 1) + n of its tile, dims kb * 32 + 8 * jg .. + 8
+};
+template <int EXPOSE, bool PAGED>
+__global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const uint16_t* K, const int32_t* ctx_len, const int32_t* q_len,
+                                                                        const int64_t k_sb, const int64_t k_sh, const uint32_t k_st,
+                                                                        const int n_sink, const int row_cap, const int len_cap,
+                                                                        const AttnArgs a) {
+  typedef typename RowOff<PAGED>::type OffT;
+  __shared__ __align__(16) float s_stash[kWaves][kEvidenceStash];
+  __shared__ __align__(16) float s_m[16][kWaves], s_l[16][kWaves];
+  const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int jg = lane >> 4, n = lane & 15;
+  const char* const Kb = reinterpret_cast<const char*>(K + b * k_sb + h * k_sh);
+  const uint32_t k_lane = jg * 16;
+  const int first = slot * kWaves + w;
+  int bad = 0;
+  Pages P;
+  int pg[4], pg_row[4];  // PAGED: block-table entries of the unit's rows and the rows they were read for
+  auto pages_for = [&](int hf, int t, int hi) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      pg_row[2 * hf + i] = (int)min((uint32_t)n_sink + (uint32_t)(t * kTile + 16 * i + n), (uint32_t)hi);
+      pg[2 * hf + i] = P.page_of(pg_row[2 * hf + i]);
+    }
+  };
+  // rows of tile t into half hf; rows above hi (no position of J) read row hi
+  auto issue = [&](KPair& U, int hf, int t, int hi, int last_used) {
+    OffT o[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      int row = (int)min((uint32_t)n_sink + (uint32_t)(t * kTile + 16 * i + n), (uint32_t)hi);  // (n_sink is not bounded)
+      if (PAGED) {
+        int odd = 0;
+        row = P.phys(pg_row[2 * hf + i], pg[2 * hf + i], odd);
+        if (pg_row[2 * hf + i] <= last_used) bad |= odd;
+      }
+      o[i] = (OffT)((OffT)(uint32_t)row * k_st + k_lane);
+    }
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) U.k[2 * hf + i][kb] = load_row16<false>(Kb, o[i], kb * 64);
+  };
+  KPair U;
+  // The first tile's rows follow from the arguments that the wave finds in registers (a paged cache's from the length on).
+  if (!PAGED) issue(U, 0, first, row_cap, 0);
+  const int L_in = ctx_len[b];
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(a.q), "s"(a.logits), "s"(a.part), "s"(a.guard), "s"(a.ld_pos), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.recent), "s"(a.n_split),
+               "s"(a.scale_log2));
+  const int G = a.G;
+  const int64_t head0 = (int64_t)b * a.Hq + h * G;
+  const int step = a.n_split * kWaves;
+  if (!PAGED) issue(U, 1, first + step, row_cap, 0);
+  bf16x8 qreg[4];
+  load_q_raw(qreg, a.q, head0, G, jg, n);
+  int L, recent;
+  window_view(q_len, b, guarded_len(L_in, len_cap, bad), a.recent, L, recent);
+  const int NJ = max(0, L - recent - n_sink);
+  const int nT = (NJ + kTile - 1) / kTile;
+  const int hi = max(n_sink + NJ - 1, 0);
+  const int last_used = NJ > 0 ? hi : -1;
+  if (PAGED && first < nT) {
+    P = pages_of(a, b, L);
+    pages_for(0, first, hi);
+    pages_for(1, first + step, hi);
+    issue(U, 0, first, hi, last_used);
+    issue(U, 1, first + step, hi, last_used);
+    pages_for(0, first + 2 * step, hi);
+    pages_for(1, first + 3 * step, hi);
+  }
+  mask_q(qreg, G, n);
+
+  const int rows_exp = G + (EXPOSE == 2 ? 1 : 0);
+  const int tile_f = rows_exp * kTile;
+  const int stash_cap = kEvidenceStash / tile_f;
+  float* const stash = &s_stash[w][0];
+  float* const lg = a.logits + (int64_t)(b * a.Hkv + h) * rows_exp * a.ld_pos;
+  int n_stashed = 0, k_flushed = 0;
+  auto flush = [&]() {
+    __builtin_amdgcn_wave_barrier();
+    const int n_f4 = n_stashed * (tile_f / 4);
+    for (int f = lane; f < n_f4; f += 64) {
+      const int i = f / (tile_f / 4), rem = f - i * (tile_f / 4);
+      const int t = first + (k_flushed + i) * step;
+      *reinterpret_cast<float4*>(lg + ((int64_t)t * tile_f + rem * 4)) = *reinterpret_cast<const float4*>(stash + f * 4);
+    }
+    __builtin_amdgcn_wave_barrier();
+    k_flushed += n_stashed;
+    n_stashed = 0;
+  };
+  // statistics of the positions this lane has seen (the four lanes of a head meet at the end)
+  float m_run = kNeg, l_run = 0.f;
+  // tiles t and t + step; the second may lie past the end, then it counts for nothing
+  auto pair_step = [&](int t, auto refill) {
+    float y[4][4];
+    float k2[4];  // (lanes with jg == n / 4) squared norm of row 16 i + n: the diagonal of K K^T
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f32x4 s = {0.f, 0.f, 0.f, 0.f}, d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(U.k[i][kb]), qreg[kb], s, 0, 0, 0);
+        if (EXPOSE == 2) d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(U.k[i][kb]), as_bf16x8(U.k[i][kb]), d, 0, 0, 0);
+      }
+      if (EXPOSE == 2) k2[i] = (n & 3) == 0 ? d[0] : (n & 3) == 1 ? d[1] : (n & 3) == 2 ? d[2] : d[3];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) y[i][j] = s[j] * a.scale_log2;
+      if (decltype(refill)::value && (i & 1) != 0) {
+        issue(U, i >> 1, t + (2 + (i >> 1)) * step, hi, last_used);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (decltype(refill)::value && PAGED) {
+      pages_for(0, t + 4 * step, hi);
+      pages_for(1, t + 5 * step, hi);
+    }
+    float m_new = m_run;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      if (hf == 1 && t + step >= nT) break;
+      float* st = stash + n_stashed * tile_f;
+#pragma unroll
+      for (int i = 2 * hf; i < 2 * hf + 2; ++i) {
+        // (positions past |J| land in the padding, never used)
+        float* row = st + (i & 1) * 16;
+        if (n < G) *reinterpret_cast<float4*>(row + n * kTile + 4 * jg) = make_float4(y[i][0], y[i][1], y[i][2], y[i][3]);
+        if (EXPOSE == 2 && jg == (n >> 2)) row[G * kTile + n] = k2[i];
+      }
+      if (++n_stashed == stash_cap) flush();
+    }
+    bool ok[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        ok[i][j] = (t + (i >> 1) * step) * kTile + 16 * (i & 1) + 4 * jg + j < NJ;
+        m_new = fmaxf(m_new, ok[i][j] ? y[i][j] : kNeg);
+      }
+    l_run *= fast_exp2(m_run - m_new);
+    m_run = m_new;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) l_run += ok[i][j] ? fast_exp2(y[i][j] - m_new) : 0.f;
+  };
+  if (first < nT) {
+    int t = first;
+    for (; t + 2 * step < nT; t += 2 * step) pair_step(t, std::integral_constant<bool, true>());
+    pair_step(t, std::integral_constant<bool, false>());
+    flush();
+  }
+  const float M = rows_max(m_run);
+  const float l = rows_sum(l_run * fast_exp2(m_run - M));
+  if (lane < 16) {
+    s_m[lane][w] = M;
+    s_l[lane][w] = l;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < G) {  // the record's header: no output, and nothing beyond J
+    const float4 m4 = *reinterpret_cast<const float4*>(&s_m[threadIdx.x][0]), l4 = *reinterpret_cast<const float4*>(&s_l[threadIdx.x][0]);
+    const float Mw = fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w));
+    const float lw = l4.x * fast_exp2(m4.x - Mw) + l4.y * fast_exp2(m4.y - Mw) + l4.z * fast_exp2(m4.z - Mw) + l4.w * fast_exp2(m4.w - Mw);
+    *reinterpret_cast<float4*>(a.part + ((head0 + threadIdx.x) * kSlotCap + slot) * kPartStride) = make_float4(Mw, lw, Mw, lw);
+  }
+  report_guard(a.guard, bad);
+}
+hipError_t launch_attn_evidence(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
+  const dim3 grid(n_slots, a.Hkv, B), block(kAttnThreads);
+#define SFI_EVIDENCE(EXPOSE, PAGED)                                                                                               \
+  hipLaunchKernelGGL((attn_evidence_kernel<EXPOSE, PAGED>), grid, block, 0, s, a.K, a.ctx_len, a.q_len, a.k_sb, a.k_sh,           \
+                     (uint32_t)a.k_st * 2u, a.n_sink, a.row_cap, a.len_cap, a)
+  if (a.table != nullptr) {
+    if (a.with_knorm) SFI_EVIDENCE(2, true);
+    else SFI_EVIDENCE(1, true);
+  } else {
+    if (a.with_knorm) SFI_EVIDENCE(2, false);
+    else SFI_EVIDENCE(1, false);
+  }
+#undef SFI_EVIDENCE
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1308,7 +1509,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
       sAn = W.sel_at_nonempty(pn + pstep + n);
       sBn = W.sel_at_nonempty(pn + pstep + 16 + n);
     }
-    if (p0 + kTile > W.N) mask_tail<true, WIDE>(T, y, jg, p0, W.N);
+    if (p0 + kTile > W.N) mask_tail<WIDE>(T, y, jg, p0, W.N);
     bf16x8 a_hi, a_lo;
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     pv_phase(T, a_hi, a_lo, acc);
@@ -1318,7 +1519,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
   if (first < nT) {
     float y[8];
     qk_phase<WIDE>(T, qreg, a.scale_log2, y);
-    if (p0 + kTile > W.N) mask_tail<true, WIDE>(T, y, jg, p0, W.N);
+    if (p0 + kTile > W.N) mask_tail<WIDE>(T, y, jg, p0, W.N);
     bf16x8 a_hi, a_lo;
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     pv_phase(T, a_hi, a_lo, acc);
@@ -1326,7 +1527,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
   l_run = rows_sum(l_run);
   {
     __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg<false, true, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+    finish_wg<false, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   }
   report_guard(a.guard, W.bad);  // last: the way to the record and the merge is the launch's critical path
 }
@@ -1488,7 +1689,7 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = f32x4{v, v, v, v};
     __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg<false, true, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+    finish_wg<false, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   } else {
     fold ^= __shfl_xor(fold, 32);
     if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * a.slot_cap + slot) * kPartStride) + w] = fold;
@@ -1722,7 +1923,7 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
     float y[8];
     qk_phase<WIDE>(T, qreg, a.scale_log2, y);
     issue_k_tile(t + step);
-    if (p0 + kTile > N) mask_tail<true, WIDE>(T, y, jg, p0, N);
+    if (p0 + kTile > N) mask_tail<WIDE>(T, y, jg, p0, N);
     bf16x8 a_hi, a_lo;
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     pv_phase(T, a_hi, a_lo, acc);
@@ -1731,7 +1932,7 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
   l_run = rows_sum(l_run);
   {
     __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg<false, true, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+    finish_wg<false, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   }
   report_guard(a.guard, bad);
 }
@@ -1877,34 +2078,24 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
   if (a.plan_batch > 0) {
     const dim3 pgrid(std::max(a.plan_wgs, a.plan_even * a.plan_batch), a.Hkv);
     const uint32_t strides = (uint32_t)a.ms | (uint32_t)a.fs << 16;
-#define SFI_PLANNED(EXPOSE, NOV)                                                                                             \
-  hipLaunchKernelGGL((attn_dense_planned_kernel<EXPOSE, PAGED, NOV>), pgrid, dim3(kAttnThreads), 0, s, a.ctx_len, a.is_slow, \
+#define SFI_PLANNED(EXPOSE)                                                                                             \
+  hipLaunchKernelGGL((attn_dense_planned_kernel<EXPOSE, PAGED>), pgrid, dim3(kAttnThreads), 0, s, a.ctx_len, a.is_slow, \
                      a.q_len, strides, a.plan_batch, a.plan_wgs, 1.0f / (float)a.plan_min, a.n_sink, a.recent, a.len_cap, a)
-    if (a.logits == nullptr) SFI_PLANNED(0, false);
-    else if (a.no_v && a.with_knorm) SFI_PLANNED(2, true);
-    else if (a.no_v) SFI_PLANNED(1, true);
-    else if (a.with_knorm) SFI_PLANNED(2, false);
-    else SFI_PLANNED(1, false);
+    if (a.logits == nullptr) SFI_PLANNED(0);
+    else if (a.with_knorm) SFI_PLANNED(2);
+    else SFI_PLANNED(1);
 #undef SFI_PLANNED
     return;
   }
   if constexpr (!PAGED) {
-    if (a.dense_wide && a.G <= 8 && !a.with_knorm && !a.no_v) {
-      if (a.logits != nullptr && a.big_stash) hipLaunchKernelGGL((attn_dense_kernel<1, false, true, false, true>), grid, dim3(kAttnThreads), 0, s, a);
-      else if (a.logits != nullptr) hipLaunchKernelGGL((attn_dense_kernel<1, false, false, false, true>), grid, dim3(kAttnThreads), 0, s, a);
-      else hipLaunchKernelGGL((attn_dense_kernel<0, false, false, false, true>), grid, dim3(kAttnThreads), 0, s, a);
+    if (a.dense_wide && a.G <= 8 && !a.with_knorm) {
+      if (a.logits != nullptr && a.big_stash) hipLaunchKernelGGL((attn_dense_kernel<1, false, true, true>), grid, dim3(kAttnThreads), 0, s, a);
+      else if (a.logits != nullptr) hipLaunchKernelGGL((attn_dense_kernel<1, false, false, true>), grid, dim3(kAttnThreads), 0, s, a);
+      else hipLaunchKernelGGL((attn_dense_kernel<0, false, false, true>), grid, dim3(kAttnThreads), 0, s, a);
       return;
     }
   }
-  if (a.logits != nullptr && a.no_v && a.with_knorm && a.big_stash)  // (no_v: evidence only)
-    hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, true, true>), grid, dim3(kAttnThreads), 0, s, a);
-  else if (a.logits != nullptr && a.no_v && a.with_knorm)
-    hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, false, true>), grid, dim3(kAttnThreads), 0, s, a);
-  else if (a.logits != nullptr && a.no_v && a.big_stash)
-    hipLaunchKernelGGL((attn_dense_kernel<1, PAGED, true, true>), grid, dim3(kAttnThreads), 0, s, a);
-  else if (a.logits != nullptr && a.no_v)
-    hipLaunchKernelGGL((attn_dense_kernel<1, PAGED, false, true>), grid, dim3(kAttnThreads), 0, s, a);
-  else if (a.logits != nullptr && a.with_knorm && a.big_stash)
+  if (a.logits != nullptr && a.with_knorm && a.big_stash)
     hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);
   else if (a.logits != nullptr && a.with_knorm)
     hipLaunchKernelGGL((attn_dense_kernel<2, PAGED>), grid, dim3(kAttnThreads), 0, s, a);

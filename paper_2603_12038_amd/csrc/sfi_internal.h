@@ -106,7 +106,7 @@ struct AttnArgs {
   int32_t plan_even;             //   ... workgroups per pair if all sequences turn out equally long (0: do not look)
   int32_t* slow_list;            //   ... where the plan is left for the Selector's launches (see SelArgs), or nullptr
   int32_t* seq_rec;              //   ... records per query head of each sequence, [batch]
-  const int32_t* q_len;          // dense mode, nullptr or: rows each sequence's query sees (window query under the causal mask)
+  const int32_t* q_len;          // dense and evidence mode, nullptr or: rows each sequence's query sees (window query under the causal mask)
   const int32_t* recent_start;   // gather mode
   const int32_t* sel_idx;        // gather mode
   const int32_t* n_sel;          // gather mode
@@ -117,7 +117,6 @@ struct AttnArgs {
                                  //   caller's workspace)
   float* logits;                 // dense mode, nullptr: do not expose logits
   int32_t with_knorm;            // dense mode: also expose the squared key norms (full Selector)
-  int32_t no_v;                  // dense mode with logits: evidence only -- V is not read, the records hold no output
   int32_t dense_wide;            // dense mode: K rows read as whole 128-byte lines (query groups of at most 8 heads, flat cache)
   int32_t big_stash;             // dense mode with logits: the variant with the 32 KB stash per wave (one workgroup per CU)
   float* out_direct;             // gather / compact mode with n_split == 1: write the output here, no record
@@ -223,6 +222,7 @@ struct SelArgs {
 };
 
 hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t s);
+hipError_t launch_attn_evidence(const AttnArgs& a, int B, int n_slots, hipStream_t s);  // a query of a window: logits and statistics of J
 hipError_t launch_attn_dense_floor(const AttnArgs& a, int B, int n_slots, int wide, int idle_units, int writer, hipStream_t s);
 hipError_t launch_attn_compact(const AttnArgs& a, int B, int n_slots, hipStream_t s);
 hipError_t launch_reorg(const ReorgArgs& a, int B, int rows, hipStream_t s);

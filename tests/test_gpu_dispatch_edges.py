@@ -101,7 +101,7 @@ def test_fast_step_merge(oracle, G, tiles_per_wave):
         r.close()
 
 
-# evidence alone (no output), split over two workgroups per compute unit where a wave's share fits the small stash
+# evidence alone (no output): several workgroups per compute unit, shares that fill the LDS stash more than once
 @pytest.mark.parametrize("B,Hkv,G,lens", [(2, 8, 4, [4200, 700]), (2, 8, 16, [9000, 8990]), (2, 8, 15, [4097, 33]), (1, 8, 4, [2000]),
                                           (9, 8, 5, [1500] * 8 + [70]), (1, 8, 1, [131])])
 @pytest.mark.parametrize("mode", [0, 1])
@@ -133,6 +133,41 @@ def test_evidence_of_a_window(oracle, B, Hkv, G, lens, mode, page):
         torch.cuda.synchronize()
         sel_ref, nsel_ref, z = oracle.selector(q_cat, w.K, ctx, w.budget, w.n_sink, w.recent, sp=sp, vis=vis)
         check_selection(sel.cpu().numpy(), nsel.cpu().numpy(), sel_ref, nsel_ref, z, ctx, w.n_sink, w.recent, w.budget)
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
+    finally:
+        r.close()
+
+
+# the evidence launch: a wave has two tiles of 32 rows in flight; |J| around one tile, one and two tiles of a workgroup's four
+# waves, and a sink that leaves no J (the last one is as large as an int: first rows are requested before the length is known)
+@pytest.mark.parametrize("n_j", [0, 1, 31, 32, 33, 127, 128, 129, 255, 256, 257, 511, 513, 1025, -1])
+@pytest.mark.parametrize("mode,G,page", [(0, 2, 0), (1, 4, 0), (1, 16, 0), (0, 16, 16), (1, 3, 16)])
+def test_evidence_at_the_edges_of_its_tiles(oracle, n_j, mode, G, page):
+    import torch
+    from helpers import i32_dev, to_dev
+    print(f"[gpu-edges] evidence: |J| = {n_j}, G = {G} mode={mode} page={page}", flush=True)
+    w = _workload(2, 2, G, [n_j + N_SINK + RECENT, max(n_j - 40, 3) + N_SINK + RECENT], 65, seed=800 + n_j)
+    if n_j < 0:
+        w.n_sink = 2 ** 31 - 1
+    sp = dataclasses.replace(SelectorParams(mode=mode), alpha=0.5)
+    d = {k: getattr(sp, k) for k in ("gamma", "beta", "p", "eta", "lambda_clip", "alpha_soft", "alpha_cross", "temp", "eps",
+                                      "nms_radius")} if mode else None
+    r = Runner(w, selector=d, alpha=0.5, page_size=page)
+    try:
+        c = w.ctx_len(0)
+        sel = torch.full((2, 2, w.budget), -7, dtype=torch.int32, device="cuda")
+        nsel = torch.full((2, 2), -7, dtype=torch.int32, device="cuda")
+        qs = [w.q(t) for t in range(2)]
+        for t, q in enumerate(qs):
+            r.sfi.sfi_evidence_add(r.ctx.handle, to_dev(q), r.K, None, i32_dev(c), int(c.max()), None, t == 0)
+        r.sfi.sfi_evidence_select(r.ctx.handle, 2, i32_dev(c), int(c.max()), w.budget, sel, nsel)
+        torch.cuda.synchronize()
+        if n_j < 0:
+            assert (nsel == 0).all() and (sel == -1).all()
+        else:
+            q_all = np.stack([q.reshape(2, 2, G, w.d) for q in qs], axis=2).reshape(2, 4 * G, w.d)
+            sel_ref, nsel_ref, z = oracle.selector(q_all, w.K, c, w.budget, w.n_sink, w.recent, sp=sp)
+            check_selection(sel.cpu().numpy(), nsel.cpu().numpy(), sel_ref, nsel_ref, z, c, w.n_sink, w.recent, w.budget)
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()

@@ -132,7 +132,7 @@ def test_long_form_threshold_below_the_histograms_range(oracle, budget):
         r.close()
 
 
-# 8 sequences of 8 KV heads and 8200 rows at most: 16576 tiles, from 16384 on the evidence-only launch is planned on the device
+# 8 sequences of 8 KV heads and 8200 rows at most: 16 workgroups per pair, eight tiles a wave
 @pytest.mark.parametrize("lens", [[8200, 6000, 7777, 5001, 8199, 4100, 7001, 8000], [8200] * 8], ids=["unequal", "equal"])
 @pytest.mark.parametrize("page", [0, 16])
 @pytest.mark.parametrize("mode", [0, 1])
