@@ -417,6 +417,13 @@ int sfi_set_dense_k_layout(sfi_ctx* ctx, int32_t whole_lines);
  * exit at once.  Same results.  Other values: SFI_EINVAL. */
 int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);
 
+/* A/B knob of the split fast-step launches (sfi_fast_step, sfi_fast_step_compact and the ragged steps), whose workgroups hand
+ * partial results to one another.  mode = 1 (default): where the launch can deal all workgroups of a (sequence, KV head)
+ * pair to one XCD, through that XCD's L2; a pair whose workgroups turn out to sit on different XCDs is computed again by
+ * the last of them.  mode = 0: at device scope.  mode = 2: as 1, but every split pair is taken for one on different XCDs (for
+ * tests).  Same results up to the order of the sums.  Other values: SFI_EINVAL. */
+int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
+
 /* Launch geometry the library would choose, without launching anything (host arithmetic only): split
  * workgroups per (sequence, KV head) of a dense launch bounded by max_len rows (0 = cfg.max_ctx) and
  * of a fast step whose index lists are sel_stride wide.  Either output may be NULL.  SFI_EINVAL for a

@@ -22,6 +22,7 @@ struct sfi_ctx {
   int tail_merge;           // split fast-step launches merge in the attention kernel (no merge launch)
   int dense_wide;           // dense kernel reads K rows as whole 128-byte lines (A/B knob, sfi_set_dense_k_layout)
   int mixed_plan;           // the ragged step's dense launch plans itself on the device (default; A/B knob, sfi_set_mixed_plan)
+  int handover;             // fast-step records: 0 device scope, 1 XCD-local where the launch allows it (default), 2 (sfi_set_handover)
   int last_dense_splits, last_fast_splits;
   int last_dense_planned;   // the last dense launch planned itself: its records per sequence are in ws.seq_rec
   // profiling: a ring of event pairs, one set of stages per hot call, read back in one go so that
@@ -299,6 +300,18 @@ int compact_splits_for(const sfi_ctx* x, int sel_stride) {
   return s;
 }
 
+// How the workgroups of a split fast-step launch hand their records over: through the L2 of one XCD where the pairs spread
+// evenly over the eight XCDs, and for a launch of a few workgroups.  (All of a pair's rows then come through one XCD: with fewer
+// pairs than XCDs and many workgroups the others would stand idle.  Other numbers of KV heads need a division in front of
+// the first request.)  Device scope / XCD-local, us a layer: 1 x 4096 rows, 2 KV heads, 3 workgroups per pair 5.6 / 5.4; 1 x 8192, 4 KV heads, 4 per pair 6.1 / 5.8; figures
+// for even launches: finish_wg.
+int handover_for(const sfi_ctx* x, int n_split) {
+  const int Hkv = x->cfg.n_kv_heads, pairs = x->cfg.batch * Hkv;
+  if (x->handover == 0 || n_split < 2) return 0;
+  const bool even = Hkv % 8 == 0 || ((Hkv == 4 || Hkv == 2 || Hkv == 1) && (pairs % 8 == 0 || (pairs < 8 && n_split <= 4)));
+  return even ? x->handover : 0;
+}
+
 struct StageTimer {
   sfi_ctx* x;
   hipStream_t s;
@@ -477,6 +490,7 @@ int sfi_create(const sfi_config* cfg, void* workspace, size_t workspace_bytes, s
   x->fast_tiles_per_wave = 0;
   x->tail_merge = 1;
   x->mixed_plan = 1;
+  x->handover = 1;
   // The arrival counters of split launches start at zero (and every launch leaves them there).
   // A workspace the runtime knows (device, managed, pinned) is cleared here and a failure to do so is an error: with stale
   // counters no workgroup would ever take itself for the last one.  (Without a device, or with a
@@ -744,7 +758,7 @@ int fast_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const 
   a.n_split = fast_splits_for(x, sel_stride, max_splits);
   x->last_fast_splits = a.n_split;
   if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
-  else if (x->tail_merge) { a.out_merge = out; a.arrive = arrive; }
+  else if (x->tail_merge) { a.out_merge = out; a.arrive = arrive; a.handover = handover_for(x, a.n_split); }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_gather(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
   MergeArgs m{part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};
@@ -801,7 +815,7 @@ int sfi_fast_step_floor(sfi_ctx* x, const void* q, const void* K, const void* V,
   }
   x->last_fast_splits = a.n_split;
   if (tail && a.n_split == 1) a.out_direct = (float*)out;
-  else if (tail) { a.out_merge = (float*)out; a.arrive = x->ws.arrive; }
+  else if (tail) { a.out_merge = (float*)out; a.arrive = x->ws.arrive; a.handover = handover_for(x, a.n_split); }
   SFI_TRY(launch_attn_gather_floor(a, x->cfg.batch, a.n_split, tail, burst, tpw, depth, (hipStream_t)stream));
   return SFI_OK;
 }
@@ -868,6 +882,7 @@ int sfi_fast_step_static(const sfi_config* cfg, const void* q, const void* K, co
   x.alpha = cfg->alpha > 0.f ? cfg->alpha : 1.0f;
   x.n_cu = S.n_cu;
   x.tail_merge = 1;
+  x.handover = 1;
   if ((rc = check_fast(&x, q, K, V, sel_idx, n_sel, sel_stride, recent_start, ctx_len, out)) != SFI_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   float* part = reinterpret_cast<float*>(S.ptr);
@@ -957,7 +972,7 @@ int sfi_fast_step_compact(sfi_ctx* x, const void* q, const void* Kc, const void*
   a.n_split = compact_splits_for(x, sel_stride);
   x->last_fast_splits = a.n_split;
   if (a.n_split == 1) a.out_direct = out;
-  else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; }
+  else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; a.handover = handover_for(x, a.n_split); }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_compact(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
   MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};
@@ -1017,7 +1032,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
     f.n_split = fast_splits_for(x, budget);
   }
   if (f.n_split == 1) f.out_direct = out;
-  else if (x->tail_merge) { f.out_merge = out; f.arrive = x->ws.arrive; }  // slow sequences' workgroups never arrive
+  else if (x->tail_merge) { f.out_merge = out; f.arrive = x->ws.arrive; f.handover = handover_for(x, f.n_split); }  // slow sequences' workgroups never arrive
   x->last_fast_splits = f.n_split;
   // Fast sequences finish inside their launch unless their split records need the merge launch;
   // slow sequences are merged by the first scoring launch (as in sfi_slow_step).  The merge kernel only
@@ -1176,6 +1191,12 @@ int sfi_set_tuning(sfi_ctx* x, int32_t dense_target_wgs, int32_t fast_tiles_per_
 int sfi_set_mixed_plan(sfi_ctx* x, int32_t on) {
   if (x == nullptr || on < 0 || on > 1) return SFI_EINVAL;
   x->mixed_plan = on;
+  return SFI_OK;
+}
+
+int sfi_set_handover(sfi_ctx* x, int32_t mode) {
+  if (x == nullptr || mode < 0 || mode > 2) return SFI_EINVAL;
+  x->handover = mode;
   return SFI_OK;
 }
 

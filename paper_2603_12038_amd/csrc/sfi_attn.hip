@@ -462,40 +462,62 @@ __device__ __forceinline__ void pv_phase(const Tile& T, const bf16x8& a_hi, cons
   }
 }
 
-// Device-scope accesses: visible to / from every compute unit of the device whatever L2 it sits behind,
-// without a fence (records that one workgroup hands to another inside a launch).  They go through a buffer
-// descriptor, 16 bytes at a time: the records of one (b, h) pair as a raw buffer
-// (byte offsets, out-of-range accesses dropped by the hardware), every access with the device-scope cache policy.
+// Accesses that one workgroup's records are handed to another with inside a launch, without a fence.  LOCAL false: device
+// scope, visible to / from every compute unit whatever L2 it sits behind.  LOCAL true: they go to the L2 of this XCD and no
+// further, visible to / from the compute units of the same XCD (the first-level caches are written through, and a load
+// with sc0 does not hit in them).  They go through a buffer descriptor, 16 bytes at a time: the records of one (b, h) pair
+// as a raw buffer (byte offsets, out-of-range accesses dropped by the hardware).
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-constexpr int kScopeDevice = 16;  // cache-policy bit sc1 of the buffer instructions
+template <bool LOCAL>
+constexpr int scope_bits() { return LOCAL ? 1 : 16; }  // cache-policy bits sc0, sc1 of the buffer instructions
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t pair_records(float* base, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
 }
-__device__ __forceinline__ void store_device4(__amdgpu_buffer_rsrc_t r, int byte_off, float4 v) {
+template <bool LOCAL>
+__device__ __forceinline__ void store_record4(__amdgpu_buffer_rsrc_t r, int byte_off, float4 v) {
   __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)},
-                                         r, byte_off, 0, kScopeDevice);
+                                         r, byte_off, 0, scope_bits<LOCAL>());
 }
-__device__ __forceinline__ void store_device2(__amdgpu_buffer_rsrc_t r, int byte_off, float v0, float v1) {
-  __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{__float_as_uint(v0), __float_as_uint(v1)}, r, byte_off, 0, kScopeDevice);
+template <bool LOCAL>
+__device__ __forceinline__ void store_record2(__amdgpu_buffer_rsrc_t r, int byte_off, float v0, float v1) {
+  __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{__float_as_uint(v0), __float_as_uint(v1)}, r, byte_off, 0, scope_bits<LOCAL>());
 }
-__device__ __forceinline__ float4 load_device4(__amdgpu_buffer_rsrc_t r, int byte_off) {
-  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, kScopeDevice);
+template <bool LOCAL>
+__device__ __forceinline__ float4 load_record4(__amdgpu_buffer_rsrc_t r, int byte_off) {
+  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, scope_bits<LOCAL>());
   return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
-__device__ __forceinline__ float2 load_device2(__amdgpu_buffer_rsrc_t r, int byte_off) {
-  const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, kScopeDevice);
+template <bool LOCAL>
+__device__ __forceinline__ float2 load_record2(__amdgpu_buffer_rsrc_t r, int byte_off) {
+  const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, scope_bits<LOCAL>());
   return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+}
+
+// Which cell a workgroup of a fast-step launch takes.  LOCAL: the grid is laid out so that all workgroups of a pair have the
+// same linear index modulo 8, and consecutive indices go round the eight XCDs: blockIdx = (pair in the row, slot, row) with
+// max(8, Hkv) pairs in a row.  shape: Hkv | log2 of the metadata stride << 16 | is_slow given << 20 |
+// log2 of the sequences in a row << 21 | log2 of Hkv, or 31 where a row is one sequence << 23 | pairs in a row that is not full, or 0 << 28.
+struct FastCell {
+  int slot, h, b;
+  bool off;  // no pair behind this workgroup
+};
+template <bool LOCAL>
+__device__ __forceinline__ FastCell fast_cell(uint32_t shape) {
+  if (!LOCAL) return FastCell{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, false};
+  const uint32_t x = blockIdx.x, lg = (shape >> 23) & 31u, np = shape >> 28, q = x >> lg;
+  return FastCell{(int)blockIdx.y, (int)(x - (q << lg)), (int)((blockIdx.z << ((shape >> 21) & 3u)) + q), np != 0u && x >= np};
 }
 
 // Where an attention workgroup's result goes.
 struct WgOut {
   float* out_direct;   // the workgroup is the only one of its (b, h) pair: it writes O / l straight to out[b, head, :]
-  float* out_merge;    // or: records go out in device-scope stores and the last waves to finish merge them into this;
+  float* out_merge;    // or: records go out in stores that the pair's other workgroups can see and the last waves to finish merge them into this;
   uint32_t* arrive;    //   arrive[w * kArriveStride] counts the pair's workgroups whose wave w has sent its heads' records
   float* part;         // the records (with neither pointer above: a merge launch follows)
   int n_split, slot_cap;
   bool out_bf16;
+  bool apart;          // LOCAL, tests: take the workgroups for ones on different XCDs
 };
 __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
   WgOut o;
@@ -506,6 +528,7 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
   o.n_split = a.n_split;
   o.slot_cap = a.slot_cap;
   o.out_bf16 = a.out_bf16 != 0;
+  o.apart = a.handover == 2;
   return o;
 }
 // The way out of an attention workgroup: the four waves' partial results are combined through LDS and sent where WgOut
@@ -514,7 +537,7 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
 // This is the launch's critical path (a third of a short fast step), so it is one barrier long.  Every wave leaves its
 // raw partial result in LDS; behind the barrier wave w finishes the heads w, w + 4, ... by itself: it combines the four
 // waves' parts (lanes 0..31 one head, 32..63 the head four further on, four output dims per lane), stores the
-// workgroup's record of those heads in device-scope stores, waits for their acknowledgement and counts itself in on the
+// workgroup's record of those heads, waits for their acknowledgement and counts itself in on the
 // pair's counter for wave w.  The wave that finds all n_split - 1 others counted merges the records of its heads (even
 // records in lanes 0..31, odd ones in lanes 32..63, sixteen records in flight) and puts its counter back to zero.
 // The heads of a pair are thus merged by up to four waves, usually on as many compute units, each behind its own
@@ -524,13 +547,21 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
 // workgroup merging): 131072 rows, 8 KV heads, budget 4096: 10.9 -> 9.6 us; 4 x 32768 rows, budget 2048: 11.6 -> 11.1 us;
 // 4096 rows, 2 KV heads, budget 256: 6.8 -> 6.4 us.
 // red: G x 128 floats of LDS per wave, wave_stride floats apart.
+// LOCAL (fast_cell): the pair's workgroups are dealt to one XCD, and the records stay in its L2: the acknowledgement and the
+// record loads take a trip to the L2 instead of one to memory.  That the workgroups did meet on one XCD is not assumed:
+// the counter, which stays at device scope, adds up their XCDs x and x^2 beside their number n, and n sum x^2 = (sum x)^2
+// holds only if all x are the same.  If it does not, the records cannot be read; the function returns true, and the wave does
+// the pair's whole list again for its heads.  Device scope / LOCAL, us a layer: 4096 rows, 2 KV heads 5.54 / 5.25; 4 x 32768 rows, 8 KV
+// heads, budget 2048 10.55 / 10.28; 131072 rows, 8 KV heads, budget 4096 9.03 / 8.63; 8 sequences of 20011..24571 rows, G = 5, paged, budget 1024
+// 12.29 / 11.85; 12 x 32768 rows, budget 1000 14.55 / 13.68; 8 x 32768 rows, one KV head, budget 2000 9.03 / 8.34.  (With the counter in the L2 as
+// well another 1 %, but then workgroups on different XCDs would not find one another.)
 // JSTAT (dense kernel with exposed logits): the record's header also carries the statistics over the allowed set J alone,
 // { m, l, m_J, l_J } (the fast step and the dense kernel without logits leave the last two words).
 // AT_ONCE: heads a wave merges at a time.  Two where a group has more than eight heads (the kernels with the plain K layout),
 // so that up to four heads take two chains of trips, not four: 16 heads, 33 records, fast step 13.5 -> 12.8 us.  One for
 // smaller groups, whose waves have one or two: the second head's code costs them 0.1 us.
-template <bool JSTAT = false, int AT_ONCE = 1>
-__device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, int slot, const f32x4 (&acc)[8], float m_run,
+template <bool JSTAT = false, int AT_ONCE = 1, bool LOCAL = false>
+__device__ __forceinline__ bool finish_wg(const WgOut& o, int64_t head0, int G, int slot, const f32x4 (&acc)[8], float m_run,
                                           float l_run, float* red, int wave_stride, float m_j = 0.f, float l_j = 0.f) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
@@ -556,7 +587,7 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
     }
   }
   __syncthreads();
-  if (w >= G) return;
+  if (w >= G) return false;
   const int half = lane >> 5, c = lane & 31;
   constexpr int kRec = kPartStride * (int)sizeof(float);
   // slot_cap: records each query head has room for (kSlotCap in a caller's workspace, fewer in the static scratch)
@@ -584,8 +615,8 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
     } else if (mine) {
       const int off = (hh * o.slot_cap + slot) * kRec;  // from the pair's first record
       if (!JSTAT && o.out_merge != nullptr) {
-        store_device4(R, off + 16 + 16 * c, t);
-        if (c == 0) store_device2(R, off, M, ls);
+        store_record4<LOCAL>(R, off + 16 + 16 * c, t);
+        if (c == 0) store_record2<LOCAL>(R, off, M, ls);
       } else {
         float* dst = pair_base + (hh * o.slot_cap + slot) * kPartStride;
         *reinterpret_cast<float4*>(dst + 4 + 4 * c) = t;
@@ -600,12 +631,19 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
       }
     }
   }
-  if (JSTAT || o.out_merge == nullptr) return;
+  if (JSTAT || o.out_merge == nullptr) return false;
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's record stores have been performed
+  const uint32_t xcd = !LOCAL ? 0u : o.apart ? (uint32_t)slot & 1u : __builtin_amdgcn_s_getreg(20 | 3 << 11);  // HW_REG_XCC_ID, 4 bits
+  const uint32_t mine = 1u | xcd << 7 | (xcd * xcd) << 17;  // (at most 63 workgroups, XCDs 0 .. 15: no field overflows)
   uint32_t before = 0;
-  if (lane == 0) before = __hip_atomic_fetch_add(o.arrive + w * kArriveStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) != (uint32_t)(o.n_split - 1)) return;
+  if (lane == 0) before = __hip_atomic_fetch_add(o.arrive + w * kArriveStride, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)before) + mine;
+  if ((total & 127u) != (uint32_t)o.n_split) return false;
   if (lane == 0) __hip_atomic_store(o.arrive + w * kArriveStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (LOCAL) {
+    const uint32_t sum = (total >> 7) & 1023u, squares = total >> 17;
+    if (__builtin_expect((uint32_t)o.n_split * squares != sum * sum, 0)) return true;
+  }
   const int n_rec = o.n_split;
   for (int hh = w; hh < G; hh += AT_ONCE * kWaves) {
     const bool two = AT_ONCE > 1 && hh + kWaves < G;  // wave-uniform
@@ -628,8 +666,8 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
         for (int i = 0; i < 8; ++i) {
           const int rec = P[k] + min(s0 + 2 * i, n_rec - 1) * kRec;
           if ((k == 0 || two) && (i == 0 || s0 - half + 2 * i < n_rec)) {  // wave-uniform
-            ml[k][i] = load_device2(R, rec);
-            r4[k][i] = load_device4(R, rec + 16 + 16 * c);
+            ml[k][i] = load_record2<LOCAL>(R, rec);
+            r4[k][i] = load_record4<LOCAL>(R, rec + 16 + 16 * c);
           } else {
             ml[k][i] = make_float2(kNeg, 0.f);
             r4[k][i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -670,6 +708,28 @@ __device__ __forceinline__ void finish_wg(const WgOut& o, int64_t head0, int G, 
       if (half == 0)
         store_out4(o.out_merge, (head0 + hh + k * kWaves) * kHeadDim + 4 * c, make_float4(ts.x * inv, ts.y * inv, ts.z * inv, ts.w * inv), o.out_bf16);
     }
+  }
+  return false;
+}
+// LOCAL, records that cannot be read: the wave has the whole list's sums and writes its heads w, w + 4, ... itself.
+__device__ __forceinline__ void store_heads(const WgOut& o, int64_t head0, int G, const f32x4 (&acc)[8], float l_run) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int jg = lane >> 4, n = lane & 15;
+  const float l_n = rows_sum(l_run);  // of head n
+  const float l4[4] = {row_quad<0>(l_n), row_quad<1>(l_n), row_quad<2>(l_n), row_quad<3>(l_n)};
+  float l = 0.f, v[8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (i != w) continue;
+    l = l4[i];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = acc[e][i];
+  }
+  const float inv = l > 0.f ? 1.0f / l : 0.f;
+  if (4 * jg + w < G) {
+    const int64_t at = (head0 + 4 * jg + w) * kHeadDim + 8 * n;
+    store_out4(o.out_merge, at, make_float4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv), o.out_bf16);
+    store_out4(o.out_merge, at + 4, make_float4(v[4] * inv, v[5] * inv, v[6] * inv, v[7] * inv), o.out_bf16);
   }
 }
 
@@ -1388,13 +1448,15 @@ hipError_t launch_attn_evidence(const AttnArgs& a, int B, int n_slots, hipStream
 // against arguments read where they are used and q masked where it is loaded: 131072 rows / 8 KV heads 9.6 -> 9.0 us,
 // 4 x 32768 rows 11.1 -> 10.6 us, 4096 rows / 2 KV heads 6.4 -> 5.6 us.
 // ------------------------------------------------------------------------------------------------
-// The preloaded arguments: shape = Hkv | (log2 of the metadata stride) << 16 | (is_slow given) << 20.
-template <bool PAGED, bool WIDE>
+// The preloaded arguments: shape, see fast_cell.
+template <bool PAGED, bool WIDE, bool LOCAL>
 __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int32_t* sel_idx, const int32_t* n_sel_p, const int32_t* ctx_len_p,
                                                                       const int32_t* recent_start_p, const uint8_t* is_slow_p,
                                                                       const uint32_t sel_stride, const uint32_t shape, const int n_sink,
                                                                       const int n_split, const AttnArgs a) {
-  const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const FastCell cell = fast_cell<LOCAL>(shape);
+  if (cell.off) return;
+  const int slot = cell.slot, h = cell.h, b = cell.b;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
   const int bh = b * (int)(shape & 0xffffu) + h;
@@ -1524,10 +1586,29 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     pv_phase(T, a_hi, a_lo, acc);
   }
-  l_run = rows_sum(l_run);
-  {
-    __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg<false, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+  __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
+  const WgOut o = wg_out_of(a, bh);
+  if (finish_wg<false, WIDE ? 1 : 2, LOCAL>(o, head0, G, slot, acc, m_run, rows_sum(l_run), &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim)) {
+    m_run = kNeg;
+    l_run = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int p = 0; p < W.N; p += kTile) {
+      int ra = W.row_of(p + n, W.sel_at_nonempty(p + n)), rb = W.row_of(p + 16 + n, W.sel_at_nonempty(p + 16 + n));
+      if (PAGED) {
+        ra = P.phys(ra, P.page_of(ra), W.bad);
+        rb = P.phys(rb, P.page_of(rb), W.bad);
+      }
+      issue_rows<typename RowOff<PAGED>::type, WIDE>(T, R, ra, rb);
+      float y[8];
+      qk_phase<WIDE>(T, qreg, a.scale_log2, y);
+      if (p + kTile > W.N) mask_tail<WIDE>(T, y, jg, p, W.N);
+      bf16x8 a_hi, a_lo;
+      softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
+      pv_phase(T, a_hi, a_lo, acc);
+    }
+    store_heads(o, head0, G, acc, l_run);
   }
   report_guard(a.guard, W.bad);  // last: the way to the record and the merge is the launch's critical path
 }
@@ -1551,7 +1632,7 @@ __device__ __forceinline__ uint32_t fold16(const uint4& v) { return v.x ^ v.y ^ 
 //   depth  1: stop after the scalars and indices; 2: load nothing at all (the cost of the bare launch).
 // The leading arguments are the gather kernel's: they arrive in registers, and the scalars and the first indices are
 // requested from them before the arguments that come from memory are asked for.
-template <bool WIDE, bool TAIL, bool BURST>
+template <bool WIDE, int TAIL, bool BURST>  // TAIL 2: as LOCAL
 __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor_kernel(const int32_t* sel_idx, const int32_t* n_sel_p,
                                                                                         const int32_t* ctx_len_p, const int32_t* recent_start_p,
                                                                                         const uint8_t*, const uint32_t sel_stride,
@@ -1559,14 +1640,16 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
                                                                                         const int n_split, const AttnArgs a, int tpw,
                                                                                         int depth) {
   extern __shared__ uint4 s_rows[];  // BURST: [tpw][16 instructions][64 lanes]
-  const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const FastCell cell = fast_cell<TAIL == 2>(shape);
+  if (cell.off) return;
+  const int slot = cell.slot, h = cell.h, b = cell.b;
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int jg = lane >> 4, n = lane & 15;
   const int bh = b * (int)(shape & 0xffffu) + h;
   const int bm = b << ((shape >> 16) & 15u);
   uint32_t fold = 0u;
-  if (!TAIL && !BURST && depth == 2) {  // wave-uniform: the bare launch
+  if (TAIL == 0 && !BURST && depth == 2) {  // wave-uniform: the bare launch
     const int64_t head0 = (int64_t)b * a.Hq + h * a.G;
     if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * a.slot_cap + slot) * kPartStride) + w] = (uint32_t)slot;
     return;
@@ -1593,7 +1676,7 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
   R.v_lane = n * 16;
   R.jg = jg;
   R.n = n;
-  if (!TAIL && !BURST && depth == 1) {  // wave-uniform: scalars and the first tile's indices, nothing else
+  if (TAIL == 0 && !BURST && depth == 1) {  // wave-uniform: scalars and the first tile's indices, nothing else
     fold = (uint32_t)(L_in ^ n_sel_in ^ rs_in ^ sA0 ^ sB0);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) fold ^= __shfl_xor(fold, d);
@@ -1683,13 +1766,13 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
       for (int i = 0; i < 8; ++i) fold ^= fold16(T.v[i]);
     }
   }
-  if (TAIL) {
+  if (TAIL != 0) {
     f32x4 acc[8];
     const float v = (float)(fold & 0xffu);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = f32x4{v, v, v, v};
     __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg<false, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+    finish_wg<false, WIDE ? 1 : 2, TAIL == 2>(wg_out_of(a, bh), head0, G, slot, acc, 0.f, 1.f, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
   } else {
     fold ^= __shfl_xor(fold, 32);
     if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * a.slot_cap + slot) * kPartStride) + w] = fold;
@@ -1697,15 +1780,24 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
   report_guard(a.guard, W.bad);
 }
 
-// The leading arguments of the gather kernel and its skeleton (gather_shape: see attn_gather_kernel).
-static uint32_t gather_shape(const AttnArgs& a) {
-  return (uint32_t)a.Hkv | (a.ms == 4 ? 2u << 16 : 0u) | (a.is_slow != nullptr ? 1u << 20 : 0u);
+// The leading arguments of the gather kernel, its skeleton and the compact kernel, and their grid (fast_cell).
+static uint32_t fast_shape(const AttnArgs& a, int B) {
+  const uint32_t meta = (uint32_t)a.Hkv | (a.ms == 4 ? 2u << 16 : 0u) | (a.is_slow != nullptr ? 1u << 20 : 0u);
+  if (a.handover == 0) return meta;
+  if (a.Hkv >= 8) return meta | 31u << 23;
+  const uint32_t lg = a.Hkv == 4 ? 2u : a.Hkv == 2 ? 1u : 0u;
+  return meta | (3u - lg) << 21 | lg << 23 | (B * a.Hkv < 8 ? (uint32_t)(B * a.Hkv) << 28 : 0u);
+}
+static dim3 fast_grid(const AttnArgs& a, int B, int n_slots) {
+  if (a.handover == 0) return dim3(n_slots, a.Hkv, B);
+  const int row = a.Hkv >= 8 ? a.Hkv : 8;
+  return dim3(row, n_slots, (B * a.Hkv + row - 1) / row);
 }
 static const uint8_t* gather_flags(const AttnArgs& a) {  // (a readable byte in any case)
   return a.is_slow != nullptr ? a.is_slow : reinterpret_cast<const uint8_t*>(a.ctx_len);
 }
 hipError_t launch_attn_gather_floor(const AttnArgs& a, int B, int n_slots, int tail, int burst, int tpw, int depth, hipStream_t s) {
-  const dim3 grid(n_slots, a.Hkv, B);
+  const dim3 grid = fast_grid(a, B, n_slots);
   const size_t lds = burst ? (size_t)tpw * 16 * 64 * sizeof(uint4) : 0;
 #define SFI_FLOOR(WIDE, TAIL, BURST)                                                                                   \
   do {                                                                                                                 \
@@ -1713,18 +1805,19 @@ hipError_t launch_attn_gather_floor(const AttnArgs& a, int B, int n_slots, int t
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)            \
       return hipGetLastError();                                                                                        \
     hipLaunchKernelGGL((attn_gather_floor_kernel<WIDE, TAIL, BURST>), grid, dim3(kAttnThreads), lds, s, a.sel_idx, a.n_sel,   \
-                       a.ctx_len, a.recent_start, gather_flags(a), (uint32_t)a.sel_stride, gather_shape(a), a.n_sink,          \
+                       a.ctx_len, a.recent_start, gather_flags(a), (uint32_t)a.sel_stride, fast_shape(a, B), a.n_sink,        \
                        a.n_split, a, tpw, depth);                                                                              \
   } while (0)
   const bool wide = a.G <= 8;
-  if (wide && tail && burst) SFI_FLOOR(true, true, true);
-  else if (wide && tail) SFI_FLOOR(true, true, false);
-  else if (wide && burst) SFI_FLOOR(true, false, true);
-  else if (wide) SFI_FLOOR(true, false, false);
-  else if (tail && burst) SFI_FLOOR(false, true, true);
-  else if (tail) SFI_FLOOR(false, true, false);
-  else if (burst) SFI_FLOOR(false, false, true);
-  else SFI_FLOOR(false, false, false);
+  if (tail) {  // (never with a burst)
+    if (wide && a.handover != 0) SFI_FLOOR(true, 2, false);
+    else if (wide) SFI_FLOOR(true, 1, false);
+    else if (a.handover != 0) SFI_FLOOR(false, 2, false);
+    else SFI_FLOOR(false, 1, false);
+  } else if (wide && burst) SFI_FLOOR(true, 0, true);
+  else if (wide) SFI_FLOOR(true, 0, false);
+  else if (burst) SFI_FLOOR(false, 0, true);
+  else SFI_FLOOR(false, 0, false);
 #undef SFI_FLOOR
   return hipGetLastError();
 }
@@ -1837,39 +1930,48 @@ hipError_t launch_attn_dense_floor(const AttnArgs& a, int B, int n_slots, int wi
 // index is read: a wave's first tile is on its way before any scalar of the step has arrived.
 // Tiles never straddle the two segments: the compact segment ends with a ragged tile of its own.
 // ------------------------------------------------------------------------------------------------
-template <bool PAGED, bool WIDE>  // PAGED: the recent window is read from a paged cache (the compact buffers are always flat)
-__global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kernel(const AttnArgs a) {
-  const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (a.is_slow != nullptr && a.is_slow[b * a.fs] != 0) return;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
+// What the first tile's rows need arrives in registers, and the flag of a ragged step is looked at behind their requests.
+template <bool PAGED, bool WIDE, bool LOCAL>  // PAGED: the recent window is read from a paged cache (the compact buffers are always flat)
+__global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kernel(const uint16_t* Kc, const uint16_t* Vc, const uint8_t* is_slow_p,
+                                                                                   const int64_t c_sb, const int64_t c_sh, const uint32_t shape,
+                                                                                   const int c_rows, const int n_split, const AttnArgs a) {
+  const FastCell cell = fast_cell<LOCAL>(shape);
+  if (cell.off) return;
+  const int slot = cell.slot, h = cell.h, b = cell.b;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
-  const int G = a.G;
-  const int bh = b * a.Hkv + h;
-  const int64_t head0 = (int64_t)b * a.Hq + h * G;
-  const int first = slot * kWaves + w, step = a.n_split * kWaves;
+  const bool flagged = ((shape >> 20) & 1u) != 0u;
+  const int first = slot * kWaves + w, step = n_split * kWaves;
 
   Rows Rc;  // compact segment
-  Rc.Kb = reinterpret_cast<const char*>(a.Kc + b * a.c_sb + h * a.c_sh);
-  Rc.Vb = reinterpret_cast<const char*>(a.Vc + b * a.c_sb + h * a.c_sh);
+  Rc.Kb = reinterpret_cast<const char*>(Kc + b * c_sb + h * c_sh);
+  Rc.Vb = reinterpret_cast<const char*>(Vc + b * c_sb + h * c_sh);
   Rc.k_st = Rc.v_st = kHeadDim * 2u;
   Rc.k_lane = k_lane_of<WIDE>(jg, n);
   Rc.v_lane = n * 16;
   Rc.jg = jg;
   Rc.n = n;
+  Tile T;
+  const bool spec = first * kTile < c_rows;  // almost every wave's tile lies in the compact segment
+  if (spec) issue_affine<WIDE>(T, Rc, first * kTile, c_rows - 1);
+  const int slow = is_slow_p[flagged ? (uint32_t)b << (2u * ((shape >> 16) & 15u)) : 0u];  // (a readable byte in any case)
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(a.q), "s"(a.K), "s"(a.V), "s"(a.k_sb), "s"(a.k_sh), "s"(a.k_st), "s"(a.v_sb), "s"(a.v_sh), "s"(a.v_st), "s"(a.ctx_len),
+               "s"(a.n_sel), "s"(a.recent_start), "s"(a.ms), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.n_sink), "s"(a.len_cap), "s"(a.sel_stride));
+  const int G = a.G;
+  const int bh = b * a.Hkv + h;
+  const int64_t head0 = (int64_t)b * a.Hq + h * G;
   Rows R = Rc;  // recent segment, in the cache
   R.Kb = reinterpret_cast<const char*>(a.K + b * a.k_sb + h * a.k_sh);
   R.Vb = reinterpret_cast<const char*>(a.V + b * a.v_sb + h * a.v_sh);
   R.k_st = (uint32_t)a.k_st * 2u;
   R.v_st = (uint32_t)a.v_st * 2u;
 
-  Tile T;
-  const bool spec = first * kTile < a.c_rows;  // almost every wave's tile lies in the compact segment
-  if (spec) issue_affine<WIDE>(T, Rc, first * kTile, a.c_rows - 1);
   bf16x8 qreg[4];
   load_q<WIDE>(qreg, a.q, head0, G, jg, n);
   int bad = 0;
   const int L_in = a.ctx_len[b * a.ms], nSel0 = a.n_sel[bh], rs_in = a.recent_start[b * a.ms];  // one round trip for the three
+  if (flagged && __builtin_amdgcn_readfirstlane(slow) != 0) return;
   const int L = guarded_len(L_in, a.len_cap, bad);
   const int nSel = min(max(nSel0, 0), (int)a.sel_stride);
   bad |= nSel != nSel0 ? kGuardNSel : 0;
@@ -1894,7 +1996,7 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
   int pra_n = 0, prb_n = 0;  // PAGED: physical rows of the recent tile whose K half was issued last
   auto issue_k_tile = [&](int t) {
     if (t < Tc) {
-      issue_k_affine<WIDE>(T, Rc, t * kTile, a.c_rows - 1);
+      issue_k_affine<WIDE>(T, Rc, t * kTile, c_rows - 1);
     } else if (PAGED) {
       const Pages P = pages_of(a, b, L);
       const int ra = min(rs + (t - Tc) * kTile + n, L - 1), rb = min(rs + (t - Tc) * kTile + 16 + n, L - 1);
@@ -1906,7 +2008,7 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
     }
   };
   auto issue_v_tile = [&](int t) {
-    if (t < Tc) issue_v_affine<WIDE>(T, Rc, t * kTile, a.c_rows - 1);
+    if (t < Tc) issue_v_affine<WIDE>(T, Rc, t * kTile, c_rows - 1);
     else if (PAGED) issue_v_rows<uint64_t, WIDE>(T, R, pra_n, prb_n);
     else issue_v_affine<WIDE>(T, R, rs + (t - Tc) * kTile, L - 1);
   };
@@ -1915,24 +2017,39 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
     issue_k_tile(first);
     issue_v_tile(first);
   }
-  // the dense kernel's loop: K half refilled after S^T, V half after P V
-  for (int k = 0; k < K; ++k) {
-    const int t = first + k * step;
+  // the dense kernel's loop: K half refilled after S^T, V half after P V (next < 0: not refilled)
+  auto tile_step = [&](int t, int next) {
     const int p0 = (t < Tc ? t : t - Tc) * kTile;
     const int N = t < Tc ? Nc : Nr;
     float y[8];
     qk_phase<WIDE>(T, qreg, a.scale_log2, y);
-    issue_k_tile(t + step);
+    if (next >= 0) issue_k_tile(next);
     if (p0 + kTile > N) mask_tail<WIDE>(T, y, jg, p0, N);
     bf16x8 a_hi, a_lo;
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     pv_phase(T, a_hi, a_lo, acc);
-    issue_v_tile(t + step);
+    if (next >= 0) issue_v_tile(next);
+  };
+  // (the last tile apart: no rows are requested for a tile that does not exist)
+  if (K > 0) {
+    int t = first;
+    for (int k = 1; k < K; ++k, t += step) tile_step(t, t + step);
+    tile_step(t, -1);
   }
-  l_run = rows_sum(l_run);
-  {
-    __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
-    finish_wg<false, WIDE ? 1 : 2>(wg_out_of(a, bh), head0, G, slot, acc, m_run, l_run, &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim);
+  __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
+  const WgOut o = wg_out_of(a, bh);
+  if (finish_wg<false, WIDE ? 1 : 2, LOCAL>(o, head0, G, slot, acc, m_run, rows_sum(l_run), &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim)) {
+    m_run = kNeg;
+    l_run = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int t = 0; t < nT; ++t) {
+      issue_k_tile(t);
+      issue_v_tile(t);
+      tile_step(t, -1);
+    }
+    store_heads(o, head0, G, acc, l_run);
   }
   report_guard(a.guard, bad);
 }
@@ -2120,14 +2237,24 @@ hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t 
   return hipGetLastError();
 }
 hipError_t launch_attn_compact(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
-  const dim3 grid(n_slots, a.Hkv, B);
+  const dim3 grid = fast_grid(a, B, n_slots), block(kAttnThreads);
+#define SFI_COMPACT(PAGED, WIDE)                                                                                                            \
+  do {                                                                                                                                      \
+    if (a.handover != 0)                                                                                                                    \
+      hipLaunchKernelGGL((attn_compact_kernel<PAGED, WIDE, true>), grid, block, 0, s, a.Kc, a.Vc, gather_flags(a), a.c_sb, a.c_sh,           \
+                         fast_shape(a, B), a.c_rows, a.n_split, a);                                                                          \
+    else                                                                                                                                    \
+      hipLaunchKernelGGL((attn_compact_kernel<PAGED, WIDE, false>), grid, block, 0, s, a.Kc, a.Vc, gather_flags(a), a.c_sb, a.c_sh,          \
+                         fast_shape(a, B), a.c_rows, a.n_split, a);                                                                          \
+  } while (0)
   if (a.G <= 8) {
-    if (a.table != nullptr) hipLaunchKernelGGL((attn_compact_kernel<true, true>), grid, dim3(kAttnThreads), 0, s, a);
-    else hipLaunchKernelGGL((attn_compact_kernel<false, true>), grid, dim3(kAttnThreads), 0, s, a);
+    if (a.table != nullptr) SFI_COMPACT(true, true);
+    else SFI_COMPACT(false, true);
   } else {
-    if (a.table != nullptr) hipLaunchKernelGGL((attn_compact_kernel<true, false>), grid, dim3(kAttnThreads), 0, s, a);
-    else hipLaunchKernelGGL((attn_compact_kernel<false, false>), grid, dim3(kAttnThreads), 0, s, a);
+    if (a.table != nullptr) SFI_COMPACT(true, false);
+    else SFI_COMPACT(false, false);
   }
+#undef SFI_COMPACT
   return hipGetLastError();
 }
 hipError_t launch_reorg(const ReorgArgs& a, int B, int rows, hipStream_t s) {
@@ -2137,10 +2264,16 @@ hipError_t launch_reorg(const ReorgArgs& a, int B, int rows, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_attn_gather(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
-  const dim3 grid(n_slots, a.Hkv, B), block(kAttnThreads);
+  const dim3 grid = fast_grid(a, B, n_slots), block(kAttnThreads);
 #define SFI_GATHER(PAGED, WIDE)                                                                                             \
-  hipLaunchKernelGGL((attn_gather_kernel<PAGED, WIDE>), grid, block, 0, s, a.sel_idx, a.n_sel, a.ctx_len, a.recent_start,  \
-                     gather_flags(a), (uint32_t)a.sel_stride, gather_shape(a), a.n_sink, a.n_split, a)
+  do {                                                                                                                      \
+    if (a.handover != 0)                                                                                                    \
+      hipLaunchKernelGGL((attn_gather_kernel<PAGED, WIDE, true>), grid, block, 0, s, a.sel_idx, a.n_sel, a.ctx_len,         \
+                         a.recent_start, gather_flags(a), (uint32_t)a.sel_stride, fast_shape(a, B), a.n_sink, a.n_split, a); \
+    else                                                                                                                    \
+      hipLaunchKernelGGL((attn_gather_kernel<PAGED, WIDE, false>), grid, block, 0, s, a.sel_idx, a.n_sel, a.ctx_len,        \
+                         a.recent_start, gather_flags(a), (uint32_t)a.sel_stride, fast_shape(a, B), a.n_sink, a.n_split, a); \
+  } while (0)
   if (a.G <= 8) {
     if (a.table != nullptr) SFI_GATHER(true, true);
     else SFI_GATHER(false, true);

@@ -171,3 +171,34 @@ def test_evidence_at_the_edges_of_its_tiles(oracle, n_j, mode, G, page):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
+
+
+# the hand-over of a split fast step: device scope (0), the L2 of one XCD (1), and workgroups taken for ones on different XCDs,
+# whose last wave does the list again (2); pairs in rows of eight and of a sequence, a row that is not full, heads that keep
+# device scope (3), bf16 outputs.  Each mode twice: the counters have to be back at zero.
+@pytest.mark.parametrize("B,Hkv,G", [(1, 8, 4), (4, 2, 4), (2, 4, 8), (8, 1, 5), (1, 2, 3), (3, 1, 16), (1, 16, 9), (2, 3, 4)])
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_fast_step_hand_over(oracle, B, Hkv, G, page, bf16):
+    from helpers import check_out_bf16
+    print(f"[gpu-edges] hand-over: B={B} Hkv={Hkv} G={G} page={page} bf16={bf16}", flush=True)
+    w = _workload(B, Hkv, G, [1500 - 13 * i for i in range(B)], 333, seed=600 + G)
+    r = Runner(w, page_size=page, out_bf16=bf16)
+    check = check_out_bf16 if bf16 else check_out
+    try:
+        q0, c0 = w.q(0), w.ctx_len(0)
+        _, sel, nsel = r.slow(q0, c0, w.budget)
+        r.reorg(sel, nsel, c0)
+        q, c, rs = w.q(1), w.ctx_len(1), w.recent_start(1)
+        want = oracle.sparse(q, w.K, w.V, sel, nsel, rs, c, w.n_sink)
+        for mode in (1, 2, 0, 2, 1):
+            r.sfi.sfi_set_handover(r.ctx.handle, mode)
+            for tiles_per_wave in (-1, 1):
+                r.sfi.sfi_set_tuning(r.ctx.handle, -1, tiles_per_wave, 1)
+                check(r.fast(q, sel, nsel, rs, c), want)
+                assert r.sfi.sfi_query_splits(r.ctx.handle)[1] > 1
+                check(r.fast_compact(q, nsel, sel.shape[2], rs, c), want)
+        with pytest.raises(RuntimeError):
+            r.sfi.sfi_set_handover(r.ctx.handle, 3)
+    finally:
+        r.close()
