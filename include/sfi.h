@@ -379,7 +379,7 @@ enum {
   SFI_STAGE_COUNT = 4,    /* not used: always 0 */
   SFI_STAGE_WRITE = 5,    /* ordered index write; short J: the whole selection, with the scoring and the output's merge
                              where no SCORE stage ran in a slow step */
-  SFI_STAGE_ATTN2 = 6,    /* the gather attention kernel of a mixed step */
+  SFI_STAGE_ATTN2 = 6,    /* the fast sequences' attention of a mixed step, where it is a launch of its own */
   SFI_STAGE_REORG = 7,    /* compact-buffer gather */
   SFI_N_STAGES = 8
 };

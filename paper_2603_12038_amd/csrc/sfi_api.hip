@@ -312,6 +312,15 @@ int handover_for(const sfi_ctx* x, int n_split) {
   return even ? x->handover : 0;
 }
 
+// Whether a ragged step's fast cells ride in its planned dense launch (attn_ragged_kernel): one per unit at most, and records
+// handed over as that kernel does it, if at all.  (The full Selector keeps two launches: the kernels are large, and
+// its three scoring launches leave less to gain.)
+bool one_ragged_launch(const sfi_ctx* x, const AttnArgs& f) {
+  const int Hkv = x->cfg.n_kv_heads, row = f.handover == 0 || Hkv >= 8 ? Hkv : 8;
+  const int cells = (x->cfg.batch * Hkv + row - 1) / row * row * f.n_split;
+  return x->cfg.selector_mode == 0 && cells <= x->n_cu && (f.n_split == 1 || f.handover != 0);
+}
+
 struct StageTimer {
   sfi_ctx* x;
   hipStream_t s;
@@ -1045,13 +1054,19 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   if (planned) d.slow_list = x->ws.slow_list;
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
-  {
-    StageTimer t(x, st, SFI_STAGE_ATTN2);
-    if (cb != nullptr) SFI_TRY(launch_attn_compact(f, x->cfg.batch, f.n_split, st));
-    else SFI_TRY(launch_attn_gather(f, x->cfg.batch, f.n_split, st));
+  if (planned && one_ragged_launch(x, f)) {
+    StageTimer t(x, st, SFI_STAGE_ATTN);
+    SFI_TRY(launch_attn_ragged(d, f, st));
     if (!t.stop()) return SFI_ELAUNCH;
+  } else {
+    {
+      StageTimer t(x, st, SFI_STAGE_ATTN2);
+      if (cb != nullptr) SFI_TRY(launch_attn_compact(f, x->cfg.batch, f.n_split, st));
+      else SFI_TRY(launch_attn_gather(f, x->cfg.batch, f.n_split, st));
+      if (!t.stop()) return SFI_ELAUNCH;
+    }
+    { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(d, x->cfg.batch, d.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   }
-  { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(d, x->cfg.batch, d.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (!merge_in_score) {
     MergeArgs m{x->ws.part, out, is_slow, x->cfg.n_q_heads, d.n_split, fast_done ? 0 : f.n_split, 2, x->ws.jstat, nullptr, x->G, x->alpha, x->cfg.out_bf16, fs};
     StageTimer t(x, st, SFI_STAGE_MERGE);

@@ -786,12 +786,12 @@ struct DenseShare {
   int bad;           // PLANNED: guard bits so far
   bool have_k;       // PLANNED: K rows of the first tile are on their way into T
 };
+// Floats of lds per wave: the logits stash, and at the end the wave's O for the combine (finish_wg).
+constexpr int patch_floats(int expose, bool big) { return expose == 0 ? 16 * kHeadDim : big ? 2 * kStashFloats : kStashFloats; }
 template <int EXPOSE, bool PAGED, bool BIG, bool WIDE, bool PLANNED>
-__device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& sh, const int h, const int b, Tile& T, const int tid_bias = 0) {
+__device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& sh, const int h, const int b, Tile& T, float* lds, const int tid_bias = 0) {
   constexpr int kStash = BIG ? 2 * kStashFloats : kStashFloats;
-  // per-wave LDS: the logits stash, and at the end the wave's O for the combine (finish_wg)
-  constexpr int kPatch = EXPOSE != 0 ? kStash : 16 * kHeadDim;
-  __shared__ __align__(16) float s_patch[kWaves][kPatch];
+  constexpr int kPatch = patch_floats(EXPOSE, BIG);
   // everything uniform is asked for at once (the first argument load of a wave takes 0.4 us)
   asm volatile("" ::"s"(a.q), "s"(a.K), "s"(a.V), "s"(a.k_sb), "s"(a.k_sh), "s"(a.k_st), "s"(a.v_sb), "s"(a.v_sh), "s"(a.v_st),
                "s"(a.ctx_len), "s"(a.is_slow), "s"(a.q_len), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.n_sink), "s"(a.recent),
@@ -934,7 +934,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   // With EXPOSE == 2 a tile has one more row: ||k_j||^2 of its 32 positions, for the key-norm factor of
   // the Selector's prior (Eq. selector_prior_kn).
   const int rows_exp = G + (EXPOSE == 2 ? 1 : 0);
-  float* stash = &s_patch[w][0];
+  float* stash = lds + w * kPatch;
   float* lg_base = EXPOSE != 0 ? a.logits + (int64_t)bh * rows_exp * a.ld_pos : nullptr;
   const int tile_f4 = rows_exp * (kTile / 4);        // float4 per tile
   const int stash_cap = kStash / (rows_exp * kTile);  // tiles the stash holds
@@ -1035,7 +1035,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
     o.out_direct = o.out_merge;
     o.out_merge = nullptr;
   }
-  finish_wg<EXPOSE != 0>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), &s_patch[0][0], kPatch, m_j,
+  finish_wg<EXPOSE != 0>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), lds, kPatch, m_j,
                                EXPOSE != 0 ? rows_sum(l_j) : 0.f);
   report_guard(a.guard, bad);
 }
@@ -1043,8 +1043,9 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
 template <int EXPOSE, bool PAGED, bool BIG = false, bool WIDE = false>
 __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(const AttnArgs a) {
   const DenseShare sh{(int)blockIdx.x * kWaves, a.n_split * kWaves, 0, (int)blockIdx.x, a.n_split, 0, 0, 0, false};
+  __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, BIG)];
   Tile T;
-  dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.y, blockIdx.z, T);
+  dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.y, blockIdx.z, T, s_patch);
 }
 // The launch planned on the device: more than one sequence, every one with a length of its own (which only the device
 // knows) and, in the ragged step (sfi_mixed_step*), only some of them slow.  With a workgroup per cell the shares follow the
@@ -1080,11 +1081,11 @@ __device__ __forceinline__ int plan_border(const PlanArgs& p, int P, int rank, i
   if (P == p.total) x = p.W << kShareLg, off = 0;
   return x;
 }
-template <int EXPOSE, bool PAGED>
-__global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
-                                                                             uint32_t strides, int B, int W_max, float per_min, int n_sink,
-                                                                             int recent_in, int len_cap, const AttnArgs a) {
-  const int j = blockIdx.x, h = blockIdx.y;
+// GUESS: the workgroup requests its first rows on the guess that all sequences are equally long (a.plan_even).
+template <int EXPOSE, bool PAGED, bool GUESS>
+__device__ __forceinline__ void planned_body(const int j, const int h, const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
+                                             uint32_t strides, int B, int W_max, float per_min, int n_sink, int recent_in, int len_cap,
+                                             const AttnArgs& a, float* lds) {
   const int lane = threadIdx.x & 63;
   const int ms = strides & 0xffff, fs = strides >> 16;
   // rows seen, recent window seen and tiles of sequence b (at least one tile: an empty context has a record too)
@@ -1112,10 +1113,10 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
   if (is_slow != nullptr) on0 = is_slow[bc0 * fs];
   __builtin_amdgcn_sched_barrier(0);
   // the guess: this workgroup's place if all sequences are equally long
-  const int even = a.plan_even;
+  const int even = GUESS ? a.plan_even : 0;
   const int b_even = even > 0 ? j / even : B, slot_even = j - b_even * even;
   Tile T;
-  if (!PAGED && b_even < B) {
+  if (GUESS && !PAGED && b_even < B) {
     Rows R;
     R.Kb = reinterpret_cast<const char*>(a.K + b_even * a.k_sb + h * a.k_sh);
     R.k_st = (uint32_t)a.k_st * 2u;
@@ -1138,7 +1139,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     count += t > 0;
     least = t > 0 ? fminf(least, (float)t) : least;
   }
-  if (__all(same)) {
+  if (GUESS && __all(same)) {
     if (b_even >= B) return;
     DenseShare sh;
     sh.bad = 0;
@@ -1150,7 +1151,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     sh.n_rec = even;
     sh.have_k = !PAGED;
     if (slot_even == 0 && h == 0 && threadIdx.x == 0) a.seq_rec[b_even] = even;
-    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b_even, T);
+    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b_even, T, lds);
     return;
   }
   const int inc_t = (int)wave_incl_scan((uint32_t)tiles), inc_c = (int)wave_incl_scan((uint32_t)count);
@@ -1223,7 +1224,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     int zero = 0;
     asm volatile("" : "+s"(zero));
     sh.have_k = false;
-    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b, T, zero);
+    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b, T, lds, zero);
     P += t_b;
     if (__builtin_amdgcn_readfirstlane(x1) >= start + (1 << kShareLg)) return;
     do {  // (there is one: the list goes on)
@@ -1233,6 +1234,14 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
     L_in = ctx_len[b * ms];
     __syncthreads();  // the combine of this sequence is read before the next one's logits go into the same LDS
   }
+}
+template <int EXPOSE, bool PAGED>
+__global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
+                                                                             uint32_t strides, int B, int W_max, float per_min, int n_sink,
+                                                                             int recent_in, int len_cap, const AttnArgs a) {
+  __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, true)];
+  planned_body<EXPOSE, PAGED, true>(blockIdx.x, blockIdx.y, ctx_len, is_slow, q_len, strides, B, W_max, per_min, n_sink, recent_in, len_cap, a,
+                                    s_patch);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1450,12 +1459,9 @@ hipError_t launch_attn_evidence(const AttnArgs& a, int B, int n_slots, hipStream
 // ------------------------------------------------------------------------------------------------
 // The preloaded arguments: shape, see fast_cell.
 template <bool PAGED, bool WIDE, bool LOCAL>
-__global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int32_t* sel_idx, const int32_t* n_sel_p, const int32_t* ctx_len_p,
-                                                                      const int32_t* recent_start_p, const uint8_t* is_slow_p,
-                                                                      const uint32_t sel_stride, const uint32_t shape, const int n_sink,
-                                                                      const int n_split, const AttnArgs a) {
-  const FastCell cell = fast_cell<LOCAL>(shape);
-  if (cell.off) return;
+__device__ __forceinline__ void gather_body(const FastCell& cell, const int32_t* sel_idx, const int32_t* n_sel_p, const int32_t* ctx_len_p,
+                                            const int32_t* recent_start_p, const uint8_t* is_slow_p, const uint32_t sel_stride,
+                                            const uint32_t shape, const int n_sink, const int n_split, const AttnArgs& a, float* lds) {
   const int slot = cell.slot, h = cell.h, b = cell.b;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
@@ -1586,9 +1592,8 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
     softmax_phase(y, acc, m_run, l_run, jg, a_hi, a_lo);
     pv_phase(T, a_hi, a_lo, acc);
   }
-  __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
   const WgOut o = wg_out_of(a, bh);
-  if (finish_wg<false, WIDE ? 1 : 2, LOCAL>(o, head0, G, slot, acc, m_run, rows_sum(l_run), &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim)) {
+  if (finish_wg<false, WIDE ? 1 : 2, LOCAL>(o, head0, G, slot, acc, m_run, rows_sum(l_run), lds, (WIDE ? 8 : 16) * kHeadDim)) {
     m_run = kNeg;
     l_run = 0.f;
 #pragma unroll
@@ -1611,6 +1616,16 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int3
     store_heads(o, head0, G, acc, l_run);
   }
   report_guard(a.guard, W.bad);  // last: the way to the record and the merge is the launch's critical path
+}
+template <bool PAGED, bool WIDE, bool LOCAL>
+__global__ __launch_bounds__(kAttnThreads, 3) void attn_gather_kernel(const int32_t* sel_idx, const int32_t* n_sel_p, const int32_t* ctx_len_p,
+                                                                      const int32_t* recent_start_p, const uint8_t* is_slow_p,
+                                                                      const uint32_t sel_stride, const uint32_t shape, const int n_sink,
+                                                                      const int n_split, const AttnArgs a) {
+  const FastCell cell = fast_cell<LOCAL>(shape);
+  if (cell.off) return;
+  __shared__ __align__(16) float s_red[kWaves * (WIDE ? 8 : 16) * kHeadDim];
+  gather_body<PAGED, WIDE, LOCAL>(cell, sel_idx, n_sel_p, ctx_len_p, recent_start_p, is_slow_p, sel_stride, shape, n_sink, n_split, a, s_red);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1932,11 +1947,9 @@ hipError_t launch_attn_dense_floor(const AttnArgs& a, int B, int n_slots, int wi
 // ------------------------------------------------------------------------------------------------
 // What the first tile's rows need arrives in registers, and the flag of a ragged step is looked at behind their requests.
 template <bool PAGED, bool WIDE, bool LOCAL>  // PAGED: the recent window is read from a paged cache (the compact buffers are always flat)
-__global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kernel(const uint16_t* Kc, const uint16_t* Vc, const uint8_t* is_slow_p,
-                                                                                   const int64_t c_sb, const int64_t c_sh, const uint32_t shape,
-                                                                                   const int c_rows, const int n_split, const AttnArgs a) {
-  const FastCell cell = fast_cell<LOCAL>(shape);
-  if (cell.off) return;
+__device__ __forceinline__ void compact_body(const FastCell& cell, const uint16_t* Kc, const uint16_t* Vc, const uint8_t* is_slow_p,
+                                             const int64_t c_sb, const int64_t c_sh, const uint32_t shape, const int c_rows, const int n_split,
+                                             const AttnArgs& a, float* lds) {
   const int slot = cell.slot, h = cell.h, b = cell.b;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
@@ -2036,9 +2049,8 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
     for (int k = 1; k < K; ++k, t += step) tile_step(t, t + step);
     tile_step(t, -1);
   }
-  __shared__ __align__(16) float s_red[kWaves][WIDE ? 8 : 16][kHeadDim];
   const WgOut o = wg_out_of(a, bh);
-  if (finish_wg<false, WIDE ? 1 : 2, LOCAL>(o, head0, G, slot, acc, m_run, rows_sum(l_run), &s_red[0][0][0], (WIDE ? 8 : 16) * kHeadDim)) {
+  if (finish_wg<false, WIDE ? 1 : 2, LOCAL>(o, head0, G, slot, acc, m_run, rows_sum(l_run), lds, (WIDE ? 8 : 16) * kHeadDim)) {
     m_run = kNeg;
     l_run = 0.f;
 #pragma unroll
@@ -2052,6 +2064,47 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
     store_heads(o, head0, G, acc, l_run);
   }
   report_guard(a.guard, bad);
+}
+template <bool PAGED, bool WIDE, bool LOCAL>
+__global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kernel(const uint16_t* Kc, const uint16_t* Vc, const uint8_t* is_slow_p,
+                                                                                   const int64_t c_sb, const int64_t c_sh, const uint32_t shape,
+                                                                                   const int c_rows, const int n_split, const AttnArgs a) {
+  const FastCell cell = fast_cell<LOCAL>(shape);
+  if (cell.off) return;
+  __shared__ __align__(16) float s_red[kWaves * (WIDE ? 8 : 16) * kHeadDim];
+  compact_body<PAGED, WIDE, LOCAL>(cell, Kc, Vc, is_slow_p, c_sb, c_sh, shape, c_rows, n_split, a, s_red);
+}
+
+// ------------------------------------------------------------------------------------------------
+// The ragged step's attention in one launch: a workgroup takes a cell of the fast sequences, as in the gather or the compact
+// launch, and then its share of the slow ones, as in the planned dense launch, for as many cells as there are shares.  One
+// launch less, the start of the dense part and the hand-over of the fast part hide behind each other, and a workgroup whose
+// cell belongs to a slow sequence begins its share at once.  (The other order gains half of that: the cell's first loads
+// wait for the acknowledgement of the share's last stores.)
+// Two launches / one, us a step with the Selector behind it: 12 x 5003..30011 rows, budget 1024, 1 slow, compact buffers 53.2 / 51.1; 32 x 16384..65536
+// rows, G = 8, budget 2048, none slow 59.3 / 57.8, 1 103.0 / 99.9, 2 132.9 / 130.5, 4 195.8 / 196.0, 8 337.4 / 346.1 (a quarter slow: their
+// cells' workgroups are done early); 2 x 5003..30011, 1 slow 48.4 / 45.2; 8 x 3000..8000, G = 16, 1 slow 40.5 / 37.1; 64 x 1000..3000, 2 KV heads, 3 slow
+// 34.5 / 31.1.
+// With more cells than shares the fast part loses the two other workgroups a unit would hold: 128 x 3000..8000 rows 128 / 136.
+// ------------------------------------------------------------------------------------------------
+template <bool PAGED, bool WIDE, bool COMPACT>
+__global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* recent_start,
+                                                                      const int32_t* sel_idx, const uint32_t strides, const uint32_t shape, const int B,
+                                                                      const int W_max, const int n_sink, const int n_split, const float per_min,
+                                                                      const int row, const AttnArgs f, const AttnArgs d) {
+  __shared__ __align__(16) float s_patch[kWaves * patch_floats(1, true)];
+  const uint32_t id = blockIdx.x, Hkv = shape & 0xffffu;
+  // the cells in the order of fast_grid: row pairs side by side, n_split slots of them, then the next row
+  const uint32_t q = id / (uint32_t)row, z = q / (uint32_t)n_split, pair = z * row + (id - q * row);
+  const FastCell cell{(int)(q - z * n_split), (int)(pair % Hkv), (int)(pair / Hkv), false};
+  if (cell.b < B) {
+    if (COMPACT) compact_body<PAGED, WIDE, true>(cell, f.Kc, f.Vc, is_slow, f.c_sb, f.c_sh, shape, f.c_rows, n_split, f, s_patch);
+    else gather_body<PAGED, WIDE, true>(cell, sel_idx, f.n_sel, ctx_len, recent_start, is_slow, (uint32_t)f.sel_stride, shape, n_sink, n_split, f, s_patch);
+  }
+  __syncthreads();  // the cell's results in LDS have been read
+  if (id < (uint32_t)W_max * Hkv)
+    planned_body<1, PAGED, false>(id % (uint32_t)W_max, id / (uint32_t)W_max, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent,
+                                  d.len_cap, d, s_patch);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2234,6 +2287,28 @@ hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t 
   const dim3 grid(n_slots, a.Hkv, B);
   if (a.table != nullptr) launch_dense_t<true>(a, grid, s);
   else launch_dense_t<false>(a, grid, s);
+  return hipGetLastError();
+}
+hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, hipStream_t s) {
+  const int B = d.plan_batch;
+  const dim3 g = fast_grid(f, B, f.n_split);
+  const dim3 grid(std::max((unsigned)(d.plan_wgs * d.Hkv), g.x * g.y * g.z)), block(kAttnThreads);
+  const uint32_t strides = (uint32_t)d.ms | (uint32_t)d.fs << 16;
+  const int row = f.handover == 0 ? f.Hkv : (int)g.x;
+#define SFI_RAGGED(PAGED, WIDE, COMPACT)                                                                                                         \
+  hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start, f.sel_idx, strides, \
+                     fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min, row, f, d)
+#define SFI_RAGGED_C(PAGED, COMPACT)                  \
+  do {                                                \
+    if (f.G <= 8) SFI_RAGGED(PAGED, true, COMPACT);   \
+    else SFI_RAGGED(PAGED, false, COMPACT);           \
+  } while (0)
+  if (d.table != nullptr && f.Kc != nullptr) SFI_RAGGED_C(true, true);
+  else if (d.table != nullptr) SFI_RAGGED_C(true, false);
+  else if (f.Kc != nullptr) SFI_RAGGED_C(false, true);
+  else SFI_RAGGED_C(false, false);
+#undef SFI_RAGGED_C
+#undef SFI_RAGGED
   return hipGetLastError();
 }
 hipError_t launch_attn_compact(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
