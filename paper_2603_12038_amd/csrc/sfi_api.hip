@@ -305,9 +305,11 @@ int compact_splits_for(const sfi_ctx* x, int sel_stride) {
 // pairs than XCDs and many workgroups the others would stand idle.  Other numbers of KV heads need a division in front of
 // the first request.)  Device scope / XCD-local, us a layer: 1 x 4096 rows, 2 KV heads, 3 workgroups per pair 5.6 / 5.4; 1 x 8192, 4 KV heads, 4 per pair 6.1 / 5.8; figures
 // for even launches: finish_wg.
-int handover_for(const sfi_ctx* x, int n_split) {
+// A head's last record must not share a cache line with the next head's first one, which may not be written yet when that
+// line is read: with as many workgroups as a head has slots (static scratch only) the records go at device scope.
+int handover_for(const sfi_ctx* x, int n_split, int slot_cap) {
   const int Hkv = x->cfg.n_kv_heads, pairs = x->cfg.batch * Hkv;
-  if (x->handover == 0 || n_split < 2) return 0;
+  if (x->handover == 0 || n_split < 2 || n_split >= slot_cap) return 0;
   const bool even = Hkv % 8 == 0 || ((Hkv == 4 || Hkv == 2 || Hkv == 1) && (pairs % 8 == 0 || (pairs < 8 && n_split <= 4)));
   return even ? x->handover : 0;
 }
@@ -767,7 +769,7 @@ int fast_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const 
   a.n_split = fast_splits_for(x, sel_stride, max_splits);
   x->last_fast_splits = a.n_split;
   if (a.n_split == 1) a.out_direct = out;  // one workgroup per pair finishes the softmax itself
-  else if (x->tail_merge) { a.out_merge = out; a.arrive = arrive; a.handover = handover_for(x, a.n_split); }
+  else if (x->tail_merge) { a.out_merge = out; a.arrive = arrive; a.handover = handover_for(x, a.n_split, a.slot_cap); }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_gather(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
   MergeArgs m{part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};
@@ -824,7 +826,7 @@ int sfi_fast_step_floor(sfi_ctx* x, const void* q, const void* K, const void* V,
   }
   x->last_fast_splits = a.n_split;
   if (tail && a.n_split == 1) a.out_direct = (float*)out;
-  else if (tail) { a.out_merge = (float*)out; a.arrive = x->ws.arrive; a.handover = handover_for(x, a.n_split); }
+  else if (tail) { a.out_merge = (float*)out; a.arrive = x->ws.arrive; a.handover = handover_for(x, a.n_split, a.slot_cap); }
   SFI_TRY(launch_attn_gather_floor(a, x->cfg.batch, a.n_split, tail, burst, tpw, depth, (hipStream_t)stream));
   return SFI_OK;
 }
@@ -981,7 +983,7 @@ int sfi_fast_step_compact(sfi_ctx* x, const void* q, const void* Kc, const void*
   a.n_split = compact_splits_for(x, sel_stride);
   x->last_fast_splits = a.n_split;
   if (a.n_split == 1) a.out_direct = out;
-  else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; a.handover = handover_for(x, a.n_split); }
+  else if (x->tail_merge) { a.out_merge = out; a.arrive = x->ws.arrive; a.handover = handover_for(x, a.n_split, a.slot_cap); }
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_compact(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (a.n_split == 1 || a.out_merge != nullptr) return SFI_OK;
   MergeArgs m{x->ws.part, out, nullptr, x->cfg.n_q_heads, 0, a.n_split, 1, nullptr, nullptr, x->G, x->alpha, x->cfg.out_bf16};
@@ -1041,7 +1043,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
     f.n_split = fast_splits_for(x, budget);
   }
   if (f.n_split == 1) f.out_direct = out;
-  else if (x->tail_merge) { f.out_merge = out; f.arrive = x->ws.arrive; f.handover = handover_for(x, f.n_split); }  // slow sequences' workgroups never arrive
+  else if (x->tail_merge) { f.out_merge = out; f.arrive = x->ws.arrive; f.handover = handover_for(x, f.n_split, f.slot_cap); }  // slow sequences' workgroups never arrive
   x->last_fast_splits = f.n_split;
   // Fast sequences finish inside their launch unless their split records need the merge launch;
   // slow sequences are merged by the first scoring launch (as in sfi_slow_step).  The merge kernel only

@@ -464,8 +464,9 @@ __device__ __forceinline__ void pv_phase(const Tile& T, const bf16x8& a_hi, cons
 
 // Accesses that one workgroup's records are handed to another with inside a launch, without a fence.  LOCAL false: device
 // scope, visible to / from every compute unit whatever L2 it sits behind.  LOCAL true: they go to the L2 of this XCD and no
-// further, visible to / from the compute units of the same XCD (the first-level caches are written through, and a load
-// with sc0 does not hit in them).  They go through a buffer descriptor, 16 bytes at a time: the records of one (b, h) pair
+// further, visible to / from the compute units of the same XCD: the first-level caches are written through, and hold no
+// older copy of a record, since its lines are read only once all workgroups have sent theirs (a launch starts with these
+// caches empty; handover_for keeps the records of two heads out of one line).  They go through a buffer descriptor, 16 bytes at a time: the records of one (b, h) pair
 // as a raw buffer (byte offsets, out-of-range accesses dropped by the hardware).
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));

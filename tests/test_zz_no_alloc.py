@@ -86,3 +86,13 @@ def test_static_scratch_limits_and_coarser_split(oracle):
     with pytest.raises(SfiError) as e:
         sfi.sfi_fast_step_static(cfg, dummy, dummy, dummy, dummy, dummy, 64, dummy, dummy, dummy)
     assert e.value.code == -2
+
+
+def test_static_scratch_with_as_many_workgroups_as_slots(oracle):
+    """Where a head's records fill its slots, the last one shares a cache line with the next head's first one."""
+    # 3952 query heads leave room for two records each, and 304 pairs on 256 compute units are split in two
+    w = syn.make_tiny(L0=2300, steps=2, budget=2048, recent=64, n_support=8, B=304, Hq=13, Hkv=1)
+    _step(f"slots full: B={w.B} Hq={w.Hq} Hkv={w.Hkv}")
+    got, ref, splits = _case(oracle, w, w.budget, 14)
+    assert splits == 8192 // (w.B * w.Hq) == 2, "the case is meant to fill the slots"
+    assert np.array_equal(got, ref), "same launch plan, same arithmetic, whatever the records' scope"
