@@ -1286,17 +1286,13 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
       pg[2 * hf + i] = P.page_of(pg_row[2 * hf + i]);
     }
   };
-  // rows of tile t into half hf; rows above hi (no position of J) read row hi
-  auto issue = [&](KPair& U, int hf, int t, int hi, int last_used) {
+  // rows of tile t into half hf; rows above hi (no position of J) read row hi, whose block is a valid one
+  auto issue = [&](KPair& U, int hf, int t, int hi) {
     OffT o[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       int row = (int)min((uint32_t)n_sink + (uint32_t)(t * kTile + 16 * i + n), (uint32_t)hi);  // (n_sink is not bounded)
-      if (PAGED) {
-        int odd = 0;
-        row = P.phys(pg_row[2 * hf + i], pg[2 * hf + i], odd);
-        if (pg_row[2 * hf + i] <= last_used) bad |= odd;
-      }
+      if (PAGED) row = P.phys(pg_row[2 * hf + i], pg[2 * hf + i], bad);
       o[i] = (OffT)((OffT)(uint32_t)row * k_st + k_lane);
     }
 #pragma unroll
@@ -1306,7 +1302,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
   };
   KPair U;
   // The first tile's rows follow from the arguments that the wave finds in registers (a paged cache's from the length on).
-  if (!PAGED) issue(U, 0, first, row_cap, 0);
+  if (!PAGED) issue(U, 0, first, row_cap);
   const int L_in = ctx_len[b];
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("" ::"s"(a.q), "s"(a.logits), "s"(a.part), "s"(a.guard), "s"(a.ld_pos), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.recent), "s"(a.n_split),
@@ -1314,7 +1310,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
   const int G = a.G;
   const int64_t head0 = (int64_t)b * a.Hq + h * G;
   const int step = a.n_split * kWaves;
-  if (!PAGED) issue(U, 1, first + step, row_cap, 0);
+  if (!PAGED) issue(U, 1, first + step, row_cap);
   bf16x8 qreg[4];
   load_q_raw(qreg, a.q, head0, G, jg, n);
   int L, recent;
@@ -1322,13 +1318,12 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
   const int NJ = max(0, L - recent - n_sink);
   const int nT = (NJ + kTile - 1) / kTile;
   const int hi = max(n_sink + NJ - 1, 0);
-  const int last_used = NJ > 0 ? hi : -1;
   if (PAGED && first < nT) {
     P = pages_of(a, b, L);
     pages_for(0, first, hi);
     pages_for(1, first + step, hi);
-    issue(U, 0, first, hi, last_used);
-    issue(U, 1, first + step, hi, last_used);
+    issue(U, 0, first, hi);
+    issue(U, 1, first + step, hi);
     pages_for(0, first + 2 * step, hi);
     pages_for(1, first + 3 * step, hi);
   }
@@ -1370,7 +1365,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
 #pragma unroll
       for (int j = 0; j < 4; ++j) y[i][j] = s[j] * a.scale_log2;
       if (decltype(refill)::value && (i & 1) != 0) {
-        issue(U, i >> 1, t + (2 + (i >> 1)) * step, hi, last_used);
+        issue(U, i >> 1, t + (2 + (i >> 1)) * step, hi);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -2005,8 +2000,7 @@ __device__ __forceinline__ void compact_body(const FastCell& cell, const uint16_
   for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Tile t < Tc is rows 32 t .. of the compact segment, tile t >= Tc rows rs + 32 (t - Tc) .. of the cache
-  // (clamped to L - 1, which is also what the refill past the wave's last tile reads).  The branch is
-  // wave-uniform and both sides issue the same number of loads.
+  // (clamped to L - 1).  The branch is wave-uniform and both sides issue the same number of loads.
   int pra_n = 0, prb_n = 0;  // PAGED: physical rows of the recent tile whose K half was issued last
   auto issue_k_tile = [&](int t) {
     if (t < Tc) {
