@@ -1,4 +1,5 @@
 // C-ABI of libsfi: argument checks, workspace carving, launch sequencing.  No arithmetic here.
+#include <algorithm>
 #include <math.h>
 #include <mutex>
 #include <new>
@@ -196,6 +197,16 @@ int evidence_splits_for(const sfi_ctx* x, int max_len) {
   if (s < 1) s = 1;
   const int per_wave = (tiles + kWaves * s - 1) / (kWaves * s);
   return (tiles + kWaves * per_wave - 1) / (kWaves * per_wave);
+}
+
+// A launch whose K may be larger than the caches looks at the lengths (attn_evidence_kernel, LINES).  Strides of zero: sequences or
+// heads that share their rows.
+void set_evidence_cache(const sfi_ctx* x, AttnArgs* a, int max_len) {
+  const int64_t heads = a->k_sh != 0 ? x->cfg.n_kv_heads : 1, seqs = a->k_sb != 0 || x->table != nullptr ? x->cfg.batch : 1;
+  const int64_t cached = kCacheBytes / (kHeadDim * 2) / heads;
+  if (seqs * max_len <= cached) return;
+  a->cached_rows = (int32_t)std::max<int64_t>(cached, 1);
+  a->plan_batch = (int32_t)seqs;
 }
 
 // Where the dense launch plans itself on the device: more than one sequence (with one there is nothing to even out, and
@@ -624,6 +635,7 @@ int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.with_knorm = x->cfg.selector_mode == 1;
   if (out == nullptr) {  // evidence only (sfi_evidence_add without an output)
     a.n_split = evidence_splits_for(x, ml);
+    set_evidence_cache(x, &a, ml);
     x->last_dense_splits = a.n_split;
     x->last_dense_planned = 0;
     StageTimer t(x, st, SFI_STAGE_ATTN);

@@ -1248,8 +1248,17 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
 // ------------------------------------------------------------------------------------------------
 // evidence kernel: the logits of one query over the allowed set J (and the key norms), and their softmax statistics;
 // no V row is read.  This is a query of a window: the next launches read the same K rows, so their loads leave them to the
-// caches instead of streaming past them (16 queries over 58 MB of K: 309 us streamed, 274 not; over 800 MB, more than the caches hold, 4 queries 835 / 747: the
-// two halves of a 128-byte line are asked for one after the other, and a streamed line may be gone in between).
+// caches instead of streaming past them (16 queries over 58 MB of K: 309 us streamed, 274 not), as long as the caches can hold them.
+// LINES, for a K that may be larger: left to the caches such a K pushes out the logits and the accumulator, which the
+// accumulation behind this launch then fetches from memory (32 x 16000 rows, 8 KV heads, one head each: 13.9 us, streamed 12.1), and
+// streamed in pieces of half a line, as the product wants them, a line may be gone before its other half is asked for
+// (210 us; from the caches 193).  So a request is 8 whole lines of 8 rows, streamed (175), and lanes n and n ^ 8 swap what they got
+// for each other: 32 register moves a tile, from there on the layout is the other's.  Whether K fits, the kernel finds by
+// adding up the lengths, which only the device knows: up to a.cached_rows the same requests go through the caches, as a wave's
+// first two tiles do in any case.
+// Windows of 8 queries, 16000 rows, 8 KV heads, us, plain requests / this: G = 4, 10 sequences (312 MB) 568 / 509, 12 (375) 681 / 581, 16 (500) 914 / 756;
+// G = 1, 493 / 453, 619 / 515, 835 / 668; 16 x 4000..16000 (312) 628 / 534.  All streamed although K fits: 6 sequences (188) 305 / 337, 8 (250) 414 / 457,
+// 9 (281) 459 / 489.  A launch whose bound fits stays with the plain requests: 4 sequences 221, G = 1 203, with norms 237; by lines 224, 207, 244.
 // What bounds it: the rows, at the rate the last-level cache gives them (58 MB: loads alone 10.0 us behind a launch of
 // 1.6 us).  So every wave has two tiles on their way all the time, each refilled when its products are done; the
 // statistics are kept per lane (its own positions of its head) and meet once at the end, so that nothing in the loop
@@ -1261,8 +1270,24 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
 constexpr int kEvidenceStash = 2432;  // floats of logits a wave parks in LDS: four tiles of 16 heads and norms, 15 of 4 heads and norms
 struct KPair {    // two tiles of K: tile hf is blocks 2 hf and 2 hf + 1
   uint4 k[4][4];  // block i: row 16 (i & 1) + n of its tile, dims kb * 32 + 8 * jg .. + 8
+                  // (LINES, until swapped: row 16 (i & 1) + 8 (kb & 1) + (n & 7), dims (kb / 2) * 64 + 32 * (n / 8) + 8 * jg .. + 8)
 };
-template <int EXPOSE, bool PAGED>
+// Within a row of 16 lanes: the value of lane n & 7, or of lane 8 + (n & 7).
+__device__ __forceinline__ int lower_half(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x128, 0xf, 0xc, false); }
+__device__ __forceinline__ int upper_half(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x128, 0xf, 0x3, false); }
+// Two requests for whole lines become two operands: lanes n >= 8 trade their x for the y of lane n - 8.
+__device__ __forceinline__ void swap_halves(uint32_t& x, uint32_t& y) {
+  const int a = (int)x, b = (int)y;
+  x = (uint32_t)__builtin_amdgcn_update_dpp(a, b, 0x128, 0xf, 0xc, false);
+  y = (uint32_t)__builtin_amdgcn_update_dpp(b, a, 0x128, 0xf, 0x3, false);
+}
+__device__ __forceinline__ void swap_halves(uint4& x, uint4& y) {
+  swap_halves(x.x, y.x);
+  swap_halves(x.y, y.y);
+  swap_halves(x.z, y.z);
+  swap_halves(x.w, y.w);
+}
+template <int EXPOSE, bool PAGED, bool LINES>
 __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const uint16_t* K, const int32_t* ctx_len, const int32_t* q_len,
                                                                         const int64_t k_sb, const int64_t k_sh, const uint32_t k_st,
                                                                         const int n_sink, const int row_cap, const int len_cap,
@@ -1274,7 +1299,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
   const char* const Kb = reinterpret_cast<const char*>(K + b * k_sb + h * k_sh);
-  const uint32_t k_lane = jg * 16;
+  const uint32_t k_lane = LINES ? (n >> 3) * 64 + jg * 16 : jg * 16;
   const int first = slot * kWaves + w;
   int bad = 0;
   Pages P;
@@ -1287,18 +1312,40 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
     }
   };
   // rows of tile t into half hf; rows above hi (no position of J) read row hi, whose block is a valid one
+  bool stream = false;  // LINES, the same for all workgroups once the lengths are known
   auto issue = [&](KPair& U, int hf, int t, int hi) {
-    OffT o[2];
+    auto row_at = [&](int i) { return (int)min((uint32_t)n_sink + (uint32_t)(t * kTile + i), (uint32_t)hi); };  // (n_sink is not bounded)
+    auto offset = [&](int row) { return (OffT)((OffT)(uint32_t)row * k_st + k_lane); };
+    if constexpr (LINES) {
+      OffT o[4];  // rows 8 j + (n & 7)
+      if (PAGED) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      int row = (int)min((uint32_t)n_sink + (uint32_t)(t * kTile + 16 * i + n), (uint32_t)hi);  // (n_sink is not bounded)
-      if (PAGED) row = P.phys(pg_row[2 * hf + i], pg[2 * hf + i], bad);
-      o[i] = (OffT)((OffT)(uint32_t)row * k_st + k_lane);
+        for (int i = 0; i < 2; ++i) {
+          const int row = P.phys(pg_row[2 * hf + i], pg[2 * hf + i], bad);
+          o[2 * i] = offset(lower_half(row));
+          o[2 * i + 1] = offset(upper_half(row));
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = offset(row_at(8 * j + (n & 7)));
+      }
+      auto request = [&](auto past_caches) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int l = 0; l < 2; ++l) U.k[2 * hf + (j >> 1)][2 * l + (j & 1)] = load_row16<decltype(past_caches)::value>(Kb, o[j], l * 128);
+      };
+      if (stream) request(std::integral_constant<bool, true>());  // (wave-uniform, as many loads on either side)
+      else request(std::integral_constant<bool, false>());
+    } else {
+      OffT o[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) o[i] = offset(PAGED ? P.phys(pg_row[2 * hf + i], pg[2 * hf + i], bad) : row_at(16 * i + n));
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) U.k[2 * hf + i][kb] = load_row16<false>(Kb, o[i], kb * 64);
     }
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) U.k[2 * hf + i][kb] = load_row16<false>(Kb, o[i], kb * 64);
   };
   KPair U;
   // The first tile's rows follow from the arguments that the wave finds in registers (a paged cache's from the length on).
@@ -1355,6 +1402,10 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
     float k2[4];  // (lanes with jg == n / 4) squared norm of row 16 i + n: the diagonal of K K^T
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+      if (LINES) {
+        swap_halves(U.k[i][0], U.k[i][1]);
+        swap_halves(U.k[i][2], U.k[i][3]);
+      }
       f32x4 s = {0.f, 0.f, 0.f, 0.f}, d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
@@ -1403,6 +1454,11 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
       for (int j = 0; j < 4; ++j) l_run += ok[i][j] ? fast_exp2(y[i][j] - m_new) : 0.f;
   };
   if (first < nT) {
+    if (LINES) {
+      float rows = 0.f;
+      for (int i = lane; i < a.plan_batch; i += 64) rows += (float)min(max(ctx_len[i], 0), len_cap);
+      stream = __builtin_amdgcn_readfirstlane(wave_sum_f(rows) > (float)a.cached_rows) != 0;
+    }
     int t = first;
     for (; t + 2 * step < nT; t += 2 * step) pair_step(t, std::integral_constant<bool, true>());
     pair_step(t, std::integral_constant<bool, false>());
@@ -1425,9 +1481,14 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
 }
 hipError_t launch_attn_evidence(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
   const dim3 grid(n_slots, a.Hkv, B), block(kAttnThreads);
-#define SFI_EVIDENCE(EXPOSE, PAGED)                                                                                               \
-  hipLaunchKernelGGL((attn_evidence_kernel<EXPOSE, PAGED>), grid, block, 0, s, a.K, a.ctx_len, a.q_len, a.k_sb, a.k_sh,           \
+#define SFI_EVIDENCE_L(EXPOSE, PAGED, LINES)                                                                                     \
+  hipLaunchKernelGGL((attn_evidence_kernel<EXPOSE, PAGED, LINES>), grid, block, 0, s, a.K, a.ctx_len, a.q_len, a.k_sb, a.k_sh,    \
                      (uint32_t)a.k_st * 2u, a.n_sink, a.row_cap, a.len_cap, a)
+#define SFI_EVIDENCE(EXPOSE, PAGED)                          \
+  do {                                                       \
+    if (a.cached_rows > 0) SFI_EVIDENCE_L(EXPOSE, PAGED, true); \
+    else SFI_EVIDENCE_L(EXPOSE, PAGED, false);               \
+  } while (0)
   if (a.table != nullptr) {
     if (a.with_knorm) SFI_EVIDENCE(2, true);
     else SFI_EVIDENCE(1, true);
@@ -1436,6 +1497,7 @@ hipError_t launch_attn_evidence(const AttnArgs& a, int B, int n_slots, hipStream
     else SFI_EVIDENCE(1, false);
   }
 #undef SFI_EVIDENCE
+#undef SFI_EVIDENCE_L
   return hipGetLastError();
 }
 

@@ -32,6 +32,7 @@ constexpr int kHistBins = 512;     // bins of a segment's coarse key histogram (
 constexpr int kHistGroup = 64;      // segments whose histograms a launch of its own adds up ...
 constexpr int kHistGroupFrom = 128;  // ... of a J of more segments than this
 constexpr int kStateWords = 8;     // per (b, h) Selector state, see SelState
+constexpr int64_t kCacheBytes = (int64_t)288 << 20;  // 256 MB of last-level cache and eight L2s of 4 MB
 constexpr float kNeg = -1.0e30f;   // "minus infinity" that stays finite under subtraction
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -102,11 +103,13 @@ struct AttnArgs {
   int32_t ms, fs;                // strides of the per-sequence entries: ctx_len / recent_start in int32, is_slow in bytes
                                  //   (1, 1 for plain arrays; 4, 16 when they are fields of a packed sfi_step_desc array)
   int32_t plan_batch;            // dense mode: > 0 = the launch plans itself on the device (attn_dense_planned_kernel); the batch
+                                 //   (evidence mode with cached_rows: the sequences whose lengths add up to the launch's rows)
   int32_t plan_wgs, plan_min;    //   ... workgroups per KV head; fewest tiles a workgroup takes
   int32_t plan_even;             //   ... workgroups per pair if all sequences turn out equally long (0: do not look)
   int32_t* slow_list;            //   ... where the plan is left for the Selector's launches (see SelArgs), or nullptr
   int32_t* seq_rec;              //   ... records per query head of each sequence, [batch]
   const int32_t* q_len;          // dense and evidence mode, nullptr or: rows each sequence's query sees (window query under the causal mask)
+  int32_t cached_rows;           // evidence mode: 0 = all rows the launch may read fit the caches; else how many rows per head do
   const int32_t* recent_start;   // gather mode
   const int32_t* sel_idx;        // gather mode
   const int32_t* n_sel;          // gather mode

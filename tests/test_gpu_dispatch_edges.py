@@ -173,6 +173,56 @@ def test_evidence_at_the_edges_of_its_tiles(oracle, n_j, mode, G, page):
         r.close()
 
 
+# the evidence launch whose K may be larger than the caches (288 MB): whole-line requests, through the caches where the lengths say
+# that K fits after all (|J| around its tiles) and streamed where it does not; two heads share 294912 rows of two sequences
+@pytest.mark.parametrize("lens", [[69, 101], [196, 197], [581, 580], [1093, 8000], [295500, 295463]], ids=str)
+@pytest.mark.parametrize("mode,G,page", [(0, 1, 0), (1, 4, 0), (0, 16, 16), (1, 3, 64)])
+def test_evidence_of_a_k_beyond_the_caches(oracle, lens, mode, G, page):
+    import torch
+    import paper_2603_12038_amd as sfi
+    from helpers import i32_dev
+    print(f"[gpu-edges] evidence by whole lines: lens={lens} mode={mode} G={G} page={page}", flush=True)
+    B, Hkv, d, budget, max_ctx = 2, 2, 128, 65, 295552  # a multiple of 64 rows; K is 303 MB
+    gen = torch.Generator(device="cuda").manual_seed(sum(lens) + G)
+    L = -(-max(lens) // 64) * 64
+    K = torch.empty((B, Hkv, L, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    K.mul_((1 + 3 * (torch.rand(K.shape[:-1], generator=gen, device="cuda") < 0.01)).to(torch.bfloat16).unsqueeze(-1))
+    qs = torch.empty((2, B, Hkv * G, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    if page:
+        pages = max_ctx // page
+        table = torch.zeros((B, pages), dtype=torch.int32, device="cuda")  # (entries beyond the rows in use: any block)
+        n = L // page
+        table[:, :n] = torch.randperm(B * n, generator=gen, device="cuda").to(torch.int32).view(B, n)
+        pool = torch.empty((B * n, Hkv, page, d), dtype=torch.bfloat16, device="cuda")
+        pool[table[:, :n].long()] = K.view(B, Hkv, n, page, d).transpose(1, 2)
+    else:
+        pool = torch.zeros((B, Hkv, max_ctx, d), dtype=torch.bfloat16, device="cuda")
+        pool[:, :, :L] = K
+    sp = dataclasses.replace(SelectorParams(mode=mode), alpha=0.5)
+    sel_cfg = {k: getattr(sp, k) for k in ("gamma", "beta", "p", "eta", "lambda_clip", "alpha_soft", "alpha_cross", "temp", "eps",
+                                           "nms_radius")} if mode else None
+    ctx = sfi.SfiContext(B, Hkv * G, Hkv, max_ctx, budget, N_SINK, RECENT, pool, pool, selector=sel_cfg, alpha=0.5, page_size=page,
+                         page_layout="htd")
+    try:
+        if page:
+            sfi.sfi_set_block_table(ctx.handle, table, pool.shape[0])
+        c = i32_dev(lens)
+        bits = lambda t: t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+        q_all = np.stack([bits(q).reshape(B, Hkv, G, d) for q in qs], axis=2).reshape(B, 2 * Hkv * G, d)
+        sel_ref, nsel_ref, z = oracle.selector(q_all, bits(K), np.array(lens, np.int32), budget, N_SINK, RECENT, sp=sp)
+        for max_len in ((max_ctx,) if max(lens) > 10000 else (max_ctx, max(lens))):  # by whole lines, by the plain requests
+            sel = torch.full((B, Hkv, budget), -7, dtype=torch.int32, device="cuda")
+            nsel = torch.full((B, Hkv), -7, dtype=torch.int32, device="cuda")
+            for t in range(2):
+                sfi.sfi_evidence_add(ctx.handle, qs[t], pool, None, c, max_len, None, t == 0)
+            sfi.sfi_evidence_select(ctx.handle, 2, c, max(lens), budget, sel, nsel)
+            torch.cuda.synchronize()
+            check_selection(sel.cpu().numpy(), nsel.cpu().numpy(), sel_ref, nsel_ref, z, np.array(lens), N_SINK, RECENT, budget)
+        assert sfi.sfi_device_status(ctx.handle) == 0
+    finally:
+        ctx.close()
+
+
 # the hand-over of a split fast step: device scope (0), the L2 of one XCD (1), and workgroups taken for ones on different XCDs,
 # whose last wave does the list again (2); pairs in rows of eight and of a sequence, a row that is not full, heads that keep
 # device scope (3), bf16 outputs.  Each mode twice: the counters have to be back at zero.
