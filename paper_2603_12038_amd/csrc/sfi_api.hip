@@ -328,10 +328,20 @@ int handover_for(const sfi_ctx* x, int n_split, int slot_cap) {
 // Whether a ragged step's fast cells ride in its planned dense launch (attn_ragged_kernel): one per unit at most, and records
 // handed over as that kernel does it, if at all.  (The full Selector keeps two launches: the kernels are large, and
 // its three scoring launches leave less to gain.)
-bool one_ragged_launch(const sfi_ctx* x, const AttnArgs& f) {
+// One launch saves 2 to 4 us, but the shares no longer run at one pace: a workgroup whose cell belongs to a slow sequence is ahead by
+// a cell.  With many slow sequences (only the device knows how many) that costs a long launch 1 to 5 %.  So: cells of up to 24
+// tiles, and up to 384 tiles of dense work per unit if half of the sequences are slow.  Two launches / one, us a step with the
+// Selector behind it, 8 KV heads, G = 4 where not given, a quarter or a half slow: within the lines 12 x 16384..65536 rows (384 tiles), 18 tiles a cell, 120.2 /
+// 118.1 and 210.1 / 208.4; 32 x 4000..16000 (250), 20 a cell, 92.4 / 89.7 and 149.4 / 147.8.  Longer work: 32 x 16384..65536 (1024), G = 8, 12 a cell 310.7 /
+// 313.6 and 611 / 617; 16 x 16384..65536 (512), 18 a cell, 149.3 / 148.7 and 275.2 / 278.7.  Longer cells: 32 x 16384..65536, G = 8, 69 a cell 337 / 346 and 634 / 651;
+// 16 x 16384..49152 (384), 35 a cell, 131.7 / 132.2 and 226.1 / 231.2; 128 x 4096..16384 (256), 2 KV heads, 69 a cell, 120.9 / 127.5 a quarter slow.
+bool one_ragged_launch(const sfi_ctx* x, const AttnArgs& f, int max_len) {
   const int Hkv = x->cfg.n_kv_heads, row = f.handover == 0 || Hkv >= 8 ? Hkv : 8;
   const int cells = (x->cfg.batch * Hkv + row - 1) / row * row * f.n_split;
-  return x->cfg.selector_mode == 0 && cells <= x->n_cu && (f.n_split == 1 || f.handover != 0);
+  if (x->cfg.selector_mode != 0 || cells > x->n_cu || (f.n_split > 1 && f.handover == 0)) return false;
+  const int64_t fast_rows = std::min<int64_t>((int64_t)x->cfg.n_sink + f.sel_stride + x->cfg.recent, max_len);
+  const int64_t dense_rows = (int64_t)max_len * x->cfg.batch * Hkv / 2;
+  return fast_rows <= 24 * kTile * f.n_split && dense_rows <= (int64_t)384 * kTile * x->n_cu;
 }
 
 struct StageTimer {
@@ -1068,7 +1078,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   if (planned) d.slow_list = x->ws.slow_list;
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
-  if (planned && one_ragged_launch(x, f)) {
+  if (planned && one_ragged_launch(x, f, d.len_cap)) {
     StageTimer t(x, st, SFI_STAGE_ATTN);
     SFI_TRY(launch_attn_ragged(d, f, st));
     if (!t.stop()) return SFI_ELAUNCH;

@@ -294,3 +294,58 @@ def test_ragged_step_in_one_launch(oracle, B, Hkv, G, budget, page):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
+
+
+ATTN, ATTN2 = 0, 6  # stages whose launches are counted
+
+
+# One launch for cells of up to 24 tiles (768 rows with the sink and the recent window) and up to 384 tiles of dense work per unit
+# with half of the sequences slow (32 x 8 pairs on 256 units: 24576 rows); beyond either it is slower where many are slow.  All
+# heads share their rows; the selected rows are all of J, so that either kind of step is full attention.
+@pytest.mark.parametrize("budget,max_len,one", [(700, 24576, True), (701, 24576, False), (700, 24577, False)])
+@pytest.mark.parametrize("compact", [False, True])
+def test_ragged_step_of_long_cells_or_contexts(oracle, budget, max_len, one, compact):
+    import torch
+    import paper_2603_12038_amd as sfi
+    from helpers import i32_dev, to_dev
+    print(f"[gpu-edges] ragged step: budget {budget}, rows up to {max_len}, compact {compact}", flush=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are those of 256 compute units")
+    B, Hkv, G, d, L = 32, 8, 2, 128, 300
+    w = syn.make_tiny(L0=L, steps=1, budget=budget, recent=RECENT, n_support=4, B=1, Hq=G, Hkv=1, seed=9)
+    rows = torch.zeros((1, 1, 24640, d), dtype=torch.bfloat16, device="cuda").expand(B, Hkv, -1, -1), \
+        torch.zeros((1, 1, 24640, d), dtype=torch.bfloat16, device="cuda").expand(B, Hkv, -1, -1)
+    for pool, bits in zip(rows, (w.K, w.V)):
+        pool[0, 0, :L] = to_dev(bits)[0, 0, :L]
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q = torch.empty((B, Hkv * G, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    lens = np.array([L - 3 * i for i in range(B)], np.int32)
+    n_j = lens - RECENT - N_SINK
+    sel = np.full((B, Hkv, budget), -1, np.int32)
+    for b in range(B):
+        sel[b, :, :n_j[b]] = N_SINK + np.arange(n_j[b])
+    nsel = np.repeat(n_j[:, None], Hkv, axis=1)
+    flags = np.arange(B) % 4 == 1
+    ctx = sfi.SfiContext(B, Hkv * G, Hkv, 24640, budget, N_SINK, RECENT, *rows)
+    try:
+        c, sel_d, nsel_d = i32_dev(lens), i32_dev(sel), i32_dev(nsel)
+        out = torch.full((B, Hkv * G, d), float("nan"), device="cuda")
+        args = (ctx.handle, q, *rows, torch.from_numpy(flags.astype(np.uint8)).cuda(), c, i32_dev(lens - RECENT), max_len, budget, out, sel_d, nsel_d)
+        compact_rows = [torch.zeros((B, Hkv, N_SINK + budget, d), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        if compact:
+            sfi.sfi_reorg(ctx.handle, *rows, sel_d, nsel_d, budget, c, None, *compact_rows)
+        sfi.sfi_set_profiling(ctx.handle, 1)
+        if compact:
+            sfi.sfi_mixed_step_compact(*args, *compact_rows)
+        else:
+            sfi.sfi_mixed_step(*args)
+        count = sfi.sfi_stage_times(ctx.handle)[1]
+        assert (count[ATTN], count[ATTN2]) == (1, 0 if one else 1)
+        torch.cuda.synchronize()
+        bits = q.view(torch.int16).cpu().numpy().view(np.uint16)
+        K, V = (np.ascontiguousarray(np.broadcast_to(x[:, :, :L], (B, Hkv, L, d))) for x in (w.K, w.V))
+        check_out(out.cpu().numpy(), oracle.dense(bits, K, V, lens))
+        assert np.array_equal(sel_d.cpu().numpy(), sel) and np.array_equal(nsel_d.cpu().numpy(), nsel)
+        assert sfi.sfi_device_status(ctx.handle) == 0
+    finally:
+        ctx.close()
