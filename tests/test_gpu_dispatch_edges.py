@@ -254,11 +254,16 @@ def test_fast_step_hand_over(oracle, B, Hkv, G, page, bf16):
         r.close()
 
 
+ATTN, ATTN2 = 0, 6  # stages whose launches are counted
+
+
 # the ragged step's attention in one launch (up to one fast cell per unit) and in two (more, or records at device scope): none,
-# some and all sequences slow, both fast paths, every hand-over
-@pytest.mark.parametrize("B,Hkv,G,budget", [(32, 8, 2, 40), (33, 8, 1, 40), (4, 2, 9, 300), (3, 1, 4, 500), (2, 8, 16, 300), (5, 4, 5, 200)])
+# some and all sequences slow, both fast paths, every hand-over, rows of cells that are not full
+@pytest.mark.parametrize("B,Hkv,G,budget,one", [(32, 8, 2, 40, (0, 1, 2)), (33, 8, 1, 40, ()), (4, 2, 9, 300, (1, 2)), (3, 1, 4, 500, ()),
+                                                (3, 1, 4, 300, (1, 2)), (2, 2, 4, 300, (1, 2)), (2, 8, 16, 300, (1, 2)), (5, 4, 5, 200, ())])
 @pytest.mark.parametrize("page", [0, 16])
-def test_ragged_step_in_one_launch(oracle, B, Hkv, G, budget, page):
+def test_ragged_step_in_one_launch(oracle, B, Hkv, G, budget, one, page):
+    """one: the hand-overs with which the step is one launch."""
     import torch
     from helpers import i32_dev, to_dev
     print(f"[gpu-edges] ragged step: B={B} Hkv={Hkv} G={G} budget={budget} page={page}", flush=True)
@@ -267,23 +272,30 @@ def test_ragged_step_in_one_launch(oracle, B, Hkv, G, budget, page):
     try:
         q0, c0 = w.q(0), w.ctx_len(0)
         _, sel0, nsel0 = r.slow(q0, c0, budget, max_len=int(c0.max()))
-        q, c, rs = w.q(1), w.ctx_len(1), w.recent_start(1)
-        dense, sparse = oracle.dense(q, w.K, w.V, c), oracle.sparse(q, w.K, w.V, sel0, nsel0, rs, c, w.n_sink)
-        sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, budget, w.n_sink, w.recent)
+        c, rs = w.ctx_len(1), w.recent_start(1)
+        steps = []  # two queries in turn: a record of the step before is a wrong one
+        for q in (w.q(1), w.q(2)):
+            steps.append((q, oracle.dense(q, w.K, w.V, c), oracle.sparse(q, w.K, w.V, sel0, nsel0, rs, c, w.n_sink),
+                          oracle.selector(q, w.K, c, budget, w.n_sink, w.recent)))
         for slow in ([], [1], [0, B - 1], list(range(B))):
             flags = np.zeros(B, np.uint8)
             flags[slow] = 1
             for compact in (False, True):
-                for mode in (1, 2, 0):
+                for i, mode in enumerate((1, 2, 0)):
+                    q, dense, sparse, (sel_ref, nsel_ref, z) = steps[i % 2]
                     r.sfi.sfi_set_handover(r.ctx.handle, mode)
                     r.reorg(sel0, nsel0, c0)
                     sel, nsel = i32_dev(sel0), i32_dev(nsel0)
                     r.out.fill_(float("nan"))
                     args = (r.ctx.handle, to_dev(q), r.K, r.V, torch.from_numpy(flags).cuda(), i32_dev(c), i32_dev(rs), int(c.max()), budget, r.out, sel, nsel)
+                    r.sfi.sfi_set_profiling(r.ctx.handle, 1)
                     if compact:
                         r.sfi.sfi_mixed_step_compact(*args, r.Kc, r.Vc)
                     else:
                         r.sfi.sfi_mixed_step(*args)
+                    count = r.sfi.sfi_stage_times(r.ctx.handle)[1]
+                    r.sfi.sfi_set_profiling(r.ctx.handle, 0)
+                    assert (count[ATTN], count[ATTN2]) == (1, 0 if mode in one else 1)
                     torch.cuda.synchronize()
                     check_out(r.out.cpu().numpy(), np.where(flags[:, None, None] != 0, dense, sparse))
                     got, ngot = sel.cpu().numpy(), nsel.cpu().numpy()
@@ -294,9 +306,6 @@ def test_ragged_step_in_one_launch(oracle, B, Hkv, G, budget, page):
         assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
         r.close()
-
-
-ATTN, ATTN2 = 0, 6  # stages whose launches are counted
 
 
 # One launch for cells of up to 24 tiles (768 rows with the sink and the recent window) and up to 384 tiles of dense work per unit
