@@ -420,8 +420,9 @@ int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);
 /* A/B knob of the split fast-step launches (sfi_fast_step, sfi_fast_step_compact and the ragged steps), whose workgroups hand
  * partial results to one another.  mode = 1 (default): where the launch can deal all workgroups of a (sequence, KV head)
  * pair to one XCD, through that XCD's L2; a pair whose workgroups turn out to sit on different XCDs is computed again by
- * the last of them.  mode = 0: at device scope.  mode = 2: as 1, but every split pair is taken for one on different XCDs (for
- * tests).  Same results up to the order of the sums.  Other values: SFI_EINVAL. */
+ * the last of them.  mode = 0: at device scope; the same results as where mode 1 computes nothing again.  mode = 2 (for
+ * tests): the launches that mode 1 hands over through an L2 deal a pair's workgroups to different XCDs, so that every
+ * pair is computed again: the same results up to the order of the sums.  Other values: SFI_EINVAL. */
 int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
 
 /* Launch geometry the library would choose, without launching anything (host arithmetic only): split

@@ -498,15 +498,17 @@ __device__ __forceinline__ float2 load_record2(__amdgpu_buffer_rsrc_t r, int byt
 // Which cell a workgroup of a fast-step launch takes.  LOCAL: the grid is laid out so that all workgroups of a pair have the
 // same linear index modulo 8, and consecutive indices go round the eight XCDs: blockIdx = (pair in the row, slot, row) with
 // max(8, Hkv) pairs in a row.  shape: Hkv | log2 of the metadata stride << 16 | is_slow given << 20 |
-// log2 of the sequences in a row << 21 | log2 of Hkv, or 31 where a row is one sequence << 23 | pairs in a row that is not full, or 0 << 28.
+// log2 of the sequences in a row << 21 | log2 of Hkv, or 31 where a row is one sequence << 23 | pairs in a row that is not full, or 0 << 28
+// | (tests) the slots of a pair go to different XCDs << 31.
 struct FastCell {
   int slot, h, b;
   bool off;  // no pair behind this workgroup
 };
+__device__ __forceinline__ uint32_t apart_bits(uint32_t shape, uint32_t slot) { return (uint32_t)((int32_t)shape >> 31) & slot & 7u; }
 template <bool LOCAL>
 __device__ __forceinline__ FastCell fast_cell(uint32_t shape) {
   if (!LOCAL) return FastCell{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, false};
-  const uint32_t x = blockIdx.x, lg = (shape >> 23) & 31u, np = shape >> 28, q = x >> lg;
+  const uint32_t x = blockIdx.x ^ apart_bits(shape, blockIdx.y), lg = (shape >> 23) & 31u, np = (shape >> 28) & 7u, q = x >> lg;
   return FastCell{(int)blockIdx.y, (int)(x - (q << lg)), (int)((blockIdx.z << ((shape >> 21) & 3u)) + q), np != 0u && x >= np};
 }
 
@@ -518,7 +520,6 @@ struct WgOut {
   float* part;         // the records (with neither pointer above: a merge launch follows)
   int n_split, slot_cap;
   bool out_bf16;
-  bool apart;          // LOCAL, tests: take the workgroups for ones on different XCDs
 };
 __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
   WgOut o;
@@ -529,7 +530,6 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
   o.n_split = a.n_split;
   o.slot_cap = a.slot_cap;
   o.out_bf16 = a.out_bf16 != 0;
-  o.apart = a.handover == 2;
   return o;
 }
 // The way out of an attention workgroup: the four waves' partial results are combined through LDS and sent where WgOut
@@ -634,7 +634,7 @@ __device__ __forceinline__ bool finish_wg(const WgOut& o, int64_t head0, int G, 
   }
   if (JSTAT || o.out_merge == nullptr) return false;
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's record stores have been performed
-  const uint32_t xcd = !LOCAL ? 0u : o.apart ? (uint32_t)slot & 1u : __builtin_amdgcn_s_getreg(20 | 3 << 11);  // HW_REG_XCC_ID, 4 bits
+  const uint32_t xcd = LOCAL ? __builtin_amdgcn_s_getreg(20 | 3 << 11) : 0u;  // HW_REG_XCC_ID, 4 bits
   const uint32_t mine = 1u | xcd << 7 | (xcd * xcd) << 17;  // (at most 63 workgroups, XCDs 0 .. 15: no field overflows)
   uint32_t before = 0;
   if (lane == 0) before = __hip_atomic_fetch_add(o.arrive + w * kArriveStride, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1857,9 +1857,10 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
 static uint32_t fast_shape(const AttnArgs& a, int B) {
   const uint32_t meta = (uint32_t)a.Hkv | (a.ms == 4 ? 2u << 16 : 0u) | (a.is_slow != nullptr ? 1u << 20 : 0u);
   if (a.handover == 0) return meta;
-  if (a.Hkv >= 8) return meta | 31u << 23;
+  const uint32_t apart = a.handover == 2 ? 1u << 31 : 0u;
+  if (a.Hkv >= 8) return meta | apart | 31u << 23;
   const uint32_t lg = a.Hkv == 4 ? 2u : a.Hkv == 2 ? 1u : 0u;
-  return meta | (3u - lg) << 21 | lg << 23 | (B * a.Hkv < 8 ? (uint32_t)(B * a.Hkv) << 28 : 0u);
+  return meta | apart | (3u - lg) << 21 | lg << 23 | (B * a.Hkv < 8 ? (uint32_t)(B * a.Hkv) << 28 : 0u);
 }
 static dim3 fast_grid(const AttnArgs& a, int B, int n_slots) {
   if (a.handover == 0) return dim3(n_slots, a.Hkv, B);
@@ -2152,8 +2153,8 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int3
   __shared__ __align__(16) float s_patch[kWaves * patch_floats(1, true)];
   const uint32_t id = blockIdx.x, Hkv = shape & 0xffffu;
   // the cells in the order of fast_grid: row pairs side by side, n_split slots of them, then the next row
-  const uint32_t q = id / (uint32_t)row, z = q / (uint32_t)n_split, pair = z * row + (id - q * row);
-  const FastCell cell{(int)(q - z * n_split), (int)(pair % Hkv), (int)(pair / Hkv), false};
+  const uint32_t q = id / (uint32_t)row, z = q / (uint32_t)n_split, slot = q - z * n_split, pair = z * row + ((id - q * row) ^ apart_bits(shape, slot));
+  const FastCell cell{(int)slot, (int)(pair % Hkv), (int)(pair / Hkv), false};
   if (cell.b < B) {
     if (COMPACT) compact_body<PAGED, WIDE, true>(cell, f.Kc, f.Vc, is_slow, f.c_sb, f.c_sh, shape, f.c_rows, n_split, f, s_patch);
     else gather_body<PAGED, WIDE, true>(cell, sel_idx, f.n_sel, ctx_len, recent_start, is_slow, (uint32_t)f.sel_stride, shape, n_sink, n_split, f, s_patch);

@@ -127,7 +127,7 @@ struct AttnArgs {
   uint32_t* arrive;              //   pair's records into out_merge; arrive[((b * Hkv + h) * kWaves + w) * kArriveStride] counts the
                                  //   workgroups whose wave w is done (zero between launches)
   int32_t handover;              //   0: records at device scope; 1: the pair's workgroups on one XCD, records in its L2 (finish_wg);
-                                 //   2: as 1, but taken for workgroups on different XCDs
+                                 //   2: as 1, but the pair's workgroups are dealt to different XCDs
   const int32_t* table;          // paged cache: block table [B][table_stride], logical page -> block of the pool
   int64_t table_stride;
   int32_t page_lg;               // log2 of the page size in rows

@@ -223,31 +223,50 @@ def test_evidence_of_a_k_beyond_the_caches(oracle, lens, mode, G, page):
         ctx.close()
 
 
-# the hand-over of a split fast step: device scope (0), the L2 of one XCD (1), and workgroups taken for ones on different XCDs,
-# whose last wave does the list again (2); pairs in rows of eight and of a sequence, a row that is not full, heads that keep
-# device scope (3), bf16 outputs.  Each mode twice: the counters have to be back at zero.
-@pytest.mark.parametrize("B,Hkv,G", [(1, 8, 4), (4, 2, 4), (2, 4, 8), (8, 1, 5), (1, 2, 3), (3, 1, 16), (1, 16, 9), (2, 3, 4)])
+# the hand-over of a split fast step: device scope (0), the L2 of one XCD (1), and workgroups dealt to different XCDs, whose last
+# wave does the list again (2); pairs in rows of eight and of a sequence, a row that is not full, heads that keep
+# device scope (3, and 3 pairs with more than four workgroups), more records than the merge reads at a time, bf16 outputs.
+# Two queries in turn, so that a record of the launch before is a wrong one; the counters have to be back at zero each time.
+# Bits tell which way was taken: records merged are the same sums at either scope, a list done again is another order.
+@pytest.mark.parametrize("B,Hkv,G,L0,budget", [(1, 8, 4, 1500, 333), (4, 2, 4, 1500, 333), (2, 4, 8, 1500, 333), (8, 1, 5, 1500, 333),
+                                               (1, 2, 3, 1500, 333), (3, 1, 16, 1500, 333), (1, 16, 9, 1500, 333), (2, 3, 4, 1500, 333),
+                                               (3, 1, 4, 1500, 555), (1, 8, 4, 4200, 2600), (2, 4, 16, 4200, 2300)])
 @pytest.mark.parametrize("page", [0, 16])
 @pytest.mark.parametrize("bf16", [False, True])
-def test_fast_step_hand_over(oracle, B, Hkv, G, page, bf16):
+def test_fast_step_hand_over(oracle, B, Hkv, G, L0, budget, page, bf16):
     from helpers import check_out_bf16
-    print(f"[gpu-edges] hand-over: B={B} Hkv={Hkv} G={G} page={page} bf16={bf16}", flush=True)
-    w = _workload(B, Hkv, G, [1500 - 13 * i for i in range(B)], 333, seed=600 + G)
+    print(f"[gpu-edges] hand-over: B={B} Hkv={Hkv} G={G} budget={budget} page={page} bf16={bf16}", flush=True)
+    w = _workload(B, Hkv, G, [L0 - 13 * i for i in range(B)], budget, seed=600 + G)
     r = Runner(w, page_size=page, out_bf16=bf16)
     check = check_out_bf16 if bf16 else check_out
     try:
         q0, c0 = w.q(0), w.ctx_len(0)
         _, sel, nsel = r.slow(q0, c0, w.budget)
         r.reorg(sel, nsel, c0)
-        q, c, rs = w.q(1), w.ctx_len(1), w.recent_start(1)
-        want = oracle.sparse(q, w.K, w.V, sel, nsel, rs, c, w.n_sink)
-        for mode in (1, 2, 0, 2, 1):
-            r.sfi.sfi_set_handover(r.ctx.handle, mode)
-            for tiles_per_wave in (-1, 1):
-                r.sfi.sfi_set_tuning(r.ctx.handle, -1, tiles_per_wave, 1)
-                check(r.fast(q, sel, nsel, rs, c), want)
-                assert r.sfi.sfi_query_splits(r.ctx.handle)[1] > 1
-                check(r.fast_compact(q, nsel, sel.shape[2], rs, c), want)
+        qs, c, rs = [w.q(1), w.q(2)], w.ctx_len(1), w.recent_start(1)
+        want = [oracle.sparse(q, w.K, w.V, sel, nsel, rs, c, w.n_sink) for q in qs]
+        for tiles_per_wave in (-1, 1):
+            r.sfi.sfi_set_tuning(r.ctx.handle, -1, tiles_per_wave, 1)
+            got = {}
+            for i, mode in enumerate((0, 2, 1, 1, 2, 0)):
+                r.sfi.sfi_set_handover(r.ctx.handle, mode)
+                q = qs[i % 2]
+                fast = r.fast(q, sel, nsel, rs, c)
+                compact = r.fast_compact(q, nsel, sel.shape[2], rs, c)
+                check(fast, want[i % 2])
+                check(compact, want[i % 2])
+                got.setdefault(mode, {})[i % 2] = (fast, compact)
+            splits = r.sfi.sfi_query_splits(r.ctx.handle)[1]
+            assert splits > (16 if budget > 2000 and tiles_per_wave == 1 else 1)
+            through_l2 = Hkv % 8 == 0 or (Hkv in (1, 2, 4) and (B * Hkv % 8 == 0 or (B * Hkv < 8 and splits <= 4)))
+            for t in range(2):
+                for path in range(2):
+                    at = [got[m][t][path] for m in (0, 1, 2)]
+                    assert np.array_equal(at[0], at[1]), "records merged, nothing done again"
+                    if not through_l2:
+                        assert np.array_equal(at[0], at[2])
+                    elif not bf16:
+                        assert not np.array_equal(at[0], at[2]), "the list done again by one wave"
         with pytest.raises(RuntimeError):
             r.sfi.sfi_set_handover(r.ctx.handle, 3)
     finally:
