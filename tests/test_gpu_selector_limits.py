@@ -1,5 +1,6 @@
 """GPU parity of the Selector at the limits of its inputs: logits whose exponentials overflow, head groups between the built
-ones, tie classes and threshold bins of the long form, and windows large enough for the launch planned on the device.
+ones, tie classes and threshold bins of the long form, and windows over more rows than a unit's first shares hold, as evidence
+alone and with the queries' outputs (the dense launch planned on the device).
 Against the fp64 oracle with the library's own bars, as in the other parity tests."""
 import dataclasses
 
@@ -30,8 +31,8 @@ def _check_slow(oracle, w, r, sp, q, **bars):
     return sel, nsel
 
 
-def _check_window(oracle, w, r, sp, queries, **bars):
-    """Evidence of the queries of the last rows (causal, no output), then the index set."""
+def _check_window(oracle, w, r, sp, queries, with_out=False, **bars):
+    """Evidence of the queries of the last rows (causal), and their outputs if asked for, then the index set."""
     import torch
     B, Hkv, G, W = w.B, w.Hkv, w.Hq // w.Hkv, len(queries)
     c = w.ctx_len(0)
@@ -41,8 +42,13 @@ def _check_window(oracle, w, r, sp, queries, **bars):
     vis = np.empty((B, Hkv, W, G), np.int32)
     for t, q in enumerate(queries):
         q_len = np.maximum(c - W + t + 1, 0).astype(np.int32)
-        r.sfi.sfi_evidence_add_causal(r.ctx.handle, to_dev(q), r.K, None, c_d, i32_dev(q_len), max_len, None, t == 0)
+        r.out.fill_(float("nan"))
+        r.sfi.sfi_evidence_add_causal(r.ctx.handle, to_dev(q), r.K, r.V if with_out else None, c_d, i32_dev(q_len), max_len,
+                                      r.out if with_out else None, t == 0)
         vis[:, :, t] = q_len[:, None, None]
+        if with_out:
+            torch.cuda.synchronize()
+            check_out(r.out.cpu().numpy(), oracle.dense(q, w.K, w.V, q_len))
     r.sfi.sfi_evidence_select(r.ctx.handle, W, c_d, max_len, w.budget, sel, nsel)
     torch.cuda.synchronize()
     q_all = np.stack([q.reshape(B, Hkv, G, w.d) for q in queries], axis=2).reshape(B, Hkv * W * G, w.d)
@@ -132,17 +138,20 @@ def test_long_form_threshold_below_the_histograms_range(oracle, budget):
         r.close()
 
 
-# 8 sequences of 8 KV heads and 8200 rows at most: 16 workgroups per pair, eight tiles a wave
+# 8 sequences of 8 KV heads and 8200 rows at most.  Without an output: 16 workgroups per pair, four tiles a wave.  With one: 16
+# tiles per wave of every unit, twice what the dense launch planned on the device asks for; it guesses equal lengths, which
+# then has to hold for the rows that the query sees as well.
 @pytest.mark.parametrize("lens", [[8200, 6000, 7777, 5001, 8199, 4100, 7001, 8000], [8200] * 8], ids=["unequal", "equal"])
 @pytest.mark.parametrize("page", [0, 16])
 @pytest.mark.parametrize("mode", [0, 1])
-def test_planned_launch_that_leaves_evidence_only(oracle, mode, page, lens):
-    print(f"[gpu-limits] planned evidence-only launch: mode {mode}, page {page}, {lens}", flush=True)
+@pytest.mark.parametrize("with_out", [False, True], ids=["evidence", "out"])
+def test_window_of_many_tiles(oracle, with_out, mode, page, lens):
+    print(f"[gpu-limits] window of many tiles: with_out {with_out}, mode {mode}, page {page}, {lens}", flush=True)
     w = _workload(8, 8, 2, lens, 129, seed=300)
     sp, d = _selector(mode)
     r = Runner(w, selector=d, alpha=1.0, page_size=page)
     try:
-        _check_window(oracle, w, r, sp, [w.q(t) for t in range(3)])
+        _check_window(oracle, w, r, sp, [w.q(t) for t in range(3)], with_out)
     finally:
         r.close()
 
