@@ -109,7 +109,6 @@ struct AttnArgs {
   int32_t* slow_list;            //   ... where the plan is left for the Selector's launches (see SelArgs), or nullptr
   int32_t* seq_rec;              //   ... records per query head of each sequence, [batch]
   const int32_t* q_len;          // dense and evidence mode, nullptr or: rows each sequence's query sees (window query under the causal mask)
-  int32_t cached_rows;           // evidence mode: 0 = all rows the launch may read fit the caches; else how many rows per head do
   const int32_t* recent_start;   // gather mode
   const int32_t* sel_idx;        // gather mode
   const int32_t* n_sel;          // gather mode
@@ -118,6 +117,7 @@ struct AttnArgs {
   float* part;
   int32_t slot_cap;              // gather / compact mode: records each query head has room for in part (kSlotCap in a
                                  //   caller's workspace)
+  int32_t cached_rows;           // evidence mode: 0 = all rows the launch may read fit the caches; else how many rows per head do
   float* logits;                 // dense mode, nullptr: do not expose logits
   int32_t with_knorm;            // dense mode: also expose the squared key norms (full Selector)
   int32_t dense_wide;            // dense mode: K rows read as whole 128-byte lines (query groups of at most 8 heads, flat cache)
