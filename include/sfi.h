@@ -422,7 +422,7 @@ int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);
  * pair to one XCD, through that XCD's L2; a pair whose workgroups turn out to sit on different XCDs is computed again by
  * the last of them.  mode = 0: at device scope; the same results as where mode 1 computes nothing again.  mode = 2 (for
  * tests): the launches that mode 1 hands over through an L2 deal a pair's workgroups to different XCDs, so that every
- * pair is computed again: the same results up to the order of the sums.  Other values: SFI_EINVAL. */
+ * pair is computed again (more than eight KV heads: as mode 0): the same results up to the order of the sums.  Other values: SFI_EINVAL. */
 int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
 
 /* Launch geometry the library would choose, without launching anything (host arithmetic only): split

@@ -322,7 +322,7 @@ int handover_for(const sfi_ctx* x, int n_split, int slot_cap) {
   const int Hkv = x->cfg.n_kv_heads, pairs = x->cfg.batch * Hkv;
   if (x->handover == 0 || n_split < 2 || n_split >= slot_cap) return 0;
   const bool even = Hkv % 8 == 0 || ((Hkv == 4 || Hkv == 2 || Hkv == 1) && (pairs % 8 == 0 || (pairs < 8 && n_split <= 4)));
-  return even ? x->handover : 0;
+  return even && (x->handover != 2 || Hkv <= 8) ? x->handover : 0;
 }
 
 // Whether a ragged step's fast cells ride in its planned dense launch (attn_ragged_kernel): one per unit at most, and records

@@ -498,17 +498,16 @@ __device__ __forceinline__ float2 load_record2(__amdgpu_buffer_rsrc_t r, int byt
 // Which cell a workgroup of a fast-step launch takes.  LOCAL: the grid is laid out so that all workgroups of a pair have the
 // same linear index modulo 8, and consecutive indices go round the eight XCDs: blockIdx = (pair in the row, slot, row) with
 // max(8, Hkv) pairs in a row.  shape: Hkv | log2 of the metadata stride << 16 | is_slow given << 20 |
-// log2 of the sequences in a row << 21 | log2 of Hkv, or 31 where a row is one sequence << 23 | pairs in a row that is not full, or 0 << 28
-// | (tests) the slots of a pair go to different XCDs << 31.
+// log2 of the sequences in a row << 21 | log2 of Hkv, or 31 where a row is one sequence << 23 | pairs in a row that is not full, or 0 << 28.
+// (Tests: a ninth workgroup to each row of eight, without a pair, sends a pair's slots to different XCDs.)
 struct FastCell {
   int slot, h, b;
   bool off;  // no pair behind this workgroup
 };
-__device__ __forceinline__ uint32_t apart_bits(uint32_t shape, uint32_t slot) { return (uint32_t)((int32_t)shape >> 31) & slot & 7u; }
 template <bool LOCAL>
 __device__ __forceinline__ FastCell fast_cell(uint32_t shape) {
   if (!LOCAL) return FastCell{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, false};
-  const uint32_t x = blockIdx.x ^ apart_bits(shape, blockIdx.y), lg = (shape >> 23) & 31u, np = (shape >> 28) & 7u, q = x >> lg;
+  const uint32_t x = blockIdx.x, lg = (shape >> 23) & 31u, np = shape >> 28, q = x >> lg;
   return FastCell{(int)blockIdx.y, (int)(x - (q << lg)), (int)((blockIdx.z << ((shape >> 21) & 3u)) + q), np != 0u && x >= np};
 }
 
@@ -1857,15 +1856,15 @@ __global__ __launch_bounds__(kAttnThreads, BURST ? 1 : 3) void attn_gather_floor
 static uint32_t fast_shape(const AttnArgs& a, int B) {
   const uint32_t meta = (uint32_t)a.Hkv | (a.ms == 4 ? 2u << 16 : 0u) | (a.is_slow != nullptr ? 1u << 20 : 0u);
   if (a.handover == 0) return meta;
-  const uint32_t apart = a.handover == 2 ? 1u << 31 : 0u;
-  if (a.Hkv >= 8) return meta | apart | 31u << 23;
+  const uint32_t full = a.handover == 2 ? 8u << 28 : 0u;
+  if (a.Hkv >= 8) return meta | 31u << 23 | full;
   const uint32_t lg = a.Hkv == 4 ? 2u : a.Hkv == 2 ? 1u : 0u;
-  return meta | apart | (3u - lg) << 21 | lg << 23 | (B * a.Hkv < 8 ? (uint32_t)(B * a.Hkv) << 28 : 0u);
+  return meta | (3u - lg) << 21 | lg << 23 | (B * a.Hkv < 8 ? (uint32_t)(B * a.Hkv) << 28 : full);
 }
 static dim3 fast_grid(const AttnArgs& a, int B, int n_slots) {
   if (a.handover == 0) return dim3(n_slots, a.Hkv, B);
   const int row = a.Hkv >= 8 ? a.Hkv : 8;
-  return dim3(row, n_slots, (B * a.Hkv + row - 1) / row);
+  return dim3(row + (a.handover == 2 ? 1 : 0), n_slots, (B * a.Hkv + row - 1) / row);
 }
 static const uint8_t* gather_flags(const AttnArgs& a) {  // (a readable byte in any case)
   return a.is_slow != nullptr ? a.is_slow : reinterpret_cast<const uint8_t*>(a.ctx_len);
@@ -2149,11 +2148,13 @@ template <bool PAGED, bool WIDE, bool COMPACT>
 __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* recent_start,
                                                                       const int32_t* sel_idx, const uint32_t strides, const uint32_t shape, const int B,
                                                                       const int W_max, const int n_sink, const int n_split, const float per_min,
-                                                                      const int row, const AttnArgs f, const AttnArgs d) {
+                                                                      const int row_in, const AttnArgs f, const AttnArgs d) {
   __shared__ __align__(16) float s_patch[kWaves * patch_floats(1, true)];
   const uint32_t id = blockIdx.x, Hkv = shape & 0xffffu;
-  // the cells in the order of fast_grid: row pairs side by side, n_split slots of them, then the next row
-  const uint32_t q = id / (uint32_t)row, z = q / (uint32_t)n_split, slot = q - z * n_split, pair = z * row + ((id - q * row) ^ apart_bits(shape, slot));
+  // the cells in the order of fast_grid: row pairs side by side, n_split slots of them, then the next row.  row_in: the pairs in a
+  // row, negative (tests): which of them a workgroup has changes from slot to slot, and with it the XCD of a pair's slots.
+  const uint32_t row = abs(row_in), q = id / row, z = q / (uint32_t)n_split, slot = q - z * n_split;
+  const uint32_t pair = z * row + ((id - q * row) ^ (row_in < 0 ? slot & 7u : 0u));
   const FastCell cell{(int)slot, (int)(pair % Hkv), (int)(pair / Hkv), false};
   if (cell.b < B) {
     if (COMPACT) compact_body<PAGED, WIDE, true>(cell, f.Kc, f.Vc, is_slow, f.c_sb, f.c_sh, shape, f.c_rows, n_split, f, s_patch);
@@ -2349,13 +2350,13 @@ hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t 
 }
 hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, hipStream_t s) {
   const int B = d.plan_batch;
-  const dim3 g = fast_grid(f, B, f.n_split);
-  const dim3 grid(std::max((unsigned)(d.plan_wgs * d.Hkv), g.x * g.y * g.z)), block(kAttnThreads);
+  const int row = f.handover == 0 || f.Hkv >= 8 ? f.Hkv : 8;  // as fast_grid
+  const int cells = (B * f.Hkv + row - 1) / row * row * f.n_split;
+  const dim3 grid(std::max(d.plan_wgs * d.Hkv, cells)), block(kAttnThreads);
   const uint32_t strides = (uint32_t)d.ms | (uint32_t)d.fs << 16;
-  const int row = f.handover == 0 ? f.Hkv : (int)g.x;
 #define SFI_RAGGED(PAGED, WIDE, COMPACT)                                                                                                         \
   hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start, f.sel_idx, strides, \
-                     fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min, row, f, d)
+                     fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min, f.handover == 2 ? -row : row, f, d)
 #define SFI_RAGGED_C(PAGED, COMPACT)                  \
   do {                                                \
     if (f.G <= 8) SFI_RAGGED(PAGED, true, COMPACT);   \

@@ -225,7 +225,7 @@ def test_evidence_of_a_k_beyond_the_caches(oracle, lens, mode, G, page):
 
 # the hand-over of a split fast step: device scope (0), the L2 of one XCD (1), and workgroups dealt to different XCDs, whose last
 # wave does the list again (2); pairs in rows of eight and of a sequence, a row that is not full, heads that keep
-# device scope (3, and 3 pairs with more than four workgroups), more records than the merge reads at a time, bf16 outputs.
+# device scope (3, and 3 pairs with more than four workgroups; with 16, mode 2 does as well), more records than the merge reads at a time, bf16 outputs.
 # Two queries in turn, so that a record of the launch before is a wrong one; the counters have to be back at zero each time.
 # Bits tell which way was taken: records merged are the same sums at either scope, a list done again is another order.
 @pytest.mark.parametrize("B,Hkv,G,L0,budget", [(1, 8, 4, 1500, 333), (4, 2, 4, 1500, 333), (2, 4, 8, 1500, 333), (8, 1, 5, 1500, 333),
@@ -258,7 +258,7 @@ def test_fast_step_hand_over(oracle, B, Hkv, G, L0, budget, page, bf16):
                 got.setdefault(mode, {})[i % 2] = (fast, compact)
             splits = r.sfi.sfi_query_splits(r.ctx.handle)[1]
             assert splits > (16 if budget > 2000 and tiles_per_wave == 1 else 1)
-            through_l2 = Hkv % 8 == 0 or (Hkv in (1, 2, 4) and (B * Hkv % 8 == 0 or (B * Hkv < 8 and splits <= 4)))
+            through_l2 = Hkv == 8 or (Hkv in (1, 2, 4) and (B * Hkv % 8 == 0 or (B * Hkv < 8 and splits <= 4)))
             for t in range(2):
                 for path in range(2):
                     at = [got[m][t][path] for m in (0, 1, 2)]
