@@ -263,7 +263,7 @@ def bench_serving(args):
         us2 = [ms2[i] / max(cnt2[i], 1) * 1e3 for i in range(len(ms2))]
         rows = int(L_p[fl != 0].sum()) + (int(fast_rows[fl == 0].sum()) if one_launch else 0)
         attn_bytes = rows * Hkv * d * 2 * 2
-        by_slow.append({"slow_sequences": len(which), "dense_kv_bytes": attn_bytes, "dense_us": us2[0],
+        by_slow.append({"slow_sequences": len(which), "fast_rows_in_dense_launch": one_launch, "dense_kv_bytes": attn_bytes, "dense_us": us2[0],
                         "dense_frac_of_8TBps": attn_bytes / (us2[0] * 1e-6) / 1e9 / HBM_PEAK_GBS if attn_bytes else None,
                         "gather_us": None if one_launch else us2[6], "score_us": us2[2], "cand_us": us2[3], "write_us": us2[5]})
     fast_bytes = int(fast_rows.sum()) * Hkv * d * 2 * 2
@@ -281,7 +281,7 @@ def bench_serving(args):
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": fast_gbs / HBM_PEAK_GBS, "traffic": None,
                      "algorithmic_bytes_per_launch": fast_bytes, "us_per_launch": gather_us},
         "whole_run_kv_GBps": kv / wall / 1e9, "whole_run_frac_of_8TBps": kv / wall / 1e9 / HBM_PEAK_GBS,
-        "all_fast_step_stage_us": {"gather": gather_us, "merge": ms[1] / max(cnt[1], 1) * 1e3},
+        "all_fast_step_stage_us": {"ragged" if one_launch else "gather": gather_us, "merge": ms[1] / max(cnt[1], 1) * 1e3},
         "ragged_step_by_slow_sequences": by_slow,
         "us_per_decode_step_per_layer": wall * 1e6 / (n_t * NL),
         "parity_sample": parity,

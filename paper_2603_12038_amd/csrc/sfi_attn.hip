@@ -551,7 +551,8 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
 // record loads take a trip to the L2 instead of one to memory.  That the workgroups did meet on one XCD is not assumed:
 // the counter, which stays at device scope, adds up their XCDs x and x^2 beside their number n, and n sum x^2 = (sum x)^2
 // holds only if all x are the same.  If it does not, the records cannot be read; the function returns true, and the wave does
-// the pair's whole list again for its heads.  Device scope / LOCAL, us a layer: 4096 rows, 2 KV heads 5.54 / 5.25; 4 x 32768 rows, 8 KV
+// the pair's whole list again for its heads.  That is no path to be on (4 x 32768 rows 10.1 -> 146 us a layer, 131072 8.6 -> 271: one
+// wave, tile by tile): it is there for a dealing of workgroups other than round robin, which has not been seen.  Device scope / LOCAL, us a layer: 4096 rows, 2 KV heads 5.54 / 5.25; 4 x 32768 rows, 8 KV
 // heads, budget 2048 10.55 / 10.28; 131072 rows, 8 KV heads, budget 4096 9.03 / 8.63; 8 sequences of 20011..24571 rows, G = 5, paged, budget 1024
 // 12.29 / 11.85; 12 x 32768 rows, budget 1000 14.55 / 13.68; 8 x 32768 rows, one KV head, budget 2000 9.03 / 8.34.  (With the counter in the L2 as
 // well another 1 %, but then workgroups on different XCDs would not find one another.)
@@ -2003,7 +2004,9 @@ hipError_t launch_attn_dense_floor(const AttnArgs& a, int B, int n_slots, int wi
 // index is read: a wave's first tile is on its way before any scalar of the step has arrived.
 // Tiles never straddle the two segments: the compact segment ends with a ragged tile of its own.
 // ------------------------------------------------------------------------------------------------
-// What the first tile's rows need arrives in registers, and the flag of a ragged step is looked at behind their requests.
+// What the first tile's rows need arrives in registers, the flag of a ragged step is looked at behind their requests, and the last
+// tile is not refilled: us a layer, 8 KV heads, at device scope 15.31 -> 15.15 (12 x 5003..30011 rows, budget 1024), 11.92 -> 11.75 (4 x 32768, 2048),
+// 10.49 -> 9.78 (131072, 4096); records through the L2 14.92, 11.63, 9.66.
 template <bool PAGED, bool WIDE, bool LOCAL>  // PAGED: the recent window is read from a paged cache (the compact buffers are always flat)
 __device__ __forceinline__ void compact_body(const FastCell& cell, const uint16_t* Kc, const uint16_t* Vc, const uint8_t* is_slow_p,
                                              const int64_t c_sb, const int64_t c_sh, const uint32_t shape, const int c_rows, const int n_split,
@@ -2138,10 +2141,9 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
 // launch less, the start of the dense part and the hand-over of the fast part hide behind each other, and a workgroup whose
 // cell belongs to a slow sequence begins its share at once.  (The other order gains half of that: the cell's first loads
 // wait for the acknowledgement of the share's last stores.)
-// Two launches / one, us a step with the Selector behind it: 12 x 5003..30011 rows, budget 1024, 1 slow, compact buffers 53.2 / 51.1; 32 x 16384..65536
-// rows, G = 8, budget 2048, none slow 59.3 / 57.8, 1 103.0 / 99.9, 2 132.9 / 130.5, 4 195.8 / 196.0, 8 337.4 / 346.1 (a quarter slow: their
-// cells' workgroups are done early); 2 x 5003..30011, 1 slow 48.4 / 45.2; 8 x 3000..8000, G = 16, 1 slow 40.5 / 37.1; 64 x 1000..3000, 2 KV heads, 3 slow
-// 34.5 / 31.1.
+// Two launches / one, us a step with the Selector behind it: 12 x 5003..30011 rows, budget 1024, compact buffers, 1 slow 53.6 / 50.7, 4 slow 93.2 / 90.2; 8 x
+// 20011..24571, G = 5, paged, 1 slow 48.1 / 44.6; 4 x 5515..14434, G = 8, 1 slow 38.2 / 35.4; 64 x 1000..3000, 2 KV heads, 3 slow 25.0 / 22.2, 16 slow 29.8 / 27.4.
+// With long cells or long shares it is the slower one where many sequences are slow: one_ragged_launch.
 // With more cells than shares the fast part loses the two other workgroups a unit would hold: 128 x 3000..8000 rows 128 / 136.
 // ------------------------------------------------------------------------------------------------
 template <bool PAGED, bool WIDE, bool COMPACT>
