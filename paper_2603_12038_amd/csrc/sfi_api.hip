@@ -328,20 +328,26 @@ int handover_for(const sfi_ctx* x, int n_split, int slot_cap) {
 // Whether a ragged step's fast cells ride in its planned dense launch (attn_ragged_kernel): one per unit at most, and records
 // handed over as that kernel does it, if at all.  (The full Selector keeps two launches: the kernels are large, and
 // its three scoring launches leave less to gain.)
-// One launch saves 2 to 4 us, but the shares no longer run at one pace: a workgroup whose cell belongs to a slow sequence is ahead by
-// a cell.  With many slow sequences (only the device knows how many) that costs a long launch 1 to 5 %.  So: cells of up to 24
-// tiles, and up to 384 tiles of dense work per unit if half of the sequences are slow.  Two launches / one, us a step with the
-// Selector behind it, 8 KV heads, G = 4 where not given, a quarter or a half slow: within the lines 12 x 16384..65536 rows (384 tiles), 18 tiles a cell, 120.2 /
-// 118.1 and 210.1 / 208.4; 32 x 4000..16000 (250), 20 a cell, 92.4 / 89.7 and 149.4 / 147.8.  Longer work: 32 x 16384..65536 (1024), G = 8, 12 a cell 310.7 /
-// 313.6 and 611 / 617; 16 x 16384..65536 (512), 18 a cell, 149.3 / 148.7 and 275.2 / 278.7.  Longer cells: 32 x 16384..65536, G = 8, 69 a cell 337 / 346 and 634 / 651;
-// 16 x 16384..49152 (384), 35 a cell, 131.7 / 132.2 and 226.1 / 231.2; 128 x 4096..16384 (256), 2 KV heads, 69 a cell, 120.9 / 127.5 a quarter slow.
-bool one_ragged_launch(const sfi_ctx* x, const AttnArgs& f, int max_len) {
+bool one_ragged_launch(const sfi_ctx* x, const AttnArgs& f) {
   const int Hkv = x->cfg.n_kv_heads, row = f.handover == 0 || Hkv >= 8 ? Hkv : 8;
   const int cells = (x->cfg.batch * Hkv + row - 1) / row * row * f.n_split;
-  if (x->cfg.selector_mode != 0 || cells > x->n_cu || (f.n_split > 1 && f.handover == 0)) return false;
+  return x->cfg.selector_mode == 0 && cells <= x->n_cu && (f.n_split == 1 || f.handover != 0);
+}
+// Whether that launch's dense shares are cut by what a workgroup has had already.  A workgroup whose cell belongs to a slow
+// sequence is ahead of the others by a cell; only the device knows how many are.  Planning for it costs every step about 1 us,
+// so it is done for cells of more than 24 tiles, and for more than 384 tiles of dense work per unit if half of the sequences are slow.
+// Two launches / equal shares / by what was had, us a step with the Selector behind it, 8 KV heads and G = 4 where not given:
+//   16 x 16384..65536 rows (512), 67 tiles a cell, 1 slow 94.9 / 91.2 / 91.2, 4 slow 172.8 / 176.8 / 168.4, 8 slow 295.4 / 300.0 / 291.4
+//   128 x 4096..16384 (256), 2 KV heads, 69 a cell, 1 slow 72.8 / 69.5 / 70.8, 32 slow 122.2 / 126.6 / 119.7, 64 slow 187.5 / 187.0 / 182.2
+//   16 x 16384..49152 (384), 35 a cell, 1 slow 67.3 / 64.5 / 65.2, 4 slow 133.0 / 132.2 / 128.2, 8 slow 226.6 / 228.0 / 219.5
+//   32 x 16384..65536 (1024), G = 8, 69 a cell, 1 slow 99.4 / 97.0 / 96.2, 2 slow 127.4 / 126.2 / 125.6, 4 slow 193.7 / 194.8 / 193.4, 8 slow 338.3 / 347.0 / 344.0,
+//     16 slow 635.7 / 650.9 / 645.1 (with eight heads and a quarter or more slow two launches stay 1 to 2 % ahead, so with 16 x 32768 rows, 8 slow, 236.8 / 241.3 / 242.4)
+//   within the lines: 12 x 5003..30011 (176), 18 a cell, compact buffers, two layers, 1 slow 107.1 / 101.7 / 102.9, 4 slow 186.3 / 181.3 / 174.7; 64 x 1000..3000 (47),
+//     2 KV heads, 10 a cell, 3 slow 25.0 / 22.1 / 24.1
+bool balanced_shares(const sfi_ctx* x, const AttnArgs& f, int max_len) {
   const int64_t fast_rows = std::min<int64_t>((int64_t)x->cfg.n_sink + f.sel_stride + x->cfg.recent, max_len);
-  const int64_t dense_rows = (int64_t)max_len * x->cfg.batch * Hkv / 2;
-  return fast_rows <= 24 * kTile * f.n_split && dense_rows <= (int64_t)384 * kTile * x->n_cu;
+  const int64_t dense_rows = (int64_t)max_len * x->cfg.batch * x->cfg.n_kv_heads / 2;
+  return fast_rows > 24 * kTile * f.n_split || dense_rows > (int64_t)384 * kTile * x->n_cu;
 }
 
 struct StageTimer {
@@ -1078,9 +1084,9 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   if (planned) d.slow_list = x->ws.slow_list;
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
-  if (planned && one_ragged_launch(x, f, d.len_cap)) {
+  if (planned && one_ragged_launch(x, f)) {
     StageTimer t(x, st, SFI_STAGE_ATTN);
-    SFI_TRY(launch_attn_ragged(d, f, st));
+    SFI_TRY(launch_attn_ragged(d, f, balanced_shares(x, f, d.len_cap), st));
     if (!t.stop()) return SFI_ELAUNCH;
   } else {
     {

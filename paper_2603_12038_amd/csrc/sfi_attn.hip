@@ -1068,25 +1068,55 @@ __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(c
 struct PlanArgs {
   int W, n_on, total;
   float scale;
-  int h;  // half a border's gap, in positions; also how far a border moves
+  int h;          // half a border's gap, in positions; also how far a border moves
+  int n_a, s_b;   // CELLS: workgroups with a whole share of 1 << kShareLg positions, and the share of the others, which follow
 };
 constexpr int kShareLg = 10;
 constexpr float kCross = 5.f;
+// Where workgroup w's share begins, and whose share position x is in.
+template <bool CELLS>
+__device__ __forceinline__ int share_start(const PlanArgs& p, int w) {
+  return !CELLS || w <= p.n_a ? w << kShareLg : (p.n_a << kShareLg) + (w - p.n_a) * p.s_b;
+}
+template <bool CELLS>
+__device__ __forceinline__ int share_of(const PlanArgs& p, int x) {
+  const int y = x - (p.n_a << kShareLg);
+  if (!CELLS || y < 0) return x >> kShareLg;
+  int w = (int)((float)y * __builtin_amdgcn_rcpf((float)p.s_b));
+  w -= w * p.s_b > y;
+  w += (w + 1) * p.s_b <= y;
+  return p.n_a + w;
+}
 // Position of the border in front of sequence `rank` with P tiles before it; off: the gap on either side of it.
+template <bool CELLS>
 __device__ __forceinline__ int plan_border(const PlanArgs& p, int P, int rank, int& off) {
   int x = (int)((float)P * p.scale) + rank;
-  const int f = x & ((1 << kShareLg) - 1), up = (1 << kShareLg) - f;
-  off = f > p.h && up > p.h ? p.h : 0;
-  x += f <= p.h ? -f : up <= p.h ? up : 0;
+  const int w = share_of<CELLS>(p, x);
+  const int f = x - share_start<CELLS>(p, w), up = share_start<CELLS>(p, w + 1) - x;
+  const int h = CELLS && w >= p.n_a ? min(p.h, p.s_b >> 2) : p.h;
+  off = f > h && up > h ? h : 0;
+  x += f <= h ? -f : up <= h ? up : 0;
   if (P == 0) x = 0, off = 0;
-  if (P == p.total) x = p.W << kShareLg, off = 0;
+  if (P == p.total) x = share_start<CELLS>(p, p.W), off = 0;
   return x;
 }
+// CELLS: the launch also has the ragged step's fast cells (attn_ragged_kernel), each as much work as `tiles` of this list's
+// tiles.  Which workgroups have one follows from the flags; where there are enough without one, a workgroup that has had a cell
+// takes that much less, so that all do the same in all.  There are then two sizes of shares, the whole ones first.  A
+// sequence on both sides of the line between them is interleaved on each side by itself.  Where that
+// takes less than kLeastGain tiles off the longest, the shares stay equal (32 x 8192 rows, one slow, 64.4 us a step, with two sizes 66.0; a
+// line at 8 tiles: 16 x 16384..49152, 4 slow, 128.5 -> 132.9).
+constexpr float kLeastGain = 4.f;
+struct PlanCells {
+  int n_split, row_lg;  // cells of a pair; log2 of the sequences whose cells alternate (fast_cell)
+  float tiles;
+  int L0, on0;          // length and flag of this lane's first sequence, requested in front of the cell's work
+};
 // GUESS: the workgroup requests its first rows on the guess that all sequences are equally long (a.plan_even).
-template <int EXPOSE, bool PAGED, bool GUESS>
-__device__ __forceinline__ void planned_body(const int j, const int h, const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
+template <int EXPOSE, bool PAGED, bool GUESS, bool CELLS = false>
+__device__ __forceinline__ void planned_body(int j, int h, const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
                                              uint32_t strides, int B, int W_max, float per_min, int n_sink, int recent_in, int len_cap,
-                                             const AttnArgs& a, float* lds) {
+                                             const AttnArgs& a, float* lds, const PlanCells cells = {}) {
   const int lane = threadIdx.x & 63;
   const int ms = strides & 0xffff, fs = strides >> 16;
   // rows seen, recent window seen and tiles of sequence b (at least one tile: an empty context has a record too)
@@ -1109,9 +1139,9 @@ __device__ __forceinline__ void planned_body(const int j, const int h, const int
     return tiles_of(b, bc, L_in, is_slow == nullptr || is_slow[bc * fs] != 0, L);
   };
   const int b0 = lane * per, bc0 = min(b0, B - 1);
-  int L0 = ctx_len[bc0 * ms];
-  int on0 = 1;
-  if (is_slow != nullptr) on0 = is_slow[bc0 * fs];
+  int L0 = CELLS ? cells.L0 : ctx_len[bc0 * ms];
+  int on0 = CELLS ? cells.on0 : 1;
+  if (!CELLS && is_slow != nullptr) on0 = is_slow[bc0 * fs];
   __builtin_amdgcn_sched_barrier(0);
   // the guess: this workgroup's place if all sequences are equally long
   const int even = GUESS ? a.plan_even : 0;
@@ -1155,24 +1185,63 @@ __device__ __forceinline__ void planned_body(const int j, const int h, const int
     dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b_even, T, lds);
     return;
   }
+  if (CELLS) {
+    // above the sequences that take part (10 bits): this head's workgroups with a fast cell (10), those in front of this one
+    // (10), and whether this is one (a launch has at most 256 cells; cells of a sequence lie 1 << row_lg workgroups apart)
+    const int apart = 1 << cells.row_lg;
+    for (int i = 0; i < per; ++i) {
+      const int b = b0 + i, z = (b >> cells.row_lg) * (cells.n_split << cells.row_lg) + (b & (apart - 1));
+      auto cells_below = [&](int w) { return min(max((w - z + apart - 1) >> cells.row_lg, 0), cells.n_split); };
+      const int before = cells_below(j), here = cells_below(j + 1) - before;
+      int L_in = L0, L;
+      const int t = i == 0 ? t0 : lane_seq(i, L_in, L);
+      count += b < B && t == 0 ? cells_below(W_max) << 10 | before << 20 | here << 30 : 0;
+    }
+  }
   const int inc_t = (int)wave_incl_scan((uint32_t)tiles), inc_c = (int)wave_incl_scan((uint32_t)count);
   PlanArgs p;
   p.total = __builtin_amdgcn_readlane(inc_t, 63);
-  p.n_on = __builtin_amdgcn_readlane(inc_c, 63);
+  const uint32_t counts = __builtin_amdgcn_readlane(inc_c, 63);
+  p.n_on = CELLS ? counts & 1023u : counts;
   if (a.slow_list != nullptr && h == 0 && j == 0 && threadIdx.x == 0) a.slow_list[0] = p.n_on;
   p.W = max(1, min(W_max, (int)((float)p.total * per_min)));
-  if (j >= p.W || p.total == 0) return;
-  p.scale = (float)((p.W << kShareLg) - p.n_on) * __builtin_amdgcn_rcpf((float)p.total) * 0.999999f;
+  if (p.total == 0) return;
+  p.n_a = p.W;
+  p.s_b = 1 << kShareLg;
+  if (CELLS) {
+    const int n_fast = (counts >> 10) & 1023u, fast_before = (counts >> 20) & 1023u, n_whole = W_max - n_fast;
+    const bool fast = counts >> 30;
+    // (a workgroup with a cell does cells.tiles * n_whole / W_max less than with equal shares)
+    if (n_fast > 0 && cells.tiles * (float)n_whole > kLeastGain * (float)W_max) {
+      // Smaller shares are at least plan_min tiles (and what the rounding of their size may take) and 1/16 of a whole one.
+      const float t = (float)p.total, least_b = fmaxf(1.0625f * __builtin_amdgcn_rcpf(per_min) + 1.f, cells.tiles * (1.f / 15.f));
+      const float over = t - (float)n_whole * cells.tiles;
+      const int n_b = max(0, min(n_fast, (int)(over * __builtin_amdgcn_rcpf(least_b)) - n_whole));
+      p.n_a = max(1, min(n_whole, (int)(t * per_min)));
+      p.W = p.n_a + n_b;
+      const float whole = (t + (float)n_b * cells.tiles) * __builtin_amdgcn_rcpf((float)p.W);
+      if (n_b > 0) p.s_b = (int)((float)(1 << kShareLg) * (1.f - cells.tiles * __builtin_amdgcn_rcpf(whole)));
+      j = fast ? p.n_a + fast_before : j - fast_before;
+      if (!fast && j >= p.n_a) return;
+    } else if (n_fast == 0) {  // head after head, as without cells (32 x 16384..65536 rows, G = 8: 1279 -> 1256 us a step)
+      const int i = j * a.Hkv + h;
+      h = i / W_max;
+      j = i - h * W_max;
+    }
+  }
+  if (j >= p.W) return;
+  p.scale = (float)(share_start<CELLS>(p, p.W) - p.n_on) * __builtin_amdgcn_rcpf((float)p.total) * 0.999999f;
   p.h = -wave_max(-least) * p.scale > 2.f * kCross * p.scale + 8.f ? min((int)(0.5f * kCross * p.scale) + 1, 1 << (kShareLg - 2)) : 0;
-  const int start = j << kShareLg;
+  const int start = share_start<CELLS>(p, j);
   // the sequence at the share's start
   int before = inc_t - tiles, rank = inc_c - count;  // tiles, sequences in front of this lane's
+  if (CELLS) rank &= 1023;
   int hit_i = -1, hit_P = 0, hit_rank = 0, hit_L = 0;
   for (int i = 0; i < per; ++i) {
     int L_in = L0;
     int off, L;
     const int t = i == 0 ? t0 : lane_seq(i, L_in, L);
-    if (t > 0 && plan_border(p, before, rank, off) <= start && start < plan_border(p, before + t, rank + 1, off)) {
+    if (t > 0 && plan_border<CELLS>(p, before, rank, off) <= start && start < plan_border<CELLS>(p, before + t, rank + 1, off)) {
       hit_i = i;
       hit_P = before;
       hit_rank = rank;
@@ -1189,17 +1258,23 @@ __device__ __forceinline__ void planned_body(const int j, const int h, const int
     sh.bad = 0;
     const int t_b = view_of(b, L_in, sh.L, sh.recent, sh.bad);
     int g0, g1;
-    const int x0 = plan_border(p, P, r, g0), x1 = plan_border(p, P + t_b, r + 1, g1);
-    const int w0 = __builtin_amdgcn_readfirstlane(x0 >> kShareLg), w1 = __builtin_amdgcn_readfirstlane((x1 - 1) >> kShareLg);
+    const int x0 = plan_border<CELLS>(p, P, r, g0), x1 = plan_border<CELLS>(p, P + t_b, r + 1, g1);
+    const int w0 = __builtin_amdgcn_readfirstlane(share_of<CELLS>(p, x0)), w1 = __builtin_amdgcn_readfirstlane(share_of<CELLS>(p, x1 - 1));
     sh.slot = j - w0;
     sh.n_rec = w1 - w0 + 1;
     // the tiles of the first workgroup and those in front of the last one, where they share with another sequence
     const int lo = x0 + g0, hi = x1 - g1;
     const float f = (float)t_b * __builtin_amdgcn_rcpf((float)(hi - lo));
-    const bool part0 = w1 > w0 && (x0 & ((1 << kShareLg) - 1)) != 0, part1 = w1 > w0 && (x1 & ((1 << kShareLg) - 1)) != 0;
-    const int A = part0 ? min(t_b, (int)((float)(((w0 + 1) << kShareLg) - lo) * f)) : 0;
-    const int Z = part1 ? min(t_b, (int)((float)((w1 << kShareLg) - lo) * f)) : t_b;
-    const int n_full = sh.n_rec - part0 - part1;
+    const bool part0 = w1 > w0 && x0 != share_start<CELLS>(p, w0), part1 = w1 > w0 && x1 != share_start<CELLS>(p, w1 + 1);
+    auto tiles_to = [&](int w) { return min(t_b, (int)((float)(share_start<CELLS>(p, w) - lo) * f)); };  // in front of workgroup w's share
+    const int A = part0 ? tiles_to(w0 + 1) : 0;
+    const int Z = part1 ? tiles_to(w1) : t_b;
+    // the workgroups that interleave with this one, and their tiles
+    int full0 = w0 + part0, full1 = w1 + 1 - part1, a0 = A, z0 = Z;
+    if (CELLS && full0 < p.n_a && p.n_a < full1) {
+      if (j < p.n_a) full1 = p.n_a, z0 = tiles_to(p.n_a);
+      else full0 = p.n_a, a0 = tiles_to(p.n_a);
+    }
     int first, step = kWaves, end;
     if (part0 && sh.slot == 0) {
       first = 0;
@@ -1208,9 +1283,9 @@ __device__ __forceinline__ void planned_body(const int j, const int h, const int
       first = Z;
       end = t_b;
     } else {
-      first = A + (sh.slot - part0) * kWaves;
-      step = n_full * kWaves;
-      end = Z;
+      first = a0 + (j - full0) * kWaves;
+      step = (full1 - full0) * kWaves;
+      end = z0;
     }
     sh.first = __builtin_amdgcn_readfirstlane(first);
     sh.step = __builtin_amdgcn_readfirstlane(step);
@@ -1227,7 +1302,7 @@ __device__ __forceinline__ void planned_body(const int j, const int h, const int
     sh.have_k = false;
     dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b, T, lds, zero);
     P += t_b;
-    if (__builtin_amdgcn_readfirstlane(x1) >= start + (1 << kShareLg)) return;
+    if (__builtin_amdgcn_readfirstlane(x1) >= share_start<CELLS>(p, j + 1)) return;
     do {  // (there is one: the list goes on)
       ++b;
     } while (is_slow != nullptr && is_slow[b * fs] == 0);
@@ -2143,14 +2218,15 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
 // wait for the acknowledgement of the share's last stores.)
 // Two launches / one, us a step with the Selector behind it: 12 x 5003..30011 rows, budget 1024, compact buffers, 1 slow 53.6 / 50.7, 4 slow 93.2 / 90.2; 8 x
 // 20011..24571, G = 5, paged, 1 slow 48.1 / 44.6; 4 x 5515..14434, G = 8, 1 slow 38.2 / 35.4; 64 x 1000..3000, 2 KV heads, 3 slow 25.0 / 22.2, 16 slow 29.8 / 27.4.
-// With long cells or long shares it is the slower one where many sequences are slow: one_ragged_launch.
 // With more cells than shares the fast part loses the two other workgroups a unit would hold: 128 x 3000..8000 rows 128 / 136.
 // ------------------------------------------------------------------------------------------------
-template <bool PAGED, bool WIDE, bool COMPACT>
+// BALANCED (balanced_shares): the shares are cut by what a workgroup has had already (PlanCells).  For that every head has to have
+// workgroups with a cell in the same places: the heads' shares alternate as the cells do.
+template <bool PAGED, bool WIDE, bool COMPACT, bool BALANCED>
 __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* recent_start,
                                                                       const int32_t* sel_idx, const uint32_t strides, const uint32_t shape, const int B,
                                                                       const int W_max, const int n_sink, const int n_split, const float per_min,
-                                                                      const int row_in, const AttnArgs f, const AttnArgs d) {
+                                                                      const int row_in, const float cell_tiles, const AttnArgs f, const AttnArgs d) {
   __shared__ __align__(16) float s_patch[kWaves * patch_floats(1, true)];
   const uint32_t id = blockIdx.x, Hkv = shape & 0xffffu;
   // the cells in the order of fast_grid: row pairs side by side, n_split slots of them, then the next row.  row_in: the pairs in a
@@ -2158,14 +2234,19 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int3
   const uint32_t row = abs(row_in), q = id / row, z = q / (uint32_t)n_split, slot = q - z * n_split;
   const uint32_t pair = z * row + ((id - q * row) ^ (row_in < 0 ? slot & 7u : 0u));
   const FastCell cell{(int)slot, (int)(pair % Hkv), (int)(pair / Hkv), false};
+  const int j = BALANCED ? id / Hkv : id % (uint32_t)W_max, h = BALANCED ? id % Hkv : id / (uint32_t)W_max;
+  PlanCells cells;
+  if (BALANCED) {
+    const int bc0 = min((int)(threadIdx.x & 63) * ((B + 63) / 64), B - 1);
+    cells = PlanCells{n_split, (int)((shape >> 21) & 3u), cell_tiles, ctx_len[bc0 * (int)(strides & 0xffffu)], is_slow[bc0 * (int)(strides >> 16)]};
+  }
   if (cell.b < B) {
     if (COMPACT) compact_body<PAGED, WIDE, true>(cell, f.Kc, f.Vc, is_slow, f.c_sb, f.c_sh, shape, f.c_rows, n_split, f, s_patch);
     else gather_body<PAGED, WIDE, true>(cell, sel_idx, f.n_sel, ctx_len, recent_start, is_slow, (uint32_t)f.sel_stride, shape, n_sink, n_split, f, s_patch);
   }
   __syncthreads();  // the cell's results in LDS have been read
   if (id < (uint32_t)W_max * Hkv)
-    planned_body<1, PAGED, false>(id % (uint32_t)W_max, id / (uint32_t)W_max, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent,
-                                  d.len_cap, d, s_patch);
+    planned_body<1, PAGED, false, BALANCED>(j, h, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent, d.len_cap, d, s_patch, cells);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2350,19 +2431,25 @@ hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t 
   else launch_dense_t<false>(a, grid, s);
   return hipGetLastError();
 }
-hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, hipStream_t s) {
+hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, bool balanced, hipStream_t s) {
   const int B = d.plan_batch;
   const int row = f.handover == 0 || f.Hkv >= 8 ? f.Hkv : 8;  // as fast_grid
   const int cells = (B * f.Hkv + row - 1) / row * row * f.n_split;
   const dim3 grid(std::max(d.plan_wgs * d.Hkv, cells)), block(kAttnThreads);
   const uint32_t strides = (uint32_t)d.ms | (uint32_t)d.fs << 16;
-#define SFI_RAGGED(PAGED, WIDE, COMPACT)                                                                                                         \
-  hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start, f.sel_idx, strides, \
-                     fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min, f.handover == 2 ? -row : row, f, d)
-#define SFI_RAGGED_C(PAGED, COMPACT)                  \
-  do {                                                \
-    if (f.G <= 8) SFI_RAGGED(PAGED, true, COMPACT);   \
-    else SFI_RAGGED(PAGED, false, COMPACT);           \
+  // A cell's tile takes less than the list's, whose logits are exposed.  (0.8 / 0.9, us a step: 32 x 8192 rows, half slow, 125.1 / 131.2; 16 x
+  // 16384..49152, half slow, 219.5 / 222.2; 16 x 16384..65536, budget 1024, a quarter slow, 148.5 / 146.0.)
+  const float cell_tiles = 0.8f * std::min((float)f.n_sink + (float)f.sel_stride + (float)f.recent, (float)d.len_cap) / (float)(kTile * f.n_split);
+#define SFI_RAGGED(PAGED, WIDE, COMPACT, BALANCED)                                                                                                 \
+  hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT, BALANCED>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start, f.sel_idx,     \
+                     strides, fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min, f.handover == 2 ? -row : row,       \
+                     cell_tiles, f, d)
+#define SFI_RAGGED_C(PAGED, COMPACT)                                   \
+  do {                                                                 \
+    if (f.G <= 8 && balanced) SFI_RAGGED(PAGED, true, COMPACT, true);  \
+    else if (f.G <= 8) SFI_RAGGED(PAGED, true, COMPACT, false);        \
+    else if (balanced) SFI_RAGGED(PAGED, false, COMPACT, true);        \
+    else SFI_RAGGED(PAGED, false, COMPACT, false);                     \
   } while (0)
   if (d.table != nullptr && f.Kc != nullptr) SFI_RAGGED_C(true, true);
   else if (d.table != nullptr) SFI_RAGGED_C(true, false);

@@ -327,53 +327,52 @@ def test_ragged_step_in_one_launch(oracle, B, Hkv, G, budget, one, page):
         r.close()
 
 
-# One launch for cells of up to 24 tiles (768 rows with the sink and the recent window) and up to 384 tiles of dense work per unit
-# with half of the sequences slow (32 x 8 pairs on 256 units: 24576 rows); beyond either it is slower where many are slow.  All
-# heads share their rows; the selected rows are all of J, so that either kind of step is full attention.
-@pytest.mark.parametrize("budget,max_len,one", [(700, 24576, True), (701, 24576, False), (700, 24577, False)])
-@pytest.mark.parametrize("compact", [False, True])
-def test_ragged_step_of_long_cells_or_contexts(oracle, budget, max_len, one, compact):
+# Cells of more than 24 tiles (768 rows with the sink and the recent window): the dense shares are cut by what a workgroup has had
+# already.  None, one, a quarter, half, all but one and all sequences slow: equal shares, one size of shares (the cells are more
+# work than the list has for their workgroups) and two sizes, with lists that cross sequences on either side.  Several
+# cells a pair by force (tiles per wave), in rows that are full and not; more sequences than lanes.
+@pytest.mark.parametrize("B,Hkv,G,lo,hi,budget,tiles_per_wave", [(32, 8, 2, 1100, 1400, 800, -1), (16, 8, 4, 900, 3000, 850, 9), (4, 2, 9, 2000, 5000, 1800, 8),
+                                                                 (3, 1, 4, 3000, 6000, 2600, 8), (5, 3, 1, 1500, 3500, 900, 9), (100, 2, 5, 850, 1200, 800, 9)])
+@pytest.mark.parametrize("page", [0, 16])
+def test_ragged_step_of_long_cells(oracle, B, Hkv, G, lo, hi, budget, tiles_per_wave, page):
     import torch
-    import paper_2603_12038_amd as sfi
     from helpers import i32_dev, to_dev
-    print(f"[gpu-edges] ragged step: budget {budget}, rows up to {max_len}, compact {compact}", flush=True)
-    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
-        pytest.skip("the sizes are those of 256 compute units")
-    B, Hkv, G, d, L = 32, 8, 2, 128, 300
-    w = syn.make_tiny(L0=L, steps=1, budget=budget, recent=RECENT, n_support=4, B=1, Hq=G, Hkv=1, seed=9)
-    rows = torch.zeros((1, 1, 24640, d), dtype=torch.bfloat16, device="cuda").expand(B, Hkv, -1, -1), \
-        torch.zeros((1, 1, 24640, d), dtype=torch.bfloat16, device="cuda").expand(B, Hkv, -1, -1)
-    for pool, bits in zip(rows, (w.K, w.V)):
-        pool[0, 0, :L] = to_dev(bits)[0, 0, :L]
-    gen = torch.Generator(device="cuda").manual_seed(7)
-    q = torch.empty((B, Hkv * G, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
-    lens = np.array([L - 3 * i for i in range(B)], np.int32)
-    n_j = lens - RECENT - N_SINK
-    sel = np.full((B, Hkv, budget), -1, np.int32)
-    for b in range(B):
-        sel[b, :, :n_j[b]] = N_SINK + np.arange(n_j[b])
-    nsel = np.repeat(n_j[:, None], Hkv, axis=1)
-    flags = np.arange(B) % 4 == 1
-    ctx = sfi.SfiContext(B, Hkv * G, Hkv, 24640, budget, N_SINK, RECENT, *rows)
+    print(f"[gpu-edges] ragged step, long cells: B={B} Hkv={Hkv} G={G} rows {lo}..{hi} budget={budget} page={page}", flush=True)
+    w = _workload(B, Hkv, G, [lo + (hi - lo) * (7 * i % B) // B for i in range(B)], budget, seed=2000 + B)
+    r = Runner(w, page_size=page)
     try:
-        c, sel_d, nsel_d = i32_dev(lens), i32_dev(sel), i32_dev(nsel)
-        out = torch.full((B, Hkv * G, d), float("nan"), device="cuda")
-        args = (ctx.handle, q, *rows, torch.from_numpy(flags.astype(np.uint8)).cuda(), c, i32_dev(lens - RECENT), max_len, budget, out, sel_d, nsel_d)
-        compact_rows = [torch.zeros((B, Hkv, N_SINK + budget, d), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
-        if compact:
-            sfi.sfi_reorg(ctx.handle, *rows, sel_d, nsel_d, budget, c, None, *compact_rows)
-        sfi.sfi_set_profiling(ctx.handle, 1)
-        if compact:
-            sfi.sfi_mixed_step_compact(*args, *compact_rows)
-        else:
-            sfi.sfi_mixed_step(*args)
-        count = sfi.sfi_stage_times(ctx.handle)[1]
-        assert (count[ATTN], count[ATTN2]) == (1, 0 if one else 1)
-        torch.cuda.synchronize()
-        bits = q.view(torch.int16).cpu().numpy().view(np.uint16)
-        K, V = (np.ascontiguousarray(np.broadcast_to(x[:, :, :L], (B, Hkv, L, d))) for x in (w.K, w.V))
-        check_out(out.cpu().numpy(), oracle.dense(bits, K, V, lens))
-        assert np.array_equal(sel_d.cpu().numpy(), sel) and np.array_equal(nsel_d.cpu().numpy(), nsel)
-        assert sfi.sfi_device_status(ctx.handle) == 0
+        q0, c0 = w.q(0), w.ctx_len(0)
+        _, sel0, nsel0 = r.slow(q0, c0, budget, max_len=int(c0.max()))
+        q, c, rs = w.q(1), w.ctx_len(1), w.recent_start(1)
+        dense, sparse = oracle.dense(q, w.K, w.V, c), oracle.sparse(q, w.K, w.V, sel0, nsel0, rs, c, w.n_sink)
+        sel_ref, nsel_ref, z = oracle.selector(q, w.K, c, budget, w.n_sink, w.recent)
+        r.sfi.sfi_set_tuning(r.ctx.handle, -1, tiles_per_wave, 1)
+        every = list(range(B))
+        for slow in ([], [1], every[::4], every[1::2], every[1:], every):
+            flags = np.zeros(B, np.uint8)
+            flags[slow] = 1
+            for compact in (False, True):
+                r.reorg(sel0, nsel0, c0)
+                sel, nsel = i32_dev(sel0), i32_dev(nsel0)
+                r.out.fill_(float("nan"))
+                args = (r.ctx.handle, to_dev(q), r.K, r.V, torch.from_numpy(flags).cuda(), i32_dev(c), i32_dev(rs), int(c.max()), budget, r.out, sel, nsel)
+                r.sfi.sfi_set_profiling(r.ctx.handle, 1)
+                if compact:
+                    r.sfi.sfi_mixed_step_compact(*args, r.Kc, r.Vc)
+                else:
+                    r.sfi.sfi_mixed_step(*args)
+                count = r.sfi.sfi_stage_times(r.ctx.handle)[1]
+                r.sfi.sfi_set_profiling(r.ctx.handle, 0)
+                splits = r.sfi.sfi_query_splits(r.ctx.handle)[1]
+                assert (count[ATTN], count[ATTN2]) == (1, 0) and N_SINK + budget + RECENT > 24 * 32 * splits
+                torch.cuda.synchronize()
+                check_out(r.out.cpu().numpy(), np.where(flags[:, None, None] != 0, dense, sparse))
+                got, ngot = sel.cpu().numpy(), nsel.cpu().numpy()
+                keep = flags == 0
+                assert (got[keep] == sel0[keep]).all() and (ngot[keep] == nsel0[keep]).all()
+                on = flags != 0
+                if on.any():
+                    check_selection(got[on], ngot[on], sel_ref[on], nsel_ref[on], z[on], c[on], w.n_sink, w.recent, budget)
+        assert r.sfi.sfi_device_status(r.ctx.handle) == 0
     finally:
-        ctx.close()
+        r.close()
