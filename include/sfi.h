@@ -412,7 +412,7 @@ int sfi_set_dense_k_layout(sfi_ctx* ctx, int32_t whole_lines);
  * workgroup per compute unit; every wave derives the same plan from the flags and lengths -- per KV head, the tiles of
  * the slow sequences laid end to end and cut into one equal share per workgroup, which may reach into several
  * sequences -- so the shares are equal whatever the mix (batches of 2 to 1024 sequences, and only where the fast
- * step's merge runs inside its kernel; otherwise as with on = 0).  on = 0: one workgroup per (split, KV head, sequence)
+ * step's merge runs inside its kernel; otherwise as with on = 0).  on = 0: one workgroup per (KV head, split, sequence)
  * cell of the whole batch with the finest split (a batch of one: the slow step's split); workgroups of fast sequences
  * exit at once.  Same results.  Other values: SFI_EINVAL. */
 int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);

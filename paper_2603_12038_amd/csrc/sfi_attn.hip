@@ -1040,13 +1040,15 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
                                EXPOSE != 0 ? rows_sum(l_j) : 0.f);
   report_guard(a.guard, bad);
 }
-// One workgroup per (split, KV head, sequence) cell: wave w of split s takes tiles 4 s + w, 4 (s + n_split) + w, ...
+// One workgroup per (KV head, split, sequence) cell: wave w of split s takes tiles 4 s + w, 4 (s + n_split) + w, ...
+// The head is the grid's first index here and in the planned launch, for the Selector's sake (Place in sfi_select.hip); by itself the order is worth
+// little (16 x 16384 rows, dense alone, splits first 158.1 us, heads first 156.9).
 template <int EXPOSE, bool PAGED, bool BIG = false, bool WIDE = false>
 __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(const AttnArgs a) {
-  const DenseShare sh{(int)blockIdx.x * kWaves, a.n_split * kWaves, 0, (int)blockIdx.x, a.n_split, 0, 0, 0, false};
+  const DenseShare sh{(int)blockIdx.y * kWaves, a.n_split * kWaves, 0, (int)blockIdx.y, a.n_split, 0, 0, 0, false};
   __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, BIG)];
   Tile T;
-  dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.y, blockIdx.z, T, s_patch);
+  dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.x, blockIdx.z, T, s_patch);
 }
 // The launch planned on the device: more than one sequence, every one with a length of its own (which only the device
 // knows) and, in the ragged step (sfi_mixed_step*), only some of them slow.  With a workgroup per cell the shares follow the
@@ -1316,7 +1318,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
                                                                              uint32_t strides, int B, int W_max, float per_min, int n_sink,
                                                                              int recent_in, int len_cap, const AttnArgs a) {
   __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, true)];
-  planned_body<EXPOSE, PAGED, true>(blockIdx.x, blockIdx.y, ctx_len, is_slow, q_len, strides, B, W_max, per_min, n_sink, recent_in, len_cap, a,
+  planned_body<EXPOSE, PAGED, true>(blockIdx.y, blockIdx.x, ctx_len, is_slow, q_len, strides, B, W_max, per_min, n_sink, recent_in, len_cap, a,
                                     s_patch);
 }
 
@@ -1341,6 +1343,8 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
 // tiles lie a workgroup's stride apart: as neighbours (16 KB in one piece per wave) they take 13 % longer.
 // Against the dense kernel without its V half, which this replaces, us per query with the accumulation behind it, 8 KV heads: 2 sequences of
 // 12000..16384 rows with norms 19.9 -> 17.0; 2 x 4096 11.7 -> 9.6; 8 x 8000..16000 51.7 -> 42.6; 1 x 130000 54.6 -> 45.1.
+// With the head as the first index of both launches, so that the accumulation finds the logits in its L2, on another box: 15.86 -> 15.52, 7.85 -> 7.45,
+// 41.3 -> 39.4, 48.8 -> 48.4; 32 x 512..4000, two heads a group 34.2 -> 31.2.
 // ------------------------------------------------------------------------------------------------
 constexpr int kEvidenceStash = 2432;  // floats of logits a wave parks in LDS: four tiles of 16 heads and norms, 15 of 4 heads and norms
 struct KPair {    // two tiles of K: tile hf is blocks 2 hf and 2 hf + 1
@@ -1370,7 +1374,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
   typedef typename RowOff<PAGED>::type OffT;
   __shared__ __align__(16) float s_stash[kWaves][kEvidenceStash];
   __shared__ __align__(16) float s_m[16][kWaves], s_l[16][kWaves];
-  const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int h = blockIdx.x, slot = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int jg = lane >> 4, n = lane & 15;
   const char* const Kb = reinterpret_cast<const char*>(K + b * k_sb + h * k_sh);
@@ -1555,7 +1559,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_evidence_kernel(const ui
   report_guard(a.guard, bad);
 }
 hipError_t launch_attn_evidence(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
-  const dim3 grid(n_slots, a.Hkv, B), block(kAttnThreads);
+  const dim3 grid(a.Hkv, n_slots, B), block(kAttnThreads);  // heads first: Place in sfi_select.hip
 #define SFI_EVIDENCE_L(EXPOSE, PAGED, LINES)                                                                                     \
   hipLaunchKernelGGL((attn_evidence_kernel<EXPOSE, PAGED, LINES>), grid, block, 0, s, a.K, a.ctx_len, a.q_len, a.k_sb, a.k_sh,    \
                      (uint32_t)a.k_st * 2u, a.n_sink, a.row_cap, a.len_cap, a)
@@ -1991,7 +1995,7 @@ __device__ __forceinline__ void idle(int units) {
 }
 template <bool WIDE>
 __global__ __launch_bounds__(kAttnThreads + 64, 1) void attn_dense_floor_kernel(const AttnArgs a, int idle_units, int writer) {
-  const int slot = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int slot = blockIdx.y, h = blockIdx.x, b = blockIdx.z;
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
   const int jg = lane >> 4, n = lane & 15;
@@ -2065,7 +2069,7 @@ __global__ __launch_bounds__(kAttnThreads + 64, 1) void attn_dense_floor_kernel(
   if (lane == 0) reinterpret_cast<uint32_t*>(a.part)[((head0 * kSlotCap + slot) * kPartStride) + w] = fold;
 }
 hipError_t launch_attn_dense_floor(const AttnArgs& a, int B, int n_slots, int wide, int idle_units, int writer, hipStream_t s) {
-  const dim3 grid(n_slots, a.Hkv, B);
+  const dim3 grid(a.Hkv, n_slots, B);
   const dim3 block(writer != 0 ? kAttnThreads + 64 : kAttnThreads);
   if (wide) hipLaunchKernelGGL(attn_dense_floor_kernel<true>, grid, block, 0, s, a, idle_units, writer);
   else hipLaunchKernelGGL(attn_dense_floor_kernel<false>, grid, block, 0, s, a, idle_units, writer);
@@ -2220,8 +2224,8 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
 // 20011..24571, G = 5, paged, 1 slow 48.1 / 44.6; 4 x 5515..14434, G = 8, 1 slow 38.2 / 35.4; 64 x 1000..3000, 2 KV heads, 3 slow 25.0 / 22.2, 16 slow 29.8 / 27.4.
 // With more cells than shares the fast part loses the two other workgroups a unit would hold: 128 x 3000..8000 rows 128 / 136.
 // ------------------------------------------------------------------------------------------------
-// BALANCED (balanced_shares): the shares are cut by what a workgroup has had already (PlanCells).  For that every head has to have
-// workgroups with a cell in the same places: the heads' shares alternate as the cells do.
+// BALANCED (balanced_shares): the shares are cut by what a workgroup has had already (PlanCells).  (Every head has its
+// workgroups with a cell in the same places: the heads' shares alternate as the cells do.)
 template <bool PAGED, bool WIDE, bool COMPACT, bool BALANCED>
 __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* recent_start,
                                                                       const int32_t* sel_idx, const uint32_t strides, const uint32_t shape, const int B,
@@ -2234,7 +2238,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int3
   const uint32_t row = abs(row_in), q = id / row, z = q / (uint32_t)n_split, slot = q - z * n_split;
   const uint32_t pair = z * row + ((id - q * row) ^ (row_in < 0 ? slot & 7u : 0u));
   const FastCell cell{(int)slot, (int)(pair % Hkv), (int)(pair / Hkv), false};
-  const int j = BALANCED ? id / Hkv : id % (uint32_t)W_max, h = BALANCED ? id % Hkv : id / (uint32_t)W_max;
+  const int j = id / Hkv, h = id - (uint32_t)j * Hkv;
   PlanCells cells;
   if (BALANCED) {
     const int bc0 = min((int)(threadIdx.x & 63) * ((B + 63) / 64), B - 1);
@@ -2388,7 +2392,7 @@ hipError_t launch_trigger(const int32_t* last_token, const uint32_t* bitmap, int
 template <bool PAGED>
 static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
   if (a.plan_batch > 0) {
-    const dim3 pgrid(std::max(a.plan_wgs, a.plan_even * a.plan_batch), a.Hkv);
+    const dim3 pgrid(a.Hkv, std::max(a.plan_wgs, a.plan_even * a.plan_batch));
     const uint32_t strides = (uint32_t)a.ms | (uint32_t)a.fs << 16;
 #define SFI_PLANNED(EXPOSE)                                                                                             \
   hipLaunchKernelGGL((attn_dense_planned_kernel<EXPOSE, PAGED>), pgrid, dim3(kAttnThreads), 0, s, a.ctx_len, a.is_slow, \
@@ -2426,7 +2430,7 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
   }
 }
 hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t s) {
-  const dim3 grid(n_slots, a.Hkv, B);
+  const dim3 grid(a.Hkv, n_slots, B);
   if (a.table != nullptr) launch_dense_t<true>(a, grid, s);
   else launch_dense_t<false>(a, grid, s);
   return hipGetLastError();

@@ -224,6 +224,7 @@ struct SelArgs {
   float* merge_out;        // nullptr: nothing to merge here
   int32_t len_cap;         // the clamp the dense launch applied to ctx_len
   int32_t out_bf16;        // merge_out is bf16
+  int32_t place_x;         // the launch's segments lie along the grid's first index, not its second (set by the launch)
 };
 
 hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t s);
@@ -236,14 +237,14 @@ hipError_t launch_attn_gather(const AttnArgs& a, int B, int n_slots, hipStream_t
 hipError_t launch_attn_gather_floor(const AttnArgs& a, int B, int n_slots, int tail, int burst, int tpw, int depth, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, int B, hipStream_t s);
 // nJ: upper bound of |J|; hist: with the segments' histograms (sel_cand and sel_write follow, else sel_pick)
-hipError_t launch_sel_score(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s);
-hipError_t launch_sel_accum(const SelArgs& a, int B, int nJ, hipStream_t s);
-hipError_t launch_sel_finalize(const SelArgs& a, int B, int nJ, hipStream_t s);
-hipError_t launch_sel_full(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s);
+hipError_t launch_sel_score(SelArgs a, int B, int nJ, bool hist, hipStream_t s);
+hipError_t launch_sel_accum(SelArgs a, int B, int nJ, hipStream_t s);
+hipError_t launch_sel_finalize(SelArgs a, int B, int nJ, hipStream_t s);
+hipError_t launch_sel_full(SelArgs a, int B, int nJ, bool hist, hipStream_t s);
 bool sel_pick_scores(int nJ, int G, int pairs, int n_cu);  // whether the selecting workgroup also scores (src 1)
-hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t s);  // src 0: keys, 1: logits, 2: window evidence
-hipError_t launch_sel_cand(const SelArgs& a, int B, int nJ, hipStream_t s);
-hipError_t launch_sel_write(const SelArgs& a, int B, int nJ, hipStream_t s);
+hipError_t launch_sel_pick(SelArgs a, int B, int nJ, int src, hipStream_t s);  // src 0: keys, 1: logits, 2: window evidence
+hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s);
+hipError_t launch_sel_write(SelArgs a, int B, int nJ, hipStream_t s);
 hipError_t launch_trigger(const int32_t* last_token, const uint32_t* bitmap, int vocab, int t_max, int32_t* since_slow,
                           uint8_t* is_slow, int B, hipStream_t s);
 hipError_t launch_advance(int32_t* ctx_len, int32_t* recent_start, int B, int n_sink, int recent, hipStream_t s);

@@ -91,6 +91,20 @@ __device__ __forceinline__ void find_kth_desc_lds(const uint32_t* hist, int nbin
 // each { sequence, ctx_len (clamped), records per query head, - }, with their number in front; workgroups with blockIdx.z =
 // r, r + gridDim.z, ... take list entries (few workgroups are launched, whatever the batch).
 // Otherwise blockIdx.z is the sequence, and what does not depend on its length can be requested before the length is there.
+//
+// The grids' first index is the KV head (place 0, segments in the second): with eight heads, or a multiple, consecutive workgroups go
+// round the eight XCDs, so all workgroups of a head, here and in the dense launch, sit behind one L2, and what
+// a launch leaves for the next one -- logits, keys, histograms, candidates -- is read from there and not through the last-level cache.  A slow
+// step, us, segments first / heads first, both launches (one of them alone is worth a quarter of it): 4 x 32768 rows, G = 4 101.9 / 98.5; 8 x 20011..24571, G = 5, paged
+// 146.4 / 141.0; ragged, 12 x 5003..30011, one slow, compact 50.9 / 49.3; 32 x 16384..65536, G = 8, two slow 125.8 / 124.5; the window of 2 x 12000..16384 rows 273 / 270.
+// Where the second index would not do (n_place beyond kMaxPlaceY) the two change places.
+struct Place {
+  int head, i;  // i: segment (or what a launch has for one)
+  int n;        // how many of them the launch has
+};
+__device__ __forceinline__ Place place_of(const SelArgs& a) {
+  return a.place_x != 0 ? Place{(int)blockIdx.y, (int)blockIdx.x, (int)gridDim.x} : Place{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y};
+}
 struct Cell {
   int b, bh;
   int L_in;      // ctx_len as it was read
@@ -99,7 +113,7 @@ struct Cell {
 template <bool LIST>
 __device__ __forceinline__ int cell_count(const SelArgs& a) { return LIST ? __builtin_amdgcn_readfirstlane(a.slow_list[0]) : (int)gridDim.z; }
 template <bool LIST>
-__device__ __forceinline__ Cell cell_of(const SelArgs& a, int r) {
+__device__ __forceinline__ Cell cell_of(const SelArgs& a, int r, int head) {
   Cell c;
   if (LIST) {
     const int4 e = reinterpret_cast<const int4*>(a.slow_list)[1 + r];
@@ -111,7 +125,7 @@ __device__ __forceinline__ Cell cell_of(const SelArgs& a, int r) {
     c.L_in = a.ctx_len[r * a.ms];
     c.n_rec = a.seq_rec != nullptr ? a.seq_rec[r] : a.n_rec;
   }
-  c.bh = c.b * a.Hkv + (int)blockIdx.y;
+  c.bh = c.b * a.Hkv + head;
   return c;
 }
 // A sequence that does not take part (flags without a list: the ragged step's launch with a workgroup per cell).
@@ -124,13 +138,13 @@ __device__ __forceinline__ uint32_t ksel_of(const SelArgs& a, int nJ) { return (
 // Uniform arguments every kernel here reads, asked for at once.
 __device__ __forceinline__ void ask(const SelArgs& a) {
   asm volatile("" ::"s"(a.slow_list), "s"(a.ctx_len), "s"(a.is_slow), "s"(a.ms), "s"(a.fs), "s"(a.Hkv), "s"(a.len_cap), "s"(a.recent),
-               "s"(a.n_sink), "s"(a.n_rec), "s"(a.seq_rec), "s"(a.ld_pos), "s"(a.keys), "s"(a.budget));
+               "s"(a.n_sink), "s"(a.n_rec), "s"(a.seq_rec), "s"(a.ld_pos), "s"(a.keys), "s"(a.budget), "s"(a.place_x));
 }
-// Runs body(cell, thread index) for the workgroup's cells; a cell's LDS is free for the next behind a barrier.
+// Runs body(cell, thread index) for the workgroup's cells of a head; a cell's LDS is free for the next behind a barrier.
 template <bool LIST, typename F>
-__device__ __forceinline__ void for_cells(const SelArgs& a, F body) {
+__device__ __forceinline__ void for_cells(const SelArgs& a, int head, F body) {
   if (!LIST) {
-    body(cell_of<false>(a, blockIdx.z), (int)threadIdx.x);
+    body(cell_of<false>(a, blockIdx.z, head), (int)threadIdx.x);
     return;
   }
   const int n = cell_count<true>(a);
@@ -139,7 +153,7 @@ __device__ __forceinline__ void for_cells(const SelArgs& a, F body) {
     // computed once in front of this loop and kept in registers across the body.
     int zero = 0;
     asm volatile("" : "+s"(zero));
-    body(cell_of<true>(a, r), (int)threadIdx.x + zero);
+    body(cell_of<true>(a, r, head), (int)threadIdx.x + zero);
     __syncthreads();
   }
 }
@@ -249,19 +263,20 @@ template <int NQ, bool HIST, bool ACCUM, bool LIST, bool FLAGS, int GT>
 __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.logits), "s"(a.lg_rows), "s"(a.part), "s"(a.G), "s"(a.alpha), "s"(a.jstat), "s"(a.merge_out));
-  const int seg = blockIdx.x;
+  const Place place = place_of(a);
+  const int seg = place.i;
   const int G = a.G, rows = a.lg_rows;
   __shared__ float s_jM[GT], s_jc[GT];
   __shared__ uint32_t s_hist[HIST ? kHistBins / 2 : 1];
-  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+  for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     if (FLAGS && cell_off<LIST>(a, c)) return;
     const int p_lo = seg * (NQ * 1024);
     const float* lg = a.logits + (int64_t)c.bh * rows * a.ld_pos;
     int p[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) p[q] = p_lo + q * 1024 + tid * 4;
-    if (a.merge_out != nullptr && seg >= (int)gridDim.x - G) {  // workgroup-uniform
-      merge_head(a, c, seg - ((int)gridDim.x - G));
+    if (a.merge_out != nullptr && seg >= place.n - G) {  // workgroup-uniform
+      merge_head(a, c, seg - (place.n - G));
       return;
     }
     // (rows of logits and of the accumulator are padded to whole segments: readable whatever |J| is)
@@ -316,8 +331,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_score_kernel(const SelArgs a)
 // Windowed evidence, mode 0, long J: the accumulated mu times 1 / (number of queries added) is the ranking value.
 __global__ __launch_bounds__(kSelThreads) void sel_finalize_kernel(const SelArgs a) {
   ask(a);
-  const int seg = blockIdx.x, tid = threadIdx.x;
-  const Cell c = cell_of<false>(a, blockIdx.z);
+  const Place place = place_of(a);
+  const int seg = place.i, tid = threadIdx.x;
+  const Cell c = cell_of<false>(a, blockIdx.z, place.head);
   const int p_lo = seg * kSelSeg;
   const int nJ = nJ_of(a, c);
   if (p_lo >= nJ) return;
@@ -357,14 +373,15 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
   ask(a);
   asm volatile("" ::"s"(a.logits), "s"(a.part), "s"(a.G), "s"(a.alpha), "s"(a.jstat), "s"(a.prior), "s"(a.segstat), "s"(a.n_seg_cap),
                "s"(a.merge_out), "s"(a.gamma), "s"(a.beta), "s"(a.p), "s"(a.eta), "s"(a.eps));
-  const int seg = blockIdx.x;
+  const Place place = place_of(a);
+  const int seg = place.i;
   const int G = a.G, rows = G + 1;
   __shared__ float s_jM[GT], s_jc[GT];
   __shared__ double s_scr[kSelThreads / 64][kSegStats];
-  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+  for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     if (FLAGS && cell_off<LIST>(a, c)) return;
-    if (!FROM_MU && a.merge_out != nullptr && seg >= (int)gridDim.x - G) {
-      merge_head(a, c, seg - ((int)gridDim.x - G));
+    if (!FROM_MU && a.merge_out != nullptr && seg >= place.n - G) {
+      merge_head(a, c, seg - (place.n - G));
       return;
     }
     const int p_lo = seg * kPriorSeg;
@@ -458,7 +475,7 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
   __shared__ float s_w[2][kGroup];  // weights of f and of the prior
   const int Hkv = a.Hkv, rad = a.nms_radius;
   const int zs = kFuseSpan + 2 * rad;
-  for_cells<LIST>(a, [&](const Cell& c, const int tid) {  // (blockIdx.y is 0: c.bh is the sequence's first pair)
+  for_cells<LIST>(a, 0, [&](const Cell& c, const int tid) {  // (c.bh is the sequence's first pair)
     const int lane = tid & 63, w = tid >> 6;
     const int nJ = nJ_of(a, c);
     const int p_lo = blockIdx.x * kFuseSpan;
@@ -596,7 +613,7 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
 }
 
 // ---- short J: one workgroup per pair selects --------------------------------------------------------
-// SRC 0: the keys a scoring launch left; 1: straight from the logits (scoring included; workgroups blockIdx.x > 0 merge the
+// SRC 0: the keys a scoring launch left; 1: straight from the logits (scoring included; workgroups of places > 0 merge the
 // dense records, four query heads each); 2: the accumulated evidence of a window.
 // A thread holds P consecutive positions in registers.  The three radix passes run on LDS histograms over all of J;
 // no list of candidates, no global histogram.
@@ -609,10 +626,11 @@ __global__ __launch_bounds__(kPickThreads) void sel_pick_kernel(const SelArgs a)
   __shared__ __align__(16) uint32_t s_h[4096 + 1024 + 512];
   __shared__ uint32_t s_res[2], s_scr[4][NW];
   __shared__ float s_jM[GT], s_jc[GT];
-  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+  const Place place = place_of(a);
+  for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     if (cell_off<LIST>(a, c)) return;
-    if (SRC == 1 && blockIdx.x > 0) {  // workgroup-uniform: one head per 256 threads
-      const int g = ((int)blockIdx.x - 1) * (kPickThreads / kMergeThreads) + (tid >> 8);
+    if (SRC == 1 && place.i > 0) {  // workgroup-uniform: one head per 256 threads
+      const int g = (place.i - 1) * (kPickThreads / kMergeThreads) + (tid >> 8);
       merge_records<kPickThreads / kMergeThreads>(a.part, a.merge_out, c.bh * a.G + min(g, a.G - 1), c.n_rec, nullptr, a.G, a.alpha,
                                                   a.out_bf16 != 0, g < a.G);
       return;
@@ -712,8 +730,9 @@ template <bool LIST>
 __global__ __launch_bounds__(kSelThreads) void sel_group_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.hist), "s"(a.n_seg_cap));
-  const int grp = blockIdx.x;
-  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+  const Place place = place_of(a);
+  const int grp = place.i;
+  for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     const int n_seg = (nJ_of(a, c) + kSelSeg - 1) / kSelSeg;
     const int s0 = grp * kHistGroup, s1 = min(s0 + kHistGroup, n_seg);
     if (s0 >= n_seg || cell_off<LIST>(a, c)) return;
@@ -734,12 +753,13 @@ template <bool LIST, bool GROUPS>
 __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.hist), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap));
-  const int seg = blockIdx.x;
+  const Place place = place_of(a);
+  const int seg = place.i;
   const int p_lo = seg * kSelSeg;
   __shared__ __align__(16) uint32_t s_cnt[kSelThreads / 64][kHistBins];
   __shared__ uint32_t s_res[2], s_before[kSelThreads / 64], s_all[kSelThreads / 64];
   __shared__ uint32_t s_scr[2][kSelThreads / 64];
-  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+  for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     const int lane = tid & 63, w = tid >> 6;
     if (cell_off<LIST>(a, c)) return;
     const int nJ = nJ_of(a, c);
@@ -841,12 +861,13 @@ template <bool LIST>
 __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap), "s"(a.sel_idx), "s"(a.n_sel));
-  const int seg = blockIdx.x;
-  const int n_seg = gridDim.x;
+  const Place place = place_of(a);
+  const int seg = place.i;
+  const int n_seg = place.n;
   __shared__ __align__(16) uint32_t s_h[2048 + 1024 + 1024];
   __shared__ uint32_t s_res[2], s_gt[kSelThreads / 64], s_eq[kSelThreads / 64];
   __shared__ uint32_t s_scr[4][kSelThreads / 64];
-  for_cells<LIST>(a, [&](const Cell& c, const int tid) {
+  for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     if (cell_off<LIST>(a, c)) return;
     const int nJ = nJ_of(a, c);
     const uint32_t ksel = ksel_of(a, nJ);
@@ -973,6 +994,12 @@ static unsigned z_of(const SelArgs& a, int B, int n_wgs) {
   const int z = 8192 / (n_wgs < 1 ? 1 : n_wgs);
   return (unsigned)(z < 1 ? 1 : z > B ? B : z);
 }
+// The grid of n_place places (see Place).
+constexpr int kMaxPlaceY = 65535;
+static dim3 place_grid(SelArgs* a, int n_place, unsigned z) {
+  a->place_x = n_place > kMaxPlaceY;
+  return a->place_x ? dim3(n_place, a->Hkv, z) : dim3(a->Hkv, n_place, z);
+}
 static int ceil_seg(int nJ, int per) { return nJ > 0 ? (nJ + per - 1) / per : 1; }
 // Head counts the scoring kernels are built for: the smallest that holds G.
 template <int NQ, bool HIST, bool ACCUM, bool LIST, bool FLAGS>
@@ -985,10 +1012,10 @@ static void launch_score_t(const SelArgs& a, dim3 grid, hipStream_t s) {
   else if (a.G <= 8) hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 8>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((sel_score_kernel<NQ, HIST, ACCUM, LIST, FLAGS, 16>), grid, block, 0, s, a);
 }
-hipError_t launch_sel_score(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s) {
+hipError_t launch_sel_score(SelArgs a, int B, int nJ, bool hist, hipStream_t s) {
   // with the merge on board: one more workgroup per query head
   const int n_seg = ceil_seg(nJ, hist ? kSelSeg : 1024) + (a.merge_out != nullptr ? a.G : 0);
-  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
+  const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv));
   if (a.slow_list != nullptr) {
     if (hist) launch_score_t<2, true, false, true, false>(a, grid, s);
     else launch_score_t<1, false, false, true, false>(a, grid, s);
@@ -1001,12 +1028,14 @@ hipError_t launch_sel_score(const SelArgs& a, int B, int nJ, bool hist, hipStrea
   }
   return hipGetLastError();
 }
-hipError_t launch_sel_accum(const SelArgs& a, int B, int nJ, hipStream_t s) {
-  launch_score_t<1, false, true, false, false>(a, dim3(ceil_seg(nJ, 1024) + (a.merge_out != nullptr ? a.G : 0), a.Hkv, B), s);
+hipError_t launch_sel_accum(SelArgs a, int B, int nJ, hipStream_t s) {
+  const dim3 grid = place_grid(&a, ceil_seg(nJ, 1024) + (a.merge_out != nullptr ? a.G : 0), B);
+  launch_score_t<1, false, true, false, false>(a, grid, s);
   return hipGetLastError();
 }
-hipError_t launch_sel_finalize(const SelArgs& a, int B, int nJ, hipStream_t s) {
-  hipLaunchKernelGGL(sel_finalize_kernel, dim3(ceil_seg(nJ, kSelSeg), a.Hkv, B), dim3(kSelThreads), 0, s, a);
+hipError_t launch_sel_finalize(SelArgs a, int B, int nJ, hipStream_t s) {
+  const dim3 grid = place_grid(&a, ceil_seg(nJ, kSelSeg), B);
+  hipLaunchKernelGGL(sel_finalize_kernel, grid, dim3(kSelThreads), 0, s, a);
   return hipGetLastError();
 }
 template <bool FROM_MU, bool LIST, bool FLAGS>
@@ -1019,9 +1048,9 @@ static void launch_prior_t(const SelArgs& a, dim3 grid, hipStream_t s) {
   else if (a.G <= 8) hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 8>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 16>), grid, block, 0, s, a);
 }
-hipError_t launch_sel_full(const SelArgs& a, int B, int nJ, bool hist, hipStream_t s) {
+hipError_t launch_sel_full(SelArgs a, int B, int nJ, bool hist, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kPriorSeg) + (a.merge_out != nullptr ? a.G : 0);
-  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
+  const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv));
   if (a.f_from_mu) launch_prior_t<true, false, false>(a, grid, s);  // (a window's evidence is never ranked in the ragged step)
   else if (a.slow_list != nullptr) launch_prior_t<false, true, false>(a, grid, s);
   else if (a.is_slow != nullptr) launch_prior_t<false, false, true>(a, grid, s);
@@ -1064,10 +1093,10 @@ static void launch_pick_keys_t(const SelArgs& a, int nJ, dim3 grid, hipStream_t 
 bool sel_pick_scores(int nJ, int G, int pairs, int n_cu) {
   return (int64_t)nJ * G <= kPickLogits && nJ <= (G <= 5 ? 8 : 4) * kPickThreads && (G <= 8 || 4 * pairs <= n_cu);
 }
-hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t s) {
+hipError_t launch_sel_pick(SelArgs a, int B, int nJ, int src, hipStream_t s) {
   const int per_wg = kPickThreads / kMergeThreads;
   const int extra = src == 1 ? (a.G + per_wg - 1) / per_wg : 0;
-  const dim3 grid(1 + extra, a.Hkv, z_of(a, B, (1 + extra) * a.Hkv * 4));
+  const dim3 grid = place_grid(&a, 1 + extra, z_of(a, B, (1 + extra) * a.Hkv * 4));
   const bool list = a.slow_list != nullptr;
   if (src == 1) {
     if (nJ <= 4 * kPickThreads) {
@@ -1085,15 +1114,16 @@ hipError_t launch_sel_pick(const SelArgs& a, int B, int nJ, int src, hipStream_t
   }
   return hipGetLastError();
 }
-hipError_t launch_sel_cand(const SelArgs& a, int B, int nJ, hipStream_t s) {
+hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kSelSeg);
-  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv)), block(kSelThreads);
+  const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv)), block(kSelThreads);
   const bool list = a.slow_list != nullptr;
   if (n_seg > kHistGroupFrom) {
     const int n_grp = (n_seg + kHistGroup - 1) / kHistGroup;
-    const dim3 ggrid(n_grp, a.Hkv, z_of(a, B, n_grp * a.Hkv));
-    if (list) hipLaunchKernelGGL(sel_group_kernel<true>, ggrid, block, 0, s, a);
-    else hipLaunchKernelGGL(sel_group_kernel<false>, ggrid, block, 0, s, a);
+    SelArgs ag = a;
+    const dim3 ggrid = place_grid(&ag, n_grp, z_of(a, B, n_grp * a.Hkv));
+    if (list) hipLaunchKernelGGL(sel_group_kernel<true>, ggrid, block, 0, s, ag);
+    else hipLaunchKernelGGL(sel_group_kernel<false>, ggrid, block, 0, s, ag);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (list) hipLaunchKernelGGL((sel_cand_kernel<true, true>), grid, block, 0, s, a);
@@ -1105,9 +1135,9 @@ hipError_t launch_sel_cand(const SelArgs& a, int B, int nJ, hipStream_t s) {
   }
   return hipGetLastError();
 }
-hipError_t launch_sel_write(const SelArgs& a, int B, int nJ, hipStream_t s) {
+hipError_t launch_sel_write(SelArgs a, int B, int nJ, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kSelSeg);
-  const dim3 grid(n_seg, a.Hkv, z_of(a, B, n_seg * a.Hkv));
+  const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv));
   if (a.slow_list != nullptr) hipLaunchKernelGGL(sel_write_kernel<true>, grid, dim3(kSelThreads), 0, s, a);
   else hipLaunchKernelGGL(sel_write_kernel<false>, grid, dim3(kSelThreads), 0, s, a);
   return hipGetLastError();

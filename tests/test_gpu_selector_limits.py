@@ -336,3 +336,35 @@ def test_large_groups_score_by_the_number_of_pairs(oracle, G, B):
         _check_slow(oracle, w, r, None, w.q(0))
     finally:
         r.close()
+
+
+# A J of more segments than a grid's second index takes: the segments move to the first one.  One block of 65536 rows stands behind every entry of
+# the block table, so that each of its rows comes 2049 times: the index set is the first copies of the row with the largest logit.
+def test_more_segments_than_the_second_grid_index_takes():
+    import torch
+    import paper_2603_12038_amd as sfi
+    page, n_page, budget, recent = 65536, 2049, 100, 64
+    L = page * n_page - 77
+    print(f"[gpu-limits] one sequence of {L} rows, paged onto one block", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    K = torch.empty((1, 1, page, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    V = torch.empty((1, 1, page, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    q = torch.empty((1, 1, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    y = (K[0, 0].float() * q[0, 0].float()).sum(-1)
+    best = int(y.argmax())
+    assert float(y.max() - y[torch.arange(page, device="cuda") != best].max()) > 1e-3
+    want = [p for p in range(best, L - recent, page) if p >= N_SINK][:budget]
+    ctx = sfi.SfiContext(1, 1, 1, page * n_page, budget, N_SINK, recent, K, V, page_size=page, page_layout="htd")
+    try:
+        sfi.sfi_set_block_table(ctx.handle, torch.zeros((1, n_page), dtype=torch.int32, device="cuda"), 1)
+        out = torch.zeros((1, 1, 128), device="cuda")
+        sel = torch.full((1, 1, budget), -7, dtype=torch.int32, device="cuda")
+        nsel = torch.full((1, 1), -7, dtype=torch.int32, device="cuda")
+        sfi.sfi_slow_step(ctx.handle, q, K, V, i32_dev([L]), L, budget, out, sel, nsel)
+        torch.cuda.synchronize()
+        assert int(nsel) == budget and sel.flatten().tolist() == want
+        p = torch.softmax(y.double() / 128 ** 0.5, 0)  # (the 77 rows that are missing from the last copy do not show)
+        ref = p @ V[0, 0].double()
+        assert float((out[0, 0].double() - ref).abs().max() / ref.abs().max()) < 2e-3
+    finally:
+        ctx.close()
