@@ -374,7 +374,8 @@ enum {
   SFI_STAGE_ATTN = 0,     /* split attention kernel (dense; gather or compact in a fast step) */
   SFI_STAGE_MERGE = 1,    /* split merge */
   SFI_STAGE_SCORE = 2,    /* evidence and ranking keys, with the segments' histograms where J is long (mode 1: both
-                             kernels together); none where one workgroup per pair scores or reads a window's evidence */
+                             kernels together); none where one workgroup per pair scores or reads a window's evidence;
+                             counted, with nothing in it, where the dense launch scores (sfi_set_dense_scores) */
   SFI_STAGE_CAND = 3,     /* long J only: threshold-bin candidates (very long J: and the histograms' sums by groups) */
   SFI_STAGE_COUNT = 4,    /* not used: always 0 */
   SFI_STAGE_WRITE = 5,    /* ordered index write; short J: the whole selection, with the scoring and the output's merge
@@ -424,6 +425,13 @@ int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);
  * tests): the launches that mode 1 hands over through an L2 deal a pair's workgroups to different XCDs, so that every
  * pair is computed again (more than eight KV heads: as mode 0): the same results up to the order of the sums.  Other values: SFI_EINVAL. */
 int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
+
+/* A/B knob of sfi_slow_step and the ragged steps (selector_mode 0, more than 16384 positions to rank, batches of up to 64 sequences).
+ * mode = 1 (default): where that is faster the dense launch also scores, each workgroup what it has read, once it has the others'
+ * statistics of its sequence; it waits 64 us for them at most, and what is missing then (a launch that has to share the GPU) the
+ * Selector scores.  mode = 0: a scoring launch, as behind sfi_slow_attn.  mode = 2, 3, 4 (for tests): scored in the dense launch
+ * wherever it can be, with no wait at all, a wait of one tick, and the whole wait.  Same results.  Other values: SFI_EINVAL. */
+int sfi_set_dense_scores(sfi_ctx* ctx, int32_t mode);
 
 /* Launch geometry the library would choose, without launching anything (host arithmetic only): split
  * workgroups per (sequence, KV head) of a dense launch bounded by max_len rows (0 = cfg.max_ctx) and

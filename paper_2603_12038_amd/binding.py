@@ -46,7 +46,7 @@ _hot = None  # the CPython module with the hot calls
 EXPORTS = ("sfi_workspace_bytes", "sfi_create", "sfi_set_block_table", "sfi_destroy", "sfi_strerror", "sfi_slow_step", "sfi_slow_attn",
            "sfi_slow_select", "sfi_evidence_add", "sfi_evidence_add_causal", "sfi_evidence_select", "sfi_dense_attn",
            "sfi_fast_step", "sfi_fast_step_static", "sfi_fast_step_floor", "sfi_dense_attn_floor", "sfi_reorg", "sfi_fast_step_compact", "sfi_mixed_step", "sfi_mixed_step_compact", "sfi_step_begin", "sfi_mixed_step_desc", "sfi_trigger", "sfi_advance", "sfi_set_profiling", "sfi_stage_times",
-           "sfi_set_tuning", "sfi_set_dense_k_layout", "sfi_set_mixed_plan", "sfi_set_handover", "sfi_plan_splits", "sfi_device_status", "sfi_query_splits")
+           "sfi_set_tuning", "sfi_set_dense_k_layout", "sfi_set_mixed_plan", "sfi_set_handover", "sfi_set_dense_scores", "sfi_plan_splits", "sfi_device_status", "sfi_query_splits")
 
 
 def load_library() -> C.CDLL:
@@ -118,6 +118,8 @@ def load_library() -> C.CDLL:
     lib.sfi_set_mixed_plan.argtypes = [vp, i32]
     lib.sfi_set_handover.restype = C.c_int
     lib.sfi_set_handover.argtypes = [vp, i32]
+    lib.sfi_set_dense_scores.restype = C.c_int
+    lib.sfi_set_dense_scores.argtypes = [vp, i32]
     lib.sfi_plan_splits.restype = C.c_int
     lib.sfi_plan_splits.argtypes = [vp, i32, i32, C.POINTER(i32), C.POINTER(i32)]
     lib.sfi_device_status.restype = C.c_int
@@ -314,6 +316,10 @@ def sfi_set_mixed_plan(ctx, on: bool) -> None:
 
 def sfi_set_handover(ctx, mode: int) -> None:
     _check(load_library().sfi_set_handover(ctx, int(mode)), "sfi_set_handover")
+
+
+def sfi_set_dense_scores(ctx, mode: int) -> None:
+    _check(load_library().sfi_set_dense_scores(ctx, int(mode)), "sfi_set_dense_scores")
 
 
 def sfi_set_dense_k_layout(ctx, whole_lines: bool) -> None:

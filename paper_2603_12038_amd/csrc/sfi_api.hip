@@ -24,7 +24,9 @@ struct sfi_ctx {
   int dense_wide;           // dense kernel reads K rows as whole 128-byte lines (A/B knob, sfi_set_dense_k_layout)
   int mixed_plan;           // the ragged step's dense launch plans itself on the device (default; A/B knob, sfi_set_mixed_plan)
   int handover;             // fast-step records: 0 device scope, 1 XCD-local where the launch allows it (default), 2 (sfi_set_handover)
+  int dense_scores;         // the slow step's dense launch scores: 0 no, 1 where that is faster (default), 2 to 4 (sfi_set_dense_scores)
   int last_dense_splits, last_fast_splits;
+  int last_dense_scored;    // the last dense launch of a slow step has scored
   int last_dense_planned;   // the last dense launch planned itself: its records per sequence are in ws.seq_rec
   // profiling: a ring of event pairs, one set of stages per hot call, read back in one go so that
   // no host synchronisation sits between the profiled calls
@@ -101,14 +103,17 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   // exposed rows per (b, h): the G heads' y and, for the full Selector, the squared key norms
   ws->logits = (float*)take((size_t)(B * Hq + (full ? B * Hkv : 0)) * ld * sizeof(float));
   ws->keys = (uint32_t*)take((size_t)(B * Hkv) * ld * sizeof(uint32_t));
-  ws->cand = (uint32_t*)take((size_t)(B * Hkv) * ld * 2 * sizeof(uint32_t));
+  ws->cand = (uint32_t*)take((size_t)(B * Hkv) * ld * sizeof(uint32_t));
   ws->state = (uint32_t*)take((size_t)(B * Hkv) * kStateWords * sizeof(uint32_t));
   ws->segcnt = (uint32_t*)take((size_t)(B * Hkv) * n_seg * sizeof(uint32_t));
   ws->jstat = (float2*)take((size_t)(B * Hq) * sizeof(float2));
   ws->mu = (float*)take((size_t)(B * Hkv) * ld * sizeof(float));
   ws->hist = (uint32_t*)take((size_t)(B * Hkv) * n_seg * (kHistBins / 2) * sizeof(uint32_t));
   ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * kWaves * kArriveStride * sizeof(uint32_t));
-  ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears both
+  ws->met = (uint64_t*)take((size_t)(B * Hq) * kSlotCap * sizeof(uint64_t));
+  ws->met_late = (unsigned long long*)take((size_t)(B * Hkv) * sizeof(unsigned long long));
+  ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears them all
+  ws->wg_hist = B <= kScoreCap && !full && c->max_ctx > kPickMax ? (uint32_t*)take((size_t)(B * Hkv) * kSlotCap * kHistBins * sizeof(uint32_t)) : nullptr;
   ws->prior = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->fbuf = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->segstat = full ? (double*)take((size_t)(B * Hkv) * n_seg * kSegStats * sizeof(double)) : nullptr;
@@ -266,6 +271,36 @@ bool merges_in_kernel(const sfi_ctx* x, int n_split, int max_len) {
   return x->G <= 8 || n_split <= 16 || (max_len + kTile - 1) / kTile > 16 * kWaves * n_split;
 }
 
+// Whether a slow step's dense launch also scores (score_tail), so that the Selector's scoring launch falls away: where three Selector
+// launches would follow, and all of the launch's workgroups are on the chip together (one per unit: their LDS).  a: planned
+// or, for one sequence, not.
+// - A wave has at least five tiles (ragged: eight if the longest sequence is the only slow one; the others are shorter), else the
+//   scoring launch costs no more than the wait.
+// - Logits that LDS does not hold go to memory and come back to the few waves of a unit; up to four times what it holds that
+//   is still the faster way.  (How many sequences of a ragged step are slow the host does not know: few, as a rule.)
+// Scoring launch / in the dense launch, us a slow step, 8 KV heads and G = 4 where not given: 4 x 32768 rows 98.4 / 94.4; 8 x 20011..24571, G = 5, paged 141.3 / 132.5;
+// 1 x 131072 102.8 / 99.3, G = 16 (three times LDS) 138.4 / 133.7; 8 x 32768, 2 KV heads 59.5 / 56.0; 16 x 20000..60000 511.0 / 504.5;
+// 2 x 20000..30000, G = 8, 4 KV heads (7 tiles) 37.8 / 37.6; ragged, 32 x 16384..65536, G = 8, two slow 126.6 / 118.0, 16 x 20000..60000, half slow 271.5 / 246.0, all 517 / 511.
+// Beyond the lines: 1 x 17000 (4 tiles) 28.6 / 28.7, 2 KV heads 24.2 / 24.8; ragged, 4 x 17000, one slow 35.5 / 36.3, 12 x 5003..30011, one slow, compact 49.9 / 50.2;
+// more than four times LDS: 16 x 20000..60000, G = 8 573.2 / 578.6, 16 x 20000..30000, G = 16 407.8 / 410.7.
+bool score_in_dense(const sfi_ctx* x, const AttnArgs& a, int max_len, bool mixed) {
+  const int nJ = max_len - x->cfg.recent - x->cfg.n_sink, B = x->cfg.batch, Hkv = x->cfg.n_kv_heads;
+  if (x->dense_scores == 0 || x->ws.wg_hist == nullptr || nJ <= kPickMax || x->dense_wide || (a.plan_batch == 0 && B > 1)) return false;
+  const int wgs = a.plan_batch > 0 ? std::max(a.plan_wgs, a.plan_even * B) : a.n_split;
+  if (wgs * Hkv > x->n_cu) return false;
+  if (x->dense_scores > 1) return true;
+  const int64_t tiles = (int64_t)((max_len + kTile - 1) / kTile) * (mixed ? 1 : B) * Hkv, waves = (int64_t)kWaves * x->n_cu;
+  return tiles >= (mixed ? 8 : 5) * waves && (mixed || tiles <= 4 * score_stay(x->G) * waves);
+}
+void set_dense_scores(const sfi_ctx* x, AttnArgs* a) {
+  a->met = x->ws.met;
+  a->met_late = x->ws.met_late;
+  a->wg_hist = x->ws.wg_hist;
+  a->keys = x->ws.keys;
+  a->alpha = x->alpha;
+  a->met_ticks = x->dense_scores == 2 ? 0 : x->dense_scores == 3 ? 1 : kScoreWaitTicks;
+}
+
 void set_dense_bounds(const sfi_ctx* x, AttnArgs* a, int max_len) {
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink;
   a->max_tiles = nJ > 0 ? (nJ + kTile - 1) / kTile : 0;
@@ -399,6 +434,7 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
   memset(s, 0, sizeof(*s));
   const sfi_config& c = x->cfg;
   s->jstat = x->ws.jstat; s->logits = x->ws.logits; s->keys = x->ws.keys; s->cand = x->ws.cand;
+  s->wg_hist = x->ws.wg_hist;
   s->hist = x->ws.hist; s->state = x->ws.state; s->segcnt = x->ws.segcnt;
   s->ctx_len = ctx_len; s->is_slow = is_slow; s->sel_idx = sel_idx; s->n_sel = n_sel;
   s->ms = 1; s->fs = 1;
@@ -443,7 +479,8 @@ int run_selector(sfi_ctx* x, const SelArgs& sa, int max_len, hipStream_t st, boo
   else if (!full && !windowed && sa.part != nullptr && pick && sel_pick_scores(nJ, x->G, B * x->cfg.n_kv_heads, x->n_cu)) src = 1;  // ... the logits
   if (src == 0) {
     StageTimer t(x, st, SFI_STAGE_SCORE);
-    if (full) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
+    if (sa.met != nullptr) {}  // the dense launch has scored: nothing between the stage's events
+    else if (full) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
     else if (windowed) SFI_TRY(launch_sel_finalize(sa, B, nJ, st));
     else SFI_TRY(launch_sel_score(sa, B, nJ, !pick, st));
     if (!t.stop()) return SFI_ELAUNCH;
@@ -529,6 +566,7 @@ int sfi_create(const sfi_config* cfg, void* workspace, size_t workspace_bytes, s
   x->tail_merge = 1;
   x->mixed_plan = 1;
   x->handover = 1;
+  x->dense_scores = 1;
   // The arrival counters of split launches start at zero (and every launch leaves them there).
   // A workspace the runtime knows (device, managed, pinned) is cleared here and a failure to do so is an error: with stale
   // counters no workgroup would ever take itself for the last one.  (Without a device, or with a
@@ -642,7 +680,7 @@ namespace {
 // First half of a slow step: dense attention with the evidence (y over J, Selector state cleared,
 // J-only softmax statistics) left in the workspace.
 int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, const int32_t* ctx_len, int ml,
-                   float* out, hipStream_t st, bool merge_later = false, const int32_t* q_len = nullptr) {
+                   float* out, hipStream_t st, bool merge_later = false, const int32_t* q_len = nullptr, bool select_next = false) {
   AttnArgs a;
   fill_attn(x, &a, q, K, V, ctx_len);
   a.q_len = q_len;
@@ -661,6 +699,8 @@ int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.n_split = dense_splits_for(x, ml, false);
   a.big_stash = 1;  // every sequence is dense: one workgroup per compute unit, half as many write bursts
   plan_dense(x, &a, ml, false);
+  x->last_dense_scored = select_next && score_in_dense(x, a, ml, false);
+  if (x->last_dense_scored) set_dense_scores(x, &a);
   x->last_dense_splits = a.n_split;
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (merge_later) return SFI_OK;  // the Selector's scoring launch merges
@@ -689,11 +729,12 @@ int sfi_slow_step(sfi_ctx* x, const void* q, const void* K, const void* V, const
   hipStream_t st = (hipStream_t)stream;
   CallRecord call_record(x);
   // no merge launch: the merge rides in the Selector's first launch (one launch less on the step's critical path)
-  if ((rc = slow_attn_impl(x, q, K, V, ctx_len, ml, out, st, true)) != SFI_OK) return rc;
+  if ((rc = slow_attn_impl(x, q, K, V, ctx_len, ml, out, st, true, nullptr, true)) != SFI_OK) return rc;
   SelArgs sa;
   fill_sel(x, &sa, ctx_len, ml, nullptr, budget, x->last_dense_splits, sel_idx, n_sel);
   sa.part = x->ws.part;
   sa.merge_out = out;
+  if (x->last_dense_scored) { sa.met = x->ws.met; sa.met_late = x->ws.met_late; }
   if (x->last_dense_planned) sa.seq_rec = x->ws.seq_rec;
   return run_selector(x, sa, ml, st);
 }
@@ -1082,6 +1123,8 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   if (x->mixed_plan != 0 && merge_in_score) plan_dense(x, &d, ml, true);
   const bool planned = d.plan_batch > 0;
   if (planned) d.slow_list = x->ws.slow_list;
+  const bool scored = planned && score_in_dense(x, d, ml, true);
+  if (scored) set_dense_scores(x, &d);
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
   if (planned && one_ragged_launch(x, f)) {
@@ -1111,6 +1154,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
     sa.merge_out = out;
   }
   if (planned) sa.slow_list = x->ws.slow_list;
+  if (scored) { sa.met = x->ws.met; sa.met_late = x->ws.met_late; }
   if ((rc = run_selector(x, sa, ml, st)) != SFI_OK) return rc;
   if (cb == nullptr) return SFI_OK;
   // Reorg_i for the sequences that were refreshed (Sel_i -> Reorg_i)
@@ -1242,6 +1286,12 @@ int sfi_set_mixed_plan(sfi_ctx* x, int32_t on) {
 int sfi_set_handover(sfi_ctx* x, int32_t mode) {
   if (x == nullptr || mode < 0 || mode > 2) return SFI_EINVAL;
   x->handover = mode;
+  return SFI_OK;
+}
+
+int sfi_set_dense_scores(sfi_ctx* x, int32_t mode) {
+  if (x == nullptr || mode < 0 || mode > 4) return SFI_EINVAL;
+  x->dense_scores = mode;
   return SFI_OK;
 }
 

@@ -33,6 +33,7 @@
 
 #include "sfi_internal.h"
 #include "sfi_merge.h"
+#include "sfi_score.h"
 #include "sfi_wave.h"
 
 namespace sfi {
@@ -519,6 +520,7 @@ struct WgOut {
   float* part;         // the records (with neither pointer above: a merge launch follows)
   int n_split, slot_cap;
   bool out_bf16;
+  uint64_t* met;       // JSTAT 2: the pair's statistics for score_tail, [G][kSlotCap]
 };
 __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
   WgOut o;
@@ -529,6 +531,7 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
   o.n_split = a.n_split;
   o.slot_cap = a.slot_cap;
   o.out_bf16 = a.out_bf16 != 0;
+  o.met = nullptr;
   return o;
 }
 // The way out of an attention workgroup: the four waves' partial results are combined through LDS and sent where WgOut
@@ -557,11 +560,12 @@ __device__ __forceinline__ WgOut wg_out_of(const AttnArgs& a, int bh) {
 // 12.29 / 11.85; 12 x 32768 rows, budget 1000 14.55 / 13.68; 8 x 32768 rows, one KV head, budget 2000 9.03 / 8.34.  (With the counter in the L2 as
 // well another 1 %, but then workgroups on different XCDs would not find one another.)
 // JSTAT (dense kernel with exposed logits): the record's header also carries the statistics over the allowed set J alone,
-// { m, l, m_J, l_J } (the fast step and the dense kernel without logits leave the last two words).
+// { m, l, m_J, l_J } (the fast step and the dense kernel without logits leave the last two words).  2: m_J and l_J also go out for
+// the pair's other workgroups, l_J with its sign bit set, so that they cannot be zero (score_tail).
 // AT_ONCE: heads a wave merges at a time.  Two where a group has more than eight heads (the kernels with the plain K layout),
 // so that up to four heads take two chains of trips, not four: 16 heads, 33 records, fast step 13.5 -> 12.8 us.  One for
 // smaller groups, whose waves have one or two: the second head's code costs them 0.1 us.
-template <bool JSTAT = false, int AT_ONCE = 1, bool LOCAL = false>
+template <int JSTAT = 0, int AT_ONCE = 1, bool LOCAL = false>
 __device__ __forceinline__ bool finish_wg(const WgOut& o, int64_t head0, int G, int slot, const f32x4 (&acc)[8], float m_run,
                                           float l_run, float* red, int wave_stride, float m_j = 0.f, float l_j = 0.f) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -625,6 +629,8 @@ __device__ __forceinline__ bool finish_wg(const WgOut& o, int64_t head0, int G, 
           const float4 mj = *reinterpret_cast<const float4*>(&s_mj[hh][0]), lj = *reinterpret_cast<const float4*>(&s_lj[hh][0]);
           const float MJ = fmaxf(fmaxf(mj.x, mj.y), fmaxf(mj.z, mj.w));
           const float LJ = lj.x * fast_exp2(mj.x - MJ) + lj.y * fast_exp2(mj.y - MJ) + lj.z * fast_exp2(mj.z - MJ) + lj.w * fast_exp2(mj.w - MJ);
+          if (JSTAT == 2 && c == 0)
+            __hip_atomic_store(o.met + hh * kSlotCap + slot, (uint64_t)(__float_as_uint(LJ) | 0x80000000u) << 32 | __float_as_uint(MJ), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           if (c == 0) *reinterpret_cast<float4*>(dst) = make_float4(M, ls, MJ, LJ);
         } else if (c == 0) {
           *reinterpret_cast<float2*>(dst) = make_float2(M, ls);
@@ -772,7 +778,7 @@ struct ListWalk {
 // dense kernel
 // ------------------------------------------------------------------------------------------------
 // PAGED: K / V are block pools addressed through the sequence's block table.
-// EXPOSE 1: also write y over J for the Selector; 2: y and the squared key norms.
+// EXPOSE 1: also write y over J for the Selector; 2: y and the squared key norms; 3: y stays in LDS as far as it fits, for score_tail.
 // BIG: twice the logits stash per wave, which leaves room for one workgroup per compute unit only
 // (launches where every sequence is dense, and the planned launch, run one per unit anyway; the ragged
 // step's launch with a workgroup per cell keeps two, although that kernel spills 6 to 26 of its 256 registers: with one,
@@ -787,10 +793,20 @@ struct DenseShare {
   int bad;           // PLANNED: guard bits so far
   bool have_k;       // PLANNED: K rows of the first tile are on their way into T
 };
-// Floats of lds per wave: the logits stash, and at the end the wave's O for the combine (finish_wg).
-constexpr int patch_floats(int expose, bool big) { return expose == 0 ? 16 * kHeadDim : big ? 2 * kStashFloats : kStashFloats; }
+// Floats of lds per wave: the logits stash, and at the end the wave's O for the combine (finish_wg).  EXPOSE 3: the four waves' O in
+// front, then their stashes, which outlive it (score_tail), then the list of the sequences the workgroup has had.
+constexpr int kScoreEntryFloats = 8;
+constexpr int patch_floats(int expose, bool big) {
+  return expose == 3 ? (kScoreFloats + kScoreCap * kScoreEntryFloats) / kWaves : expose == 0 ? 16 * kHeadDim : big ? 2 * kStashFloats : kStashFloats;
+}
+struct Scored {
+  int4* entry;  // two words per sequence: { head, sequence, first, step }, { end of J's tiles, |J|, records, own record }
+  int n;        // sequences so far
+  int used;     // tiles of J this wave has had so far
+};
+__device__ __forceinline__ Scored scored_of(float* lds) { return Scored{reinterpret_cast<int4*>(lds + kScoreFloats), 0, 0}; }
 template <int EXPOSE, bool PAGED, bool BIG, bool WIDE, bool PLANNED>
-__device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& sh, const int h, const int b, Tile& T, float* lds, const int tid_bias = 0) {
+__device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& sh, const int h, const int b, Tile& T, float* lds, Scored& sc, const int tid_bias = 0) {
   constexpr int kStash = BIG ? 2 * kStashFloats : kStashFloats;
   constexpr int kPatch = patch_floats(EXPOSE, BIG);
   // everything uniform is asked for at once (the first argument load of a wave takes 0.4 us)
@@ -935,18 +951,21 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   // With EXPOSE == 2 a tile has one more row: ||k_j||^2 of its 32 positions, for the key-norm factor of
   // the Selector's prior (Eq. selector_prior_kn).
   const int rows_exp = G + (EXPOSE == 2 ? 1 : 0);
-  float* stash = lds + w * kPatch;
+  float* stash = EXPOSE == 3 ? lds + kWaves * G * kHeadDim + w * score_stash_floats(G) : lds + w * kPatch;
   float* lg_base = EXPOSE != 0 ? a.logits + (int64_t)bh * rows_exp * a.ld_pos : nullptr;
   const int tile_f4 = rows_exp * (kTile / 4);        // float4 per tile
-  const int stash_cap = kStash / (rows_exp * kTile);  // tiles the stash holds
-  int n_stashed = 0, k_flushed = 0;
+  // EXPOSE 3: the first tiles stay where they are, for score_tail; what goes to memory lies behind them.
+  const int stay = EXPOSE == 3 ? score_stay(G) : 0;
+  const int stash_cap = EXPOSE == 3 ? kScoreBurst : kStash / (rows_exp * kTile);  // tiles the stash holds until they are written
+  int n_stashed = 0, k_flushed = EXPOSE == 3 ? max(0, stay - sc.used) : 0;
+  const float* const burst = stash + stay * (G * kTile);
   auto flush_stash = [&]() {
     __builtin_amdgcn_wave_barrier();
     const int n_f4 = n_stashed * tile_f4;
     for (int f = lane; f < n_f4; f += 64) {
       const int i = f / tile_f4, rem = f - i * tile_f4;
       const int t = first + (k_flushed + i) * step;
-      *reinterpret_cast<float4*>(lg_base + ((int64_t)t * tile_f4 + rem) * 4) = *reinterpret_cast<const float4*>(stash + f * 4);
+      *reinterpret_cast<float4*>(lg_base + ((int64_t)t * tile_f4 + rem) * 4) = *reinterpret_cast<const float4*>(burst + f * 4);
     }
     __builtin_amdgcn_wave_barrier();
     k_flushed += n_stashed;
@@ -987,13 +1006,14 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
       qk_join_wide(s4, a.scale_log2, y);
     }
     if (EXPOSE != 0 && inJ) {  // positions past |J| land in the padding of the last tile, never used
-      float* st = stash + n_stashed * (rows_exp * kTile);
+      const bool stays = EXPOSE == 3 && sc.used + k < stay;
+      float* st = stash + (EXPOSE == 3 ? min(sc.used + k, stay) + n_stashed : n_stashed) * (rows_exp * kTile);
       stage_logits<WIDE>(st, y, jg, n, G);
       if (EXPOSE == 2 && jg == (n >> 2)) {
         st[G * kTile + n] = k2a;
         st[G * kTile + 16 + n] = k2b;
       }
-      if (++n_stashed == stash_cap) flush_stash();
+      if (!stays && ++n_stashed == stash_cap) flush_stash();
     }
     const int p0 = (inJ ? t : t - nTJ) * kTile;
     const int N = inJ ? NJ : NS;
@@ -1032,13 +1052,121 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   }
   WgOut o = wg_out_of(a, bh);
   o.n_split = sh.n_rec;
+  if (EXPOSE == 3) o.met = a.met + (int64_t)bh * G * kSlotCap;
   if (PLANNED && sh.n_rec == 1) {
     o.out_direct = o.out_merge;
     o.out_merge = nullptr;
   }
-  finish_wg<EXPOSE != 0>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), lds, kPatch, m_j,
-                               EXPOSE != 0 ? rows_sum(l_j) : 0.f);
+  finish_wg<EXPOSE == 3 ? 2 : EXPOSE != 0>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), lds, EXPOSE == 3 ? G * kHeadDim : kPatch, m_j,
+                                           EXPOSE != 0 ? rows_sum(l_j) : 0.f);
+  if (EXPOSE == 3) {
+    sc.used += KJ;
+    if (tid == 0) {
+      sc.entry[2 * sc.n] = make_int4(h, b, sh.first, sh.step);
+      sc.entry[2 * sc.n + 1] = make_int4(nTJw, NJ, sh.n_rec, sh.slot);
+    }
+    ++sc.n;
+  }
   report_guard(a.guard, bad);
+}
+// ---- scoring in the dense launch (EXPOSE 3) ------------------------------------------------------------------
+// The evidence of a position is a sum over the group's heads, each over its own normaliser (Eq. selector_mu), and those are known
+// when all workgroups of a pair have left their statistics.  A workgroup that has done its share therefore waits for
+// the pair's others and turns the logits, which it still has in LDS, into keys and a histogram of its own: a G-th of the
+// bytes to memory, and no scoring launch.
+// A workgroup's statistics of a head are one word of eight bytes that is never zero, written and read at device scope and put back
+// to zero by the Selector's last launch: what has arrived is seen in the value itself, so nothing is ordered or counted.  (A
+// counter behind acknowledged headers, in front of their loads, was 0.7 us longer, in the L2 of one XCD no shorter.)
+// All workgroups of the launch are on the chip together where it has the chip to itself (score_in_dense); where it has
+// not, some may only start when others have ended, so the wait has a limit.  Behind it a workgroup writes its logits,
+// marks its record in the pair's mask and ends; the next launch then scores that record's tiles (late_records).
+// Nothing of this is decided before all of the workgroup's own shares are done and out, so no workgroup waits for one that waits.
+// The keys are bit for bit what the scoring launch (sel_score_kernel) makes of the same logits.
+__device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, float* lds) {
+  __shared__ __align__(16) uint32_t s_hist[kHistBins];
+  __shared__ float s_M[16], s_c[16];
+  __shared__ uint32_t s_met[kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = a.G, tile_f = G * kTile, stay = score_stay(G);
+  const float* const stash = lds + kWaves * G * kHeadDim + w * score_stash_floats(G);
+  reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);
+  __syncthreads();  // (the list is there)
+  int used = 0;  // tiles of this wave in front of the sequence's
+  for (int e = 0; e < sc.n; ++e) {
+    const int4 e0 = sc.entry[2 * e], e1 = sc.entry[2 * e + 1];
+    const int h = __builtin_amdgcn_readfirstlane(e0.x), b = __builtin_amdgcn_readfirstlane(e0.y);
+    const int first = __builtin_amdgcn_readfirstlane(e0.z) + w, step = __builtin_amdgcn_readfirstlane(e0.w);
+    const int nTJ = __builtin_amdgcn_readfirstlane(e1.x), NJ = __builtin_amdgcn_readfirstlane(e1.y);
+    const int n_rec = __builtin_amdgcn_readfirstlane(e1.z), slot = __builtin_amdgcn_readfirstlane(e1.w);
+    const int KJ = first < nTJ ? (nTJ - first + step - 1) / step : 0;
+    const int bh = b * a.Hkv + h;
+    float* const lg = a.logits + (int64_t)bh * tile_f / kTile * a.ld_pos;
+    uint32_t* const hist = a.wg_hist + ((int64_t)bh * kSlotCap + slot) * kHistBins;
+    // wave w: the statistics of heads w, w + 4, ..., a record per lane
+    const uint64_t t0 = wall_clock64();
+    bool all = true;
+    for (int g = w; g < 16; g += kWaves) {
+      float M = -kNeg, c = 0.f;  // (heads past the group count for nothing)
+      if (g < G) {
+        const uint64_t* const met = a.met + ((int64_t)bh * G + g) * kSlotCap + min(lane, n_rec - 1);
+        uint64_t v = 0;
+        all = false;
+        while (a.met_ticks > 0) {
+          v = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          all = __all(v != 0);
+          if (all || wall_clock64() - t0 >= (uint64_t)a.met_ticks) break;
+          __builtin_amdgcn_s_sleep(2);
+        }
+        if (!all) break;
+        const float2 ml = lane < n_rec ? make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32) & 0x7fffffffu)) : make_float2(kNeg, 0.f);
+        c = group_stat(ml, a.alpha, G, M);
+      }
+      if (lane == 0) {
+        s_M[g] = M;
+        s_c[g] = c;
+      }
+    }
+    if (lane == 0) s_met[w] = all;
+    __syncthreads();
+    if ((s_met[0] & s_met[1] & s_met[2] & s_met[3]) == 0u) {  // workgroup-uniform
+      const int n_f4 = max(0, min(KJ, stay - used)) * (tile_f / 4);
+      for (int f = lane; f < n_f4; f += 64) {
+        const int i = f / (tile_f / 4), rem = f - i * (tile_f / 4);
+        *reinterpret_cast<float4*>(lg + (int64_t)(first + i * step) * tile_f + rem * 4) = *reinterpret_cast<const float4*>(stash + used * tile_f + f * 4);
+      }
+      if (tid == 0) {
+        *reinterpret_cast<int4*>(hist) = make_int4(first, step, nTJ, 0);
+        __hip_atomic_fetch_or(a.met_late + bh, 1ull << slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      used += KJ;
+      __syncthreads();
+      continue;
+    }
+    // eight tiles at a time, a quad of positions per lane
+    uint32_t* const keys = a.keys + (int64_t)bh * a.ld_pos;
+    auto score = [&](int k, int p, const float* src) {
+      if (k >= KJ || p >= NJ) return;
+      float f[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int g = 0; g < G; ++g) add_evidence(f, *reinterpret_cast<const float4*>(src + g * kTile), a.alpha, s_M[g], s_c[g]);
+      const uint32_t key[4] = {__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+      *reinterpret_cast<uint4*>(keys + p) = make_uint4(key[0], key[1], key[2], key[3]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (p + i < NJ) atomicAdd(&s_hist[bin_of(key[i])], 1u);
+    };
+    const int in_lds = max(0, min(KJ, stay - used));
+    if (in_lds < KJ) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the wave's other logits are written
+    for (int k0 = 0; k0 < KJ; k0 += 8) {
+      const int k = k0 + (lane >> 3), p = (first + k * step) * kTile + (lane & 7) * 4;
+      if (k < in_lds) score(k, p, stash + (used + k) * tile_f + (lane & 7) * 4);
+      else if (k < KJ) score(k, p, lg + (int64_t)(first + k * step) * tile_f + (lane & 7) * 4);
+    }
+    used += KJ;
+    __syncthreads();
+    reinterpret_cast<uint2*>(hist)[tid] = reinterpret_cast<const uint2*>(s_hist)[tid];
+    reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);  // for the next sequence, in front of its barrier
+  }
 }
 // One workgroup per (KV head, split, sequence) cell: wave w of split s takes tiles 4 s + w, 4 (s + n_split) + w, ...
 // The head is the grid's first index here and in the planned launch, for the Selector's sake (Place in sfi_select.hip); by itself the order is worth
@@ -1048,7 +1176,9 @@ __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(c
   const DenseShare sh{(int)blockIdx.y * kWaves, a.n_split * kWaves, 0, (int)blockIdx.y, a.n_split, 0, 0, 0, false};
   __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, BIG)];
   Tile T;
-  dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.x, blockIdx.z, T, s_patch);
+  Scored sc = scored_of(s_patch);
+  dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.x, blockIdx.z, T, s_patch, sc);
+  if (EXPOSE == 3) score_tail(a, sc, s_patch);
 }
 // The launch planned on the device: more than one sequence, every one with a length of its own (which only the device
 // knows) and, in the ragged step (sfi_mixed_step*), only some of them slow.  With a workgroup per cell the shares follow the
@@ -1118,7 +1248,7 @@ struct PlanCells {
 template <int EXPOSE, bool PAGED, bool GUESS, bool CELLS = false>
 __device__ __forceinline__ void planned_body(int j, int h, const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* q_len,
                                              uint32_t strides, int B, int W_max, float per_min, int n_sink, int recent_in, int len_cap,
-                                             const AttnArgs& a, float* lds, const PlanCells cells = {}) {
+                                             const AttnArgs& a, float* lds, Scored& sc, const PlanCells cells = {}) {
   const int lane = threadIdx.x & 63;
   const int ms = strides & 0xffff, fs = strides >> 16;
   // rows seen, recent window seen and tiles of sequence b (at least one tile: an empty context has a record too)
@@ -1184,7 +1314,7 @@ __device__ __forceinline__ void planned_body(int j, int h, const int32_t* ctx_le
     sh.n_rec = even;
     sh.have_k = !PAGED;
     if (slot_even == 0 && h == 0 && threadIdx.x == 0) a.seq_rec[b_even] = even;
-    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b_even, T, lds);
+    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b_even, T, lds, sc);
     return;
   }
   if (CELLS) {
@@ -1302,7 +1432,7 @@ __device__ __forceinline__ void planned_body(int j, int h, const int32_t* ctx_le
     int zero = 0;
     asm volatile("" : "+s"(zero));
     sh.have_k = false;
-    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b, T, lds, zero);
+    dense_body<EXPOSE, PAGED, true, false, true>(a, sh, h, b, T, lds, sc, zero);
     P += t_b;
     if (__builtin_amdgcn_readfirstlane(x1) >= share_start<CELLS>(p, j + 1)) return;
     do {  // (there is one: the list goes on)
@@ -1318,8 +1448,10 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
                                                                              uint32_t strides, int B, int W_max, float per_min, int n_sink,
                                                                              int recent_in, int len_cap, const AttnArgs a) {
   __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, true)];
+  Scored sc = scored_of(s_patch);
   planned_body<EXPOSE, PAGED, true>(blockIdx.y, blockIdx.x, ctx_len, is_slow, q_len, strides, B, W_max, per_min, n_sink, recent_in, len_cap, a,
-                                    s_patch);
+                                    s_patch, sc);
+  if (EXPOSE == 3) score_tail(a, sc, s_patch);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2226,12 +2358,12 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
 // ------------------------------------------------------------------------------------------------
 // BALANCED (balanced_shares): the shares are cut by what a workgroup has had already (PlanCells).  (Every head has its
 // workgroups with a cell in the same places: the heads' shares alternate as the cells do.)
-template <bool PAGED, bool WIDE, bool COMPACT, bool BALANCED>
+template <bool PAGED, bool WIDE, bool COMPACT, bool BALANCED, int EXPOSE>
 __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* recent_start,
                                                                       const int32_t* sel_idx, const uint32_t strides, const uint32_t shape, const int B,
                                                                       const int W_max, const int n_sink, const int n_split, const float per_min,
                                                                       const int row_in, const float cell_tiles, const AttnArgs f, const AttnArgs d) {
-  __shared__ __align__(16) float s_patch[kWaves * patch_floats(1, true)];
+  __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, true)];
   const uint32_t id = blockIdx.x, Hkv = shape & 0xffffu;
   // the cells in the order of fast_grid: row pairs side by side, n_split slots of them, then the next row.  row_in: the pairs in a
   // row, negative (tests): which of them a workgroup has changes from slot to slot, and with it the XCD of a pair's slots.
@@ -2249,8 +2381,10 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int3
     else gather_body<PAGED, WIDE, true>(cell, sel_idx, f.n_sel, ctx_len, recent_start, is_slow, (uint32_t)f.sel_stride, shape, n_sink, n_split, f, s_patch);
   }
   __syncthreads();  // the cell's results in LDS have been read
+  Scored sc = scored_of(s_patch);
   if (id < (uint32_t)W_max * Hkv)
-    planned_body<1, PAGED, false, BALANCED>(j, h, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent, d.len_cap, d, s_patch, cells);
+    planned_body<EXPOSE, PAGED, false, BALANCED>(j, h, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent, d.len_cap, d, s_patch, sc, cells);
+  if (EXPOSE == 3) score_tail(d, sc, s_patch);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2399,6 +2533,7 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
                      a.q_len, strides, a.plan_batch, a.plan_wgs, 1.0f / (float)a.plan_min, a.n_sink, a.recent, a.len_cap, a)
     if (a.logits == nullptr) SFI_PLANNED(0);
     else if (a.with_knorm) SFI_PLANNED(2);
+    else if (a.met != nullptr) SFI_PLANNED(3);
     else SFI_PLANNED(1);
 #undef SFI_PLANNED
     return;
@@ -2411,7 +2546,9 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
       return;
     }
   }
-  if (a.logits != nullptr && a.with_knorm && a.big_stash)
+  if (a.met != nullptr)
+    hipLaunchKernelGGL((attn_dense_kernel<3, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);
+  else if (a.logits != nullptr && a.with_knorm && a.big_stash)
     hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);
   else if (a.logits != nullptr && a.with_knorm)
     hipLaunchKernelGGL((attn_dense_kernel<2, PAGED>), grid, dim3(kAttnThreads), 0, s, a);
@@ -2444,10 +2581,15 @@ hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, bool balance
   // A cell's tile takes less than the list's, whose logits are exposed.  (0.8 / 0.9, us a step: 32 x 8192 rows, half slow, 125.1 / 131.2; 16 x
   // 16384..49152, half slow, 219.5 / 222.2; 16 x 16384..65536, budget 1024, a quarter slow, 148.5 / 146.0.)
   const float cell_tiles = 0.8f * std::min((float)f.n_sink + (float)f.sel_stride + (float)f.recent, (float)d.len_cap) / (float)(kTile * f.n_split);
-#define SFI_RAGGED(PAGED, WIDE, COMPACT, BALANCED)                                                                                                 \
-  hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT, BALANCED>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start, f.sel_idx,     \
-                     strides, fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min, f.handover == 2 ? -row : row,       \
-                     cell_tiles, f, d)
+#define SFI_RAGGED_E(PAGED, WIDE, COMPACT, BALANCED, EXPOSE)                                                                                       \
+  hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT, BALANCED, EXPOSE>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start,        \
+                     f.sel_idx, strides, fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min,                          \
+                     f.handover == 2 ? -row : row, cell_tiles, f, d)
+#define SFI_RAGGED(PAGED, WIDE, COMPACT, BALANCED)                                 \
+  do {                                                                             \
+    if (d.met != nullptr) SFI_RAGGED_E(PAGED, WIDE, COMPACT, BALANCED, 3);         \
+    else SFI_RAGGED_E(PAGED, WIDE, COMPACT, BALANCED, 1);                          \
+  } while (0)
 #define SFI_RAGGED_C(PAGED, COMPACT)                                   \
   do {                                                                 \
     if (f.G <= 8 && balanced) SFI_RAGGED(PAGED, true, COMPACT, true);  \
@@ -2461,6 +2603,7 @@ hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, bool balance
   else SFI_RAGGED_C(false, false);
 #undef SFI_RAGGED_C
 #undef SFI_RAGGED
+#undef SFI_RAGGED_E
   return hipGetLastError();
 }
 hipError_t launch_attn_compact(const AttnArgs& a, int B, int n_slots, hipStream_t s) {

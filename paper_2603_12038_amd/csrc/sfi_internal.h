@@ -29,6 +29,12 @@ constexpr int kPriorSeg = 1024;     // positions per workgroup of the full Selec
 constexpr int kFuseThreads = 1024;   // full Selector, second kernel: workgroup ...
 constexpr int kFuseSpan = 512;      // ... and positions (of every KV head) it takes
 constexpr int kHistBins = 512;     // bins of a segment's coarse key histogram (long J)
+constexpr int kScoreCap = 64;       // batch up to which the dense launch scores (a workgroup can meet that many sequences)
+constexpr int kScoreFloats = 38400;  // LDS of a dense workgroup that scores: the waves' outputs for the combine, then their logits
+constexpr int kScoreBurst = 4;       // tiles written together where a wave's part does not hold them all
+__host__ __device__ constexpr int score_stash_floats(int G) { return kScoreFloats / kWaves - G * kHeadDim; }  // of a wave
+__host__ __device__ constexpr int score_stay(int G) { return score_stash_floats(G) / (G * kTile) - kScoreBurst; }  // tiles of a wave that stay in LDS
+constexpr int kScoreWaitTicks = 6400;  // longest wait for a pair's other workgroups there (ticks of 10 ns)
 constexpr int kHistGroup = 64;      // segments whose histograms a launch of its own adds up ...
 constexpr int kHistGroupFrom = 128;  // ... of a J of more segments than this
 constexpr int kStateWords = 8;     // per (b, h) Selector state, see SelState
@@ -50,7 +56,7 @@ __device__ __forceinline__ void store_out4(float* out, int64_t elem, float4 v, b
 }
 
 // Per (sequence, KV head) Selector state words.
-enum SelState { ST_CAND = 0, ST_BIN1 = 1, ST_K1 = 2 };
+enum SelState { ST_BIN1 = 0, ST_K1 = 1 };
 
 // A window query under the causal mask (Eq. window_logits): the query sits at row q_len - 1 of a context that ends
 // at row L_end - 1, sees rows [0, q_len) only, and its evidence covers the part of the allowed set
@@ -72,10 +78,10 @@ struct Workspace {
   float* part;        // [B*Hq][kSlotCap][kPartStride]
   float* logits;      // [B*Hq][ld_pos]   J-relative positions
   uint32_t* keys;     // [B*Hkv][ld_pos]  fp32 bit pattern of the evidence f
-  uint32_t* cand;     // [B*Hkv][ld_pos][2]  keys falling into the threshold bin, each with its segment
+  uint32_t* cand;     // [B*Hkv][ld_pos]  keys falling into the threshold bin, each segment's from its first position on
   uint32_t* hist;     // [B*Hkv][n_seg_cap][kHistBins / 2]  coarse key histogram of each segment, 16-bit counters
   uint32_t* state;    // [B*Hkv][kStateWords]
-  uint32_t* segcnt;   // [B*Hkv][n_seg_cap]  keys of each segment above the threshold bin
+  uint32_t* segcnt;   // [B*Hkv][n_seg_cap]  keys of each segment in the threshold bin, and above it << 16
   int32_t* slow_list;   // [4 + 4 * B]  ragged step: the slow sequences as the dense launch planned them (see SelArgs)
   int32_t* seq_rec;     // [B]  records per query head a planned dense launch left for each sequence
   float2* jstat;      // [B*Hq]  J-only softmax statistics of each query head (slow step)
@@ -84,6 +90,9 @@ struct Workspace {
   double* segstat;    // [B*Hkv][n_seg_cap][kSegStats]  full Selector: sums for lambda* per kPriorSeg positions
   float* mu;          // [B*Hkv][ld]  windowed evidence: accumulator over the window's queries
   uint32_t* arrive;   // [B*Hkv][kWaves][kArriveStride]  workgroups of a split fast-step launch whose wave w has written its heads' records
+  uint64_t* met;      // [B*Hq][kSlotCap]  scoring in the dense launch: each workgroup's statistics over J (zero between steps)
+  unsigned long long* met_late;  // [B*Hkv]  ... mask of the records whose workgroup has not waited to the end (zero between steps)
+  uint32_t* wg_hist;  // [B*Hkv][kSlotCap][kHistBins]  ... key histogram of each workgroup; { first, step, end, - } of its tiles where masked
   int32_t* guard;     // [1]  SFI_GUARD_* bits of device-side inputs the kernels found out of range and clamped
   int64_t ld_pos;     // multiple of kSelSeg
   int32_t n_seg_cap;
@@ -119,6 +128,12 @@ struct AttnArgs {
                                  //   caller's workspace)
   int32_t cached_rows;           // evidence mode: 0 = all rows the launch may read fit the caches; else how many rows per head do
   float* logits;                 // dense mode, nullptr: do not expose logits
+  uint64_t* met;                 // dense mode, nullptr or: the launch scores (score_tail); Workspace::met
+  unsigned long long* met_late;  //   ... Workspace::met_late
+  uint32_t* wg_hist;             //   ... Workspace::wg_hist
+  uint32_t* keys;                //   ... Workspace::keys
+  float alpha;                   //   ... power-mean exponent of the evidence
+  int32_t met_ticks;             //   ... longest wait, in ticks of 10 ns
   int32_t with_knorm;            // dense mode: also expose the squared key norms (full Selector)
   int32_t dense_wide;            // dense mode: K rows read as whole 128-byte lines (query groups of at most 8 heads, flat cache)
   int32_t big_stash;             // dense mode with logits: the variant with the 32 KB stash per wave (one workgroup per CU)
@@ -224,7 +239,11 @@ struct SelArgs {
   float* merge_out;        // nullptr: nothing to merge here
   int32_t len_cap;         // the clamp the dense launch applied to ctx_len
   int32_t out_bf16;        // merge_out is bf16
+  uint64_t* met;           // nullptr or: the dense launch has scored; Workspace::met
+  unsigned long long* met_late;  //   ... Workspace::met_late
+  const uint32_t* wg_hist;  //   ... Workspace::wg_hist
   int32_t place_x;         // the launch's segments lie along the grid's first index, not its second (set by the launch)
+  int32_t n_place;         //   ... how many of them it has
 };
 
 hipError_t launch_attn_dense(const AttnArgs& a, int B, int n_slots, hipStream_t s);

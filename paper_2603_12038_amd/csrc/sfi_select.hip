@@ -16,21 +16,19 @@
 // barriers.  So the number of launches follows the size of J (launch rules in sfi_api.hip):
 //   one workgroup per pair does it all (sel_pick_kernel): from the logits where they are few, else from the keys that a
 //   scoring launch of many workgroups has left;
-//   long J: scoring with a coarse histogram per segment (stage 1), the keys of the threshold bin collected with the segment
-//   they came from (stage 2), the exact refinement among those few keys and the compaction (stage 3), a workgroup per
-//   segment each.  The segments' histograms are added up by their readers: device-scope atomics on one cache line are
+//   long J: scoring with a coarse histogram per segment (stage 1; the dense launch may have done it, with a histogram
+//   per workgroup: score_tail), the keys of the threshold bin collected in a run per segment (stage 2), the exact refinement
+//   among those few keys and the compaction (stage 3), a workgroup per segment each.  The segments' histograms are added up by their readers: device-scope atomics on one cache line are
 //   performed word by word, about 30 ns each, and a common histogram per pair cost a slow step 8 us (32768 positions) to
 //   25 us (131072 positions, full Selector).
 // In the kernels all loads that do not depend on another are requested together, uniform arguments at once, and
 // prefix sums and reductions over a wave run on the vector ALU (row shifts) instead of the LDS crossbar.
 #include "sfi_internal.h"
 #include "sfi_merge.h"
+#include "sfi_score.h"
 #include "sfi_wave.h"
 
 namespace sfi {
-
-__device__ __forceinline__ float fast_exp2s(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float fast_log2s(float x) { return __builtin_amdgcn_logf(x); }
 
 // ---- block primitives -----------------------------------------------------------------
 // Exclusive prefix sum of one value per thread over an NT-thread block; returns the exclusive
@@ -103,7 +101,7 @@ struct Place {
   int n;        // how many of them the launch has
 };
 __device__ __forceinline__ Place place_of(const SelArgs& a) {
-  return a.place_x != 0 ? Place{(int)blockIdx.y, (int)blockIdx.x, (int)gridDim.x} : Place{(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y};
+  return a.place_x != 0 ? Place{(int)blockIdx.y, (int)blockIdx.x, a.n_place} : Place{(int)blockIdx.x, (int)blockIdx.y, a.n_place};
 }
 struct Cell {
   int b, bh;
@@ -138,7 +136,7 @@ __device__ __forceinline__ uint32_t ksel_of(const SelArgs& a, int nJ) { return (
 // Uniform arguments every kernel here reads, asked for at once.
 __device__ __forceinline__ void ask(const SelArgs& a) {
   asm volatile("" ::"s"(a.slow_list), "s"(a.ctx_len), "s"(a.is_slow), "s"(a.ms), "s"(a.fs), "s"(a.Hkv), "s"(a.len_cap), "s"(a.recent),
-               "s"(a.n_sink), "s"(a.n_rec), "s"(a.seq_rec), "s"(a.ld_pos), "s"(a.keys), "s"(a.budget), "s"(a.place_x));
+               "s"(a.n_sink), "s"(a.n_rec), "s"(a.seq_rec), "s"(a.ld_pos), "s"(a.keys), "s"(a.budget), "s"(a.place_x), "s"(a.n_place));
 }
 // Runs body(cell, thread index) for the workgroup's cells of a head; a cell's LDS is free for the next behind a barrier.
 template <bool LIST, typename F>
@@ -161,17 +159,16 @@ __device__ __forceinline__ void for_cells(const SelArgs& a, int head, F body) {
 // J-only softmax statistics of the group's heads from the headers of the dense records (one per workgroup of the dense
 // launch): wave w takes heads w, w + n_waves, ..., a record per lane.  sM[g] = max of y over J, sc[g] = Z^(-alpha) / G;
 // valid after the next barrier.
-__device__ __forceinline__ void group_jstat(const SelArgs& a, const Cell& c, int n_waves, float* sM, float* sc) {
+__device__ __forceinline__ void group_jstat(const SelArgs& a, const Cell& cell, int n_waves, float* sM, float* sc) {
   const int lane = threadIdx.x & 63;
   for (int g = threadIdx.x >> 6; g < a.G; g += n_waves) {
-    const float* P = a.part + (int64_t)(c.bh * a.G + g) * kSlotCap * kPartStride;
-    const float2 ml = lane < c.n_rec ? *reinterpret_cast<const float2*>(P + (int64_t)lane * kPartStride + 2) : make_float2(kNeg, 0.f);
-    const float M = wave_max(ml.x);
-    const float Z = wave_sum_f(ml.y * fast_exp2s(ml.x - M));
+    const float* P = a.part + (int64_t)(cell.bh * a.G + g) * kSlotCap * kPartStride;
+    const float2 ml = lane < cell.n_rec ? *reinterpret_cast<const float2*>(P + (int64_t)lane * kPartStride + 2) : make_float2(kNeg, 0.f);
+    float M;
+    const float c = group_stat(ml, a.alpha, a.G, M);
     if (lane == 0) {
-      const float zpow = a.alpha == 1.0f ? Z : fast_exp2s(a.alpha * fast_log2s(Z));
       sM[g] = M;
-      sc[g] = 1.0f / ((float)a.G * zpow);
+      sc[g] = c;
     }
   }
 }
@@ -184,12 +181,6 @@ __device__ __forceinline__ void merge_head(const SelArgs& a, const Cell& c, int 
 // Logits of (b, h): tile-major, [tile of 32 positions][rows][32], rows = the G heads (and the key norms in mode 1).
 __device__ __forceinline__ float4 logits4(const float* lg, int rows, int p, int g) {
   return *reinterpret_cast<const float4*>(lg + (int64_t)(p >> 5) * (rows * kTile) + g * kTile + (p & 31));
-}
-__device__ __forceinline__ void add_evidence(float (&f)[4], const float4& l, float al, float M, float c) {
-  f[0] += c * fast_exp2s(al * (l.x - M));
-  f[1] += c * fast_exp2s(al * (l.y - M));
-  f[2] += c * fast_exp2s(al * (l.z - M));
-  f[3] += c * fast_exp2s(al * (l.w - M));
 }
 // mu of NQ quads of positions p[q]: sum over heads of sc[g] 2^(alpha (y_g - sM[g])) (Eq. selector_mu).  GT >= G heads are
 // loaded, all at once and without a branch; the columns past G repeat the last head and count for nothing: weight 0 and a
@@ -231,11 +222,7 @@ __device__ __forceinline__ void group_stats(const SelArgs& a, const Cell& c, int
   }
 }
 
-// The coarse histogram of a segment of kSelSeg keys: kHistBins bins of an eighth of an octave from 2^-63 up (keys outside
-// fall into the end bins), two 16-bit counters per word.
-__device__ __forceinline__ uint32_t bin_of(uint32_t key) {
-  return (uint32_t)min(max((int)(key >> 20) - (1024 - kHistBins), 0), kHistBins - 1);
-}
+// The coarse histogram of a segment of kSelSeg keys (bin_of), two 16-bit counters per word.
 __device__ __forceinline__ void hist_add4(uint32_t* s_hist, const uint32_t (&k)[4], int p, int nJ) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -747,21 +734,64 @@ __global__ __launch_bounds__(kSelThreads) void sel_group_kernel(const SelArgs a)
   });
 }
 
+// Records whose workgroup of the dense launch gave the wait up (score_tail): their tiles' logits are in memory, their
+// histograms are not there.  Each of the pair's workgroups scores all of them, for the histogram, and keeps the keys of its segment.  This
+// is no path to be on: it is there for a dense launch that had to share the chip.
+// h: kHistBins words of LDS for the histogram of these records; valid, and the keys in memory, behind this.
+__device__ __forceinline__ void late_records(const SelArgs& a, const Cell& c, const uint64_t late, const int p_lo, const int nJ, uint32_t* h,
+                                             float* s_M, float* s_c) {
+  const int tid = threadIdx.x, G = a.G;
+  const uint32_t* wh = a.wg_hist + (int64_t)c.bh * kSlotCap * kHistBins;
+  const float* lg = a.logits + (int64_t)c.bh * a.lg_rows * a.ld_pos;
+  uint32_t* keys = a.keys + (int64_t)c.bh * a.ld_pos;
+  group_stats<16>(a, c, kSelThreads / 64, s_M, s_c);
+  reinterpret_cast<uint2*>(h)[tid] = make_uint2(0u, 0u);
+  __syncthreads();
+  for (int sl = 0; sl < c.n_rec; ++sl) {
+    if ((late >> sl & 1u) == 0u) continue;
+    const int first = (int)wh[sl * kHistBins], step = (int)wh[sl * kHistBins + 1], end = (int)wh[sl * kHistBins + 2];
+    for (int k0 = 0; first + k0 * step < end; k0 += 8) {  // eight times four tiles, one per wave of the dense workgroup, eight quads each
+      const int t = first + (k0 + (tid >> 5)) * step + (tid >> 3 & 3), p = t * kTile + (tid & 7) * 4;
+      if (t >= end || p >= nJ) continue;
+      float f[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int g = 0; g < G; ++g) add_evidence(f, logits4(lg, a.lg_rows, p, g), a.alpha, s_M[g], s_c[g]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (p + i < nJ) atomicAdd(&h[bin_of(__float_as_uint(f[i]))], 1u);
+        if (p >= p_lo && p < p_lo + kSelSeg) __hip_atomic_store(keys + p + i, __float_as_uint(f[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the keys are out before another thread reads them
+  __syncthreads();
+}
+
 // ---- long J, stage 2: find the threshold bin, collect its keys ------------------------------------------
-// GROUPS: behind sel_group_kernel.
-template <bool LIST, bool GROUPS>
+// FROM: whose histograms are added up, FROM_SEGS, FROM_GROUPS (behind sel_group_kernel) or FROM_WGS: the dense launch has
+// scored, each of its workgroups (records) with a histogram of its own; the workgroups behind the segments' merge its records.
+enum { FROM_SEGS = 0, FROM_GROUPS = 1, FROM_WGS = 2 };
+template <bool LIST, int FROM>
 __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.hist), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap));
+  constexpr bool GROUPS = FROM == FROM_GROUPS, WGS = FROM == FROM_WGS;
+  if (WGS) asm volatile("" ::"s"(a.met_late), "s"(a.wg_hist), "s"(a.merge_out), "s"(a.part), "s"(a.G));
   const Place place = place_of(a);
   const int seg = place.i;
   const int p_lo = seg * kSelSeg;
   __shared__ __align__(16) uint32_t s_cnt[kSelThreads / 64][kHistBins];
-  __shared__ uint32_t s_res[2], s_before[kSelThreads / 64], s_all[kSelThreads / 64];
+  __shared__ uint32_t s_res[2];
   __shared__ uint32_t s_scr[2][kSelThreads / 64];
+  __shared__ __align__(16) uint32_t s_late[WGS ? kHistBins : 1];
+  __shared__ float s_M[16], s_c[16];
   for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     const int lane = tid & 63, w = tid >> 6;
     if (cell_off<LIST>(a, c)) return;
+    if (WGS && seg >= place.n - a.G) {  // workgroup-uniform
+      merge_head(a, c, seg - (place.n - a.G));
+      return;
+    }
     const int nJ = nJ_of(a, c);
     const uint32_t ksel = ksel_of(a, nJ);
     const int n_seg = (nJ + kSelSeg - 1) / kSelSeg;
@@ -791,8 +821,28 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
         cnt[4] += q1.x; cnt[5] += q1.y; cnt[6] += q1.z; cnt[7] += q1.w;
       }
     }
+    if (WGS) {
+      const uint64_t late = a.met_late[c.bh];
+      const uint32_t* wh = a.wg_hist + (int64_t)c.bh * kSlotCap * kHistBins;
+#pragma unroll 2
+      for (int sl = w; sl < c.n_rec; sl += kSelThreads / 64) {
+        const uint4* gh = reinterpret_cast<const uint4*>(wh + sl * kHistBins) + 2 * lane;
+        uint4 q0 = gh[0], q1 = gh[1];
+        if (late >> sl & 1u) q0 = q1 = make_uint4(0u, 0u, 0u, 0u);  // no histogram
+        cnt[0] += q0.x; cnt[1] += q0.y; cnt[2] += q0.z; cnt[3] += q0.w;
+        cnt[4] += q1.x; cnt[5] += q1.y; cnt[6] += q1.z; cnt[7] += q1.w;
+      }
+      if (late != 0) {  // uniform over the pair
+        late_records(a, c, late, p_lo, nJ, s_late, s_M, s_c);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          cnt[i] += w == 0 ? s_late[8 * lane + i] : 0u;
+          key[i] = __hip_atomic_load(a.keys + (int64_t)c.bh * a.ld_pos + p0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+    }
 #pragma unroll 4
-    for (int sg = w; !GROUPS && sg < n_seg; sg += kSelThreads / 64) {
+    for (int sg = w; FROM == FROM_SEGS && sg < n_seg; sg += kSelThreads / 64) {
       const uint4 q = reinterpret_cast<const uint4*>(seg_hist(a, c.bh, sg))[lane];
       cnt[0] += q.x & 0xffffu; cnt[1] += q.x >> 16; cnt[2] += q.y & 0xffffu; cnt[3] += q.y >> 16;
       cnt[4] += q.z & 0xffffu; cnt[5] += q.z >> 16; cnt[6] += q.w & 0xffffu; cnt[7] += q.w >> 16;
@@ -807,29 +857,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
       hv[i] = s_cnt[0][bin] + s_cnt[1][bin] + s_cnt[2][bin] + s_cnt[3][bin];
     }
     uint32_t* st = a.state + (int64_t)c.bh * kStateWords;
-    uint2* cand = reinterpret_cast<uint2*>(a.cand) + (int64_t)c.bh * a.ld_pos;  // (key, segment it came from)
+    uint32_t* cand = a.cand + (int64_t)c.bh * a.ld_pos + p_lo;  // the segment's own run
     find_kth_desc<kSelThreads, 2>(hv, kHistBins, ksel, s_res, s_scr[0]);
     const uint32_t bin1 = s_res[0];
-    // candidates of the segments before this one: where this segment's run starts in the pair's list
-    uint32_t before = 0, all = 0;
-    const int my_grp = seg / kHistGroup;
-    for (int gr = tid; GROUPS && gr < n_grp; gr += kSelThreads) {
-      const uint32_t x = group_hist(a, c.bh, gr)[bin1];
-      all += x;
-      before += gr < my_grp ? x : 0u;
-    }
-    for (int sg = (GROUPS ? my_grp * kHistGroup : 0) + tid; sg < (GROUPS ? seg : n_seg); sg += kSelThreads) {
-      const uint32_t v = seg_hist(a, c.bh, sg)[bin1 >> 1];
-      const uint32_t x = (bin1 & 1u) ? v >> 16 : v & 0xffffu;
-      if (!GROUPS) all += x;
-      before += sg < seg ? x : 0u;
-    }
-    before = wave_sum(before);
-    all = wave_sum(all);
-    if (lane == 0) {
-      s_before[w] = before;
-      s_all[w] = all;
-    }
     uint32_t mine = 0;  // bit i: key i falls into the threshold bin
     uint32_t above = 0; // keys of this thread in a higher bin: selected whatever the exact threshold is
 #pragma unroll
@@ -840,19 +870,18 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
         above += bin > bin1;
       }
     }
-    // One prefix sum over the workgroup gives both the segment's count of keys above the threshold bin (for
+    // One prefix sum over the workgroup gives the segment's counts of candidates and of keys above the threshold bin (for
     // the write stage's prefix) and every thread's place in the segment's run of candidates.
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kSelThreads>((uint32_t)__popc(mine) | (above << 16), s_scr[1], &total);  // (its barrier covers s_before)
+    const uint32_t ex = block_excl_scan<kSelThreads>((uint32_t)__popc(mine) | (above << 16), s_scr[1], &total);
     if (tid == 0) {
-      a.segcnt[(int64_t)c.bh * a.n_seg_cap + seg] = total >> 16;
-      if (seg == 0)
-        *reinterpret_cast<uint4*>(st) = make_uint4(s_all[0] + s_all[1] + s_all[2] + s_all[3], bin1, s_res[1], 0u);
+      a.segcnt[(int64_t)c.bh * a.n_seg_cap + seg] = total;
+      if (seg == 0) *reinterpret_cast<uint2*>(st) = make_uint2(bin1, s_res[1]);
     }
-    uint32_t base = s_before[0] + s_before[1] + s_before[2] + s_before[3] + (ex & 0xffffu);
+    uint32_t at = ex & 0xffffu;
 #pragma unroll
     for (int i = 0; i < kPer; ++i)
-      if (mine & (1u << i)) cand[base++] = make_uint2(key[i], (uint32_t)seg);
+      if (mine & (1u << i)) cand[at++] = key[i];
   });
 }
 
@@ -860,12 +889,13 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
 template <bool LIST>
 __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a) {
   ask(a);
-  asm volatile("" ::"s"(a.state), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap), "s"(a.sel_idx), "s"(a.n_sel));
+  asm volatile("" ::"s"(a.state), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap), "s"(a.sel_idx), "s"(a.n_sel), "s"(a.met), "s"(a.met_late));
   const Place place = place_of(a);
   const int seg = place.i;
   const int n_seg = place.n;
   __shared__ __align__(16) uint32_t s_h[2048 + 1024 + 1024];
-  __shared__ uint32_t s_res[2], s_gt[kSelThreads / 64], s_eq[kSelThreads / 64];
+  __shared__ uint32_t s_res[2], s_gt[kSelThreads / 64], s_eq[kSelThreads / 64], s_more[kSelThreads / 64];
+  static_assert(kSelThreads == 256, "lg_grp, s_more");
   __shared__ uint32_t s_scr[4][kSelThreads / 64];
   for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     if (cell_off<LIST>(a, c)) return;
@@ -877,13 +907,18 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
     const int p0 = p_lo + tid * kPer;
     const int64_t bh = c.bh;
     // Requested together: the state words, the thread's keys (the key row is padded to whole segments), the counts of the
-    // segments before this one, and the first kSpec candidates per thread, whether or not there are so many.
-    constexpr int kSpec = 4;
-    const uint4 st4 = *reinterpret_cast<const uint4*>(a.state + bh * kStateWords);
-    const uint2* cand = reinterpret_cast<const uint2*>(a.cand) + bh * a.ld_pos;
-    uint2 cd[kSpec];
+    // segments before this one, and kSpec candidates, whether or not there are so many: the threads go round the segments in
+    // equal groups, each with the first candidates of its segment.
+    constexpr int kSpec = 8;
+    const uint2 st2 = *reinterpret_cast<const uint2*>(a.state + bh * kStateWords);
+    const uint32_t* cand = a.cand + bh * a.ld_pos;
+    const uint32_t* segcnt = a.segcnt + bh * a.n_seg_cap;
+    const int lg_grp = max(0, __builtin_clz((n_seg - 1) | 1) - 24);  // log2 of the threads of a segment
+    const int c_seg = min(tid >> lg_grp, n_seg - 1), c_at = tid & ((1 << lg_grp) - 1), n_spec = kSpec << lg_grp;
+    uint32_t cd[kSpec];  // candidates c_at, c_at + group, ... of the segment: a short run leaves the later rounds empty for a whole wave
 #pragma unroll
-    for (int i = 0; i < kSpec; ++i) cd[i] = cand[tid + i * kSelThreads];
+    for (int i = 0; i < kSpec; ++i) cd[i] = cand[(int64_t)c_seg * kSelSeg + c_at + (i << lg_grp)];
+    int n_cd = (int)(segcnt[c_seg] & 0xffffu);
     uint32_t key[kPer];
     {
       const uint32_t* keys = a.keys + bh * a.ld_pos;
@@ -893,11 +928,17 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
       key[4] = hi4.x; key[5] = hi4.y; key[6] = hi4.z; key[7] = hi4.w;
     }
     uint32_t gt = 0, eq = 0;
-    for (int sg = tid; sg < seg; sg += kSelThreads) gt += a.segcnt[bh * a.n_seg_cap + sg];
+    for (int sg = tid; sg < seg; sg += kSelThreads) gt += segcnt[sg] >> 16;
     int32_t* out = a.sel_idx + bh * a.budget;
     // padding and n_sel, spread over the segments' workgroups
     for (int i = (int)ksel + seg * kSelThreads + tid; i < a.budget; i += n_seg * kSelThreads) out[i] = -1;
-    if (seg == 0 && tid == 0) a.n_sel[bh] = (int32_t)ksel;
+    if (seg == 0 && tid == 0) {
+      a.n_sel[bh] = (int32_t)ksel;
+      if (a.met != nullptr) a.met_late[bh] = 0;
+    }
+    if (seg == 0 && a.met != nullptr) {  // for the next dense launch
+      for (int i = tid; i < a.G * (kSlotCap / 2); i += kSelThreads) reinterpret_cast<uint4*>(a.met + bh * a.G * kSlotCap)[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
     if (ksel == 0u || p_lo >= nJ) return;
     const int p_hi = min(p_lo + kSelSeg, nJ);
     if (ksel == (uint32_t)nJ) {  // everything is selected
@@ -907,20 +948,32 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
     // Exact threshold tau and tie quota among the keys of the threshold bin (typically a few hundred): two LDS radix
     // passes, bits [19:10] then [9:0]; every workgroup of the pair does the same.  The end bins of the histogram
     // hold keys of any magnitude: a pass over bits [30:20] comes first.
-    const uint32_t n_cand = st4.x, bin1 = st4.y;
-    uint32_t k_left = st4.z, prefix = bin1 + (1024 - kHistBins);  // bits [30:20] of the threshold
-    static_assert(ST_CAND == 0 && ST_BIN1 == 1 && ST_K1 == 2, "one 16-byte load");
+    const uint32_t bin1 = st2.x;
+    uint32_t k_left = st2.y, prefix = bin1 + (1024 - kHistBins);  // bits [30:20] of the threshold
+    static_assert(ST_BIN1 == 0 && ST_K1 == 1, "one 8-byte load");
     const bool end_bin = bin1 == 0u || bin1 == (uint32_t)kHistBins - 1u;
+    const int n_run = (nJ + kSelSeg - 1) / kSelSeg;  // segments that have a run
+    const int n_first = min(n_run, kSelThreads >> lg_grp);  // segments whose first candidates are here
+    if (tid >> lg_grp >= n_first) n_cd = 0;
+    bool more = n_run > n_first || n_cd > n_spec;
     for (int i = tid; i < (2048 + 1024 + 1024) / 4; i += kSelThreads) reinterpret_cast<uint4*>(s_h)[i] = make_uint4(0u, 0u, 0u, 0u);
+    const uint64_t any = __ballot(more);
+    if ((tid & 63) == 0) s_more[tid >> 6] = any != 0;
     __syncthreads();
+    more = (s_more[0] | s_more[1] | s_more[2] | s_more[3]) != 0u;
     auto each_candidate = [&](auto f) {
 #pragma unroll
       for (int i = 0; i < kSpec; ++i)
-        if (tid + i * kSelThreads < n_cand) f(cd[i]);
-      for (uint32_t i = tid + kSpec * kSelThreads; i < n_cand; i += kSelThreads) f(cand[i]);
+        if (c_at + (i << lg_grp) < n_cd) f(cd[i], c_seg);
+      if (more) {  // the rest of longer runs: a wave takes a segment
+        for (int sg = tid >> 6; sg < n_run; sg += kSelThreads / 64) {
+          const int n = (int)(segcnt[sg] & 0xffffu);
+          for (int i = (sg < n_first ? n_spec : 0) + (tid & 63); i < n; i += 64) f(cand[(int64_t)sg * kSelSeg + i], sg);
+        }
+      }
     };
     if (end_bin) {  // uniform over the pair
-      each_candidate([&](const uint2& x) { atomicAdd(&s_h[2048 + ((x.x >> 20) & 2047u)], 1u); });
+      each_candidate([&](uint32_t x, int) { atomicAdd(&s_h[2048 + ((x >> 20) & 2047u)], 1u); });
       __syncthreads();
       find_kth_desc_lds<kSelThreads, 8>(s_h + 2048, 2048, k_left, s_res, s_scr[3]);
       prefix = s_res[0];
@@ -928,14 +981,14 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
       for (int i = tid; i < 1024 / 4; i += kSelThreads) reinterpret_cast<uint4*>(s_h + 2048)[i] = make_uint4(0u, 0u, 0u, 0u);
       __syncthreads();
     }
-    each_candidate([&](const uint2& x) {
-      if ((x.x >> 20) == prefix) atomicAdd(&s_h[(x.x >> 10) & 1023u], 1u);
+    each_candidate([&](uint32_t x, int) {
+      if ((x >> 20) == prefix) atomicAdd(&s_h[(x >> 10) & 1023u], 1u);
     });
     __syncthreads();
     find_kth_desc_lds<kSelThreads, 4>(s_h, 1024, k_left, s_res, s_scr[0]);
     const uint32_t top21 = prefix << 10 | s_res[0], k2 = s_res[1];
-    each_candidate([&](const uint2& x) {
-      if ((x.x >> 10) == top21) atomicAdd(&s_h[1024 + (x.x & 1023u)], 1u);
+    each_candidate([&](uint32_t x, int) {
+      if ((x >> 10) == top21) atomicAdd(&s_h[1024 + (x & 1023u)], 1u);
     });
     __syncthreads();
     find_kth_desc_lds<kSelThreads, 4>(s_h + 1024, 1024, k2, s_res, s_scr[1]);
@@ -943,10 +996,10 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
     const uint32_t take = s_res[1];
     // keys selected in the segments before this one: those above the threshold bin (counted by stage 2)
     // plus the bin's own keys above tau; and the ties before this segment
-    each_candidate([&](const uint2& x) {
-      if ((int)x.y < seg) {
-        gt += x.x > tau;
-        eq += x.x == tau;
+    each_candidate([&](uint32_t x, int sg) {
+      if (sg < seg) {
+        gt += x > tau;
+        eq += x == tau;
       }
     });
     gt = wave_sum(gt);
@@ -998,6 +1051,7 @@ static unsigned z_of(const SelArgs& a, int B, int n_wgs) {
 constexpr int kMaxPlaceY = 65535;
 static dim3 place_grid(SelArgs* a, int n_place, unsigned z) {
   a->place_x = n_place > kMaxPlaceY;
+  a->n_place = n_place;
   return a->place_x ? dim3(n_place, a->Hkv, z) : dim3(a->Hkv, n_place, z);
 }
 static int ceil_seg(int nJ, int per) { return nJ > 0 ? (nJ + per - 1) / per : 1; }
@@ -1116,8 +1170,15 @@ hipError_t launch_sel_pick(SelArgs a, int B, int nJ, int src, hipStream_t s) {
 }
 hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kSelSeg);
-  const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv)), block(kSelThreads);
   const bool list = a.slow_list != nullptr;
+  const dim3 block(kSelThreads);
+  if (a.met != nullptr) {  // one more workgroup per query head
+    const dim3 grid = place_grid(&a, n_seg + a.G, z_of(a, B, (n_seg + a.G) * a.Hkv));
+    if (list) hipLaunchKernelGGL((sel_cand_kernel<true, FROM_WGS>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sel_cand_kernel<false, FROM_WGS>), grid, block, 0, s, a);
+    return hipGetLastError();
+  }
+  const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv));
   if (n_seg > kHistGroupFrom) {
     const int n_grp = (n_seg + kHistGroup - 1) / kHistGroup;
     SelArgs ag = a;
@@ -1126,12 +1187,12 @@ hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s) {
     else hipLaunchKernelGGL(sel_group_kernel<false>, ggrid, block, 0, s, ag);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (list) hipLaunchKernelGGL((sel_cand_kernel<true, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((sel_cand_kernel<false, true>), grid, block, 0, s, a);
+    if (list) hipLaunchKernelGGL((sel_cand_kernel<true, FROM_GROUPS>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sel_cand_kernel<false, FROM_GROUPS>), grid, block, 0, s, a);
   } else if (list) {
-    hipLaunchKernelGGL((sel_cand_kernel<true, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((sel_cand_kernel<true, FROM_SEGS>), grid, block, 0, s, a);
   } else {
-    hipLaunchKernelGGL((sel_cand_kernel<false, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((sel_cand_kernel<false, FROM_SEGS>), grid, block, 0, s, a);
   }
   return hipGetLastError();
 }

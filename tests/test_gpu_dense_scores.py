@@ -1,0 +1,120 @@
+"""Scoring in the dense launch (sfi_set_dense_scores) against the scoring launch: the same keys, so the same bits in every output.
+One sequence, planned launches with equal and with ragged lengths, more logits than a workgroup's LDS holds, several sequences in
+one workgroup, and waits that go to the end, that end at once (every record scored by the Selector) or after a tick (some of them)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+N_SINK, RECENT, BUDGET = 4, 64, 700
+
+
+def _setup(B, Hkv, G, lens, page, alpha):
+    import torch
+    from paper_2603_12038_amd.binding import SfiContext
+    import paper_2603_12038_amd as sfi
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B * 1000 + Hkv * 10 + G)
+    n = max(lens)
+    per = (n + 15) // 16
+    shape = (B * per, Hkv, 16, 128) if page else (B, Hkv, n, 128)
+    K, V = (torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(2))
+    ctx = SfiContext(B, Hkv * G, Hkv, n, BUDGET, N_SINK, RECENT, K, V, alpha=alpha, page_size=page, page_layout="htd")
+    table = None
+    if page:
+        table = torch.randperm(B * per, generator=gen, device="cuda").to(torch.int32).view(B, per)
+        sfi.sfi_set_block_table(ctx.handle, table, table.numel())
+    q = torch.empty((2, B, Hkv * G, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    return sfi, ctx, K, V, table, q, torch.tensor(lens, dtype=torch.int32, device="cuda")
+
+
+# (batch, KV heads, heads a group, lengths, page, alpha)
+SHAPES = [(1, 2, 1, [16384 + 68 + 1], 0, 1.0),                 # the shortest J with three Selector launches
+          (1, 8, 16, [60000], 0, 0.5),                         # 15 tiles a wave, of which LDS holds 10
+          (3, 8, 5, [40000, 100, 17003], 16, 1.0),             # a short sequence between two borders, paged
+          (4, 4, 4, [33000] * 4, 0, 1.0),                      # equal lengths: whole workgroups
+          (2, 7, 2, [50000, 20001], 0, 0.5),                   # heads that do not divide the units; workgroups of a pair on several XCDs
+          (6, 8, 8, [30000, 0, 66, 60001, 69, 31], 0, 1.0),    # nothing to rank, one position, more sequences than borders
+          (2, 1, 4, [131072, 70000], 0, 1.0)]                  # more records than one trip of the merge
+
+
+@pytest.mark.parametrize("B,Hkv,G,lens,page,alpha", SHAPES)
+@pytest.mark.parametrize("ragged", [False, True])
+def test_same_bits_as_the_scoring_launch(B, Hkv, G, lens, page, alpha, ragged):
+    import torch
+    if ragged and B == 1:
+        pytest.skip("a ragged step of one sequence is not planned")
+    print(f"[gpu-dense-scores] B={B} Hkv={Hkv} G={G} lens={lens} page={page} ragged={ragged}", flush=True)
+    sfi, ctx, K, V, table, q, c = _setup(B, Hkv, G, lens, page, alpha)
+    h, n = ctx.handle, max(lens)
+    rs = (c - RECENT).clamp(min=N_SINK)
+    flag_sets = [[0], [0, B - 1], list(range(B))] if ragged else [None]
+    sel0 = torch.full((B, Hkv, BUDGET), -1, dtype=torch.int32, device="cuda")
+    nsel0 = torch.zeros((B, Hkv), dtype=torch.int32, device="cuda")
+    try:
+        for slow in flag_sets:
+            want = {}
+            # two queries in turn: keys, histograms or statistics of the step before are wrong ones
+            for i, mode in enumerate((0, 0, 4, 4, 2, 2, 3, 3, 1, 1, 4, 4)):
+                sfi.sfi_set_dense_scores(h, mode)
+                out = torch.full((B, Hkv * G, 128), float("nan"), device="cuda")
+                sel, nsel = sel0.clone(), nsel0.clone()
+                if slow is None:
+                    sfi.sfi_slow_step(h, q[i % 2], K, V, c, n, BUDGET, out, sel, nsel)
+                else:
+                    flags = torch.zeros(B, dtype=torch.uint8)
+                    flags[slow] = 1
+                    sfi.sfi_mixed_step(h, q[i % 2], K, V, flags.cuda(), c, rs, n, BUDGET, out, sel, nsel)
+                torch.cuda.synchronize()
+                got = (out, sel, nsel)
+                if mode == 0:
+                    want[i % 2] = got
+                    live = [b for b in (range(B) if slow is None else slow) if lens[b] > N_SINK + RECENT]
+                    assert all(int(nsel[b].min()) == min(BUDGET, lens[b] - N_SINK - RECENT) for b in live)
+                for name, a, b in zip(("out", "sel", "n_sel"), got, want[i % 2]):
+                    assert torch.equal(a, b) or (name == "out" and torch.equal(a.nan_to_num(7.0), b.nan_to_num(7.0))), (mode, name, slow)
+        assert sfi.sfi_device_status(h) == 0
+        with pytest.raises(RuntimeError):
+            sfi.sfi_set_dense_scores(h, 5)
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+
+
+def test_graph_replays():
+    """The statistics are back at zero behind every step, in a graph's replays and in eager steps between them."""
+    import torch
+    sfi, ctx, K, V, table, q, c = _setup(2, 8, 4, [40000, 33001], 0, 1.0)
+    h = ctx.handle
+    try:
+        sfi.sfi_set_dense_scores(h, 4)
+        out = torch.zeros((2, 32, 128), device="cuda")
+        sel = torch.zeros((2, 8, BUDGET), dtype=torch.int32, device="cuda")
+        nsel = torch.zeros((2, 8), dtype=torch.int32, device="cuda")
+        qq = q[0].clone()
+
+        def step():
+            sfi.sfi_slow_step(h, qq, K, V, c, 40000, BUDGET, out, sel, nsel)
+
+        want = []
+        for t in range(2):
+            qq.copy_(q[t])
+            step()
+            torch.cuda.synchronize()
+            want.append([x.clone() for x in (out, sel, nsel)])
+        s = torch.cuda.Stream()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            step()
+            step()
+        for i in range(6):
+            qq.copy_(q[i % 2])
+            out.fill_(float("nan"))
+            sel.fill_(-7)
+            if i % 3 == 2:
+                step()
+            else:
+                g.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip((out, sel, nsel), want[i % 2])), i
+    finally:
+        ctx.close()
