@@ -113,7 +113,10 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->met = (uint64_t*)take((size_t)(B * Hq) * kSlotCap * sizeof(uint64_t));
   ws->met_late = (unsigned long long*)take((size_t)(B * Hkv) * sizeof(unsigned long long));
   ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears them all
-  ws->wg_hist = B <= kScoreCap && !full && c->max_ctx > kPickMax ? (uint32_t*)take((size_t)(B * Hkv) * kSlotCap * kHistBins * sizeof(uint32_t)) : nullptr;
+  const bool scores = B <= kScoreCap && c->max_ctx > kPickMax;
+  ws->met_tiles = scores ? (int4*)take((size_t)(B * Hkv) * kSlotCap * sizeof(int4)) : nullptr;
+  ws->wg_hist = scores && !full ? (uint32_t*)take((size_t)(B * Hkv) * kSlotCap * kHistBins * sizeof(uint32_t)) : nullptr;
+  ws->wg_stat = scores && full ? (double*)take((size_t)(B * Hkv) * kSlotCap * kSegStats * sizeof(double)) : nullptr;
   ws->prior = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->fbuf = full ? (float*)take((size_t)(B * Hkv) * ld * sizeof(float)) : nullptr;
   ws->segstat = full ? (double*)take((size_t)(B * Hkv) * n_seg * kSegStats * sizeof(double)) : nullptr;
@@ -281,21 +284,35 @@ bool merges_in_kernel(const sfi_ctx* x, int n_split, int max_len) {
 // Scoring launch / in the dense launch, us a slow step, 8 KV heads and G = 4 where not given: 4 x 32768 rows 98.4 / 94.4; 8 x 20011..24571, G = 5, paged 141.3 / 132.5;
 // 1 x 131072 102.8 / 99.3, G = 16 (three times LDS) 138.4 / 133.7; 8 x 32768, 2 KV heads 59.5 / 56.0; 16 x 20000..60000 511.0 / 504.5;
 // 2 x 20000..30000, G = 8, 4 KV heads (7 tiles) 37.8 / 37.6; ragged, 32 x 16384..65536, G = 8, two slow 126.6 / 118.0, 16 x 20000..60000, half slow 271.5 / 246.0, all 517 / 511.
+// full Selector, 1 x 131072 116.2 / 112.0, 4 x 32768 115.3 / 110.7, 8 x 20000..30000, G = 5, paged 187.6 / 177.9 (ragged steps and a J of more
+// than 262144 positions keep the launch there).
 // Beyond the lines: 1 x 17000 (4 tiles) 28.6 / 28.7, 2 KV heads 24.2 / 24.8; ragged, 4 x 17000, one slow 35.5 / 36.3, 12 x 5003..30011, one slow, compact 49.9 / 50.2;
 // more than four times LDS: 16 x 20000..60000, G = 8 573.2 / 578.6, 16 x 20000..30000, G = 16 407.8 / 410.7.
 bool score_in_dense(const sfi_ctx* x, const AttnArgs& a, int max_len, bool mixed) {
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink, B = x->cfg.batch, Hkv = x->cfg.n_kv_heads;
-  if (x->dense_scores == 0 || x->ws.wg_hist == nullptr || nJ <= kPickMax || x->dense_wide || (a.plan_batch == 0 && B > 1)) return false;
+  if (x->dense_scores == 0 || x->ws.met_tiles == nullptr || nJ <= kPickMax || x->dense_wide || (a.plan_batch == 0 && B > 1)) return false;
   const int wgs = a.plan_batch > 0 ? std::max(a.plan_wgs, a.plan_even * B) : a.n_split;
-  if (wgs * Hkv > x->n_cu) return false;
+  if (wgs * Hkv > x->n_cu || (x->cfg.selector_mode == 1 && (mixed || nJ > kHistGroupFrom * kSelSeg))) return false;
   if (x->dense_scores > 1) return true;
   const int64_t tiles = (int64_t)((max_len + kTile - 1) / kTile) * (mixed ? 1 : B) * Hkv, waves = (int64_t)kWaves * x->n_cu;
-  return tiles >= (mixed ? 8 : 5) * waves && (mixed || tiles <= 4 * score_stay(x->G) * waves);
+  return tiles >= (mixed ? 8 : 5) * waves && (mixed || tiles <= 4 * score_stay(x->G, x->G + x->cfg.selector_mode) * waves);
+}
+PriorArgs prior_args_of(const sfi_ctx* x) {
+  const sfi_config& c = x->cfg;
+  return PriorArgs{c.gamma, c.beta, c.p, c.eta, c.eps > 0.f ? c.eps : 1e-8f};
 }
 void set_dense_scores(const sfi_ctx* x, AttnArgs* a) {
   a->met = x->ws.met;
   a->met_late = x->ws.met_late;
+  a->met_tiles = x->ws.met_tiles;
   a->wg_hist = x->ws.wg_hist;
+  a->wg_stat = x->ws.wg_stat;
+  a->fbuf = x->ws.fbuf;
+  a->prior = x->ws.prior;
+  a->hist = x->ws.hist;
+  a->n_seg_cap = x->ws.n_seg_cap;
+  a->inv_alpha = 1.0f / x->alpha;
+  a->prior_args = prior_args_of(x);
   a->keys = x->ws.keys;
   a->alpha = x->alpha;
   a->met_ticks = x->dense_scores == 2 ? 0 : x->dense_scores == 3 ? 1 : kScoreWaitTicks;
@@ -434,7 +451,7 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
   memset(s, 0, sizeof(*s));
   const sfi_config& c = x->cfg;
   s->jstat = x->ws.jstat; s->logits = x->ws.logits; s->keys = x->ws.keys; s->cand = x->ws.cand;
-  s->wg_hist = x->ws.wg_hist;
+  s->met_tiles = x->ws.met_tiles; s->wg_hist = x->ws.wg_hist; s->wg_stat = x->ws.wg_stat;
   s->hist = x->ws.hist; s->state = x->ws.state; s->segcnt = x->ws.segcnt;
   s->ctx_len = ctx_len; s->is_slow = is_slow; s->sel_idx = sel_idx; s->n_sel = n_sel;
   s->ms = 1; s->fs = 1;
@@ -442,7 +459,8 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
   s->Hq = c.n_q_heads; s->Hkv = c.n_kv_heads; s->G = x->G;
   s->n_sink = c.n_sink; s->recent = c.recent; s->n_rec = n_split; s->budget = budget;
   s->prior = x->ws.prior; s->fbuf = x->ws.fbuf; s->segstat = x->ws.segstat;
-  s->gamma = c.gamma; s->beta = c.beta; s->p = c.p; s->eta = c.eta; s->lambda_clip = c.lambda_clip;
+  s->prior_args = prior_args_of(x);
+  s->lambda_clip = c.lambda_clip;
   s->alpha_soft = c.alpha_soft; s->alpha_cross = c.alpha_cross;
   s->inv_temp = c.temp > 0.f ? 1.0f / c.temp : 1.0f;
   s->eps = c.eps > 0.f ? c.eps : 1e-8f;
@@ -479,7 +497,7 @@ int run_selector(sfi_ctx* x, const SelArgs& sa, int max_len, hipStream_t st, boo
   else if (!full && !windowed && sa.part != nullptr && pick && sel_pick_scores(nJ, x->G, B * x->cfg.n_kv_heads, x->n_cu)) src = 1;  // ... the logits
   if (src == 0) {
     StageTimer t(x, st, SFI_STAGE_SCORE);
-    if (sa.met != nullptr) {}  // the dense launch has scored: nothing between the stage's events
+    if (sa.met != nullptr && !full) {}  // the dense launch has scored: nothing between the stage's events
     else if (full) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
     else if (windowed) SFI_TRY(launch_sel_finalize(sa, B, nJ, st));
     else SFI_TRY(launch_sel_score(sa, B, nJ, !pick, st));

@@ -778,7 +778,7 @@ struct ListWalk {
 // dense kernel
 // ------------------------------------------------------------------------------------------------
 // PAGED: K / V are block pools addressed through the sequence's block table.
-// EXPOSE 1: also write y over J for the Selector; 2: y and the squared key norms; 3: y stays in LDS as far as it fits, for score_tail.
+// EXPOSE 1: also write y over J for the Selector; 2: y and the squared key norms; 3, 4: y (and the norms) stay in LDS as far as they fit, for score_tail.
 // BIG: twice the logits stash per wave, which leaves room for one workgroup per compute unit only
 // (launches where every sequence is dense, and the planned launch, run one per unit anyway; the ragged
 // step's launch with a workgroup per cell keeps two, although that kernel spills 6 to 26 of its 256 registers: with one,
@@ -797,7 +797,7 @@ struct DenseShare {
 // front, then their stashes, which outlive it (score_tail), then the list of the sequences the workgroup has had.
 constexpr int kScoreEntryFloats = 8;
 constexpr int patch_floats(int expose, bool big) {
-  return expose == 3 ? (kScoreFloats + kScoreCap * kScoreEntryFloats) / kWaves : expose == 0 ? 16 * kHeadDim : big ? 2 * kStashFloats : kStashFloats;
+  return expose >= 3 ? (kScoreFloats + kScoreCap * kScoreEntryFloats) / kWaves : expose == 0 ? 16 * kHeadDim : big ? 2 * kStashFloats : kStashFloats;
 }
 struct Scored {
   int4* entry;  // two words per sequence: { head, sequence, first, step }, { end of J's tiles, |J|, records, own record }
@@ -809,6 +809,7 @@ template <int EXPOSE, bool PAGED, bool BIG, bool WIDE, bool PLANNED>
 __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& sh, const int h, const int b, Tile& T, float* lds, Scored& sc, const int tid_bias = 0) {
   constexpr int kStash = BIG ? 2 * kStashFloats : kStashFloats;
   constexpr int kPatch = patch_floats(EXPOSE, BIG);
+  constexpr bool SCORE = EXPOSE >= 3, NORM = EXPOSE == 2 || EXPOSE == 4;
   // everything uniform is asked for at once (the first argument load of a wave takes 0.4 us)
   asm volatile("" ::"s"(a.q), "s"(a.K), "s"(a.V), "s"(a.k_sb), "s"(a.k_sh), "s"(a.k_st), "s"(a.v_sb), "s"(a.v_sh), "s"(a.v_st),
                "s"(a.ctx_len), "s"(a.is_slow), "s"(a.q_len), "s"(a.Hq), "s"(a.Hkv), "s"(a.G), "s"(a.n_sink), "s"(a.recent),
@@ -948,17 +949,17 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   // memory counter.  It parks them in its LDS stash, laid out as they go to memory, and writes the
   // stash out in one burst when it is full and once more after its last tile, when nothing is
   // left to wait for.
-  // With EXPOSE == 2 a tile has one more row: ||k_j||^2 of its 32 positions, for the key-norm factor of
+  // With NORM a tile has one more row: ||k_j||^2 of its 32 positions, for the key-norm factor of
   // the Selector's prior (Eq. selector_prior_kn).
-  const int rows_exp = G + (EXPOSE == 2 ? 1 : 0);
-  float* stash = EXPOSE == 3 ? lds + kWaves * G * kHeadDim + w * score_stash_floats(G) : lds + w * kPatch;
+  const int rows_exp = G + (NORM ? 1 : 0);
+  float* stash = SCORE ? lds + kWaves * G * kHeadDim + w * score_stash_floats(G) : lds + w * kPatch;
   float* lg_base = EXPOSE != 0 ? a.logits + (int64_t)bh * rows_exp * a.ld_pos : nullptr;
   const int tile_f4 = rows_exp * (kTile / 4);        // float4 per tile
   // EXPOSE 3: the first tiles stay where they are, for score_tail; what goes to memory lies behind them.
-  const int stay = EXPOSE == 3 ? score_stay(G) : 0;
-  const int stash_cap = EXPOSE == 3 ? kScoreBurst : kStash / (rows_exp * kTile);  // tiles the stash holds until they are written
-  int n_stashed = 0, k_flushed = EXPOSE == 3 ? max(0, stay - sc.used) : 0;
-  const float* const burst = stash + stay * (G * kTile);
+  const int stay = SCORE ? score_stay(G, rows_exp) : 0;
+  const int stash_cap = SCORE ? kScoreBurst : kStash / (rows_exp * kTile);  // tiles the stash holds until they are written
+  int n_stashed = 0, k_flushed = SCORE ? max(0, stay - sc.used) : 0;
+  const float* const burst = stash + stay * (rows_exp * kTile);
   auto flush_stash = [&]() {
     __builtin_amdgcn_wave_barrier();
     const int n_f4 = n_stashed * tile_f4;
@@ -989,7 +990,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
     if (WIDE) qk_products_wide(T, qreg, s4);  // the refill of the K half below goes out before the lane exchanges
     else qk_phase(T, qreg, a.scale_log2, y);
     float k2a = 0.f, k2b = 0.f;
-    if (EXPOSE == 2) knorm_phase(T, jg, n, k2a, k2b);
+    if (NORM) knorm_phase(T, jg, n, k2a, k2b);
     int pra = 0, prb = 0;
     if (!kRefill) {
     } else if (PAGED) {
@@ -1006,10 +1007,10 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
       qk_join_wide(s4, a.scale_log2, y);
     }
     if (EXPOSE != 0 && inJ) {  // positions past |J| land in the padding of the last tile, never used
-      const bool stays = EXPOSE == 3 && sc.used + k < stay;
-      float* st = stash + (EXPOSE == 3 ? min(sc.used + k, stay) + n_stashed : n_stashed) * (rows_exp * kTile);
+      const bool stays = SCORE && sc.used + k < stay;
+      float* st = stash + (SCORE ? min(sc.used + k, stay) + n_stashed : n_stashed) * (rows_exp * kTile);
       stage_logits<WIDE>(st, y, jg, n, G);
-      if (EXPOSE == 2 && jg == (n >> 2)) {
+      if (NORM && jg == (n >> 2)) {
         st[G * kTile + n] = k2a;
         st[G * kTile + 16 + n] = k2b;
       }
@@ -1052,14 +1053,14 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   }
   WgOut o = wg_out_of(a, bh);
   o.n_split = sh.n_rec;
-  if (EXPOSE == 3) o.met = a.met + (int64_t)bh * G * kSlotCap;
+  if (SCORE) o.met = a.met + (int64_t)bh * G * kSlotCap;
   if (PLANNED && sh.n_rec == 1) {
     o.out_direct = o.out_merge;
     o.out_merge = nullptr;
   }
-  finish_wg<EXPOSE == 3 ? 2 : EXPOSE != 0>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), lds, EXPOSE == 3 ? G * kHeadDim : kPatch, m_j,
+  finish_wg<SCORE ? 2 : EXPOSE != 0>(o, head0, G, sh.slot, acc, m_run, rows_sum(l_run), lds, SCORE ? G * kHeadDim : kPatch, m_j,
                                            EXPOSE != 0 ? rows_sum(l_j) : 0.f);
-  if (EXPOSE == 3) {
+  if (SCORE) {
     sc.used += KJ;
     if (tid == 0) {
       sc.entry[2 * sc.n] = make_int4(h, b, sh.first, sh.step);
@@ -1069,7 +1070,7 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
   }
   report_guard(a.guard, bad);
 }
-// ---- scoring in the dense launch (EXPOSE 3) ------------------------------------------------------------------
+// ---- scoring in the dense launch (EXPOSE 3, 4) ------------------------------------------------------------------
 // The evidence of a position is a sum over the group's heads, each over its own normaliser (Eq. selector_mu), and those are known
 // when all workgroups of a pair have left their statistics.  A workgroup that has done its share therefore waits for
 // the pair's others and turns the logits, which it still has in LDS, into keys and a histogram of its own: a G-th of the
@@ -1082,12 +1083,16 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
 // marks its record in the pair's mask and ends; the next launch then scores that record's tiles (late_records).
 // Nothing of this is decided before all of the workgroup's own shares are done and out, so no workgroup waits for one that waits.
 // The keys are bit for bit what the scoring launch (sel_score_kernel) makes of the same logits.
+// FULL: evidence, prior and their sums for the full Selector, as sel_prior_kernel leaves them (the sums per workgroup, not per segment).
+template <bool FULL>
 __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, float* lds) {
-  __shared__ __align__(16) uint32_t s_hist[kHistBins];
+  __shared__ __align__(16) uint32_t s_hist[FULL ? 2 * kAttnThreads : kHistBins];
+  __shared__ double s_sums[kWaves][kSegStats];
   __shared__ float s_M[16], s_c[16];
   __shared__ uint32_t s_met[kWaves];
+  static_assert(kHistBins == 2 * kAttnThreads, "two bins, or one word of a segment's histogram, per thread");
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int G = a.G, tile_f = G * kTile, stay = score_stay(G);
+  const int G = a.G, rows = G + (FULL ? 1 : 0), tile_f = rows * kTile, stay = score_stay(G, rows);
   const float* const stash = lds + kWaves * G * kHeadDim + w * score_stash_floats(G);
   reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);
   __syncthreads();  // (the list is there)
@@ -1101,9 +1106,10 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
     const int KJ = first < nTJ ? (nTJ - first + step - 1) / step : 0;
     const int bh = b * a.Hkv + h;
     float* const lg = a.logits + (int64_t)bh * tile_f / kTile * a.ld_pos;
-    uint32_t* const hist = a.wg_hist + ((int64_t)bh * kSlotCap + slot) * kHistBins;
     // wave w: the statistics of heads w, w + 4, ..., a record per lane
     const uint64_t t0 = wall_clock64();
+    if (FULL)  // (the next launch adds to the segments' histograms)
+      for (int sg = slot; sg * kSelSeg < NJ; sg += n_rec) a.hist[((int64_t)bh * a.n_seg_cap + sg) * (kHistBins / 2) + tid] = 0u;
     bool all = true;
     for (int g = w; g < 16; g += kWaves) {
       float M = -kNeg, c = 0.f;  // (heads past the group count for nothing)
@@ -1135,7 +1141,7 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
         *reinterpret_cast<float4*>(lg + (int64_t)(first + i * step) * tile_f + rem * 4) = *reinterpret_cast<const float4*>(stash + used * tile_f + f * 4);
       }
       if (tid == 0) {
-        *reinterpret_cast<int4*>(hist) = make_int4(first, step, nTJ, 0);
+        a.met_tiles[(int64_t)bh * kSlotCap + slot] = make_int4(first, step, nTJ, 0);
         __hip_atomic_fetch_or(a.met_late + bh, 1ull << slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       used += KJ;
@@ -1143,14 +1149,25 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
       continue;
     }
     // eight tiles at a time, a quad of positions per lane
-    uint32_t* const keys = a.keys + (int64_t)bh * a.ld_pos;
-    auto score = [&](int k, int p, const float* src) {
-      if (k >= KJ || p >= NJ) return;
+    const int64_t row = (int64_t)bh * a.ld_pos;
+    const Prior prior(a.prior_args, NJ);
+    double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    auto score = [&](int p, const float* src) {
+      if (p >= NJ) return;
       float f[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
       for (int g = 0; g < G; ++g) add_evidence(f, *reinterpret_cast<const float4*>(src + g * kTile), a.alpha, s_M[g], s_c[g]);
+      if (FULL) {
+        const float4 k4 = *reinterpret_cast<const float4*>(src + G * kTile);
+        const float rr[4] = {prior(k4.x, p), prior(k4.y, p + 1), prior(k4.z, p + 2), prior(k4.w, p + 3)};
+        evidence_of_mu(f, a.alpha, a.inv_alpha, p, NJ);
+        add_sums(sums, f, rr);
+        *reinterpret_cast<float4*>(a.fbuf + row + p) = make_float4(f[0], f[1], f[2], f[3]);
+        *reinterpret_cast<float4*>(a.prior + row + p) = make_float4(rr[0], rr[1], rr[2], rr[3]);
+        return;
+      }
       const uint32_t key[4] = {__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
-      *reinterpret_cast<uint4*>(keys + p) = make_uint4(key[0], key[1], key[2], key[3]);
+      *reinterpret_cast<uint4*>(a.keys + row + p) = make_uint4(key[0], key[1], key[2], key[3]);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (p + i < NJ) atomicAdd(&s_hist[bin_of(key[i])], 1u);
@@ -1159,13 +1176,27 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
     if (in_lds < KJ) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the wave's other logits are written
     for (int k0 = 0; k0 < KJ; k0 += 8) {
       const int k = k0 + (lane >> 3), p = (first + k * step) * kTile + (lane & 7) * 4;
-      if (k < in_lds) score(k, p, stash + (used + k) * tile_f + (lane & 7) * 4);
-      else if (k < KJ) score(k, p, lg + (int64_t)(first + k * step) * tile_f + (lane & 7) * 4);
+      if (k < in_lds) score(p, stash + (used + k) * tile_f + (lane & 7) * 4);
+      else if (k < KJ) score(p, lg + (int64_t)(first + k * step) * tile_f + (lane & 7) * 4);
     }
     used += KJ;
+    if (FULL) {
+#pragma unroll
+      for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
+      if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < kSegStats; ++i) s_sums[w][i] = sums[i];
+      }
+    }
     __syncthreads();
-    reinterpret_cast<uint2*>(hist)[tid] = reinterpret_cast<const uint2*>(s_hist)[tid];
-    reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);  // for the next sequence, in front of its barrier
+    if (FULL) {
+      if (tid < kSegStats)
+        a.wg_stat[((int64_t)bh * kSlotCap + slot) * kSegStats + tid] = (s_sums[0][tid] + s_sums[1][tid]) + (s_sums[2][tid] + s_sums[3][tid]);
+      __syncthreads();
+    } else {
+      reinterpret_cast<uint2*>(a.wg_hist + ((int64_t)bh * kSlotCap + slot) * kHistBins)[tid] = reinterpret_cast<const uint2*>(s_hist)[tid];
+      reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);  // for the next sequence, in front of its barrier
+    }
   }
 }
 // One workgroup per (KV head, split, sequence) cell: wave w of split s takes tiles 4 s + w, 4 (s + n_split) + w, ...
@@ -1178,7 +1209,7 @@ __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(c
   Tile T;
   Scored sc = scored_of(s_patch);
   dense_body<EXPOSE, PAGED, BIG, WIDE, false>(a, sh, blockIdx.x, blockIdx.z, T, s_patch, sc);
-  if (EXPOSE == 3) score_tail(a, sc, s_patch);
+  if (EXPOSE >= 3) score_tail<EXPOSE == 4>(a, sc, s_patch);
 }
 // The launch planned on the device: more than one sequence, every one with a length of its own (which only the device
 // knows) and, in the ragged step (sfi_mixed_step*), only some of them slow.  With a workgroup per cell the shares follow the
@@ -1451,7 +1482,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_dense_planned_kernel(con
   Scored sc = scored_of(s_patch);
   planned_body<EXPOSE, PAGED, true>(blockIdx.y, blockIdx.x, ctx_len, is_slow, q_len, strides, B, W_max, per_min, n_sink, recent_in, len_cap, a,
                                     s_patch, sc);
-  if (EXPOSE == 3) score_tail(a, sc, s_patch);
+  if (EXPOSE >= 3) score_tail<EXPOSE == 4>(a, sc, s_patch);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2384,7 +2415,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int3
   Scored sc = scored_of(s_patch);
   if (id < (uint32_t)W_max * Hkv)
     planned_body<EXPOSE, PAGED, false, BALANCED>(j, h, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent, d.len_cap, d, s_patch, sc, cells);
-  if (EXPOSE == 3) score_tail(d, sc, s_patch);
+  if (EXPOSE >= 3) score_tail<EXPOSE == 4>(d, sc, s_patch);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2532,6 +2563,7 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
   hipLaunchKernelGGL((attn_dense_planned_kernel<EXPOSE, PAGED>), pgrid, dim3(kAttnThreads), 0, s, a.ctx_len, a.is_slow, \
                      a.q_len, strides, a.plan_batch, a.plan_wgs, 1.0f / (float)a.plan_min, a.n_sink, a.recent, a.len_cap, a)
     if (a.logits == nullptr) SFI_PLANNED(0);
+    else if (a.with_knorm && a.met != nullptr) SFI_PLANNED(4);
     else if (a.with_knorm) SFI_PLANNED(2);
     else if (a.met != nullptr) SFI_PLANNED(3);
     else SFI_PLANNED(1);
@@ -2546,7 +2578,9 @@ static void launch_dense_t(const AttnArgs& a, dim3 grid, hipStream_t s) {
       return;
     }
   }
-  if (a.met != nullptr)
+  if (a.met != nullptr && a.with_knorm)
+    hipLaunchKernelGGL((attn_dense_kernel<4, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);
+  else if (a.met != nullptr)
     hipLaunchKernelGGL((attn_dense_kernel<3, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);
   else if (a.logits != nullptr && a.with_knorm && a.big_stash)
     hipLaunchKernelGGL((attn_dense_kernel<2, PAGED, true>), grid, dim3(kAttnThreads), 0, s, a);

@@ -33,7 +33,7 @@ constexpr int kScoreCap = 64;       // batch up to which the dense launch scores
 constexpr int kScoreFloats = 38400;  // LDS of a dense workgroup that scores: the waves' outputs for the combine, then their logits
 constexpr int kScoreBurst = 4;       // tiles written together where a wave's part does not hold them all
 __host__ __device__ constexpr int score_stash_floats(int G) { return kScoreFloats / kWaves - G * kHeadDim; }  // of a wave
-__host__ __device__ constexpr int score_stay(int G) { return score_stash_floats(G) / (G * kTile) - kScoreBurst; }  // tiles of a wave that stay in LDS
+__host__ __device__ constexpr int score_stay(int G, int rows) { return score_stash_floats(G) / (rows * kTile) - kScoreBurst; }  // tiles of a wave that stay in LDS
 constexpr int kScoreWaitTicks = 6400;  // longest wait for a pair's other workgroups there (ticks of 10 ns)
 constexpr int kHistGroup = 64;      // segments whose histograms a launch of its own adds up ...
 constexpr int kHistGroupFrom = 128;  // ... of a J of more segments than this
@@ -74,6 +74,11 @@ __device__ __forceinline__ void window_view(const int32_t* q_len, int b, int L_e
 
 constexpr int kListCap = 1024;  // sequences a dense launch is planned on the device for (attn_dense_planned_kernel)
 
+// Parameters of the full Selector's prior.
+struct PriorArgs {
+  float gamma, beta, p, eta, eps;
+};
+
 struct Workspace {
   float* part;        // [B*Hq][kSlotCap][kPartStride]
   float* logits;      // [B*Hq][ld_pos]   J-relative positions
@@ -92,7 +97,9 @@ struct Workspace {
   uint32_t* arrive;   // [B*Hkv][kWaves][kArriveStride]  workgroups of a split fast-step launch whose wave w has written its heads' records
   uint64_t* met;      // [B*Hq][kSlotCap]  scoring in the dense launch: each workgroup's statistics over J (zero between steps)
   unsigned long long* met_late;  // [B*Hkv]  ... mask of the records whose workgroup has not waited to the end (zero between steps)
-  uint32_t* wg_hist;  // [B*Hkv][kSlotCap][kHistBins]  ... key histogram of each workgroup; { first, step, end, - } of its tiles where masked
+  int4* met_tiles;    // [B*Hkv][kSlotCap]  ... { first, step, end, - } of the tiles of the records in the mask
+  uint32_t* wg_hist;  // [B*Hkv][kSlotCap][kHistBins]  ... mode 0: key histogram of each workgroup
+  double* wg_stat;    // [B*Hkv][kSlotCap][kSegStats]  ... full Selector: each workgroup's sums for lambda*
   int32_t* guard;     // [1]  SFI_GUARD_* bits of device-side inputs the kernels found out of range and clamped
   int64_t ld_pos;     // multiple of kSelSeg
   int32_t n_seg_cap;
@@ -130,8 +137,16 @@ struct AttnArgs {
   float* logits;                 // dense mode, nullptr: do not expose logits
   uint64_t* met;                 // dense mode, nullptr or: the launch scores (score_tail); Workspace::met
   unsigned long long* met_late;  //   ... Workspace::met_late
+  int4* met_tiles;               //   ... Workspace::met_tiles
   uint32_t* wg_hist;             //   ... Workspace::wg_hist
   uint32_t* keys;                //   ... Workspace::keys
+  double* wg_stat;               //   ... full Selector: Workspace::wg_stat, fbuf, prior, hist, n_seg_cap, and the prior's parameters
+  float* fbuf;
+  float* prior;
+  uint32_t* hist;
+  int32_t n_seg_cap;
+  float inv_alpha;
+  PriorArgs prior_args;
   float alpha;                   //   ... power-mean exponent of the evidence
   int32_t met_ticks;             //   ... longest wait, in ticks of 10 ns
   int32_t with_knorm;            // dense mode: also expose the squared key norms (full Selector)
@@ -224,7 +239,8 @@ struct SelArgs {
   float* prior;
   float* fbuf;
   double* segstat;
-  float gamma, beta, p, eta, lambda_clip, alpha_soft, alpha_cross, inv_temp, eps;
+  PriorArgs prior_args;
+  float lambda_clip, alpha_soft, alpha_cross, inv_temp, eps;
   int32_t nms_radius;
   float alpha, inv_alpha;  // power-mean exponent of the evidence and its reciprocal
   // windowed evidence
@@ -241,7 +257,9 @@ struct SelArgs {
   int32_t out_bf16;        // merge_out is bf16
   uint64_t* met;           // nullptr or: the dense launch has scored; Workspace::met
   unsigned long long* met_late;  //   ... Workspace::met_late
-  const uint32_t* wg_hist;  //   ... Workspace::wg_hist
+  const int4* met_tiles;   //   ... Workspace::met_tiles
+  const uint32_t* wg_hist;  //   ... Workspace::wg_hist (mode 0)
+  const double* wg_stat;   //   ... Workspace::wg_stat (full Selector)
   int32_t place_x;         // the launch's segments lie along the grid's first index, not its second (set by the launch)
   int32_t n_place;         //   ... how many of them it has
 };

@@ -27,4 +27,42 @@ __device__ __forceinline__ uint32_t bin_of(uint32_t key) {
   return (uint32_t)min(max((int)(key >> 20) - (1024 - kHistBins), 0), kHistBins - 1);
 }
 
+// The unnormalised prior pi_kn * pi_pos of position pc (Eqs. selector_prior_kn, selector_u, selector_prior_pos) from its squared key norm.
+struct Prior {
+  float gamma, beta2, p, eta, eps, inv_D;
+  int nJ;
+  // u(j) = p / D, 1 - u(j) + eps = ((|J| - 1 - p) + eps) / D + eps with D = |J| - 1 + eps: the second
+  // form keeps full relative precision near the tail, where 1 - u cancels.
+  __device__ __forceinline__ Prior(const PriorArgs& a, int nJ_)
+      : gamma(a.gamma), beta2(a.beta * 1.4426950408889634f), p(a.p), eta(a.eta), eps(a.eps), inv_D(1.0f / ((float)(nJ_ - 1) + a.eps)), nJ(nJ_) {}
+  __device__ __forceinline__ float operator()(float k2, int pc) const {
+    const float kn = -gamma * fast_log2s(sqrtf(k2) + eps);
+    const float u = (float)pc * inv_D;
+    const float omu = ((float)(nJ - 1 - pc) + eps) * inv_D + eps;
+    const float up = u > 0.f ? fast_exp2s(p * fast_log2s(u)) : 0.f;
+    const float pos = -beta2 * up + eta * fast_log2s(omu);
+    return pc < nJ ? fast_exp2s(kn) * fast_exp2s(pos) : 0.f;
+  }
+};
+// Evidence (of mu) and prior of a quad of positions added to the sums for lambda*.
+__device__ __forceinline__ void add_sums(double (&sums)[kSegStats], const float (&f)[4], const float (&rr)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double fd = (double)f[i], rd = (double)rr[i];
+    sums[0] += fd;
+    sums[1] += rd;
+    sums[2] += fd * fd;
+    sums[3] += fd * rd;
+    sums[4] += rd * rd;
+  }
+}
+// f = mu^(1/alpha) up to the normalisation done with the sums (Eq. selector_f); nothing past J.
+__device__ __forceinline__ void evidence_of_mu(float (&f)[4], float alpha, float inv_alpha, int p, int nJ) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (alpha != 1.0f) f[i] = fast_exp2s(inv_alpha * fast_log2s(f[i]));
+    f[i] = p + i < nJ ? f[i] : 0.f;
+  }
+}
+
 }  // namespace sfi

@@ -359,7 +359,7 @@ template <bool FROM_MU, bool LIST, bool FLAGS, int GT>
 __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.logits), "s"(a.part), "s"(a.G), "s"(a.alpha), "s"(a.jstat), "s"(a.prior), "s"(a.segstat), "s"(a.n_seg_cap),
-               "s"(a.merge_out), "s"(a.gamma), "s"(a.beta), "s"(a.p), "s"(a.eta), "s"(a.eps));
+               "s"(a.merge_out), "s"(a.prior_args.gamma), "s"(a.prior_args.beta), "s"(a.prior_args.p), "s"(a.prior_args.eta), "s"(a.prior_args.eps));
   const Place place = place_of(a);
   const int seg = place.i;
   const int G = a.G, rows = G + 1;
@@ -384,23 +384,8 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
     if (p_lo >= nJ) return;
     // (the next launch adds to the segments' histograms)
     if (seg % (kSelSeg / kPriorSeg) == 0) seg_hist(a, c.bh, seg / (kSelSeg / kPriorSeg))[tid] = 0u;
-    // u(j) = p / D, 1 - u(j) + eps = ((|J| - 1 - p) + eps) / D + eps with D = |J| - 1 + eps: the second
-    // form keeps full relative precision near the tail, where 1 - u cancels.
-    const float D = (float)(nJ - 1) + a.eps;
-    const float inv_D = 1.0f / D;
-    const float beta2 = a.beta * 1.4426950408889634f;
-    const float k2[4] = {k4.x, k4.y, k4.z, k4.w};
-    float rr[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int pc = p[0] + i;
-      const float kn = -a.gamma * fast_log2s(sqrtf(k2[i]) + a.eps);  
-      const float u = (float)pc * inv_D;
-      const float omu = ((float)(nJ - 1 - pc) + a.eps) * inv_D + a.eps;
-      const float up = u > 0.f ? fast_exp2s(a.p * fast_log2s(u)) : 0.f;
-      const float pos = -beta2 * up + a.eta * fast_log2s(omu);
-      rr[i] = pc < nJ ? fast_exp2s(kn) * fast_exp2s(pos) : 0.f;
-    }
+    const Prior prior(a.prior_args, nJ);
+    const float rr[4] = {prior(k4.x, p[0]), prior(k4.y, p[0] + 1), prior(k4.z, p[0] + 2), prior(k4.w, p[0] + 3)};
     if (!FROM_MU) __syncthreads();
     float f4[1][4];
     float(&f)[4] = f4[0];
@@ -409,21 +394,9 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
     } else {
       evidence<1, GT>(f4, lq, a.alpha, s_jM, s_jc);
     }
-    if (a.alpha != 1.0f) {  // f = mu^(1/alpha) up to the normalisation done with the segment sums (Eq. selector_f)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) f[i] = fast_exp2s(a.inv_alpha * fast_log2s(f[i]));
-    }
+    evidence_of_mu(f, a.alpha, a.inv_alpha, p[0], nJ);
     double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f[i] = p[0] + i < nJ ? f[i] : 0.f;
-      const double fd = (double)f[i], rd = (double)rr[i];
-      sums[0] += fd;
-      sums[1] += rd;
-      sums[2] += fd * fd;
-      sums[3] += fd * rd;
-      sums[4] += rd * rd;
-    }
+    add_sums(sums, f, rr);
     if (p[0] < nJ) {
       *reinterpret_cast<float4*>(a.fbuf + (int64_t)c.bh * a.ld_pos + p[0]) = make_float4(f[0], f[1], f[2], f[3]);
       *reinterpret_cast<float4*>(a.prior + (int64_t)c.bh * a.ld_pos + p[0]) = make_float4(rr[0], rr[1], rr[2], rr[3]);
@@ -449,9 +422,12 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
 // rows, took 27 us for a J of 131072 positions of 8 heads).  More than eight heads: the scores are worked out twice, once
 // for the head softmax's running maximum and sum, once for the keys.
 // HIST: also the heads' histograms, added to their segment's (kSelSeg / kFuseSpan workgroups share one).
-template <bool HIST, bool LIST>
+// WGS: the dense launch has scored (score_tail), and the sums are its workgroups'.  Records whose workgroup gave the wait up are worked off here, by every workgroup for itself: the sums of
+// all of them, the evidence and the prior of its own columns.  (As late_records: no path to be on.)
+template <bool HIST, bool LIST, bool WGS>
 __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a) {
   ask(a);
+  if (WGS) asm volatile("" ::"s"(a.met_late), "s"(a.wg_stat));
   asm volatile("" ::"s"(a.fbuf), "s"(a.prior), "s"(a.segstat), "s"(a.n_seg_cap), "s"(a.nms_radius), "s"(a.eps), "s"(a.alpha_soft),
                "s"(a.alpha_cross), "s"(a.inv_temp), "s"(a.lambda_clip));
   constexpr int kGroup = 8;
@@ -460,7 +436,65 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
   __shared__ __align__(16) float s_zn[kGroup][kFuseSpan];
   __shared__ float s_mx[kFuseSpan], s_sum[kFuseSpan];
   __shared__ float s_w[2][kGroup];  // weights of f and of the prior
+  __shared__ double s_lsum[WGS ? kGroup : 1][kSegStats];
+  __shared__ double s_lred[WGS ? kFuseThreads / 64 : 1][kSegStats];
+  __shared__ float s_lM[16], s_lc[16];
   const int Hkv = a.Hkv, rad = a.nms_radius;
+  // records that were left: sums to s_lsum, evidence and prior of this workgroup's columns to memory
+  auto late_columns = [&](int h0, int nh, int nJ, int p_lo, int tid, const Cell& c) {
+    const Prior prior(a.prior_args, nJ);
+    const int rows = a.lg_rows;
+#pragma unroll 1
+    for (int hh = 0; hh < nh; ++hh) {
+      Cell ch = c;
+      ch.bh = c.bh + h0 + hh;
+      const uint64_t left = a.met_late[ch.bh];
+      if (left == 0) continue;  // uniform
+      __syncthreads();
+      group_stats<16>(a, ch, kFuseThreads / 64, s_lM, s_lc);
+      __syncthreads();
+      const float* lg = a.logits + (int64_t)ch.bh * rows * a.ld_pos;
+      const int64_t row = (int64_t)ch.bh * a.ld_pos;
+      double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+      for (int sl = 0; sl < c.n_rec; ++sl) {
+        if ((left >> sl & 1u) == 0u) continue;
+        const int4 tiles = a.met_tiles[(int64_t)ch.bh * kSlotCap + sl];
+#pragma unroll 1
+        for (int k0 = 0; tiles.x + k0 * tiles.y < tiles.z; k0 += kFuseThreads / 32) {
+          const int t = tiles.x + (k0 + (tid >> 5)) * tiles.y + (tid >> 3 & 3), p = t * kTile + (tid & 7) * 4;
+          if (t >= tiles.z || p >= nJ) continue;
+          float f[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int g = 0; g < a.G; ++g) add_evidence(f, logits4(lg, rows, p, g), a.alpha, s_lM[g], s_lc[g]);
+          const float4 k4 = logits4(lg, rows, p, a.G);
+          const float rr[4] = {prior(k4.x, p), prior(k4.y, p + 1), prior(k4.z, p + 2), prior(k4.w, p + 3)};
+          evidence_of_mu(f, a.alpha, a.inv_alpha, p, nJ);
+          add_sums(sums, f, rr);
+          if (p + 3 >= p_lo - rad && p < p_lo + kFuseSpan + rad) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              __hip_atomic_store(a.fbuf + row + p + i, f[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(a.prior + row + p + i, rr[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
+      if ((tid & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < kSegStats; ++i) s_lred[tid >> 6][i] = sums[i];
+      __syncthreads();
+      if (tid < kSegStats) {
+        double t = 0.0;
+        for (int i = 0; i < kFuseThreads / 64; ++i) t += s_lred[i][tid];
+        s_lsum[hh][tid] = t;
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the columns are out before another thread reads them
+    __syncthreads();
+  };
   const int zs = kFuseSpan + 2 * rad;
   for_cells<LIST>(a, 0, [&](const Cell& c, const int tid) {  // (c.bh is the sequence's first pair)
     const int lane = tid & 63, w = tid >> 6;
@@ -470,18 +504,32 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
     const int n_here = min(kFuseSpan, nJ - p_lo);
     // scores after Soft-NMS of heads h0 .. h0 + nh - 1 -> s_zn
     auto scores = [&](int h0, int nh) {
-      const int n_seg = (nJ + kPriorSeg - 1) / kPriorSeg;
+      const int n_seg = WGS ? c.n_rec : (nJ + kPriorSeg - 1) / kPriorSeg;
+      uint64_t late = 0;  // lane: records of head h0 + lane that were left
+      if (WGS) late = a.met_late[c.bh + h0 + min(lane, nh - 1)];
       float fb[kGroup], pr[kGroup];  // this thread's column (position p_lo - rad + tid) of all heads, requested together
       {
         const int64_t o = (int64_t)(c.bh + h0) * a.ld_pos + min(max(p_lo - rad + tid, 0), nJ - 1);
 #pragma unroll
         for (int hh = 0; hh < kGroup; ++hh) {
-          fb[hh] = a.fbuf[o + (int64_t)min(hh, nh - 1) * a.ld_pos];
-          pr[hh] = a.prior[o + (int64_t)min(hh, nh - 1) * a.ld_pos];
+          const int64_t at = o + (int64_t)min(hh, nh - 1) * a.ld_pos;
+          fb[hh] = a.fbuf[at];
+          pr[hh] = a.prior[at];
+        }
+        if (WGS && __ballot(late != 0) != 0) {  // uniform over the sequence
+          late_columns(h0, nh, nJ, p_lo, tid, c);
+#pragma unroll
+          for (int hh = 0; hh < kGroup; ++hh) {  // (behind the stores of other threads)
+            const int64_t at = o + (int64_t)min(hh, nh - 1) * a.ld_pos;
+            fb[hh] = __hip_atomic_load(a.fbuf + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            pr[hh] = __hip_atomic_load(a.prior + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
         }
       }
       if (w < nh) {  // a wave per head: lambda* in double precision, in a fixed order
-        const double* st = a.segstat + (int64_t)(c.bh + h0 + w) * a.n_seg_cap * kSegStats;
+        const double* st = WGS ? a.wg_stat + (int64_t)(c.bh + h0 + w) * kSlotCap * kSegStats : a.segstat + (int64_t)(c.bh + h0 + w) * a.n_seg_cap * kSegStats;
+        // records without sums
+        const uint64_t off = WGS ? (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(late >> 32), __builtin_amdgcn_readfirstlane(w)) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)late, __builtin_amdgcn_readfirstlane(w)) : 0;
         double tot[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
         for (int s0 = lane; s0 - lane < n_seg; s0 += 128) {  // two segments' sums in flight per lane
           double t0[kSegStats], t1[kSegStats];
@@ -491,8 +539,11 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
             t1[i] = st[(int64_t)min(s0 + 64, n_seg - 1) * kSegStats + i];
           }
 #pragma unroll
-          for (int i = 0; i < kSegStats; ++i) tot[i] += (s0 < n_seg ? t0[i] : 0.0) + (s0 + 64 < n_seg ? t1[i] : 0.0);
+          for (int i = 0; i < kSegStats; ++i) tot[i] += (s0 < n_seg && (!WGS || (off >> s0 & 1u) == 0u) ? t0[i] : 0.0) + (s0 + 64 < n_seg ? t1[i] : 0.0);
         }
+        if (WGS && off != 0 && lane == 0)
+#pragma unroll
+          for (int i = 0; i < kSegStats; ++i) tot[i] += s_lsum[w][i];
 #pragma unroll
         for (int i = 0; i < kSegStats; ++i) tot[i] = wave_sum_d(tot[i]);
         // f and r normalised to sum 1: |f|^2 = tot2 / F^2, f.r = tot3 / (F R), |r|^2 = tot4 / R^2
@@ -741,7 +792,6 @@ __global__ __launch_bounds__(kSelThreads) void sel_group_kernel(const SelArgs a)
 __device__ __forceinline__ void late_records(const SelArgs& a, const Cell& c, const uint64_t late, const int p_lo, const int nJ, uint32_t* h,
                                              float* s_M, float* s_c) {
   const int tid = threadIdx.x, G = a.G;
-  const uint32_t* wh = a.wg_hist + (int64_t)c.bh * kSlotCap * kHistBins;
   const float* lg = a.logits + (int64_t)c.bh * a.lg_rows * a.ld_pos;
   uint32_t* keys = a.keys + (int64_t)c.bh * a.ld_pos;
   group_stats<16>(a, c, kSelThreads / 64, s_M, s_c);
@@ -749,7 +799,8 @@ __device__ __forceinline__ void late_records(const SelArgs& a, const Cell& c, co
   __syncthreads();
   for (int sl = 0; sl < c.n_rec; ++sl) {
     if ((late >> sl & 1u) == 0u) continue;
-    const int first = (int)wh[sl * kHistBins], step = (int)wh[sl * kHistBins + 1], end = (int)wh[sl * kHistBins + 2];
+    const int4 tiles = a.met_tiles[(int64_t)c.bh * kSlotCap + sl];
+    const int first = tiles.x, step = tiles.y, end = tiles.z;
     for (int k0 = 0; first + k0 * step < end; k0 += 8) {  // eight times four tiles, one per wave of the dense workgroup, eight quads each
       const int t = first + (k0 + (tid >> 5)) * step + (tid >> 3 & 3), p = t * kTile + (tid & 7) * 4;
       if (t >= end || p >= nJ) continue;
@@ -769,14 +820,16 @@ __device__ __forceinline__ void late_records(const SelArgs& a, const Cell& c, co
 
 // ---- long J, stage 2: find the threshold bin, collect its keys ------------------------------------------
 // FROM: whose histograms are added up, FROM_SEGS, FROM_GROUPS (behind sel_group_kernel) or FROM_WGS: the dense launch has
-// scored, each of its workgroups (records) with a histogram of its own; the workgroups behind the segments' merge its records.
-enum { FROM_SEGS = 0, FROM_GROUPS = 1, FROM_WGS = 2 };
+// scored, each of its workgroups (records) with a histogram of its own.  FROM_WGS, FROM_SEGS_MERGE (the full Selector behind such a
+// launch): the workgroups behind the segments' merge the dense records.
+enum { FROM_SEGS = 0, FROM_GROUPS = 1, FROM_WGS = 2, FROM_SEGS_MERGE = 3 };
 template <bool LIST, int FROM>
 __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.hist), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap));
-  constexpr bool GROUPS = FROM == FROM_GROUPS, WGS = FROM == FROM_WGS;
-  if (WGS) asm volatile("" ::"s"(a.met_late), "s"(a.wg_hist), "s"(a.merge_out), "s"(a.part), "s"(a.G));
+  constexpr bool GROUPS = FROM == FROM_GROUPS, WGS = FROM == FROM_WGS, MERGE = WGS || FROM == FROM_SEGS_MERGE;
+  if (WGS) asm volatile("" ::"s"(a.met_late), "s"(a.wg_hist));
+  if (MERGE) asm volatile("" ::"s"(a.merge_out), "s"(a.part), "s"(a.G));
   const Place place = place_of(a);
   const int seg = place.i;
   const int p_lo = seg * kSelSeg;
@@ -788,7 +841,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
   for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     const int lane = tid & 63, w = tid >> 6;
     if (cell_off<LIST>(a, c)) return;
-    if (WGS && seg >= place.n - a.G) {  // workgroup-uniform
+    if (MERGE && seg >= place.n - a.G) {  // workgroup-uniform
       merge_head(a, c, seg - (place.n - a.G));
       return;
     }
@@ -842,7 +895,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
       }
     }
 #pragma unroll 4
-    for (int sg = w; FROM == FROM_SEGS && sg < n_seg; sg += kSelThreads / 64) {
+    for (int sg = w; (FROM == FROM_SEGS || FROM == FROM_SEGS_MERGE) && sg < n_seg; sg += kSelThreads / 64) {
       const uint4 q = reinterpret_cast<const uint4*>(seg_hist(a, c.bh, sg))[lane];
       cnt[0] += q.x & 0xffffu; cnt[1] += q.x >> 16; cnt[2] += q.y & 0xffffu; cnt[3] += q.y >> 16;
       cnt[4] += q.z & 0xffffu; cnt[5] += q.z >> 16; cnt[6] += q.w & 0xffffu; cnt[7] += q.w >> 16;
@@ -965,10 +1018,18 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
 #pragma unroll
       for (int i = 0; i < kSpec; ++i)
         if (c_at + (i << lg_grp) < n_cd) f(cd[i], c_seg);
-      if (more) {  // the rest of longer runs: a wave takes a segment
-        for (int sg = tid >> 6; sg < n_run; sg += kSelThreads / 64) {
+      if (more) {  // the rest of longer runs, kSpec candidates a thread and trip, and of the segments behind the threads'
+        for (int i0 = n_spec + c_at; i0 - c_at < n_cd; i0 += n_spec) {
+          uint32_t x[kSpec];
+#pragma unroll
+          for (int i = 0; i < kSpec; ++i) x[i] = cand[(int64_t)c_seg * kSelSeg + min(i0 + (i << lg_grp), kSelSeg - 1)];
+#pragma unroll
+          for (int i = 0; i < kSpec; ++i)
+            if (i0 + (i << lg_grp) < n_cd) f(x[i], c_seg);
+        }
+        for (int sg = n_first + (tid >> 6); sg < n_run; sg += kSelThreads / 64) {
           const int n = (int)(segcnt[sg] & 0xffffu);
-          for (int i = (sg < n_first ? n_spec : 0) + (tid & 63); i < n; i += 64) f(cand[(int64_t)sg * kSelSeg + i], sg);
+          for (int i = tid & 63; i < n; i += 64) f(cand[(int64_t)sg * kSelSeg + i], sg);
         }
       }
     };
@@ -1103,6 +1164,11 @@ static void launch_prior_t(const SelArgs& a, dim3 grid, hipStream_t s) {
   else hipLaunchKernelGGL((sel_prior_kernel<false, LIST, FLAGS, 16>), grid, block, 0, s, a);
 }
 hipError_t launch_sel_full(SelArgs a, int B, int nJ, bool hist, hipStream_t s) {
+  const int n_span = ceil_seg(nJ, kFuseSpan);
+  if (a.met != nullptr) {  // (long J, no list)
+    hipLaunchKernelGGL((sel_fuse_kernel<true, false, true>), dim3(n_span, 1, B), dim3(kFuseThreads), 0, s, a);
+    return hipGetLastError();
+  }
   const int n_seg = ceil_seg(nJ, kPriorSeg) + (a.merge_out != nullptr ? a.G : 0);
   const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv));
   if (a.f_from_mu) launch_prior_t<true, false, false>(a, grid, s);  // (a window's evidence is never ranked in the ragged step)
@@ -1111,14 +1177,13 @@ hipError_t launch_sel_full(SelArgs a, int B, int nJ, bool hist, hipStream_t s) {
   else launch_prior_t<false, false, false>(a, grid, s);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int n_span = ceil_seg(nJ, kFuseSpan);
   const dim3 fgrid(n_span, 1, z_of(a, B, n_span)), fblock(kFuseThreads);
   if (a.slow_list != nullptr) {
-    if (hist) hipLaunchKernelGGL((sel_fuse_kernel<true, true>), fgrid, fblock, 0, s, a);
-    else hipLaunchKernelGGL((sel_fuse_kernel<false, true>), fgrid, fblock, 0, s, a);
+    if (hist) hipLaunchKernelGGL((sel_fuse_kernel<true, true, false>), fgrid, fblock, 0, s, a);
+    else hipLaunchKernelGGL((sel_fuse_kernel<false, true, false>), fgrid, fblock, 0, s, a);
   } else {
-    if (hist) hipLaunchKernelGGL((sel_fuse_kernel<true, false>), fgrid, fblock, 0, s, a);
-    else hipLaunchKernelGGL((sel_fuse_kernel<false, false>), fgrid, fblock, 0, s, a);
+    if (hist) hipLaunchKernelGGL((sel_fuse_kernel<true, false, false>), fgrid, fblock, 0, s, a);
+    else hipLaunchKernelGGL((sel_fuse_kernel<false, false, false>), fgrid, fblock, 0, s, a);
   }
   return hipGetLastError();
 }
@@ -1174,7 +1239,8 @@ hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s) {
   const dim3 block(kSelThreads);
   if (a.met != nullptr) {  // one more workgroup per query head
     const dim3 grid = place_grid(&a, n_seg + a.G, z_of(a, B, (n_seg + a.G) * a.Hkv));
-    if (list) hipLaunchKernelGGL((sel_cand_kernel<true, FROM_WGS>), grid, block, 0, s, a);
+    if (a.wg_hist == nullptr) hipLaunchKernelGGL((sel_cand_kernel<false, FROM_SEGS_MERGE>), grid, block, 0, s, a);
+    else if (list) hipLaunchKernelGGL((sel_cand_kernel<true, FROM_WGS>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((sel_cand_kernel<false, FROM_WGS>), grid, block, 0, s, a);
     return hipGetLastError();
   }
