@@ -24,7 +24,7 @@ struct sfi_ctx {
   int dense_wide;           // dense kernel reads K rows as whole 128-byte lines (A/B knob, sfi_set_dense_k_layout)
   int mixed_plan;           // the ragged step's dense launch plans itself on the device (default; A/B knob, sfi_set_mixed_plan)
   int handover;             // fast-step records: 0 device scope, 1 XCD-local where the launch allows it (default), 2 (sfi_set_handover)
-  int dense_scores;         // the slow step's dense launch scores: 0 no, 1 where that is faster (default), 2 to 4 (sfi_set_dense_scores)
+  int dense_scores;         // the slow step's dense launch scores: 0 no, 1 where that is faster (default), others for tests (sfi_set_dense_scores)
   int last_dense_splits, last_fast_splits;
   int last_dense_scored;    // the last dense launch of a slow step has scored
   int last_dense_planned;   // the last dense launch planned itself: its records per sequence are in ws.seq_rec
@@ -315,7 +315,7 @@ void set_dense_scores(const sfi_ctx* x, AttnArgs* a) {
   a->prior_args = prior_args_of(x);
   a->keys = x->ws.keys;
   a->alpha = x->alpha;
-  a->met_ticks = x->dense_scores == 2 ? 0 : x->dense_scores == 3 ? 1 : kScoreWaitTicks;
+  a->met_ticks = x->dense_scores == 2 ? 0 : x->dense_scores == 3 ? 1 : x->dense_scores == 12 ? -kScoreWaitTicks : kScoreWaitTicks;
 }
 
 void set_dense_bounds(const sfi_ctx* x, AttnArgs* a, int max_len) {
@@ -1308,7 +1308,7 @@ int sfi_set_handover(sfi_ctx* x, int32_t mode) {
 }
 
 int sfi_set_dense_scores(sfi_ctx* x, int32_t mode) {
-  if (x == nullptr || mode < 0 || mode > 4) return SFI_EINVAL;
+  if (x == nullptr || mode < 0 || (mode > 4 && mode != 12)) return SFI_EINVAL;
   x->dense_scores = mode;
   return SFI_OK;
 }

@@ -1096,6 +1096,8 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
   const float* const stash = lds + kWaves * G * kHeadDim + w * score_stash_floats(G);
   reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);
   __syncthreads();  // (the list is there)
+  const uint64_t t0 = wall_clock64();  // the limit is for all sequences together
+  const uint64_t limit = (uint64_t)abs(a.met_ticks);
   int used = 0;  // tiles of this wave in front of the sequence's
   for (int e = 0; e < sc.n; ++e) {
     const int4 e0 = sc.entry[2 * e], e1 = sc.entry[2 * e + 1];
@@ -1107,7 +1109,6 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
     const int bh = b * a.Hkv + h;
     float* const lg = a.logits + (int64_t)bh * tile_f / kTile * a.ld_pos;
     // wave w: the statistics of heads w, w + 4, ..., a record per lane
-    const uint64_t t0 = wall_clock64();
     if (FULL)  // (the next launch adds to the segments' histograms)
       for (int sg = slot; sg * kSelSeg < NJ; sg += n_rec) a.hist[((int64_t)bh * a.n_seg_cap + sg) * (kHistBins / 2) + tid] = 0u;
     bool all = true;
@@ -1117,10 +1118,10 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
         const uint64_t* const met = a.met + ((int64_t)bh * G + g) * kSlotCap + min(lane, n_rec - 1);
         uint64_t v = 0;
         all = false;
-        while (a.met_ticks > 0) {
+        while (limit > 0) {
           v = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          all = __all(v != 0);
-          if (all || wall_clock64() - t0 >= (uint64_t)a.met_ticks) break;
+          all = __all(v != 0 && a.met_ticks > 0);
+          if (all || wall_clock64() - t0 >= limit) break;
           __builtin_amdgcn_s_sleep(2);
         }
         if (!all) break;

@@ -34,7 +34,7 @@ constexpr int kScoreFloats = 38400;  // LDS of a dense workgroup that scores: th
 constexpr int kScoreBurst = 4;       // tiles written together where a wave's part does not hold them all
 __host__ __device__ constexpr int score_stash_floats(int G) { return kScoreFloats / kWaves - G * kHeadDim; }  // of a wave
 __host__ __device__ constexpr int score_stay(int G, int rows) { return score_stash_floats(G) / (rows * kTile) - kScoreBurst; }  // tiles of a wave that stay in LDS
-constexpr int kScoreWaitTicks = 6400;  // longest wait for a pair's other workgroups there (ticks of 10 ns)
+constexpr int kScoreWaitTicks = 6400;  // longest wait of a workgroup for the others of its pairs there, all sequences together (ticks of 10 ns)
 constexpr int kHistGroup = 64;      // segments whose histograms a launch of its own adds up ...
 constexpr int kHistGroupFrom = 128;  // ... of a J of more segments than this
 constexpr int kStateWords = 8;     // per (b, h) Selector state, see SelState
@@ -148,7 +148,7 @@ struct AttnArgs {
   float inv_alpha;
   PriorArgs prior_args;
   float alpha;                   //   ... power-mean exponent of the evidence
-  int32_t met_ticks;             //   ... longest wait, in ticks of 10 ns
+  int32_t met_ticks;             //   ... longest wait, in ticks of 10 ns; negative (tests): as long, and nothing is taken as arrived
   int32_t with_knorm;            // dense mode: also expose the squared key norms (full Selector)
   int32_t dense_wide;            // dense mode: K rows read as whole 128-byte lines (query groups of at most 8 heads, flat cache)
   int32_t big_stash;             // dense mode with logits: the variant with the 32 KB stash per wave (one workgroup per CU)

@@ -149,3 +149,42 @@ def test_graph_replays():
             assert all(torch.equal(a, b) for a, b in zip((out, sel, nsel), want[i % 2])), i
     finally:
         ctx.close()
+
+
+def test_the_wait_has_one_limit_for_all_of_a_workgroups_sequences():
+    """Statistics that never count as arrived: 32 short sequences of which every workgroup has about eight.  It waits 64 us once; with
+    a limit of its own for each sequence the step would take 64 us longer for every one of them, about 500 us in all."""
+    import torch
+    from paper_2603_12038_amd.binding import SfiContext
+    import paper_2603_12038_amd as sfi
+    B, Hkv, n = 32, 64, 16384 + 200
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    K, V = (torch.empty((1, 1, n, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=gen).expand(B, Hkv, n, 128) for _ in range(2))
+    q = torch.empty((B, Hkv, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    ctx = SfiContext(B, Hkv, Hkv, n, BUDGET, N_SINK, RECENT, K, V)
+    h = ctx.handle
+    c = torch.full((B,), 1500, dtype=torch.int32, device="cuda")
+    flags = torch.ones(B, dtype=torch.uint8, device="cuda")
+    outs, best = {}, {}
+    try:
+        for mode in (0, 2, 12):
+            sfi.sfi_set_dense_scores(h, mode)
+            out = torch.zeros((B, Hkv, 128), device="cuda")
+            sel = torch.zeros((B, Hkv, BUDGET), dtype=torch.int32, device="cuda")
+            nsel = torch.zeros((B, Hkv), dtype=torch.int32, device="cuda")
+            for _ in range(6):
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record()
+                sfi.sfi_mixed_step(h, q, K, V, flags, c, c - RECENT, n, BUDGET, out, sel, nsel)
+                e1.record()
+                torch.cuda.synchronize()
+                best[mode] = min(best.get(mode, 1e9), e0.elapsed_time(e1) * 1e3)
+            outs[mode] = (out, sel, nsel)
+        print("[gpu-dense-scores] us a step:", best, flush=True)
+        for mode in (2, 12):
+            assert all(torch.equal(a, b) for a, b in zip(outs[mode], outs[0])), mode
+        assert best[12] - best[2] < 2 * 64
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
