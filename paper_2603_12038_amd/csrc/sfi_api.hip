@@ -27,6 +27,7 @@ struct sfi_ctx {
   int dense_scores;         // the slow step's dense launch scores: 0 no, 1 where that is faster (default), others for tests (sfi_set_dense_scores)
   int last_dense_splits, last_fast_splits;
   int last_dense_scored;    // the last dense launch of a slow step has scored
+  int met_left;             // a step that scored there ended with an error: its statistics may still be in ws.met
   int last_dense_planned;   // the last dense launch planned itself: its records per sequence are in ws.seq_rec
   // profiling: a ring of event pairs, one set of stages per hot call, read back in one go so that
   // no host synchronisation sits between the profiled calls
@@ -301,7 +302,19 @@ PriorArgs prior_args_of(const sfi_ctx* x) {
   const sfi_config& c = x->cfg;
   return PriorArgs{c.gamma, c.beta, c.p, c.eta, c.eps > 0.f ? c.eps : 1e-8f};
 }
-void set_dense_scores(const sfi_ctx* x, AttnArgs* a) {
+__global__ void clear_words_kernel(uint32_t* p, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0u;
+}
+// The launch takes any word of ws.met that is not zero for this step's, and only the Selector's last launch puts them back to zero: behind a
+// step that did not come so far they are cleared first (scores_done).
+int set_dense_scores(sfi_ctx* x, AttnArgs* a, hipStream_t st) {
+  if (x->met_left) {
+    const int n = (int)(((char*)x->ws.guard - (char*)x->ws.met) / sizeof(uint32_t));
+    hipLaunchKernelGGL(clear_words_kernel, dim3((n + 255) / 256), dim3(256), 0, st, (uint32_t*)x->ws.met, n);
+    if (hipGetLastError() != hipSuccess) return SFI_ELAUNCH;
+  }
+  x->met_left = 1;
   a->met = x->ws.met;
   a->met_late = x->ws.met_late;
   a->met_tiles = x->ws.met_tiles;
@@ -316,6 +329,12 @@ void set_dense_scores(const sfi_ctx* x, AttnArgs* a) {
   a->keys = x->ws.keys;
   a->alpha = x->alpha;
   a->met_ticks = x->dense_scores == 2 ? 0 : x->dense_scores == 3 ? 1 : x->dense_scores == 12 ? -kScoreWaitTicks : kScoreWaitTicks;
+  return SFI_OK;
+}
+// rc: of the Selector behind such a launch.
+int scores_done(sfi_ctx* x, int rc) {
+  if (rc == SFI_OK) x->met_left = 0;
+  return rc;
 }
 
 void set_dense_bounds(const sfi_ctx* x, AttnArgs* a, int max_len) {
@@ -718,7 +737,7 @@ int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.big_stash = 1;  // every sequence is dense: one workgroup per compute unit, half as many write bursts
   plan_dense(x, &a, ml, false);
   x->last_dense_scored = select_next && score_in_dense(x, a, ml, false);
-  if (x->last_dense_scored) set_dense_scores(x, &a);
+  if (x->last_dense_scored && set_dense_scores(x, &a, st) != SFI_OK) return SFI_ELAUNCH;
   x->last_dense_splits = a.n_split;
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
   if (merge_later) return SFI_OK;  // the Selector's scoring launch merges
@@ -754,7 +773,8 @@ int sfi_slow_step(sfi_ctx* x, const void* q, const void* K, const void* V, const
   sa.merge_out = out;
   if (x->last_dense_scored) { sa.met = x->ws.met; sa.met_late = x->ws.met_late; }
   if (x->last_dense_planned) sa.seq_rec = x->ws.seq_rec;
-  return run_selector(x, sa, ml, st);
+  rc = run_selector(x, sa, ml, st);
+  return x->last_dense_scored ? scores_done(x, rc) : rc;
 }
 
 int sfi_slow_attn(sfi_ctx* x, const void* q, const void* K, const void* V, const int32_t* ctx_len,
@@ -937,11 +957,6 @@ struct StaticScratch {
 };
 StaticScratch g_static[kMaxDevices];
 std::mutex g_static_mutex;
-
-__global__ void clear_words_kernel(uint32_t* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
 }  // namespace
 
 int sfi_fast_step_static(const sfi_config* cfg, const void* q, const void* K, const void* V, const int32_t* sel_idx,
@@ -1142,7 +1157,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   const bool planned = d.plan_batch > 0;
   if (planned) d.slow_list = x->ws.slow_list;
   const bool scored = planned && score_in_dense(x, d, ml, true);
-  if (scored) set_dense_scores(x, &d);
+  if (scored && set_dense_scores(x, &d, st) != SFI_OK) return SFI_ELAUNCH;
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
   if (planned && one_ragged_launch(x, f)) {
@@ -1173,7 +1188,8 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   }
   if (planned) sa.slow_list = x->ws.slow_list;
   if (scored) { sa.met = x->ws.met; sa.met_late = x->ws.met_late; }
-  if ((rc = run_selector(x, sa, ml, st)) != SFI_OK) return rc;
+  rc = run_selector(x, sa, ml, st);
+  if ((scored ? scores_done(x, rc) : rc) != SFI_OK) return rc;
   if (cb == nullptr) return SFI_OK;
   // Reorg_i for the sequences that were refreshed (Sel_i -> Reorg_i)
   return reorg_on(x, K, V, sel_idx, n_sel, budget, ctx_len, is_slow, cb->Kc, cb->Vc, cb->stride_b, cb->stride_h, st, meta_stride);

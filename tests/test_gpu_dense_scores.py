@@ -188,3 +188,46 @@ def test_the_wait_has_one_limit_for_all_of_a_workgroups_sequences():
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("ragged", [False, True])
+def test_step_behind_one_that_ended_with_an_error(ragged):
+    """A call that returns an error behind the dense launch leaves that launch's statistics in the workspace: the next step must not
+    take them for its own.  The error: one the HIP runtime still has from a call of the caller's (a device that does not exist), which
+    the library finds when it looks behind its first launch."""
+    import torch
+    sfi, ctx, K, V, table, q, c = _setup(2, 8, 4, [40000, 33001], 0, 1.0)
+    from paper_2603_12038_amd.binding import SfiError
+    h, lib = ctx.handle, sfi.load_library()
+    rs = c - RECENT
+    flags = torch.ones(2, dtype=torch.uint8, device="cuda")
+    out = torch.zeros((2, 32, 128), device="cuda")
+    sel = torch.zeros((2, 8, BUDGET), dtype=torch.int32, device="cuda")
+    nsel = torch.zeros((2, 8), dtype=torch.int32, device="cuda")
+
+    def step(t):  # (no call of torch's here: it would find the error and report it itself)
+        if ragged:
+            sfi.sfi_mixed_step(h, q[t], K, V, flags, c, rs, 40000, BUDGET, out, sel, nsel)
+        else:
+            sfi.sfi_slow_step(h, q[t], K, V, c, 40000, BUDGET, out, sel, nsel)
+
+    try:
+        want = []
+        for t in range(2):
+            sfi.sfi_set_dense_scores(h, 0)
+            step(t)
+            torch.cuda.synchronize()
+            want.append([x.clone() for x in (out, sel, nsel)])
+        sfi.sfi_set_dense_scores(h, 4)
+        for t in (0, 1, 1, 0):
+            assert lib.hipSetDevice(10000) != 0
+            with pytest.raises(SfiError):
+                step(t)
+            torch.cuda.synchronize()
+            for u in (1 - t, t):
+                step(u)
+                torch.cuda.synchronize()
+                assert all(torch.equal(a, b) for a, b in zip((out, sel, nsel), want[u])), (t, u)
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
