@@ -426,7 +426,7 @@ int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);
  * pair is computed again (more than eight KV heads: as mode 0): the same results up to the order of the sums.  Other values: SFI_EINVAL. */
 int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
 
-/* A/B knob of sfi_slow_step and, with selector_mode 0, the ragged steps (more than 16384 positions to rank, batches of up to 64 sequences).
+/* A/B knob of sfi_slow_step (more than 16384 positions to rank, batches of up to 64 sequences).
  * mode = 1 (default): where that is faster the dense launch also scores, each workgroup what it has read, once it has the others'
  * statistics of its sequences; it waits 64 us for them at most, for all its sequences together, and what is missing then (a launch
  * that has to share the GPU) the Selector scores.  mode = 0: a scoring launch, as behind sfi_slow_attn.  mode = 2, 3, 4 (for tests): scored in the dense launch

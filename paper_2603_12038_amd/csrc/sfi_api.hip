@@ -278,25 +278,26 @@ bool merges_in_kernel(const sfi_ctx* x, int n_split, int max_len) {
 // Whether a slow step's dense launch also scores (score_tail), so that the Selector's scoring launch falls away: where three Selector
 // launches would follow, and all of the launch's workgroups are on the chip together (one per unit: their LDS).  a: planned
 // or, for one sequence, not.
-// - A wave has at least five tiles (ragged: eight if the longest sequence is the only slow one; the others are shorter), else the
-//   scoring launch costs no more than the wait.
+// - A pair has at most eight records on average.  Where the launch has to share the chip, some of its workgroups start when others are done: those wait for nothing,
+//   and what they leave has to be made up for, the more of it the more records a pair has.  (The ragged step's launch never scores: how many of its
+//   sequences are slow, and with it the records of a pair, the host does not know.  Two of 32: up to 32 records.)
+// - A wave has at least five tiles, else the scoring launch costs no more than the wait.
 // - Logits that LDS does not hold go to memory and come back to the few waves of a unit; up to four times what it holds that
-//   is still the faster way.  (How many sequences of a ragged step are slow the host does not know: few, as a rule.)
+//   is still the faster way.
 // Scoring launch / in the dense launch, us a slow step, 8 KV heads and G = 4 where not given: 4 x 32768 rows 98.4 / 94.4; 8 x 20011..24571, G = 5, paged 141.3 / 132.5;
-// 1 x 131072 102.8 / 99.3, G = 16 (three times LDS) 138.4 / 133.7; 8 x 32768, 2 KV heads 59.5 / 56.0; 16 x 20000..60000 511.0 / 504.5;
-// 2 x 20000..30000, G = 8, 4 KV heads (7 tiles) 37.8 / 37.6; ragged, 32 x 16384..65536, G = 8, two slow 126.6 / 118.0, 16 x 20000..60000, half slow 271.5 / 246.0, all 517 / 511.
-// full Selector, 1 x 131072 116.2 / 112.0, 4 x 32768 115.3 / 110.7, 8 x 20000..30000, G = 5, paged 187.6 / 177.9 (ragged steps and a J of more
-// than 262144 positions keep the launch there).
-// Beyond the lines: 1 x 17000 (4 tiles) 28.6 / 28.7, 2 KV heads 24.2 / 24.8; ragged, 4 x 17000, one slow 35.5 / 36.3, 12 x 5003..30011, one slow, compact 49.9 / 50.2;
-// more than four times LDS: 16 x 20000..60000, G = 8 573.2 / 578.6, 16 x 20000..30000, G = 16 407.8 / 410.7.
-bool score_in_dense(const sfi_ctx* x, const AttnArgs& a, int max_len, bool mixed) {
+// 16 x 20000..60000 511.0 / 504.5; full Selector, 4 x 32768 115.3 / 110.7, 8 x 20000..30000, G = 5, paged 187.6 / 177.9 (a J of more than 262144 positions
+// keeps the launch there).  Two contexts at once: 4 x 32768 192 / 178.
+// Beyond the lines: 32 records, 1 x 131072 102.8 / 99.3, full Selector 116.2 / 112.0, two contexts at once 214 / 400 to 600; ragged, 32 x 16384..65536, G = 8, two slow 126.6 / 118.0,
+// four contexts at once 488 / 583; 43 records, 3 x 17000..60000, G = 5, 2 KV heads 42.1 / 43.1; 4 tiles, 1 x 17000 28.6 / 28.7; more than four times LDS: 16 x 20000..60000, G = 8
+// 573.2 / 578.6, 16 x 20000..30000, G = 16 407.8 / 410.7.
+bool score_in_dense(const sfi_ctx* x, const AttnArgs& a, int max_len) {
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink, B = x->cfg.batch, Hkv = x->cfg.n_kv_heads;
   if (x->dense_scores == 0 || x->ws.met_tiles == nullptr || nJ <= kPickMax || x->dense_wide || (a.plan_batch == 0 && B > 1)) return false;
   const int wgs = a.plan_batch > 0 ? std::max(a.plan_wgs, a.plan_even * B) : a.n_split;
-  if (wgs * Hkv > x->n_cu || (x->cfg.selector_mode == 1 && (mixed || nJ > kHistGroupFrom * kSelSeg))) return false;
+  if (wgs * Hkv > x->n_cu || (x->cfg.selector_mode == 1 && nJ > kHistGroupFrom * kSelSeg)) return false;
   if (x->dense_scores > 1) return true;
-  const int64_t tiles = (int64_t)((max_len + kTile - 1) / kTile) * (mixed ? 1 : B) * Hkv, waves = (int64_t)kWaves * x->n_cu;
-  return tiles >= (mixed ? 8 : 5) * waves && (mixed || tiles <= 4 * score_stay(x->G, x->G + x->cfg.selector_mode) * waves);
+  const int64_t tiles = (int64_t)((max_len + kTile - 1) / kTile) * B * Hkv, waves = (int64_t)kWaves * x->n_cu;
+  return wgs <= kScoreRecords * B && tiles >= 5 * waves && tiles <= 4 * score_stay(x->G, x->G + x->cfg.selector_mode) * waves;
 }
 PriorArgs prior_args_of(const sfi_ctx* x) {
   const sfi_config& c = x->cfg;
@@ -736,7 +737,7 @@ int slow_attn_impl(sfi_ctx* x, const void* q, const void* K, const void* V, cons
   a.n_split = dense_splits_for(x, ml, false);
   a.big_stash = 1;  // every sequence is dense: one workgroup per compute unit, half as many write bursts
   plan_dense(x, &a, ml, false);
-  x->last_dense_scored = select_next && score_in_dense(x, a, ml, false);
+  x->last_dense_scored = select_next && score_in_dense(x, a, ml);
   if (x->last_dense_scored && set_dense_scores(x, &a, st) != SFI_OK) return SFI_ELAUNCH;
   x->last_dense_splits = a.n_split;
   { StageTimer t(x, st, SFI_STAGE_ATTN); SFI_TRY(launch_attn_dense(a, x->cfg.batch, a.n_split, st)); if (!t.stop()) return SFI_ELAUNCH; }
@@ -1156,8 +1157,6 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
   if (x->mixed_plan != 0 && merge_in_score) plan_dense(x, &d, ml, true);
   const bool planned = d.plan_batch > 0;
   if (planned) d.slow_list = x->ws.slow_list;
-  const bool scored = planned && score_in_dense(x, d, ml, true);
-  if (scored && set_dense_scores(x, &d, st) != SFI_OK) return SFI_ELAUNCH;
   // the fast part reads last segment's sel rows (or compact rows) of fast sequences; the Selector and Reorg below
   // only rewrite rows of slow sequences, so the order of the two attention launches is free.
   if (planned && one_ragged_launch(x, f)) {
@@ -1187,9 +1186,7 @@ int mixed_step_on(sfi_ctx* x, const void* q, const void* K, const void* V, const
     sa.merge_out = out;
   }
   if (planned) sa.slow_list = x->ws.slow_list;
-  if (scored) { sa.met = x->ws.met; sa.met_late = x->ws.met_late; }
-  rc = run_selector(x, sa, ml, st);
-  if ((scored ? scores_done(x, rc) : rc) != SFI_OK) return rc;
+  if ((rc = run_selector(x, sa, ml, st)) != SFI_OK) return rc;
   if (cb == nullptr) return SFI_OK;
   // Reorg_i for the sequences that were refreshed (Sel_i -> Reorg_i)
   return reorg_on(x, K, V, sel_idx, n_sel, budget, ctx_len, is_slow, cb->Kc, cb->Vc, cb->stride_b, cb->stride_h, st, meta_stride);

@@ -2390,12 +2390,12 @@ __global__ __launch_bounds__(kAttnThreads, PAGED ? 2 : 3) void attn_compact_kern
 // ------------------------------------------------------------------------------------------------
 // BALANCED (balanced_shares): the shares are cut by what a workgroup has had already (PlanCells).  (Every head has its
 // workgroups with a cell in the same places: the heads' shares alternate as the cells do.)
-template <bool PAGED, bool WIDE, bool COMPACT, bool BALANCED, int EXPOSE>
+template <bool PAGED, bool WIDE, bool COMPACT, bool BALANCED>
 __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int32_t* ctx_len, const uint8_t* is_slow, const int32_t* recent_start,
                                                                       const int32_t* sel_idx, const uint32_t strides, const uint32_t shape, const int B,
                                                                       const int W_max, const int n_sink, const int n_split, const float per_min,
                                                                       const int row_in, const float cell_tiles, const AttnArgs f, const AttnArgs d) {
-  __shared__ __align__(16) float s_patch[kWaves * patch_floats(EXPOSE, true)];
+  __shared__ __align__(16) float s_patch[kWaves * patch_floats(1, true)];
   const uint32_t id = blockIdx.x, Hkv = shape & 0xffffu;
   // the cells in the order of fast_grid: row pairs side by side, n_split slots of them, then the next row.  row_in: the pairs in a
   // row, negative (tests): which of them a workgroup has changes from slot to slot, and with it the XCD of a pair's slots.
@@ -2415,8 +2415,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attn_ragged_kernel(const int3
   __syncthreads();  // the cell's results in LDS have been read
   Scored sc = scored_of(s_patch);
   if (id < (uint32_t)W_max * Hkv)
-    planned_body<EXPOSE, PAGED, false, BALANCED>(j, h, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent, d.len_cap, d, s_patch, sc, cells);
-  if (EXPOSE >= 3) score_tail<EXPOSE == 4>(d, sc, s_patch);
+    planned_body<1, PAGED, false, BALANCED>(j, h, ctx_len, is_slow, nullptr, strides, B, W_max, per_min, n_sink, d.recent, d.len_cap, d, s_patch, sc, cells);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2616,15 +2615,10 @@ hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, bool balance
   // A cell's tile takes less than the list's, whose logits are exposed.  (0.8 / 0.9, us a step: 32 x 8192 rows, half slow, 125.1 / 131.2; 16 x
   // 16384..49152, half slow, 219.5 / 222.2; 16 x 16384..65536, budget 1024, a quarter slow, 148.5 / 146.0.)
   const float cell_tiles = 0.8f * std::min((float)f.n_sink + (float)f.sel_stride + (float)f.recent, (float)d.len_cap) / (float)(kTile * f.n_split);
-#define SFI_RAGGED_E(PAGED, WIDE, COMPACT, BALANCED, EXPOSE)                                                                                       \
-  hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT, BALANCED, EXPOSE>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start,        \
-                     f.sel_idx, strides, fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min,                          \
-                     f.handover == 2 ? -row : row, cell_tiles, f, d)
-#define SFI_RAGGED(PAGED, WIDE, COMPACT, BALANCED)                                 \
-  do {                                                                             \
-    if (d.met != nullptr) SFI_RAGGED_E(PAGED, WIDE, COMPACT, BALANCED, 3);         \
-    else SFI_RAGGED_E(PAGED, WIDE, COMPACT, BALANCED, 1);                          \
-  } while (0)
+#define SFI_RAGGED(PAGED, WIDE, COMPACT, BALANCED)                                                                                                 \
+  hipLaunchKernelGGL((attn_ragged_kernel<PAGED, WIDE, COMPACT, BALANCED>), grid, block, 0, s, d.ctx_len, d.is_slow, f.recent_start, f.sel_idx,     \
+                     strides, fast_shape(f, B), B, d.plan_wgs, d.n_sink, f.n_split, 1.0f / (float)d.plan_min, f.handover == 2 ? -row : row,       \
+                     cell_tiles, f, d)
 #define SFI_RAGGED_C(PAGED, COMPACT)                                   \
   do {                                                                 \
     if (f.G <= 8 && balanced) SFI_RAGGED(PAGED, true, COMPACT, true);  \
@@ -2638,7 +2632,6 @@ hipError_t launch_attn_ragged(const AttnArgs& d, const AttnArgs& f, bool balance
   else SFI_RAGGED_C(false, false);
 #undef SFI_RAGGED_C
 #undef SFI_RAGGED
-#undef SFI_RAGGED_E
   return hipGetLastError();
 }
 hipError_t launch_attn_compact(const AttnArgs& a, int B, int n_slots, hipStream_t s) {

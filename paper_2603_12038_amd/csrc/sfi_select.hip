@@ -1237,10 +1237,9 @@ hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kSelSeg);
   const bool list = a.slow_list != nullptr;
   const dim3 block(kSelThreads);
-  if (a.met != nullptr) {  // one more workgroup per query head
+  if (a.met != nullptr) {  // (no list) one more workgroup per query head
     const dim3 grid = place_grid(&a, n_seg + a.G, z_of(a, B, (n_seg + a.G) * a.Hkv));
     if (a.wg_hist == nullptr) hipLaunchKernelGGL((sel_cand_kernel<false, FROM_SEGS_MERGE>), grid, block, 0, s, a);
-    else if (list) hipLaunchKernelGGL((sel_cand_kernel<true, FROM_WGS>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((sel_cand_kernel<false, FROM_WGS>), grid, block, 0, s, a);
     return hipGetLastError();
   }
