@@ -429,7 +429,7 @@ int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
 /* A/B knob of sfi_slow_step (more than 16384 positions to rank, batches of up to 64 sequences).
  * mode = 1 (default): where that is faster the dense launch also scores, each workgroup what it has read, once it has the others'
  * statistics of its sequences; it waits 64 us for them at most, for all its sequences together, and what is missing then (a launch
- * that has to share the GPU) the Selector scores.  mode = 0: a scoring launch, as behind sfi_slow_attn.  mode = 2, 3, 4 (for tests): scored in the dense launch
+ * that has to share the GPU) falls to the last workgroups.  mode = 0: a scoring launch, as behind sfi_slow_attn.  mode = 2, 3, 4 (for tests): scored in the dense launch
  * wherever it can be, with no wait at all, a wait of one tick, and the whole wait; mode = 12 (for tests): the
  * whole wait, and nothing is taken as arrived.  Same results.  Other values: SFI_EINVAL. */
 int sfi_set_dense_scores(sfi_ctx* ctx, int32_t mode);

@@ -27,7 +27,7 @@ struct sfi_ctx {
   int dense_scores;         // the slow step's dense launch scores: 0 no, 1 where that is faster (default), others for tests (sfi_set_dense_scores)
   int last_dense_splits, last_fast_splits;
   int last_dense_scored;    // the last dense launch of a slow step has scored
-  int met_left;             // a step that scored there ended with an error: its statistics may still be in ws.met
+  int met_dirty;            // a step that scored there ended with an error: its statistics may still be in ws.met
   int last_dense_planned;   // the last dense launch planned itself: its records per sequence are in ws.seq_rec
   // profiling: a ring of event pairs, one set of stages per hot call, read back in one go so that
   // no host synchronisation sits between the profiled calls
@@ -112,7 +112,8 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->hist = (uint32_t*)take((size_t)(B * Hkv) * n_seg * (kHistBins / 2) * sizeof(uint32_t));
   ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * kWaves * kArriveStride * sizeof(uint32_t));
   ws->met = (uint64_t*)take((size_t)(B * Hq) * kSlotCap * sizeof(uint64_t));
-  ws->met_late = (unsigned long long*)take((size_t)(B * Hkv) * sizeof(unsigned long long));
+  ws->met_left = (unsigned long long*)take((size_t)(B * Hkv) * sizeof(unsigned long long));
+  ws->met_out = (unsigned long long*)take((size_t)(B * Hkv) * sizeof(unsigned long long));
   ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears them all
   const bool scores = B <= kScoreCap && c->max_ctx > kPickMax;
   ws->met_tiles = scores ? (int4*)take((size_t)(B * Hkv) * kSlotCap * sizeof(int4)) : nullptr;
@@ -310,14 +311,15 @@ __global__ void clear_words_kernel(uint32_t* p, int n) {
 // The launch takes any word of ws.met that is not zero for this step's, and only the Selector's last launch puts them back to zero: behind a
 // step that did not come so far they are cleared first (scores_done).
 int set_dense_scores(sfi_ctx* x, AttnArgs* a, hipStream_t st) {
-  if (x->met_left) {
+  if (x->met_dirty) {
     const int n = (int)(((char*)x->ws.guard - (char*)x->ws.met) / sizeof(uint32_t));
     hipLaunchKernelGGL(clear_words_kernel, dim3((n + 255) / 256), dim3(256), 0, st, (uint32_t*)x->ws.met, n);
     if (hipGetLastError() != hipSuccess) return SFI_ELAUNCH;
   }
-  x->met_left = 1;
+  x->met_dirty = 1;
   a->met = x->ws.met;
-  a->met_late = x->ws.met_late;
+  a->met_left = x->ws.met_left;
+  a->met_out = x->ws.met_out;
   a->met_tiles = x->ws.met_tiles;
   a->wg_hist = x->ws.wg_hist;
   a->wg_stat = x->ws.wg_stat;
@@ -334,7 +336,7 @@ int set_dense_scores(sfi_ctx* x, AttnArgs* a, hipStream_t st) {
 }
 // rc: of the Selector behind such a launch.
 int scores_done(sfi_ctx* x, int rc) {
-  if (rc == SFI_OK) x->met_left = 0;
+  if (rc == SFI_OK) x->met_dirty = 0;
   return rc;
 }
 
@@ -471,7 +473,7 @@ void fill_sel(const sfi_ctx* x, SelArgs* s, const int32_t* ctx_len, int max_len,
   memset(s, 0, sizeof(*s));
   const sfi_config& c = x->cfg;
   s->jstat = x->ws.jstat; s->logits = x->ws.logits; s->keys = x->ws.keys; s->cand = x->ws.cand;
-  s->met_tiles = x->ws.met_tiles; s->wg_hist = x->ws.wg_hist; s->wg_stat = x->ws.wg_stat;
+  s->wg_hist = x->ws.wg_hist; s->wg_stat = x->ws.wg_stat;
   s->hist = x->ws.hist; s->state = x->ws.state; s->segcnt = x->ws.segcnt;
   s->ctx_len = ctx_len; s->is_slow = is_slow; s->sel_idx = sel_idx; s->n_sel = n_sel;
   s->ms = 1; s->fs = 1;
@@ -772,7 +774,7 @@ int sfi_slow_step(sfi_ctx* x, const void* q, const void* K, const void* V, const
   fill_sel(x, &sa, ctx_len, ml, nullptr, budget, x->last_dense_splits, sel_idx, n_sel);
   sa.part = x->ws.part;
   sa.merge_out = out;
-  if (x->last_dense_scored) { sa.met = x->ws.met; sa.met_late = x->ws.met_late; }
+  if (x->last_dense_scored) { sa.met = x->ws.met; sa.met_out = x->ws.met_out; }
   if (x->last_dense_planned) sa.seq_rec = x->ws.seq_rec;
   rc = run_selector(x, sa, ml, st);
   return x->last_dense_scored ? scores_done(x, rc) : rc;

@@ -1079,17 +1079,47 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
 // to zero by the Selector's last launch: what has arrived is seen in the value itself, so nothing is ordered or counted.  (A
 // counter behind acknowledged headers, in front of their loads, was 0.7 us longer, in the L2 of one XCD no shorter.)
 // All workgroups of the launch are on the chip together where it has the chip to itself (score_in_dense); where it has
-// not, some may only start when others have ended, so the wait has a limit.  Behind it a workgroup writes its logits,
-// marks its record in the pair's mask and ends; the next launch then scores that record's tiles (late_records).
+// not, some may only start when others have ended, so the wait has a limit.  Behind it a workgroup writes its logits and leaves its
+// record to the pair's others: it marks it in the pair's mask, counts itself out and ends.  A workgroup that has scored its own record, and on
+// counting itself out finds that some were left, claims them from the mask one by one; the last of the pair to be counted out finds
+// the statistics complete and works off all that nobody has claimed, its own among them if it was left.  So every record is
+// scored once, in this launch, and the next one does not see which way it went.  (With every record left, which the last workgroups of the pairs
+// then work off alone, us a slow step of 4 x 32768 rows 103 -> 127, of 1 x 131071 with the full Selector 122 -> 293; left to the Selector's launches, of which each workgroup
+// scored all of them again, 140 and 880.)
 // Nothing of this is decided before all of the workgroup's own shares are done and out, so no workgroup waits for one that waits.
 // The keys are bit for bit what the scoring launch (sel_score_kernel) makes of the same logits.
 // FULL: evidence, prior and their sums for the full Selector, as sel_prior_kernel leaves them (the sums per workgroup, not per segment).
+// A record that was left is handed over without a fence: its logits and tiles go out and come back at device scope, and are performed before the mask
+// has its bit.
+__device__ __forceinline__ void store_far4(float* dst, float4 v) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(dst), (uint64_t)__float_as_uint(v.y) << 32 | __float_as_uint(v.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(dst) + 1, (uint64_t)__float_as_uint(v.w) << 32 | __float_as_uint(v.z), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float4 load_far4(const float* src) {
+  const uint64_t a = __hip_atomic_load(reinterpret_cast<const uint64_t*>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t b = __hip_atomic_load(reinterpret_cast<const uint64_t*>(src) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float4(__uint_as_float((uint32_t)a), __uint_as_float((uint32_t)(a >> 32)), __uint_as_float((uint32_t)b), __uint_as_float((uint32_t)(b >> 32)));
+}
+// Records of the mask that are this workgroup's from now on: all there are, or one (0: there is none).
+__device__ __forceinline__ uint64_t claim_left(unsigned long long* mask, bool every) {
+  if (every) return __hip_atomic_exchange(mask, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  uint64_t m = __hip_atomic_load(mask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  while (m != 0) {  // (at most one trip per record: a bit that somebody else has claimed does not come back)
+    const uint64_t bit = m & (0 - m);
+    const uint64_t old = __hip_atomic_fetch_and(mask, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((old & bit) != 0) return bit;
+    m = old & ~bit;
+  }
+  return 0;
+}
 template <bool FULL>
 __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, float* lds) {
   __shared__ __align__(16) uint32_t s_hist[FULL ? 2 * kAttnThreads : kHistBins];
   __shared__ double s_sums[kWaves][kSegStats];
   __shared__ float s_M[16], s_c[16];
-  __shared__ uint32_t s_met[kWaves];
+  __shared__ uint32_t s_met[kWaves], s_go;
+  __shared__ uint64_t s_claim;
+  __shared__ int4 s_tiles[kSlotCap];  // of the records claimed
   static_assert(kHistBins == 2 * kAttnThreads, "two bins, or one word of a segment's histogram, per thread");
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.G, rows = G + (FULL ? 1 : 0), tile_f = rows * kTile, stay = score_stay(G, rows);
@@ -1102,101 +1132,178 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
   for (int e = 0; e < sc.n; ++e) {
     const int4 e0 = sc.entry[2 * e], e1 = sc.entry[2 * e + 1];
     const int h = __builtin_amdgcn_readfirstlane(e0.x), b = __builtin_amdgcn_readfirstlane(e0.y);
-    const int first = __builtin_amdgcn_readfirstlane(e0.z) + w, step = __builtin_amdgcn_readfirstlane(e0.w);
-    const int nTJ = __builtin_amdgcn_readfirstlane(e1.x), NJ = __builtin_amdgcn_readfirstlane(e1.y);
-    const int n_rec = __builtin_amdgcn_readfirstlane(e1.z), slot = __builtin_amdgcn_readfirstlane(e1.w);
-    const int KJ = first < nTJ ? (nTJ - first + step - 1) / step : 0;
+    const int first0 = __builtin_amdgcn_readfirstlane(e0.z), step0 = __builtin_amdgcn_readfirstlane(e0.w);
+    const int nTJ0 = __builtin_amdgcn_readfirstlane(e1.x), NJ = __builtin_amdgcn_readfirstlane(e1.y);
+    const int n_rec = __builtin_amdgcn_readfirstlane(e1.z), slot0 = __builtin_amdgcn_readfirstlane(e1.w);
+    auto tiles_of_wave = [&](int first, int step, int end) { return first < end ? (end - first + step - 1) / step : 0; };
+    const int KJ = tiles_of_wave(first0 + w, step0, nTJ0), in_lds = max(0, min(KJ, stay - used));
     const int bh = b * a.Hkv + h;
+    const float* const kept = stash + used * tile_f;
     float* const lg = a.logits + (int64_t)bh * tile_f / kTile * a.ld_pos;
-    // wave w: the statistics of heads w, w + 4, ..., a record per lane
+    uint64_t* const left_tiles = reinterpret_cast<uint64_t*>(a.met_tiles + (int64_t)bh * kSlotCap);
+    used += KJ;
+    if (in_lds < KJ) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's other logits are written
     if (FULL)  // (the next launch adds to the segments' histograms)
-      for (int sg = slot; sg * kSelSeg < NJ; sg += n_rec) a.hist[((int64_t)bh * a.n_seg_cap + sg) * (kHistBins / 2) + tid] = 0u;
-    bool all = true;
-    for (int g = w; g < 16; g += kWaves) {
-      float M = -kNeg, c = 0.f;  // (heads past the group count for nothing)
-      if (g < G) {
-        const uint64_t* const met = a.met + ((int64_t)bh * G + g) * kSlotCap + min(lane, n_rec - 1);
-        uint64_t v = 0;
-        all = false;
-        while (limit > 0) {
-          v = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          all = __all(v != 0 && a.met_ticks > 0);
-          if (all || wall_clock64() - t0 >= limit) break;
-          __builtin_amdgcn_s_sleep(2);
+      for (int sg = slot0; sg * kSelSeg < NJ; sg += n_rec) a.hist[((int64_t)bh * a.n_seg_cap + sg) * (kHistBins / 2) + tid] = 0u;
+    bool own = true, last = false;  // the workgroup's record has not been left; it is the pair's last one to be counted out (both workgroup-uniform)
+    for (;;) {
+      // wave w: the statistics of heads w, w + 4, ..., a record per lane
+      bool all = true;
+      for (int g = w; g < 16; g += kWaves) {
+        float M = -kNeg, c = 0.f;  // (heads past the group count for nothing)
+        if (g < G) {
+          const uint64_t* const met = a.met + ((int64_t)bh * G + g) * kSlotCap + min(lane, n_rec - 1);
+          uint64_t v = 0;
+          all = false;
+          while (limit > 0 || !own) {
+            v = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            all = __all(v != 0 && (a.met_ticks > 0 || !own));
+            if (all || !own || wall_clock64() - t0 >= limit) break;
+            __builtin_amdgcn_s_sleep(2);
+          }
+          if (!all && own) break;
+          const float2 ml = lane < n_rec ? make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32) & 0x7fffffffu)) : make_float2(kNeg, 0.f);
+          c = group_stat(ml, a.alpha, G, M);
         }
-        if (!all) break;
-        const float2 ml = lane < n_rec ? make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32) & 0x7fffffffu)) : make_float2(kNeg, 0.f);
-        c = group_stat(ml, a.alpha, G, M);
+        if (lane == 0) {
+          s_M[g] = M;
+          s_c[g] = c;
+        }
       }
-      if (lane == 0) {
-        s_M[g] = M;
-        s_c[g] = c;
-      }
-    }
-    if (lane == 0) s_met[w] = all;
-    __syncthreads();
-    if ((s_met[0] & s_met[1] & s_met[2] & s_met[3]) == 0u) {  // workgroup-uniform
-      const int n_f4 = max(0, min(KJ, stay - used)) * (tile_f / 4);
-      for (int f = lane; f < n_f4; f += 64) {
+      if (lane == 0) s_met[w] = all;
+      __syncthreads();
+      if (!own || (s_met[0] & s_met[1] & s_met[2] & s_met[3]) != 0u) break;
+      // The record is left.  (Logits beyond LDS are in memory already, but perhaps only in this XCD's L2.)
+      for (int f = lane; f < KJ * (tile_f / 4); f += 64) {
         const int i = f / (tile_f / 4), rem = f - i * (tile_f / 4);
-        *reinterpret_cast<float4*>(lg + (int64_t)(first + i * step) * tile_f + rem * 4) = *reinterpret_cast<const float4*>(stash + used * tile_f + f * 4);
+        float* const dst = lg + (int64_t)(first0 + w + i * step0) * tile_f + rem * 4;
+        if (i < in_lds) store_far4(dst, *reinterpret_cast<const float4*>(kept + f * 4));
+        else store_far4(dst, *reinterpret_cast<const float4*>(dst));
       }
       if (tid == 0) {
-        a.met_tiles[(int64_t)bh * kSlotCap + slot] = make_int4(first, step, nTJ, 0);
-        __hip_atomic_fetch_or(a.met_late + bh, 1ull << slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(left_tiles + 2 * slot0, (uint64_t)(uint32_t)step0 << 32 | (uint32_t)first0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(left_tiles + 2 * slot0 + 1, (uint64_t)(uint32_t)nTJ0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      used += KJ;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's statistics, logits and tiles have been performed
       __syncthreads();
-      continue;
+      if (tid == 0) {
+        const uint64_t was_left = __hip_atomic_fetch_or(a.met_left + bh, 1ull << slot0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::"v"((uint32_t)was_left) : "memory");  // (in the mask before it is counted)
+        const uint64_t out = __hip_atomic_fetch_add(a.met_out + bh, 1ull << 32 | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_go = (uint32_t)out == (uint32_t)(n_rec - 1);
+      }
+      __syncthreads();
+      own = false;
+      last = s_go != 0u;
+      if (!last) break;
     }
-    // eight tiles at a time, a quad of positions per lane
+    if (!own && !last) continue;
+    uint64_t out = 0;  // looked at when the record is scored
+    if (own && tid == 0) out = __hip_atomic_fetch_add(a.met_out + bh, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t row = (int64_t)bh * a.ld_pos;
     const Prior prior(a.prior_args, NJ);
-    double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    auto score = [&](int p, const float* src) {
-      if (p >= NJ) return;
-      float f[4] = {0.f, 0.f, 0.f, 0.f};
+    int first = first0, step = step0, end = nTJ0, slot = slot0;
+    uint64_t claimed = 0;
+    for (;;) {
+      if (!own) {
+        __syncthreads();
+        if (claimed == 0) {
+          if (w == 0) {
+            uint64_t m = 0;
+            if (lane == 0) m = claim_left(a.met_left + bh, last);
+            m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+            if (m >> lane & 1u) {
+              const uint64_t t0 = __hip_atomic_load(left_tiles + 2 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              const uint64_t t1 = __hip_atomic_load(left_tiles + 2 * lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              s_tiles[lane] = make_int4((int)(uint32_t)t0, (int)(t0 >> 32), (int)(uint32_t)t1, 0);
+            }
+            if (lane == 0) s_claim = m;
+          }
+          __syncthreads();
+          claimed = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s_claim >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)s_claim);
+          if (claimed == 0) break;
+        }
+        slot = __builtin_ctzll(claimed);
+        claimed &= claimed - 1;
+        const int4 rec = s_tiles[slot];
+        first = __builtin_amdgcn_readfirstlane(rec.x), step = __builtin_amdgcn_readfirstlane(rec.y), end = __builtin_amdgcn_readfirstlane(rec.z);
+      }
+      double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
+      auto rank = [&](int p, float (&f)[4], const float4& k4) {
+        if (p >= NJ) return;
+        if (FULL) {
+          const float rr[4] = {prior(k4.x, p), prior(k4.y, p + 1), prior(k4.z, p + 2), prior(k4.w, p + 3)};
+          evidence_of_mu(f, a.alpha, a.inv_alpha, p, NJ);
+          add_sums(sums, f, rr);
+          *reinterpret_cast<float4*>(a.fbuf + row + p) = make_float4(f[0], f[1], f[2], f[3]);
+          *reinterpret_cast<float4*>(a.prior + row + p) = make_float4(rr[0], rr[1], rr[2], rr[3]);
+          return;
+        }
+        const uint32_t key[4] = {__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+        *reinterpret_cast<uint4*>(a.keys + row + p) = make_uint4(key[0], key[1], key[2], key[3]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (p + i < NJ) atomicAdd(&s_hist[bin_of(key[i])], 1u);
+      };
+      auto score = [&](int p, const float* src) {
+        float f[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-      for (int g = 0; g < G; ++g) add_evidence(f, *reinterpret_cast<const float4*>(src + g * kTile), a.alpha, s_M[g], s_c[g]);
+        for (int g = 0; g < G; ++g) add_evidence(f, *reinterpret_cast<const float4*>(src + g * kTile), a.alpha, s_M[g], s_c[g]);
+        rank(p, f, FULL ? *reinterpret_cast<const float4*>(src + G * kTile) : make_float4(0.f, 0.f, 0.f, 0.f));
+      };
+      // eight tiles at a time, a quad of positions per lane
+      if (own) {
+        for (int k0 = 0; k0 < KJ; k0 += 8) {
+          const int k = k0 + (lane >> 3), t = first0 + w + k * step0, p = t * kTile + (lane & 7) * 4;
+          if (p >= NJ) continue;
+          if (k < in_lds) score(p, kept + k * tile_f + (lane & 7) * 4);
+          else if (k < KJ) score(p, lg + (int64_t)t * tile_f + (lane & 7) * 4);
+        }
+      } else {  // the same lanes in the same order, four trips' requests at once
+        const int K = tiles_of_wave(first + w, step, end);
+        for (int k0 = 0; k0 < K; k0 += 32) {
+          float f[4][4] = {};
+          const float* src[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) src[i] = lg + (int64_t)(first + w + min(k0 + 8 * i + (lane >> 3), K - 1) * step) * tile_f + (lane & 7) * 4;
+#pragma unroll 4
+          for (int g = 0; g < G; ++g) {
+            float4 l[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) l[i] = load_far4(src[i] + g * kTile);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) add_evidence(f[i], l[i], a.alpha, s_M[g], s_c[g]);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int k = k0 + 8 * i + (lane >> 3);
+            const float4 k4 = FULL ? load_far4(src[i] + G * kTile) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k < K) rank((first + w + k * step) * kTile + (lane & 7) * 4, f[i], k4);
+          }
+        }
+      }
       if (FULL) {
-        const float4 k4 = *reinterpret_cast<const float4*>(src + G * kTile);
-        const float rr[4] = {prior(k4.x, p), prior(k4.y, p + 1), prior(k4.z, p + 2), prior(k4.w, p + 3)};
-        evidence_of_mu(f, a.alpha, a.inv_alpha, p, NJ);
-        add_sums(sums, f, rr);
-        *reinterpret_cast<float4*>(a.fbuf + row + p) = make_float4(f[0], f[1], f[2], f[3]);
-        *reinterpret_cast<float4*>(a.prior + row + p) = make_float4(rr[0], rr[1], rr[2], rr[3]);
-        return;
+#pragma unroll
+        for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
+        if (lane == 0) {
+#pragma unroll
+          for (int i = 0; i < kSegStats; ++i) s_sums[w][i] = sums[i];
+        }
       }
-      const uint32_t key[4] = {__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
-      *reinterpret_cast<uint4*>(a.keys + row + p) = make_uint4(key[0], key[1], key[2], key[3]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (p + i < NJ) atomicAdd(&s_hist[bin_of(key[i])], 1u);
-    };
-    const int in_lds = max(0, min(KJ, stay - used));
-    if (in_lds < KJ) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the wave's other logits are written
-    for (int k0 = 0; k0 < KJ; k0 += 8) {
-      const int k = k0 + (lane >> 3), p = (first + k * step) * kTile + (lane & 7) * 4;
-      if (k < in_lds) score(p, stash + (used + k) * tile_f + (lane & 7) * 4);
-      else if (k < KJ) score(p, lg + (int64_t)(first + k * step) * tile_f + (lane & 7) * 4);
-    }
-    used += KJ;
-    if (FULL) {
-#pragma unroll
-      for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
-      if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < kSegStats; ++i) s_sums[w][i] = sums[i];
-      }
-    }
-    __syncthreads();
-    if (FULL) {
-      if (tid < kSegStats)
-        a.wg_stat[((int64_t)bh * kSlotCap + slot) * kSegStats + tid] = (s_sums[0][tid] + s_sums[1][tid]) + (s_sums[2][tid] + s_sums[3][tid]);
+      if (own && tid == 0) s_go = out >> 32 == 0 ? 0u : (uint32_t)out == (uint32_t)(n_rec - 1) ? 2u : 1u;
       __syncthreads();
-    } else {
-      reinterpret_cast<uint2*>(a.wg_hist + ((int64_t)bh * kSlotCap + slot) * kHistBins)[tid] = reinterpret_cast<const uint2*>(s_hist)[tid];
-      reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);  // for the next sequence, in front of its barrier
+      if (FULL) {
+        if (tid < kSegStats)
+          a.wg_stat[((int64_t)bh * kSlotCap + slot) * kSegStats + tid] = (s_sums[0][tid] + s_sums[1][tid]) + (s_sums[2][tid] + s_sums[3][tid]);
+      } else {
+        reinterpret_cast<uint2*>(a.wg_hist + ((int64_t)bh * kSlotCap + slot) * kHistBins)[tid] = reinterpret_cast<const uint2*>(s_hist)[tid];
+        reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);  // for the next record, in front of its barrier
+      }
+      if (own) {
+        if (s_go == 0u) break;
+        last = s_go == 2u;
+      }
+      own = false;
     }
   }
 }

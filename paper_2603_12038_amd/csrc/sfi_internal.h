@@ -97,7 +97,8 @@ struct Workspace {
   float* mu;          // [B*Hkv][ld]  windowed evidence: accumulator over the window's queries
   uint32_t* arrive;   // [B*Hkv][kWaves][kArriveStride]  workgroups of a split fast-step launch whose wave w has written its heads' records
   uint64_t* met;      // [B*Hq][kSlotCap]  scoring in the dense launch: each workgroup's statistics over J (zero between steps)
-  unsigned long long* met_late;  // [B*Hkv]  ... mask of the records whose workgroup has not waited to the end (zero between steps)
+  unsigned long long* met_left;  // [B*Hkv]  ... mask of the records that their workgroup has left to the pair's others (zero between steps)
+  unsigned long long* met_out;   // [B*Hkv]  ... workgroups counted out, and how many of them have left their record << 32 (zero between steps)
   int4* met_tiles;    // [B*Hkv][kSlotCap]  ... { first, step, end, - } of the tiles of the records in the mask
   uint32_t* wg_hist;  // [B*Hkv][kSlotCap][kHistBins]  ... mode 0: key histogram of each workgroup
   double* wg_stat;    // [B*Hkv][kSlotCap][kSegStats]  ... full Selector: each workgroup's sums for lambda*
@@ -137,7 +138,8 @@ struct AttnArgs {
   int32_t cached_rows;           // evidence mode: 0 = all rows the launch may read fit the caches; else how many rows per head do
   float* logits;                 // dense mode, nullptr: do not expose logits
   uint64_t* met;                 // dense mode, nullptr or: the launch scores (score_tail); Workspace::met
-  unsigned long long* met_late;  //   ... Workspace::met_late
+  unsigned long long* met_left;  //   ... Workspace::met_left
+  unsigned long long* met_out;   //   ... Workspace::met_out
   int4* met_tiles;               //   ... Workspace::met_tiles
   uint32_t* wg_hist;             //   ... Workspace::wg_hist
   uint32_t* keys;                //   ... Workspace::keys
@@ -257,8 +259,7 @@ struct SelArgs {
   int32_t len_cap;         // the clamp the dense launch applied to ctx_len
   int32_t out_bf16;        // merge_out is bf16
   uint64_t* met;           // nullptr or: the dense launch has scored; Workspace::met
-  unsigned long long* met_late;  //   ... Workspace::met_late
-  const int4* met_tiles;   //   ... Workspace::met_tiles
+  unsigned long long* met_out;  //   ... Workspace::met_out
   const uint32_t* wg_hist;  //   ... Workspace::wg_hist (mode 0)
   const double* wg_stat;   //   ... Workspace::wg_stat (full Selector)
   int32_t place_x;         // the launch's segments lie along the grid's first index, not its second (set by the launch)

@@ -422,12 +422,11 @@ __global__ __launch_bounds__(kSelThreads) void sel_prior_kernel(const SelArgs a)
 // rows, took 27 us for a J of 131072 positions of 8 heads).  More than eight heads: the scores are worked out twice, once
 // for the head softmax's running maximum and sum, once for the keys.
 // HIST: also the heads' histograms, added to their segment's (kSelSeg / kFuseSpan workgroups share one).
-// WGS: the dense launch has scored (score_tail), and the sums are its workgroups'.  Records whose workgroup gave the wait up are worked off here, by every workgroup for itself: the sums of
-// all of them, the evidence and the prior of its own columns.  (As late_records: no path to be on.)
+// WGS: the dense launch has scored (score_tail), and the sums are its workgroups'.
 template <bool HIST, bool LIST, bool WGS>
 __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a) {
   ask(a);
-  if (WGS) asm volatile("" ::"s"(a.met_late), "s"(a.wg_stat));
+  if (WGS) asm volatile("" ::"s"(a.wg_stat));
   asm volatile("" ::"s"(a.fbuf), "s"(a.prior), "s"(a.segstat), "s"(a.n_seg_cap), "s"(a.nms_radius), "s"(a.eps), "s"(a.alpha_soft),
                "s"(a.alpha_cross), "s"(a.inv_temp), "s"(a.lambda_clip));
   constexpr int kGroup = 8;
@@ -436,65 +435,7 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
   __shared__ __align__(16) float s_zn[kGroup][kFuseSpan];
   __shared__ float s_mx[kFuseSpan], s_sum[kFuseSpan];
   __shared__ float s_w[2][kGroup];  // weights of f and of the prior
-  __shared__ double s_lsum[WGS ? kGroup : 1][kSegStats];
-  __shared__ double s_lred[WGS ? kFuseThreads / 64 : 1][kSegStats];
-  __shared__ float s_lM[16], s_lc[16];
   const int Hkv = a.Hkv, rad = a.nms_radius;
-  // records that were left: sums to s_lsum, evidence and prior of this workgroup's columns to memory
-  auto late_columns = [&](int h0, int nh, int nJ, int p_lo, int tid, const Cell& c) {
-    const Prior prior(a.prior_args, nJ);
-    const int rows = a.lg_rows;
-#pragma unroll 1
-    for (int hh = 0; hh < nh; ++hh) {
-      Cell ch = c;
-      ch.bh = c.bh + h0 + hh;
-      const uint64_t left = a.met_late[ch.bh];
-      if (left == 0) continue;  // uniform
-      __syncthreads();
-      group_stats<16>(a, ch, kFuseThreads / 64, s_lM, s_lc);
-      __syncthreads();
-      const float* lg = a.logits + (int64_t)ch.bh * rows * a.ld_pos;
-      const int64_t row = (int64_t)ch.bh * a.ld_pos;
-      double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-      for (int sl = 0; sl < c.n_rec; ++sl) {
-        if ((left >> sl & 1u) == 0u) continue;
-        const int4 tiles = a.met_tiles[(int64_t)ch.bh * kSlotCap + sl];
-#pragma unroll 1
-        for (int k0 = 0; tiles.x + k0 * tiles.y < tiles.z; k0 += kFuseThreads / 32) {
-          const int t = tiles.x + (k0 + (tid >> 5)) * tiles.y + (tid >> 3 & 3), p = t * kTile + (tid & 7) * 4;
-          if (t >= tiles.z || p >= nJ) continue;
-          float f[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-          for (int g = 0; g < a.G; ++g) add_evidence(f, logits4(lg, rows, p, g), a.alpha, s_lM[g], s_lc[g]);
-          const float4 k4 = logits4(lg, rows, p, a.G);
-          const float rr[4] = {prior(k4.x, p), prior(k4.y, p + 1), prior(k4.z, p + 2), prior(k4.w, p + 3)};
-          evidence_of_mu(f, a.alpha, a.inv_alpha, p, nJ);
-          add_sums(sums, f, rr);
-          if (p + 3 >= p_lo - rad && p < p_lo + kFuseSpan + rad) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              __hip_atomic_store(a.fbuf + row + p + i, f[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              __hip_atomic_store(a.prior + row + p + i, rr[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
-      if ((tid & 63) == 0)
-#pragma unroll
-        for (int i = 0; i < kSegStats; ++i) s_lred[tid >> 6][i] = sums[i];
-      __syncthreads();
-      if (tid < kSegStats) {
-        double t = 0.0;
-        for (int i = 0; i < kFuseThreads / 64; ++i) t += s_lred[i][tid];
-        s_lsum[hh][tid] = t;
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the columns are out before another thread reads them
-    __syncthreads();
-  };
   const int zs = kFuseSpan + 2 * rad;
   for_cells<LIST>(a, 0, [&](const Cell& c, const int tid) {  // (c.bh is the sequence's first pair)
     const int lane = tid & 63, w = tid >> 6;
@@ -505,31 +446,17 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
     // scores after Soft-NMS of heads h0 .. h0 + nh - 1 -> s_zn
     auto scores = [&](int h0, int nh) {
       const int n_seg = WGS ? c.n_rec : (nJ + kPriorSeg - 1) / kPriorSeg;
-      uint64_t late = 0;  // lane: records of head h0 + lane that were left
-      if (WGS) late = a.met_late[c.bh + h0 + min(lane, nh - 1)];
       float fb[kGroup], pr[kGroup];  // this thread's column (position p_lo - rad + tid) of all heads, requested together
       {
         const int64_t o = (int64_t)(c.bh + h0) * a.ld_pos + min(max(p_lo - rad + tid, 0), nJ - 1);
 #pragma unroll
         for (int hh = 0; hh < kGroup; ++hh) {
-          const int64_t at = o + (int64_t)min(hh, nh - 1) * a.ld_pos;
-          fb[hh] = a.fbuf[at];
-          pr[hh] = a.prior[at];
-        }
-        if (WGS && __ballot(late != 0) != 0) {  // uniform over the sequence
-          late_columns(h0, nh, nJ, p_lo, tid, c);
-#pragma unroll
-          for (int hh = 0; hh < kGroup; ++hh) {  // (behind the stores of other threads)
-            const int64_t at = o + (int64_t)min(hh, nh - 1) * a.ld_pos;
-            fb[hh] = __hip_atomic_load(a.fbuf + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            pr[hh] = __hip_atomic_load(a.prior + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
+          fb[hh] = a.fbuf[o + (int64_t)min(hh, nh - 1) * a.ld_pos];
+          pr[hh] = a.prior[o + (int64_t)min(hh, nh - 1) * a.ld_pos];
         }
       }
       if (w < nh) {  // a wave per head: lambda* in double precision, in a fixed order
         const double* st = WGS ? a.wg_stat + (int64_t)(c.bh + h0 + w) * kSlotCap * kSegStats : a.segstat + (int64_t)(c.bh + h0 + w) * a.n_seg_cap * kSegStats;
-        // records without sums
-        const uint64_t off = WGS ? (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(late >> 32), __builtin_amdgcn_readfirstlane(w)) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)late, __builtin_amdgcn_readfirstlane(w)) : 0;
         double tot[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
         for (int s0 = lane; s0 - lane < n_seg; s0 += 128) {  // two segments' sums in flight per lane
           double t0[kSegStats], t1[kSegStats];
@@ -539,11 +466,8 @@ __global__ __launch_bounds__(kFuseThreads) void sel_fuse_kernel(const SelArgs a)
             t1[i] = st[(int64_t)min(s0 + 64, n_seg - 1) * kSegStats + i];
           }
 #pragma unroll
-          for (int i = 0; i < kSegStats; ++i) tot[i] += (s0 < n_seg && (!WGS || (off >> s0 & 1u) == 0u) ? t0[i] : 0.0) + (s0 + 64 < n_seg ? t1[i] : 0.0);
+          for (int i = 0; i < kSegStats; ++i) tot[i] += (s0 < n_seg ? t0[i] : 0.0) + (s0 + 64 < n_seg ? t1[i] : 0.0);
         }
-        if (WGS && off != 0 && lane == 0)
-#pragma unroll
-          for (int i = 0; i < kSegStats; ++i) tot[i] += s_lsum[w][i];
 #pragma unroll
         for (int i = 0; i < kSegStats; ++i) tot[i] = wave_sum_d(tot[i]);
         // f and r normalised to sum 1: |f|^2 = tot2 / F^2, f.r = tot3 / (F R), |r|^2 = tot4 / R^2
@@ -785,39 +709,6 @@ __global__ __launch_bounds__(kSelThreads) void sel_group_kernel(const SelArgs a)
   });
 }
 
-// Records whose workgroup of the dense launch gave the wait up (score_tail): their tiles' logits are in memory, their
-// histograms are not there.  Each of the pair's workgroups scores all of them, for the histogram, and keeps the keys of its segment.  This
-// is no path to be on: it is there for a dense launch that had to share the chip.
-// h: kHistBins words of LDS for the histogram of these records; valid, and the keys in memory, behind this.
-__device__ __forceinline__ void late_records(const SelArgs& a, const Cell& c, const uint64_t late, const int p_lo, const int nJ, uint32_t* h,
-                                             float* s_M, float* s_c) {
-  const int tid = threadIdx.x, G = a.G;
-  const float* lg = a.logits + (int64_t)c.bh * a.lg_rows * a.ld_pos;
-  uint32_t* keys = a.keys + (int64_t)c.bh * a.ld_pos;
-  group_stats<16>(a, c, kSelThreads / 64, s_M, s_c);
-  reinterpret_cast<uint2*>(h)[tid] = make_uint2(0u, 0u);
-  __syncthreads();
-  for (int sl = 0; sl < c.n_rec; ++sl) {
-    if ((late >> sl & 1u) == 0u) continue;
-    const int4 tiles = a.met_tiles[(int64_t)c.bh * kSlotCap + sl];
-    const int first = tiles.x, step = tiles.y, end = tiles.z;
-    for (int k0 = 0; first + k0 * step < end; k0 += 8) {  // eight times four tiles, one per wave of the dense workgroup, eight quads each
-      const int t = first + (k0 + (tid >> 5)) * step + (tid >> 3 & 3), p = t * kTile + (tid & 7) * 4;
-      if (t >= end || p >= nJ) continue;
-      float f[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-      for (int g = 0; g < G; ++g) add_evidence(f, logits4(lg, a.lg_rows, p, g), a.alpha, s_M[g], s_c[g]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (p + i < nJ) atomicAdd(&h[bin_of(__float_as_uint(f[i]))], 1u);
-        if (p >= p_lo && p < p_lo + kSelSeg) __hip_atomic_store(keys + p + i, __float_as_uint(f[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the keys are out before another thread reads them
-  __syncthreads();
-}
-
 // ---- long J, stage 2: find the threshold bin, collect its keys ------------------------------------------
 // FROM: whose histograms are added up, FROM_SEGS, FROM_GROUPS (behind sel_group_kernel) or FROM_WGS: the dense launch has
 // scored, each of its workgroups (records) with a histogram of its own.  FROM_WGS, FROM_SEGS_MERGE (the full Selector behind such a
@@ -828,7 +719,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.hist), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap));
   constexpr bool GROUPS = FROM == FROM_GROUPS, WGS = FROM == FROM_WGS, MERGE = WGS || FROM == FROM_SEGS_MERGE;
-  if (WGS) asm volatile("" ::"s"(a.met_late), "s"(a.wg_hist));
+  if (WGS) asm volatile("" ::"s"(a.wg_hist));
   if (MERGE) asm volatile("" ::"s"(a.merge_out), "s"(a.part), "s"(a.G));
   const Place place = place_of(a);
   const int seg = place.i;
@@ -836,8 +727,6 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
   __shared__ __align__(16) uint32_t s_cnt[kSelThreads / 64][kHistBins];
   __shared__ uint32_t s_res[2];
   __shared__ uint32_t s_scr[2][kSelThreads / 64];
-  __shared__ __align__(16) uint32_t s_late[WGS ? kHistBins : 1];
-  __shared__ float s_M[16], s_c[16];
   for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     const int lane = tid & 63, w = tid >> 6;
     if (cell_off<LIST>(a, c)) return;
@@ -875,23 +764,13 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
       }
     }
     if (WGS) {
-      const uint64_t late = a.met_late[c.bh];
       const uint32_t* wh = a.wg_hist + (int64_t)c.bh * kSlotCap * kHistBins;
 #pragma unroll 2
       for (int sl = w; sl < c.n_rec; sl += kSelThreads / 64) {
         const uint4* gh = reinterpret_cast<const uint4*>(wh + sl * kHistBins) + 2 * lane;
-        uint4 q0 = gh[0], q1 = gh[1];
-        if (late >> sl & 1u) q0 = q1 = make_uint4(0u, 0u, 0u, 0u);  // no histogram
+        const uint4 q0 = gh[0], q1 = gh[1];
         cnt[0] += q0.x; cnt[1] += q0.y; cnt[2] += q0.z; cnt[3] += q0.w;
         cnt[4] += q1.x; cnt[5] += q1.y; cnt[6] += q1.z; cnt[7] += q1.w;
-      }
-      if (late != 0) {  // uniform over the pair
-        late_records(a, c, late, p_lo, nJ, s_late, s_M, s_c);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          cnt[i] += w == 0 ? s_late[8 * lane + i] : 0u;
-          key[i] = __hip_atomic_load(a.keys + (int64_t)c.bh * a.ld_pos + p0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
       }
     }
 #pragma unroll 4
@@ -942,7 +821,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
 template <bool LIST>
 __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a) {
   ask(a);
-  asm volatile("" ::"s"(a.state), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap), "s"(a.sel_idx), "s"(a.n_sel), "s"(a.met), "s"(a.met_late));
+  asm volatile("" ::"s"(a.state), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap), "s"(a.sel_idx), "s"(a.n_sel), "s"(a.met), "s"(a.met_out));
   const Place place = place_of(a);
   const int seg = place.i;
   const int n_seg = place.n;
@@ -987,7 +866,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
     for (int i = (int)ksel + seg * kSelThreads + tid; i < a.budget; i += n_seg * kSelThreads) out[i] = -1;
     if (seg == 0 && tid == 0) {
       a.n_sel[bh] = (int32_t)ksel;
-      if (a.met != nullptr) a.met_late[bh] = 0;
+      if (a.met != nullptr) a.met_out[bh] = 0;
     }
     if (seg == 0 && a.met != nullptr) {  // for the next dense launch
       for (int i = tid; i < a.G * (kSlotCap / 2); i += kSelThreads) reinterpret_cast<uint4*>(a.met + bh * a.G * kSlotCap)[i] = make_uint4(0u, 0u, 0u, 0u);

@@ -82,8 +82,9 @@ def test_same_bits_as_the_scoring_launch(B, Hkv, G, lens, page, alpha, ragged):
         ctx.close()
 
 
-# The full Selector.  The sums for lambda* are fp64 sums taken in another order, so a weight may round to the neighbouring float and
-# two positions at the threshold change places: at most two of a set here (none is seen), everything else the same bits.
+# The full Selector.  The sums for lambda* are fp64 sums taken in another order than the scoring launch's, so a weight may round to the neighbouring
+# float and two positions at the threshold change places: at most two of a set here (none is seen), everything else the same bits.  Whether records
+# were left or not, the order is the same, and so are all bits.
 @pytest.mark.parametrize("B,Hkv,G,lens,page,alpha", [(1, 8, 4, [131071], 0, 1.0), (1, 16, 16, [40000], 0, 0.5), (3, 8, 5, [40000, 100, 17003], 16, 1.0),
                                                      (2, 7, 2, [50000, 20001], 0, 0.5), (4, 4, 4, [33000] * 4, 0, 1.0), (2, 3, 1, [30000, 66], 0, 1.0)])
 def test_full_selector(B, Hkv, G, lens, page, alpha):
@@ -92,7 +93,7 @@ def test_full_selector(B, Hkv, G, lens, page, alpha):
     sfi, ctx, K, V, table, q, c = _setup(B, Hkv, G, lens, page, alpha, full=True)
     h, n = ctx.handle, max(lens)
     try:
-        want = {}
+        want, scored = {}, {}
         for i, mode in enumerate((0, 0, 4, 4, 2, 2, 3, 3, 1, 1, 4, 4)):
             sfi.sfi_set_dense_scores(h, mode)
             out = torch.full((B, Hkv * G, 128), float("nan"), device="cuda")
@@ -103,6 +104,8 @@ def test_full_selector(B, Hkv, G, lens, page, alpha):
             want.setdefault(i % 2, (out, sel, nsel))
             w_out, w_sel, w_nsel = want[i % 2]
             assert torch.equal(out, w_out) and torch.equal(nsel, w_nsel), mode
+            if mode > 1:
+                assert torch.equal(scored.setdefault(i % 2, sel), sel), mode
             for a, b in zip(sel.view(B * Hkv, -1).tolist(), w_sel.view(B * Hkv, -1).tolist()):
                 assert len(set(a) - set(b)) <= 2, mode
         assert sfi.sfi_device_status(h) == 0
@@ -289,3 +292,29 @@ def test_contexts_that_share_the_gpu(name, contexts, B, lens, G, full, ragged):
         torch.cuda.synchronize()
         for ctx in ctxs:
             ctx.close()
+
+
+def test_records_that_are_left_are_scored_once():
+    """With no wait every record is left.  A record scored by every workgroup of a later launch took 7 times the step here; scored once, by the last
+    workgroup of its pair, 2.4 times, which is the most it can be: eight workgroups do the scoring of the whole launch."""
+    import torch
+    sfi, ctx, K, V, table, q, c = _setup(1, 8, 4, [131071], 0, 1.0, full=True)
+    h, best = ctx.handle, {}
+    out = torch.zeros((1, 32, 128), device="cuda")
+    sel = torch.zeros((1, 8, BUDGET), dtype=torch.int32, device="cuda")
+    nsel = torch.zeros((1, 8), dtype=torch.int32, device="cuda")
+    try:
+        for mode in (0, 2) * 6:
+            sfi.sfi_set_dense_scores(h, mode)
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            e0.record()
+            for _ in range(3):
+                sfi.sfi_slow_step(h, q[0], K, V, c, 131071, BUDGET, out, sel, nsel)
+            e1.record()
+            torch.cuda.synchronize()
+            best[mode] = min(best.get(mode, 1e9), e0.elapsed_time(e1) * 1e3 / 3)
+        print("[gpu-dense-scores] us a step:", best, flush=True)
+        assert best[2] < 4 * best[0]
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
