@@ -104,7 +104,7 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   // exposed rows per (b, h): the G heads' y and, for the full Selector, the squared key norms
   ws->logits = (float*)take((size_t)(B * Hq + (full ? B * Hkv : 0)) * ld * sizeof(float));
   ws->keys = (uint32_t*)take((size_t)(B * Hkv) * ld * sizeof(uint32_t));
-  ws->cand = (uint32_t*)take((size_t)(B * Hkv) * ld * sizeof(uint32_t));
+  ws->cand = (uint32_t*)take((size_t)(B * Hkv) * ld * 2 * sizeof(uint32_t));
   ws->state = (uint32_t*)take((size_t)(B * Hkv) * kStateWords * sizeof(uint32_t));
   ws->segcnt = (uint32_t*)take((size_t)(B * Hkv) * n_seg * sizeof(uint32_t));
   ws->jstat = (float2*)take((size_t)(B * Hq) * sizeof(float2));

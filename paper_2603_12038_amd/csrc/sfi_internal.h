@@ -57,7 +57,7 @@ __device__ __forceinline__ void store_out4(float* out, int64_t elem, float4 v, b
 }
 
 // Per (sequence, KV head) Selector state words.
-enum SelState { ST_BIN1 = 0, ST_K1 = 1 };
+enum SelState { ST_BIN1 = 0, ST_K1 = 1, ST_CAND = 2 };
 
 // A window query under the causal mask (Eq. window_logits): the query sits at row q_len - 1 of a context that ends
 // at row L_end - 1, sees rows [0, q_len) only, and its evidence covers the part of the allowed set
@@ -84,7 +84,8 @@ struct Workspace {
   float* part;        // [B*Hq][kSlotCap][kPartStride]
   float* logits;      // [B*Hq][ld_pos]   J-relative positions
   uint32_t* keys;     // [B*Hkv][ld_pos]  fp32 bit pattern of the evidence f
-  uint32_t* cand;     // [B*Hkv][ld_pos]  keys falling into the threshold bin, each segment's from its first position on
+  uint32_t* cand;     // [B*Hkv][ld_pos][2]  keys falling into the threshold bin: the pair's list, each with its segment, or a run per segment from its
+                      //   first position on, the keys alone
   uint32_t* hist;     // [B*Hkv][n_seg_cap][kHistBins / 2]  coarse key histogram of each segment, 16-bit counters
   uint32_t* state;    // [B*Hkv][kStateWords]
   uint32_t* segcnt;   // [B*Hkv][n_seg_cap]  keys of each segment in the threshold bin, and above it << 16

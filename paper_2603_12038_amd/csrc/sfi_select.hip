@@ -714,18 +714,21 @@ __global__ __launch_bounds__(kSelThreads) void sel_group_kernel(const SelArgs a)
 // scored, each of its workgroups (records) with a histogram of its own.  FROM_WGS, FROM_SEGS_MERGE (the full Selector behind such a
 // launch): the workgroups behind the segments' merge the dense records.
 enum { FROM_SEGS = 0, FROM_GROUPS = 1, FROM_WGS = 2, FROM_SEGS_MERGE = 3 };
+// The candidates lie in one list per pair, each key with its segment: the segments' histograms say where a segment's part begins, and the write
+// launch's threads share the list out evenly.  FROM_WGS: those histograms are not there, and each segment has a run of its own from its first position
+// on, with its length in segcnt.  (Runs there too: 16 x 20000..60000 rows, half slow, write launch 8.9 -> 12.3 us; 32 x 16384..65536, two slow, 6.2 -> 8.0.)
 template <bool LIST, int FROM>
 __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.hist), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap));
-  constexpr bool GROUPS = FROM == FROM_GROUPS, WGS = FROM == FROM_WGS, MERGE = WGS || FROM == FROM_SEGS_MERGE;
+  constexpr bool GROUPS = FROM == FROM_GROUPS, WGS = FROM == FROM_WGS, RUNS = WGS, MERGE = WGS || FROM == FROM_SEGS_MERGE;
   if (WGS) asm volatile("" ::"s"(a.wg_hist));
   if (MERGE) asm volatile("" ::"s"(a.merge_out), "s"(a.part), "s"(a.G));
   const Place place = place_of(a);
   const int seg = place.i;
   const int p_lo = seg * kSelSeg;
   __shared__ __align__(16) uint32_t s_cnt[kSelThreads / 64][kHistBins];
-  __shared__ uint32_t s_res[2];
+  __shared__ uint32_t s_res[2], s_before[kSelThreads / 64], s_all[kSelThreads / 64];
   __shared__ uint32_t s_scr[2][kSelThreads / 64];
   for_cells<LIST>(a, place.head, [&](const Cell& c, const int tid) {
     const int lane = tid & 63, w = tid >> 6;
@@ -789,9 +792,29 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
       hv[i] = s_cnt[0][bin] + s_cnt[1][bin] + s_cnt[2][bin] + s_cnt[3][bin];
     }
     uint32_t* st = a.state + (int64_t)c.bh * kStateWords;
-    uint32_t* cand = a.cand + (int64_t)c.bh * a.ld_pos + p_lo;  // the segment's own run
     find_kth_desc<kSelThreads, 2>(hv, kHistBins, ksel, s_res, s_scr[0]);
     const uint32_t bin1 = s_res[0];
+    if (!RUNS) {  // candidates of the segments before this one: where this segment's part of the list begins
+      uint32_t before = 0, all = 0;
+      const int my_grp = seg / kHistGroup;
+      for (int gr = tid; GROUPS && gr < n_grp; gr += kSelThreads) {
+        const uint32_t x = group_hist(a, c.bh, gr)[bin1];
+        all += x;
+        before += gr < my_grp ? x : 0u;
+      }
+      for (int sg = (GROUPS ? my_grp * kHistGroup : 0) + tid; sg < (GROUPS ? seg : n_seg); sg += kSelThreads) {
+        const uint32_t v = seg_hist(a, c.bh, sg)[bin1 >> 1];
+        const uint32_t x = (bin1 & 1u) ? v >> 16 : v & 0xffffu;
+        if (!GROUPS) all += x;
+        before += sg < seg ? x : 0u;
+      }
+      before = wave_sum(before);
+      all = wave_sum(all);
+      if (lane == 0) {
+        s_before[w] = before;
+        s_all[w] = all;
+      }
+    }
     uint32_t mine = 0;  // bit i: key i falls into the threshold bin
     uint32_t above = 0; // keys of this thread in a higher bin: selected whatever the exact threshold is
 #pragma unroll
@@ -803,22 +826,27 @@ __global__ __launch_bounds__(kSelThreads) void sel_cand_kernel(const SelArgs a) 
       }
     }
     // One prefix sum over the workgroup gives the segment's counts of candidates and of keys above the threshold bin (for
-    // the write stage's prefix) and every thread's place in the segment's run of candidates.
+    // the write stage's prefix) and every thread's place among the segment's candidates.
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kSelThreads>((uint32_t)__popc(mine) | (above << 16), s_scr[1], &total);
+    const uint32_t ex = block_excl_scan<kSelThreads>((uint32_t)__popc(mine) | (above << 16), s_scr[1], &total);  // (its barrier covers s_before)
     if (tid == 0) {
       a.segcnt[(int64_t)c.bh * a.n_seg_cap + seg] = total;
-      if (seg == 0) *reinterpret_cast<uint2*>(st) = make_uint2(bin1, s_res[1]);
+      if (seg == 0) *reinterpret_cast<uint4*>(st) = make_uint4(bin1, s_res[1], RUNS ? 0u : s_all[0] + s_all[1] + s_all[2] + s_all[3], 0u);
     }
-    uint32_t at = ex & 0xffffu;
+    uint2* const list = reinterpret_cast<uint2*>(a.cand) + (int64_t)c.bh * a.ld_pos;
+    uint32_t* const run = a.cand + (int64_t)c.bh * a.ld_pos + p_lo;
+    uint32_t at = (RUNS ? 0u : s_before[0] + s_before[1] + s_before[2] + s_before[3]) + (ex & 0xffffu);
 #pragma unroll
-    for (int i = 0; i < kPer; ++i)
-      if (mine & (1u << i)) cand[at++] = key[i];
+    for (int i = 0; i < kPer; ++i) {
+      if ((mine & (1u << i)) == 0u) continue;
+      if (RUNS) run[at++] = key[i];
+      else list[at++] = make_uint2(key[i], (uint32_t)seg);
+    }
   });
 }
 
 // ---- long J, stage 3: exact threshold among the candidates, index-ordered write of the selected set -------
-template <bool LIST>
+template <bool LIST, bool RUNS>
 __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a) {
   ask(a);
   asm volatile("" ::"s"(a.state), "s"(a.cand), "s"(a.segcnt), "s"(a.n_seg_cap), "s"(a.sel_idx), "s"(a.n_sel), "s"(a.met), "s"(a.met_out));
@@ -839,18 +867,26 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
     const int p0 = p_lo + tid * kPer;
     const int64_t bh = c.bh;
     // Requested together: the state words, the thread's keys (the key row is padded to whole segments), the counts of the
-    // segments before this one, and kSpec candidates, whether or not there are so many: the threads go round the segments in
-    // equal groups, each with the first candidates of its segment.
-    constexpr int kSpec = 8;
-    const uint2 st2 = *reinterpret_cast<const uint2*>(a.state + bh * kStateWords);
+    // segments before this one, and the first kSpec candidates per thread, whether or not there are so many.  RUNS: the threads go round
+    // the segments in equal groups, each with the first candidates of its segment.
+    constexpr int kSpec = RUNS ? 8 : 4;
+    const uint4 st4 = *reinterpret_cast<const uint4*>(a.state + bh * kStateWords);
     const uint32_t* cand = a.cand + bh * a.ld_pos;
+    const uint2* list = reinterpret_cast<const uint2*>(a.cand) + bh * a.ld_pos;
     const uint32_t* segcnt = a.segcnt + bh * a.n_seg_cap;
     const int lg_grp = max(0, __builtin_clz((n_seg - 1) | 1) - 24);  // log2 of the threads of a segment
     const int c_seg = min(tid >> lg_grp, n_seg - 1), c_at = tid & ((1 << lg_grp) - 1), n_spec = kSpec << lg_grp;
-    uint32_t cd[kSpec];  // candidates c_at, c_at + group, ... of the segment: a short run leaves the later rounds empty for a whole wave
+    uint32_t cd[RUNS ? kSpec : 1];  // candidates c_at, c_at + group, ... of the segment: a short run leaves the later rounds empty for a whole wave
+    uint2 ld[RUNS ? 1 : kSpec];
+    int n_cd = 0;
+    if (RUNS) {
 #pragma unroll
-    for (int i = 0; i < kSpec; ++i) cd[i] = cand[(int64_t)c_seg * kSelSeg + c_at + (i << lg_grp)];
-    int n_cd = (int)(segcnt[c_seg] & 0xffffu);
+      for (int i = 0; i < kSpec; ++i) cd[RUNS ? i : 0] = cand[(int64_t)c_seg * kSelSeg + c_at + (i << lg_grp)];
+      n_cd = (int)(segcnt[c_seg] & 0xffffu);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kSpec; ++i) ld[RUNS ? 0 : i] = list[tid + i * kSelThreads];
+    }
     uint32_t key[kPer];
     {
       const uint32_t* keys = a.keys + bh * a.ld_pos;
@@ -880,23 +916,38 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
     // Exact threshold tau and tie quota among the keys of the threshold bin (typically a few hundred): two LDS radix
     // passes, bits [19:10] then [9:0]; every workgroup of the pair does the same.  The end bins of the histogram
     // hold keys of any magnitude: a pass over bits [30:20] comes first.
-    const uint32_t bin1 = st2.x;
-    uint32_t k_left = st2.y, prefix = bin1 + (1024 - kHistBins);  // bits [30:20] of the threshold
-    static_assert(ST_BIN1 == 0 && ST_K1 == 1, "one 8-byte load");
+    const uint32_t bin1 = st4.x;
+    uint32_t k_left = st4.y, prefix = bin1 + (1024 - kHistBins);  // bits [30:20] of the threshold
+    static_assert(ST_BIN1 == 0 && ST_K1 == 1 && ST_CAND == 2, "one 16-byte load");
     const bool end_bin = bin1 == 0u || bin1 == (uint32_t)kHistBins - 1u;
+    const uint32_t n_list = st4.z;
     const int n_run = (nJ + kSelSeg - 1) / kSelSeg;  // segments that have a run
     const int n_first = min(n_run, kSelThreads >> lg_grp);  // segments whose first candidates are here
     if (tid >> lg_grp >= n_first) n_cd = 0;
     bool more = n_run > n_first || n_cd > n_spec;
     for (int i = tid; i < (2048 + 1024 + 1024) / 4; i += kSelThreads) reinterpret_cast<uint4*>(s_h)[i] = make_uint4(0u, 0u, 0u, 0u);
-    const uint64_t any = __ballot(more);
-    if ((tid & 63) == 0) s_more[tid >> 6] = any != 0;
+    if (RUNS) {
+      const uint64_t any = __ballot(more);
+      if ((tid & 63) == 0) s_more[tid >> 6] = any != 0;
+    }
     __syncthreads();
-    more = (s_more[0] | s_more[1] | s_more[2] | s_more[3]) != 0u;
+    if (RUNS) more = (s_more[0] | s_more[1] | s_more[2] | s_more[3]) != 0u;
     auto each_candidate = [&](auto f) {
+      if (!RUNS) {
+#pragma unroll
+        for (int i = 0; i < kSpec; ++i) {
+          const uint2 x = ld[RUNS ? 0 : i];
+          if ((uint32_t)(tid + i * kSelThreads) < n_list) f(x.x, (int)x.y);
+        }
+        for (uint32_t i = tid + kSpec * kSelThreads; i < n_list; i += kSelThreads) {
+          const uint2 x = list[i];
+          f(x.x, (int)x.y);
+        }
+        return;
+      }
 #pragma unroll
       for (int i = 0; i < kSpec; ++i)
-        if (c_at + (i << lg_grp) < n_cd) f(cd[i], c_seg);
+        if (c_at + (i << lg_grp) < n_cd) f(cd[RUNS ? i : 0], c_seg);
       if (more) {  // the rest of longer runs, kSpec candidates a thread and trip, and of the segments behind the threads'
         for (int i0 = n_spec + c_at; i0 - c_at < n_cd; i0 += n_spec) {
           uint32_t x[kSpec];
@@ -1112,14 +1163,15 @@ hipError_t launch_sel_pick(SelArgs a, int B, int nJ, int src, hipStream_t s) {
   }
   return hipGetLastError();
 }
+static bool from_wgs(const SelArgs& a) { return a.met != nullptr && a.wg_hist != nullptr; }
 hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kSelSeg);
   const bool list = a.slow_list != nullptr;
   const dim3 block(kSelThreads);
   if (a.met != nullptr) {  // (no list) one more workgroup per query head
     const dim3 grid = place_grid(&a, n_seg + a.G, z_of(a, B, (n_seg + a.G) * a.Hkv));
-    if (a.wg_hist == nullptr) hipLaunchKernelGGL((sel_cand_kernel<false, FROM_SEGS_MERGE>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((sel_cand_kernel<false, FROM_WGS>), grid, block, 0, s, a);
+    if (from_wgs(a)) hipLaunchKernelGGL((sel_cand_kernel<false, FROM_WGS>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sel_cand_kernel<false, FROM_SEGS_MERGE>), grid, block, 0, s, a);
     return hipGetLastError();
   }
   const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv));
@@ -1143,8 +1195,10 @@ hipError_t launch_sel_cand(SelArgs a, int B, int nJ, hipStream_t s) {
 hipError_t launch_sel_write(SelArgs a, int B, int nJ, hipStream_t s) {
   const int n_seg = ceil_seg(nJ, kSelSeg);
   const dim3 grid = place_grid(&a, n_seg, z_of(a, B, n_seg * a.Hkv));
-  if (a.slow_list != nullptr) hipLaunchKernelGGL(sel_write_kernel<true>, grid, dim3(kSelThreads), 0, s, a);
-  else hipLaunchKernelGGL(sel_write_kernel<false>, grid, dim3(kSelThreads), 0, s, a);
+  const dim3 block(kSelThreads);
+  if (a.slow_list != nullptr) hipLaunchKernelGGL((sel_write_kernel<true, false>), grid, block, 0, s, a);
+  else if (from_wgs(a)) hipLaunchKernelGGL((sel_write_kernel<false, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sel_write_kernel<false, false>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
