@@ -137,10 +137,11 @@ typedef struct sfi_ctx sfi_ctx; /* opaque; host memory owned by the library */
 size_t sfi_workspace_bytes(const sfi_config* cfg);
 
 /* Validate cfg, bind the caller's workspace, return a context in *out.
- * Touches the device to read its properties and to clear a few hundred bytes of the workspace (the
- * arrival counters of the fast step's in-kernel merge and the status word of sfi_device_status; a blocking
- * memset followed by a device synchronisation, so not to be called while a stream of the device is
- * capturing).  SFI_ELAUNCH if the workspace is memory the runtime knows (device, managed or pinned host
+ * Touches the device to read its properties and to clear what the kernels expect to be zero between two calls: the
+ * arrival counters of the fast step's in-kernel merge (512 bytes per sequence and KV head), for contexts whose slow step can
+ * score in its dense launch (sfi_set_dense_scores) the statistics handed over there (512 bytes per sequence and query head), and the status word
+ * of sfi_device_status.  A blocking memset followed by a device synchronisation, so not to be called while a stream of the device is
+ * capturing.  SFI_ELAUNCH if the workspace is memory the runtime knows (device, managed or pinned host
  * memory) and could not be cleared. */
 int sfi_create(const sfi_config* cfg, void* workspace, size_t workspace_bytes, sfi_ctx** out);
 
@@ -426,7 +427,7 @@ int sfi_set_mixed_plan(sfi_ctx* ctx, int32_t on);
  * pair is computed again (more than eight KV heads: as mode 0): the same results up to the order of the sums.  Other values: SFI_EINVAL. */
 int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
 
-/* A/B knob of sfi_slow_step (more than 16384 positions to rank, batches of up to 64 sequences).
+/* A/B knob of sfi_slow_step (more than 16384 positions to rank, batches of up to 64 sequences and 256 pairs of sequence and KV head).
  * mode = 1 (default): where that is faster the dense launch also scores, each workgroup what it has read, once it has the others'
  * statistics of its sequences; it waits 64 us for them at most, for all its sequences together, and what is missing then (a launch
  * that has to share the GPU) falls to the last workgroups.  mode = 0: a scoring launch, as behind sfi_slow_attn.  mode = 2, 3, 4 (for tests): scored in the dense launch

@@ -111,11 +111,11 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->mu = (float*)take((size_t)(B * Hkv) * ld * sizeof(float));
   ws->hist = (uint32_t*)take((size_t)(B * Hkv) * n_seg * (kHistBins / 2) * sizeof(uint32_t));
   ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * kWaves * kArriveStride * sizeof(uint32_t));
-  ws->met = (uint64_t*)take((size_t)(B * Hq) * kSlotCap * sizeof(uint64_t));
-  ws->met_left = (unsigned long long*)take((size_t)(B * Hkv) * sizeof(unsigned long long));
-  ws->met_out = (unsigned long long*)take((size_t)(B * Hkv) * sizeof(unsigned long long));
+  const bool scores = B <= kScoreCap && B * Hkv <= kScorePairs && c->max_ctx - c->recent - c->n_sink > kPickMax;  // its dense launch can (score_in_dense)
+  ws->met = (uint64_t*)take(scores ? (size_t)(B * Hq) * kSlotCap * sizeof(uint64_t) : 0);
+  ws->met_left = (unsigned long long*)take(scores ? (size_t)(B * Hkv) * sizeof(unsigned long long) : 0);
+  ws->met_out = (unsigned long long*)take(scores ? (size_t)(B * Hkv) * sizeof(unsigned long long) : 0);
   ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears them all
-  const bool scores = B <= kScoreCap && c->max_ctx > kPickMax;
   ws->met_tiles = scores ? (int4*)take((size_t)(B * Hkv) * kSlotCap * sizeof(int4)) : nullptr;
   ws->wg_hist = scores && !full ? (uint32_t*)take((size_t)(B * Hkv) * kSlotCap * kHistBins * sizeof(uint32_t)) : nullptr;
   ws->wg_stat = scores && full ? (double*)take((size_t)(B * Hkv) * kSlotCap * kSegStats * sizeof(double)) : nullptr;

@@ -49,6 +49,18 @@ def test_workspace_bytes_and_config_validation():
     assert sfi.sfi_workspace_bytes(good_cfg(alpha=0.5)) == sfi.sfi_workspace_bytes(good_cfg())
 
 
+def test_workspace_has_no_hand_over_for_steps_that_cannot_score():
+    """What the dense launch hands over where it scores, 512 bytes per query head and sequence (and 132 KB per pair), only for contexts whose
+    dense launch can: another 32 query heads are otherwise their records, logits and statistics."""
+    def heads(**shape):
+        cfg = dict(k_stride_b=0, v_stride_b=0, n_kv_heads=8, **shape)
+        return sfi.sfi_workspace_bytes(good_cfg(n_q_heads=64, **cfg)) - sfi.sfi_workspace_bytes(good_cfg(n_q_heads=32, **cfg))
+
+    for batch, ctx, scores in ((32, 32768, True), (33, 32768, False), (64, 32768, False), (1024, 32768, False), (32, 16384, False), (32, 16384 + 68, False)):
+        ld = (ctx + 2047) // 2048 * 2048
+        assert heads(batch=batch, max_ctx=ctx) == batch * 32 * (64 * 528 + 4 * ld + 8 + (512 if scores else 0)), (batch, ctx)
+
+
 FULL = dict(selector_mode=1, gamma=0.5, beta=1.0, p=2.0, eta=0.5, lambda_clip=0.02, alpha_soft=0.5, alpha_cross=0.35,
             temp=1.0, eps=1e-8, nms_radius=2)
 
