@@ -375,8 +375,8 @@ enum {
   SFI_STAGE_ATTN = 0,     /* split attention kernel (dense; gather or compact in a fast step) */
   SFI_STAGE_MERGE = 1,    /* split merge */
   SFI_STAGE_SCORE = 2,    /* evidence and ranking keys, with the segments' histograms where J is long (mode 1: both
-                             kernels together); none where one workgroup per pair scores or reads a window's evidence;
-                             counted, with nothing in it, where the dense launch scores (sfi_set_dense_scores) */
+                             kernels together); none where one workgroup per pair scores or reads a window's evidence, or where
+                             the dense launch scores (sfi_set_dense_scores; mode 1: the second kernel alone) */
   SFI_STAGE_CAND = 3,     /* long J only: threshold-bin candidates (very long J: and the histograms' sums by groups) */
   SFI_STAGE_COUNT = 4,    /* not used: always 0 */
   SFI_STAGE_WRITE = 5,    /* ordered index write; short J: the whole selection, with the scoring and the output's merge

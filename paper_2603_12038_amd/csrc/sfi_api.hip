@@ -517,10 +517,9 @@ int run_selector(sfi_ctx* x, const SelArgs& sa, int max_len, hipStream_t st, boo
   int src = 0;  // what the selecting workgroup reads: keys that a scoring launch leaves, or (nothing is launched before it) ...
   if (!full && windowed && pick) src = 2;                                                             // ... the window's evidence
   else if (!full && !windowed && sa.part != nullptr && pick && sel_pick_scores(nJ, x->G, B * x->cfg.n_kv_heads, x->n_cu)) src = 1;  // ... the logits
-  if (src == 0) {
+  if (src == 0 && (sa.met == nullptr || full)) {  // (else the dense launch has scored)
     StageTimer t(x, st, SFI_STAGE_SCORE);
-    if (sa.met != nullptr && !full) {}  // the dense launch has scored: nothing between the stage's events
-    else if (full) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
+    if (full) SFI_TRY(launch_sel_full(sa, B, nJ, !pick, st));
     else if (windowed) SFI_TRY(launch_sel_finalize(sa, B, nJ, st));
     else SFI_TRY(launch_sel_score(sa, B, nJ, !pick, st));
     if (!t.stop()) return SFI_ELAUNCH;

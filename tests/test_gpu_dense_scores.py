@@ -1,6 +1,7 @@
 """Scoring in the dense launch (sfi_set_dense_scores) against the scoring launch: the same keys, so the same bits in every output.
 One sequence, planned launches with equal and with ragged lengths, more logits than a workgroup's LDS holds, several sequences in
-one workgroup, and waits that go to the end, that end at once (every record scored by the Selector) or after a tick (some of them)."""
+one workgroup, and waits that go to the end, that end at once (every record left to the last workgroup of its pair) or after a tick
+(some of them).  Ragged steps have the scoring launch whatever the knob says."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -112,6 +113,38 @@ def test_full_selector(B, Hkv, G, lens, page, alpha):
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,lens", [(1, 10, 2, [19000]), (2, 8, 8, [20000, 17003])])
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_against_the_oracle(oracle, B, Hq, Hkv, lens, full, out_bf16):
+    """Both Selectors with every kind of wait against the fp64 oracle, and the outputs, which the candidates' launch merges, in both types."""
+    import numpy as np
+    import sfi_synth as syn
+    from helpers import Runner, check_out, check_out_bf16, check_selection
+    from paper_2603_12038_amd.binding import STAGE_NAMES
+    from oracle.sfi_oracle import SelectorParams
+    w = syn.make_tiny(L0=max(lens), steps=2, budget=160, recent=48, n_support=64, B=B, Hq=Hq, Hkv=Hkv)
+    w.L0 = np.array(lens, np.int32)
+    sp = SelectorParams(mode=1) if full else SelectorParams()
+    r = Runner(w, selector={k: getattr(sp, k) for k in FULL} if full else None, alpha=sp.alpha, out_bf16=out_bf16)
+    try:
+        for t in range(2):
+            q, ctx = w.q(t), w.ctx_len(t)
+            ref = oracle.dense(q, w.K, w.V, ctx)
+            sel_ref, nsel_ref, z = oracle.selector(q, w.K, ctx, w.budget, w.n_sink, w.recent, sp=sp)
+            for mode in (4, 3, 2, 12):
+                print(f"[gpu-dense-scores] oracle: full={full} bf16={out_bf16} query {t} mode {mode}", flush=True)
+                r.sfi.sfi_set_dense_scores(r.ctx.handle, mode)
+                r.sfi.sfi_set_profiling(r.ctx.handle, 1)
+                out, sel, nsel = r.slow(q, ctx, w.budget)
+                stages = dict(zip(STAGE_NAMES, r.sfi.sfi_stage_times(r.ctx.handle)[1]))
+                assert (stages["attn"], stages["score"], stages["cand"], stages["write"]) == (1, int(full), 1, 1)
+                (check_out_bf16 if out_bf16 else check_out)(out, ref)
+                check_selection(sel, nsel, sel_ref, nsel_ref, z, ctx, w.n_sink, w.recent, w.budget)
+    finally:
+        r.close()
 
 
 def test_graph_replays():
