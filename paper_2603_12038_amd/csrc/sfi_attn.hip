@@ -1080,12 +1080,13 @@ __device__ __forceinline__ void dense_body(const AttnArgs& a, const DenseShare& 
 // counter behind acknowledged headers, in front of their loads, was 0.7 us longer, in the L2 of one XCD no shorter.)
 // All workgroups of the launch are on the chip together where it has the chip to itself (score_in_dense); where it has
 // not, some may only start when others have ended, so the wait has a limit.  Behind it a workgroup writes its logits and leaves its
-// record to the pair's others: it marks it in the pair's mask, counts itself out and ends.  A workgroup that has scored its own record, and on
-// counting itself out finds that some were left, claims them from the mask one by one; the last of the pair to be counted out finds
-// the statistics complete and works off all that nobody has claimed, its own among them if it was left.  So every record is
+// record to the pair's others: it marks it in the pair's mask and counts itself out.  The others count themselves out when all they have is scored: who then
+// finds that records of the pair were left claims them from the mask one by one, and the pair's last one, who
+// finds the statistics complete whatever the others saw, takes all that nobody has claimed.  So every record is
 // scored once, in this launch, and the next one does not see which way it went.  (With every record left, which the last workgroups of the pairs
-// then work off alone, us a slow step of 4 x 32768 rows 103 -> 127, of 1 x 131071 with the full Selector 122 -> 293; left to the Selector's launches, of which each workgroup
-// scored all of them again, 140 and 880.)
+// then work off alone, us a slow step of 4 x 32768 rows 103 -> 125, of 1 x 131071 with the full Selector 117 -> 288; left to the Selector's launches, of which each workgroup
+// scored all of them again, 140 and 880.)  Counting at the end of each sequence instead, with the answer looked at behind its keys, made the way to the next
+// one wait for them: 8 x 20011..24571 rows, G = 5, paged 135.3 -> 133.7 us for the present form.
 // Nothing of this is decided before all of the workgroup's own shares are done and out, so no workgroup waits for one that waits.
 // The keys are bit for bit what the scoring launch (sel_score_kernel) makes of the same logits.
 // FULL: evidence, prior and their sums for the full Selector, as sel_prior_kernel leaves them (the sums per workgroup, not per segment).
@@ -1112,15 +1113,31 @@ __device__ __forceinline__ uint64_t claim_left(unsigned long long* mask, bool ev
   }
   return 0;
 }
+// An entry of the workgroup's list, in scalar registers.
+struct ScoredEntry {
+  int h, b, first, step, end, NJ, n_rec, slot;
+};
+__device__ __forceinline__ ScoredEntry scored_entry(const Scored& sc, int e) {
+  const int4 e0 = sc.entry[2 * e], e1 = sc.entry[2 * e + 1];
+  return ScoredEntry{__builtin_amdgcn_readfirstlane(e0.x), __builtin_amdgcn_readfirstlane(e0.y), __builtin_amdgcn_readfirstlane(e0.z),
+                     __builtin_amdgcn_readfirstlane(e0.w), __builtin_amdgcn_readfirstlane(e1.x), __builtin_amdgcn_readfirstlane(e1.y),
+                     __builtin_amdgcn_readfirstlane(e1.z), __builtin_amdgcn_readfirstlane(e1.w)};
+}
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
 template <bool FULL>
 __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, float* lds) {
   __shared__ __align__(16) uint32_t s_hist[FULL ? 2 * kAttnThreads : kHistBins];
   __shared__ double s_sums[kWaves][kSegStats];
   __shared__ float s_M[16], s_c[16];
-  __shared__ uint32_t s_met[kWaves], s_go;
-  __shared__ uint64_t s_claim;
+  __shared__ uint32_t s_met[kWaves];
+  __shared__ uint8_t s_out[kScoreCap];  // of an entry: OUT_...
+  __shared__ uint64_t s_mask[2];
   __shared__ int4 s_tiles[kSlotCap];  // of the records claimed
+  enum { OUT_SCORED = 0, OUT_LEFT = 1, OUT_LAST = 2 };  // scored and not counted out yet; left; left, and the pair's last one
   static_assert(kHistBins == 2 * kAttnThreads, "two bins, or one word of a segment's histogram, per thread");
+  static_assert(kScoreCap <= 64 && kSlotCap <= 64, "an entry, a record per lane");
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.G, rows = G + (FULL ? 1 : 0), tile_f = rows * kTile, stay = score_stay(G, rows);
   const float* const stash = lds + kWaves * G * kHeadDim + w * score_stash_floats(G);
@@ -1128,182 +1145,182 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
   __syncthreads();  // (the list is there)
   const uint64_t t0 = wall_clock64();  // the limit is for all sequences together
   const uint64_t limit = (uint64_t)abs(a.met_ticks);
+  auto tiles_of_wave = [&](int first, int step, int end) { return first < end ? (end - first + step - 1) / step : 0; };
+  // The statistics of a pair's heads, to s_M and s_c: wave w takes heads w, w + 4, ..., a record per lane.  WAIT: until they are there or the limit is over
+  // (false: they are not); else they are known to be.
+  auto statistics = [&](const ScoredEntry& E, int bh, auto WAIT) -> bool {
+    bool all = true;
+    for (int g = w; g < 16; g += kWaves) {
+      float M = -kNeg, c = 0.f;  // (heads past the group count for nothing)
+      if (g < G) {
+        const uint64_t* const met = a.met + ((int64_t)bh * G + g) * kSlotCap + min(lane, E.n_rec - 1);
+        uint64_t v = 0;
+        if (WAIT) {
+          all = false;
+          while (limit > 0) {
+            v = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            all = __all(v != 0 && a.met_ticks > 0);
+            if (all || wall_clock64() - t0 >= limit) break;
+            __builtin_amdgcn_s_sleep(2);
+          }
+          if (!all) break;
+        } else {
+          v = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const float2 ml = lane < E.n_rec ? make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32) & 0x7fffffffu)) : make_float2(kNeg, 0.f);
+        c = group_stat(ml, a.alpha, G, M);
+      }
+      if (lane == 0) {
+        s_M[g] = M;
+        s_c[g] = c;
+      }
+    }
+    return all;
+  };
+  double sums[kSegStats];
+  // (FULL: this wave's sums, of one record, in front of the barrier behind which they are stored)
+  auto put_sums = [&]() {
+    if (!FULL) return;
+#pragma unroll
+    for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < kSegStats; ++i) s_sums[w][i] = sums[i];
+    }
+  };
   int used = 0;  // tiles of this wave in front of the sequence's
   for (int e = 0; e < sc.n; ++e) {
-    const int4 e0 = sc.entry[2 * e], e1 = sc.entry[2 * e + 1];
-    const int h = __builtin_amdgcn_readfirstlane(e0.x), b = __builtin_amdgcn_readfirstlane(e0.y);
-    const int first0 = __builtin_amdgcn_readfirstlane(e0.z), step0 = __builtin_amdgcn_readfirstlane(e0.w);
-    const int nTJ0 = __builtin_amdgcn_readfirstlane(e1.x), NJ = __builtin_amdgcn_readfirstlane(e1.y);
-    const int n_rec = __builtin_amdgcn_readfirstlane(e1.z), slot0 = __builtin_amdgcn_readfirstlane(e1.w);
-    auto tiles_of_wave = [&](int first, int step, int end) { return first < end ? (end - first + step - 1) / step : 0; };
-    const int KJ = tiles_of_wave(first0 + w, step0, nTJ0), in_lds = max(0, min(KJ, stay - used));
-    const int bh = b * a.Hkv + h;
+    const ScoredEntry E = scored_entry(sc, e);
+    const int first = E.first + w, KJ = tiles_of_wave(first, E.step, E.end), in_lds = max(0, min(KJ, stay - used));
+    const int bh = E.b * a.Hkv + E.h;
     const float* const kept = stash + used * tile_f;
     float* const lg = a.logits + (int64_t)bh * tile_f / kTile * a.ld_pos;
-    uint64_t* const left_tiles = reinterpret_cast<uint64_t*>(a.met_tiles + (int64_t)bh * kSlotCap);
     used += KJ;
     if (in_lds < KJ) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's other logits are written
     if (FULL)  // (the next launch adds to the segments' histograms)
-      for (int sg = slot0; sg * kSelSeg < NJ; sg += n_rec) a.hist[((int64_t)bh * a.n_seg_cap + sg) * (kHistBins / 2) + tid] = 0u;
-    bool own = true, last = false;  // the workgroup's record has not been left; it is the pair's last one to be counted out (both workgroup-uniform)
-    for (;;) {
-      // wave w: the statistics of heads w, w + 4, ..., a record per lane
-      bool all = true;
-      for (int g = w; g < 16; g += kWaves) {
-        float M = -kNeg, c = 0.f;  // (heads past the group count for nothing)
-        if (g < G) {
-          const uint64_t* const met = a.met + ((int64_t)bh * G + g) * kSlotCap + min(lane, n_rec - 1);
-          uint64_t v = 0;
-          all = false;
-          while (limit > 0 || !own) {
-            v = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            all = __all(v != 0 && (a.met_ticks > 0 || !own));
-            if (all || !own || wall_clock64() - t0 >= limit) break;
-            __builtin_amdgcn_s_sleep(2);
-          }
-          if (!all && own) break;
-          const float2 ml = lane < n_rec ? make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32) & 0x7fffffffu)) : make_float2(kNeg, 0.f);
-          c = group_stat(ml, a.alpha, G, M);
-        }
-        if (lane == 0) {
-          s_M[g] = M;
-          s_c[g] = c;
-        }
-      }
-      if (lane == 0) s_met[w] = all;
-      __syncthreads();
-      if (!own || (s_met[0] & s_met[1] & s_met[2] & s_met[3]) != 0u) break;
-      // The record is left.  (Logits beyond LDS are in memory already, but perhaps only in this XCD's L2.)
-      for (int f = lane; f < KJ * (tile_f / 4); f += 64) {
+      for (int sg = E.slot; sg * kSelSeg < E.NJ; sg += E.n_rec) a.hist[((int64_t)bh * a.n_seg_cap + sg) * (kHistBins / 2) + tid] = 0u;
+    const bool all = statistics(E, bh, std::true_type{});
+    if (lane == 0) s_met[w] = all;
+    __syncthreads();
+    if ((s_met[0] & s_met[1] & s_met[2] & s_met[3]) == 0u) {  // workgroup-uniform: the record is left
+      for (int f = lane; f < KJ * (tile_f / 4); f += 64) {  // (logits beyond LDS are in memory already, but perhaps only in this XCD's L2)
         const int i = f / (tile_f / 4), rem = f - i * (tile_f / 4);
-        float* const dst = lg + (int64_t)(first0 + w + i * step0) * tile_f + rem * 4;
+        float* const dst = lg + (int64_t)(first + i * E.step) * tile_f + rem * 4;
         if (i < in_lds) store_far4(dst, *reinterpret_cast<const float4*>(kept + f * 4));
         else store_far4(dst, *reinterpret_cast<const float4*>(dst));
       }
       if (tid == 0) {
-        __hip_atomic_store(left_tiles + 2 * slot0, (uint64_t)(uint32_t)step0 << 32 | (uint32_t)first0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(left_tiles + 2 * slot0 + 1, (uint64_t)(uint32_t)nTJ0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t* const tiles = reinterpret_cast<uint64_t*>(a.met_tiles + (int64_t)bh * kSlotCap + E.slot);
+        __hip_atomic_store(tiles, (uint64_t)(uint32_t)E.step << 32 | (uint32_t)E.first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(tiles + 1, (uint64_t)(uint32_t)E.end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's statistics, logits and tiles have been performed
       __syncthreads();
       if (tid == 0) {
-        const uint64_t was_left = __hip_atomic_fetch_or(a.met_left + bh, 1ull << slot0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::"v"((uint32_t)was_left) : "memory");  // (in the mask before it is counted)
+        const uint64_t was = __hip_atomic_fetch_or(a.met_left + bh, 1ull << E.slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::"v"((uint32_t)was) : "memory");  // (in the mask before it is counted)
         const uint64_t out = __hip_atomic_fetch_add(a.met_out + bh, 1ull << 32 | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_go = (uint32_t)out == (uint32_t)(n_rec - 1);
+        s_out[e] = (uint32_t)out == (uint32_t)(E.n_rec - 1) ? OUT_LAST : OUT_LEFT;
       }
-      __syncthreads();
-      own = false;
-      last = s_go != 0u;
-      if (!last) break;
+      continue;  // (s_met is written again by the other waves only when they have seen the barrier above)
     }
-    if (!own && !last) continue;
-    uint64_t out = 0;  // looked at when the record is scored
-    if (own && tid == 0) out = __hip_atomic_fetch_add(a.met_out + bh, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) s_out[e] = OUT_SCORED;
     const int64_t row = (int64_t)bh * a.ld_pos;
-    const Prior prior(a.prior_args, NJ);
-    int first = first0, step = step0, end = nTJ0, slot = slot0;
-    uint64_t claimed = 0;
-    for (;;) {
-      if (!own) {
+    const Prior prior(a.prior_args, E.NJ);
+#pragma unroll
+    for (int i = 0; i < kSegStats; ++i) sums[i] = 0.0;
+    auto score = [&](int p, const float* src) {
+      float f[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int g = 0; g < G; ++g) add_evidence(f, *reinterpret_cast<const float4*>(src + g * kTile), a.alpha, s_M[g], s_c[g]);
+      rank_quad<FULL>(a, row, E.NJ, prior, sums, s_hist, p, f, FULL ? *reinterpret_cast<const float4*>(src + G * kTile) : make_float4(0.f, 0.f, 0.f, 0.f));
+    };
+    for (int k0 = 0; k0 < KJ; k0 += 8) {  // eight tiles at a time, a quad of positions per lane
+      const int k = k0 + (lane >> 3), t = first + k * E.step, p = t * kTile + (lane & 7) * 4;
+      if (p >= E.NJ) continue;
+      if (k < in_lds) score(p, kept + k * tile_f + (lane & 7) * 4);
+      else if (k < KJ) score(p, lg + (int64_t)t * tile_f + (lane & 7) * 4);
+    }
+    put_sums();
+    __syncthreads();
+    store_record_stats<FULL>(a, (int64_t)bh * kSlotCap + E.slot, s_hist, s_sums);  // (the next record is scored behind a barrier)
+  }
+  // Out: an entry per lane.
+  __syncthreads();
+  if (w == 0) {
+    uint64_t help = 0, last = 0;
+    if (lane < sc.n) {
+      const int4 e0 = sc.entry[2 * lane], e1 = sc.entry[2 * lane + 1];
+      const int how = s_out[lane];
+      uint64_t out = 0;
+      if (how == OUT_SCORED) out = __hip_atomic_fetch_add(a.met_out + (e0.y * a.Hkv + e0.x), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = how == OUT_LAST || (how == OUT_SCORED && (uint32_t)out == (uint32_t)(e1.z - 1));
+      help = how == OUT_LAST || out >> 32 != 0;
+    }
+    help = __ballot(help != 0);
+    last = __ballot(last != 0);
+    if (lane == 0) {
+      s_mask[0] = help;
+      s_mask[1] = last;
+    }
+  }
+  __syncthreads();
+  const uint64_t last = uniform64(s_mask[1]);
+  for (uint64_t help = uniform64(s_mask[0]); help != 0; help &= help - 1) {
+    const int e = __builtin_ctzll(help);
+    const ScoredEntry E = scored_entry(sc, e);
+    const int bh = E.b * a.Hkv + E.h;
+    const float* const lg = a.logits + (int64_t)bh * tile_f / kTile * a.ld_pos;
+    const int64_t row = (int64_t)bh * a.ld_pos;
+    const Prior prior(a.prior_args, E.NJ);
+    statistics(E, bh, std::false_type{});
+    for (uint64_t claimed = 0;;) {
+      __syncthreads();  // (statistics, histogram and sums of the record before)
+      if (claimed == 0) {
+        if (w == 0) {
+          uint64_t m = 0;
+          if (lane == 0) m = claim_left(a.met_left + bh, (last >> e & 1u) != 0);
+          m = uniform64(m);
+          if (m >> lane & 1u) {
+            const uint64_t* const tiles = reinterpret_cast<const uint64_t*>(a.met_tiles + (int64_t)bh * kSlotCap + lane);
+            const uint64_t x = __hip_atomic_load(tiles, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), y = __hip_atomic_load(tiles + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_tiles[lane] = make_int4((int)(uint32_t)x, (int)(x >> 32), (int)(uint32_t)y, 0);
+          }
+          if (lane == 0) s_mask[0] = m;
+        }
         __syncthreads();
-        if (claimed == 0) {
-          if (w == 0) {
-            uint64_t m = 0;
-            if (lane == 0) m = claim_left(a.met_left + bh, last);
-            m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
-            if (m >> lane & 1u) {
-              const uint64_t t0 = __hip_atomic_load(left_tiles + 2 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              const uint64_t t1 = __hip_atomic_load(left_tiles + 2 * lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              s_tiles[lane] = make_int4((int)(uint32_t)t0, (int)(t0 >> 32), (int)(uint32_t)t1, 0);
-            }
-            if (lane == 0) s_claim = m;
-          }
-          __syncthreads();
-          claimed = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s_claim >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)s_claim);
-          if (claimed == 0) break;
-        }
-        slot = __builtin_ctzll(claimed);
-        claimed &= claimed - 1;
-        const int4 rec = s_tiles[slot];
-        first = __builtin_amdgcn_readfirstlane(rec.x), step = __builtin_amdgcn_readfirstlane(rec.y), end = __builtin_amdgcn_readfirstlane(rec.z);
+        claimed = uniform64(s_mask[0]);
+        if (claimed == 0) break;
       }
-      double sums[kSegStats] = {0.0, 0.0, 0.0, 0.0, 0.0};
-      auto rank = [&](int p, float (&f)[4], const float4& k4) {
-        if (p >= NJ) return;
-        if (FULL) {
-          const float rr[4] = {prior(k4.x, p), prior(k4.y, p + 1), prior(k4.z, p + 2), prior(k4.w, p + 3)};
-          evidence_of_mu(f, a.alpha, a.inv_alpha, p, NJ);
-          add_sums(sums, f, rr);
-          *reinterpret_cast<float4*>(a.fbuf + row + p) = make_float4(f[0], f[1], f[2], f[3]);
-          *reinterpret_cast<float4*>(a.prior + row + p) = make_float4(rr[0], rr[1], rr[2], rr[3]);
-          return;
-        }
-        const uint32_t key[4] = {__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
-        *reinterpret_cast<uint4*>(a.keys + row + p) = make_uint4(key[0], key[1], key[2], key[3]);
+      const int slot = __builtin_ctzll(claimed);
+      claimed &= claimed - 1;
+      const int4 tiles = s_tiles[slot];
+      const int first = __builtin_amdgcn_readfirstlane(tiles.x) + w, step = __builtin_amdgcn_readfirstlane(tiles.y), K = tiles_of_wave(first, step, __builtin_amdgcn_readfirstlane(tiles.z));
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (p + i < NJ) atomicAdd(&s_hist[bin_of(key[i])], 1u);
-      };
-      auto score = [&](int p, const float* src) {
-        float f[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < kSegStats; ++i) sums[i] = 0.0;
+      for (int k0 = 0; k0 < K; k0 += 32) {  // the same lanes in the same order, four trips' requests at once
+        float f[4][4] = {};
+        const float* src[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) src[i] = lg + (int64_t)(first + min(k0 + 8 * i + (lane >> 3), K - 1) * step) * tile_f + (lane & 7) * 4;
 #pragma unroll 4
-        for (int g = 0; g < G; ++g) add_evidence(f, *reinterpret_cast<const float4*>(src + g * kTile), a.alpha, s_M[g], s_c[g]);
-        rank(p, f, FULL ? *reinterpret_cast<const float4*>(src + G * kTile) : make_float4(0.f, 0.f, 0.f, 0.f));
-      };
-      // eight tiles at a time, a quad of positions per lane
-      if (own) {
-        for (int k0 = 0; k0 < KJ; k0 += 8) {
-          const int k = k0 + (lane >> 3), t = first0 + w + k * step0, p = t * kTile + (lane & 7) * 4;
-          if (p >= NJ) continue;
-          if (k < in_lds) score(p, kept + k * tile_f + (lane & 7) * 4);
-          else if (k < KJ) score(p, lg + (int64_t)t * tile_f + (lane & 7) * 4);
+        for (int g = 0; g < G; ++g) {
+          float4 l[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) l[i] = load_far4(src[i] + g * kTile);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) add_evidence(f[i], l[i], a.alpha, s_M[g], s_c[g]);
         }
-      } else {  // the same lanes in the same order, four trips' requests at once
-        const int K = tiles_of_wave(first + w, step, end);
-        for (int k0 = 0; k0 < K; k0 += 32) {
-          float f[4][4] = {};
-          const float* src[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) src[i] = lg + (int64_t)(first + w + min(k0 + 8 * i + (lane >> 3), K - 1) * step) * tile_f + (lane & 7) * 4;
-#pragma unroll 4
-          for (int g = 0; g < G; ++g) {
-            float4 l[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) l[i] = load_far4(src[i] + g * kTile);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) add_evidence(f[i], l[i], a.alpha, s_M[g], s_c[g]);
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int k = k0 + 8 * i + (lane >> 3);
-            const float4 k4 = FULL ? load_far4(src[i] + G * kTile) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (k < K) rank((first + w + k * step) * kTile + (lane & 7) * 4, f[i], k4);
-          }
+        for (int i = 0; i < 4; ++i) {
+          const int k = k0 + 8 * i + (lane >> 3);
+          const float4 k2 = FULL ? load_far4(src[i] + G * kTile) : make_float4(0.f, 0.f, 0.f, 0.f);
+          if (k < K) rank_quad<FULL>(a, row, E.NJ, prior, sums, s_hist, (first + k * step) * kTile + (lane & 7) * 4, f[i], k2);
         }
       }
-      if (FULL) {
-#pragma unroll
-        for (int i = 0; i < kSegStats; ++i) sums[i] = wave_sum_d(sums[i]);
-        if (lane == 0) {
-#pragma unroll
-          for (int i = 0; i < kSegStats; ++i) s_sums[w][i] = sums[i];
-        }
-      }
-      if (own && tid == 0) s_go = out >> 32 == 0 ? 0u : (uint32_t)out == (uint32_t)(n_rec - 1) ? 2u : 1u;
+      put_sums();
       __syncthreads();
-      if (FULL) {
-        if (tid < kSegStats)
-          a.wg_stat[((int64_t)bh * kSlotCap + slot) * kSegStats + tid] = (s_sums[0][tid] + s_sums[1][tid]) + (s_sums[2][tid] + s_sums[3][tid]);
-      } else {
-        reinterpret_cast<uint2*>(a.wg_hist + ((int64_t)bh * kSlotCap + slot) * kHistBins)[tid] = reinterpret_cast<const uint2*>(s_hist)[tid];
-        reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);  // for the next record, in front of its barrier
-      }
-      if (own) {
-        if (s_go == 0u) break;
-        last = s_go == 2u;
-      }
-      own = false;
+      store_record_stats<FULL>(a, (int64_t)bh * kSlotCap + slot, s_hist, s_sums);
     }
   }
 }

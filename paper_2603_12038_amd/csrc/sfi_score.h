@@ -65,4 +65,37 @@ __device__ __forceinline__ void evidence_of_mu(float (&f)[4], float alpha, float
   }
 }
 
+// A quad of positions from p on, with evidence f (of mu) and squared key norms k2: keys and histogram, or (FULL) evidence and prior, added to
+// the sums for lambda*.  Args: the attention launches' or the Selector's; row: the pair's first position in their arrays.
+template <bool FULL, typename Args>
+__device__ __forceinline__ void rank_quad(const Args& a, int64_t row, int nJ, const Prior& prior, double (&sums)[kSegStats], uint32_t* s_hist, int p,
+                                          float (&f)[4], const float4& k2) {
+  if (p >= nJ) return;
+  if (FULL) {
+    const float rr[4] = {prior(k2.x, p), prior(k2.y, p + 1), prior(k2.z, p + 2), prior(k2.w, p + 3)};
+    evidence_of_mu(f, a.alpha, a.inv_alpha, p, nJ);
+    add_sums(sums, f, rr);
+    *reinterpret_cast<float4*>(a.fbuf + row + p) = make_float4(f[0], f[1], f[2], f[3]);
+    *reinterpret_cast<float4*>(a.prior + row + p) = make_float4(rr[0], rr[1], rr[2], rr[3]);
+    return;
+  }
+  const uint32_t key[4] = {__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+  *reinterpret_cast<uint4*>(a.keys + row + p) = make_uint4(key[0], key[1], key[2], key[3]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (p + i < nJ) atomicAdd(&s_hist[bin_of(key[i])], 1u);
+}
+// What a workgroup of four waves leaves of a record (slot, of its pair's kSlotCap at at): its histogram, which is put back to zero, or the sums, of every wave in
+// s_sums.  Behind a barrier that follows the last rank_quad.
+template <bool FULL, typename Args>
+__device__ __forceinline__ void store_record_stats(const Args& a, int64_t at, uint32_t* s_hist, double (*s_sums)[kSegStats]) {
+  const int tid = threadIdx.x;
+  if (FULL) {
+    if (tid < kSegStats) a.wg_stat[at * kSegStats + tid] = (s_sums[0][tid] + s_sums[1][tid]) + (s_sums[2][tid] + s_sums[3][tid]);
+  } else {
+    reinterpret_cast<uint2*>(a.wg_hist + at * kHistBins)[tid] = reinterpret_cast<const uint2*>(s_hist)[tid];
+    reinterpret_cast<uint2*>(s_hist)[tid] = make_uint2(0u, 0u);
+  }
+}
+
 }  // namespace sfi
