@@ -279,18 +279,17 @@ bool merges_in_kernel(const sfi_ctx* x, int n_split, int max_len) {
 // Whether a slow step's dense launch also scores (score_tail), so that the Selector's scoring launch falls away: where three Selector
 // launches would follow, and all of the launch's workgroups are on the chip together (one per unit: their LDS).  a: planned
 // or, for one sequence, not.
-// - A pair has at most eight records on average.  Where the launch has to share the chip, some of its workgroups start when others are done: those wait for nothing,
-//   and what they leave has to be made up for, the more of it the more records a pair has.  (The ragged step's launch never scores: how many of its
-//   sequences are slow, and with it the records of a pair, the host does not know.  Two of 32: up to 32 records.)
-// - A wave has at least five tiles, else the scoring launch costs no more than the wait.
+// - A pair has few records on average.  Where the launch has to share the chip, some of its workgroups start when others are done: those wait for nothing,
+//   and what they leave falls to the pair's last ones, the more of it the more records a pair has, and with the full Selector each takes longer.  (The ragged step's
+//   launch never scores: how many of its sequences are slow, and with it the records of a pair, the host does not know.  Two of 32: up to 32 records.)
 // - Logits that LDS does not hold go to memory and come back to the few waves of a unit; up to four times what it holds that
 //   is still the faster way.
-// Scoring launch / in the dense launch, us a slow step, 8 KV heads and G = 4 where not given: 4 x 32768 rows 98.4 / 94.4; 8 x 20011..24571, G = 5, paged 141.3 / 132.5;
-// 16 x 20000..60000 511.0 / 504.5; full Selector, 4 x 32768 115.3 / 110.7, 8 x 20000..30000, G = 5, paged 187.6 / 177.9 (a J of more than 262144 positions
-// keeps the launch there).  Two contexts at once: 4 x 32768 192 / 178.
-// Beyond the lines: 32 records, 1 x 131072 102.8 / 99.3, full Selector 116.2 / 112.0, two contexts at once 214 / 400 to 600; ragged, 32 x 16384..65536, G = 8, two slow 126.6 / 118.0,
-// four contexts at once 488 / 583; 43 records, 3 x 17000..60000, G = 5, 2 KV heads 42.1 / 43.1; 4 tiles, 1 x 17000 28.6 / 28.7; more than four times LDS: 16 x 20000..60000, G = 8
-// 573.2 / 578.6, 16 x 20000..30000, G = 16 407.8 / 410.7.
+// Scoring launch / in the dense launch, us a slow step, 8 KV heads and G = 4 where not given (records of a pair): 4 x 32768 rows (8) 98.4 / 94.4; 8 x 20011..24571, G = 5, paged (4) 141.9 / 133.1;
+// 4 x 17000 (8) 59.9 / 58.1; 16 x 20000..60000 (2) 510.2 / 505.1; 8 x 20000..24000, G = 2 (4) 130.2 / 128.4; 5 x 30000..50000, G = 7, 4 KV heads (13) 91.0 / 84.4; 3 x 40000 (11) 94.2 / 90.5; full Selector,
+// 4 x 32768 (8) 115.1 / 109.8, 8 x 20000..30000, G = 5, paged (4) 187.5 / 173.3.  Contexts at once, a stream each, us a round: two of 4 x 32768 194 / 179, three 305 / 271; three of the 8 x 20011..24571 430 / 385;
+// three of 5 x 30000..50000 274 / 244; three of 4 x 32768 with the full Selector 330 / 302.  Beside a kernel that holds 8 units all the time: 126 / 123, 194 / 193 to 202, 116 / 111 to 117 (13 records), full 162 / 169.
+// Beyond the lines: 2 x 65536 (16) 97.8 / 94.6, two contexts 189 / 199, beside the kernel 150 / 154; with the full Selector 3 x 20000..60000, paged (11) 122 / 117 and 164 / 166 to 192; 1 x 131072 (32) 98.6 / 97.1,
+// two contexts 189 / 235; 3 x 17000..60000, G = 5, 2 KV heads (43) 42.1 / 43.3; more than four times LDS: 16 x 20000..60000, G = 8 574.8 / 578.1, 16 x 20000..30000, G = 16 408.2 / 411.3.
 bool score_in_dense(const sfi_ctx* x, const AttnArgs& a, int max_len) {
   const int nJ = max_len - x->cfg.recent - x->cfg.n_sink, B = x->cfg.batch, Hkv = x->cfg.n_kv_heads;
   if (x->dense_scores == 0 || x->ws.met_tiles == nullptr || nJ <= kPickMax || x->dense_wide || (a.plan_batch == 0 && B > 1)) return false;
@@ -298,7 +297,7 @@ bool score_in_dense(const sfi_ctx* x, const AttnArgs& a, int max_len) {
   if (wgs * Hkv > x->n_cu || (x->cfg.selector_mode == 1 && nJ > kHistGroupFrom * kSelSeg)) return false;
   if (x->dense_scores > 1) return true;
   const int64_t tiles = (int64_t)((max_len + kTile - 1) / kTile) * B * Hkv, waves = (int64_t)kWaves * x->n_cu;
-  return wgs <= kScoreRecords * B && tiles >= 5 * waves && tiles <= 4 * score_stay(x->G, x->G + x->cfg.selector_mode) * waves;
+  return wgs <= (x->cfg.selector_mode == 1 ? kScoreRecordsFull : kScoreRecords) * B && tiles <= 4 * score_stay(x->G, x->G + x->cfg.selector_mode) * waves;
 }
 PriorArgs prior_args_of(const sfi_ctx* x) {
   const sfi_config& c = x->cfg;

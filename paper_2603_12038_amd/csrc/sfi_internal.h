@@ -31,7 +31,8 @@ constexpr int kFuseSpan = 512;      // ... and positions (of every KV head) it t
 constexpr int kHistBins = 512;     // bins of a segment's coarse key histogram (long J)
 constexpr int kScoreCap = 64;       // batch up to which the dense launch scores (a workgroup can meet that many sequences)
 constexpr int kScorePairs = 256;    // batch times KV heads up to which it does: a workgroup per unit and pair at least
-constexpr int kScoreRecords = 8;    // workgroups per sequence and KV head up to which it does
+constexpr int kScoreRecords = 13;   // workgroups per sequence and KV head up to which it does ...
+constexpr int kScoreRecordsFull = 8;  // ... with the full Selector
 constexpr int kScoreFloats = 38400;  // LDS of a dense workgroup that scores: the waves' outputs for the combine, then their logits
 constexpr int kScoreBurst = 4;       // tiles written together where a wave's part does not hold them all
 __host__ __device__ constexpr int score_stash_floats(int G) { return kScoreFloats / kWaves - G * kHeadDim; }  // of a wave
