@@ -1326,7 +1326,7 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
 }
 // One workgroup per (KV head, split, sequence) cell: wave w of split s takes tiles 4 s + w, 4 (s + n_split) + w, ...
 // The head is the grid's first index here and in the planned launch, for the Selector's sake (Place in sfi_select.hip); by itself the order is worth
-// little (16 x 16384 rows, dense alone, splits first 158.1 us, heads first 156.9).
+// nothing that could be told from noise (16 x 16384 rows, dense alone, splits first 157.9 us, heads first 157.2).
 template <int EXPOSE, bool PAGED, bool BIG = false, bool WIDE = false>
 __global__ __launch_bounds__(kAttnThreads, BIG ? 1 : 2) void attn_dense_kernel(const AttnArgs a) {
   const DenseShare sh{(int)blockIdx.y * kWaves, a.n_split * kWaves, 0, (int)blockIdx.y, a.n_split, 0, 0, 0, false};

@@ -17,7 +17,7 @@
 //   one workgroup per pair does it all (sel_pick_kernel): from the logits where they are few, else from the keys that a
 //   scoring launch of many workgroups has left;
 //   long J: scoring with a coarse histogram per segment (stage 1; the dense launch may have done it, with a histogram
-//   per workgroup: score_tail), the keys of the threshold bin collected in a run per segment (stage 2), the exact refinement
+//   per workgroup: score_tail), the keys of the threshold bin collected (stage 2), the exact refinement
 //   among those few keys and the compaction (stage 3), a workgroup per segment each.  The segments' histograms are added up by their readers: device-scope atomics on one cache line are
 //   performed word by word, about 30 ns each, and a common histogram per pair cost a slow step 8 us (32768 positions) to
 //   25 us (131072 positions, full Selector).
@@ -92,9 +92,10 @@ __device__ __forceinline__ void find_kth_desc_lds(const uint32_t* hist, int nbin
 //
 // The grids' first index is the KV head (place 0, segments in the second): with eight heads, or a multiple, consecutive workgroups go
 // round the eight XCDs, so all workgroups of a head, here and in the dense launch, sit behind one L2, and what
-// a launch leaves for the next one -- logits, keys, histograms, candidates -- is read from there and not through the last-level cache.  A slow
-// step, us, segments first / heads first, both launches (one of them alone is worth a quarter of it): 4 x 32768 rows, G = 4 101.9 / 98.5; 8 x 20011..24571, G = 5, paged
-// 146.4 / 141.0; ragged, 12 x 5003..30011, one slow, compact 50.9 / 49.3; 32 x 16384..65536, G = 8, two slow 125.8 / 124.5; the window of 2 x 12000..16384 rows 273 / 270.
+// a launch leaves for the next one -- logits, keys, histograms, candidates -- is read from there and not through the last-level cache.
+// us a layer, segments first / heads first, both launches (one of them alone is worth a quarter of it): 1 x 131072 rows 102.2 / 98.6; 2 x 65536 101.2 / 97.8; 1 x 17000 29.9 / 28.8; ragged, 4 x 17000,
+// one slow 37.5 / 35.2; 2 x 20000..30000, 4 KV heads 35.9 / 35.3; a query of a window over 60000 rows 26.9 / 26.3.  Where the dense work is long it is worth little: ragged, 32 x 16384..65536, two
+// slow 125.9 / 125.4, 16 x 20000..60000, half slow 267.6 / 266.6, full Selector, 1 x 131071 116.9 / 116.2; with two KV heads nothing: 3 x 17000..60000 42.1 / 42.1.
 // Where the second index would not do (n_place beyond kMaxPlaceY) the two change places.
 struct Place {
   int head, i;  // i: segment (or what a launch has for one)
