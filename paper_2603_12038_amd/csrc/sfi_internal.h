@@ -140,6 +140,21 @@ struct AttnArgs {
                                  //   caller's workspace)
   int32_t cached_rows;           // evidence mode: 0 = all rows the launch may read fit the caches; else how many rows per head do
   float* logits;                 // dense mode, nullptr: do not expose logits
+  uint64_t* met;                 // dense mode, nullptr or: the launch scores (score_tail); Workspace::met
+  unsigned long long* met_left;  //   ... Workspace::met_left
+  unsigned long long* met_out;   //   ... Workspace::met_out
+  int4* met_tiles;               //   ... Workspace::met_tiles
+  uint32_t* wg_hist;             //   ... Workspace::wg_hist
+  uint32_t* keys;                //   ... Workspace::keys
+  double* wg_stat;               //   ... full Selector: Workspace::wg_stat, fbuf, prior, hist, n_seg_cap, and the prior's parameters
+  float* fbuf;
+  float* prior;
+  uint32_t* hist;
+  int32_t n_seg_cap;
+  float inv_alpha;
+  PriorArgs prior_args;
+  float alpha;                   //   ... power-mean exponent of the evidence
+  int32_t met_ticks;             //   ... longest wait, in ticks of 10 ns; negative (tests): as long, and nothing is taken as arrived
   int32_t with_knorm;            // dense mode: also expose the squared key norms (full Selector)
   int32_t dense_wide;            // dense mode: K rows read as whole 128-byte lines (query groups of at most 8 heads, flat cache)
   int32_t big_stash;             // dense mode with logits: the variant with the 32 KB stash per wave (one workgroup per CU)
@@ -166,22 +181,6 @@ struct AttnArgs {
   int32_t len_cap;               // ctx_len[b] is clamped to [0, len_cap]: the launch's max_len, else cfg.max_ctx
   int32_t n_blocks;              // paged cache: block ids are clamped to [0, n_blocks)
   int32_t* guard;                // Workspace::guard
-  // (Behind what every launch reads: in the middle of it these lines cost a slow step of 4096 rows 0.06 us.)
-  uint64_t* met;                 // dense mode, nullptr or: the launch scores (score_tail); Workspace::met
-  unsigned long long* met_left;  //   ... Workspace::met_left
-  unsigned long long* met_out;   //   ... Workspace::met_out
-  int4* met_tiles;               //   ... Workspace::met_tiles
-  uint32_t* wg_hist;             //   ... Workspace::wg_hist
-  uint32_t* keys;                //   ... Workspace::keys
-  double* wg_stat;               //   ... full Selector: Workspace::wg_stat, fbuf, prior, hist, n_seg_cap, and the prior's parameters
-  float* fbuf;
-  float* prior;
-  uint32_t* hist;
-  int32_t n_seg_cap;
-  float inv_alpha;
-  PriorArgs prior_args;
-  float alpha;                   //   ... power-mean exponent of the evidence
-  int32_t met_ticks;             //   ... longest wait, in ticks of 10 ns; negative (tests): as long, and nothing is taken as arrived
 };
 
 // Reorg: gather the sink and the selected rows of every (b, h) into the compact buffers.
