@@ -113,8 +113,7 @@ size_t carve(const sfi_config* c, char* base, Workspace* ws) {
   ws->arrive = (uint32_t*)take((size_t)(B * Hkv) * kWaves * kArriveStride * sizeof(uint32_t));
   const bool scores = B <= kScoreCap && B * Hkv <= kScorePairs && c->max_ctx - c->recent - c->n_sink > kPickMax;  // its dense launch can (score_in_dense)
   ws->met = (uint64_t*)take(scores ? (size_t)(B * Hq) * kSlotCap * sizeof(uint64_t) : 0);
-  ws->met_left = (unsigned long long*)take(scores ? (size_t)(B * Hkv) * sizeof(unsigned long long) : 0);
-  ws->met_out = (unsigned long long*)take(scores ? (size_t)(B * Hkv) * sizeof(unsigned long long) : 0);
+  ws->met_out = (unsigned long long*)take(scores ? (size_t)(B * Hkv) * 2 * sizeof(unsigned long long) : 0);
   ws->guard = (int32_t*)take(sizeof(int32_t));  // directly behind the counters: one memset clears them all
   ws->met_tiles = scores ? (int4*)take((size_t)(B * Hkv) * kSlotCap * sizeof(int4)) : nullptr;
   ws->wg_hist = scores && !full ? (uint32_t*)take((size_t)(B * Hkv) * kSlotCap * kHistBins * sizeof(uint32_t)) : nullptr;
@@ -317,7 +316,6 @@ int set_dense_scores(sfi_ctx* x, AttnArgs* a, hipStream_t st) {
   }
   x->met_dirty = 1;
   a->met = x->ws.met;
-  a->met_left = x->ws.met_left;
   a->met_out = x->ws.met_out;
   a->met_tiles = x->ws.met_tiles;
   a->wg_hist = x->ws.wg_hist;

@@ -1217,9 +1217,9 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's statistics, logits and tiles have been performed
       __syncthreads();
       if (tid == 0) {
-        const uint64_t was = __hip_atomic_fetch_or(a.met_left + bh, 1ull << E.slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t was = __hip_atomic_fetch_or(a.met_out + 2 * bh, 1ull << E.slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::"v"((uint32_t)was) : "memory");  // (in the mask before it is counted)
-        const uint64_t out = __hip_atomic_fetch_add(a.met_out + bh, 1ull << 32 | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t out = __hip_atomic_fetch_add(a.met_out + 2 * bh + 1, 1ull << 32 | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_out[e] = (uint32_t)out == (uint32_t)(E.n_rec - 1) ? OUT_LAST : OUT_LEFT;
       }
       continue;  // (s_met is written again by the other waves only when they have seen the barrier above)
@@ -1253,7 +1253,7 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
       const int4 e0 = sc.entry[2 * lane], e1 = sc.entry[2 * lane + 1];
       const int how = s_out[lane];
       uint64_t out = 0;
-      if (how == OUT_SCORED) out = __hip_atomic_fetch_add(a.met_out + (e0.y * a.Hkv + e0.x), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (how == OUT_SCORED) out = __hip_atomic_fetch_add(a.met_out + 2 * (e0.y * a.Hkv + e0.x) + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last = how == OUT_LAST || (how == OUT_SCORED && (uint32_t)out == (uint32_t)(e1.z - 1));
       help = how == OUT_LAST || out >> 32 != 0;
     }
@@ -1279,7 +1279,7 @@ __device__ __forceinline__ void score_tail(const AttnArgs& a, const Scored& sc, 
       if (claimed == 0) {
         if (w == 0) {
           uint64_t m = 0;
-          if (lane == 0) m = claim_left(a.met_left + bh, (last >> e & 1u) != 0);
+          if (lane == 0) m = claim_left(a.met_out + 2 * bh, (last >> e & 1u) != 0);
           m = uniform64(m);
           if (m >> lane & 1u) {
             const uint64_t* const tiles = reinterpret_cast<const uint64_t*>(a.met_tiles + (int64_t)bh * kSlotCap + lane);

@@ -100,8 +100,8 @@ struct Workspace {
   float* mu;          // [B*Hkv][ld]  windowed evidence: accumulator over the window's queries
   uint32_t* arrive;   // [B*Hkv][kWaves][kArriveStride]  workgroups of a split fast-step launch whose wave w has written its heads' records
   uint64_t* met;      // [B*Hq][kSlotCap]  scoring in the dense launch: each workgroup's statistics over J (zero between steps)
-  unsigned long long* met_left;  // [B*Hkv]  ... mask of the records that their workgroup has left to the pair's others (zero between steps)
-  unsigned long long* met_out;   // [B*Hkv]  ... workgroups counted out, and how many of them have left their record << 32 (zero between steps)
+  unsigned long long* met_out;   // [B*Hkv][2]  ... mask of the records that their workgroup has left to the pair's others; workgroups counted out, and how
+                                 //   many of them have left their record << 32 (zero between steps)
   int4* met_tiles;    // [B*Hkv][kSlotCap]  ... { first, step, end, - } of the tiles of the records in the mask
   uint32_t* wg_hist;  // [B*Hkv][kSlotCap][kHistBins]  ... mode 0: key histogram of each workgroup
   double* wg_stat;    // [B*Hkv][kSlotCap][kSegStats]  ... full Selector: each workgroup's sums for lambda*
@@ -141,7 +141,6 @@ struct AttnArgs {
   int32_t cached_rows;           // evidence mode: 0 = all rows the launch may read fit the caches; else how many rows per head do
   float* logits;                 // dense mode, nullptr: do not expose logits
   uint64_t* met;                 // dense mode, nullptr or: the launch scores (score_tail); Workspace::met
-  unsigned long long* met_left;  //   ... Workspace::met_left
   unsigned long long* met_out;   //   ... Workspace::met_out
   int4* met_tiles;               //   ... Workspace::met_tiles
   uint32_t* wg_hist;             //   ... Workspace::wg_hist

@@ -903,7 +903,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_write_kernel(const SelArgs a)
     for (int i = (int)ksel + seg * kSelThreads + tid; i < a.budget; i += n_seg * kSelThreads) out[i] = -1;
     if (seg == 0 && tid == 0) {
       a.n_sel[bh] = (int32_t)ksel;
-      if (a.met != nullptr) a.met_out[bh] = 0;
+      if (a.met != nullptr) a.met_out[2 * bh + 1] = 0;  // (the mask is empty)
     }
     if (seg == 0 && a.met != nullptr) {  // for the next dense launch
       for (int i = tid; i < a.G * (kSlotCap / 2); i += kSelThreads) reinterpret_cast<uint4*>(a.met + bh * a.G * kSlotCap)[i] = make_uint4(0u, 0u, 0u, 0u);
