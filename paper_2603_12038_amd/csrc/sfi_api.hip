@@ -27,7 +27,8 @@ struct sfi_ctx {
   int dense_scores;         // the slow step's dense launch scores: 0 no, 1 where that is faster (default), others for tests (sfi_set_dense_scores)
   int last_dense_splits, last_fast_splits;
   int last_dense_scored;    // the last dense launch of a slow step has scored
-  int met_dirty;            // a step that scored there ended with an error: its statistics may still be in ws.met
+  int met_dirty;            // 1: a step that scored there ended with an error: its statistics may still be in ws.met; 2: and the step
+                            //   that clears them is being captured, not run
   int last_dense_planned;   // the last dense launch planned itself: its records per sequence are in ws.seq_rec
   // profiling: a ring of event pairs, one set of stages per hot call, read back in one go so that
   // no host synchronisation sits between the profiled calls
@@ -306,15 +307,23 @@ __global__ void clear_words_kernel(uint32_t* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
 }
-// The launch takes any word of ws.met that is not zero for this step's, and only the Selector's last launch puts them back to zero: behind a
-// step that did not come so far they are cleared first (scores_done).
+// The launch takes any word of ws.met that is not zero for this step's, and only the Selector's last launch puts them back to zero.  Behind a
+// step that did not come so far they are cleared as it ends (scores_done), for a graph that was captured before may come next, or if that cannot be launched
+// either in front of the next step.
+int clear_met(sfi_ctx* x, hipStream_t st) {
+  const int n = (int)(((char*)x->ws.guard - (char*)x->ws.met) / sizeof(uint32_t));
+  hipLaunchKernelGGL(clear_words_kernel, dim3((n + 255) / 256), dim3(256), 0, st, (uint32_t*)x->ws.met, n);
+  return hipGetLastError() == hipSuccess ? SFI_OK : SFI_ELAUNCH;
+}
 int set_dense_scores(sfi_ctx* x, AttnArgs* a, hipStream_t st) {
-  if (x->met_dirty) {
-    const int n = (int)(((char*)x->ws.guard - (char*)x->ws.met) / sizeof(uint32_t));
-    hipLaunchKernelGGL(clear_words_kernel, dim3((n + 255) / 256), dim3(256), 0, st, (uint32_t*)x->ws.met, n);
-    if (hipGetLastError() != hipSuccess) return SFI_ELAUNCH;
-  }
+  const bool dirty = x->met_dirty != 0;
   x->met_dirty = 1;
+  if (dirty) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture != hipStreamCaptureStatusNone) x->met_dirty = 2;
+    if (clear_met(x, st) != SFI_OK) return SFI_ELAUNCH;
+  }
   a->met = x->ws.met;
   a->met_out = x->ws.met_out;
   a->met_tiles = x->ws.met_tiles;
@@ -331,9 +340,13 @@ int set_dense_scores(sfi_ctx* x, AttnArgs* a, hipStream_t st) {
   a->met_ticks = x->dense_scores == 2 ? 0 : x->dense_scores == 3 ? 1 : x->dense_scores == 12 ? -kScoreWaitTicks : kScoreWaitTicks;
   return SFI_OK;
 }
-// rc: of the Selector behind such a launch.
-int scores_done(sfi_ctx* x, int rc) {
-  if (rc == SFI_OK) x->met_dirty = 0;
+// The end of a step with such a launch; rc: how it went.
+int scores_done(sfi_ctx* x, int rc, hipStream_t st) {
+  if (rc != SFI_OK) {
+    (void)hipGetLastError();
+    if (clear_met(x, st) != SFI_OK) return rc;
+  }
+  if (x->met_dirty == 1) x->met_dirty = 0;
   return rc;
 }
 
@@ -765,7 +778,7 @@ int sfi_slow_step(sfi_ctx* x, const void* q, const void* K, const void* V, const
   hipStream_t st = (hipStream_t)stream;
   CallRecord call_record(x);
   // no merge launch: the merge rides in the Selector's first launch (one launch less on the step's critical path)
-  if ((rc = slow_attn_impl(x, q, K, V, ctx_len, ml, out, st, true, nullptr, true)) != SFI_OK) return rc;
+  if ((rc = slow_attn_impl(x, q, K, V, ctx_len, ml, out, st, true, nullptr, true)) != SFI_OK) return x->last_dense_scored ? scores_done(x, rc, st) : rc;
   SelArgs sa;
   fill_sel(x, &sa, ctx_len, ml, nullptr, budget, x->last_dense_splits, sel_idx, n_sel);
   sa.part = x->ws.part;
@@ -773,7 +786,7 @@ int sfi_slow_step(sfi_ctx* x, const void* q, const void* K, const void* V, const
   if (x->last_dense_scored) { sa.met = x->ws.met; sa.met_out = x->ws.met_out; }
   if (x->last_dense_planned) sa.seq_rec = x->ws.seq_rec;
   rc = run_selector(x, sa, ml, st);
-  return x->last_dense_scored ? scores_done(x, rc) : rc;
+  return x->last_dense_scored ? scores_done(x, rc, st) : rc;
 }
 
 int sfi_slow_attn(sfi_ctx* x, const void* q, const void* K, const void* V, const int32_t* ctx_len,

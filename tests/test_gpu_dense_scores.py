@@ -226,8 +226,8 @@ def test_the_wait_has_one_limit_for_all_of_a_workgroups_sequences():
 
 
 def test_step_behind_one_that_ended_with_an_error():
-    """A call that returns an error behind the dense launch leaves that launch's statistics in the workspace: the next step must not
-    take them for its own.  The error: one the HIP runtime still has from a call of the caller's (a device that does not exist), which
+    """A call that returns an error behind the dense launch leaves that launch's statistics in the workspace: the next step, called or
+    replayed from a graph, must not take them for its own.  The error: one the HIP runtime still has from a call of the caller's (a device that does not exist), which
     the library finds when it looks behind its first launch."""
     import torch
     sfi, ctx, K, V, table, q, c = _setup(2, 8, 4, [40000, 33001], 0, 1.0)
@@ -248,15 +248,23 @@ def test_step_behind_one_that_ended_with_an_error():
             torch.cuda.synchronize()
             want.append([x.clone() for x in (out, sel, nsel)])
         sfi.sfi_set_dense_scores(h, 4)
-        for t in (0, 1, 1, 0):
-            assert lib.hipSetDevice(10000) != 0
-            with pytest.raises(SfiError):
+        graphs = []
+        for t in range(2):
+            graphs.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(graphs[t], stream=torch.cuda.Stream()):
                 step(t)
-            torch.cuda.synchronize()
-            for u in (1 - t, t):
-                step(u)
+        replay = lambda t: graphs[t].replay()
+        for t in (0, 1):
+            for runs in ((step, step), (replay, step), (step, replay), (replay, replay)):
+                assert lib.hipSetDevice(10000) != 0
+                with pytest.raises(SfiError):
+                    step(t)
                 torch.cuda.synchronize()
-                assert all(torch.equal(a, b) for a, b in zip((out, sel, nsel), want[u])), (t, u)
+                for u, run in zip((1 - t, t), runs):
+                    sel.fill_(-7)
+                    run(u)
+                    torch.cuda.synchronize()
+                    assert all(torch.equal(a, b) for a, b in zip((out, sel, nsel), want[u])), (t, u)
     finally:
         torch.cuda.synchronize()
         ctx.close()
