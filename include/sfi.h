@@ -431,7 +431,7 @@ int sfi_set_handover(sfi_ctx* ctx, int32_t mode);
  * mode = 1 (default): where that is faster (up to 13 workgroups per pair, 8 with selector_mode 1) the dense launch also scores, each workgroup
  * what it has read, once it has the others' statistics of its sequences.  It waits 64 us for them at most, for all its sequences together, and what
  * is missing then, in a launch that has to share the GPU, falls to the last workgroups: several contexts that step at once are still faster so, a
- * step beside kernels that hold compute units all the time can be up to 6 % slower.  mode = 0, the setting for that: a scoring launch, as behind
+ * step beside kernels that hold compute units all the time can be up to 7 % slower.  mode = 0, the setting for that: a scoring launch, as behind
  * sfi_slow_attn.  mode = 2, 3, 4 (for tests): scored in the dense launch wherever it can be, with no wait at all, a wait of one tick, and the whole
  * wait; mode = 12 (for tests): the whole wait, and nothing is taken as arrived.  Same results.  Other values: SFI_EINVAL. */
 int sfi_set_dense_scores(sfi_ctx* ctx, int32_t mode);
